@@ -79,7 +79,21 @@ struct FlashLds {
 constexpr int TM = FlashLds<2>::kRows;  // rows of a routed tile
 
 #define SL_LDS_PTR(p) ((__attribute__((address_space(3))) void*)(p))
-#define SL_GLOBAL_PTR(p) ((const __attribute__((address_space(1))) void*)(p))
+
+// Direct global->LDS loads go through buffer instructions: base is wave-uniform, `bytes` bounds the
+// offsets (a lane past it stores zeros).  The flat form (global_load_lds) counts as an LDS operation
+// too, and the compiler then waits for every LDS read with lgkmcnt(0): the fragment reads that run four
+// MFMAs ahead were drained at every fourth MFMA.  With the buffer form those waits are lgkmcnt(3).
+// Measured: attention of a 256K prompt 27.09 -> 26.86 ms, the paper's geometry at 48K 4.75 -> 4.56 ms (its
+// masked kernel no longer spills); the long kernel is held to 1.93 GHz by its power, so stalls cost it little.
+typedef __amdgpu_buffer_rsrc_t BufferRsrc;
+__device__ __forceinline__ BufferRsrc buffer_of(const void* base, uint32_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, bytes, 0x00020000);
+}
+__device__ __forceinline__ int64_t uniform64(int64_t v) {
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+  return (int64_t)(((uint64_t)hi << 32) | lo);
+}
 
 __device__ __forceinline__ float pair_max(float x) {
   // lanes l and l^32 hold the two halves of a query column
@@ -469,6 +483,7 @@ __device__ __forceinline__ void flash_tile(const FlashArgs& a, char* lds, const 
                                            TileDesc& next, bool has_next, RequestNext&& request_next,
                                            DescribeNext&& describe_next, FlashCarry& c) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int uwave = __builtin_amdgcn_readfirstlane(wave);
   const int grp = wave >> 2, w4 = wave & 3;  // grp 0 = early, 1 = late
   const int qc = lane & 31, hf = lane >> 5;
   const int srow = w4 * 32 + qc;             // row inside the group's 128-row half tile
@@ -492,22 +507,20 @@ __device__ __forceinline__ void flash_tile(const FlashArgs& a, char* lds, const 
   }
   // wavefront w fills blocks w*BPW .. w*BPW + BPW-1 of both tiles
   auto stage = [&](int kvh, int64_t t0, int kb, int vb) {
-    const char* kbase = reinterpret_cast<const char*>(a.K + (int64_t)kvh * a.kvsh + t0 * a.kvst);
-    const char* vbase = reinterpret_cast<const char*>(a.Vt + (int64_t)kvh * HD * a.Lp + t0);
-#pragma unroll
-    for (int i = 0; i < BPW; ++i) {
-      uint32_t off = koff[i];
-      if (LOCAL || CLIP) {  // rows past the end of the sequence re-read the last row (masked later)
-        const int row = (wave * BPW + i) * 4 + (lane >> 4);
-        if (t0 + row >= a.L) off -= (uint32_t)((t0 + row - (a.L - 1)) * a.kvst * sizeof(bf16_t));
-      }
-      __builtin_amdgcn_global_load_lds(SL_GLOBAL_PTR(kbase + off),
-                                       SL_LDS_PTR(ldsK + kb * kStageElems + (wave * BPW + i) * 512), 16, 0, 0);
-    }
+    // K rows past the end of the sequence lie beyond the buffer: zeros in LDS (masked later)
+    const int rows = __builtin_amdgcn_readfirstlane(a.L - t0 < TN ? (int)(a.L - t0) : TN);
+    const BufferRsrc kr = buffer_of(a.K + uniform64((int64_t)kvh * a.kvsh + t0 * a.kvst),
+                                    (uint32_t)(((rows - 1) * a.kvst + HD) * sizeof(bf16_t)));
+    const BufferRsrc vr = buffer_of(a.Vt + uniform64((int64_t)kvh * HD * a.Lp + t0),
+                                    (uint32_t)(((HD - 1) * a.Lp + TN) * sizeof(bf16_t)));
 #pragma unroll
     for (int i = 0; i < BPW; ++i)
-      __builtin_amdgcn_global_load_lds(SL_GLOBAL_PTR(vbase + voff[i]),
-                                       SL_LDS_PTR(ldsV + vb * kStageElems + (wave * BPW + i) * 512), 16, 0, 0);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(kr, SL_LDS_PTR(ldsK + kb * kStageElems + (uwave * BPW + i) * 512), 16,
+                                               koff[i], 0, 0, 0);
+#pragma unroll
+    for (int i = 0; i < BPW; ++i)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(vr, SL_LDS_PTR(ldsV + vb * kStageElems + (uwave * BPW + i) * 512), 16,
+                                               voff[i], 0, 0, 0);
   };
   // Q row of a lane's column, as the B operand of S^T = K Q^T
   auto load_q = [&](int64_t q_off) {
@@ -850,7 +863,7 @@ __global__ __launch_bounds__(FlashLds<2>::kThreads, 1) void span_flash_routed_ke
   // The record and the items of a workgroup's next tile are requested during the current tile's
   // first kv step as direct global->LDS loads into the wavefront's own 512 bytes (the items of tile t sit
   // at t*TM, so the two do not depend on each other) and read back at its tail.
-  int* const ahead = reinterpret_cast<int*>(lds + FlashLds<2>::kAhead) + wave * 128;
+  int* const ahead = reinterpret_cast<int*>(lds + FlashLds<2>::kAhead) + __builtin_amdgcn_readfirstlane(wave) * 128;
   const int4 info0 = a.tile_info[t_begin];
   TileDesc cur = describe(info0, a.items[t_begin * TM + qrow]);
   for (int64_t t = t_begin; t < t_end; t += NWL) {
@@ -859,10 +872,11 @@ __global__ __launch_bounds__(FlashLds<2>::kThreads, 1) void span_flash_routed_ke
     flash_tile<2, false, false, CLIP>(
         a, lds, cur, nxt, has_next,
         [&] {
-          const int* rec = reinterpret_cast<const int*>(a.tile_info + (t + NWL)) + (lane & 3);
-          const int* itm = a.items + (t + NWL) * TM + wave * 32 + (lane & 31);
-          __builtin_amdgcn_global_load_lds(SL_GLOBAL_PTR(rec), SL_LDS_PTR(ahead), 4, 0, 0);
-          __builtin_amdgcn_global_load_lds(SL_GLOBAL_PTR(itm), SL_LDS_PTR(ahead + 64), 4, 0, 0);
+          const int uw = __builtin_amdgcn_readfirstlane(wave);
+          __builtin_amdgcn_raw_ptr_buffer_load_lds(buffer_of(a.tile_info + (t + NWL), 16), SL_LDS_PTR(ahead), 4,
+                                                   (lane & 3) * 4, 0, 0, 0);
+          __builtin_amdgcn_raw_ptr_buffer_load_lds(buffer_of(a.items + (t + NWL) * TM + uw * 32, 128),
+                                                   SL_LDS_PTR(ahead + 64), 4, (lane & 31) * 4, 0, 0, 0);
         },
         [&] {
           const int4 ninfo = make_int4(ahead[0], ahead[1], ahead[2], 0);
@@ -935,7 +949,7 @@ __global__ __launch_bounds__(FlashLds<2>::kThreads, 1) void span_flash_anchor_ke
   carry.kb = carry.vb = 0;
   carry.primed = false;
   carry.pending = false;
-  int* const ahead = reinterpret_cast<int*>(lds + FlashLds<2>::kAhead) + wave * 128;
+  int* const ahead = reinterpret_cast<int*>(lds + FlashLds<2>::kAhead) + __builtin_amdgcn_readfirstlane(wave) * 128;
   const int4 info0 = a.tile_info[t_begin];
   TileDesc cur = describe(info0, a.items[t_begin * TM + qrow]);
   for (int64_t t = t_begin; t < t_end; t += NWL) {
@@ -944,10 +958,11 @@ __global__ __launch_bounds__(FlashLds<2>::kThreads, 1) void span_flash_anchor_ke
     flash_tile<2, false, false, true>(
         a, lds, cur, nxt, has_next,
         [&] {
-          const int* rec = reinterpret_cast<const int*>(a.tile_info + (t + NWL)) + (lane & 3);
-          const int* itm = a.items + (t + NWL) * TM + wave * 32 + (lane & 31);
-          __builtin_amdgcn_global_load_lds(SL_GLOBAL_PTR(rec), SL_LDS_PTR(ahead), 4, 0, 0);
-          __builtin_amdgcn_global_load_lds(SL_GLOBAL_PTR(itm), SL_LDS_PTR(ahead + 64), 4, 0, 0);
+          const int uw = __builtin_amdgcn_readfirstlane(wave);
+          __builtin_amdgcn_raw_ptr_buffer_load_lds(buffer_of(a.tile_info + (t + NWL), 16), SL_LDS_PTR(ahead), 4,
+                                                   (lane & 3) * 4, 0, 0, 0);
+          __builtin_amdgcn_raw_ptr_buffer_load_lds(buffer_of(a.items + (t + NWL) * TM + uw * 32, 128),
+                                                   SL_LDS_PTR(ahead + 64), 4, (lane & 31) * 4, 0, 0, 0);
         },
         [&] {
           const int4 ninfo = make_int4(ahead[0], ahead[1], ahead[2], 0);
