@@ -5,7 +5,7 @@
 // blocks they touch; on the fixed span grid a bucket is simply (kv head, span)), the routed part
 // makes the SPAN stationary:
 //
-//   bucket_count / bucket_scan / bucket_tiles / bucket_fill   invert idx into per-(kv, span)
+//   bucket (count) / unit_scan / scan / tiles / bucket (fill)   invert idx into per-(kv, span)
 //                                   lists of query rows (integer work, LDS histograms)
 //   span_flash_routed               persistent workgroups walk the (bucket, 256-row tile) list:
 //                                   gathered Q rows against the span's K/V tiles staged through
@@ -41,7 +41,6 @@ typedef float f32x8 __attribute__((ext_vector_type(8)));
 constexpr int TG = 128;            // rows of one wavefront group (4 wavefronts x 32 columns)
 constexpr int TN = 64;             // kv positions per staged tile
 constexpr int HD = 128;            // head dimension of this path
-constexpr int kBucketRows = 4096;  // query rows of one head per bucketing workgroup
 
 // LDS of the flash kernels (dynamic).  Main loop: stages of the V^T tile and of the K tile, filled
 // by direct global->LDS loads (16 bytes per lane, a wavefront instruction fills 1 KB
@@ -156,72 +155,159 @@ __global__ __launch_bounds__(256) void transpose_v_kernel(const bf16_t* __restri
 }
 
 // ------------------------------------------------------------------ bucketing
-// Inverts idx into per-(kv head, span) lists of (row, slot) items without a sort and without
-// global atomics, so that the item order is the same on every run: within a bucket the items come
-// by query head of the group, then by query row.
-//   bucket_kernel<false>      grid (chunks of kBucketRows rows, Hq): LDS histogram of the block's
-//                             items per span -> blk_cnt[h][chunk][span]
-//   bucket_block_scan_kernel  per (kv head, span): exclusive scan of blk_cnt over (head of the
-//                             group, chunk), in place; the total goes to g_count
+// Inverts idx into per-(kv head, bucket) lists of (row, slot) items without a sort and without
+// global atomics.  The rows of a head are cut into units of `rows` (64 .. 1024) consecutive rows, one
+// wavefront each, with a histogram of its own in LDS:
+//   bucket_kernel<false>      counts the unit's items per bucket -> cnt[kv][order of the unit][bucket]
+//   bucket_unit_scan_kernel   per (kv head, bucket): exclusive scan of cnt over the units, in place; the
+//                             total goes to g_count
 //   bucket_scan_kernel / bucket_tiles_kernel   bucket offsets and tile records
-//   bucket_kernel<true>       recounts per wavefront (each owns a contiguous quarter of the block's
-//                             rows), turns the counts into bases behind the block's prefix and
-//                             scatters the items
-template <bool FILL>
-__global__ __launch_bounds__(256) void bucket_kernel(const int32_t* __restrict__ idx,
-                                                     int* __restrict__ blk_cnt,
-                                                     const int* __restrict__ g_cursor,
-                                                     int* __restrict__ items, int64_t Lq,
-                                                     int64_t q_pos0, int G, int S, int topk, int n) {
-  extern __shared__ int s_hist[];  // count pass: [n]; fill pass: [4][n], one histogram per wavefront
+//   bucket_kernel<true>       loads the unit's bases into its histogram and scatters the items
+// The unit order is the item order inside a bucket.  On the grid it is (head of the group, row); on the
+// paper's geometry (row, head of the group), so that the rows of a tile have nearly the same span length.
+//
+// Both passes are bound by the latency of idx (a row is read 16 bytes at a time, two rows per lane in
+// flight) and by LDS atomics that meet in one counter (hence the rotated slots), so units are made short
+// enough for four wavefronts on every SIMD.  4000 rows x 32 heads x 16
+// slots: 40 + 103 us with blocks of 4096 rows that counted twice, 8 + 17 us; 262144 rows x 8 slots
+// with planted needles: 226 + 456 us, 80 + 255 us.
+
+// Grid: an entry is a span, its bucket the span itself.
+struct GridItems {
+  static constexpr bool kRotate = true;
+  int S;  // anchor spacing
+  struct Row {
+    int c;  // candidates: spans [0, c)
+  };
+  __device__ __forceinline__ Row row(int64_t i) const {
+    return {i < ((int64_t)1 << 31) ? (int)((uint32_t)i / (uint32_t)S) : (int)(i / S)};
+  }
+  __device__ __forceinline__ int bucket(const Row& r, int j) const { return j >= 0 && j < r.c ? j : -1; }
+  __device__ __forceinline__ bool empty(const Row&, int) const { return false; }
+};
+
+// The paper's geometry: an entry is an anchor token (positions fit 32 bits); an item is a (row, slot)
+// whose anchor is valid and whose span minus the window is not empty; its bucket is the block of E tokens
+// that holds the span's last token.
+struct AnchorItems {
+  static constexpr bool kRotate = false;  // a bucket is worth computing once, and neighbours' anchors differ
+  int64_t window;
+  int ab, af, aroot, E;
+  struct Row {
+    int64_t i, ell;
+  };
+  __device__ __forceinline__ Row row(int64_t i) const { return {i, span_base_length(i, aroot)}; }
+  __device__ __forceinline__ int bucket(const Row& r, int t) const {
+    const AnchorSpan sp = anchor_span_of(r.i, t, r.ell, window, ab, af);
+    return sp.hi > sp.lo ? (int)((uint32_t)(sp.hi - 1) / (uint32_t)E) : -1;
+  }
+  __device__ __forceinline__ bool empty(const Row& r, int t) const { return t >= 0 && t <= r.i; }
+};
+
+// j[x] = j[(x + BY) % 8] where `on`.
+template <int BY>
+__device__ __forceinline__ void rotate8(int (&j)[8], bool on) {
+  int t[8];
+#pragma unroll
+  for (int x = 0; x < 8; ++x) t[x] = on ? j[(x + BY) & 7] : j[x];
+#pragma unroll
+  for (int x = 0; x < 8; ++x) j[x] = t[x];
+}
+
+struct BucketPlan {
+  int rows;    // rows per unit
+  int units;   // units per head
+  int unit_h, unit_u;  // place of unit u of head hl in its kv head's order: hl * unit_h + u * unit_u
+};
+
+// FILL: the marks of valid anchors with an empty span (lse = -inf in their partial) are written too.
+template <bool FILL, typename Items>
+__global__ __launch_bounds__(256) void bucket_kernel(const int32_t* __restrict__ idx, int* __restrict__ cnt,
+                                                     const int* __restrict__ g_cursor, int* __restrict__ items,
+                                                     float* __restrict__ part_lse, int64_t Lq, int64_t q_pos0,
+                                                     int G, int topk, int n, const BucketPlan plan, const Items it) {
+  extern __shared__ int s_hist[];  // [wavefronts of the block][n]
   const int h = blockIdx.y, kv = h / G, hl = h % G;
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int64_t r0 = (int64_t)blockIdx.x * kBucketRows + wave * (kBucketRows / 4);
-  int* const blk = blk_cnt + ((int64_t)h * gridDim.x + blockIdx.x) * n;
-  int* const hist = FILL ? s_hist + wave * n : s_hist;
-  for (int b = tid; b < (FILL ? 4 : 1) * n; b += 256) s_hist[b] = 0;
-  __syncthreads();
-  auto for_items = [&](auto f) {
-    for (int i = 0; i < kBucketRows / 256; ++i) {
-      const int64_t r = r0 + 64 * i + lane;
-      if (r < Lq) {
-        const int64_t c = (q_pos0 + r) / S;
-        const int32_t* row = idx + ((int64_t)h * Lq + r) * topk;
-        for (int s = 0; s < topk; ++s) {
-          const int j = row[s];
-          if (j >= 0 && j < c) f(j, r, s);
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int u = blockIdx.x * (blockDim.x >> 6) + wave;
+  if (u >= plan.units) return;  // (no barrier below: a unit is one wavefront's)
+  int* const hist = s_hist + wave * n;
+  int* const mine = cnt + ((int64_t)kv * G * plan.units + (int64_t)hl * plan.unit_h + (int64_t)u * plan.unit_u) * n;
+  for (int b = lane; b < n; b += 64) hist[b] = FILL ? g_cursor[kv * n + b] + mine[b] : 0;
+  __builtin_amdgcn_wave_barrier();  // (LDS operations of one wavefront complete in issue order)
+  const int64_t r0 = (int64_t)u * plan.rows;
+  const int64_t r1 = r0 + plan.rows < Lq ? r0 + plan.rows : Lq;
+  const bool quads = (topk & 3) == 0;
+  // two rows per lane at a time, eight slots of each
+  for (int64_t rb = r0 + lane; rb < r1; rb += 128) {
+    typename Items::Row rw[2];
+#pragma unroll
+    for (int e = 0; e < 2; ++e) rw[e] = it.row(q_pos0 + rb + 64 * e);
+    for (int s0 = 0; s0 < topk; s0 += 8) {
+      int j[2][8];
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        const int64_t r = rb + 64 * e;
+        const int32_t* row = idx + ((int64_t)h * Lq + r) * topk + s0;
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          int4 v = make_int4(-1, -1, -1, -1);
+          if (r < r1 && s0 + 4 * q < topk) {
+            if (quads) v = *reinterpret_cast<const int4*>(row + 4 * q);
+            else {
+              v.x = row[4 * q];
+              if (s0 + 4 * q + 1 < topk) v.y = row[4 * q + 1];
+              if (s0 + 4 * q + 2 < topk) v.z = row[4 * q + 2];
+              if (s0 + 4 * q + 3 < topk) v.w = row[4 * q + 3];
+            }
+          }
+          j[e][4 * q] = v.x;
+          j[e][4 * q + 1] = v.y;
+          j[e][4 * q + 2] = v.z;
+          j[e][4 * q + 3] = v.w;
+        }
+      }
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        const int64_t r = rb + 64 * e;
+        // neighbouring rows tend to list the same span in the same slot: lane l starts with slot l % 8
+        constexpr bool kRotate = Items::kRotate;
+        if (kRotate) {
+          rotate8<1>(j[e], lane & 1);
+          rotate8<2>(j[e], lane & 2);
+          rotate8<4>(j[e], lane & 4);
+        }
+        if (r >= r1) continue;
+#pragma unroll
+        for (int x = 0; x < 8; ++x) {
+          const int s = s0 + ((kRotate ? x + lane : x) & 7);
+          if (!kRotate && s >= topk) break;
+          const int b = s < topk ? it.bucket(rw[e], j[e][x]) : -1;
+          if (b >= 0) {
+            const int at = atomicAdd(&hist[b], 1);
+            if (FILL) items[at] = (int)(((hl * Lq + r) << 5) | s);
+          } else if (FILL && s < topk && it.empty(rw[e], j[e][x])) {
+            part_lse[((int64_t)h * Lq + r) * (topk + 1) + s] = -INFINITY;
+          }
         }
       }
     }
-  };
-  for_items([&](int j, int64_t, int) { atomicAdd(&hist[j], 1); });
-  __syncthreads();
+  }
   if (!FILL) {
-    for (int b = tid; b < n; b += 256) blk[b] = s_hist[b];
-    return;
+    __builtin_amdgcn_wave_barrier();
+    for (int b = lane; b < n; b += 64) mine[b] = hist[b];
   }
-  for (int b = tid; b < n; b += 256) {
-    int base = g_cursor[kv * n + b] + blk[b];
-#pragma unroll
-    for (int w = 0; w < 4; ++w) {
-      const int cnt = s_hist[w * n + b];
-      s_hist[w * n + b] = base;
-      base += cnt;
-    }
-  }
-  __syncthreads();
-  for_items([&](int j, int64_t r, int s) { items[atomicAdd(&hist[j], 1)] = (int)(((hl * Lq + r) << 5) | s); });
 }
 
-// grid (ceil(n / 32), Hkv), 256 threads = 32 spans x 8 segments of the E = G * chunks block counts
-// of a (kv head, span): exclusive scan in place, total to g_count.
-__global__ __launch_bounds__(256) void bucket_block_scan_kernel(int* __restrict__ blk_cnt,
-                                                                int* __restrict__ g_count, int E, int n) {
-  __shared__ int s_tot[8][32];
+// grid (ceil(n / 32), Hkv), 1024 threads = 32 buckets x 32 segments of the E units of a kv head:
+// exclusive scan in place, total to g_count.
+__global__ __launch_bounds__(1024) void bucket_unit_scan_kernel(int* __restrict__ cnt, int* __restrict__ g_count,
+                                                                int E, int n) {
+  __shared__ int s_tot[32][32];
   const int bl = threadIdx.x & 31, seg = threadIdx.x >> 5;
   const int b = blockIdx.x * 32 + bl, kv = blockIdx.y;
-  const int per = (E + 7) / 8, e0 = seg * per, e1 = min(E, e0 + per);
-  int* const col = blk_cnt + (int64_t)kv * E * n + b;
+  const int per = (E + 31) / 32, e0 = min(E, seg * per), e1 = min(E, e0 + per);
+  int* const col = cnt + (int64_t)kv * E * n + b;
   int sum = 0;
   if (b < n) {
     for (int e = e0; e < e1; e += 8) {
@@ -247,63 +333,7 @@ __global__ __launch_bounds__(256) void bucket_block_scan_kernel(int* __restrict_
       run += v[u];
     }
   }
-  if (seg == 7) g_count[kv * n + b] = run;
-}
-
-// The same two passes for the paper's geometry: an item is a (row, slot) whose anchor is valid and
-// whose span minus the window is not empty; its bucket is (kv head, block of E tokens that holds the
-// span's last token).  Blocks of one kv head are ordered by (chunk of rows, head of the group), so
-// that a bucket's items come by query position first: the rows of a tile then have nearly the
-// same span length.  The fill pass also marks the partial of a valid anchor with an empty span
-// as empty (lse = -inf) for the merge.
-template <bool FILL>
-__global__ __launch_bounds__(256) void bucket_anchor_kernel(const int32_t* __restrict__ anchors,
-                                                            int* __restrict__ blk_cnt,
-                                                            const int* __restrict__ g_cursor,
-                                                            int* __restrict__ items,
-                                                            float* __restrict__ part_lse, int64_t Lq,
-                                                            int64_t q_pos0, int G, int topk, int n,
-                                                            int64_t window, int ab, int af, int aroot, int E) {
-  extern __shared__ int s_hist[];  // count pass: [n]; fill pass: [4][n], one histogram per wavefront
-  const int h = blockIdx.y, kv = h / G, hl = h % G;
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int64_t r0 = (int64_t)blockIdx.x * kBucketRows + wave * (kBucketRows / 4);
-  int* const blk = blk_cnt + (((int64_t)kv * gridDim.x + blockIdx.x) * G + hl) * n;
-  int* const hist = FILL ? s_hist + wave * n : s_hist;
-  for (int b = tid; b < (FILL ? 4 : 1) * n; b += 256) s_hist[b] = 0;
-  __syncthreads();
-  auto for_items = [&](auto f) {
-    for (int it = 0; it < kBucketRows / 256; ++it) {
-      const int64_t r = r0 + 64 * it + lane;
-      if (r < Lq) {
-        const int64_t i = q_pos0 + r;
-        const int64_t ell = span_base_length(i, aroot);
-        const int32_t* row = anchors + ((int64_t)h * Lq + r) * topk;
-        for (int s = 0; s < topk; ++s) {
-          const AnchorSpan sp = anchor_span_of(i, row[s], ell, window, ab, af);
-          if (sp.hi > sp.lo) f((int)((sp.hi - 1) / E), r, s);
-          else if (FILL && sp.valid) part_lse[((int64_t)h * Lq + r) * (topk + 1) + s] = -INFINITY;
-        }
-      }
-    }
-  };
-  for_items([&](int j, int64_t, int) { atomicAdd(&hist[j], 1); });
-  __syncthreads();
-  if (!FILL) {
-    for (int b = tid; b < n; b += 256) blk[b] = s_hist[b];
-    return;
-  }
-  for (int b = tid; b < n; b += 256) {
-    int base = g_cursor[kv * n + b] + blk[b];
-#pragma unroll
-    for (int w = 0; w < 4; ++w) {
-      const int cnt = s_hist[w * n + b];
-      s_hist[w * n + b] = base;
-      base += cnt;
-    }
-  }
-  __syncthreads();
-  for_items([&](int j, int64_t r, int s) { items[atomicAdd(&hist[j], 1)] = (int)(((hl * Lq + r) << 5) | s); });
+  if (seg == 31) g_count[kv * n + b] = run;
 }
 
 // One workgroup: exclusive scans of the item counts and of the tile counts over the B buckets.
@@ -1195,8 +1225,8 @@ __global__ __launch_bounds__(256) void merge_combined_kernel(
 
 // ------------------------------------------------------------------ workspace carving
 struct MfmaWs {
-  size_t vt, counts, blk_cnt, item_off, tile_off, cursor, tile_info, items, part_lse, part_o, total;
-  int chunks;
+  size_t vt, counts, unit_cnt, item_off, tile_off, cursor, tile_info, items, part_lse, part_o, total;
+  BucketPlan plan;
   int64_t Lp;
   int B, max_tiles;
   int64_t max_items;
@@ -1239,6 +1269,19 @@ bool device_setup(DeviceSetup* out) {
   return true;
 }
 
+// Rows per bucketing unit: 64, doubled (to 1024) while that leaves 4096 units, four wavefronts on each
+// of 1024 SIMDs, or while the unit holds fewer items than it has counters to clear, write and scan.
+BucketPlan bucket_plan(const Problem& pb) {
+  BucketPlan p;
+  p.rows = 64;
+  while (p.rows < 1024 && ((pb.Lq + 2 * p.rows - 1) / (2 * p.rows) * pb.Hq >= 4096 || (int64_t)p.rows * pb.topk < pb.n))
+    p.rows <<= 1;
+  p.units = (int)((pb.Lq + p.rows - 1) / p.rows);
+  p.unit_h = p.units;
+  p.unit_u = 1;
+  return p;
+}
+
 MfmaWs carve(const Problem& pb) {
   MfmaWs w;
   w.Lp = (int64_t)align_up((size_t)pb.L, 64);
@@ -1253,8 +1296,8 @@ MfmaWs carve(const Problem& pb) {
   };
   w.vt = take((size_t)pb.Hkv * HD * w.Lp * sizeof(bf16_t));
   w.counts = take((size_t)w.B * sizeof(int));
-  w.chunks = (int)((pb.Lq + kBucketRows - 1) / kBucketRows);
-  w.blk_cnt = take((size_t)pb.Hq * w.chunks * pb.n * sizeof(int));
+  w.plan = bucket_plan(pb);
+  w.unit_cnt = take((size_t)pb.Hq * w.plan.units * pb.n * sizeof(int));
   w.item_off = take((size_t)(w.B + 1) * sizeof(int));
   w.tile_off = take((size_t)(w.B + 1) * sizeof(int));
   w.cursor = take((size_t)w.B * sizeof(int));
@@ -1265,6 +1308,26 @@ MfmaWs carve(const Problem& pb) {
   w.part_o = take(nparts * HD * sizeof(bf16_t));
   w.total = off;
   return w;
+}
+
+// The bucketing passes.  Blocks hold as many units as their histograms fit into 64 KB of LDS (n <= 4096).
+template <typename Items>
+bool launch_buckets(const Problem& pb, const MfmaWs& w, const int32_t* idx, int* unit_cnt, int* counts,
+                    int* item_off, int* tile_off, int* cursor, int4* tile_info, int* items, float* part_lse,
+                    const Items& it, hipStream_t st) {
+  const int n = (int)pb.n;
+  const int per_block = 4;  // 4 * 4096 counters = 64 KB
+  const dim3 grid((unsigned)((w.plan.units + per_block - 1) / per_block), pb.Hq);
+  const size_t lds = (size_t)per_block * n * sizeof(int);
+  hipLaunchKernelGGL((bucket_kernel<false, Items>), grid, dim3(64 * per_block), lds, st, idx, unit_cnt, cursor,
+                     items, part_lse, pb.Lq, pb.q_pos0, pb.G, pb.topk, n, w.plan, it);
+  hipLaunchKernelGGL(bucket_unit_scan_kernel, dim3((n + 31) / 32, pb.Hkv), dim3(1024), 0, st, unit_cnt, counts,
+                     pb.G * w.plan.units, n);
+  hipLaunchKernelGGL(bucket_scan_kernel, dim3(1), dim3(1024), 0, st, counts, item_off, tile_off, cursor, w.B);
+  hipLaunchKernelGGL(bucket_tiles_kernel, dim3(w.B), dim3(256), 0, st, tile_off, item_off, tile_info, items);
+  hipLaunchKernelGGL((bucket_kernel<true, Items>), grid, dim3(64 * per_block), lds, st, idx, unit_cnt, cursor,
+                     items, part_lse, pb.Lq, pb.q_pos0, pb.G, pb.topk, n, w.plan, it);
+  return hipGetLastError() == hipSuccess;
 }
 
 }  // namespace
@@ -1293,7 +1356,7 @@ sl_status prefill_attention_mfma(const Problem& pb, const void* Q, const void* K
   char* base = static_cast<char*>(ws);
   bf16_t* Vt = reinterpret_cast<bf16_t*>(base + w.vt);
   int* counts = reinterpret_cast<int*>(base + w.counts);
-  int* blk_cnt = reinterpret_cast<int*>(base + w.blk_cnt);
+  int* unit_cnt = reinterpret_cast<int*>(base + w.unit_cnt);
   int* item_off = reinterpret_cast<int*>(base + w.item_off);
   int* tile_off = reinterpret_cast<int*>(base + w.tile_off);
   int* cursor = reinterpret_cast<int*>(base + w.cursor);
@@ -1340,18 +1403,9 @@ sl_status prefill_attention_mfma(const Problem& pb, const void* Q, const void* K
   a.kvst = pb.kvst;
 
   if (pb.topk > 0) {
-    const dim3 bgrid((unsigned)w.chunks, pb.Hq);
-    hipLaunchKernelGGL(bucket_kernel<false>, bgrid, dim3(256), (size_t)n * sizeof(int), st, idx,
-                       blk_cnt, cursor, items, pb.Lq, pb.q_pos0, pb.G, pb.A, pb.topk, n);
-    hipLaunchKernelGGL(bucket_block_scan_kernel, dim3((n + 31) / 32, pb.Hkv), dim3(256), 0, st, blk_cnt,
-                       counts, pb.G * w.chunks, n);
-    hipLaunchKernelGGL(bucket_scan_kernel, dim3(1), dim3(1024), 0, st, counts, item_off, tile_off,
-                       cursor, w.B);
-    hipLaunchKernelGGL(bucket_tiles_kernel, dim3(w.B), dim3(256), 0, st, tile_off, item_off, tile_info,
-                       items);
-    hipLaunchKernelGGL(bucket_kernel<true>, bgrid, dim3(256), (size_t)4 * n * sizeof(int), st, idx,
-                       blk_cnt, cursor, items, pb.Lq, pb.q_pos0, pb.G, pb.A, pb.topk, n);
-    if (hipGetLastError() != hipSuccess) return SL_ERR_LAUNCH;
+    if (!launch_buckets(pb, w, idx, unit_cnt, counts, item_off, tile_off, cursor, tile_info, items, part_lse,
+                        GridItems{pb.A}, st))
+      return SL_ERR_LAUNCH;
     if (pb.prof_start) (void)hipEventRecord(pb.prof_start, st);
     if (pb.A < pb.S && !pb.combined)  // overlapping spans in one joint softmax: per-row clipping
       hipLaunchKernelGGL(span_flash_routed_kernel<true>, dim3(dev.grid), dim3(FlashLds<2>::kThreads),
@@ -1436,7 +1490,7 @@ sl_status prefill_anchor_attention_mfma(const Problem& pb, int64_t window, int b
   char* base = static_cast<char*>(ws);
   bf16_t* Vt = reinterpret_cast<bf16_t*>(base + w.vt);
   int* counts = reinterpret_cast<int*>(base + w.counts);
-  int* blk_cnt = reinterpret_cast<int*>(base + w.blk_cnt);
+  int* unit_cnt = reinterpret_cast<int*>(base + w.unit_cnt);
   int* item_off = reinterpret_cast<int*>(base + w.item_off);
   int* tile_off = reinterpret_cast<int*>(base + w.tile_off);
   int* cursor = reinterpret_cast<int*>(base + w.cursor);
@@ -1482,18 +1536,12 @@ sl_status prefill_anchor_attention_mfma(const Problem& pb, int64_t window, int b
   a.kvsh = pb.kvsh;
   a.kvst = pb.kvst;
 
-  const dim3 bgrid((unsigned)w.chunks, pb.Hq);
-  hipLaunchKernelGGL(bucket_anchor_kernel<false>, bgrid, dim3(256), (size_t)n * sizeof(int), st, anchors,
-                     blk_cnt, cursor, items, part_lse, pb.Lq, pb.q_pos0, pb.G, pb.topk, n, window, b, f, root,
-                     a.E);
-  hipLaunchKernelGGL(bucket_block_scan_kernel, dim3((n + 31) / 32, pb.Hkv), dim3(256), 0, st, blk_cnt, counts,
-                     pb.G * w.chunks, n);
-  hipLaunchKernelGGL(bucket_scan_kernel, dim3(1), dim3(1024), 0, st, counts, item_off, tile_off, cursor, w.B);
-  hipLaunchKernelGGL(bucket_tiles_kernel, dim3(w.B), dim3(256), 0, st, tile_off, item_off, tile_info, items);
-  hipLaunchKernelGGL(bucket_anchor_kernel<true>, bgrid, dim3(256), (size_t)4 * n * sizeof(int), st, anchors,
-                     blk_cnt, cursor, items, part_lse, pb.Lq, pb.q_pos0, pb.G, pb.topk, n, window, b, f, root,
-                     a.E);
-  if (hipGetLastError() != hipSuccess) return SL_ERR_LAUNCH;
+  MfmaWs wa = w;
+  wa.plan.unit_h = 1;  // items of a bucket by row, then by head
+  wa.plan.unit_u = pb.G;
+  if (!launch_buckets(q, wa, anchors, unit_cnt, counts, item_off, tile_off, cursor, tile_info, items, part_lse,
+                      AnchorItems{window, b, f, root, a.E}, st))
+    return SL_ERR_LAUNCH;
   if (pb.prof_start) (void)hipEventRecord(pb.prof_start, st);
   hipLaunchKernelGGL(span_flash_anchor_kernel, dim3(dev.grid), dim3(FlashLds<2>::kThreads),
                      FlashLds<2>::kBytes, st, a);
