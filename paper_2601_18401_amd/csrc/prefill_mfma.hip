@@ -20,9 +20,9 @@
 //
 // MFMA formulation.  Both products are computed transposed so that a lane owns a query column:
 //   S^T[kv][q] = K[kv][:] . Q[q][:]      A = K tile (LDS), B = Q rows (registers)
-//   O^T[d][q] += V^T[d][kv] . P^T[kv][q] A = V^T tile (LDS), B = P^T straight from the S^T
-//                                         accumulators (no shuffle: the K rows of a tile are fed
-//                                         in an order that makes a lane's 8 consecutive
+//   O^T[d][q] += V^T[d][kv] . P^T[kv][q] A = V tile (LDS, transposing reads), B = P^T straight from
+//                                         the S^T accumulators (no shuffle: the K rows of a tile
+//                                         are fed in an order that makes a lane's 8 consecutive
 //                                         accumulators 8 consecutive kv positions)
 // With v_mfma_f32_32x32x16_bf16, lane l of the 32x32 result holds column l%32 and rows
 // 8*(r/4) + 4*(l/32) + r%4 for accumulator r = 0..15.
@@ -42,21 +42,27 @@ constexpr int TG = 128;            // rows of one wavefront group (4 wavefronts 
 constexpr int TN = 64;             // kv positions per staged tile
 constexpr int HD = 128;            // head dimension of this path
 
-// LDS of the flash kernels (dynamic).  Main loop: stages of the V^T tile and of the K tile, filled
+// LDS of the flash kernels (dynamic).  Main loop: stages of the V tile and of the K tile, filled
 // by direct global->LDS loads (16 bytes per lane, a wavefront instruction fills 1 KB
 // contiguously); rows are unpadded and their 16-byte pieces XOR-swizzled so that the MFMA
 // operand reads of 16 consecutive lanes hit 16 distinct bank groups:
-//   K tile  [64][128]: piece p of row r at position p ^ (r & 15)
-//   V^T tile [128][64]: piece p of row d at position p ^ ((d >> 1) & 7)
+//   K tile [64][128]: piece p of row r at position p ^ (r & 15)
+//   V tile [64][128]: piece p of row r at position p ^ ((r & 3) << 2): the four rows that 16 lanes read
+//                     64 bytes of (with the 16 lanes beside them) lie in different bank groups
+// V is staged as it lies in memory and transposed by the LDS reads (ds_read_b64_tr_b16): a transposed
+// copy of V in the workspace cost a pass over the whole cache per call, however few the rows: 63 us for
+// 4000 new rows behind 196000 tokens (0.945 -> 0.931 ms in all, the twice as many LDS reads take back part
+// of it), 22 us at 48K on the paper's geometry (4.45 -> 4.41 ms); with all 262144 rows, where the copy was
+// 87 us of 25.8 ms, the attention takes 26.0 ms.
 // Epilogue: each wavefront group stages its output tile [128][128] bf16 (piece p of row r at
 // p ^ (r & 15)).
 //   NG = 2 (routed, 512 threads, 256 rows, one workgroup per compute unit, 154624 bytes): two K
-//     and three V^T stages (the late group reads a V^T tile one step after the early group); the
+//     and three V stages (the late group reads a V tile one step after the early group); the
 //     output region is separate, so the first K/V tile of the next 256-row tile can be fetched
 //     while the current one is written out.
 //   NG = 1 (local window, 256 threads, 128 rows, 67072 bytes: two workgroups per compute unit, so
 //     one's epilogue runs beside the other's main loop): two stages each; the output region
-//     lies over the V^T stages, which are dead by then.
+//     lies over the V stages, which are dead by then.
 constexpr int kStageElems = TN * HD;  // 8192 bf16 = 16 KB
 template <int NG>
 struct FlashLds {
@@ -94,6 +100,16 @@ __device__ __forceinline__ int64_t uniform64(int64_t v) {
   return (int64_t)(((uint64_t)hi << 32) | lo);
 }
 
+// Two transposing LDS reads: the lane's column of kv rows 0..3 and 4..7 behind p (its own block address).
+__device__ __forceinline__ bf16x8 transposed8(const bf16_t* p) {
+  typedef short s16x4 __attribute__((ext_vector_type(4)));
+  typedef short s16x8 __attribute__((ext_vector_type(8)));
+  typedef __attribute__((address_space(3))) s16x4* LdsPtr;
+  const s16x4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LdsPtr)p);
+  const s16x4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LdsPtr)(p + 4 * HD));
+  return __builtin_bit_cast(bf16x8, __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
 __device__ __forceinline__ float pair_max(float x) {
   // lanes l and l^32 hold the two halves of a query column
   auto r = __builtin_amdgcn_permlane32_swap(__float_as_int(x), __float_as_int(x), false, false);
@@ -121,37 +137,6 @@ __device__ __forceinline__ AnchorSpan anchor_span_of(int64_t i, int64_t t, int64
   r.hi = (e1 < wlo - 1 ? e1 : wlo - 1) + 1;
   if (r.hi < r.lo || !r.valid) r.hi = r.lo;
   return r;
-}
-
-// ------------------------------------------------------------------ V transpose (workspace)
-// Vt[kv][d][t] = V[kv][t][d], row length Lp (L rounded up to 64, zero padded).
-__global__ __launch_bounds__(256) void transpose_v_kernel(const bf16_t* __restrict__ V,
-                                                          bf16_t* __restrict__ Vt, int64_t L,
-                                                          int64_t Lp, int64_t kvsh, int64_t kvst) {
-  __shared__ bf16_t s[64 * (HD + 2)];
-  const int kv = blockIdx.y, tid = threadIdx.x;
-  const int64_t t0 = (int64_t)blockIdx.x * 64;
-  for (int i = 0; i < 4; ++i) {
-    const int idx = tid + 256 * i, row = idx >> 4, piece = idx & 15;
-    const int64_t t = t0 + row;
-    uint4 v = make_uint4(0, 0, 0, 0);
-    if (t < L) v = load16(V + kv * kvsh + t * kvst + piece * 8);
-    uint32_t* dst = reinterpret_cast<uint32_t*>(&s[row * (HD + 2) + piece * 8]);
-    dst[0] = v.x; dst[1] = v.y; dst[2] = v.z; dst[3] = v.w;
-  }
-  __syncthreads();
-  for (int i = 0; i < 4; ++i) {
-    const int idx = tid + 256 * i, d = idx >> 3, piece = idx & 7;
-    uint32_t w[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const uint32_t lo = s[(piece * 8 + 2 * e) * (HD + 2) + d];
-      const uint32_t hi = s[(piece * 8 + 2 * e + 1) * (HD + 2) + d];
-      w[e] = lo | (hi << 16);
-    }
-    *reinterpret_cast<uint4*>(Vt + ((int64_t)kv * HD + d) * Lp + t0 + piece * 8) =
-        make_uint4(w[0], w[1], w[2], w[3]);
-  }
 }
 
 // ------------------------------------------------------------------ bucketing
@@ -403,7 +388,7 @@ __global__ __launch_bounds__(256) void bucket_tiles_kernel(const int* __restrict
 struct FlashArgs {
   const bf16_t* Q;
   const bf16_t* K;
-  const bf16_t* Vt;
+  const bf16_t* V;
   const int32_t* idx;
   // routed
   const int* item_off;
@@ -415,7 +400,7 @@ struct FlashArgs {
   // local + merge
   bf16_t* O;
   float* LSE;
-  int64_t L, Lp, Lq, q_pos0;
+  int64_t L, Lq, q_pos0;
   int Hq, G, S, A, topk, n;  // A: anchor spacing (= S on the disjoint grid); n = ceil(L / A)
   // The paper's own geometry (Section 3.3, Algorithm 1) instead of the grid: idx holds anchor
   // TOKENS; window > 0 marks this mode.  Span of anchor t for the query at i:
@@ -522,27 +507,24 @@ __device__ __forceinline__ void flash_tile(const FlashArgs& a, char* lds, const 
   bf16_t* const ldsV = reinterpret_cast<bf16_t*>(lds + Lds::kV);
   bf16_t* const ldsK = reinterpret_cast<bf16_t*>(lds + Lds::kK);
 
-  // Direct global -> LDS staging of one (K, V^T) tile pair in 1 KB blocks (4 K rows or 8 V^T rows
-  // each); lane L of a block lands at byte 16*L.
+  // Direct global -> LDS staging of one (K, V) tile pair in 1 KB blocks (4 rows each); lane L of a
+  // block lands at byte 16*L.
   // Per-lane byte offsets are loop-invariant 32-bit values; the kv head and the tile position
   // go into the wave-uniform base pointer.
   uint32_t koff[BPW], voff[BPW];
 #pragma unroll
   for (int i = 0; i < BPW; ++i) {
-    const int blk = wave * BPW + i;
-    const int row = blk * 4 + (lane >> 4), pc = lane & 15, gp = pc ^ (row & 15);
-    koff[i] = (uint32_t)((row * a.kvst + gp * 8) * sizeof(bf16_t));
-    const int d = blk * 8 + (lane >> 3), pv = lane & 7, gv = pv ^ ((d >> 1) & 7);
-    voff[i] = (uint32_t)((d * a.Lp + gv * 8) * sizeof(bf16_t));
+    const int row = (wave * BPW + i) * 4 + (lane >> 4), pc = lane & 15;
+    koff[i] = (uint32_t)((row * a.kvst + (pc ^ (row & 15)) * 8) * sizeof(bf16_t));
+    voff[i] = (uint32_t)((row * a.kvst + (pc ^ ((row & 3) << 2)) * 8) * sizeof(bf16_t));
   }
   // wavefront w fills blocks w*BPW .. w*BPW + BPW-1 of both tiles
   auto stage = [&](int kvh, int64_t t0, int kb, int vb) {
-    // K rows past the end of the sequence lie beyond the buffer: zeros in LDS (masked later)
+    // rows past the end of the sequence lie beyond the buffer: zeros in LDS (masked later)
     const int rows = __builtin_amdgcn_readfirstlane(a.L - t0 < TN ? (int)(a.L - t0) : TN);
-    const BufferRsrc kr = buffer_of(a.K + uniform64((int64_t)kvh * a.kvsh + t0 * a.kvst),
-                                    (uint32_t)(((rows - 1) * a.kvst + HD) * sizeof(bf16_t)));
-    const BufferRsrc vr = buffer_of(a.Vt + uniform64((int64_t)kvh * HD * a.Lp + t0),
-                                    (uint32_t)(((HD - 1) * a.Lp + TN) * sizeof(bf16_t)));
+    const int64_t first = uniform64((int64_t)kvh * a.kvsh + t0 * a.kvst);
+    const uint32_t bytes = (uint32_t)(((rows - 1) * a.kvst + HD) * sizeof(bf16_t));
+    const BufferRsrc kr = buffer_of(a.K + first, bytes), vr = buffer_of(a.V + first, bytes);
 #pragma unroll
     for (int i = 0; i < BPW; ++i)
       __builtin_amdgcn_raw_ptr_buffer_load_lds(kr, SL_LDS_PTR(ldsK + kb * kStageElems + (uwave * BPW + i) * 512), 16,
@@ -577,7 +559,14 @@ __device__ __forceinline__ void flash_tile(const FlashArgs& a, char* lds, const 
 
   const int krow = perm_row(qc);
   const int kswz = krow & 15;      // swizzle key of this lane's K rows (32*sub does not change it)
-  const int vswz = (qc >> 1) & 7;  // swizzle key of this lane's V^T rows (32*dt does not change it)
+  // V^T fragments come from transposing reads: 16 lanes read a [4 kv][16 d] block, 8 bytes each, and lane
+  // i of them receives column i.  Lane offset (elements) of the block for d tile dt, kv rows 8*hf .. 8*hf+3.
+  const int vrow = (lane & 15) >> 2;
+  int vlane[4];
+#pragma unroll
+  for (int dt = 0; dt < 4; ++dt)
+    vlane[dt] = (8 * hf + vrow) * HD + (((4 * dt + 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1)) ^ (vrow << 2)) << 3) +
+                4 * (lane & 1);
   const float sc = a.scale_log2e;
 
   // S^T = K Q^T (two 32-row halves of the tile), mask, running maximum, exponentials -> pb.
@@ -657,15 +646,14 @@ __device__ __forceinline__ void flash_tile(const FlashArgs& a, char* lds, const 
     for (int ks = 0; ks < 4; ++ks)
 #pragma unroll
       for (int dt = 0; dt < 4; ++dt) {
-        const bf16x8 va = *reinterpret_cast<const bf16x8*>(
-            &vt[(32 * dt + qc) * TN + (((2 * ks + hf) ^ vswz) << 3)]);
+        const bf16x8 va = transposed8(vt + vlane[dt] + 16 * ks * HD);
         o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, pb[ks], o[dt], 0, 0, 0);
       }
-    __builtin_amdgcn_sched_group_barrier(0x100, 4, 1);
+    __builtin_amdgcn_sched_group_barrier(0x100, 8, 1);
 #pragma unroll
     for (int i = 0; i < 12; ++i) {
       __builtin_amdgcn_sched_group_barrier(0x008, 1, 1);
-      __builtin_amdgcn_sched_group_barrier(0x100, 1, 1);
+      __builtin_amdgcn_sched_group_barrier(0x100, 2, 1);
     }
     __builtin_amdgcn_sched_group_barrier(0x008, 4, 1);
   };
@@ -673,7 +661,7 @@ __device__ __forceinline__ void flash_tile(const FlashArgs& a, char* lds, const 
   int kb = c.kb, vb = c.vb, vb_prev = c.vb;
   for (int64_t t0 = cur.kv_begin; t0 < cur.kv_end; t0 += TN) {
     // After the barrier the tile of this iteration is visible to every wavefront, every wavefront
-    // is done with the K stage of the previous tile and the late group with the V^T stage before
+    // is done with the K stage of the previous tile and the late group with the V stage before
     // that: exactly the stages that the next tile goes into.
     __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
     __syncthreads();
@@ -698,7 +686,7 @@ __device__ __forceinline__ void flash_tile(const FlashArgs& a, char* lds, const 
     vb = vb1;
   }
   // Every wavefront is past its last QK: all K stages and the Q fragments are dead, and so is
-  // every V^T stage except the last tile's (the late group still owes its PV).  Request the next
+  // every V stage except the last tile's (the late group still owes its PV).  Request the next
   // tile's first stage and Q fragments now; they land while this tile is written out.
   __syncthreads();
   c.kb = kb;
@@ -1225,9 +1213,8 @@ __global__ __launch_bounds__(256) void merge_combined_kernel(
 
 // ------------------------------------------------------------------ workspace carving
 struct MfmaWs {
-  size_t vt, counts, unit_cnt, item_off, tile_off, cursor, tile_info, items, part_lse, part_o, total;
+  size_t counts, unit_cnt, item_off, tile_off, cursor, tile_info, items, part_lse, part_o, total;
   BucketPlan plan;
-  int64_t Lp;
   int B, max_tiles;
   int64_t max_items;
 };
@@ -1284,7 +1271,6 @@ BucketPlan bucket_plan(const Problem& pb) {
 
 MfmaWs carve(const Problem& pb) {
   MfmaWs w;
-  w.Lp = (int64_t)align_up((size_t)pb.L, 64);
   w.B = pb.Hkv * (int)pb.n;
   w.max_items = (int64_t)pb.Hq * pb.Lq * pb.topk;
   w.max_tiles = (int)((w.max_items + TM - 1) / TM) + w.B;
@@ -1294,7 +1280,6 @@ MfmaWs carve(const Problem& pb) {
     off = align_up(off + bytes, 256);
     return at;
   };
-  w.vt = take((size_t)pb.Hkv * HD * w.Lp * sizeof(bf16_t));
   w.counts = take((size_t)w.B * sizeof(int));
   w.plan = bucket_plan(pb);
   w.unit_cnt = take((size_t)pb.Hq * w.plan.units * pb.n * sizeof(int));
@@ -1332,11 +1317,14 @@ bool launch_buckets(const Problem& pb, const MfmaWs& w, const int32_t* idx, int*
 
 }  // namespace
 
+// Longer sequences stay with the row-stationary kernels, whose softmax weights are fp32.
+constexpr int64_t kMaxTokens = ((int64_t)1 << 24) - 64;
+
 bool prefill_attention_mfma_supported(const Problem& pb) {
   return pb.dtype == SL_BF16 && pb.D == HD && pb.S % TN == 0 && pb.A % TN == 0 && pb.n <= 4096 &&
          (int64_t)pb.G * pb.Lq < ((int64_t)1 << 26) &&  // item = (row id << 5) | slot
-         // staging uses 32-bit byte offsets inside one kv head's V^T and inside a 64-row K tile
-         (int64_t)HD * (int64_t)align_up((size_t)pb.L, 64) * 2 < ((int64_t)1 << 32) &&
+         pb.L <= kMaxTokens &&
+         // staging uses 32-bit byte offsets inside a 64-row tile
          64 * pb.kvst * 2 < ((int64_t)1 << 31) &&
          (int64_t)pb.Hq * pb.Lq * (pb.topk + 1) < ((int64_t)1 << 31) &&
          // 32-bit positions in the tile-by-tile item list
@@ -1354,7 +1342,6 @@ sl_status prefill_attention_mfma(const Problem& pb, const void* Q, const void* K
   DeviceSetup dev;
   if (!device_setup(&dev) || !dev.lds_ok) return SL_ERR_LAUNCH;
   char* base = static_cast<char*>(ws);
-  bf16_t* Vt = reinterpret_cast<bf16_t*>(base + w.vt);
   int* counts = reinterpret_cast<int*>(base + w.counts);
   int* unit_cnt = reinterpret_cast<int*>(base + w.unit_cnt);
   int* item_off = reinterpret_cast<int*>(base + w.item_off);
@@ -1366,13 +1353,10 @@ sl_status prefill_attention_mfma(const Problem& pb, const void* Q, const void* K
   bf16_t* part_o = reinterpret_cast<bf16_t*>(base + w.part_o);
   const int n = (int)pb.n;
 
-  hipLaunchKernelGGL(transpose_v_kernel, dim3((unsigned)(w.Lp / 64), pb.Hkv), dim3(256), 0, st,
-                     static_cast<const bf16_t*>(V), Vt, pb.L, w.Lp, pb.kvsh, pb.kvst);
-
   FlashArgs a;
   a.Q = static_cast<const bf16_t*>(Q);
   a.K = static_cast<const bf16_t*>(K);
-  a.Vt = Vt;
+  a.V = static_cast<const bf16_t*>(V);
   a.idx = idx;
   a.item_off = item_off;
   a.tile_off = tile_off;
@@ -1383,7 +1367,6 @@ sl_status prefill_attention_mfma(const Problem& pb, const void* Q, const void* K
   a.O = static_cast<bf16_t*>(O);
   a.LSE = LSE;
   a.L = pb.L;
-  a.Lp = w.Lp;
   a.Lq = pb.Lq;
   a.q_pos0 = pb.q_pos0;
   a.Hq = pb.Hq;
@@ -1467,7 +1450,7 @@ bool prefill_anchor_mfma_supported(const Problem& pb, int64_t window) {
   const Problem q = anchor_view(pb);
   return window >= 1 && pb.topk >= 1 && pb.dtype == SL_BF16 && pb.D == HD && q.n <= 4096 &&
          (int64_t)pb.G * pb.Lq < ((int64_t)1 << 26) &&
-         (int64_t)HD * (int64_t)align_up((size_t)pb.L, 64) * 2 < ((int64_t)1 << 32) &&
+         pb.L <= kMaxTokens &&
          64 * pb.kvst * 2 < ((int64_t)1 << 31) &&
          (int64_t)pb.Hq * pb.Lq * (pb.topk + 1) < ((int64_t)1 << 31) &&
          (int64_t)pb.Hq * pb.Lq * pb.topk + ((int64_t)pb.Hkv * q.n + 1) * TM < ((int64_t)1 << 31) &&
@@ -1488,7 +1471,6 @@ sl_status prefill_anchor_attention_mfma(const Problem& pb, int64_t window, int b
   DeviceSetup dev;
   if (!device_setup(&dev) || !dev.lds_ok) return SL_ERR_LAUNCH;
   char* base = static_cast<char*>(ws);
-  bf16_t* Vt = reinterpret_cast<bf16_t*>(base + w.vt);
   int* counts = reinterpret_cast<int*>(base + w.counts);
   int* unit_cnt = reinterpret_cast<int*>(base + w.unit_cnt);
   int* item_off = reinterpret_cast<int*>(base + w.item_off);
@@ -1500,12 +1482,10 @@ sl_status prefill_anchor_attention_mfma(const Problem& pb, int64_t window, int b
   bf16_t* part_o = reinterpret_cast<bf16_t*>(base + w.part_o);
   const int n = (int)q.n;
 
-  hipLaunchKernelGGL(transpose_v_kernel, dim3((unsigned)(w.Lp / 64), pb.Hkv), dim3(256), 0, st,
-                     static_cast<const bf16_t*>(V), Vt, pb.L, w.Lp, pb.kvsh, pb.kvst);
   FlashArgs a;
   a.Q = static_cast<const bf16_t*>(Q);
   a.K = static_cast<const bf16_t*>(K);
-  a.Vt = Vt;
+  a.V = static_cast<const bf16_t*>(V);
   a.idx = anchors;
   a.item_off = item_off;
   a.tile_off = tile_off;
@@ -1516,7 +1496,6 @@ sl_status prefill_anchor_attention_mfma(const Problem& pb, int64_t window, int b
   a.O = static_cast<bf16_t*>(O);
   a.LSE = nullptr;
   a.L = pb.L;
-  a.Lp = w.Lp;
   a.Lq = pb.Lq;
   a.q_pos0 = pb.q_pos0;
   a.Hq = pb.Hq;
