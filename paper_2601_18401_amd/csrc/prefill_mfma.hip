@@ -413,6 +413,16 @@ struct FlashArgs {
   int64_t qsh, qst, kvsh, kvst;
 };
 
+// The kernel's arguments (its only parameter is a FlashArgs), read anew where they are used once per tile:
+// kept in scalar registers across the kv loop, they fill those, and the scheduler then gives up the
+// ordering of the loop's LDS reads and MFMAs.
+typedef const __attribute__((address_space(4))) FlashArgs* ArgsPtr;
+__device__ __forceinline__ ArgsPtr args_anew() {
+  ArgsPtr p = (ArgsPtr)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(p));
+  return p;
+}
+
 __device__ __forceinline__ int perm_row(int rho) {
   // swap bits 2 and 3: accumulator order <-> consecutive kv positions
   return (rho & 0x13) | ((rho & 4) << 1) | ((rho & 8) >> 1);
@@ -447,8 +457,9 @@ struct FlashCarry {
 // from the group's LDS region to the partial buffers: 16 lanes per row, 16 bytes per lane.
 // Called when no direct global->LDS load is in flight (the compiler orders an LDS read after all
 // outstanding vector-memory operations once such loads exist).
-__device__ __forceinline__ void flush_routed_output(const FlashArgs& a, char* lds, int grp, int w4, int lane) {
+__device__ __forceinline__ void flush_routed_output(char* lds, int grp, int w4, int lane) {
   using Lds = FlashLds<2>;
+  const ArgsPtr a = args_anew();
   const bf16_t* const ost = reinterpret_cast<const bf16_t*>(lds + Lds::kOut) + grp * TG * HD;
   const int64_t* const row_out = reinterpret_cast<const int64_t*>(lds + Lds::kRowOut) + grp * TG;
   const float* const row_lse = reinterpret_cast<const float*>(lds + Lds::kRowLse) + grp * TG;
@@ -471,8 +482,8 @@ __device__ __forceinline__ void flush_routed_output(const FlashArgs& a, char* ld
       if (outs[u] >= 0) {
         // streamed past the caches: the partials (gigabytes) are read back by a later kernel, and
         // the K/V tiles keep the L2
-        store16_stream(a.part_o + outs[u] * HD + piece * 8, vals[u]);
-        if (piece == 0) __builtin_nontemporal_store(lses[u], &a.part_lse[outs[u]]);
+        store16_stream(a->part_o + outs[u] * HD + piece * 8, vals[u]);
+        if (piece == 0) __builtin_nontemporal_store(lses[u], &a->part_lse[outs[u]]);
       }
     }
   }
@@ -502,6 +513,7 @@ __device__ __forceinline__ void flash_tile(const FlashArgs& a, char* lds, const 
   const int grp = wave >> 2, w4 = wave & 3;  // grp 0 = early, 1 = late
   const int qc = lane & 31, hf = lane >> 5;
   const int srow = w4 * 32 + qc;             // row inside the group's 128-row half tile
+  constexpr bool kMasked = LOCAL || CLIP;
   using Lds = FlashLds<NG>;
   constexpr int kStagesK = Lds::kStagesK, kStagesV = Lds::kStagesV, BPW = Lds::kBlocksPerWave;
   bf16_t* const ldsV = reinterpret_cast<bf16_t*>(lds + Lds::kV);
@@ -568,10 +580,17 @@ __device__ __forceinline__ void flash_tile(const FlashArgs& a, char* lds, const 
     vlane[dt] = (8 * hf + vrow) * HD + (((4 * dt + 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1)) ^ (vrow << 2)) << 3) +
                 4 * (lane & 1);
   const float sc = a.scale_log2e;
+  // the lane's own range [lo_q, i_q] as 32-bit offsets from the tile's first token
+  auto offset_of = [&](int64_t t) {
+    const int64_t d = t - cur.kv_begin;
+    return (int)(d < -1 ? -1 : d > (1 << 30) ? (1 << 30) : d);
+  };
+  const int lo_r = kMasked ? offset_of(cur.lo_q) : 0, hi_r = kMasked ? offset_of(cur.i_q) : 0;
 
   // S^T = K Q^T (two 32-row halves of the tile), mask, running maximum, exponentials -> pb.
   // LDS fragment reads run four MFMAs ahead (0x100 = LDS read, 0x008 = MFMA).
-  auto qk_softmax = [&](const bf16_t* kt, int64_t t0) {
+  // base: the kv tile's offset from the tile's first token.
+  auto qk_softmax = [&](const bf16_t* kt, int base) {
     f32x16 s[2];
 #pragma unroll
     for (int sub = 0; sub < 2; ++sub)
@@ -596,17 +615,23 @@ __device__ __forceinline__ void flash_tile(const FlashArgs& a, char* lds, const 
     // other wavefront; that one needs a slot every 32 cycles, this one needs most of them.
     __builtin_amdgcn_s_setprio(3);
 
+    // Per-row ranges (the causal window, a span clipped behind a lower one, an anchor's span): only the
+    // tiles at the ends of a wavefront's ranges are masked, one unsigned compare per score.  (With two
+    // 64-bit compares per score on every tile the paper's geometry at 48K took 4.50 ms, now 3.68.)
+    if (kMasked && __builtin_amdgcn_ballot_w64(lo_r > base || hi_r < base + TN - 1) != 0ull) {
+      const uint32_t width = hi_r >= lo_r ? (uint32_t)(hi_r - lo_r) : 0u;
+      const uint32_t u = hi_r >= lo_r ? (uint32_t)(base + 8 * hf - lo_r) : 0x80000000u;
+#pragma unroll
+      for (int sub = 0; sub < 2; ++sub)
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          s[sub][r] = u + (uint32_t)(32 * sub + 16 * (r >> 3) + (r & 7)) <= width ? s[sub][r] : -INFINITY;
+    }
     float mx = -INFINITY;
 #pragma unroll
     for (int sub = 0; sub < 2; ++sub)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        if (LOCAL || CLIP) {  // per-row range: the causal window, or a span clipped behind a lower one
-          const int64_t t = t0 + 32 * sub + 16 * (r >> 3) + 8 * hf + (r & 7);
-          s[sub][r] = (t <= cur.i_q && t >= cur.lo_q) ? s[sub][r] : -INFINITY;
-        }
-        mx = fmaxf(mx, s[sub][r]);
-      }
+      for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[sub][r]);
     mx = pair_max(mx) * sc;
     // Lazy rescale, decided per column: a column's running maximum only moves when that column
     // grew by more than 2^8; until then its exponentials are taken against the old maximum
@@ -658,7 +683,12 @@ __device__ __forceinline__ void flash_tile(const FlashArgs& a, char* lds, const 
     __builtin_amdgcn_sched_group_barrier(0x008, 4, 1);
   };
 
+  // a kv tile that none of the wavefront's rows attends is passed over (its weights would all be 0)
+  auto attends = [&](int base) {
+    return !kMasked || __builtin_amdgcn_ballot_w64(lo_r <= base + TN - 1 && hi_r >= base && hi_r >= lo_r) != 0ull;
+  };
   int kb = c.kb, vb = c.vb, vb_prev = c.vb;
+  bool owes_pv = false;  // late group: the previous kv tile's PV product is still to be taken
   for (int64_t t0 = cur.kv_begin; t0 < cur.kv_end; t0 += TN) {
     // After the barrier the tile of this iteration is visible to every wavefront, every wavefront
     // is done with the K stage of the previous tile and the late group with the V stage before
@@ -669,17 +699,22 @@ __device__ __forceinline__ void flash_tile(const FlashArgs& a, char* lds, const 
     if (NG == 2 && !LOCAL && c.pending) {
       // the previous tile's output: written out here, a step after it was staged, so that the wait
       // at the top of this tile did not have to cover its stores
-      flush_routed_output(a, lds, grp, w4, lane);
+      flush_routed_output(lds, grp, w4, lane);
       c.pending = false;
     }
     if (t0 + TN < cur.kv_end) stage(cur.kv, t0 + TN, kb1, vb1);
     if (NG == 2 && has_next && t0 == cur.kv_begin) request_next();
+    const int base = (int)(t0 - cur.kv_begin);
+    const bool mine = attends(base);
     if (grp == 0) {
-      qk_softmax(ldsK + kb * kStageElems, t0);
-      pv(ldsV + vb * kStageElems);
+      if (mine) {
+        qk_softmax(ldsK + kb * kStageElems, base);
+        pv(ldsV + vb * kStageElems);
+      }
     } else {
-      if (t0 > cur.kv_begin) pv(ldsV + vb_prev * kStageElems);
-      qk_softmax(ldsK + kb * kStageElems, t0);
+      if (owes_pv) pv(ldsV + vb_prev * kStageElems);
+      if (mine) qk_softmax(ldsK + kb * kStageElems, base);
+      owes_pv = mine;
     }
     vb_prev = vb;
     kb = kb1;
@@ -700,7 +735,7 @@ __device__ __forceinline__ void flash_tile(const FlashArgs& a, char* lds, const 
   // From here to the end of the tile the late group is the critical path (it still owes a PV):
   // its wavefronts go first wherever both groups want an issue slot.
   if (NG == 2 && grp == 1) __builtin_amdgcn_s_setprio(2);
-  if (grp == 1) pv(ldsV + vb_prev * kStageElems);  // the late group's last PV
+  if (grp == 1 && owes_pv) pv(ldsV + vb_prev * kStageElems);  // the late group's last PV
 
   // epilogue, wavefront-local (no workgroup barrier): normalise, stage the wavefront's 32 rows as
   // [row][d] bf16 in its own slice of the group's LDS region (swizzled 16-byte pieces), then
@@ -850,25 +885,26 @@ __global__ __launch_bounds__(FlashLds<2>::kThreads, 1) void span_flash_routed_ke
   if (t_begin >= t_end) return;
 
   auto describe = [&](const int4& info, int item) {
+    const ArgsPtr a = args_anew();
     TileDesc d;
-    d.kv = info.x / a.n;
-    const int j = info.x % a.n;
-    d.kv_end = (int64_t)(j + 1) * a.A;
-    d.kv_begin = d.kv_end - a.S > 0 ? d.kv_end - a.S : 0;
+    d.kv = info.x / a->n;
+    const int j = info.x % a->n;
+    d.kv_end = (int64_t)(j + 1) * a->A;
+    d.kv_begin = d.kv_end - a->S > 0 ? d.kv_end - a->S : 0;
     const int rowid = item >> 5, slot = item & 31;
-    const int hl = rowid / (int)a.Lq;
-    const int64_t r = rowid - (int64_t)hl * a.Lq;
-    const int h = d.kv * a.G + hl;
-    d.q_off = h * a.qsh + r * a.qst;
-    d.row_out = qrow < info.z ? ((int64_t)h * a.Lq + r) * (a.topk + 1) + slot : -1;
+    const int hl = rowid / (int)a->Lq;
+    const int64_t r = rowid - (int64_t)hl * a->Lq;
+    const int h = d.kv * a->G + hl;
+    d.q_off = h * a->qsh + r * a->qst;
+    d.row_out = qrow < info.z ? ((int64_t)h * a->Lq + r) * (a->topk + 1) + slot : -1;
     d.i_q = d.kv_end;
     d.lo_q = 0;
     if (CLIP) {
-      const int64_t c = (a.q_pos0 + r) / a.A;
-      const int32_t* irow = a.idx + ((int64_t)h * a.Lq + r) * a.topk;
-      for (int s2 = 0; s2 < a.topk; ++s2) {
+      const int64_t c = (a->q_pos0 + r) / a->A;
+      const int32_t* irow = a->idx + ((int64_t)h * a->Lq + r) * a->topk;
+      for (int s2 = 0; s2 < a->topk; ++s2) {
         const int64_t jj = irow[s2];
-        if (jj >= 0 && jj < c && jj < j && (jj + 1) * a.A > d.lo_q) d.lo_q = (jj + 1) * a.A;
+        if (jj >= 0 && jj < c && jj < j && (jj + 1) * a->A > d.lo_q) d.lo_q = (jj + 1) * a->A;
       }
     }
     d.row_base = 0;
@@ -890,10 +926,11 @@ __global__ __launch_bounds__(FlashLds<2>::kThreads, 1) void span_flash_routed_ke
     flash_tile<2, false, false, CLIP>(
         a, lds, cur, nxt, has_next,
         [&] {
+          const ArgsPtr a = args_anew();
           const int uw = __builtin_amdgcn_readfirstlane(wave);
-          __builtin_amdgcn_raw_ptr_buffer_load_lds(buffer_of(a.tile_info + (t + NWL), 16), SL_LDS_PTR(ahead), 4,
+          __builtin_amdgcn_raw_ptr_buffer_load_lds(buffer_of(a->tile_info + (t + NWL), 16), SL_LDS_PTR(ahead), 4,
                                                    (lane & 3) * 4, 0, 0, 0);
-          __builtin_amdgcn_raw_ptr_buffer_load_lds(buffer_of(a.items + (t + NWL) * TM + uw * 32, 128),
+          __builtin_amdgcn_raw_ptr_buffer_load_lds(buffer_of(a->items + (t + NWL) * TM + uw * 32, 128),
                                                    SL_LDS_PTR(ahead + 64), 4, (lane & 31) * 4, 0, 0, 0);
         },
         [&] {
@@ -904,7 +941,7 @@ __global__ __launch_bounds__(FlashLds<2>::kThreads, 1) void span_flash_routed_ke
     cur = nxt;
   }
   // the last tile's output (its epilogue ended with the wavefront's own LDS writes)
-  if (carry.pending) flush_routed_output(a, lds, wave >> 2, wave & 3, lane);
+  if (carry.pending) flush_routed_output(lds, wave >> 2, wave & 3, lane);
 }
 
 // The paper's geometry: routed tiles of a (kv head, end block) bucket.  Every row of a tile has
@@ -924,18 +961,19 @@ __global__ __launch_bounds__(FlashLds<2>::kThreads, 1) void span_flash_anchor_ke
 
   // all threads call (two barriers inside)
   auto describe = [&](const int4& info, int item) {
+    const ArgsPtr a = args_anew();
     TileDesc d;
-    d.kv = info.x / a.n;
+    d.kv = info.x / a->n;
     const int rowid = item >> 5, slot = item & 31;
-    const int hl = rowid / (int)a.Lq;
-    const int64_t r = rowid - (int64_t)hl * a.Lq;
-    const int h = d.kv * a.G + hl;
-    const int64_t i = a.q_pos0 + r;
+    const int hl = rowid / (int)a->Lq;
+    const int64_t r = rowid - (int64_t)hl * a->Lq;
+    const int h = d.kv * a->G + hl;
+    const int64_t i = a->q_pos0 + r;
     const bool real = qrow < info.z;
-    const int64_t t = a.idx[((int64_t)h * a.Lq + r) * a.topk + slot];
-    const AnchorSpan sp = anchor_span_of(i, t, span_base_length(i, a.aroot), a.window, a.ab, a.af);
-    d.q_off = h * a.qsh + r * a.qst;
-    d.row_out = real ? ((int64_t)h * a.Lq + r) * (a.topk + 1) + slot : -1;
+    const int64_t t = a->idx[((int64_t)h * a->Lq + r) * a->topk + slot];
+    const AnchorSpan sp = anchor_span_of(i, t, span_base_length(i, a->aroot), a->window, a->ab, a->af);
+    d.q_off = h * a->qsh + r * a->qst;
+    d.row_out = real ? ((int64_t)h * a->Lq + r) * (a->topk + 1) + slot : -1;
     d.lo_q = sp.lo;
     d.i_q = sp.hi - 1;
     d.row_base = 0;
@@ -976,10 +1014,11 @@ __global__ __launch_bounds__(FlashLds<2>::kThreads, 1) void span_flash_anchor_ke
     flash_tile<2, false, false, true>(
         a, lds, cur, nxt, has_next,
         [&] {
+          const ArgsPtr a = args_anew();
           const int uw = __builtin_amdgcn_readfirstlane(wave);
-          __builtin_amdgcn_raw_ptr_buffer_load_lds(buffer_of(a.tile_info + (t + NWL), 16), SL_LDS_PTR(ahead), 4,
+          __builtin_amdgcn_raw_ptr_buffer_load_lds(buffer_of(a->tile_info + (t + NWL), 16), SL_LDS_PTR(ahead), 4,
                                                    (lane & 3) * 4, 0, 0, 0);
-          __builtin_amdgcn_raw_ptr_buffer_load_lds(buffer_of(a.items + (t + NWL) * TM + uw * 32, 128),
+          __builtin_amdgcn_raw_ptr_buffer_load_lds(buffer_of(a->items + (t + NWL) * TM + uw * 32, 128),
                                                    SL_LDS_PTR(ahead + 64), 4, (lane & 31) * 4, 0, 0, 0);
         },
         [&] {
@@ -989,7 +1028,7 @@ __global__ __launch_bounds__(FlashLds<2>::kThreads, 1) void span_flash_anchor_ke
         carry);
     cur = nxt;
   }
-  if (carry.pending) flush_routed_output(a, lds, wave >> 2, wave & 3, lane);
+  if (carry.pending) flush_routed_output(lds, wave >> 2, wave & 3, lane);
 }
 
 // Row tiles of the local-window kernel and their grouping into chunks of `tps` tiles (the tiles
