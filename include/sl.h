@@ -42,7 +42,9 @@
  *     abort).  A failed kernel launch returns SL_ERR_LAUNCH.
  *   - Scratch memory comes from the caller through (ws, ws_bytes); ask sl_workspace_bytes for
  *     the size.  ws must be 256-byte aligned.  Calls that share a workspace must be ordered on
- *     one stream.
+ *     one stream.  (Prefill span-attention: for shapes that the bf16 matrix-core form does not
+ *     take -- fp32, D = 64, spans that are no multiple of 64 tokens -- the workspace is optional;
+ *     without one, or with a smaller one, the row-stationary kernels run.)
  */
 #ifndef SL_H_
 #define SL_H_

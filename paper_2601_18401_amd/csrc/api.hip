@@ -136,6 +136,10 @@ sl_status attention_entry(const sl_params* p, int op, const void* Q, const void*
   pb.combined = combined;
   pb.gate = scores;
   s = check_ws(pb, op, ws, ws_bytes);
+  if (s != SL_OK && op == SL_OP_ATTENTION_PREFILL && prefill_attention_ws_optional(pb)) {
+    ws = nullptr;  // the row-stationary kernels need none
+    s = SL_OK;
+  }
   if (s != SL_OK) return s;
   take_profile_events(&pb);
   hipStream_t st = static_cast<hipStream_t>(stream);

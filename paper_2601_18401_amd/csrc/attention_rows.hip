@@ -36,54 +36,55 @@ __global__ __launch_bounds__(256) void prefill_attention_rows_kernel(
     const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V,
     const int32_t* __restrict__ idx, T* __restrict__ O, float* __restrict__ LSE, int64_t Lq,
     int64_t q_pos0, int Hq, int G, int S, int A, int topk, float scale_log2e, int64_t qsh, int64_t qst,
-    int64_t kvsh, int64_t kvst) {
+    int64_t kvsh, int64_t kvst, const int* __restrict__ only_if) {
   // Anchors every A tokens, span j = the S tokens ending at (j+1)*A - 1 (A = S: the disjoint grid).
   // With A < S the spans of a row overlap: a span's range then starts behind the end of the
   // nearest lower span the row lists, so that every token of the union is attended once.
   using RL = RowLayout<T, D>;
   constexpr int EPL = RL::EPL, LPR = RL::LPR;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int64_t row = (int64_t)blockIdx.x * 4 + wave;
-  if (row >= (int64_t)Hq * Lq) return;
-  const int h = (int)(row / Lq);
-  const int64_t r = row % Lq, i = q_pos0 + r;
-  const int kv = h / G;
-  const int64_t c = i / A;
-  const int lr = lane % LPR;
-  float q2[EPL];
-  {
-    float qf[EPL];
-    Elem<T>::unpack(load16(Q + h * qsh + r * qst + lr * EPL), qf);
+  if (only_if && *only_if == 0) return;
+  for (int64_t row = (int64_t)blockIdx.x * 4 + wave; row < (int64_t)Hq * Lq; row += (int64_t)gridDim.x * 4) {
+    const int h = (int)(row / Lq);
+    const int64_t r = row % Lq, i = q_pos0 + r;
+    const int kv = h / G;
+    const int64_t c = i / A;
+    const int lr = lane % LPR;
+    float q2[EPL];
+    {
+      float qf[EPL];
+      Elem<T>::unpack(load16(Q + h * qsh + r * qst + lr * EPL), qf);
 #pragma unroll
-    for (int e = 0; e < EPL; ++e) q2[e] = qf[e] * scale_log2e;
-  }
-  const T* Kb = K + kv * kvsh;
-  const T* Vb = V + kv * kvsh;
-  AttendState<T, D> st;
-  st.init();
-  for (int slot = 0; slot < topk; ++slot) {
-    const int64_t j = idx[row * topk + slot];
-    if (j >= 0 && j < c) {
-      const int64_t end = (j + 1) * A;
-      int64_t begin = end - S > 0 ? end - S : 0;
-      if (A < S) {
-        for (int s2 = 0; s2 < topk; ++s2) {
-          const int64_t jj = idx[row * topk + s2];
-          if (jj >= 0 && jj < j && (jj + 1) * A > begin) begin = (jj + 1) * A;
-        }
-      }
-      attend_range<T, D, 4>(q2, Kb, Vb, kvst, begin, end, lane, st);
+      for (int e = 0; e < EPL; ++e) q2[e] = qf[e] * scale_log2e;
     }
-  }
-  attend_range<T, D, 4>(q2, Kb, Vb, kvst, c * A, i + 1, lane, st);
+    const T* Kb = K + kv * kvsh;
+    const T* Vb = V + kv * kvsh;
+    AttendState<T, D> st;
+    st.init();
+    for (int slot = 0; slot < topk; ++slot) {
+      const int64_t j = idx[row * topk + slot];
+      if (j >= 0 && j < c) {
+        const int64_t end = (j + 1) * A;
+        int64_t begin = end - S > 0 ? end - S : 0;
+        if (A < S) {
+          for (int s2 = 0; s2 < topk; ++s2) {
+            const int64_t jj = idx[row * topk + s2];
+            if (jj >= 0 && jj < j && (jj + 1) * A > begin) begin = (jj + 1) * A;
+          }
+        }
+        attend_range<T, D, 4>(q2, Kb, Vb, kvst, begin, end, lane, st);
+      }
+    }
+    attend_range<T, D, 4>(q2, Kb, Vb, kvst, c * A, i + 1, lane, st);
 
-  merge_row_groups<T, D>(st);
-  if (lane < LPR) {
-    const float inv = 1.f / st.l;  // the local window always holds the query's own token: l > 0
-    T* op = O + row * D + lr * EPL;
+    merge_row_groups<T, D>(st);
+    if (lane < LPR) {
+      const float inv = 1.f / st.l;  // the local window always holds the query's own token: l > 0
+      T* op = O + row * D + lr * EPL;
 #pragma unroll
-    for (int e = 0; e < EPL; ++e) Elem<T>::store1(op + e, st.o[e] * inv);
-    if (lane == 0) LSE[row] = (st.m + __log2f(st.l)) * kLn2;
+      for (int e = 0; e < EPL; ++e) Elem<T>::store1(op + e, st.o[e] * inv);
+      if (lane == 0) LSE[row] = (st.m + __log2f(st.l)) * kLn2;
+    }
   }
 }
 
@@ -97,62 +98,63 @@ __global__ __launch_bounds__(256) void prefill_combined_rows_kernel(
     const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V,
     const int32_t* __restrict__ idx, const float* __restrict__ gate, T* __restrict__ O, int64_t Lq,
     int64_t q_pos0, int Hq, int G, int S, int A, int topk, float scale_log2e, int64_t qsh, int64_t qst,
-    int64_t kvsh, int64_t kvst) {
+    int64_t kvsh, int64_t kvst, const int* __restrict__ only_if) {
   using RL = RowLayout<T, D>;
   constexpr int EPL = RL::EPL, LPR = RL::LPR;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int64_t row = (int64_t)blockIdx.x * 4 + wave;
-  if (row >= (int64_t)Hq * Lq) return;
-  const int h = (int)(row / Lq);
-  const int64_t r = row % Lq, i = q_pos0 + r;
-  const int kv = h / G;
-  const int64_t c = i / A;  // anchors every A tokens; every span has its own softmax: no clipping here
-  const int lr = lane % LPR;
-  float q2[EPL];
-  {
-    float qf[EPL];
-    Elem<T>::unpack(load16(Q + h * qsh + r * qst + lr * EPL), qf);
+  if (only_if && *only_if == 0) return;
+  for (int64_t row = (int64_t)blockIdx.x * 4 + wave; row < (int64_t)Hq * Lq; row += (int64_t)gridDim.x * 4) {
+    const int h = (int)(row / Lq);
+    const int64_t r = row % Lq, i = q_pos0 + r;
+    const int kv = h / G;
+    const int64_t c = i / A;  // anchors every A tokens; every span has its own softmax: no clipping here
+    const int lr = lane % LPR;
+    float q2[EPL];
+    {
+      float qf[EPL];
+      Elem<T>::unpack(load16(Q + h * qsh + r * qst + lr * EPL), qf);
 #pragma unroll
-    for (int e = 0; e < EPL; ++e) q2[e] = qf[e] * scale_log2e;
-  }
-  const T* Kb = K + kv * kvsh;
-  const T* Vb = V + kv * kvsh;
-  AttendState<T, D> win;
-  win.init();
-  attend_range<T, D, 4>(q2, Kb, Vb, kvst, c * A, i + 1, lane, win);
-  merge_row_groups<T, D>(win);  // the window always holds the query's own token: win.l > 0
+      for (int e = 0; e < EPL; ++e) q2[e] = qf[e] * scale_log2e;
+    }
+    const T* Kb = K + kv * kvsh;
+    const T* Vb = V + kv * kvsh;
+    AttendState<T, D> win;
+    win.init();
+    attend_range<T, D, 4>(q2, Kb, Vb, kvst, c * A, i + 1, lane, win);
+    merge_row_groups<T, D>(win);  // the window always holds the query's own token: win.l > 0
 
-  // gate: softmax of the scores of the valid slots
-  float smax = -INFINITY;
-  for (int slot = 0; slot < topk; ++slot) {
-    const int64_t j = idx[row * topk + slot];
-    if (j >= 0 && j < c) smax = fmaxf(smax, gate[row * topk + slot]);
-  }
-  float acc[EPL];
+    // gate: softmax of the scores of the valid slots
+    float smax = -INFINITY;
+    for (int slot = 0; slot < topk; ++slot) {
+      const int64_t j = idx[row * topk + slot];
+      if (j >= 0 && j < c) smax = fmaxf(smax, gate[row * topk + slot]);
+    }
+    float acc[EPL];
 #pragma unroll
-  for (int e = 0; e < EPL; ++e) acc[e] = 0.f;
-  float asum = 0.f;
-  for (int slot = 0; slot < topk; ++slot) {
-    const int64_t j = idx[row * topk + slot];
-    if (!(j >= 0 && j < c)) continue;
-    AttendState<T, D> st;
-    st.init();
-    attend_range<T, D, 4>(q2, Kb, Vb, kvst, (j + 1) * A - S > 0 ? (j + 1) * A - S : 0, (j + 1) * A, lane, st);
-    merge_row_groups<T, D>(st);
-    const float M = fmaxf(st.m, win.m);
-    const float wa = fast_exp2(st.m - M), wb = fast_exp2(win.m - M);
-    const float a = __expf(gate[row * topk + slot] - smax);
-    const float f = a / (st.l * wa + win.l * wb);
-    asum += a;
+    for (int e = 0; e < EPL; ++e) acc[e] = 0.f;
+    float asum = 0.f;
+    for (int slot = 0; slot < topk; ++slot) {
+      const int64_t j = idx[row * topk + slot];
+      if (!(j >= 0 && j < c)) continue;
+      AttendState<T, D> st;
+      st.init();
+      attend_range<T, D, 4>(q2, Kb, Vb, kvst, (j + 1) * A - S > 0 ? (j + 1) * A - S : 0, (j + 1) * A, lane, st);
+      merge_row_groups<T, D>(st);
+      const float M = fmaxf(st.m, win.m);
+      const float wa = fast_exp2(st.m - M), wb = fast_exp2(win.m - M);
+      const float a = __expf(gate[row * topk + slot] - smax);
+      const float f = a / (st.l * wa + win.l * wb);
+      asum += a;
 #pragma unroll
-    for (int e = 0; e < EPL; ++e) acc[e] = fmaf(f, st.o[e] * wa + win.o[e] * wb, acc[e]);
-  }
-  if (lane < LPR) {
-    T* op = O + row * D + lr * EPL;
-    const bool any = asum > 0.f;
-    const float inv = any ? 1.f / asum : 1.f / win.l;
+      for (int e = 0; e < EPL; ++e) acc[e] = fmaf(f, st.o[e] * wa + win.o[e] * wb, acc[e]);
+    }
+    if (lane < LPR) {
+      T* op = O + row * D + lr * EPL;
+      const bool any = asum > 0.f;
+      const float inv = any ? 1.f / asum : 1.f / win.l;
 #pragma unroll
-    for (int e = 0; e < EPL; ++e) Elem<T>::store1(op + e, (any ? acc[e] : win.o[e]) * inv);
+      for (int e = 0; e < EPL; ++e) Elem<T>::store1(op + e, (any ? acc[e] : win.o[e]) * inv);
+    }
   }
 }
 
@@ -250,23 +252,24 @@ sl_status launch_anchor_rows(const Problem& pb, int64_t window, int b, int f, in
 
 template <typename T, int D>
 sl_status launch_rows(const Problem& pb, const void* Q, const void* K, const void* V,
-                      const int32_t* idx, void* O, float* LSE, hipStream_t st) {
+                      const int32_t* idx, void* O, float* LSE, hipStream_t st, const int* only_if) {
   const int64_t rows = (int64_t)pb.Hq * pb.Lq;
+  // a conditional call, which nearly always ends at once, is a short grid that would loop over the rows
+  const int64_t blocks = (rows + 3) / 4;
+  const dim3 grid((unsigned)(only_if && blocks > 2048 ? 2048 : blocks));
   if (pb.prof_start) (void)hipEventRecord(pb.prof_start, st);
   if (pb.combined) {
-    hipLaunchKernelGGL((prefill_combined_rows_kernel<T, D>), dim3((unsigned)((rows + 3) / 4)),
-                       dim3(256), 0, st, static_cast<const T*>(Q), static_cast<const T*>(K),
+    hipLaunchKernelGGL((prefill_combined_rows_kernel<T, D>), grid, dim3(256), 0, st, static_cast<const T*>(Q), static_cast<const T*>(K),
                        static_cast<const T*>(V), idx, pb.gate, static_cast<T*>(O), pb.Lq, pb.q_pos0,
                        pb.Hq, pb.G, pb.S, pb.A, pb.topk, pb.scale * kLog2e, pb.qsh, pb.qst, pb.kvsh,
-                       pb.kvst);
+                       pb.kvst, only_if);
     if (pb.prof_stop) (void)hipEventRecord(pb.prof_stop, st);
     return hipGetLastError() == hipSuccess ? SL_OK : SL_ERR_LAUNCH;
   }
-  hipLaunchKernelGGL((prefill_attention_rows_kernel<T, D>), dim3((unsigned)((rows + 3) / 4)),
-                     dim3(256), 0, st, static_cast<const T*>(Q), static_cast<const T*>(K),
+  hipLaunchKernelGGL((prefill_attention_rows_kernel<T, D>), grid, dim3(256), 0, st, static_cast<const T*>(Q), static_cast<const T*>(K),
                      static_cast<const T*>(V), idx, static_cast<T*>(O), LSE, pb.Lq, pb.q_pos0,
                      pb.Hq, pb.G, pb.S, pb.A, pb.topk, pb.scale * kLog2e, pb.qsh, pb.qst, pb.kvsh,
-                     pb.kvst);
+                     pb.kvst, only_if);
   if (pb.prof_stop) (void)hipEventRecord(pb.prof_stop, st);
   return hipGetLastError() == hipSuccess ? SL_OK : SL_ERR_LAUNCH;
 }
@@ -274,13 +277,13 @@ sl_status launch_rows(const Problem& pb, const void* Q, const void* K, const voi
 }  // namespace
 
 sl_status prefill_attention_rows(const Problem& pb, const void* Q, const void* K, const void* V,
-                                 const int32_t* idx, void* O, float* LSE, hipStream_t st) {
+                                 const int32_t* idx, void* O, float* LSE, hipStream_t st, const int* only_if) {
   if (pb.dtype == SL_BF16) {
-    if (pb.D == 128) return launch_rows<bf16_t, 128>(pb, Q, K, V, idx, O, LSE, st);
-    return launch_rows<bf16_t, 64>(pb, Q, K, V, idx, O, LSE, st);
+    if (pb.D == 128) return launch_rows<bf16_t, 128>(pb, Q, K, V, idx, O, LSE, st, only_if);
+    return launch_rows<bf16_t, 64>(pb, Q, K, V, idx, O, LSE, st, only_if);
   }
-  if (pb.D == 128) return launch_rows<float, 128>(pb, Q, K, V, idx, O, LSE, st);
-  return launch_rows<float, 64>(pb, Q, K, V, idx, O, LSE, st);
+  if (pb.D == 128) return launch_rows<float, 128>(pb, Q, K, V, idx, O, LSE, st, only_if);
+  return launch_rows<float, 64>(pb, Q, K, V, idx, O, LSE, st, only_if);
 }
 
 sl_status anchor_attention_prefill(const Problem& pb, int64_t window, int b, int f, int root,

@@ -71,9 +71,10 @@ sl_status prefill_search(const Problem& pb, const void* Qs, const void* K, const
 sl_status prefill_search_rows(const Problem& pb, const void* Qs, const void* K, const void* Ks,
                               int32_t* idx, float* scores, hipStream_t st);
 
-// a4 .. a6, row-stationary form
+// a4 .. a6, row-stationary form (only_if: the kernel does nothing where that device word is 0)
 sl_status prefill_attention_rows(const Problem& pb, const void* Q, const void* K, const void* V,
-                                 const int32_t* idx, void* O, float* LSE, hipStream_t st);
+                                 const int32_t* idx, void* O, float* LSE, hipStream_t st,
+                                 const int* only_if = nullptr);
 
 // a1 + a2 on the matrix cores (bf16, D = 128)
 bool prefill_search_mfma_supported(const Problem& pb);
@@ -86,7 +87,15 @@ size_t prefill_attention_mfma_ws_bytes(const Problem& pb);
 sl_status prefill_attention_mfma(const Problem& pb, const void* Q, const void* K, const void* V,
                                  const int32_t* idx, void* O, float* LSE, void* ws, hipStream_t st);
 
-// a3 .. a6: prefill span-attention
+// a3 .. a6 on the matrix cores with fp32 softmax weights and partials (bf16, any span length, D = 64 or 128)
+bool prefill_attention_fine_supported(const Problem& pb);
+size_t prefill_attention_fine_ws_bytes(const Problem& pb);
+sl_status prefill_attention_fine(const Problem& pb, const void* Q, const void* K, const void* V,
+                                 const int32_t* idx, void* O, float* LSE, void* ws, hipStream_t st);
+
+// a3 .. a6: prefill span-attention.  Where the workspace is optional (no matrix-core form, or the one with
+// fp32 weights), ws may be NULL.
+bool prefill_attention_ws_optional(const Problem& pb);
 size_t prefill_attention_ws_bytes(const Problem& pb);
 sl_status prefill_attention(const Problem& pb, const void* Q, const void* K, const void* V,
                             const int32_t* idx, void* O, float* LSE, void* ws, hipStream_t st);

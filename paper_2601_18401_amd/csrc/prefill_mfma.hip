@@ -40,7 +40,7 @@ typedef float f32x8 __attribute__((ext_vector_type(8)));
 
 constexpr int TG = 128;            // rows of one wavefront group (4 wavefronts x 32 columns)
 constexpr int TN = 64;             // kv positions per staged tile
-constexpr int HD = 128;            // head dimension of this path
+constexpr int HD = 128;            // head dimension of the kernels with bf16 weights
 
 // LDS of the flash kernels (dynamic).  Main loop: stages of the V tile and of the K tile, filled
 // by direct global->LDS loads (16 bytes per lane, a wavefront instruction fills 1 KB
@@ -63,15 +63,19 @@ constexpr int HD = 128;            // head dimension of this path
 //   NG = 1 (local window, 256 threads, 128 rows, 67072 bytes: two workgroups per compute unit, so
 //     one's epilogue runs beside the other's main loop): two stages each; the output region
 //     lies over the V stages, which are dead by then.
-constexpr int kStageElems = TN * HD;  // 8192 bf16 = 16 KB
-template <int NG>
+//   fp32-weight kernels: a wavefront's 32 rows go out in fp32, 64 columns at a time, through a slice of the
+//     same size (32 x 64 fp32 = 32 x 128 bf16); at D = 64 the V stages are too small to lie under it.
+template <int NG, int D = HD>
 struct FlashLds {
+  static constexpr int kStageElems = TN * D;  // D = 128: 8192 bf16 = 16 KB
   static constexpr int kStagesK = 2, kStagesV = NG == 2 ? 3 : 2;
   static constexpr int kV = 0;
   static constexpr int kK = kStagesV * kStageElems * 2;
   static constexpr int kStagesEnd = (kStagesV + kStagesK) * kStageElems * 2;
-  static constexpr int kOut = NG == 2 ? kStagesEnd : 0;                             // bf16[NG][TG][HD]
-  static constexpr int kRowOut = NG == 2 ? kOut + NG * TG * HD * 2 : kStagesEnd;    // int64[NG][TG]
+  static constexpr bool kOver = NG == 1 && D == 128;  // the output region lies over the V stages
+  static constexpr int kOutBytes = NG * TG * 256;
+  static constexpr int kOut = kOver ? 0 : kStagesEnd;                               // [NG][TG][256 bytes]
+  static constexpr int kRowOut = kOver ? kStagesEnd : kOut + kOutBytes;             // int64[NG][TG]
   static constexpr int kRowLse = kRowOut + NG * TG * 8;                             // float[NG][TG]
   // NG = 2: per wavefront 256 bytes for the next tile's record and 256 for its items, fetched by
   // direct global->LDS loads while the current tile runs (they hold no registers meanwhile)
@@ -79,7 +83,7 @@ struct FlashLds {
   static constexpr int kBytes = kAhead + (NG == 2 ? 8 * 512 : 0);
   static constexpr int kThreads = NG * 256;
   static constexpr int kRows = NG * TG;  // query rows per workgroup
-  static constexpr int kBlocksPerWave = 16 / (4 * NG);  // 1 KB blocks of a staged tile per wavefront
+  static constexpr int kBlocksPerWave = kStageElems * 2 / 1024 / (4 * NG);  // 1 KB blocks of a staged tile per wavefront
 };
 constexpr int TM = FlashLds<2>::kRows;  // rows of a routed tile
 
@@ -101,12 +105,13 @@ __device__ __forceinline__ int64_t uniform64(int64_t v) {
 }
 
 // Two transposing LDS reads: the lane's column of kv rows 0..3 and 4..7 behind p (its own block address).
+template <int D>
 __device__ __forceinline__ bf16x8 transposed8(const bf16_t* p) {
   typedef short s16x4 __attribute__((ext_vector_type(4)));
   typedef short s16x8 __attribute__((ext_vector_type(8)));
   typedef __attribute__((address_space(3))) s16x4* LdsPtr;
   const s16x4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LdsPtr)p);
-  const s16x4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LdsPtr)(p + 4 * HD));
+  const s16x4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LdsPtr)(p + 4 * D));
   return __builtin_bit_cast(bf16x8, __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7));
 }
 
@@ -322,22 +327,24 @@ __global__ __launch_bounds__(1024) void bucket_unit_scan_kernel(int* __restrict_
 }
 
 // One workgroup: exclusive scans of the item counts and of the tile counts over the B buckets.
-// item_off[B] / tile_off[B] receive the totals.  The item list is laid out tile by tile, TM
-// entries per tile (a bucket's last tile is padded), so that the items of tile t start at t*TM
-// whatever its record says: cursor[b] = tile_off[b] * TM for the fill pass.
+// item_off[B] / tile_off[B] receive the totals.  The item list is laid out tile by tile, tm
+// entries per tile (a bucket's last tile is padded), so that the items of tile t start at t*tm
+// whatever its record says: cursor[b] = tile_off[b] * tm for the fill pass.
 __global__ __launch_bounds__(1024) void bucket_scan_kernel(const int* __restrict__ g_count,
                                                            int* __restrict__ item_off,
                                                            int* __restrict__ tile_off,
-                                                           int* __restrict__ g_cursor, int B) {
+                                                           int* __restrict__ g_cursor, int B, int tm,
+                                                           int* __restrict__ flag) {
   __shared__ int s_items[1024], s_tiles[1024];
   const int tid = threadIdx.x;
+  if (flag && tid == 0) *flag = 0;
   const int per = (B + 1023) / 1024;
   const int b0 = tid * per, b1 = min(B, b0 + per);
   int ni = 0, nt = 0;
   for (int b = b0; b < b1; ++b) {
     const int cnt = g_count[b];
     ni += cnt;
-    nt += (cnt + TM - 1) / TM;
+    nt += (cnt + tm - 1) / tm;
   }
   s_items[tid] = ni;
   s_tiles[tid] = nt;
@@ -355,9 +362,9 @@ __global__ __launch_bounds__(1024) void bucket_scan_kernel(const int* __restrict
     const int cnt = g_count[b];
     item_off[b] = io;
     tile_off[b] = to;
-    g_cursor[b] = to * TM;
+    g_cursor[b] = to * tm;
     io += cnt;
-    to += (cnt + TM - 1) / TM;
+    to += (cnt + tm - 1) / tm;
   }
   if (tid == 1023) {
     item_off[B] = s_items[1023];
@@ -366,21 +373,21 @@ __global__ __launch_bounds__(1024) void bucket_scan_kernel(const int* __restrict
 }
 
 // One workgroup per bucket writes the record of each of its tiles,
-// {bucket, first item = t*TM, number of items (1..TM), unused}, and fills the padding of the
+// {bucket, first item = t*tm, number of items (1..tm), unused}, and fills the padding of the
 // bucket's last tile with item 0 (row 0, slot 0 of the kv head's first query head: a valid row to
 // read, whose result the flash kernel drops because the lane lies beyond the tile's item count).
 __global__ __launch_bounds__(256) void bucket_tiles_kernel(const int* __restrict__ tile_off,
                                                            const int* __restrict__ item_off,
                                                            int4* __restrict__ tile_info,
-                                                           int* __restrict__ items) {
+                                                           int* __restrict__ items, int tm) {
   const int b = blockIdx.x;
   const int t0 = tile_off[b], t1 = tile_off[b + 1];
   const int cnt = item_off[b + 1] - item_off[b];
   for (int t = t0 + threadIdx.x; t < t1; t += 256)
-    tile_info[t] = make_int4(b, t * TM, min(TM, cnt - (t - t0) * TM), 0);
+    tile_info[t] = make_int4(b, t * tm, min(tm, cnt - (t - t0) * tm), 0);
   if (t1 > t0) {
-    const int last = cnt - (t1 - 1 - t0) * TM;  // items of the last tile, 1..TM
-    for (int e = last + threadIdx.x; e < TM; e += 256) items[(int64_t)(t1 - 1) * TM + e] = 0;
+    const int last = cnt - (t1 - 1 - t0) * tm;  // items of the last tile, 1..tm
+    for (int e = last + threadIdx.x; e < tm; e += 256) items[(int64_t)(t1 - 1) * tm + e] = 0;
   }
 }
 
@@ -395,7 +402,8 @@ struct FlashArgs {
   const int* tile_off;
   const int4* tile_info;
   const int* items;
-  bf16_t* part_o;
+  bf16_t* part_o;   // bf16 partials
+  float* part_of;   // fp32 partials (fp32-weight kernels)
   float* part_lse;
   // local + merge
   bf16_t* O;
@@ -409,6 +417,7 @@ struct FlashArgs {
   // [e*E, (e+1)*E), E a multiple of 64 (the key-block bucketing of Section 4.3); n = ceil(L / E).
   int64_t window;
   int ab, af, aroot, E;
+  int clip;  // fp32-weight kernels: overlapping spans in one joint softmax
   float scale_log2e;
   int64_t qsh, qst, kvsh, kvst;
 };
@@ -421,6 +430,17 @@ __device__ __forceinline__ ArgsPtr args_anew() {
   ArgsPtr p = (ArgsPtr)__builtin_amdgcn_kernarg_segment_ptr();
   asm volatile("" : "+s"(p));
   return p;
+}
+
+// Swizzle keys of the staged rows: the 16-byte pieces of the rows that 16 lanes read together fall into
+// distinct bank groups (D = 64: two rows share 256 bytes).
+template <int D>
+__device__ __forceinline__ int k_swizzle(int row) {
+  return D == 128 ? row & 15 : (row >> 1) & 7;
+}
+template <int D>
+__device__ __forceinline__ int v_swizzle(int row) {
+  return D == 128 ? (row & 3) << 2 : ((row >> 1) & 1) << 2;
 }
 
 __device__ __forceinline__ int perm_row(int rho) {
@@ -504,7 +524,12 @@ __device__ __forceinline__ void flush_routed_output(char* lds, int grp, int w4, 
 // When the kv loop is over, the first K/V stage and the Q fragments of the next tile are
 // requested before the output tile is normalised and staged in LDS; a routed tile's staged
 // output goes to HBM during the next tile's first kv step (c.pending), a window tile's at once.
-template <int NG, bool LOCAL, bool FUSED, bool CLIP, typename RequestNext, typename DescribeNext>
+//
+// FINE: the softmax weights keep fp32 precision: each is split into two bf16 parts (16 bits of mantissa
+// between them) and V is multiplied with both; the row sum is taken over the unsplit weights, partials are
+// written in fp32, and the output of a tile goes to HBM before the next one starts.
+template <int NG, bool LOCAL, bool FUSED, bool CLIP, int D = HD, bool FINE = false, typename RequestNext,
+          typename DescribeNext>
 __device__ __forceinline__ void flash_tile(const FlashArgs& a, char* lds, const TileDesc& cur,
                                            TileDesc& next, bool has_next, RequestNext&& request_next,
                                            DescribeNext&& describe_next, FlashCarry& c) {
@@ -514,28 +539,33 @@ __device__ __forceinline__ void flash_tile(const FlashArgs& a, char* lds, const 
   const int qc = lane & 31, hf = lane >> 5;
   const int srow = w4 * 32 + qc;             // row inside the group's 128-row half tile
   constexpr bool kMasked = LOCAL || CLIP;
-  using Lds = FlashLds<NG>;
+  using Lds = FlashLds<NG, D>;
+  constexpr int kStageElems = Lds::kStageElems;
+  constexpr int PPR = D / 8, RPB = 64 / PPR;  // 16-byte pieces per staged row, rows per 1 KB block
+  constexpr int NDT = D / 32, NKK = D / 16;   // 32-row output tiles, 16-deep steps of the QK product
   constexpr int kStagesK = Lds::kStagesK, kStagesV = Lds::kStagesV, BPW = Lds::kBlocksPerWave;
   bf16_t* const ldsV = reinterpret_cast<bf16_t*>(lds + Lds::kV);
   bf16_t* const ldsK = reinterpret_cast<bf16_t*>(lds + Lds::kK);
 
-  // Direct global -> LDS staging of one (K, V) tile pair in 1 KB blocks (4 rows each); lane L of a
-  // block lands at byte 16*L.
+  // Direct global -> LDS staging of one (K, V) tile pair in 1 KB blocks (4 rows each at D = 128); lane L
+  // of a block lands at byte 16*L.
   // Per-lane byte offsets are loop-invariant 32-bit values; the kv head and the tile position
   // go into the wave-uniform base pointer.
   uint32_t koff[BPW], voff[BPW];
 #pragma unroll
   for (int i = 0; i < BPW; ++i) {
-    const int row = (wave * BPW + i) * 4 + (lane >> 4), pc = lane & 15;
-    koff[i] = (uint32_t)((row * a.kvst + (pc ^ (row & 15)) * 8) * sizeof(bf16_t));
-    voff[i] = (uint32_t)((row * a.kvst + (pc ^ ((row & 3) << 2)) * 8) * sizeof(bf16_t));
+    const int row = (wave * BPW + i) * RPB + lane / PPR, pc = lane % PPR;
+    koff[i] = (uint32_t)((row * a.kvst + (pc ^ k_swizzle<D>(row)) * 8) * sizeof(bf16_t));
+    voff[i] = (uint32_t)((row * a.kvst + (pc ^ v_swizzle<D>(row)) * 8) * sizeof(bf16_t));
   }
   // wavefront w fills blocks w*BPW .. w*BPW + BPW-1 of both tiles
-  auto stage = [&](int kvh, int64_t t0, int kb, int vb) {
-    // rows past the end of the sequence lie beyond the buffer: zeros in LDS (masked later)
-    const int rows = __builtin_amdgcn_readfirstlane(a.L - t0 < TN ? (int)(a.L - t0) : TN);
+  auto stage = [&](int kvh, int64_t t0, int64_t t_end, int kb, int vb) {
+    // rows past the end of the sequence (FINE: of the tile's range) lie beyond the buffer: zeros in LDS
+    // (masked later)
+    const int64_t stop = FINE ? t_end : a.L;
+    const int rows = __builtin_amdgcn_readfirstlane(stop - t0 < TN ? (int)(stop - t0) : TN);
     const int64_t first = uniform64((int64_t)kvh * a.kvsh + t0 * a.kvst);
-    const uint32_t bytes = (uint32_t)(((rows - 1) * a.kvst + HD) * sizeof(bf16_t));
+    const uint32_t bytes = (uint32_t)(((rows - 1) * a.kvst + D) * sizeof(bf16_t));
     const BufferRsrc kr = buffer_of(a.K + first, bytes), vr = buffer_of(a.V + first, bytes);
 #pragma unroll
     for (int i = 0; i < BPW; ++i)
@@ -550,16 +580,16 @@ __device__ __forceinline__ void flash_tile(const FlashArgs& a, char* lds, const 
   auto load_q = [&](int64_t q_off) {
     const bf16_t* qp = a.Q + q_off;
 #pragma unroll
-    for (int kk = 0; kk < 8; ++kk) c.qf[kk] = *reinterpret_cast<const bf16x8*>(qp + kk * 16 + hf * 8);
+    for (int kk = 0; kk < NKK; ++kk) c.qf[kk] = *reinterpret_cast<const bf16x8*>(qp + kk * 16 + hf * 8);
   };
   if (!c.primed) {
-    stage(cur.kv, cur.kv_begin, c.kb, c.vb);
+    stage(cur.kv, cur.kv_begin, cur.kv_end, c.kb, c.vb);
     load_q(cur.q_off);
   }
 
-  f32x16 o[4];
+  f32x16 o[NDT];
 #pragma unroll
-  for (int dt = 0; dt < 4; ++dt)
+  for (int dt = 0; dt < NDT; ++dt)
 #pragma unroll
     for (int r = 0; r < 16; ++r) o[dt][r] = 0.f;
   float m = -INFINITY, l = 0.f;  // m in log2 units of the scaled logit
@@ -568,17 +598,18 @@ __device__ __forceinline__ void flash_tile(const FlashArgs& a, char* lds, const 
   for (int ks = 0; ks < 4; ++ks)
 #pragma unroll
     for (int e = 0; e < 8; ++e) pb[ks][e] = (__bf16)0.f;
+  bf16x8 pl[FINE ? 4 : 1];       // FINE: what pb leaves of the weights
 
   const int krow = perm_row(qc);
-  const int kswz = krow & 15;      // swizzle key of this lane's K rows (32*sub does not change it)
+  const int kswz = k_swizzle<D>(krow);  // swizzle key of this lane's K rows (32*sub does not change it)
   // V^T fragments come from transposing reads: 16 lanes read a [4 kv][16 d] block, 8 bytes each, and lane
   // i of them receives column i.  Lane offset (elements) of the block for d tile dt, kv rows 8*hf .. 8*hf+3.
   const int vrow = (lane & 15) >> 2;
-  int vlane[4];
+  int vlane[NDT];
 #pragma unroll
-  for (int dt = 0; dt < 4; ++dt)
-    vlane[dt] = (8 * hf + vrow) * HD + (((4 * dt + 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1)) ^ (vrow << 2)) << 3) +
-                4 * (lane & 1);
+  for (int dt = 0; dt < NDT; ++dt)
+    vlane[dt] = (8 * hf + vrow) * D +
+                (((4 * dt + 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1)) ^ v_swizzle<D>(vrow)) << 3) + 4 * (lane & 1);
   const float sc = a.scale_log2e;
   // the lane's own range [lo_q, i_q] as 32-bit offsets from the tile's first token
   auto offset_of = [&](int64_t t) {
@@ -597,16 +628,16 @@ __device__ __forceinline__ void flash_tile(const FlashArgs& a, char* lds, const 
 #pragma unroll
       for (int r = 0; r < 16; ++r) s[sub][r] = 0.f;
 #pragma unroll
-    for (int kk = 0; kk < 8; ++kk)
+    for (int kk = 0; kk < NKK; ++kk)
 #pragma unroll
       for (int sub = 0; sub < 2; ++sub) {
         const bf16x8 ka = *reinterpret_cast<const bf16x8*>(
-            &kt[(32 * sub + krow) * HD + (((2 * kk + hf) ^ kswz) << 3)]);
+            &kt[(32 * sub + krow) * D + (((2 * kk + hf) ^ kswz) << 3)]);
         s[sub] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka, c.qf[kk], s[sub], 0, 0, 0);
       }
     __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
 #pragma unroll
-    for (int i = 0; i < 12; ++i) {
+    for (int i = 0; i < 2 * NKK - 4; ++i) {
       __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
       __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
     }
@@ -643,7 +674,7 @@ __device__ __forceinline__ void flash_tile(const FlashArgs& a, char* lds, const 
       m = grow ? mx : m;
       l *= alpha;
 #pragma unroll
-      for (int dt = 0; dt < 4; ++dt)
+      for (int dt = 0; dt < NDT; ++dt)
 #pragma unroll
         for (int r = 0; r < 16; ++r) o[dt][r] *= alpha;
     }
@@ -654,6 +685,12 @@ __device__ __forceinline__ void flash_tile(const FlashArgs& a, char* lds, const 
 #pragma unroll
       for (int e = 0; e < 8; ++e) p[e] = fast_exp2(fmaf(s[ks >> 1][8 * (ks & 1) + e], sc, nm));
       pb[ks] = __builtin_convertvector(p, bf16x8);
+      if constexpr (FINE) {
+        pl[ks] = __builtin_convertvector(p - __builtin_convertvector(pb[ks], f32x8), bf16x8);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) l += p[e];
+        continue;
+      }
       // the row sum is taken over the rounded weights, the ones the PV product uses
 #pragma unroll
       for (int e = 0; e < 8; e += 2) {
@@ -670,17 +707,19 @@ __device__ __forceinline__ void flash_tile(const FlashArgs& a, char* lds, const 
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks)
 #pragma unroll
-      for (int dt = 0; dt < 4; ++dt) {
-        const bf16x8 va = transposed8(vt + vlane[dt] + 16 * ks * HD);
+      for (int dt = 0; dt < NDT; ++dt) {
+        const bf16x8 va = transposed8<D>(vt + vlane[dt] + 16 * ks * D);
         o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, pb[ks], o[dt], 0, 0, 0);
+        if constexpr (FINE) o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, pl[ks], o[dt], 0, 0, 0);
       }
+    constexpr int kPer = FINE ? 2 : 1;  // MFMAs per fragment
     __builtin_amdgcn_sched_group_barrier(0x100, 8, 1);
 #pragma unroll
-    for (int i = 0; i < 12; ++i) {
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 1);
+    for (int i = 0; i < 4 * NDT - 4; ++i) {
+      __builtin_amdgcn_sched_group_barrier(0x008, kPer, 1);
       __builtin_amdgcn_sched_group_barrier(0x100, 2, 1);
     }
-    __builtin_amdgcn_sched_group_barrier(0x008, 4, 1);
+    __builtin_amdgcn_sched_group_barrier(0x008, 4 * kPer, 1);
   };
 
   // a kv tile that none of the wavefront's rows attends is passed over (its weights would all be 0)
@@ -696,13 +735,13 @@ __device__ __forceinline__ void flash_tile(const FlashArgs& a, char* lds, const 
     __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
     __syncthreads();
     const int kb1 = kb == kStagesK - 1 ? 0 : kb + 1, vb1 = vb == kStagesV - 1 ? 0 : vb + 1;
-    if (NG == 2 && !LOCAL && c.pending) {
+    if (NG == 2 && !LOCAL && !FINE && c.pending) {
       // the previous tile's output: written out here, a step after it was staged, so that the wait
       // at the top of this tile did not have to cover its stores
       flush_routed_output(lds, grp, w4, lane);
       c.pending = false;
     }
-    if (t0 + TN < cur.kv_end) stage(cur.kv, t0 + TN, kb1, vb1);
+    if (t0 + TN < cur.kv_end) stage(cur.kv, t0 + TN, cur.kv_end, kb1, vb1);
     if (NG == 2 && has_next && t0 == cur.kv_begin) request_next();
     const int base = (int)(t0 - cur.kv_begin);
     const bool mine = attends(base);
@@ -729,7 +768,7 @@ __device__ __forceinline__ void flash_tile(const FlashArgs& a, char* lds, const 
   c.primed = NG == 2 && has_next;  // NG = 1: the output region lies over the stages, nothing is fetched ahead
   if (NG == 2 && has_next) {
     next = describe_next();
-    stage(next.kv, next.kv_begin, kb, vb);
+    stage(next.kv, next.kv_begin, next.kv_end, kb, vb);
     load_q(next.q_off);
   }
   // From here to the end of the tile the late group is the critical path (it still owes a PV):
@@ -743,15 +782,47 @@ __device__ __forceinline__ void flash_tile(const FlashArgs& a, char* lds, const 
   // issue order, so the reads below see the writes of the other lanes.
   const float lt = pair_sum(l);
   const float inv = 1.f / lt;
-  bf16_t* const ost = reinterpret_cast<bf16_t*>(lds + Lds::kOut) + grp * TG * HD;
+  bf16_t* const ost = reinterpret_cast<bf16_t*>(lds + Lds::kOut) + grp * TG * HD;  // 256 bytes per row
   int64_t* const row_out = reinterpret_cast<int64_t*>(lds + Lds::kRowOut) + grp * TG;
   float* const row_lse = reinterpret_cast<float*>(lds + Lds::kRowLse) + grp * TG;
   if (hf == 0) {
     row_lse[srow] = (m + __log2f(lt)) * kLn2;
     row_out[srow] = cur.row_out;
   }
+  if constexpr (FINE) {
+    // fp32 partial, 64 columns at a time: 16 lanes per row, 16 bytes per lane
+    float* const fst = reinterpret_cast<float*>(ost);
+    const ArgsPtr b = args_anew();
+    const int piece = lane & 15;
 #pragma unroll
-  for (int dt = 0; dt < 4; ++dt)
+    for (int half = 0; half < D / 64; ++half) {
+#pragma unroll
+      for (int dd = 0; dd < 2; ++dd)
+#pragma unroll
+        for (int g4 = 0; g4 < 4; ++g4) {
+          f32x4 v;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) v[e] = o[2 * half + dd][4 * g4 + e] * inv;
+          *reinterpret_cast<f32x4*>(&fst[srow * 64 + (((8 * dd + 2 * g4 + hf) ^ (srow & 15)) << 2)]) = v;
+        }
+      __builtin_amdgcn_wave_barrier();
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const int row = w4 * 32 + u * 4 + (lane >> 4);
+        const int64_t at = row_out[row];
+        const uint4 v = *reinterpret_cast<const uint4*>(&fst[row * 64 + ((piece ^ (row & 15)) << 2)]);
+        if (at >= 0) {
+          *reinterpret_cast<uint4*>(b->part_of + at * D + half * 64 + piece * 4) = v;
+          if (half == 0 && piece == 0) b->part_lse[at] = row_lse[row];
+        }
+      }
+      __builtin_amdgcn_wave_barrier();
+    }
+    __builtin_amdgcn_s_setprio(0);
+    return;
+  }
+#pragma unroll
+  for (int dt = 0; dt < NDT; ++dt)
 #pragma unroll
     for (int g4 = 0; g4 < 4; ++g4) {
       const int unit = (4 * dt + g4) ^ (srow & 15);
@@ -872,8 +943,13 @@ __device__ __forceinline__ void flash_tile(const FlashArgs& a, char* lds, const 
 // of a workgroup's next tile are fetched while its current tile is computed.
 // CLIP (overlapping spans, anchor spacing A < S, joint softmax): a row's range in span j starts behind
 // the end of the nearest lower span that the row lists, so that every token of the union counts once.
-template <bool CLIP>
-__global__ __launch_bounds__(FlashLds<2>::kThreads, 1) void span_flash_routed_kernel(const FlashArgs a) {
+// FINE (with CLIP): fp32 weights and partials, spans of any length at any offset; a row's range is its whole
+// span unless a->clip says that spans of a row overlap in one softmax.
+template <bool CLIP, int NG = 2, int D = HD, bool FINE = false>
+__global__ __launch_bounds__(NG * 256, NG == 2 ? 1 : 2) void span_flash_routed_kernel(
+    const FlashArgs a) {
+  using Lds = FlashLds<NG, D>;
+  constexpr int TM = Lds::kRows;
   extern __shared__ __align__(16) char lds[];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int qrow = (wave >> 2) * TG + (wave & 3) * 32 + (lane & 31);
@@ -897,9 +973,9 @@ __global__ __launch_bounds__(FlashLds<2>::kThreads, 1) void span_flash_routed_ke
     const int h = d.kv * a->G + hl;
     d.q_off = h * a->qsh + r * a->qst;
     d.row_out = qrow < info.z ? ((int64_t)h * a->Lq + r) * (a->topk + 1) + slot : -1;
-    d.i_q = d.kv_end;
-    d.lo_q = 0;
-    if (CLIP) {
+    d.i_q = d.kv_end - 1;
+    d.lo_q = d.kv_begin;
+    if (FINE ? a->clip : CLIP) {
       const int64_t c = (a->q_pos0 + r) / a->A;
       const int32_t* irow = a->idx + ((int64_t)h * a->Lq + r) * a->topk;
       for (int s2 = 0; s2 < a->topk; ++s2) {
@@ -917,13 +993,22 @@ __global__ __launch_bounds__(FlashLds<2>::kThreads, 1) void span_flash_routed_ke
   // The record and the items of a workgroup's next tile are requested during the current tile's
   // first kv step as direct global->LDS loads into the wavefront's own 512 bytes (the items of tile t sit
   // at t*TM, so the two do not depend on each other) and read back at its tail.
-  int* const ahead = reinterpret_cast<int*>(lds + FlashLds<2>::kAhead) + __builtin_amdgcn_readfirstlane(wave) * 128;
+  if constexpr (NG == 1) {
+    // two workgroups per compute unit: one's tile ends run beside the other's kv loop
+    for (int64_t t = t_begin; t < t_end; t += NWL) {
+      TileDesc cur = describe(a.tile_info[t], a.items[t * TM + qrow]), unused = cur;
+      flash_tile<1, false, false, CLIP, D, FINE>(a, lds, cur, unused, false, [] {}, [&] { return cur; }, carry);
+      __syncthreads();  // the next tile's stages lie over the output slices of all wavefronts
+    }
+    return;
+  }
+  int* const ahead = reinterpret_cast<int*>(lds + Lds::kAhead) + __builtin_amdgcn_readfirstlane(wave) * 128;
   const int4 info0 = a.tile_info[t_begin];
   TileDesc cur = describe(info0, a.items[t_begin * TM + qrow]);
   for (int64_t t = t_begin; t < t_end; t += NWL) {
     const bool has_next = t + NWL < t_end;
     TileDesc nxt = cur;
-    flash_tile<2, false, false, CLIP>(
+    flash_tile<NG, false, false, CLIP, D, FINE>(
         a, lds, cur, nxt, has_next,
         [&] {
           const ArgsPtr a = args_anew();
@@ -941,7 +1026,7 @@ __global__ __launch_bounds__(FlashLds<2>::kThreads, 1) void span_flash_routed_ke
     cur = nxt;
   }
   // the last tile's output (its epilogue ended with the wavefront's own LDS writes)
-  if (carry.pending) flush_routed_output(lds, wave >> 2, wave & 3, lane);
+  if (!FINE && carry.pending) flush_routed_output(lds, wave >> 2, wave & 3, lane);
 }
 
 // The paper's geometry: routed tiles of a (kv head, end block) bucket.  Every row of a tile has
@@ -1061,7 +1146,7 @@ inline unsigned local_grid(int64_t Lq, int S, int Hkv, int G) {
 // FUSED = true (joint softmax, topk <= 8): merges the row's routed partials in the epilogue and
 // writes the final output, which takes the merge's HBM traffic off the critical path of a
 // separate kernel and saves the window partial's round trip.
-template <bool FUSED>
+template <bool FUSED, int D = HD, bool FINE = false>
 __global__ __launch_bounds__(FlashLds<1>::kThreads, 2) void span_flash_local_kernel(const FlashArgs a) {
   extern __shared__ __align__(16) char lds[];
   constexpr int TML = FlashLds<1>::kRows;
@@ -1101,33 +1186,56 @@ __global__ __launch_bounds__(FlashLds<1>::kThreads, 2) void span_flash_local_ker
     d.lo_q = (d.i_q / a.A) * a.A;
     d.kv_begin = (i_first / a.A) * a.A;
   }
-  d.kv_end = d.kv_begin + ((i_last - d.kv_begin) / TN + 1) * TN;
+  d.kv_end = FINE ? i_last + 1 : d.kv_begin + ((i_last - d.kv_begin) / TN + 1) * TN;
   FlashCarry carry;
   carry.kb = carry.vb = 0;
   carry.primed = false;
   carry.pending = false;
   TileDesc unused = d;
-  flash_tile<1, true, FUSED, false>(a, lds, d, unused, false, [] {}, [&] { return d; }, carry);
+  flash_tile<1, true, FUSED, false, D, FINE>(a, lds, d, unused, false, [] {}, [&] { return d; }, carry);
 }
 
 // ------------------------------------------------------------------ merge
+// A lane's 16 bytes of a partial: 8 bf16 (P = bf16_t) or 4 fp32 (P = float) columns.
+template <typename P>
+__device__ __forceinline__ void store_columns(bf16_t* p, const float* v) {
+  uint32_t w[Elem<P>::EPL / 2];
+#pragma unroll
+  for (int e = 0; e < Elem<P>::EPL / 2; ++e)
+    w[e] = (uint32_t)f32_to_bf16(v[2 * e]) | ((uint32_t)f32_to_bf16(v[2 * e + 1]) << 16);
+  if constexpr (Elem<P>::EPL == 8) *reinterpret_cast<uint4*>(p) = make_uint4(w[0], w[1], w[2], w[3]);
+  else *reinterpret_cast<uint2*>(p) = make_uint2(w[0], w[1]);
+}
+
+// fp32 partials: an output that is not finite marks the call (see rerun_flag).
+template <typename P>
+__device__ __forceinline__ void mark_not_finite(const float* v, int* flag) {
+  if constexpr (Elem<P>::EPL == 4) {
+    bool bad = false;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) bad = bad || !(fabsf(v[e]) < INFINITY);
+    if (bad) *flag = 1;
+  }
+}
+
 // Log-sum-exp merge of a row's partials: up to topk routed slots plus the local window (slot
-// topk).  16 lanes per row, 16 bytes per lane; every load of a lane is issued before the first
-// dependent use, so the kernel streams at HBM rate.
-template <int KMAX>
+// topk).  16 bytes per lane, D * sizeof(P) / 16 lanes per row; every load of a lane is issued before the
+// first dependent use, so the kernel streams at HBM rate.
+template <int KMAX, typename P = bf16_t, int D = HD>
 __global__ __launch_bounds__(256) void merge_partials_kernel(
-    const int32_t* __restrict__ idx, const bf16_t* __restrict__ part_o,
+    const int32_t* __restrict__ idx, const P* __restrict__ part_o,
     const float* __restrict__ part_lse, bf16_t* __restrict__ O, float* __restrict__ LSE,
-    int64_t rows, int64_t Lq, int64_t q_pos0, int S, int topk) {
-  const int64_t row = (int64_t)blockIdx.x * 16 + (threadIdx.x >> 4);
-  const int piece = threadIdx.x & 15;
+    int64_t rows, int64_t Lq, int64_t q_pos0, int S, int topk, int* __restrict__ flag) {
+  constexpr int E = Elem<P>::EPL, LPRW = D / E;
+  const int64_t row = (int64_t)blockIdx.x * (256 / LPRW) + threadIdx.x / LPRW;
+  const int piece = threadIdx.x % LPRW;
   if (row >= rows) return;
   const int64_t r = row % Lq;
   const int c = (int)((q_pos0 + r) / S);
   const int nslot = topk + 1;
   const int32_t* irow = idx + row * topk;
   const float* lrow = part_lse + row * nslot;
-  const bf16_t* orow = part_o + row * nslot * HD + piece * 8;
+  const P* orow = part_o + row * nslot * D + piece * E;
 
   int js[KMAX];
   float ls[KMAX + 1];
@@ -1141,34 +1249,32 @@ __global__ __launch_bounds__(256) void merge_partials_kernel(
 #pragma unroll
     for (int u = 0; u < s; ++u) ok = ok && js[u] != js[s];
     ls[s] = ok ? lrow[s] : -INFINITY;
-    ov[s] = ok ? load16_stream(orow + (int64_t)s * HD) : make_uint4(0, 0, 0, 0);
+    ov[s] = ok ? load16_stream(orow + (int64_t)s * D) : make_uint4(0, 0, 0, 0);
   }
   ls[KMAX] = lrow[topk];
-  ov[KMAX] = load16_stream(orow + (int64_t)topk * HD);
+  ov[KMAX] = load16_stream(orow + (int64_t)topk * D);
 
   float M = ls[KMAX];
 #pragma unroll
   for (int s = 0; s < KMAX; ++s) M = fmaxf(M, ls[s]);
-  float acc[8], f[8];
+  float acc[E], f[E];
   float wsum = __expf(ls[KMAX] - M);
-  Elem<bf16_t>::unpack(ov[KMAX], f);
+  Elem<P>::unpack(ov[KMAX], f);
 #pragma unroll
-  for (int e = 0; e < 8; ++e) acc[e] = wsum * f[e];
+  for (int e = 0; e < E; ++e) acc[e] = wsum * f[e];
 #pragma unroll
   for (int s = 0; s < KMAX; ++s) {
     const float w = ls[s] > -INFINITY ? __expf(ls[s] - M) : 0.f;
     wsum += w;
-    Elem<bf16_t>::unpack(ov[s], f);
+    Elem<P>::unpack(ov[s], f);
 #pragma unroll
-    for (int e = 0; e < 8; ++e) acc[e] = fmaf(w, f[e], acc[e]);
+    for (int e = 0; e < E; ++e) acc[e] = fmaf(w, f[e], acc[e]);
   }
   const float winv = 1.f / wsum;
-  uint4 res;
-  res.x = (uint32_t)f32_to_bf16(acc[0] * winv) | ((uint32_t)f32_to_bf16(acc[1] * winv) << 16);
-  res.y = (uint32_t)f32_to_bf16(acc[2] * winv) | ((uint32_t)f32_to_bf16(acc[3] * winv) << 16);
-  res.z = (uint32_t)f32_to_bf16(acc[4] * winv) | ((uint32_t)f32_to_bf16(acc[5] * winv) << 16);
-  res.w = (uint32_t)f32_to_bf16(acc[6] * winv) | ((uint32_t)f32_to_bf16(acc[7] * winv) << 16);
-  *reinterpret_cast<uint4*>(O + row * HD + piece * 8) = res;
+#pragma unroll
+  for (int e = 0; e < E; ++e) acc[e] *= winv;
+  mark_not_finite<P>(acc, flag);
+  store_columns<P>(O + row * D + piece * E, acc);
   if (piece == 0) LSE[row] = M + __logf(wsum);
 }
 
@@ -1180,13 +1286,14 @@ __global__ __launch_bounds__(256) void merge_partials_kernel(
 // ANCHOR: the paper's geometry.  idx holds anchor tokens, a slot is valid if its anchor is one of
 // the row's (0 <= t <= i); a valid slot whose span minus the window is empty has lse = -inf and
 // A_t is then the window's attention alone.
-template <int KMAX, bool ANCHOR>
+template <int KMAX, bool ANCHOR, typename P = bf16_t, int D = HD>
 __global__ __launch_bounds__(256) void merge_combined_kernel(
     const int32_t* __restrict__ idx, const float* __restrict__ gate,
-    const bf16_t* __restrict__ part_o, const float* __restrict__ part_lse, bf16_t* __restrict__ O,
-    int64_t rows, int64_t Lq, int64_t q_pos0, int S, int topk) {
-  const int64_t row = (int64_t)blockIdx.x * 16 + (threadIdx.x >> 4);
-  const int piece = threadIdx.x & 15;
+    const P* __restrict__ part_o, const float* __restrict__ part_lse, bf16_t* __restrict__ O,
+    int64_t rows, int64_t Lq, int64_t q_pos0, int S, int topk, int* __restrict__ flag) {
+  constexpr int E = Elem<P>::EPL, LPRW = D / E;
+  const int64_t row = (int64_t)blockIdx.x * (256 / LPRW) + threadIdx.x / LPRW;
+  const int piece = threadIdx.x % LPRW;
   if (row >= rows) return;
   const int64_t r = row % Lq;
   const int64_t limit = ANCHOR ? q_pos0 + r + 1 : (q_pos0 + r) / S;  // valid entries lie in [0, limit)
@@ -1194,7 +1301,7 @@ __global__ __launch_bounds__(256) void merge_combined_kernel(
   const int32_t* irow = idx + row * topk;
   const float* grow = gate + row * topk;
   const float* lrow = part_lse + row * nslot;
-  const bf16_t* orow = part_o + row * nslot * HD + piece * 8;
+  const P* orow = part_o + row * nslot * D + piece * E;
 
   int js[KMAX];
   float ls[KMAX], gs[KMAX];
@@ -1212,17 +1319,17 @@ __global__ __launch_bounds__(256) void merge_combined_kernel(
     }
     ls[s] = ok ? lrow[s] : -INFINITY;
     gs[s] = ok ? grow[s] : -INFINITY;
-    ov[s] = (ok && ls[s] > -INFINITY) ? load16_stream(orow + (int64_t)s * HD) : make_uint4(0, 0, 0, 0);
+    ov[s] = (ok && ls[s] > -INFINITY) ? load16_stream(orow + (int64_t)s * D) : make_uint4(0, 0, 0, 0);
     gmax = fmaxf(gmax, gs[s]);
     okmask |= ok ? (1u << s) : 0u;
   }
   const float lw = lrow[topk];
-  ov[KMAX] = load16_stream(orow + (int64_t)topk * HD);
+  ov[KMAX] = load16_stream(orow + (int64_t)topk * D);
 
-  float acc[8], fw[8], f[8];
-  Elem<bf16_t>::unpack(ov[KMAX], fw);
+  float acc[E], fw[E], f[E];
+  Elem<P>::unpack(ov[KMAX], fw);
 #pragma unroll
-  for (int e = 0; e < 8; ++e) acc[e] = 0.f;
+  for (int e = 0; e < E; ++e) acc[e] = 0.f;
   float asum = 0.f;
 #pragma unroll
   for (int s = 0; s < KMAX; ++s) {
@@ -1232,27 +1339,23 @@ __global__ __launch_bounds__(256) void merge_combined_kernel(
       const float a = __expf(gs[s] - gmax);
       const float fa = a * wa / (wa + wb), fb = a * wb / (wa + wb);
       asum += a;
-      Elem<bf16_t>::unpack(ov[s], f);
+      Elem<P>::unpack(ov[s], f);
 #pragma unroll
-      for (int e = 0; e < 8; ++e) acc[e] = fmaf(fa, f[e], fmaf(fb, fw[e], acc[e]));
+      for (int e = 0; e < E; ++e) acc[e] = fmaf(fa, f[e], fmaf(fb, fw[e], acc[e]));
     }
   }
   const bool any = asum > 0.f;
   const float inv = any ? 1.f / asum : 1.f;
-  uint4 res;
-  float o8[8];
 #pragma unroll
-  for (int e = 0; e < 8; ++e) o8[e] = (any ? acc[e] : fw[e]) * inv;
-  res.x = (uint32_t)f32_to_bf16(o8[0]) | ((uint32_t)f32_to_bf16(o8[1]) << 16);
-  res.y = (uint32_t)f32_to_bf16(o8[2]) | ((uint32_t)f32_to_bf16(o8[3]) << 16);
-  res.z = (uint32_t)f32_to_bf16(o8[4]) | ((uint32_t)f32_to_bf16(o8[5]) << 16);
-  res.w = (uint32_t)f32_to_bf16(o8[6]) | ((uint32_t)f32_to_bf16(o8[7]) << 16);
-  *reinterpret_cast<uint4*>(O + row * HD + piece * 8) = res;
+  for (int e = 0; e < E; ++e) acc[e] = (any ? acc[e] : fw[e]) * inv;
+  mark_not_finite<P>(acc, flag);
+  store_columns<P>(O + row * D + piece * E, acc);
 }
 
 // ------------------------------------------------------------------ workspace carving
 struct MfmaWs {
-  size_t counts, unit_cnt, item_off, tile_off, cursor, tile_info, items, part_lse, part_o, total;
+  int tm;  // rows of a tile
+  size_t counts, unit_cnt, item_off, tile_off, cursor, tile_info, items, part_lse, part_o, flag, total;
   BucketPlan plan;
   int B, max_tiles;
   int64_t max_items;
@@ -1308,11 +1411,12 @@ BucketPlan bucket_plan(const Problem& pb) {
   return p;
 }
 
-MfmaWs carve(const Problem& pb) {
+MfmaWs carve(const Problem& pb, int tm = TM, size_t part_elem = sizeof(bf16_t)) {
   MfmaWs w;
+  w.tm = tm;
   w.B = pb.Hkv * (int)pb.n;
   w.max_items = (int64_t)pb.Hq * pb.Lq * pb.topk;
-  w.max_tiles = (int)((w.max_items + TM - 1) / TM) + w.B;
+  w.max_tiles = (int)((w.max_items + tm - 1) / tm) + w.B;
   size_t off = 0;
   auto take = [&](size_t bytes) {
     const size_t at = off;
@@ -1326,10 +1430,11 @@ MfmaWs carve(const Problem& pb) {
   w.tile_off = take((size_t)(w.B + 1) * sizeof(int));
   w.cursor = take((size_t)w.B * sizeof(int));
   w.tile_info = take((size_t)w.max_tiles * sizeof(int4));
-  w.items = take((size_t)w.max_tiles * TM * sizeof(int));  // tile by tile, TM entries each
+  w.items = take((size_t)w.max_tiles * tm * sizeof(int));  // tile by tile, tm entries each
   const size_t nparts = (size_t)pb.Hq * pb.Lq * (pb.topk + 1);  // routed slots + the local window
   w.part_lse = take(nparts * sizeof(float));
-  w.part_o = take(nparts * HD * sizeof(bf16_t));
+  w.part_o = take(nparts * pb.D * part_elem);
+  w.flag = take(256);
   w.total = off;
   return w;
 }
@@ -1338,7 +1443,7 @@ MfmaWs carve(const Problem& pb) {
 template <typename Items>
 bool launch_buckets(const Problem& pb, const MfmaWs& w, const int32_t* idx, int* unit_cnt, int* counts,
                     int* item_off, int* tile_off, int* cursor, int4* tile_info, int* items, float* part_lse,
-                    const Items& it, hipStream_t st) {
+                    const Items& it, int* flag, hipStream_t st) {
   const int n = (int)pb.n;
   const int per_block = 4;  // 4 * 4096 counters = 64 KB
   const dim3 grid((unsigned)((w.plan.units + per_block - 1) / per_block), pb.Hq);
@@ -1347,8 +1452,9 @@ bool launch_buckets(const Problem& pb, const MfmaWs& w, const int32_t* idx, int*
                      items, part_lse, pb.Lq, pb.q_pos0, pb.G, pb.topk, n, w.plan, it);
   hipLaunchKernelGGL(bucket_unit_scan_kernel, dim3((n + 31) / 32, pb.Hkv), dim3(1024), 0, st, unit_cnt, counts,
                      pb.G * w.plan.units, n);
-  hipLaunchKernelGGL(bucket_scan_kernel, dim3(1), dim3(1024), 0, st, counts, item_off, tile_off, cursor, w.B);
-  hipLaunchKernelGGL(bucket_tiles_kernel, dim3(w.B), dim3(256), 0, st, tile_off, item_off, tile_info, items);
+  hipLaunchKernelGGL(bucket_scan_kernel, dim3(1), dim3(1024), 0, st, counts, item_off, tile_off, cursor, w.B,
+                     w.tm, flag);
+  hipLaunchKernelGGL(bucket_tiles_kernel, dim3(w.B), dim3(256), 0, st, tile_off, item_off, tile_info, items, w.tm);
   hipLaunchKernelGGL((bucket_kernel<true, Items>), grid, dim3(64 * per_block), lds, st, idx, unit_cnt, cursor,
                      items, part_lse, pb.Lq, pb.q_pos0, pb.G, pb.topk, n, w.plan, it);
   return hipGetLastError() == hipSuccess;
@@ -1402,6 +1508,7 @@ sl_status prefill_attention_mfma(const Problem& pb, const void* Q, const void* K
   a.tile_info = tile_info;
   a.items = items;
   a.part_o = part_o;
+  a.part_of = nullptr;
   a.part_lse = part_lse;
   a.O = static_cast<bf16_t*>(O);
   a.LSE = LSE;
@@ -1416,6 +1523,7 @@ sl_status prefill_attention_mfma(const Problem& pb, const void* Q, const void* K
   a.ab = a.af = 0;
   a.aroot = 2;
   a.E = 0;
+  a.clip = 0;
   a.topk = pb.topk;
   a.n = n;
   a.scale_log2e = pb.scale * kLog2e;
@@ -1426,7 +1534,7 @@ sl_status prefill_attention_mfma(const Problem& pb, const void* Q, const void* K
 
   if (pb.topk > 0) {
     if (!launch_buckets(pb, w, idx, unit_cnt, counts, item_off, tile_off, cursor, tile_info, items, part_lse,
-                        GridItems{pb.A}, st))
+                        GridItems{pb.A}, nullptr, st))
       return SL_ERR_LAUNCH;
     if (pb.prof_start) (void)hipEventRecord(pb.prof_start, st);
     if (pb.A < pb.S && !pb.combined)  // overlapping spans in one joint softmax: per-row clipping
@@ -1451,10 +1559,10 @@ sl_status prefill_attention_mfma(const Problem& pb, const void* Q, const void* K
   do {                                                                                           \
     if (pb.combined)                                                                                 \
       hipLaunchKernelGGL((merge_combined_kernel<KM, false>), mgrid, dim3(256), 0, st, idx, pb.gate, \
-                         part_o, part_lse, a.O, rows, pb.Lq, pb.q_pos0, pb.A, pb.topk);          \
+                         part_o, part_lse, a.O, rows, pb.Lq, pb.q_pos0, pb.A, pb.topk, static_cast<int*>(nullptr));          \
     else                                                                                         \
       hipLaunchKernelGGL(merge_partials_kernel<KM>, mgrid, dim3(256), 0, st, idx, part_o,        \
-                         part_lse, a.O, LSE, rows, pb.Lq, pb.q_pos0, pb.A, pb.topk);             \
+                         part_lse, a.O, LSE, rows, pb.Lq, pb.q_pos0, pb.A, pb.topk, static_cast<int*>(nullptr));             \
   } while (0)
   if (pb.topk == 0) SL_MERGE(1);
   else if (pb.topk <= 8) SL_MERGE(8);
@@ -1462,6 +1570,191 @@ sl_status prefill_attention_mfma(const Problem& pb, const void* Q, const void* K
   else SL_MERGE(32);
 #undef SL_MERGE
   return hipGetLastError() == hipSuccess ? SL_OK : SL_ERR_LAUNCH;
+}
+
+// ------------------------------------------------------------------ any span length, fp32 weights
+// bf16 inputs that the kernels above do not take -- spans that are no multiple of 64 tokens, D = 64 -- on
+// the matrix cores without giving up the row-stationary kernels' precision: every product of the weights
+// with V is taken twice, with the weight's leading bf16 part and with what that leaves, partials are fp32.
+// Error against 64 bits as the row-stationary kernels' (1.6e-3 of a bf16 output, all of it the rounding of
+// the output; 2.4e-3 with bf16 weights and partials).
+//
+// Measured (32:4 heads, top-8, D = 128 unless said otherwise; row-stationary -> this form, us):
+//   20011 rows, spans of 142: 16000 -> 1970; at D = 64: 8110 -> 1210; 2500 rows, spans of 50: 779 -> 181;
+//   200 rows behind 60000 tokens, spans of 245: 602 -> 77; 8 rows there: 158 -> 63.
+// 128-row tiles, two workgroups per compute unit (one's tile ends beside the other's kv loop): a span of
+// 142 tokens is three kv tiles, and 256-row tiles with one workgroup took 1381 us for the routed part where
+// these take 1288.
+// Calls without a workspace, or with one too small, take the row-stationary kernels as before.
+namespace {
+
+constexpr int kFineGroups = 1;
+
+// Estimated us of the two forms; the call takes the smaller.  Row-stationary: 0.02 ns per row and key, with
+// about 13 keys' worth of latency per slot, and no less than one row's own chain of loads.  This form: nine
+// launches, tiles of 4 us plus 2.2 us per kv tile on 512 workgroups (a bucket's last tile is padded),
+// partials written and read.  Of 22 measured calls (2 to 20000 rows, spans of 4 to 245 tokens) the estimates
+// choose the faster form in 18; the other four stay with the row kernels and lose 5 to 15 us, or half of
+// 415 us (1000 rows behind 60000 tokens in spans of 30, buckets a quarter full).
+bool fine_is_faster(const Problem& pb) {
+  const double rows = (double)pb.Hq * pb.Lq, items = rows * pb.topk, keys = (double)pb.topk * pb.S + pb.A / 2;
+  const double d = pb.D / 128.0;
+  const double by_rows = fmax(0.075 * keys, 2e-5 * d * rows * (keys + 13.0 * pb.topk));
+  const double tiles = fmin(items, (double)pb.Hkv * pb.n) + items / 128;
+  const double steps = (double)((pb.S + TN - 1) / TN);
+  return 45 + tiles * (4 + 2.2 * steps) / 512 + (items + rows) * pb.D * 8 / 4.5e6 < by_rows;
+}
+
+constexpr size_t kFineMaxScratch = (size_t)4 << 30;
+
+Problem fine_part(const Problem& pb, int kv_heads) {  // the first kv_heads kv heads and their query heads
+  Problem q = pb;
+  q.Hkv = kv_heads;
+  q.Hq = kv_heads * pb.G;
+  return q;
+}
+
+size_t fine_bytes(const Problem& pb) {
+  return carve(pb, kFineGroups * TG, sizeof(float)).total;
+}
+
+// kv heads per pass: as many as fit the scratch limit
+int fine_heads(const Problem& pb) {
+  int h = pb.Hkv;
+  while (h > 1 && fine_bytes(fine_part(pb, h)) > kFineMaxScratch) --h;
+  return h;
+}
+
+template <int D>
+bool fine_setup(DeviceSetup* out) {
+  static std::mutex mu;
+  static bool done[kMaxDevices];
+  int dev = -1;
+  if (!device_setup(out) || hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return false;
+  std::lock_guard<std::mutex> lock(mu);
+  if (!done[dev])
+    done[dev] = hipFuncSetAttribute(reinterpret_cast<const void*>(span_flash_routed_kernel<true, kFineGroups, D, true>),
+                                    hipFuncAttributeMaxDynamicSharedMemorySize,
+                                    FlashLds<kFineGroups, D>::kBytes) == hipSuccess &&
+                hipFuncSetAttribute(reinterpret_cast<const void*>(span_flash_local_kernel<false, D, true>),
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, FlashLds<1, D>::kBytes) == hipSuccess;
+  return done[dev];
+}
+
+template <int D>
+sl_status fine_pass(const Problem& pb, const DeviceSetup& dev, const bf16_t* Q, const bf16_t* K, const bf16_t* V,
+                    const int32_t* idx, bf16_t* O, float* LSE, char* base, hipStream_t st) {
+  const MfmaWs w = carve(pb, kFineGroups * TG, sizeof(float));
+  int* item_off = reinterpret_cast<int*>(base + w.item_off);
+  int* tile_off = reinterpret_cast<int*>(base + w.tile_off);
+  int4* tile_info = reinterpret_cast<int4*>(base + w.tile_info);
+  int* items = reinterpret_cast<int*>(base + w.items);
+  float* part_lse = reinterpret_cast<float*>(base + w.part_lse);
+  float* part_o = reinterpret_cast<float*>(base + w.part_o);
+  int* flag = reinterpret_cast<int*>(base + w.flag);
+  FlashArgs a = {};
+  a.Q = Q;
+  a.K = K;
+  a.V = V;
+  a.idx = idx;
+  a.item_off = item_off;
+  a.tile_off = tile_off;
+  a.tile_info = tile_info;
+  a.items = items;
+  a.part_of = part_o;
+  a.part_lse = part_lse;
+  a.O = O;
+  a.LSE = LSE;
+  a.L = pb.L;
+  a.Lq = pb.Lq;
+  a.q_pos0 = pb.q_pos0;
+  a.Hq = pb.Hq;
+  a.G = pb.G;
+  a.S = pb.S;
+  a.A = pb.A;
+  a.clip = pb.A < pb.S && !pb.combined;
+  a.aroot = 2;
+  a.topk = pb.topk;
+  a.n = (int)pb.n;
+  a.scale_log2e = pb.scale * kLog2e;
+  a.qsh = pb.qsh;
+  a.qst = pb.qst;
+  a.kvsh = pb.kvsh;
+  a.kvst = pb.kvst;
+  if (!launch_buckets(pb, w, idx, reinterpret_cast<int*>(base + w.unit_cnt), reinterpret_cast<int*>(base + w.counts),
+                      item_off, tile_off, reinterpret_cast<int*>(base + w.cursor), tile_info, items, part_lse,
+                      GridItems{pb.A}, flag, st))
+    return SL_ERR_LAUNCH;
+  if (pb.prof_start) (void)hipEventRecord(pb.prof_start, st);
+  using RoutedLds = FlashLds<kFineGroups, D>;
+  using LocalLds = FlashLds<1, D>;
+  hipLaunchKernelGGL((span_flash_routed_kernel<true, kFineGroups, D, true>),
+                     dim3(dev.grid * (kFineGroups == 1 ? 2 : 1)), dim3(RoutedLds::kThreads), RoutedLds::kBytes, st, a);
+  if (pb.prof_stop) (void)hipEventRecord(pb.prof_stop, st);
+  hipLaunchKernelGGL((span_flash_local_kernel<false, D, true>), dim3(local_grid(pb.Lq, pb.A, pb.Hkv, pb.G)),
+                     dim3(LocalLds::kThreads), LocalLds::kBytes, st, a);
+  const int64_t rows = (int64_t)pb.Hq * pb.Lq;
+  constexpr int kRowsPerBlock = 256 / (D / 4);
+  const dim3 mgrid((unsigned)((rows + kRowsPerBlock - 1) / kRowsPerBlock));
+#define SL_MERGE(KM)                                                                                       \
+  do {                                                                                                     \
+    if (pb.combined)                                                                                       \
+      hipLaunchKernelGGL((merge_combined_kernel<KM, false, float, D>), mgrid, dim3(256), 0, st, idx, pb.gate, \
+                         part_o, part_lse, O, rows, pb.Lq, pb.q_pos0, pb.A, pb.topk, flag);                \
+    else                                                                                                   \
+      hipLaunchKernelGGL((merge_partials_kernel<KM, float, D>), mgrid, dim3(256), 0, st, idx, part_o,      \
+                         part_lse, O, LSE, rows, pb.Lq, pb.q_pos0, pb.A, pb.topk, flag);                   \
+  } while (0)
+  if (pb.topk <= 8) SL_MERGE(8);
+  else if (pb.topk <= 16) SL_MERGE(16);
+  else SL_MERGE(32);
+#undef SL_MERGE
+  if (hipGetLastError() != hipSuccess) return SL_ERR_LAUNCH;
+  // A V row that is not finite meets zero weights of rows that do not attend it (the later rows of a window
+  // tile, the rows of clipped spans): where any output is not finite the row-stationary kernels, which
+  // never touch such a row, compute the pass again.
+  return prefill_attention_rows(pb, Q, K, V, idx, O, LSE, st, flag);
+}
+
+template <int D>
+sl_status fine_all(const Problem& pb, const void* Q, const void* K, const void* V, const int32_t* idx, void* O,
+                   float* LSE, void* ws, hipStream_t st) {
+  DeviceSetup dev;
+  if (!fine_setup<D>(&dev)) return SL_ERR_LAUNCH;
+  const int step = fine_heads(pb);
+  for (int kv = 0; kv < pb.Hkv; kv += step) {
+    Problem q = fine_part(pb, pb.Hkv - kv < step ? pb.Hkv - kv : step);
+    if (kv > 0) q.prof_start = q.prof_stop = nullptr;
+    const int64_t h = (int64_t)kv * pb.G, row = h * pb.Lq;
+    if (pb.gate) q.gate = pb.gate + row * pb.topk;
+    const sl_status s = fine_pass<D>(q, dev, static_cast<const bf16_t*>(Q) + h * pb.qsh,
+                                     static_cast<const bf16_t*>(K) + kv * pb.kvsh,
+                                     static_cast<const bf16_t*>(V) + kv * pb.kvsh, idx + row * pb.topk,
+                                     static_cast<bf16_t*>(O) + row * D, LSE ? LSE + row : nullptr,
+                                     static_cast<char*>(ws), st);
+    if (s != SL_OK) return s;
+  }
+  return SL_OK;
+}
+
+}  // namespace
+
+bool prefill_attention_fine_supported(const Problem& pb) {
+  if (pb.dtype != SL_BF16 || prefill_attention_mfma_supported(pb) || pb.topk < 1 || pb.n > 4096) return false;
+  const int64_t rows = (int64_t)pb.Hq * pb.Lq;
+  return fine_is_faster(pb) && (int64_t)pb.G * pb.Lq < ((int64_t)1 << 26) && pb.L <= kMaxTokens && 64 * pb.kvst * 2 < ((int64_t)1 << 31) &&
+         rows * (pb.topk + 1) < ((int64_t)1 << 31) &&
+         rows * pb.topk + ((int64_t)pb.Hkv * pb.n + 1) * TM < ((int64_t)1 << 31) &&
+         pb.Hq * pb.qsh + pb.Lq * pb.qst < ((int64_t)1 << 31) &&
+         fine_bytes(fine_part(pb, 1)) <= kFineMaxScratch;
+}
+
+size_t prefill_attention_fine_ws_bytes(const Problem& pb) { return fine_bytes(fine_part(pb, fine_heads(pb))); }
+
+sl_status prefill_attention_fine(const Problem& pb, const void* Q, const void* K, const void* V, const int32_t* idx,
+                                 void* O, float* LSE, void* ws, hipStream_t st) {
+  return pb.D == 64 ? fine_all<64>(pb, Q, K, V, idx, O, LSE, ws, st)
+                    : fine_all<128>(pb, Q, K, V, idx, O, LSE, ws, st);
 }
 
 // ------------------------------------------------------------------ the paper's geometry on the matrix cores
@@ -1531,6 +1824,7 @@ sl_status prefill_anchor_attention_mfma(const Problem& pb, int64_t window, int b
   a.tile_info = tile_info;
   a.items = items;
   a.part_o = part_o;
+  a.part_of = nullptr;
   a.part_lse = part_lse;
   a.O = static_cast<bf16_t*>(O);
   a.LSE = nullptr;
@@ -1548,6 +1842,7 @@ sl_status prefill_anchor_attention_mfma(const Problem& pb, int64_t window, int b
   a.af = f;
   a.aroot = root;
   a.E = q.A;
+  a.clip = 0;
   a.scale_log2e = pb.scale * kLog2e;
   a.qsh = pb.qsh;
   a.qst = pb.qst;
@@ -1558,7 +1853,7 @@ sl_status prefill_anchor_attention_mfma(const Problem& pb, int64_t window, int b
   wa.plan.unit_h = 1;  // items of a bucket by row, then by head
   wa.plan.unit_u = pb.G;
   if (!launch_buckets(q, wa, anchors, unit_cnt, counts, item_off, tile_off, cursor, tile_info, items, part_lse,
-                      AnchorItems{window, b, f, root, a.E}, st))
+                      AnchorItems{window, b, f, root, a.E}, nullptr, st))
     return SL_ERR_LAUNCH;
   if (pb.prof_start) (void)hipEventRecord(pb.prof_start, st);
   hipLaunchKernelGGL(span_flash_anchor_kernel, dim3(dev.grid), dim3(FlashLds<2>::kThreads),
@@ -1571,13 +1866,13 @@ sl_status prefill_anchor_attention_mfma(const Problem& pb, int64_t window, int b
   const dim3 mgrid((unsigned)((rows + 15) / 16));
   if (pb.topk <= 8)
     hipLaunchKernelGGL((merge_combined_kernel<8, true>), mgrid, dim3(256), 0, st, anchors, pb.gate, part_o,
-                       part_lse, a.O, rows, pb.Lq, pb.q_pos0, 1, pb.topk);
+                       part_lse, a.O, rows, pb.Lq, pb.q_pos0, 1, pb.topk, static_cast<int*>(nullptr));
   else if (pb.topk <= 16)
     hipLaunchKernelGGL((merge_combined_kernel<16, true>), mgrid, dim3(256), 0, st, anchors, pb.gate, part_o,
-                       part_lse, a.O, rows, pb.Lq, pb.q_pos0, 1, pb.topk);
+                       part_lse, a.O, rows, pb.Lq, pb.q_pos0, 1, pb.topk, static_cast<int*>(nullptr));
   else
     hipLaunchKernelGGL((merge_combined_kernel<32, true>), mgrid, dim3(256), 0, st, anchors, pb.gate, part_o,
-                       part_lse, a.O, rows, pb.Lq, pb.q_pos0, 1, pb.topk);
+                       part_lse, a.O, rows, pb.Lq, pb.q_pos0, 1, pb.topk, static_cast<int*>(nullptr));
   return hipGetLastError() == hipSuccess ? SL_OK : SL_ERR_LAUNCH;
 }
 
