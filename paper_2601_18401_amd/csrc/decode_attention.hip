@@ -32,7 +32,7 @@ __device__ __forceinline__ void decode_split_body(
     const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V,
     const int32_t* __restrict__ idx, float* __restrict__ part, int64_t q_pos, int Hq, int Hkv,
     int S, int A, bool clip, int topk, int nchunks, int CT, float scale_log2e, int64_t qsh, int64_t kvsh,
-    int64_t kvst, int n_routed_blocks, int local_stride, bool share_window, const AnchorRanges ar) {
+    int64_t kvst, int n_routed_blocks, int local_stride, bool share_spans, const AnchorRanges ar) {
   // Grid: anchors every A tokens, span j = the S tokens ending at (j+1)*A - 1 (A = S: disjoint spans).
   // clip (joint softmax with A < S): spans of one head overlap, and a token must count once, so an
   // entry's range starts behind the end of the nearest lower span that the same head lists.
@@ -146,28 +146,27 @@ __device__ __forceinline__ void decode_split_body(
   const int per_wave = CT / (kDecodeThreads / 64);
   const bool one_batch = U <= 8 && per_wave <= RPW * U;  // (wide batches go with chunks of several batches)
 
-  // Rows that several heads of a kv head attend are read once.  (1) Grid: a span that several
+  // Rows that several heads of a kv head attend (share_spans).  Grid: a span that several
   // heads select; paper's geometry: a chunk that the spans of several (head, slot) entries cover
-  // (equal anchors, or merely overlapping spans).  The entry that comes first in the group's index
-  // rows owns the chunk and computes the partial of every other entry that attends it; the
-  // workgroups of those entries leave at once.  Needs the group's G * topk indices in one pass of
-  // a wavefront (larger groups: every entry reads its own rows).  (2) share_window: the local
-  // window, which all G heads attend: the first head's workgroup serves the group.  When the
-  // wave's rows fit one batch they stay in registers and every entry is computed from them;
-  // otherwise (and for clipped overlapping grid spans, whose range differs per entry) the owner
-  // reads the rows again per entry, through the L2.
+  // (equal anchors, or merely overlapping spans).  The entries that share a chunk go in pairs, in the
+  // order of the group's index rows: the first of a pair computes the second's partial too, whose
+  // workgroup leaves at once.  (One owner for all of them took the entries one after the other, about a
+  // microsecond each, on the critical path.)  Needs the group's G * topk indices in one pass of
+  // a wavefront (larger groups: every entry reads its own rows).  When the wave's rows fit one batch they
+  // stay in registers and both entries are computed from them; otherwise (and for clipped overlapping
+  // grid spans, whose range differs per entry) they are read again, through the L2.  The local window,
+  // which all G heads attend, is left to the caches: its G workgroups run on one XCD, and one workgroup
+  // serving the group head by head measured 58.5 us per step at 1M against 57.6.
   constexpr int kShareWords = 4;  // up to 256 (head, slot) entries per kv head
-  const bool dedup = slot < topk && G * topk <= 64 * kShareWords && G > 1;
-  const bool window_group = slot == topk && share_window && one_batch && G > 1 && G <= 64;
+  const bool dedup = share_spans && slot < topk && G * topk <= 64 * kShareWords && G > 1;
   unsigned long long share[kShareWords] = {0ull, 0ull, 0ull, 0ull};
-  // entry numbers: (head in group) * topk + slot for a span, head in group for the window
-  const int my_entry = window_group ? h - kv * G : (h - kv * G) * topk + slot;
+  const int my_entry = (h - kv * G) * topk + slot;
   bool multi = false;
   if (dedup && (!AG || t0 < t1)) {
     // every wavefront builds the masks by itself (no LDS, no barrier): lane l looks at entries
     // l, l + 64, ... of the group's index rows, which are contiguous
     const int64_t jmine = idx[(int64_t)h * topk + slot];
-    int first = -1, count = 0;
+    int rank = 0, partner = -1;  // entries that share the chunk in front of this one; the one behind it
 #pragma unroll
     for (int w = kShareWords - 1; w >= 0; --w) {
       const int e = 64 * w + lane;
@@ -181,20 +180,23 @@ __device__ __forceinline__ void decode_split_body(
       } else {
         same = jmine >= 0 && jmine < c && jother == jmine;
       }
-      share[w] = __ballot(same);
-      if (share[w]) first = 64 * w + __builtin_ctzll(share[w]);
-      count += __builtin_popcountll(share[w]);
+      const unsigned long long all = __ballot(same);
+      const unsigned long long me = (my_entry >> 6) == w ? 1ull << (my_entry & 63) : 0ull;
+      const unsigned long long front = (my_entry >> 6) == w ? all & (me - 1ull) : (my_entry >> 6) > w ? all : 0ull;
+      const unsigned long long behind = all & ~front & ~me;
+      rank += __builtin_popcountll(front);
+      if (behind) partner = 64 * w + __builtin_ctzll(behind);
+      share[w] = me;
     }
-    if (count > 1) {
-      if (first != my_entry) return;  // the owner writes this entry's record
+    if (rank & 1) return;  // the entry in front of this one writes its record
+    if (partner >= 0) {
+#pragma unroll
+      for (int w = 0; w < kShareWords; ++w)
+        if ((partner >> 6) == w) share[w] |= 1ull << (partner & 63);
       multi = true;
     }
-  } else if (window_group) {
-    if (my_entry != 0) return;
-    share[0] = G == 64 ? ~0ull : (1ull << G) - 1ull;
-    multi = true;
   }
-  const bool per_entry_range = multi && !window_group && clip && !AG;
+  const bool per_entry_range = multi && clip && !AG;
   const bool from_regs = multi && one_batch && !per_entry_range;
 
   const int g = lane / LPR, lr = lane % LPR;
@@ -246,8 +248,8 @@ __device__ __forceinline__ void decode_split_body(
     for (int e = 0; e < EPL; ++e) q2[e] = qf[e] * scale_log2e;
   };
   // entry -> (head, slot) of the record
-  auto entry_head = [&](int e) { return window_group ? kv * G + e : kv * G + e / topk; };
-  auto entry_slot = [&](int e) { return window_group ? topk : e % topk; };
+  auto entry_head = [&](int e) { return kv * G + e / topk; };
+  auto entry_slot = [&](int e) { return e % topk; };
   // takes `entry` out of the masks and returns the next entry that attends the same rows, or -1
   // (all threads hold the same masks)
   auto next_entry = [&](int entry) {
@@ -301,7 +303,7 @@ __device__ __forceinline__ void decode_split_body(
       int64_t anchor_next = -1;
       if (next >= 0) {
         qraw = load16(Q + (int64_t)entry_head(next) * qsh + lr * EPL);
-        if (!window_group) anchor_next = idx[(int64_t)kv * G * topk + next];
+        anchor_next = idx[(int64_t)kv * G * topk + next];
       }
       int64_t lo, hi;
       float* prec = entry_piece(entry_head(entry), entry_slot(entry), anchor, lo, hi);
@@ -375,9 +377,9 @@ void decode_split_kernel(
     const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V,
     const int32_t* __restrict__ idx, float* __restrict__ part, int64_t q_pos, int Hq, int Hkv,
     int S, int A, bool clip, int topk, int nchunks, int CT, float scale_log2e, int64_t qsh, int64_t kvsh,
-    int64_t kvst, int n_routed_blocks, int local_stride, bool share_window, const AnchorRanges ar) {
+    int64_t kvst, int n_routed_blocks, int local_stride, bool share_spans, const AnchorRanges ar) {
   decode_split_body<T, D, U, AG>(Q, K, V, idx, part, q_pos, Hq, Hkv, S, A, clip, topk, nchunks, CT, scale_log2e,
-                          qsh, kvsh, kvst, n_routed_blocks, local_stride, share_window, ar);
+                          qsh, kvsh, kvst, n_routed_blocks, local_stride, share_spans, ar);
 }
 
 // Batched decode: blockIdx.y is the sequence; its tensors and length come from the device array.
@@ -398,8 +400,7 @@ __global__ __launch_bounds__(kDecodeThreads) __attribute__((amdgpu_waves_per_eu(
 void decode_split_batched_kernel(
     const sl_decode_seq* __restrict__ seqs, float* __restrict__ part, int64_t part_stride, int Hq,
     int Hkv, int S, int A, bool clip, int topk, int nchunks, int CT, float scale_log2e, int64_t qsh,
-    int64_t kvsh, int64_t kvst, int n_routed_blocks, int local_stride, bool share_window,
-    const AnchorBatch ab) {
+    int64_t kvsh, int64_t kvst, int n_routed_blocks, int local_stride, bool share_spans, const AnchorBatch ab) {
   const sl_decode_seq sq = seqs[blockIdx.y];
   const int64_t i = sq.L - 1;
   AnchorRanges ar{false, 0, 0, 0, 0};
@@ -414,7 +415,7 @@ void decode_split_batched_kernel(
   decode_split_body<T, D, U, AG>(static_cast<const T*>(sq.Q), static_cast<const T*>(sq.K),
                           static_cast<const T*>(sq.V), sq.idx, part + blockIdx.y * part_stride, i, Hq,
                           Hkv, S, A, clip, topk, nchunks, CT, scale_log2e, qsh, kvsh ? kvsh : sq.L * kvst,
-                          kvst, n_routed_blocks, local_stride, share_window, ar);
+                          kvst, n_routed_blocks, local_stride, share_spans, ar);
 }
 
 // Merges the (topk + 1) * nchunks partial records of a head.  grid (Hq, D / 32): each workgroup
@@ -692,11 +693,15 @@ __global__ __launch_bounds__(256) void decode_reduce_combined_batched_kernel(
 // wavefront per SIMD.
 inline bool wide_batches(int CT) { return CT >= 512; }
 
-// One workgroup serving the window of all G heads of a kv head computes them one after the other,
-// about a microsecond per head; that pays (fewer workgroups, the rows pulled once) only while the
-// rest of the grid runs much longer: from 128 MB of routed K/V rows, about 20 us of streaming.
-inline bool window_by_one_workgroup(int64_t routed_items, int CT, int D, size_t elem_bytes) {
-  return routed_items * CT * 2 * D * (int64_t)elem_bytes >= ((int64_t)128 << 20);
+// Reading a chunk once for two entries saves HBM traffic and costs the second entry's arithmetic in line.
+// Below 256 MB of routed K/V rows the caches serve the second reader and only the cost is left.  Whole
+// steps, one owner for all entries (as it was) / pairs / every entry by itself, us:
+//   16411 tokens: 24.3 / 20.0 / 17.4;  262144: 48.3 / 48.4 / 43.9;  1M: 58.3 / 58.5 / 58.7;
+//   10M: 177.4 / 176.7 / 183.6;  8 sequences of 60000 .. 300000: 187 / 176 / 178
+// with the heads of a group on the same spans:
+//   16411 tokens: 37.0 / 20.3 / 16.0;  1M: 57.1 / 48.5 / 43.6;  10M: 176 / 105 / 142.
+inline bool spans_in_pairs(int64_t routed_items, int CT, int D, size_t elem_bytes) {
+  return routed_items * CT * 2 * D * (int64_t)elem_bytes >= ((int64_t)256 << 20);
 }
 
 template <typename T, int D, int U, bool AG>
@@ -705,7 +710,7 @@ void launch_split_u(int grid, hipStream_t st, hipEvent_t e0, hipEvent_t e1, cons
                     int CT, int n_routed, int local_stride, const AnchorRanges& ar) {
   const float scale_log2e = pb.scale * kLog2e;
   const bool clip = !AG && pb.A < pb.S && !pb.combined;  // overlapping spans in one joint softmax
-  const bool share_window = window_by_one_workgroup(n_routed, CT, D, sizeof(T));
+  const bool share_spans = spans_in_pairs(n_routed, CT, D, sizeof(T));
   if (e0) {
     // With profiling events the launch itself carries them: they then hold the kernel's own
     // begin and end timestamps (events recorded on the stream before / after a 45 us kernel would
@@ -714,12 +719,12 @@ void launch_split_u(int grid, hipStream_t st, hipEvent_t e0, hipEvent_t e1, cons
                           0, static_cast<const T*>(Q), static_cast<const T*>(K),
                           static_cast<const T*>(V), idx, part, pb.q_pos0, pb.Hq, pb.Hkv, S, AG ? S : pb.A,
                           clip, pb.topk, nchunks, CT, scale_log2e, pb.qsh, pb.kvsh, pb.kvst, n_routed,
-                          local_stride, share_window, ar);
+                          local_stride, share_spans, ar);
   } else {
     hipLaunchKernelGGL((decode_split_kernel<T, D, U, AG>), dim3(grid), dim3(kDecodeThreads), 0, st,
                        static_cast<const T*>(Q), static_cast<const T*>(K), static_cast<const T*>(V), idx,
                        part, pb.q_pos0, pb.Hq, pb.Hkv, S, AG ? S : pb.A, clip, pb.topk, nchunks, CT,
-                       scale_log2e, pb.qsh, pb.kvsh, pb.kvst, n_routed, local_stride, share_window, ar);
+                       scale_log2e, pb.qsh, pb.kvsh, pb.kvst, n_routed, local_stride, share_spans, ar);
   }
 }
 
@@ -750,10 +755,10 @@ void launch_split_batched_u(int grid, int B, hipStream_t st, const sl_decode_seq
   const int64_t kvsh = pb.kvsh_given ? pb.kvsh : (int64_t)0;
   const int A = AG ? S : pb.A;
   const bool clip = !AG && pb.A < pb.S && !pb.combined;
-  const bool share_window = window_by_one_workgroup((int64_t)n_routed * B, CT, D, sizeof(T));
+  const bool share_spans = spans_in_pairs((int64_t)n_routed * B, CT, D, sizeof(T));
   hipLaunchKernelGGL((decode_split_batched_kernel<T, D, U, AG>), dim3(grid, B), dim3(kDecodeThreads), 0, st,
                      seqs, part, part_stride, pb.Hq, pb.Hkv, S, A, clip, pb.topk, nchunks, CT, scale_log2e,
-                     pb.qsh, kvsh, pb.kvst, n_routed, local_stride, share_window, ab);
+                     pb.qsh, kvsh, pb.kvst, n_routed, local_stride, share_spans, ab);
 }
 
 template <typename T, int D>

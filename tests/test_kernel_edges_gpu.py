@@ -115,3 +115,54 @@ def test_any_span_length_keeps_what_is_not_finite_to_the_rows_that_attend_it(bad
     attends = (idx == t // S).any(dim=2) | ((pos // S == t // S) & (pos >= t))[None, :]
     attends[G:] = False
     assert torch.equal(~torch.isfinite(O.float()).all(dim=2), attends)
+
+
+@pytest.mark.parametrize("form,dtype,Hq,Hkv,S,A,k", [
+    ("joint", torch.bfloat16, 32, 4, 256, 256, 16),     # one batch of rows, kept in registers for both entries
+    ("joint", torch.bfloat16, 32, 4, 1024, 1024, 16),   # 512-token chunks: read again
+    ("joint", torch.bfloat16, 24, 8, 256, 128, 16),     # overlapping spans: every entry its own range
+    ("gated", torch.float32, 16, 2, 200, 200, 16),
+    ("anchor", torch.bfloat16, 32, 4, 1, 1, 8),
+])
+def test_decode_entries_sharing_chunks_go_in_pairs(form, dtype, Hq, Hkv, S, A, k):
+    """Steps of 256 MB and more of routed rows pair the entries that share a chunk: a batch of the same
+    sequence against the single step, which is below that and pairs nothing.  Heads list the same spans,
+    partly the same, an odd number of them, and empty slots.  Chunks may be cut differently: fp32 sums in
+    another order (1e-5 of outputs below 5), then one rounding to the output's type."""
+    D, G, nb = 128, Hq // Hkv, 8
+    rng = np.random.default_rng(S + k)
+    L = 40000 if form == "anchor" else max(S * 22, 9000) + 37
+    Q, K, V = make(900 + S, Hq, Hkv, L, D, dtype, Lq=1, scale=0.5)
+    if form == "anchor":
+        from tests.test_parity_gpu import clustered_anchors
+        idx = clustered_anchors(rng, L - 1, 1088, 2, Hkv, G, k)
+    else:
+        c = (L - 1) // A
+        idx = np.full((Hq, 1, k), -1, np.int32)
+        for h in range(Hq):
+            common = np.random.default_rng(h // G).choice(c, size=k, replace=False)
+            own = rng.choice(c, size=k, replace=False)
+            pick = common if h % G in (0, 2, 3) else np.unique(np.concatenate([common[:k // 2], own]))[:k] if h % 2 else own
+            pick = np.sort(pick)[: k - (h % 3)]
+            idx[h, 0, :len(pick)] = pick
+    sc = rng.standard_normal((Hq, 1, k)).astype(np.float32)
+    idx_t, sc_t = torch.from_numpy(idx).to(DEV), torch.from_numpy(sc).to(DEV)
+    stride = 0 if A == S else A
+    batch = B.DecodeBatch([Q] * nb, [Q] * nb, [K] * nb, [V] * nb, None, S, k, want_scores=True, span_stride=stride)
+    batch.idx.copy_(idx_t.expand(nb, -1, -1, -1))
+    batch.scores.copy_(sc_t.expand(nb, -1, -1, -1))
+    if form == "anchor":
+        one = B.sl_anchor_attention_decode(Q, K, V, idx_t, sc_t, 1088, 4, 2)
+        many = B.sl_anchor_attention_decode_batched(batch, 1088, 4, 2)
+    elif form == "gated":
+        one = B.sl_span_attention_combined_decode(Q, K, V, idx_t, sc_t, S, span_stride=stride)
+        many = B.sl_span_attention_combined_decode_batched(batch)
+    else:
+        one, lse = B.sl_span_attention_decode(Q, K, V, idx_t, S, span_stride=stride)
+        many, lses = B.sl_span_attention_decode_batched(batch)
+        torch.cuda.synchronize()
+        assert float((lses - lse).abs().max()) <= 1e-5
+    torch.cuda.synchronize()
+    step = 2 ** -7 if dtype == torch.bfloat16 else 0.0
+    diff = (many.float() - one.float()[None]).abs() - step * one.float().abs()[None]
+    assert float(diff.max()) <= 1e-5
