@@ -557,6 +557,11 @@ sl_status launch_span_keys(const Problem& pb, const void* K, void* Ks, hipStream
   return hipGetLastError() == hipSuccess ? SL_OK : SL_ERR_LAUNCH;
 }
 
+// Up to this many candidates the selecting workgroup scores them itself: its 16 wavefronts hold all their key
+// rows in one round of loads, and the second launch costs more than it saves (whole steps, two launches ->
+// one: 128 candidates 18.1 -> 17.0 us, 511: 43.5 -> 43.0, 744: 54.2 -> 54.0, 1023: 58.2 -> 59.3).
+constexpr int64_t kOneLaunchCandidates = 768;
+
 template <typename T, int D>
 sl_status launch_decode_search(const Problem& pb, const void* Qs, const void* K, const void* Ks,
                                int32_t* idx, float* scores, void* ws, hipStream_t st) {
@@ -567,7 +572,7 @@ sl_status launch_decode_search(const Problem& pb, const void* Qs, const void* K,
     // per head selects (block-parallel selection: candidates fit 4 registers per thread).
     // (a cache with more spans than that sizes no workspace: its shorter queries score in the
     // selecting workgroup itself)
-    float* sc_ws = pb.n <= (int64_t)kDecodeSearchThreads * 4 ? static_cast<float*>(ws) : nullptr;
+    float* sc_ws = c > kOneLaunchCandidates && pb.n <= (int64_t)kDecodeSearchThreads * 4 ? static_cast<float*>(ws) : nullptr;
     const int64_t ld = decode_score_ld(pb);
     if (c > 0 && sc_ws)
       hipLaunchKernelGGL((decode_score_group_kernel<T, D>), dim3((unsigned)((c + kScoreCand - 1) / kScoreCand), pb.Hkv),
