@@ -148,12 +148,20 @@ def _dtype_code(t: torch.Tensor) -> int:
     raise TypeError(f"unsupported dtype {t.dtype}: fp32 or bf16 only")
 
 
+# A short decode step is bound by this module: its kernels take 17 us, its two calls took 28.
+# Hence plain integers where ctypes converts them itself, the parameter record built in one call, and the
+# current stream's handle without a Stream object (whole decode step of a 16411-token cache 28.0 -> 20.5 us).
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
+
+
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 def _arm(prof):
@@ -162,19 +170,19 @@ def _arm(prof):
         load().sl_set_profile_events(ctypes.c_void_p(prof[0]), ctypes.c_void_p(prof[1]))
 
 
+_LAYOUT = "expect Q [Hq, Lq, D] and K [Hkv, L, D] with contiguous innermost dimension"
+
+
 def make_params(Q, K, S, topk, q_pos0=0, scale=0.0, span_stride=0) -> SlParams:
     """Q: [Hq, Lq, D] (innermost contiguous), K: [Hkv, L, D]."""
-    if Q.dim() != 3 or K.dim() != 3 or Q.stride(2) != 1 or K.stride(2) != 1:
-        raise ValueError("expect Q [Hq, Lq, D] and K [Hkv, L, D] with contiguous innermost dimension")
-    p = SlParams()
-    p.L, p.Lq, p.q_pos0 = K.shape[1], Q.shape[1], int(q_pos0)
-    p.Hq, p.Hkv, p.D = Q.shape[0], K.shape[0], Q.shape[2]
-    p.S, p.topk, p.dtype = int(S), int(topk), _dtype_code(Q)
-    p.scale = float(scale)
-    p.span_stride = int(span_stride)
-    p.q_stride_h, p.q_stride_t = Q.stride(0), Q.stride(1)
-    p.kv_stride_h, p.kv_stride_t = K.stride(0), K.stride(1)
-    return p
+    if Q.dim() != 3 or K.dim() != 3:
+        raise ValueError(_LAYOUT)
+    (Hq, Lq, D), (Hkv, L, _) = Q.shape, K.shape
+    (qh, qt, qd), (kh, kt, kd) = Q.stride(), K.stride()
+    if qd != 1 or kd != 1:
+        raise ValueError(_LAYOUT)
+    return SlParams(L, Lq, int(q_pos0), Hq, Hkv, D, int(S), int(topk), _dtype_code(Q), float(scale), int(span_stride),
+                    qh, qt, kh, kt)
 
 
 def workspace_bytes(p: SlParams, op: int) -> int:
@@ -195,8 +203,9 @@ class Workspace:
             return None, 0
         if self.buf is None or self.buf.numel() < nbytes:
             self.buf = torch.empty(int(nbytes) + 256, dtype=torch.uint8, device=self.device)
-        off = (-self.buf.data_ptr()) % 256
-        return ctypes.c_void_p(self.buf.data_ptr() + off), self.buf.numel() - off
+        at = self.buf.data_ptr()
+        off = -at % 256
+        return at + off, self.buf.numel() - off
 
 
 _default_ws = None
