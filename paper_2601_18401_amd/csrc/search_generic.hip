@@ -5,6 +5,7 @@
 //
 // Scores are eq. (2): raw dot products, accumulated in fp32 from exact products.
 #include <cmath>
+#include <type_traits>
 
 #include "kernels.h"
 #include "select.h"
@@ -447,7 +448,7 @@ __global__ __launch_bounds__(256) void prefill_anchor_search_rows_kernel(
                    scores ? scores + row * topk : nullptr, i, s0, root);
 }
 
-// The same search with the key rows shared by the query heads of a kv group: a row group of LPR
+// The same search (fp32) with the key rows shared by the query heads of a kv group: a row group of LPR
 // lanes owns one query row and up to 8 query heads of its kv head; every candidate's key row is
 // loaded once and scored against all of them (the row-per-wavefront kernel above loads it once per
 // head: 8x the L2 traffic at GQA 8:1, which is what bounds it).  Lane lr of a group keeps the
@@ -535,6 +536,163 @@ __global__ __launch_bounds__(256) void prefill_anchor_search_group_kernel(
 #pragma unroll
         for (int e2 = 0; e2 < KMAX; ++e2) rank += (e2 < topk && id[e2] >= 0 && id[e2] < id[e]) ? 1 : 0;
         oa[rank] = (int32_t)anchor_token_of(i, (int64_t)s0 + id[e], root);
+        if (os) os[rank] = v[e];
+      }
+    }
+    for (int e = kk; e < topk; ++e) {
+      oa[e] = -1;
+      if (os) os[e] = -INFINITY;
+    }
+  }
+}
+
+// The same search for bf16 on the matrix cores.  A wavefront owns two query rows and up to 8 query heads of
+// a kv head; the 16 columns of v_mfma_f32_16x16x32_bf16 are (row, head).  Sixteen candidates of one row
+// -- gathered key rows -- are the A operand; each row's keys are multiplied with all 16 columns and a lane
+// keeps the half that belongs to its row (the other half is thrown away: the rows have no key in common).
+// Lane l holds column l % 16 and candidates 4 * (l / 16) + 0..3 of a batch, and keeps the running top-KMAX
+// of those; the four lanes of a column merge their lists at the end (equal scores: the nearer anchor).
+//
+// Every row has its own keys (256 bytes per row and candidate), so loads are what it does.  The A operand
+// wants a different row in each of 16 neighbouring lanes: read that way from memory every lane is an access
+// of its own, and the address and data units were busy 82 and 93 % of the time (695 us).  The rows are
+// therefore brought to LDS by direct loads, whole rows by neighbouring lanes, in 8 KB of the wavefront's own
+// (pieces swizzled for the operand reads); while one batch is scored the next is on its way.  A block's 8
+// rows lie beside those of the other blocks of its XCD (chunks of 512 rows, dealt to the XCDs in turn):
+// at the same stride index their keys are neighbours and the next index finds them in that L2.  Rows with
+// the most candidates come first.  49157 rows, 32:4 heads, window 1088, top-2: 956 us with vector
+// instructions (two-element dot products and a lane-group sum per score), 508 us.
+constexpr int kAnchorRowsPerBlock = 8, kAnchorBlocksPerChunk = 64;
+
+template <int D, int KMAX>
+__global__ __launch_bounds__(256) void prefill_anchor_search_mfma_kernel(
+    const bf16_t* __restrict__ Qs, const bf16_t* __restrict__ K, int32_t* __restrict__ anchors,
+    float* __restrict__ scores, int64_t Lq, int64_t q_pos0, int G, int topk, int s0, int root, int blocks,
+    int64_t qsh, int64_t qst, int64_t kvsh, int64_t kvst) {
+  typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+  typedef float f32x4 __attribute__((ext_vector_type(4)));
+  constexpr int KS = D / 32, HB = 8;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int n = lane & 15, q4 = lane >> 4;
+  const int nb = (G + HB - 1) / HB;
+  const int kv = blockIdx.y / nb, h0 = (blockIdx.y % nb) * HB;
+  const int xcd = blockIdx.x & 7, at = blockIdx.x >> 3;
+  const int blk = ((at / kAnchorBlocksPerChunk) * 8 + xcd) * kAnchorBlocksPerChunk + at % kAnchorBlocksPerChunk;
+  if (blk >= blocks) return;
+  const int64_t r0 = ((int64_t)(blocks - 1 - blk) * 4 + wave) * 2;
+  if (r0 >= Lq) return;
+  const int64_t r1 = r0 + 1 < Lq ? r0 + 1 : r0;
+  const int i0 = (int)(q_pos0 + r0), i1 = (int)(q_pos0 + r1);  // positions fit 32 bits
+  auto candidates = [&](int i) {
+    const int s_max = (int)iroot_floor((int64_t)i + 1, root) - 1;  // (s+1)^root <= i + 1
+    return __builtin_amdgcn_readfirstlane(s_max >= s0 ? s_max - s0 + 1 : 0);
+  };
+  const int c0 = candidates(i0), c1 = candidates(i1);
+  const bool second = n >= HB;
+  const int c = second ? c1 : c0;
+  const int head = h0 + (n & 7) < G ? h0 + (n & 7) : G - 1;
+  bf16x8 qf[KS];
+  {
+    const bf16_t* qp = Qs + (int64_t)(kv * G + head) * qsh + (second ? r1 : r0) * qst + q4 * 8;
+#pragma unroll
+    for (int kk = 0; kk < KS; ++kk) qf[kk] = *reinterpret_cast<const bf16x8*>(qp + kk * 32);
+  }
+  // Sixteen candidates from jb on of both rows to LDS: staged row m (first row) and 16 + m (second row) hold
+  // candidate jb + m, piece p of a row at p ^ (its swizzle key).
+  constexpr int PPR = D / 8, RPI = 64 / PPR;  // 16-byte pieces per row, rows per load
+  __shared__ __align__(16) bf16_t s_keys[4][32 * D];
+  bf16_t* const mine = s_keys[wave];
+  const bf16_t* const Kh = K + kv * kvsh;
+  auto swizzle = [](int m) { return D == 128 ? m & 15 : (m >> 1) & 7; };
+  // candidate tokens are top - (s+1)^root; a row without candidates takes any valid row, its own
+  const int some0 = c0 > 0 ? -1 : 0, some1 = c1 > 0 ? -1 : 0, top0 = i0 - some0, top1 = i1 - some1;
+  auto stage = [&](int jb) {
+#pragma unroll
+    for (int u = 0; u < 32 / RPI; ++u) {
+      const bool b = u * RPI >= 16;
+      const int m = (u * RPI & 15) + lane / PPR, cnt = b ? c1 : c0;
+      const int e = s0 + 1 + (jb + m < cnt ? jb + m : cnt - 1);
+      const int back = e * (root == 2 ? e : e * e);
+      const int t = b ? top1 - (back & some1) : top0 - (back & some0);
+      const bf16_t* src = Kh + (int64_t)t * kvst + ((lane % PPR) ^ swizzle(m)) * 8;
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
+                                       (__attribute__((address_space(3))) void*)(mine + u * 512), 16, 0, 0);
+    }
+  };
+  float v[KMAX];
+  int id[KMAX];
+#pragma unroll
+  for (int e = 0; e < KMAX; ++e) {
+    v[e] = -INFINITY;
+    id[e] = -1;
+  }
+  // (candidates come in ascending order per lane: a strictly larger score displaces an entry)
+  auto insert = [&](float x, int j, bool ties) {
+#pragma unroll
+    for (int e = KMAX - 1; e >= 0; --e) {
+      const int p = e > 0 ? e - 1 : 0;
+      const bool up = e > 0 && (x > v[p] || (ties && x == v[p] && j < id[p]));
+      const bool here = !up && (x > v[e] || (ties && x == v[e] && j < id[e]));
+      id[e] = up ? id[p] : (here ? j : id[e]);
+      v[e] = up ? v[p] : (here ? x : v[e]);
+    }
+  };
+  if (c1 > 0) stage(0);
+  for (int jb = 0; jb < c1; jb += 16) {  // c1 >= c0
+    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the batch is in LDS (this wavefront's own: no barrier)
+    asm volatile("" ::: "memory");
+    bf16x8 ka[KS], kb[KS];
+#pragma unroll
+    for (int kk = 0; kk < KS; ++kk) {
+      const int piece = ((4 * kk + q4) ^ swizzle(n)) * 8;
+      ka[kk] = *reinterpret_cast<const bf16x8*>(&mine[n * D + piece]);
+      kb[kk] = *reinterpret_cast<const bf16x8*>(&mine[(16 + n) * D + piece]);
+    }
+    // the operands are in registers before the next batch may overwrite them
+#pragma unroll
+    for (int kk = 0; kk < KS; ++kk) asm volatile("" : "+v"(ka[kk]), "+v"(kb[kk])::"memory");
+    if (jb + 16 < c1) stage(jb + 16);
+    f32x4 sa = {0.f, 0.f, 0.f, 0.f}, sb = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int kk = 0; kk < KS; ++kk) {
+      sa = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka[kk], qf[kk], sa, 0, 0, 0);
+      sb = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kb[kk], qf[kk], sb, 0, 0, 0);
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int j = jb + 4 * q4 + r;
+      const float x = second ? sb[r] : sa[r];
+      insert(j < c ? x : -INFINITY, j, false);
+    }
+  }
+#pragma unroll
+  for (int off = 16; off <= 32; off <<= 1) {
+    float ov[KMAX];
+    int oi[KMAX];
+#pragma unroll
+    for (int e = 0; e < KMAX; ++e) {
+      ov[e] = __shfl_xor(v[e], off, 64);
+      oi[e] = __shfl_xor(id[e], off, 64);
+    }
+#pragma unroll
+    for (int e = 0; e < KMAX; ++e) insert(oi[e] >= 0 ? ov[e] : -INFINITY, oi[e], oi[e] >= 0);
+  }
+  const int64_t r = second ? r0 + 1 : r0;
+  if (q4 == 0 && r < Lq && h0 + (n & 7) < G) {
+    const int64_t row = (int64_t)(kv * G + head) * Lq + r;
+    int32_t* oa = anchors + row * topk;
+    float* os = scores ? scores + row * topk : nullptr;
+    int kk = 0;
+#pragma unroll
+    for (int e = 0; e < KMAX; ++e) kk += (e < topk && id[e] >= 0) ? 1 : 0;
+    // nearest anchor first: a selected entry's slot is the number of selected entries with a lower stride index
+#pragma unroll
+    for (int e = 0; e < KMAX; ++e) {
+      if (e < topk && id[e] >= 0) {
+        int rank = 0;
+#pragma unroll
+        for (int e2 = 0; e2 < KMAX; ++e2) rank += (e2 < topk && id[e2] >= 0 && id[e2] < id[e]) ? 1 : 0;
+        oa[rank] = (int32_t)anchor_token_of(q_pos0 + r, (int64_t)s0 + id[e], root);
         if (os) os[rank] = v[e];
       }
     }
@@ -680,19 +838,36 @@ sl_status launch_anchor_search_rows(const Problem& pb, const void* Qs, const voi
                                     int32_t* anchors, float* scores, int64_t c_max, int s0,
                                     int root, hipStream_t st) {
   if (pb.topk <= 8) {  // key rows shared by the heads of a kv group, top-k lists in registers
-    constexpr int RPW = RowLayout<T, D>::RPW;
-    const dim3 grid((unsigned)((pb.Lq + 4 * RPW - 1) / (4 * RPW)), (unsigned)(pb.Hkv * ((pb.G + 7) / 8)));
+    const unsigned groups = (unsigned)(pb.Hkv * ((pb.G + 7) / 8));
     if (pb.prof_start) (void)hipEventRecord(pb.prof_start, st);
+    if constexpr (std::is_same<T, bf16_t>::value) {
+      const int blocks = (int)((pb.Lq + kAnchorRowsPerBlock - 1) / kAnchorRowsPerBlock);
+      const int chunk = 8 * kAnchorBlocksPerChunk;  // one chunk of each XCD
+      const dim3 grid((unsigned)((blocks + chunk - 1) / chunk * chunk), groups);
+#define SL_ANCHOR_MFMA(KM)                                                                                   \
+  hipLaunchKernelGGL((prefill_anchor_search_mfma_kernel<D, KM>), grid, dim3(256), 0, st,                     \
+                     static_cast<const bf16_t*>(Qs), static_cast<const bf16_t*>(K), anchors, scores, pb.Lq,  \
+                     pb.q_pos0, pb.G, pb.topk, s0, root, blocks, pb.qsh, pb.qst, pb.kvsh, pb.kvst)
+      if (pb.topk <= 2) SL_ANCHOR_MFMA(2);
+      else if (pb.topk <= 4) SL_ANCHOR_MFMA(4);
+      else SL_ANCHOR_MFMA(8);
+#undef SL_ANCHOR_MFMA
+      if (pb.prof_stop) (void)hipEventRecord(pb.prof_stop, st);
+      return hipGetLastError() == hipSuccess ? SL_OK : SL_ERR_LAUNCH;
+    } else {
+      constexpr int RPW = RowLayout<T, D>::RPW;
+      const dim3 grid((unsigned)((pb.Lq + 4 * RPW - 1) / (4 * RPW)), groups);
 #define SL_ANCHOR_GROUP(KM)                                                                               \
   hipLaunchKernelGGL((prefill_anchor_search_group_kernel<T, D, KM>), grid, dim3(256), 0, st,              \
                      static_cast<const T*>(Qs), static_cast<const T*>(K), anchors, scores, pb.Lq, pb.q_pos0, \
                      pb.G, pb.topk, s0, root, pb.qsh, pb.qst, pb.kvsh, pb.kvst)
-    if (pb.topk <= 2) SL_ANCHOR_GROUP(2);
-    else if (pb.topk <= 4) SL_ANCHOR_GROUP(4);
-    else SL_ANCHOR_GROUP(8);
+      if (pb.topk <= 2) SL_ANCHOR_GROUP(2);
+      else if (pb.topk <= 4) SL_ANCHOR_GROUP(4);
+      else SL_ANCHOR_GROUP(8);
 #undef SL_ANCHOR_GROUP
-    if (pb.prof_stop) (void)hipEventRecord(pb.prof_stop, st);
-    return hipGetLastError() == hipSuccess ? SL_OK : SL_ERR_LAUNCH;
+      if (pb.prof_stop) (void)hipEventRecord(pb.prof_stop, st);
+      return hipGetLastError() == hipSuccess ? SL_OK : SL_ERR_LAUNCH;
+    }
   }
   const int lds_per_wave = LaneMajor::make(c_max).lds_floats();
   int W = 4;

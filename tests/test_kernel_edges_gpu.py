@@ -166,3 +166,52 @@ def test_decode_entries_sharing_chunks_go_in_pairs(form, dtype, Hq, Hkv, S, A, k
     step = 2 ** -7 if dtype == torch.bfloat16 else 0.0
     diff = (many.float() - one.float()[None]).abs() - step * one.float().abs()[None]
     assert float(diff.max()) <= 1e-5
+
+
+@pytest.mark.parametrize("Hq,Hkv,D,L,k,w,root,Lq,q0", [
+    (8, 1, 128, 700, 2, 0, 2, None, 0),          # rows with no candidate, with one, with a batch and a remainder
+    (12, 1, 64, 3001, 4, 24, 2, 1501, 1500),     # more than 8 heads a group, D = 64, odd row count
+    (4, 4, 128, 40000, 8, 255, 2, 9, 39991),     # one head a group, many batches, lists of 8
+    (6, 2, 128, 9000, 3, 8, 3, 1030, 7970),      # cubes; rows past one chunk of the block order
+    (8, 2, 128, 20, 2, 1088, 2, None, 0),        # no row has a candidate
+])
+def test_anchor_search_on_the_matrix_cores(Hq, Hkv, D, L, k, w, root, Lq, q0):
+    """Batches of 16 candidates, pairs of rows and the lists' merge against fp64 scores: the selection by the
+    tie margin of the search tests, the scores to 1e-4 (fp32 sums of up to 128 exact products below 10)."""
+    from tests.test_parity_gpu import check_anchor_row
+    Q, K, _ = make(1000 + L, Hq, Hkv, L, D, torch.bfloat16, Lq=Lq, scale=0.5)
+    an, sc = B.sl_anchor_search_prefill(Q, K, k, w, q_pos0=q0, want_scores=True, search_root=root)
+    torch.cuda.synchronize()
+    Qn, Kn, an, sc = f64(Q), f64(K), an.cpu().numpy(), sc.cpu().numpy()
+    G, n = Hq // Hkv, Q.shape[1]
+    for h in range(Hq):
+        for r in sorted({0, 1, 2, 3, n // 2, n - 2, n - 1, *range(0, n, 97)}):
+            if not 0 <= r < n:
+                continue
+            cand = orc.anchor_candidates(q0 + r, w, root)
+            s = np.array([float(Qn[h, r] @ Kn[h // G, t]) for _, t in cand])
+            order = sorted(np.lexsort((np.arange(len(s)), -s))[:k].tolist())
+            want = [cand[j][1] for j in order] + [-1] * (k - len(order))
+            check_anchor_row(an[h, r].tolist(), want, cand, s, k, (h, r))
+            of = {t: x for (_, t), x in zip(cand, s)}
+            for t, x in zip(an[h, r], sc[h, r]):
+                assert (t < 0 and x == -np.inf) or abs(x - of[t]) <= 1e-4
+
+
+def test_anchor_search_ties_go_to_the_nearer_anchor():
+    """Every key one of three rows: nearly all candidates tie, across the four lanes of a column."""
+    L, k, w = 30000, 4, 24
+    Q, K, _ = make(1101, 8, 1, L, 128, torch.bfloat16, Lq=3)
+    base = K[0, :3].clone()
+    K[0] = base[torch.arange(L, device=DEV) % 3]
+    an, sc = B.sl_anchor_search_prefill(Q, K, k, w, q_pos0=L - 3, want_scores=True)
+    torch.cuda.synchronize()
+    an = an.cpu().numpy()
+    for r in range(3):
+        i = L - 3 + r
+        toks = np.array([t for _, t in orc.anchor_candidates(i, w, 2)])
+        s3 = f64(Q[:, r]) @ f64(base).T
+        for h in range(8):
+            s = s3[h][toks % 3]
+            pick = np.sort(np.lexsort((np.arange(len(s)), -s))[:k])
+            assert an[h, r].tolist() == toks[pick].tolist()
