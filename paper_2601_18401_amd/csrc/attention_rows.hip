@@ -31,7 +31,7 @@ __device__ __forceinline__ void merge_row_groups(AttendState<T, D>& st) {
   }
 }
 
-template <typename T, int D>
+template <typename T, int D, bool COND>
 __global__ __launch_bounds__(256) void prefill_attention_rows_kernel(
     const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V,
     const int32_t* __restrict__ idx, T* __restrict__ O, float* __restrict__ LSE, int64_t Lq,
@@ -43,7 +43,8 @@ __global__ __launch_bounds__(256) void prefill_attention_rows_kernel(
   using RL = RowLayout<T, D>;
   constexpr int EPL = RL::EPL, LPR = RL::LPR;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  if (only_if && *only_if == 0) return;
+  if (COND && *only_if == 0) return;
+  // (COND: a short grid loops over the rows; otherwise it has a wavefront for every row)
   for (int64_t row = (int64_t)blockIdx.x * 4 + wave; row < (int64_t)Hq * Lq; row += (int64_t)gridDim.x * 4) {
     const int h = (int)(row / Lq);
     const int64_t r = row % Lq, i = q_pos0 + r;
@@ -85,6 +86,7 @@ __global__ __launch_bounds__(256) void prefill_attention_rows_kernel(
       for (int e = 0; e < EPL; ++e) Elem<T>::store1(op + e, st.o[e] * inv);
       if (lane == 0) LSE[row] = (st.m + __log2f(st.l)) * kLn2;
     }
+    if (!COND) break;
   }
 }
 
@@ -93,7 +95,7 @@ __global__ __launch_bounds__(256) void prefill_attention_rows_kernel(
 // over span t and the local window with its own softmax, O = sum_t alpha_t A_t with
 // alpha = softmax of the slots' search scores; no valid slot: the window alone.  The window is
 // streamed once and its (m, l, o) state is merged into every span's state.
-template <typename T, int D>
+template <typename T, int D, bool COND>
 __global__ __launch_bounds__(256) void prefill_combined_rows_kernel(
     const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V,
     const int32_t* __restrict__ idx, const float* __restrict__ gate, T* __restrict__ O, int64_t Lq,
@@ -102,7 +104,8 @@ __global__ __launch_bounds__(256) void prefill_combined_rows_kernel(
   using RL = RowLayout<T, D>;
   constexpr int EPL = RL::EPL, LPR = RL::LPR;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  if (only_if && *only_if == 0) return;
+  if (COND && *only_if == 0) return;
+  // (COND: a short grid loops over the rows; otherwise it has a wavefront for every row)
   for (int64_t row = (int64_t)blockIdx.x * 4 + wave; row < (int64_t)Hq * Lq; row += (int64_t)gridDim.x * 4) {
     const int h = (int)(row / Lq);
     const int64_t r = row % Lq, i = q_pos0 + r;
@@ -155,6 +158,7 @@ __global__ __launch_bounds__(256) void prefill_combined_rows_kernel(
 #pragma unroll
       for (int e = 0; e < EPL; ++e) Elem<T>::store1(op + e, (any ? acc[e] : win.o[e]) * inv);
     }
+    if (!COND) break;
   }
 }
 
@@ -250,28 +254,35 @@ sl_status launch_anchor_rows(const Problem& pb, int64_t window, int b, int f, in
   return hipGetLastError() == hipSuccess ? SL_OK : SL_ERR_LAUNCH;
 }
 
-template <typename T, int D>
-sl_status launch_rows(const Problem& pb, const void* Q, const void* K, const void* V,
+template <typename T, int D, bool COND>
+sl_status launch_rows_as(const Problem& pb, const void* Q, const void* K, const void* V,
                       const int32_t* idx, void* O, float* LSE, hipStream_t st, const int* only_if) {
   const int64_t rows = (int64_t)pb.Hq * pb.Lq;
   // a conditional call, which nearly always ends at once, is a short grid that would loop over the rows
   const int64_t blocks = (rows + 3) / 4;
-  const dim3 grid((unsigned)(only_if && blocks > 2048 ? 2048 : blocks));
+  const dim3 grid((unsigned)(COND && blocks > 2048 ? 2048 : blocks));
   if (pb.prof_start) (void)hipEventRecord(pb.prof_start, st);
   if (pb.combined) {
-    hipLaunchKernelGGL((prefill_combined_rows_kernel<T, D>), grid, dim3(256), 0, st, static_cast<const T*>(Q), static_cast<const T*>(K),
+    hipLaunchKernelGGL((prefill_combined_rows_kernel<T, D, COND>), grid, dim3(256), 0, st, static_cast<const T*>(Q), static_cast<const T*>(K),
                        static_cast<const T*>(V), idx, pb.gate, static_cast<T*>(O), pb.Lq, pb.q_pos0,
                        pb.Hq, pb.G, pb.S, pb.A, pb.topk, pb.scale * kLog2e, pb.qsh, pb.qst, pb.kvsh,
                        pb.kvst, only_if);
     if (pb.prof_stop) (void)hipEventRecord(pb.prof_stop, st);
     return hipGetLastError() == hipSuccess ? SL_OK : SL_ERR_LAUNCH;
   }
-  hipLaunchKernelGGL((prefill_attention_rows_kernel<T, D>), grid, dim3(256), 0, st, static_cast<const T*>(Q), static_cast<const T*>(K),
+  hipLaunchKernelGGL((prefill_attention_rows_kernel<T, D, COND>), grid, dim3(256), 0, st, static_cast<const T*>(Q), static_cast<const T*>(K),
                      static_cast<const T*>(V), idx, static_cast<T*>(O), LSE, pb.Lq, pb.q_pos0,
                      pb.Hq, pb.G, pb.S, pb.A, pb.topk, pb.scale * kLog2e, pb.qsh, pb.qst, pb.kvsh,
                      pb.kvst, only_if);
   if (pb.prof_stop) (void)hipEventRecord(pb.prof_stop, st);
   return hipGetLastError() == hipSuccess ? SL_OK : SL_ERR_LAUNCH;
+}
+
+template <typename T, int D>
+sl_status launch_rows(const Problem& pb, const void* Q, const void* K, const void* V, const int32_t* idx, void* O,
+                      float* LSE, hipStream_t st, const int* only_if) {
+  return only_if ? launch_rows_as<T, D, true>(pb, Q, K, V, idx, O, LSE, st, only_if)
+                 : launch_rows_as<T, D, false>(pb, Q, K, V, idx, O, LSE, st, nullptr);
 }
 
 }  // namespace
