@@ -816,7 +816,8 @@ __device__ __forceinline__ void flash_tile(const FlashArgs& a, char* lds, const 
         const int64_t at = row_out[row];
         const uint4 v = *reinterpret_cast<const uint4*>(&fst[row * 64 + ((piece ^ (row & 15)) << 2)]);
         if (at >= 0) {
-          *reinterpret_cast<uint4*>(b->part_of + at * D + half * 64 + piece * 4) = v;
+          // past the caches, like the bf16 partials: they are gigabytes, the K/V tiles keep the L2
+          store16_stream(b->part_of + at * D + half * 64 + piece * 4, v);
           if (half == 0 && piece == 0) b->part_lse[at] = row_lse[row];
         }
       }
@@ -929,7 +930,7 @@ __device__ __forceinline__ void flash_tile(const FlashArgs& a, char* lds, const 
     for (int u = 0; u < 8; ++u) {
       const int piece = lane & 15;
       if (outs[u] >= 0) {
-        *reinterpret_cast<uint4*>(a.part_o + outs[u] * HD + piece * 8) = vals[u];
+        store16_stream(a.part_o + outs[u] * HD + piece * 8, vals[u]);
         if (piece == 0) a.part_lse[outs[u]] = lses[u];
       }
     }
