@@ -18,8 +18,7 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 constexpr int HD = 128;
 constexpr int TMQ = 128;        // query rows per workgroup (4 wavefronts x 32 columns)
-constexpr int TNS = 64;         // span keys per staged chunk
-constexpr int KSTR = HD + 8;    // LDS row stride (bf16 elements): conflict-free 16-byte reads
+constexpr int TNS = 32;         // span keys per staged chunk
 constexpr int kEmpty = 0x7fffffff;
 
 // Running top-K VALUES of the candidates a lane has seen, sorted descending.  Inserting x is one
@@ -53,21 +52,26 @@ struct TopVals {
 // the compare-and-select chains that carrying the indices along would need.
 // WS: the scores of the selected spans are written too (their list costs LDS, which limits the
 // resident workgroups; most callers only want the indices).
-// The kernel is bound by the latency of its stages (two barriers and a global -> register -> LDS
-// hand-over per 64 span keys), so resident workgroups count: without the score list and with
-// topk <= 8 the registers are capped at 128 for a fourth workgroup per compute unit (-8 % at 256K
-// tokens, -14 % at 64K; a fifth would spill).
+// Stages of 32 span keys come by direct global -> LDS loads into two buffers, one barrier each: while one is
+// scored the next is on its way.  (64 keys through registers with two barriers, 128 VGPRs: 65536 rows x 32
+// heads, 256 spans, top-8 334 -> 318 us, 5000 rows 22.7 -> 17.2; stages of 64 in two buffers leave three
+// workgroups per compute unit instead of five, 390 us.)  Lists of at most 4 spans have their own KMAX: half
+// of the median instructions (top-4 312 -> 267 us, with scores 377 -> 281).
 template <int KMAX, bool WS>
-__global__ __launch_bounds__(256, (KMAX == 8 && !WS) ? 4 : 1) void prefill_search_mfma_kernel(
+__global__ __launch_bounds__(256, (KMAX <= 4 || (KMAX == 8 && !WS)) ? 4 : 1) void prefill_search_mfma_kernel(
     const bf16_t* __restrict__ Qs, const bf16_t* __restrict__ K, const bf16_t* __restrict__ Ks,
     int32_t* __restrict__ idx, float* __restrict__ scores, int64_t Lq, int64_t q_pos0, int G, int S,
     int topk, int64_t n, int64_t qsh, int64_t qst, int64_t kvsh, int64_t kvst) {
   constexpr int CAP = 3 * KMAX;  // list entries per column: < KMAX above T, <= KMAX at T from each lane
-  __shared__ __align__(16) bf16_t s_k[TNS * KSTR];
+  // Two stages, dynamic: for a static array that direct loads are filling the compiler waits for all of
+  // them in front of the next read of it, other stage or not.
+  extern __shared__ __align__(16) char s_stage[];
+  bf16_t* const s_k = reinterpret_cast<bf16_t*>(s_stage);
   __shared__ int s_cnt[TMQ];
   __shared__ int s_j[TMQ][CAP + 1];  // odd row stride: the lanes of a wavefront read their own rows
   __shared__ float s_x[WS ? TMQ : 1][CAP + 1];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int uwave = __builtin_amdgcn_readfirstlane(wave);
   const int qc = lane & 31, hf = lane >> 5;
   const int col = wave * 32 + qc;
   const int tiles_per_head = (int)((Lq + TMQ - 1) / TMQ);
@@ -92,30 +96,28 @@ __global__ __launch_bounds__(256, (KMAX == 8 && !WS) ? 4 : 1) void prefill_searc
   // Walks the candidate spans in tiles of 32 and hands the lane's 16 scores of a tile, in
   // ascending span order, to f(score, span index); scores of spans >= c_q come as -inf.
   auto for_each_candidate = [&](auto f) {
-    // 64 span keys per stage, 16 lanes x 16 bytes per key; the next stage's keys are fetched into
-    // registers while the current stage is scored
-    uint4 pre[4];
-    auto fetch = [&](int j0) {
+    // TNS span keys per stage by direct global -> LDS loads, 16 lanes x 16 bytes per key (1 KB per load, pieces
+    // swizzled for the operand reads); the next stage is on its way while the current one is scored
+    auto stage = [&](int j0, int buf) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int id = tid + 256 * i, row = id >> 4, piece = id & 15;
+      for (int i = 0; i < TNS / 16; ++i) {
+        const int blk = uwave * (TNS / 16) + i, row = blk * 4 + (lane >> 4), piece = (lane & 15) ^ (row & 15);
         int64_t j = j0 + row;
         j = j < c_max ? j : c_max - 1;
         const bf16_t* src = Ks ? Ks + ((int64_t)kv * n + j) * HD : K + kv * kvsh + ((j + 1) * S - 1) * kvst;
-        pre[i] = load16(src + piece * 8);
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src + piece * 8),
+                                         (__attribute__((address_space(3))) void*)(s_k + buf * TNS * HD + blk * 512), 16, 0, 0);
       }
     };
-    if (c_max > 0) fetch(0);
-    for (int j0 = 0; j0 < c_max; j0 += TNS) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int id = tid + 256 * i, row = id >> 4, piece = id & 15;
-        *reinterpret_cast<uint4*>(&s_k[row * KSTR + piece * 8]) = pre[i];
-      }
+    if (c_max > 0) stage(0, 0);
+    int buf = 0;
+    for (int j0 = 0; j0 < c_max; j0 += TNS, buf ^= 1) {
+      // every wavefront is done with the other buffer, and this one's loads have arrived
+      __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
       __syncthreads();
-      if (j0 + TNS < c_max) fetch(j0 + TNS);
+      if (j0 + TNS < c_max) stage(j0 + TNS, buf ^ 1);
 #pragma unroll
-      for (int sub = 0; sub < 2; ++sub) {
+      for (int sub = 0; sub < TNS / 32; ++sub) {
         if (j0 + 32 * sub < c_max) {  // uniform over the workgroup
           f32x16 s;
 #pragma unroll
@@ -123,7 +125,8 @@ __global__ __launch_bounds__(256, (KMAX == 8 && !WS) ? 4 : 1) void prefill_searc
 #pragma unroll
           for (int kk = 0; kk < 8; ++kk) {
             const bf16x8 ka =
-                *reinterpret_cast<const bf16x8*>(&s_k[(32 * sub + qc) * KSTR + kk * 16 + hf * 8]);
+                *reinterpret_cast<const bf16x8*>(
+                    &s_k[buf * TNS * HD + (32 * sub + qc) * HD + (((2 * kk + hf) ^ (qc & 15)) << 3)]);
             s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka, qf[kk], s, 0, 0, 0);
           }
           // causal: only complete spans below the query's own.  A tile that ends at or below the
@@ -140,8 +143,8 @@ __global__ __launch_bounds__(256, (KMAX == 8 && !WS) ? 4 : 1) void prefill_searc
           }
         }
       }
-      __syncthreads();
     }
+    __syncthreads();  // the next walk (or the lists' readers) may touch what this one used
   };
 
   // ---- pass 1: the column's top-k values
@@ -225,12 +228,12 @@ sl_status launch(const Problem& pb, const void* Qs, const void* K, const void* K
   if (pb.prof_start) (void)hipEventRecord(pb.prof_start, st);
   if (scores)
     hipLaunchKernelGGL((prefill_search_mfma_kernel<KMAX, true>), dim3(pb.Hq * tiles_per_head), dim3(256),
-                       0, st, static_cast<const bf16_t*>(Qs), static_cast<const bf16_t*>(K),
+                       2 * TNS * HD * sizeof(bf16_t), st, static_cast<const bf16_t*>(Qs), static_cast<const bf16_t*>(K),
                        static_cast<const bf16_t*>(Ks), idx, scores, pb.Lq, pb.q_pos0, pb.G, pb.S,
                        pb.topk, pb.n, pb.qsh, pb.qst, pb.kvsh, pb.kvst);
   else
     hipLaunchKernelGGL((prefill_search_mfma_kernel<KMAX, false>), dim3(pb.Hq * tiles_per_head), dim3(256),
-                       0, st, static_cast<const bf16_t*>(Qs), static_cast<const bf16_t*>(K),
+                       2 * TNS * HD * sizeof(bf16_t), st, static_cast<const bf16_t*>(Qs), static_cast<const bf16_t*>(K),
                        static_cast<const bf16_t*>(Ks), idx, scores, pb.Lq, pb.q_pos0, pb.G, pb.S,
                        pb.topk, pb.n, pb.qsh, pb.qst, pb.kvsh, pb.kvst);
   if (pb.prof_stop) (void)hipEventRecord(pb.prof_stop, st);
@@ -245,6 +248,7 @@ bool prefill_search_mfma_supported(const Problem& pb) {
 
 sl_status prefill_search_mfma(const Problem& pb, const void* Qs, const void* K, const void* Ks,
                               int32_t* idx, float* scores, hipStream_t st) {
+  if (pb.topk <= 4) return launch<4>(pb, Qs, K, Ks, idx, scores, st);
   if (pb.topk <= 8) return launch<8>(pb, Qs, K, Ks, idx, scores, st);
   if (pb.topk <= 16) return launch<16>(pb, Qs, K, Ks, idx, scores, st);
   return launch<32>(pb, Qs, K, Ks, idx, scores, st);

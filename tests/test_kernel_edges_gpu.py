@@ -215,3 +215,27 @@ def test_anchor_search_ties_go_to_the_nearer_anchor():
             s = s3[h][toks % 3]
             pick = np.sort(np.lexsort((np.arange(len(s)), -s))[:k])
             assert an[h, r].tolist() == toks[pick].tolist()
+
+
+@pytest.mark.parametrize("k,scores", [(1, False), (4, True), (5, False), (8, True), (9, False)])
+@pytest.mark.parametrize("n", [1, 31, 32, 33, 64, 97])
+def test_prefill_search_stages_and_list_lengths(n, k, scores):
+    """Candidate counts around the 32-key stages for every list length's instantiation, keys packed and read
+    from the cache, against the oracle."""
+    from tests.test_parity_gpu import check_idx
+    S = 4
+    L = S * n + 2
+    Q, K, _ = make(1200 + n, 4, 2, L, 128, torch.bfloat16)
+    Ks = B.sl_span_keys(K, S)
+    r = B.sl_span_search_prefill(Q, K, Ks, S, k, want_scores=scores)
+    idx = r[0] if scores else r
+    again = B.sl_span_search_prefill(Q, K, None, S, k)
+    torch.cuda.synchronize()
+    assert torch.equal(idx, again)
+    rows = [(h, r) for h in range(4) for r in sorted({0, S - 1, S, L // 2, L - 2, L - 1, *range(0, L, 13)}) if r < L]
+    check_idx(idx, Q, Ks, S, k, 0, rows)
+    if scores:
+        q, kn, sc, ix = f64(Q), f64(Ks), r[1].cpu().numpy(), idx.cpu().numpy()
+        for h, row in rows:
+            for j, x in zip(ix[h, row], sc[h, row]):
+                assert (j < 0 and x == -np.inf) or abs(x - q[h, row] @ kn[h // 2, j]) <= 1e-3
