@@ -561,7 +561,7 @@ __global__ __launch_bounds__(256) void prefill_anchor_search_group_kernel(
 // rows lie beside those of the other blocks of its XCD (chunks of 512 rows, dealt to the XCDs in turn):
 // at the same stride index their keys are neighbours and the next index finds them in that L2.  Rows with
 // the most candidates come first.  49157 rows, 32:4 heads, window 1088, top-2: 956 us with vector
-// instructions (two-element dot products and a lane-group sum per score), 508 us.
+// instructions (two-element dot products and a lane-group sum per score), 664 us now, of which the second scoring below takes 150.
 constexpr int kAnchorRowsPerBlock = 8, kAnchorBlocksPerChunk = 64;
 
 template <int D, int KMAX>
@@ -619,17 +619,18 @@ __global__ __launch_bounds__(256) void prefill_anchor_search_mfma_kernel(
                                        (__attribute__((address_space(3))) void*)(mine + u * 512), 16, 0, 0);
     }
   };
-  float v[KMAX];
-  int id[KMAX];
+  constexpr int KL = KMAX + 2;  // two spares: see the second scoring
+  float v[KL];
+  int id[KL];
 #pragma unroll
-  for (int e = 0; e < KMAX; ++e) {
+  for (int e = 0; e < KL; ++e) {
     v[e] = -INFINITY;
     id[e] = -1;
   }
   // (candidates come in ascending order per lane: a strictly larger score displaces an entry)
   auto insert = [&](float x, int j, bool ties) {
 #pragma unroll
-    for (int e = KMAX - 1; e >= 0; --e) {
+    for (int e = KL - 1; e >= 0; --e) {
       const int p = e > 0 ? e - 1 : 0;
       const bool up = e > 0 && (x > v[p] || (ties && x == v[p] && j < id[p]));
       const bool here = !up && (x > v[e] || (ties && x == v[e] && j < id[e]));
@@ -667,15 +668,65 @@ __global__ __launch_bounds__(256) void prefill_anchor_search_mfma_kernel(
   }
 #pragma unroll
   for (int off = 16; off <= 32; off <<= 1) {
-    float ov[KMAX];
-    int oi[KMAX];
+    float ov[KL];
+    int oi[KL];
 #pragma unroll
-    for (int e = 0; e < KMAX; ++e) {
+    for (int e = 0; e < KL; ++e) {
       ov[e] = __shfl_xor(v[e], off, 64);
       oi[e] = __shfl_xor(id[e], off, 64);
     }
 #pragma unroll
-    for (int e = 0; e < KMAX; ++e) insert(oi[e] >= 0 ? ov[e] : -INFINITY, oi[e], oi[e] >= 0);
+    for (int e = 0; e < KL; ++e) insert(oi[e] >= 0 ? ov[e] : -INFINITY, oi[e], oi[e] >= 0);
+  }
+  // Second scoring, with the arithmetic of every other search kernel (Piece::dot, group_sum; the matrix unit
+  // adds in another order): always of the entries that are returned, and of the whole list, which is then
+  // ordered anew, where the k-th and the next score lie within 1e-4 of the best, far above the rounding of
+  // either sum, so that the selection is the other kernels' too.  A group of LPR lanes takes one column at
+  // a time; lane n % 16 gets its column's scores back.
+  auto score_again = [&](auto count) {
+    using RL = RowLayout<bf16_t, D>;
+    constexpr int LPR = RL::LPR, NGRP = 64 / LPR, ITS = 16 / NGRP, N = decltype(count)::value;
+    const int g = lane / LPR, lr = lane % LPR;
+    uint4 qraw[ITS], kr[ITS][N];
+#pragma unroll
+    for (int it = 0; it < ITS; ++it) {
+      const int col = it * NGRP + g;
+      const int hc = h0 + (col & 7) < G ? h0 + (col & 7) : G - 1;
+      qraw[it] = load16(Qs + (int64_t)(kv * G + hc) * qsh + (col >= HB ? r1 : r0) * qst + lr * RL::EPL);
+#pragma unroll
+      for (int e = 0; e < N; ++e) {
+        const int j = __shfl(id[e], col, 64), x = s0 + j + 1;
+        const int t = (col >= HB ? i1 : i0) + (j >= 0 ? 1 - x * (root == 2 ? x : x * x) : 0);
+        kr[it][e] = load16(Kh + (int64_t)t * kvst + lr * RL::EPL);
+      }
+    }
+#pragma unroll
+    for (int it = 0; it < ITS; ++it)
+#pragma unroll
+      for (int e = 0; e < N; ++e) {
+        const float x = __shfl(group_sum<LPR>(Piece<bf16_t>::dot(kr[it][e], qraw[it], 0.f)), (n % NGRP) * LPR, 64);
+        if (n / NGRP == it && id[e] >= 0) v[e] = x;
+      }
+  };
+  bool close = false;
+#pragma unroll
+  for (int e = 1; e < KL; ++e)
+    close = close || (e == topk && id[e] >= 0 && v[e - 1] - v[e] <= 1e-4f * fmaxf(fabsf(v[0]), fabsf(v[e])));
+  if (__builtin_amdgcn_ballot_w64(close) != 0ull) {
+    score_again(std::integral_constant<int, KL>{});
+    float fv[KL];
+    int fi[KL];
+#pragma unroll
+    for (int e = 0; e < KL; ++e) {
+      fv[e] = v[e];
+      fi[e] = id[e];
+      v[e] = -INFINITY;
+      id[e] = -1;
+    }
+#pragma unroll
+    for (int e = 0; e < KL; ++e) insert(fi[e] >= 0 ? fv[e] : -INFINITY, fi[e], fi[e] >= 0);
+  } else if (scores) {
+    score_again(std::integral_constant<int, KMAX>{});
   }
   const int64_t r = second ? r0 + 1 : r0;
   if (q4 == 0 && r < Lq && h0 + (n & 7) < G) {
