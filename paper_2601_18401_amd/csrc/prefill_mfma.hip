@@ -1347,12 +1347,15 @@ __global__ __launch_bounds__(256) void merge_combined_kernel(
 #pragma unroll
   for (int s = 0; s < KMAX; ++s) {
     if (okmask & (1u << s)) {  // valid slot
+      // an empty span has lse = -inf.  (fp32 partials: an lse that is NaN, from a key that is not finite, goes
+      // on into the output, which then marks the call.)
+      const bool has = sizeof(P) == 4 ? !(ls[s] == -INFINITY) : ls[s] > -INFINITY;
       const float M = fmaxf(ls[s], lw);
-      const float wa = ls[s] > -INFINITY ? __expf(ls[s] - M) : 0.f, wb = __expf(lw - M);
+      const float wa = has ? __expf(ls[s] - M) : 0.f, wb = __expf(lw - M);
       const float a = __expf(gs[s] - gmax);
       const float fa = a * wa / (wa + wb), fb = a * wb / (wa + wb);
       asum += a;
-      Elem<P>::unpack(ls[s] > -INFINITY ? ov[s] : make_uint4(0, 0, 0, 0), f);
+      Elem<P>::unpack(has ? ov[s] : make_uint4(0, 0, 0, 0), f);
 #pragma unroll
       for (int e = 0; e < E; ++e) acc[e] = fmaf(fa, f[e], fmaf(fb, fw[e], acc[e]));
     }

@@ -1,4 +1,5 @@
 """Edges of the prefill kernels' tiles, units and list lengths, against the oracle."""
+import ctypes
 import math
 
 import numpy as np
@@ -67,31 +68,43 @@ FINE = [
 ]
 
 
+def row_form(Q, K, V, idx, sc, S, q_pos0=0, span_stride=0):
+    """The row-stationary kernels, which a call without a workspace runs: (O, LSE), or O where sc is given."""
+    p = B.make_params(Q, K, S, idx.shape[2], q_pos0, 0.0, span_stride)
+    ptr = lambda t: ctypes.c_void_p(t.data_ptr())
+    R, RL = torch.empty_like(Q), torch.empty(Q.shape[:2], dtype=torch.float32, device=DEV)
+    stream = ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    if sc is None:
+        st = B.load().sl_span_attention_prefill(ctypes.byref(p), ptr(Q), ptr(K), ptr(V), ptr(idx), ptr(R), ptr(RL),
+                                                None, 0, stream)
+    else:
+        st = B.load().sl_span_attention_combined_prefill(ctypes.byref(p), ptr(Q), ptr(K), ptr(V), ptr(idx), ptr(sc),
+                                                         ptr(R), None, 0, stream)
+    assert st == B.SL_OK
+    return (R, RL) if sc is None else R
+
+
+def takes_matrix_cores(Q, K, S, k, q_pos0=0, span_stride=0):
+    return B.workspace_bytes(B.make_params(Q, K, S, k, q_pos0, 0.0, span_stride), B.OP_ATTENTION_PREFILL) > 0
+
+
 @pytest.mark.parametrize("Hq,Hkv,L,D,S,A,k,form,q_pos0,Lq", FINE)
 def test_any_span_length_on_the_matrix_cores(Hq, Hkv, L, D, S, A, k, form, q_pos0, Lq):
     """Span lengths that are no multiple of 64 and D = 64: the matrix-core form with split weights against the
     row-stationary kernels (a workspace of zero bytes selects them), which the oracle covers.  Both keep the
     weights and partial sums to 16 bits of mantissa and more (errors below 1e-4) and round the output to bf16
     once: they differ by at most one bf16 step of it, 2^-7 relative."""
-    import ctypes
     stride = 0 if A == S else A
     std = 1.0 if form == "joint" else 0.35
     Q, K, V = make(700 + L + S, Hq, Hkv, L, D, torch.bfloat16, Lq=Lq, scale=std)
     idx, sc = B.sl_span_search_prefill(Q, K, None, A, k, q_pos0=q_pos0, want_scores=True)
-    p = B.make_params(Q, K, S, k, q_pos0, 0.0, stride)
-    assert B.workspace_bytes(p, B.OP_ATTENTION_PREFILL) > 0     # the matrix-core form takes this call
-    ptr = lambda t: ctypes.c_void_p(t.data_ptr())
-    R, RL = torch.empty_like(Q), torch.empty(Q.shape[:2], dtype=torch.float32, device=DEV)
-    stream = ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    assert takes_matrix_cores(Q, K, S, k, q_pos0, stride)
     if form == "joint":
         O, LSE = B.sl_span_attention_prefill(Q, K, V, idx, S, q_pos0=q_pos0, span_stride=stride)
-        st = B.load().sl_span_attention_prefill(ctypes.byref(p), ptr(Q), ptr(K), ptr(V), ptr(idx), ptr(R), ptr(RL),
-                                                None, 0, stream)
+        R, RL = row_form(Q, K, V, idx, None, S, q_pos0, stride)
     else:
         O = B.sl_span_attention_combined_prefill(Q, K, V, idx, sc, S, q_pos0=q_pos0, span_stride=stride)
-        st = B.load().sl_span_attention_combined_prefill(ctypes.byref(p), ptr(Q), ptr(K), ptr(V), ptr(idx), ptr(sc),
-                                                         ptr(R), None, 0, stream)
-    assert st == B.SL_OK
+        R = row_form(Q, K, V, idx, sc, S, q_pos0, stride)
     torch.cuda.synchronize()
     o, r = O.float(), R.float()
     assert float(((o - r).abs() - r.abs() * 2 ** -7).max()) <= 1e-4
@@ -100,21 +113,34 @@ def test_any_span_length_on_the_matrix_cores(Hq, Hkv, L, D, S, A, k, form, q_pos
         assert float((LSE - RL).abs().max()) <= 1e-5
 
 
-@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
-def test_any_span_length_keeps_what_is_not_finite_to_the_rows_that_attend_it(bad):
-    """A V row that is not finite reaches the rows that attend it and no others, as in the row-stationary form."""
-    Hq, Hkv, L, D, S, k = 8, 2, 6000, 128, 77, 8
-    Q, K, V = make(801, Hq, Hkv, L, D, torch.bfloat16)
-    idx = B.sl_span_search_prefill(Q, K, None, S, k)
-    t = 77 * 40 + 30
-    V[0, t, 5] = bad
-    O, _ = B.sl_span_attention_prefill(Q, K, V, idx, S)
+@pytest.mark.parametrize("form", ["joint", "gated"])
+@pytest.mark.parametrize("span", [12, 40])     # a span that lies in no row's window; one that does
+@pytest.mark.parametrize("which,bad", [("V", float("nan")), ("V", float("inf")), ("K", float("nan")),
+                                       ("K", float("inf")), ("K", float("-inf"))])
+def test_any_span_length_keeps_what_is_not_finite_to_the_rows_that_attend_it(which, bad, span, form):
+    """A K or V row that is not finite reaches the rows that attend it and no others, as in the row-stationary
+    form.  (An infinite key leaves those rows finite whose score it sends to -inf.)"""
+    Hq, Hkv, L, D, S, k, q0 = 8, 2, 6000, 128, 77, 8, 2000
+    Q, K, V = make(801, Hq, Hkv, L, D, torch.bfloat16, Lq=L - q0, scale=1.0 if form == "joint" else 0.35)
+    idx, sc = B.sl_span_search_prefill(Q, K, None, S, k, q_pos0=q0, want_scores=True)
+    assert takes_matrix_cores(Q, K, S, k, q0)
+    t = S * span + 30
+    (K if which == "K" else V)[0, t, 5] = bad
+    if form == "joint":
+        O, R = B.sl_span_attention_prefill(Q, K, V, idx, S, q_pos0=q0)[0], row_form(Q, K, V, idx, None, S, q0)[0]
+    else:
+        O = B.sl_span_attention_combined_prefill(Q, K, V, idx, sc, S, q_pos0=q0)
+        R = row_form(Q, K, V, idx, sc, S, q0)
     torch.cuda.synchronize()
-    pos = torch.arange(L, device=DEV)
-    G = Hq // Hkv
+    finite = torch.isfinite(O.float()).all(dim=2)
+    assert torch.equal(finite, torch.isfinite(R.float()).all(dim=2))
+    pos = q0 + torch.arange(L - q0, device=DEV)
     attends = (idx == t // S).any(dim=2) | ((pos // S == t // S) & (pos >= t))[None, :]
-    attends[G:] = False
-    assert torch.equal(~torch.isfinite(O.float()).all(dim=2), attends)
+    attends[Hq // Hkv:] = False
+    if which == "V" or math.isnan(bad):
+        assert torch.equal(~finite, attends)
+    else:
+        assert not bool((~finite & ~attends).any())
 
 
 @pytest.mark.parametrize("form,dtype,Hq,Hkv,S,A,k", [
