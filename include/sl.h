@@ -112,7 +112,9 @@ size_t sl_workspace_bytes(const sl_params* p, int op /* sl_op */);
  * (single-sequence entry points): that call records `start` immediately before, and `stop`
  * immediately after, its dominant kernel (the K/V-streaming kernel of span-attention, the scoring
  * kernel of span-search; the decode span-attention entry point attaches them to that kernel's
- * dispatch, so that they hold the kernel's own begin and end timestamps), and disarms them.
+ * dispatch, so that they hold the kernel's own begin and end timestamps), and disarms them.  A
+ * prefill that runs in several passes over the kv heads records `start` in the first pass and
+ * `stop` in the last.
  * Passing NULL for either disarms.  Do not arm while the stream is capturing. */
 void sl_set_profile_events(void* start, void* stop);
 

@@ -1729,7 +1729,9 @@ sl_status fine_pass(const Problem& pb, const DeviceSetup& dev, const bf16_t* Q, 
   // A V row that is not finite meets zero weights of rows that do not attend it (the later rows of a window
   // tile, the rows of clipped spans): where any output is not finite the row-stationary kernels, which
   // never touch such a row, compute the pass again.
-  return prefill_attention_rows(pb, Q, K, V, idx, O, LSE, st, flag);
+  Problem again = pb;
+  again.prof_start = again.prof_stop = nullptr;  // (the events hold the routed kernel)
+  return prefill_attention_rows(again, Q, K, V, idx, O, LSE, st, flag);
 }
 
 template <int D>
@@ -1740,7 +1742,8 @@ sl_status fine_all(const Problem& pb, const void* Q, const void* K, const void* 
   const int step = fine_heads(pb);
   for (int kv = 0; kv < pb.Hkv; kv += step) {
     Problem q = fine_part(pb, pb.Hkv - kv < step ? pb.Hkv - kv : step);
-    if (kv > 0) q.prof_start = q.prof_stop = nullptr;
+    if (kv > 0) q.prof_start = nullptr;
+    if (kv + step < pb.Hkv) q.prof_stop = nullptr;
     const int64_t h = (int64_t)kv * pb.G, row = h * pb.Lq;
     if (pb.gate) q.gate = pb.gate + row * pb.topk;
     const sl_status s = fine_pass<D>(q, dev, static_cast<const bf16_t*>(Q) + h * pb.qsh,

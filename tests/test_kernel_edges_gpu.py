@@ -113,6 +113,24 @@ def test_any_span_length_on_the_matrix_cores(Hq, Hkv, L, D, S, A, k, form, q_pos
         assert float((LSE - RL).abs().max()) <= 1e-5
 
 
+def test_armed_events_hold_the_routed_kernel_of_any_span_length():
+    """The routed kernel is more than half of this call; the conditional recomputation behind it, which ends at
+    once, is some microseconds."""
+    Q, K, V = make(800, 32, 4, 12000, 128, torch.bfloat16)
+    idx = B.sl_span_search_prefill(Q, K, None, 110, 8)
+    assert takes_matrix_cores(Q, K, 110, 8)
+    ev = [torch.cuda.Event(enable_timing=True) for _ in range(4)]
+    for e in ev:
+        e.record()                      # creates the handles
+    for _ in range(3):
+        ev[0].record()
+        B.sl_span_attention_prefill(Q, K, V, idx, 110, prof=(ev[1].cuda_event, ev[2].cuda_event))
+        ev[3].record()
+        torch.cuda.synchronize()
+    whole, kernel = ev[0].elapsed_time(ev[3]), ev[1].elapsed_time(ev[2])
+    assert 0.3 * whole < kernel < whole, (kernel, whole)
+
+
 @pytest.mark.parametrize("form", ["joint", "gated"])
 @pytest.mark.parametrize("span", [12, 40])     # a span that lies in no row's window; one that does
 @pytest.mark.parametrize("which,bad", [("V", float("nan")), ("V", float("inf")), ("K", float("nan")),
