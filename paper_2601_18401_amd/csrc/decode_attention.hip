@@ -151,24 +151,26 @@ __device__ __forceinline__ void decode_split_body(
   // (equal anchors, or merely overlapping spans).  The entries that share a chunk go in pairs, in the
   // order of the group's index rows: the first of a pair computes the second's partial too, whose
   // workgroup leaves at once.  (One owner for all of them took the entries one after the other, about a
-  // microsecond each, on the critical path.)  Needs the group's G * topk indices in one pass of
+  // microsecond each, on the critical path.)  Needs the group's G * topk indices in four passes of
   // a wavefront (larger groups: every entry reads its own rows).  When the wave's rows fit one batch they
   // stay in registers and both entries are computed from them; otherwise (and for clipped overlapping
   // grid spans, whose range differs per entry) they are read again, through the L2.  The local window,
-  // which all G heads attend, is left to the caches: its G workgroups run on one XCD, and one workgroup
-  // serving the group head by head measured 58.5 us per step at 1M against 57.6.
+  // which all G heads attend, is left to the caches: its G workgroups run on one XCD.
   constexpr int kShareWords = 4;  // up to 256 (head, slot) entries per kv head
   const bool dedup = share_spans && slot < topk && G * topk <= 64 * kShareWords && G > 1;
-  unsigned long long share[kShareWords] = {0ull, 0ull, 0ull, 0ull};
   const int my_entry = (h - kv * G) * topk + slot;
-  bool multi = false;
+  int partner = -1;  // the entry whose partial is computed here too
   if (dedup && (!AG || t0 < t1)) {
-    // every wavefront builds the masks by itself (no LDS, no barrier): lane l looks at entries
-    // l, l + 64, ... of the group's index rows, which are contiguous
+    // Every wavefront builds the masks by itself (no LDS, no barrier): lane l looks at entries
+    // l, l + 64, ... of the group's index rows, which are contiguous.  This stands in front of every
+    // workgroup's loads, so words without entries are passed over (taking all four, and a 64-bit mask of
+    // the pair through the loop below, cost the 1M step 0.5 %).
     const int64_t jmine = idx[(int64_t)h * topk + slot];
-    int rank = 0, partner = -1;  // entries that share the chunk in front of this one; the one behind it
+    const int mine = my_entry >> 6;
+    int rank = 0;  // entries that share the chunk in front of this one
 #pragma unroll
-    for (int w = kShareWords - 1; w >= 0; --w) {
+    for (int w = 0; w < kShareWords; ++w) {
+      if (64 * w >= G * topk) break;
       const int e = 64 * w + lane;
       int64_t jother = -1;
       if (e < G * topk) jother = idx[(int64_t)kv * G * topk + e];
@@ -181,21 +183,14 @@ __device__ __forceinline__ void decode_split_body(
         same = jmine >= 0 && jmine < c && jother == jmine;
       }
       const unsigned long long all = __ballot(same);
-      const unsigned long long me = (my_entry >> 6) == w ? 1ull << (my_entry & 63) : 0ull;
-      const unsigned long long front = (my_entry >> 6) == w ? all & (me - 1ull) : (my_entry >> 6) > w ? all : 0ull;
-      const unsigned long long behind = all & ~front & ~me;
+      const unsigned long long front = w < mine ? all : w == mine ? all & ((1ull << (my_entry & 63)) - 1ull) : 0ull;
+      const unsigned long long behind = w > mine ? all : w == mine ? (all >> (my_entry & 63)) & ~1ull : 0ull;
       rank += __builtin_popcountll(front);
-      if (behind) partner = 64 * w + __builtin_ctzll(behind);
-      share[w] = me;
+      if (partner < 0 && behind) partner = (w == mine ? my_entry : 64 * w) + __builtin_ctzll(behind);
     }
     if (rank & 1) return;  // the entry in front of this one writes its record
-    if (partner >= 0) {
-#pragma unroll
-      for (int w = 0; w < kShareWords; ++w)
-        if ((partner >> 6) == w) share[w] |= 1ull << (partner & 63);
-      multi = true;
-    }
   }
+  const bool multi = partner >= 0;
   const bool per_entry_range = multi && clip && !AG;
   const bool from_regs = multi && one_batch && !per_entry_range;
 
@@ -250,17 +245,6 @@ __device__ __forceinline__ void decode_split_body(
   // entry -> (head, slot) of the record
   auto entry_head = [&](int e) { return kv * G + e / topk; };
   auto entry_slot = [&](int e) { return e % topk; };
-  // takes `entry` out of the masks and returns the next entry that attends the same rows, or -1
-  // (all threads hold the same masks)
-  auto next_entry = [&](int entry) {
-    int next = -1;
-#pragma unroll
-    for (int w = kShareWords - 1; w >= 0; --w) {
-      if (w == (entry >> 6)) share[w] &= ~(1ull << (entry & 63));
-      if (share[w]) next = 64 * w + __builtin_ctzll(share[w]);
-    }
-    return next;
-  };
   // An entry's share of the chunk and its record.  Grid, window: the item's own [t0, t1) and
   // chunk number.  Paper's geometry: the entry's span cut to the lattice chunk, and the chunk's
   // number counted from the span's own first chunk.
@@ -284,19 +268,19 @@ __device__ __forceinline__ void decode_split_body(
   const int64_t w1 = w0 + per_wave < cend ? w0 + per_wave : cend;
 
   if (U <= 8 && from_regs) {
-    // several entries, one chunk, one batch: the rows are loaded once and stay in registers
-    if (t0 >= t1) {  // (the window past its end: the same for every head)
-      for (int entry = my_entry; entry >= 0; entry = next_entry(entry))
-        write_empty(part + (((int64_t)entry_head(entry) * (topk + 1) + entry_slot(entry)) * nchunks + ck) * (D + 2));
+    // two entries, one chunk, one batch: the rows are loaded once and stay in registers
+    if (t0 >= t1) {  // (past the end of the span: the same for both)
+      write_empty(part + (((int64_t)h * (topk + 1) + slot) * nchunks + ck) * (D + 2));
+      write_empty(part + (((int64_t)entry_head(partner) * (topk + 1) + entry_slot(partner)) * nchunks + ck) * (D + 2));
       return;
     }
     uint4 kr[U], vr[U];
     uint4 qraw = load16(Q + (int64_t)h * qsh + lr * EPL);
-    int64_t anchor = slot < topk ? idx[(int64_t)h * topk + slot] : -1;
+    int64_t anchor = idx[(int64_t)h * topk + slot];
     load_rows<T, D, U, true>(Kb, Vb, kvst, w0, w1, lane, kr, vr);
     int entry = my_entry;
     while (true) {
-      const int next = next_entry(entry);
+      const int next = entry == my_entry ? partner : -1;
       float q2[EPL];
       scaled_query(qraw, q2);
       // the next entry's query (and anchor) are fetched while this one is computed
@@ -330,7 +314,7 @@ __device__ __forceinline__ void decode_split_body(
     return;
   }
 
-  // One entry, or several whose rows are read again per entry (through the L2).
+  // One entry, or two whose rows are read again for the second (through the L2).
   int entry = my_entry;
   while (true) {
     const int he = multi ? entry_head(entry) : h;
@@ -360,10 +344,8 @@ __device__ __forceinline__ void decode_split_body(
         attend_range<T, D, U, false>(q2, Kb, Vb, kvst, v0, v1, lane, st);
       merge_and_write(st, prec);
     }
-    if (!multi) break;
-    const int next = next_entry(entry);
-    if (next < 0) break;
-    entry = next;
+    if (!multi || entry == partner) break;
+    entry = partner;
     __syncthreads();  // the merge above has read s_o / s_m / s_l
   }
 }
@@ -391,6 +373,7 @@ struct AnchorBatch {
   int64_t window;
   int b, f, root;
   int wchunks;
+  int64_t span;  // of the longest sequence
 };
 
 // (the paper's geometry for a batch carries each sequence's own span extents on top: three
@@ -693,15 +676,19 @@ __global__ __launch_bounds__(256) void decode_reduce_combined_batched_kernel(
 // wavefront per SIMD.
 inline bool wide_batches(int CT) { return CT >= 512; }
 
-// Reading a chunk once for two entries saves HBM traffic and costs the second entry's arithmetic in line.
-// Below 256 MB of routed K/V rows the caches serve the second reader and only the cost is left.  Whole
-// steps, one owner for all entries (as it was) / pairs / every entry by itself, us:
-//   16411 tokens: 24.3 / 20.0 / 17.4;  262144: 48.3 / 48.4 / 43.9;  1M: 58.3 / 58.5 / 58.7;
-//   10M: 177.4 / 176.7 / 183.6;  8 sequences of 60000 .. 300000: 187 / 176 / 178
-// with the heads of a group on the same spans:
-//   16411 tokens: 37.0 / 20.3 / 16.0;  1M: 57.1 / 48.5 / 43.6;  10M: 176 / 105 / 142.
-inline bool spans_in_pairs(int64_t routed_items, int CT, int D, size_t elem_bytes) {
-  return routed_items * CT * 2 * D * (int64_t)elem_bytes >= ((int64_t)256 << 20);
+// Reading a chunk once for two entries saves HBM traffic and costs the second entry's arithmetic, and a look
+// at the group's index rows, in line; where the caches serve the second reader only the cost is left.  Every
+// entry by itself -> pairs, us per step, bf16 32:4 heads, with independent heads / with the heads of a group on
+// the same spans (by routed K/V rows, MB of 2^20):
+//   128 MB, 262144 tokens: 41.5 -> 46.5 / 36.3 -> 42.9;      176 MB, 524288: 51.8 -> 58.3 / 46.8 -> 54.6;
+//   256 MB, 1M: 57.1 -> 56.6 / 42.0 -> 43.4;                 352 MB, 2M: 75.7 -> 73.4 / 55.4 -> 55.1;
+//   512 MB, 4M: 101.6 -> 100.6 / 65.6 -> 54.2;               1 GB, 10M: 179.7 -> 172.6 / 134.5 -> 104.0;
+//   batches of 8, up to 300000 tokens, 1 GB: 175.0 -> 172.0 / 114 -> 173;    1M, 2 GB: 340 -> 319 / 223 -> 196;
+//   but up to 50000 tokens in spans of 256, 512 MB: 109 -> 122 / 94 -> 144 (half-filled chunks).
+// (One owner for all entries of a chunk and one workgroup for a kv head's window, as it was before: 41.5 and
+// 51.8 above were 46.5 and 58.3, 8 alike heads at 1M, 2M, 10M 56.5, 64.3, 172.9, the batches 183, 324, 138.)
+inline bool spans_in_pairs(int64_t entries, int64_t span, int D, size_t elem_bytes) {
+  return span >= 512 && entries * span * 2 * D * (int64_t)elem_bytes >= ((int64_t)224 << 20);
 }
 
 template <typename T, int D, int U, bool AG>
@@ -710,7 +697,7 @@ void launch_split_u(int grid, hipStream_t st, hipEvent_t e0, hipEvent_t e1, cons
                     int CT, int n_routed, int local_stride, const AnchorRanges& ar) {
   const float scale_log2e = pb.scale * kLog2e;
   const bool clip = !AG && pb.A < pb.S && !pb.combined;  // overlapping spans in one joint softmax
-  const bool share_spans = spans_in_pairs(n_routed, CT, D, sizeof(T));
+  const bool share_spans = spans_in_pairs((int64_t)pb.Hq * pb.topk, AG ? ar.back + ar.fwd + 1 : S, D, sizeof(T));
   if (e0) {
     // With profiling events the launch itself carries them: they then hold the kernel's own
     // begin and end timestamps (events recorded on the stream before / after a 45 us kernel would
@@ -755,7 +742,7 @@ void launch_split_batched_u(int grid, int B, hipStream_t st, const sl_decode_seq
   const int64_t kvsh = pb.kvsh_given ? pb.kvsh : (int64_t)0;
   const int A = AG ? S : pb.A;
   const bool clip = !AG && pb.A < pb.S && !pb.combined;
-  const bool share_spans = spans_in_pairs((int64_t)n_routed * B, CT, D, sizeof(T));
+  const bool share_spans = spans_in_pairs((int64_t)B * pb.Hq * pb.topk, AG ? ab.span : S, D, sizeof(T));
   hipLaunchKernelGGL((decode_split_batched_kernel<T, D, U, AG>), dim3(grid, B), dim3(kDecodeThreads), 0, st,
                      seqs, part, part_stride, pb.Hq, pb.Hkv, S, A, clip, pb.topk, nchunks, CT, scale_log2e,
                      pb.qsh, kvsh, pb.kvst, n_routed, local_stride, share_spans, ab);
@@ -885,7 +872,7 @@ sl_status launch_decode_batched(const Problem& pb, const sl_decode_seq* seqs, in
   const int local_stride = (int)align_up((size_t)pb.Hkv * nchunks, 8);
   const int grid = n_routed + pb.G * local_stride;
   launch_split_batched<T, D>(grid, B, st, seqs, part, part_stride, pb, pb.S, nchunks, CT, n_routed,
-                             local_stride, AnchorBatch{false, 0, 0, 0, 2, 0});
+                             local_stride, AnchorBatch{false, 0, 0, 0, 2, 0, 0});
   if (hipGetLastError() != hipSuccess) return SL_ERR_LAUNCH;
   if (pb.combined)
     hipLaunchKernelGGL((decode_reduce_combined_batched_kernel<T, D>), dim3(pb.Hq, D / kReduceDims, B),
@@ -939,7 +926,7 @@ size_t anchor_attention_batched_ws_bytes(const Problem& pb, int64_t window, int 
 sl_status anchor_attention_decode_batched(const Problem& pb, int64_t window, int b, int f, int root,
                                           const sl_decode_seq* seqs, int B, void* ws, hipStream_t st) {
   const AnchorPlan a = plan_anchor(pb, window, b, f, root, B);
-  const AnchorBatch ab{true, window, b, f, root, a.wchunks};
+  const AnchorBatch ab{true, window, b, f, root, a.wchunks, a.back + a.fwd + 1};
   if (pb.dtype == SL_BF16) {
     if (pb.D == 128) return launch_anchor_batched<bf16_t, 128>(pb, a, ab, seqs, B, ws, st);
     return launch_anchor_batched<bf16_t, 64>(pb, a, ab, seqs, B, ws, st);

@@ -161,19 +161,22 @@ def test_any_span_length_keeps_what_is_not_finite_to_the_rows_that_attend_it(whi
         assert not bool((~finite & ~attends).any())
 
 
-@pytest.mark.parametrize("form,dtype,Hq,Hkv,S,A,k", [
-    ("joint", torch.bfloat16, 32, 4, 256, 256, 16),     # one batch of rows, kept in registers for both entries
-    ("joint", torch.bfloat16, 32, 4, 1024, 1024, 16),   # 512-token chunks: read again
-    ("joint", torch.bfloat16, 24, 8, 256, 128, 16),     # overlapping spans: every entry its own range
-    ("gated", torch.float32, 16, 2, 200, 200, 16),
-    ("anchor", torch.bfloat16, 32, 4, 1, 1, 8),
+@pytest.mark.parametrize("form,dtype,Hq,Hkv,S,A,k,nb", [
+    ("joint", torch.bfloat16, 32, 4, 512, 512, 16, 2),    # 128-token chunks: one batch of rows, kept in registers
+    ("gated", torch.float32, 16, 2, 512, 512, 16, 2),     # the same in fp32: 64-token chunks
+    ("anchor", torch.bfloat16, 32, 4, 1, 1, 8, 2),        # and where spans cover parts of a chunk
+    ("joint", torch.bfloat16, 16, 2, 1024, 1024, 16, 8),  # 512-token chunks: read again
+    ("joint", torch.bfloat16, 24, 8, 512, 256, 16, 8),    # overlapping spans: every entry its own range
+    ("gated", torch.float32, 16, 2, 600, 600, 16, 8),     # a second, shorter chunk
 ])
-def test_decode_entries_sharing_chunks_go_in_pairs(form, dtype, Hq, Hkv, S, A, k):
-    """Steps of 256 MB and more of routed rows pair the entries that share a chunk: a batch of the same
-    sequence against the single step, which is below that and pairs nothing.  Heads list the same spans,
-    partly the same, an odd number of them, and empty slots.  Chunks may be cut differently: fp32 sums in
-    another order (1e-5 of outputs below 5), then one rounding to the output's type."""
-    D, G, nb = 128, Hq // Hkv, 8
+def test_decode_entries_sharing_chunks_go_in_pairs(form, dtype, Hq, Hkv, S, A, k, nb):
+    """Steps of 224 MB and more of routed rows pair the entries that share a chunk: a batch of the same
+    sequence (256 MB and more) against the single step (157 MB at most: every entry by itself).  Heads list the
+    same spans, partly the same, an odd number of them, and empty slots.  Chunks may be cut differently: fp32
+    sums in another order (1e-5 of outputs below 5), then one rounding to the output's type."""
+    D, G = 128, Hq // Hkv
+    routed = Hq * k * (1201 if form == "anchor" else S) * 2 * D * (2 if dtype == torch.bfloat16 else 4)
+    assert routed <= 160 << 20 and nb * routed >= 256 << 20
     rng = np.random.default_rng(S + k)
     L = 40000 if form == "anchor" else max(S * 22, 9000) + 37
     Q, K, V = make(900 + S, Hq, Hkv, L, D, dtype, Lq=1, scale=0.5)
