@@ -448,7 +448,7 @@ __global__ __launch_bounds__(256) void prefill_anchor_search_rows_kernel(
                    scores ? scores + row * topk : nullptr, i, s0, root);
 }
 
-// The same search (fp32) with the key rows shared by the query heads of a kv group: a row group of LPR
+// The same search with the key rows shared by the query heads of a kv group: a row group of LPR
 // lanes owns one query row and up to 8 query heads of its kv head; every candidate's key row is
 // loaded once and scored against all of them (the row-per-wavefront kernel above loads it once per
 // head: 8x the L2 traffic at GQA 8:1, which is what bounds it).  Lane lr of a group keeps the
@@ -546,7 +546,7 @@ __global__ __launch_bounds__(256) void prefill_anchor_search_group_kernel(
   }
 }
 
-// The same search for bf16 on the matrix cores.  A wavefront owns two query rows and up to 8 query heads of
+// The same search for bf16 and short lists on the matrix cores.  A wavefront owns two query rows and up to 8 query heads of
 // a kv head; the 16 columns of v_mfma_f32_16x16x32_bf16 are (row, head).  Sixteen candidates of one row
 // -- gathered key rows -- are the A operand; each row's keys are multiplied with all 16 columns and a lane
 // keeps the half that belongs to its row (the other half is thrown away: the rows have no key in common).
@@ -891,21 +891,25 @@ sl_status launch_anchor_search_rows(const Problem& pb, const void* Qs, const voi
   if (pb.topk <= 8) {  // key rows shared by the heads of a kv group, top-k lists in registers
     const unsigned groups = (unsigned)(pb.Hkv * ((pb.G + 7) / 8));
     if (pb.prof_start) (void)hipEventRecord(pb.prof_start, st);
+    bool done = false;
     if constexpr (std::is_same<T, bf16_t>::value) {
-      const int blocks = (int)((pb.Lq + kAnchorRowsPerBlock - 1) / kAnchorRowsPerBlock);
-      const int chunk = 8 * kAnchorBlocksPerChunk;  // one chunk of each XCD
-      const dim3 grid((unsigned)((blocks + chunk - 1) / chunk * chunk), groups);
+      // Lists of up to 4: longer ones cost the matrix-core kernel, whose lanes each keep one, more than it gains
+      // (top-8, vector -> matrix cores: 20000 rows 320 -> 746 us, 512 rows behind 48645 tokens 57 -> 202 us).
+      if (pb.topk <= 4) {
+        const int blocks = (int)((pb.Lq + kAnchorRowsPerBlock - 1) / kAnchorRowsPerBlock);
+        const int chunk = 8 * kAnchorBlocksPerChunk;  // one chunk of each XCD
+        const dim3 grid((unsigned)((blocks + chunk - 1) / chunk * chunk), groups);
 #define SL_ANCHOR_MFMA(KM)                                                                                   \
   hipLaunchKernelGGL((prefill_anchor_search_mfma_kernel<D, KM>), grid, dim3(256), 0, st,                     \
                      static_cast<const bf16_t*>(Qs), static_cast<const bf16_t*>(K), anchors, scores, pb.Lq,  \
                      pb.q_pos0, pb.G, pb.topk, s0, root, blocks, pb.qsh, pb.qst, pb.kvsh, pb.kvst)
-      if (pb.topk <= 2) SL_ANCHOR_MFMA(2);
-      else if (pb.topk <= 4) SL_ANCHOR_MFMA(4);
-      else SL_ANCHOR_MFMA(8);
+        if (pb.topk <= 2) SL_ANCHOR_MFMA(2);
+        else SL_ANCHOR_MFMA(4);
 #undef SL_ANCHOR_MFMA
-      if (pb.prof_stop) (void)hipEventRecord(pb.prof_stop, st);
-      return hipGetLastError() == hipSuccess ? SL_OK : SL_ERR_LAUNCH;
-    } else {
+        done = true;
+      }
+    }
+    if (!done) {
       constexpr int RPW = RowLayout<T, D>::RPW;
       const dim3 grid((unsigned)((pb.Lq + 4 * RPW - 1) / (4 * RPW)), groups);
 #define SL_ANCHOR_GROUP(KM)                                                                               \
@@ -916,9 +920,9 @@ sl_status launch_anchor_search_rows(const Problem& pb, const void* Qs, const voi
       else if (pb.topk <= 4) SL_ANCHOR_GROUP(4);
       else SL_ANCHOR_GROUP(8);
 #undef SL_ANCHOR_GROUP
-      if (pb.prof_stop) (void)hipEventRecord(pb.prof_stop, st);
-      return hipGetLastError() == hipSuccess ? SL_OK : SL_ERR_LAUNCH;
     }
+    if (pb.prof_stop) (void)hipEventRecord(pb.prof_stop, st);
+    return hipGetLastError() == hipSuccess ? SL_OK : SL_ERR_LAUNCH;
   }
   const int lds_per_wave = LaneMajor::make(c_max).lds_floats();
   int W = 4;
