@@ -558,16 +558,18 @@ __global__ __launch_bounds__(256) void prefill_anchor_search_group_kernel(
 // of its own, and the address and data units were busy 82 and 93 % of the time (695 us).  The rows are
 // therefore brought to LDS by direct loads, whole rows by neighbouring lanes, in 8 KB of the wavefront's own
 // (pieces swizzled for the operand reads); while one batch is scored the next is on its way.  A block's 8
-// rows lie beside those of the other blocks of its XCD (chunks of 512 rows, dealt to the XCDs in turn):
+// rows lie beside those of the other blocks of its XCD (chunks of at most 512 rows, dealt to the XCDs in turn,
+// and of equal length, so that every XCD has the same work: with all of them 512 rows long, 512 rows behind
+// 48645 tokens ran on one XCD, 78 -> 25 us):
 // at the same stride index their keys are neighbours and the next index finds them in that L2.  Rows with
 // the most candidates come first.  49157 rows, 32:4 heads, window 1088, top-2: 956 us with vector
 // instructions (two-element dot products and a lane-group sum per score), 664 us now, of which the second scoring below takes 150.
-constexpr int kAnchorRowsPerBlock = 8, kAnchorBlocksPerChunk = 64;
+constexpr int kAnchorRowsPerBlock = 8, kAnchorMaxChunk = 64;
 
 template <int D, int KMAX>
 __global__ __launch_bounds__(256) void prefill_anchor_search_mfma_kernel(
     const bf16_t* __restrict__ Qs, const bf16_t* __restrict__ K, int32_t* __restrict__ anchors,
-    float* __restrict__ scores, int64_t Lq, int64_t q_pos0, int G, int topk, int s0, int root, int blocks,
+    float* __restrict__ scores, int64_t Lq, int64_t q_pos0, int G, int topk, int s0, int root, int blocks, int chunk,
     int64_t qsh, int64_t qst, int64_t kvsh, int64_t kvst) {
   typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
   typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -577,7 +579,7 @@ __global__ __launch_bounds__(256) void prefill_anchor_search_mfma_kernel(
   const int nb = (G + HB - 1) / HB;
   const int kv = blockIdx.y / nb, h0 = (blockIdx.y % nb) * HB;
   const int xcd = blockIdx.x & 7, at = blockIdx.x >> 3;
-  const int blk = ((at / kAnchorBlocksPerChunk) * 8 + xcd) * kAnchorBlocksPerChunk + at % kAnchorBlocksPerChunk;
+  const int blk = ((at / chunk) * 8 + xcd) * chunk + at % chunk;
   if (blk >= blocks) return;
   const int64_t r0 = ((int64_t)(blocks - 1 - blk) * 4 + wave) * 2;
   if (r0 >= Lq) return;
@@ -897,12 +899,14 @@ sl_status launch_anchor_search_rows(const Problem& pb, const void* Qs, const voi
       // (top-8, vector -> matrix cores: 20000 rows 320 -> 746 us, 512 rows behind 48645 tokens 57 -> 202 us).
       if (pb.topk <= 4) {
         const int blocks = (int)((pb.Lq + kAnchorRowsPerBlock - 1) / kAnchorRowsPerBlock);
-        const int chunk = 8 * kAnchorBlocksPerChunk;  // one chunk of each XCD
-        const dim3 grid((unsigned)((blocks + chunk - 1) / chunk * chunk), groups);
+        // as few rounds of one chunk for each XCD as the longest chunk allows, all chunks alike
+        const int rounds = (blocks + 8 * kAnchorMaxChunk - 1) / (8 * kAnchorMaxChunk);
+        const int chunk = (blocks + 8 * rounds - 1) / (8 * rounds);
+        const dim3 grid((unsigned)(8 * rounds * chunk), groups);
 #define SL_ANCHOR_MFMA(KM)                                                                                   \
   hipLaunchKernelGGL((prefill_anchor_search_mfma_kernel<D, KM>), grid, dim3(256), 0, st,                     \
                      static_cast<const bf16_t*>(Qs), static_cast<const bf16_t*>(K), anchors, scores, pb.Lq,  \
-                     pb.q_pos0, pb.G, pb.topk, s0, root, blocks, pb.qsh, pb.qst, pb.kvsh, pb.kvst)
+                     pb.q_pos0, pb.G, pb.topk, s0, root, blocks, chunk, pb.qsh, pb.qst, pb.kvsh, pb.kvst)
         if (pb.topk <= 2) SL_ANCHOR_MFMA(2);
         else SL_ANCHOR_MFMA(4);
 #undef SL_ANCHOR_MFMA
