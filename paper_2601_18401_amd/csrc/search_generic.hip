@@ -546,6 +546,139 @@ __global__ __launch_bounds__(256) void prefill_anchor_search_group_kernel(
   }
 }
 
+// Running top-KMAX of a lane: scores with candidate numbers, best first.
+template <int KMAX>
+struct AnchorList {
+  float v[KMAX];
+  int id[KMAX];
+  __device__ __forceinline__ void clear() {
+#pragma unroll
+    for (int e = 0; e < KMAX; ++e) {
+      v[e] = -INFINITY;
+      id[e] = -1;
+    }
+  }
+  // Slot e takes the entry above it if x belongs above that one, x itself if x belongs exactly here.  Candidates
+  // that come in ascending order need no look at ties: a strictly larger score displaces an entry.
+  __device__ __forceinline__ void insert(float x, int j, bool ties) {
+#pragma unroll
+    for (int e = KMAX - 1; e >= 0; --e) {
+      const int p = e > 0 ? e - 1 : 0;
+      const bool up = e > 0 && (x > v[p] || (ties && x == v[p] && j < id[p]));
+      const bool here = !up && (x > v[e] || (ties && x == v[e] && j < id[e]));
+      id[e] = up ? id[p] : (here ? j : id[e]);
+      v[e] = up ? v[p] : (here ? x : v[e]);
+    }
+  }
+  // With the list of the lane `off` away (equal scores: the nearer anchor).
+  __device__ __forceinline__ void merge(int off) {
+    float ov[KMAX];
+    int oi[KMAX];
+#pragma unroll
+    for (int e = 0; e < KMAX; ++e) {
+      ov[e] = __shfl_xor(v[e], off, 64);
+      oi[e] = __shfl_xor(id[e], off, 64);
+    }
+#pragma unroll
+    for (int e = 0; e < KMAX; ++e) insert(oi[e] >= 0 ? ov[e] : -INFINITY, oi[e], oi[e] >= 0);
+  }
+  // The first topk entries, nearest anchor first: a selected entry's slot is the number of selected entries with a
+  // lower stride index.
+  __device__ __forceinline__ void store(int topk, int64_t i, int s0, int root, int32_t* oa, float* os) const {
+    int kk = 0;
+#pragma unroll
+    for (int e = 0; e < KMAX; ++e) kk += (e < topk && id[e] >= 0) ? 1 : 0;
+#pragma unroll
+    for (int e = 0; e < KMAX; ++e) {
+      if (e < topk && id[e] >= 0) {
+        int rank = 0;
+#pragma unroll
+        for (int e2 = 0; e2 < KMAX; ++e2) rank += (e2 < topk && id[e2] >= 0 && id[e2] < id[e]) ? 1 : 0;
+        oa[rank] = (int32_t)anchor_token_of(i, (int64_t)s0 + id[e], root);
+        if (os) os[rank] = v[e];
+      }
+    }
+    for (int e = kk; e < topk; ++e) {
+      oa[e] = -1;
+      if (os) os[e] = -INFINITY;
+    }
+  }
+};
+
+// The rows that the matrix-core kernel below has left, whose first slot holds this mark (anchors are token
+// positions or -1): a workgroup looks at 4 * RPW rows of up to 8 heads and does the marked ones one after the
+// other, all its row groups sharing a row's candidates.  (There is hardly ever more than one in a call, and its
+// time counts in full: 189 candidates by one row group 24 us, by a wavefront's four 10 to 15, by sixteen 5.)
+constexpr int32_t kLeft = INT32_MIN;
+
+template <int D, int KMAX>
+__global__ __launch_bounds__(256) void prefill_anchor_search_left_kernel(
+    const bf16_t* __restrict__ Qs, const bf16_t* __restrict__ K, int32_t* __restrict__ anchors,
+    float* __restrict__ scores, int64_t Lq, int64_t q_pos0, int G, int topk, int s0, int root,
+    int64_t qsh, int64_t qst, int64_t kvsh, int64_t kvst) {
+  using RL = RowLayout<bf16_t, D>;
+  constexpr int EPL = RL::EPL, LPR = RL::LPR, RPW = RL::RPW, HB = 8, U = 8, STEP = 4 * RPW;
+  __shared__ unsigned long long s_left[4];
+  __shared__ AnchorList<KMAX> s_top[4][HB];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int g = lane / LPR, lr = lane % LPR;
+  const int nb = (G + HB - 1) / HB;
+  const int kv = blockIdx.y / nb, h0 = (blockIdx.y % nb) * HB;
+  const int64_t r0 = (int64_t)blockIdx.x * STEP, rl = r0 + wave * RPW + g;
+  const bool mark = rl < Lq && anchors[((int64_t)(kv * G + h0) * Lq + (rl < Lq ? rl : 0)) * topk] == kLeft;
+  const unsigned long long mine = __builtin_amdgcn_ballot_w64(mark);
+  if (lane == 0) s_left[wave] = mine;
+  __syncthreads();
+  const bf16_t* Kb = K + kv * kvsh;
+  for (int w = 0; w < 4; ++w) {
+    for (unsigned long long left = s_left[w]; left != 0ull;) {
+      const int group = __builtin_ctzll(left) / LPR;
+      left &= ~(((1ull << LPR) - 1ull) << (group * LPR));
+      const int64_t r = r0 + w * RPW + group, i = q_pos0 + r;
+      const int c = (int)(iroot_floor(i + 1, root) - s0);  // marked: there are candidates
+      uint4 qraw[HB];
+#pragma unroll
+      for (int hb = 0; hb < HB; ++hb)
+        qraw[hb] = load16(Qs + (int64_t)(kv * G + (h0 + hb < G ? h0 + hb : G - 1)) * qsh + r * qst + lr * EPL);
+      AnchorList<KMAX> top;
+      top.clear();
+      for (int jb = wave * RPW + g; jb - (wave * RPW + g) < c; jb += U * STEP) {
+        uint4 kr[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int j = jb + u * STEP < c ? jb + u * STEP : c - 1;
+          kr[u] = load16(Kb + anchor_token_of(i, (int64_t)s0 + j, root) * kvst + lr * EPL);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          float part[HB];
+#pragma unroll
+          for (int hb = 0; hb < HB; ++hb) part[hb] = Piece<bf16_t>::dot(kr[u], qraw[hb], 0.f);
+          const float x = group_sum_scatter8<LPR>(part, lr);
+          const int j = jb + u * STEP;
+          top.insert(j < c ? x : -INFINITY, j, false);
+        }
+      }
+#pragma unroll
+      for (int off = LPR; off < 64; off <<= 1) top.merge(off);
+      if (lane < HB) s_top[wave][lane] = top;
+      __syncthreads();
+      if (threadIdx.x < HB && h0 + lane < G) {
+#pragma unroll
+        for (int o = 1; o < 4; ++o) {
+          const AnchorList<KMAX> other = s_top[o][lane];
+#pragma unroll
+          for (int e = 0; e < KMAX; ++e)
+            top.insert(other.id[e] >= 0 ? other.v[e] : -INFINITY, other.id[e], other.id[e] >= 0);
+        }
+        const int64_t row = (int64_t)(kv * G + h0 + lane) * Lq + r;
+        top.store(topk, i, s0, root, anchors + row * topk, scores ? scores + row * topk : nullptr);
+      }
+      __syncthreads();  // the lists are read
+    }
+  }
+}
+
 // The same search for bf16 and short lists on the matrix cores.  A wavefront owns two query rows and up to 8 query heads of
 // a kv head; the 16 columns of v_mfma_f32_16x16x32_bf16 are (row, head).  Sixteen candidates of one row
 // -- gathered key rows -- are the A operand; each row's keys are multiplied with all 16 columns and a lane
@@ -563,11 +696,12 @@ __global__ __launch_bounds__(256) void prefill_anchor_search_group_kernel(
 // 48645 tokens ran on one XCD, 78 -> 25 us):
 // at the same stride index their keys are neighbours and the next index finds them in that L2.  Rows with
 // the most candidates come first.  49157 rows, 32:4 heads, window 1088, top-2: 956 us with vector
-// instructions (two-element dot products and a lane-group sum per score), 664 us now, of which the second scoring below takes 150.
+// instructions (two-element dot products and a lane-group sum per score), 677 us now, of which the second scoring
+// below takes 150 and keeping to the other kernels' selection (the margin, the rows left) 30.
 constexpr int kAnchorRowsPerBlock = 8, kAnchorMaxChunk = 64;
 
 template <int D, int KMAX>
-__global__ __launch_bounds__(256) void prefill_anchor_search_mfma_kernel(
+__global__ __launch_bounds__(256, 4) void prefill_anchor_search_mfma_kernel(
     const bf16_t* __restrict__ Qs, const bf16_t* __restrict__ K, int32_t* __restrict__ anchors,
     float* __restrict__ scores, int64_t Lq, int64_t q_pos0, int G, int topk, int s0, int root, int blocks, int chunk,
     int64_t qsh, int64_t qst, int64_t kvsh, int64_t kvst) {
@@ -621,25 +755,22 @@ __global__ __launch_bounds__(256) void prefill_anchor_search_mfma_kernel(
                                        (__attribute__((address_space(3))) void*)(mine + u * 512), 16, 0, 0);
     }
   };
-  constexpr int KL = KMAX + 2;  // two spares: see the second scoring
-  float v[KL];
-  int id[KL];
+  constexpr int KL = KMAX + 2;  // two spares: see the margin
+  AnchorList<KL> top;
+  top.clear();
+  float (&v)[KL] = top.v;
+  int (&id)[KL] = top.id;
+  // squared length of the longest key of each row, a quarter of the dimensions per lane: see the margin
+  auto square = [](const bf16x8 (&x)[KS]) {
+    float sum = 0.f;
 #pragma unroll
-  for (int e = 0; e < KL; ++e) {
-    v[e] = -INFINITY;
-    id[e] = -1;
-  }
-  // (candidates come in ascending order per lane: a strictly larger score displaces an entry)
-  auto insert = [&](float x, int j, bool ties) {
-#pragma unroll
-    for (int e = KL - 1; e >= 0; --e) {
-      const int p = e > 0 ? e - 1 : 0;
-      const bool up = e > 0 && (x > v[p] || (ties && x == v[p] && j < id[p]));
-      const bool here = !up && (x > v[e] || (ties && x == v[e] && j < id[e]));
-      id[e] = up ? id[p] : (here ? j : id[e]);
-      v[e] = up ? v[p] : (here ? x : v[e]);
+    for (int kk = 0; kk < KS; ++kk) {
+      const uint4 p = __builtin_bit_cast(uint4, x[kk]);
+      sum = Piece<bf16_t>::dot(p, p, sum);
     }
+    return sum;
   };
+  float len_a = 0.f, len_b = 0.f;
   if (c1 > 0) stage(0);
   for (int jb = 0; jb < c1; jb += 16) {  // c1 >= c0
     __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the batch is in LDS (this wavefront's own: no barrier)
@@ -655,6 +786,8 @@ __global__ __launch_bounds__(256) void prefill_anchor_search_mfma_kernel(
 #pragma unroll
     for (int kk = 0; kk < KS; ++kk) asm volatile("" : "+v"(ka[kk]), "+v"(kb[kk])::"memory");
     if (jb + 16 < c1) stage(jb + 16);
+    len_a = fmaxf(len_a, square(ka));
+    len_b = fmaxf(len_b, square(kb));
     f32x4 sa = {0.f, 0.f, 0.f, 0.f}, sb = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int kk = 0; kk < KS; ++kk) {
@@ -665,26 +798,41 @@ __global__ __launch_bounds__(256) void prefill_anchor_search_mfma_kernel(
     for (int r = 0; r < 4; ++r) {
       const int j = jb + 4 * q4 + r;
       const float x = second ? sb[r] : sa[r];
-      insert(j < c ? x : -INFINITY, j, false);
+      top.insert(j < c ? x : -INFINITY, j, false);
     }
   }
 #pragma unroll
-  for (int off = 16; off <= 32; off <<= 1) {
-    float ov[KL];
-    int oi[KL];
+  for (int off = 16; off <= 32; off <<= 1) top.merge(off);
+  // The matrix unit adds in another order than the other search kernels (Piece::dot, group_sum).  Both sums have at
+  // most D + 16 roundings, each of at most 2^-23 of what is added up, which is at most |q||k|: candidates whose
+  // scores lie further apart than twice that are in the same order in both.
 #pragma unroll
-    for (int e = 0; e < KL; ++e) {
-      ov[e] = __shfl_xor(v[e], off, 64);
-      oi[e] = __shfl_xor(id[e], off, 64);
-    }
-#pragma unroll
-    for (int e = 0; e < KL; ++e) insert(oi[e] >= 0 ? ov[e] : -INFINITY, oi[e], oi[e] >= 0);
+  for (int off = 1; off <= 8; off <<= 1) {  // the longest of the keys that the 16 lanes have staged ...
+    len_a = fmaxf(len_a, __shfl_xor(len_a, off, 64));
+    len_b = fmaxf(len_b, __shfl_xor(len_b, off, 64));
   }
-  // Second scoring, with the arithmetic of every other search kernel (Piece::dot, group_sum; the matrix unit
-  // adds in another order): always of the entries that are returned, and of the whole list, which is then
-  // ordered anew, where the k-th and the next score lie within 1e-4 of the best, far above the rounding of
-  // either sum, so that the selection is the other kernels' too.  A group of LPR lanes takes one column at
-  // a time; lane n % 16 gets its column's scores back.
+  float len_k = second ? len_b : len_a, len_q = square(qf);
+#pragma unroll
+  for (int off = 16; off <= 32; off <<= 1) {  // ... over all dimensions
+    len_k += __shfl_xor(len_k, off, 64);
+    len_q += __shfl_xor(len_q, off, 64);
+  }
+  const float margin = 2.f * (D + 16) * 0x1p-23f * sqrtf(len_q) * sqrtf(len_k);
+  const bool in_range = len_q > 1e-30f && len_k > 1e-30f;  // of the squares
+  bool close = false, lost = c > 0 && !(margin < INFINITY);
+#pragma unroll
+  for (int e = 1; e < KL - 1; ++e)
+    if (e == topk) {
+      close = id[e] >= 0 && !(v[e - 1] - v[e] > margin && in_range);
+      lost = lost || (id[KL - 1] >= 0 && !(v[e - 1] - v[KL - 1] > margin && in_range));
+    }
+  // A row with a head whose k-th score and the last of the list are that close (equal keys, or lengths that leave
+  // the range of their squares, or are not finite) is left to prefill_anchor_search_left_kernel: its first slot is marked.
+  const unsigned long long redo = __builtin_amdgcn_ballot_w64(lost);
+  const bool left = (redo & (second ? 0xFF00FF00FF00FF00ull : 0x00FF00FF00FF00FFull)) != 0ull;
+  // Otherwise the list holds the selection: where the k-th and the next are close (some in a thousand for random
+  // scores) it is scored again, with the other kernels' arithmetic, and ordered anew, and so are the scores that
+  // are returned.  A group of LPR lanes takes one column at a time; lane n % 16 gets its column's scores back.
   auto score_again = [&](auto count) {
     using RL = RowLayout<bf16_t, D>;
     constexpr int LPR = RL::LPR, NGRP = 64 / LPR, ITS = 16 / NGRP, N = decltype(count)::value;
@@ -710,49 +858,21 @@ __global__ __launch_bounds__(256) void prefill_anchor_search_mfma_kernel(
         if (n / NGRP == it && id[e] >= 0) v[e] = x;
       }
   };
-  bool close = false;
-#pragma unroll
-  for (int e = 1; e < KL; ++e)
-    close = close || (e == topk && id[e] >= 0 && v[e - 1] - v[e] <= 1e-4f * fmaxf(fabsf(v[0]), fabsf(v[e])));
-  if (__builtin_amdgcn_ballot_w64(close) != 0ull) {
+  if (__builtin_amdgcn_ballot_w64(close && !left) != 0ull) {
     score_again(std::integral_constant<int, KL>{});
-    float fv[KL];
-    int fi[KL];
+    const AnchorList<KL> was = top;
+    top.clear();
 #pragma unroll
-    for (int e = 0; e < KL; ++e) {
-      fv[e] = v[e];
-      fi[e] = id[e];
-      v[e] = -INFINITY;
-      id[e] = -1;
-    }
-#pragma unroll
-    for (int e = 0; e < KL; ++e) insert(fi[e] >= 0 ? fv[e] : -INFINITY, fi[e], fi[e] >= 0);
-  } else if (scores) {
+    for (int e = 0; e < KL; ++e) top.insert(was.id[e] >= 0 ? was.v[e] : -INFINITY, was.id[e], was.id[e] >= 0);
+  } else if (scores && __builtin_amdgcn_ballot_w64(!left) != 0ull) {
     score_again(std::integral_constant<int, KMAX>{});
   }
   const int64_t r = second ? r0 + 1 : r0;
-  if (q4 == 0 && r < Lq && h0 + (n & 7) < G) {
+  if (left) {
+    if (q4 == 0 && (n & 7) == 0 && r < Lq) anchors[((int64_t)(kv * G + h0) * Lq + r) * topk] = kLeft;
+  } else if (q4 == 0 && r < Lq && h0 + (n & 7) < G) {
     const int64_t row = (int64_t)(kv * G + head) * Lq + r;
-    int32_t* oa = anchors + row * topk;
-    float* os = scores ? scores + row * topk : nullptr;
-    int kk = 0;
-#pragma unroll
-    for (int e = 0; e < KMAX; ++e) kk += (e < topk && id[e] >= 0) ? 1 : 0;
-    // nearest anchor first: a selected entry's slot is the number of selected entries with a lower stride index
-#pragma unroll
-    for (int e = 0; e < KMAX; ++e) {
-      if (e < topk && id[e] >= 0) {
-        int rank = 0;
-#pragma unroll
-        for (int e2 = 0; e2 < KMAX; ++e2) rank += (e2 < topk && id[e2] >= 0 && id[e2] < id[e]) ? 1 : 0;
-        oa[rank] = (int32_t)anchor_token_of(q_pos0 + r, (int64_t)s0 + id[e], root);
-        if (os) os[rank] = v[e];
-      }
-    }
-    for (int e = kk; e < topk; ++e) {
-      oa[e] = -1;
-      if (os) os[e] = -INFINITY;
-    }
+    top.store(topk, q_pos0 + r, s0, root, anchors + row * topk, scores ? scores + row * topk : nullptr);
   }
 }
 
@@ -893,20 +1013,34 @@ sl_status launch_anchor_search_rows(const Problem& pb, const void* Qs, const voi
   if (pb.topk <= 8) {  // key rows shared by the heads of a kv group, top-k lists in registers
     const unsigned groups = (unsigned)(pb.Hkv * ((pb.G + 7) / 8));
     if (pb.prof_start) (void)hipEventRecord(pb.prof_start, st);
+    constexpr int RPW = RowLayout<T, D>::RPW;
     bool done = false;
     if constexpr (std::is_same<T, bf16_t>::value) {
-      // Lists of up to 4: longer ones cost the matrix-core kernel, whose lanes each keep one, more than it gains
-      // (top-8, vector -> matrix cores: 20000 rows 320 -> 746 us, 512 rows behind 48645 tokens 57 -> 202 us).
-      if (pb.topk <= 4) {
+      // The matrix cores where the rows have enough candidates (the middle row's number) to make up for what a
+      // wavefront does once: set up, merge its lanes' lists, score the winners again.  Vector -> matrix cores, us,
+      // 32:4 heads, whole prompts, window 1088 unless said otherwise:
+      //   up to 2 anchors: 8000 rows (31 candidates) 61 -> 65, 8000 with window 255 (48) 83 -> 73, 12000 (45)
+      //     109 -> 97, 20000 (68) 237 -> 181; D = 64: 8000 44.7 -> 47.1, 20000 128 -> 120;
+      //   3 and 4: 12000 122 -> 154, 20000 267 -> 271, 30000 (90) 486 -> 437, 49157 (124) 1066 -> 855;
+      //     D = 64: 30000 259 -> 295, 49157 555 -> 520;
+      //   5 to 8: 20000 320 -> 746: every lane keeps a list of its own; 512 rows behind 48645 tokens 57 -> 202.
+      const int64_t mid = iroot_floor(pb.q_pos0 + pb.Lq / 2 + 1, root) - s0;
+      if (pb.topk <= 4 && mid >= (pb.topk <= 2 ? 40 : D == 128 ? 80 : 110)) {
         const int blocks = (int)((pb.Lq + kAnchorRowsPerBlock - 1) / kAnchorRowsPerBlock);
         // as few rounds of one chunk for each XCD as the longest chunk allows, all chunks alike
         const int rounds = (blocks + 8 * kAnchorMaxChunk - 1) / (8 * kAnchorMaxChunk);
         const int chunk = (blocks + 8 * rounds - 1) / (8 * rounds);
         const dim3 grid((unsigned)(8 * rounds * chunk), groups);
+        const dim3 left_grid((unsigned)((pb.Lq + 4 * RPW - 1) / (4 * RPW)), groups);
 #define SL_ANCHOR_MFMA(KM)                                                                                   \
-  hipLaunchKernelGGL((prefill_anchor_search_mfma_kernel<D, KM>), grid, dim3(256), 0, st,                     \
-                     static_cast<const bf16_t*>(Qs), static_cast<const bf16_t*>(K), anchors, scores, pb.Lq,  \
-                     pb.q_pos0, pb.G, pb.topk, s0, root, blocks, chunk, pb.qsh, pb.qst, pb.kvsh, pb.kvst)
+  do {                                                                                                       \
+    hipLaunchKernelGGL((prefill_anchor_search_mfma_kernel<D, KM>), grid, dim3(256), 0, st,                   \
+                       static_cast<const bf16_t*>(Qs), static_cast<const bf16_t*>(K), anchors, scores, pb.Lq, \
+                       pb.q_pos0, pb.G, pb.topk, s0, root, blocks, chunk, pb.qsh, pb.qst, pb.kvsh, pb.kvst); \
+    hipLaunchKernelGGL((prefill_anchor_search_left_kernel<D, KM>), left_grid, dim3(256), 0, st,              \
+                       static_cast<const bf16_t*>(Qs), static_cast<const bf16_t*>(K), anchors, scores, pb.Lq, \
+                       pb.q_pos0, pb.G, pb.topk, s0, root, pb.qsh, pb.qst, pb.kvsh, pb.kvst);                \
+  } while (0)
         if (pb.topk <= 2) SL_ANCHOR_MFMA(2);
         else SL_ANCHOR_MFMA(4);
 #undef SL_ANCHOR_MFMA
@@ -914,7 +1048,6 @@ sl_status launch_anchor_search_rows(const Problem& pb, const void* Qs, const voi
       }
     }
     if (!done) {
-      constexpr int RPW = RowLayout<T, D>::RPW;
       const dim3 grid((unsigned)((pb.Lq + 4 * RPW - 1) / (4 * RPW)), groups);
 #define SL_ANCHOR_GROUP(KM)                                                                               \
   hipLaunchKernelGGL((prefill_anchor_search_group_kernel<T, D, KM>), grid, dim3(256), 0, st,              \

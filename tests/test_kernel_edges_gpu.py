@@ -221,6 +221,12 @@ def test_decode_entries_sharing_chunks_go_in_pairs(form, dtype, Hq, Hkv, S, A, k
     (4, 4, 128, 40000, 8, 255, 2, 9, 39991),     # one head a group, many batches, lists of 8
     (6, 2, 128, 9000, 3, 8, 3, 1030, 7970),      # cubes; rows past one chunk of the block order
     (8, 2, 128, 20, 2, 1088, 2, None, 0),        # no row has a candidate
+    # the same where the rows have candidates enough for the matrix cores
+    (8, 1, 128, 8000, 2, 0, 2, None, 0),
+    (8, 2, 128, 14001, 4, 0, 2, None, 0),
+    (12, 1, 64, 30001, 4, 24, 2, 1501, 28500),
+    (4, 4, 128, 40000, 3, 255, 2, 9, 39991),
+    (6, 1, 128, 600000, 3, 8, 3, 1030, 598970),
 ])
 def test_anchor_search_on_the_matrix_cores(Hq, Hkv, D, L, k, w, root, Lq, q0):
     """Batches of 16 candidates, pairs of rows and the lists' merge against fp64 scores: the selection by the
@@ -262,6 +268,41 @@ def test_anchor_search_ties_go_to_the_nearer_anchor():
             s = s3[h][toks % 3]
             pick = np.sort(np.lexsort((np.arange(len(s)), -s))[:k])
             assert an[h, r].tolist() == toks[pick].tolist()
+
+
+@pytest.mark.parametrize("kind", ["random", "cancelling", "near-equal", "zero", "infinite"])
+@pytest.mark.parametrize("Hq,Hkv,D,k", [(8, 1, 128, 2), (6, 2, 128, 4), (12, 1, 64, 3), (8, 2, 128, 6)])
+def test_anchor_search_selects_as_the_decode_search_does(Hq, Hkv, D, k, kind):
+    """Whatever the scores: the selection and the returned scores of every row are the decode search's to the
+    bit, and do not depend on how a prompt is cut.  Cancelling: two large channels of opposite sign, so that the
+    order of the additions decides between scores.  Near-equal: three keys, each varying in one small element.  Zero: queries and stretches of keys that are all zero.  Infinite: a key that is not finite
+    among finite ones."""
+    L, q0, w = 20000, 18000, 24
+    Q, K, _ = make(1300 + D + k, Hq, Hkv, L, D, torch.bfloat16, Lq=L - q0, scale=0.3)
+    if kind == "cancelling":
+        Q[..., 3], Q[..., D - 20] = 61.0, -61.0
+        K[..., 3] = K[..., D - 20] = (40 + 20 * torch.rand(K.shape[:2], device=DEV)).to(torch.bfloat16)
+    elif kind == "near-equal":
+        K.copy_(K[:, :3].clone()[:, torch.arange(L, device=DEV) % 3])
+        K[..., 5] = (2.0 ** -13 * torch.randn(K.shape[:2], device=DEV)).to(torch.bfloat16)
+    elif kind == "zero":
+        Q[:, 1::3] = 0
+        K[:, 5000:12000] = 0
+    elif kind == "infinite":
+        K[0, 12000, 7], K[0, 11000, 7] = float("inf"), float("-inf")
+    an, sc = B.sl_anchor_search_prefill(Q, K, k, w, q_pos0=q0, want_scores=True)
+    only = B.sl_anchor_search_prefill(Q, K, k, w, q_pos0=q0)
+    parts = [B.sl_anchor_search_prefill(Q[:, a:b], K[:, :q0 + b], k, w, q_pos0=q0 + a, want_scores=True)
+             for a, b in ((0, 1), (1, 500), (500, 1277), (1277, L - q0))]
+    torch.cuda.synchronize()
+    assert torch.equal(an, only)
+    assert torch.equal(an, torch.cat([p[0] for p in parts], dim=1))
+    assert torch.equal(sc.view(torch.int32), torch.cat([p[1] for p in parts], dim=1).view(torch.int32))
+    for r in sorted({0, L - q0 - 1, L - q0 - 2, *range(1, L - q0, 41)}):
+        da, ds = B.sl_anchor_search_decode(Q[:, r:r + 1], K[:, :q0 + r + 1], k, w, want_scores=True)
+        torch.cuda.synchronize()
+        assert torch.equal(da[:, 0], an[:, r]), r
+        assert torch.equal(ds[:, 0].view(torch.int32), sc[:, r].view(torch.int32)), r
 
 
 @pytest.mark.parametrize("k,scores", [(1, False), (4, True), (5, False), (8, True), (9, False)])
