@@ -18,7 +18,13 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 constexpr int HD = 128;
 constexpr int TMQ = 128;        // query rows per workgroup (4 wavefronts x 32 columns)
-constexpr int TNS = 32;         // span keys per staged chunk
+// Span keys per staged chunk and their bytes: DIRECT, two buffers of 32 keys filled by direct global -> LDS loads;
+// otherwise one of 64, through registers (LDS rows padded by 16 bytes: conflict-free 16-byte reads).
+template <bool DIRECT>
+struct Stages {
+  static constexpr int kKeys = DIRECT ? 32 : 64, kStride = DIRECT ? HD : HD + 8;
+  static constexpr int kBytes = (DIRECT ? 2 : 1) * kKeys * kStride * (int)sizeof(bf16_t);
+};
 constexpr int kEmpty = 0x7fffffff;
 
 // Running top-K VALUES of the candidates a lane has seen, sorted descending.  Inserting x is one
@@ -52,18 +58,21 @@ struct TopVals {
 // the compare-and-select chains that carrying the indices along would need.
 // WS: the scores of the selected spans are written too (their list costs LDS, which limits the
 // resident workgroups; most callers only want the indices).
-// Stages of 32 span keys come by direct global -> LDS loads into two buffers, one barrier each: while one is
-// scored the next is on its way.  (64 keys through registers with two barriers, 128 VGPRs: 65536 rows x 32
-// heads, 256 spans, top-8 334 -> 318 us, 5000 rows 22.7 -> 17.2; stages of 64 in two buffers leave three
-// workgroups per compute unit instead of five, 390 us.)  Lists of at most 4 spans have their own KMAX: half
-// of the median instructions (top-4 312 -> 267 us, with scores 377 -> 281).
-template <int KMAX, bool WS>
+// DIRECT: stages of 32 span keys by direct global -> LDS loads into two buffers, one barrier each: while one is
+// scored the next is on its way.  Otherwise 64 keys through registers with two barriers.  Direct is the faster one
+// where four or five workgroups fit a compute unit; the lists of long selections and of scores leave fewer, and so do
+// grids that give a compute unit no more than four: there the longer stages win (see the launch).  Slower than both:
+// stages of 64 in two buffers (65536 rows x 32 heads, 256 spans, top-8: 390 us against 327) and three buffers of 32
+// (1024 spans: 934 us against 877).  Lists of at most 4 spans have their own KMAX: half of the median instructions.
+template <int KMAX, bool WS, bool DIRECT>
 __global__ __launch_bounds__(256, (KMAX <= 4 || (KMAX == 8 && !WS)) ? 4 : 1) void prefill_search_mfma_kernel(
     const bf16_t* __restrict__ Qs, const bf16_t* __restrict__ K, const bf16_t* __restrict__ Ks,
     int32_t* __restrict__ idx, float* __restrict__ scores, int64_t Lq, int64_t q_pos0, int G, int S,
     int topk, int64_t n, int64_t qsh, int64_t qst, int64_t kvsh, int64_t kvst) {
   constexpr int CAP = 3 * KMAX;  // list entries per column: < KMAX above T, <= KMAX at T from each lane
-  // Two stages, dynamic: for a static array that direct loads are filling the compiler waits for all of
+  using St = Stages<DIRECT>;
+  constexpr int TNS = St::kKeys;
+  // Dynamic: for a static array that direct loads are filling the compiler waits for all of
   // them in front of the next read of it, other stage or not.
   extern __shared__ __align__(16) char s_stage[];
   bf16_t* const s_k = reinterpret_cast<bf16_t*>(s_stage);
@@ -96,26 +105,44 @@ __global__ __launch_bounds__(256, (KMAX <= 4 || (KMAX == 8 && !WS)) ? 4 : 1) voi
   // Walks the candidate spans in tiles of 32 and hands the lane's 16 scores of a tile, in
   // ascending span order, to f(score, span index); scores of spans >= c_q come as -inf.
   auto for_each_candidate = [&](auto f) {
-    // TNS span keys per stage by direct global -> LDS loads, 16 lanes x 16 bytes per key (1 KB per load, pieces
-    // swizzled for the operand reads); the next stage is on its way while the current one is scored
+    auto key = [&](int j) {  // past the last candidate: that one again
+      const int64_t jj = j < c_max ? j : c_max - 1;
+      return Ks ? Ks + ((int64_t)kv * n + jj) * HD : K + kv * kvsh + ((jj + 1) * S - 1) * kvst;
+    };
+    // 16 lanes x 16 bytes per key.  DIRECT: 1 KB per load, pieces swizzled for the operand reads
     auto stage = [&](int j0, int buf) {
 #pragma unroll
       for (int i = 0; i < TNS / 16; ++i) {
         const int blk = uwave * (TNS / 16) + i, row = blk * 4 + (lane >> 4), piece = (lane & 15) ^ (row & 15);
-        int64_t j = j0 + row;
-        j = j < c_max ? j : c_max - 1;
-        const bf16_t* src = Ks ? Ks + ((int64_t)kv * n + j) * HD : K + kv * kvsh + ((j + 1) * S - 1) * kvst;
-        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src + piece * 8),
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(key(j0 + row) + piece * 8),
                                          (__attribute__((address_space(3))) void*)(s_k + buf * TNS * HD + blk * 512), 16, 0, 0);
       }
     };
-    if (c_max > 0) stage(0, 0);
+    uint4 pre[DIRECT ? 1 : 4];
+    auto fetch = [&](int j0) {
+#pragma unroll
+      for (int i = 0; i < (DIRECT ? 0 : 4); ++i) pre[i] = load16(key(j0 + (tid >> 4) + 16 * i) + (tid & 15) * 8);
+    };
+    if (c_max > 0) {
+      if constexpr (DIRECT) stage(0, 0);
+      else fetch(0);
+    }
     int buf = 0;
-    for (int j0 = 0; j0 < c_max; j0 += TNS, buf ^= 1) {
-      // every wavefront is done with the other buffer, and this one's loads have arrived
-      __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
-      __syncthreads();
-      if (j0 + TNS < c_max) stage(j0 + TNS, buf ^ 1);
+    for (int j0 = 0; j0 < c_max; j0 += TNS) {
+      if constexpr (DIRECT) {
+        // every wavefront is done with the other buffer, and this one's loads have arrived
+        __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+        __syncthreads();
+        if (j0 + TNS < c_max) stage(j0 + TNS, buf ^ 1);
+      } else {
+        if (j0 > 0) __syncthreads();  // every wavefront is done with the stage
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          *reinterpret_cast<uint4*>(&s_k[((tid >> 4) + 16 * i) * St::kStride + (tid & 15) * 8]) = pre[i];
+        __syncthreads();
+        if (j0 + TNS < c_max) fetch(j0 + TNS);
+      }
+      const bf16_t* const cur = s_k + (DIRECT ? buf * TNS * HD : 0);
 #pragma unroll
       for (int sub = 0; sub < TNS / 32; ++sub) {
         if (j0 + 32 * sub < c_max) {  // uniform over the workgroup
@@ -126,7 +153,7 @@ __global__ __launch_bounds__(256, (KMAX <= 4 || (KMAX == 8 && !WS)) ? 4 : 1) voi
           for (int kk = 0; kk < 8; ++kk) {
             const bf16x8 ka =
                 *reinterpret_cast<const bf16x8*>(
-                    &s_k[buf * TNS * HD + (32 * sub + qc) * HD + (((2 * kk + hf) ^ (qc & 15)) << 3)]);
+                    &cur[(32 * sub + qc) * St::kStride + (((2 * kk + hf) ^ (DIRECT ? qc & 15 : 0)) << 3)]);
             s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka, qf[kk], s, 0, 0, 0);
           }
           // causal: only complete spans below the query's own.  A tile that ends at or below the
@@ -143,6 +170,7 @@ __global__ __launch_bounds__(256, (KMAX <= 4 || (KMAX == 8 && !WS)) ? 4 : 1) voi
           }
         }
       }
+      buf ^= 1;
     }
     __syncthreads();  // the next walk (or the lists' readers) may touch what this one used
   };
@@ -221,21 +249,35 @@ __global__ __launch_bounds__(256, (KMAX <= 4 || (KMAX == 8 && !WS)) ? 4 : 1) voi
   }
 }
 
+template <int KMAX, bool WS, bool DIRECT>
+void launch_as(const Problem& pb, int grid, const void* Qs, const void* K, const void* Ks, int32_t* idx, float* scores,
+               hipStream_t st) {
+  hipLaunchKernelGGL((prefill_search_mfma_kernel<KMAX, WS, DIRECT>), dim3(grid), dim3(256), Stages<DIRECT>::kBytes, st,
+                     static_cast<const bf16_t*>(Qs), static_cast<const bf16_t*>(K), static_cast<const bf16_t*>(Ks), idx,
+                     scores, pb.Lq, pb.q_pos0, pb.G, pb.S, pb.topk, pb.n, pb.qsh, pb.qst, pb.kvsh, pb.kvst);
+}
+
+// Through registers -> direct, us, 32 heads:
+//   top-4: 65536 rows x 256 spans 315 -> 272, with scores 376 -> 288;  64 rows x 4096 spans 185 -> 169;
+//   top-8: 65536 x 256 339 -> 327, 8000 x 125 40.5 -> 39.0, 2000 x 31 11.3 -> 10.8, 16384 x 4096 1377 -> 1355;
+//     but with workgroups for no more than four per compute unit and more than one stage of keys
+//     4000 x 62 18.8 -> 19.3, 64 x 4096 194 -> 199, 4000 x 4096 385 -> 397;
+//     with scores 65536 x 256 419 -> 429, 64 x 4096 199 -> 212;
+//   top-16: 65536 x 256 555 -> 561, with scores 765 -> 773;  top-32: 1328 -> 1340, with scores 2410 -> 2425.
 template <int KMAX>
 sl_status launch(const Problem& pb, const void* Qs, const void* K, const void* Ks, int32_t* idx,
                  float* scores, hipStream_t st) {
-  const int tiles_per_head = (int)((pb.Lq + TMQ - 1) / TMQ);
+  const int grid = pb.Hq * (int)((pb.Lq + TMQ - 1) / TMQ);
   if (pb.prof_start) (void)hipEventRecord(pb.prof_start, st);
-  if (scores)
-    hipLaunchKernelGGL((prefill_search_mfma_kernel<KMAX, true>), dim3(pb.Hq * tiles_per_head), dim3(256),
-                       2 * TNS * HD * sizeof(bf16_t), st, static_cast<const bf16_t*>(Qs), static_cast<const bf16_t*>(K),
-                       static_cast<const bf16_t*>(Ks), idx, scores, pb.Lq, pb.q_pos0, pb.G, pb.S,
-                       pb.topk, pb.n, pb.qsh, pb.qst, pb.kvsh, pb.kvst);
-  else
-    hipLaunchKernelGGL((prefill_search_mfma_kernel<KMAX, false>), dim3(pb.Hq * tiles_per_head), dim3(256),
-                       2 * TNS * HD * sizeof(bf16_t), st, static_cast<const bf16_t*>(Qs), static_cast<const bf16_t*>(K),
-                       static_cast<const bf16_t*>(Ks), idx, scores, pb.Lq, pb.q_pos0, pb.G, pb.S,
-                       pb.topk, pb.n, pb.qsh, pb.qst, pb.kvsh, pb.kvst);
+  if constexpr (KMAX <= 4) {
+    if (scores) launch_as<KMAX, true, true>(pb, grid, Qs, K, Ks, idx, scores, st);
+    else launch_as<KMAX, false, true>(pb, grid, Qs, K, Ks, idx, scores, st);
+  } else {
+    if (scores) launch_as<KMAX, true, false>(pb, grid, Qs, K, Ks, idx, scores, st);
+    else if (KMAX == 8 && (grid > 4 * 256 || (pb.n > 1 && pb.n <= Stages<true>::kKeys)))
+      launch_as<8, false, true>(pb, grid, Qs, K, Ks, idx, scores, st);
+    else launch_as<KMAX, false, false>(pb, grid, Qs, K, Ks, idx, scores, st);
+  }
   if (pb.prof_stop) (void)hipEventRecord(pb.prof_stop, st);
   return hipGetLastError() == hipSuccess ? SL_OK : SL_ERR_LAUNCH;
 }
