@@ -68,6 +68,27 @@ FINE = [
 ]
 
 
+@pytest.mark.parametrize("S,k,q_pos0,Lq", [(64, 7, 0, 1300), (64, 9, 300, 700), (128, 16, 1900, 300), (64, 17, 900, 400),
+                                          (64, 25, 0, 2000), (64, 32, 1900, 300)])
+def test_gated_merge_of_rows_with_and_without_a_full_list(S, k, q_pos0, Lq):
+    """Rows on both sides of position k * S, from which on there are candidates for all slots, lists of one and of
+    several batches of partials, and empty slots in the middle of lists."""
+    from tests.test_parity_gpu import check_combined
+    L = q_pos0 + Lq
+    Q, K, V = make(1400 + k, 4, 2, L, 128, torch.bfloat16, Lq=Lq, scale=0.35)
+    idx, sc = B.sl_span_search_prefill(Q, K, None, S, k, q_pos0=q_pos0, want_scores=True)
+    sc = torch.where(torch.isfinite(sc), sc, 0.0)
+    holes = idx.clone()
+    holes[:, ::2, ::3] = -1
+    holes[:, 1::4, 1] = 4000      # no candidate of any row
+    rows = [(h, r) for h in range(4) for r in sorted({0, 1, Lq - 1, *range(0, Lq, 29),
+                                                      *(x for x in range(k * S - q_pos0 - 3, k * S - q_pos0 + 3) if 0 <= x < Lq)})]
+    for sel in (idx, holes):
+        O = B.sl_span_attention_combined_prefill(Q, K, V, sel, sc, S, q_pos0=q_pos0)
+        torch.cuda.synchronize()
+        check_combined(O, Q, K, V, sel, sc, S, q_pos0, 0.0, rows)
+
+
 def row_form(Q, K, V, idx, sc, S, q_pos0=0, span_stride=0):
     """The row-stationary kernels, which a call without a workspace runs: (O, LSE), or O where sc is given."""
     p = B.make_params(Q, K, S, idx.shape[2], q_pos0, 0.0, span_stride)
