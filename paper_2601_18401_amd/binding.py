@@ -220,6 +220,24 @@ def _ws(ws):
     return _default_ws
 
 
+def _prefill_scratch(p: SlParams, ws, device):
+    """(pointer, bytes, what holds them) for a prefill span-attention call.
+
+    Shapes outside the bf16 matrix-core form run without scratch too, row by row.  What makes them
+    faster, up to 4 GiB, is the call's own unless the caller gives a workspace: it goes back to the allocator when
+    the call returns, calls on different streams do not share it, and if there is no room the call runs without."""
+    need = workspace_bytes(p, OP_ATTENTION_PREFILL)
+    optional = p.dtype != SL_BF16 or p.D != 128 or p.S % 64 != 0 or p.span_stride % 64 != 0
+    if not (optional and need):
+        ws = _ws(ws)
+        return (*ws.get(need), ws)
+    ws = Workspace(device) if ws is None else ws
+    try:
+        return (*ws.get(need), ws)
+    except torch.cuda.OutOfMemoryError:
+        return None, 0, None
+
+
 def _need(nbytes) -> int:
     """A *_workspace_bytes result as a size to allocate: invalid parameters need nothing (the entry
     point rejects them and says why)."""
@@ -281,7 +299,10 @@ def _attention(fn_name, op, Q, K, V, idx, S, q_pos0, scale, ws, prof, out, span_
         LSE = torch.empty((Hq, Lq), dtype=torch.float32, device=Q.device)
     else:
         O, LSE = out
-    wptr, wbytes = _ws(ws).get(workspace_bytes(p, op))
+    if op == OP_ATTENTION_PREFILL:
+        wptr, wbytes, held = _prefill_scratch(p, ws, Q.device)
+    else:
+        wptr, wbytes = _ws(ws).get(workspace_bytes(p, op))
     _arm(prof)
     st = getattr(lib, fn_name)(ctypes.byref(p), _ptr(Q), _ptr(K), _ptr(V), _ptr(idx), _ptr(O), _ptr(LSE),
                                wptr, wbytes, _stream())
@@ -319,7 +340,10 @@ def _combined(fn_name, op, Q, K, V, idx, scores, S, q_pos0, scale, ws, out, span
         raise ValueError("scores must be a contiguous float32 tensor of the shape of idx")
     Hq, Lq, D = Q.shape
     O = torch.empty((Hq, Lq, D), dtype=Q.dtype, device=Q.device) if out is None else out
-    wptr, wbytes = _ws(ws).get(workspace_bytes(p, op))
+    if op == OP_ATTENTION_PREFILL:
+        wptr, wbytes, held = _prefill_scratch(p, ws, Q.device)
+    else:
+        wptr, wbytes = _ws(ws).get(workspace_bytes(p, op))
     st = getattr(lib, fn_name)(ctypes.byref(p), _ptr(Q), _ptr(K), _ptr(V), _ptr(idx), _ptr(scores), _ptr(O),
                                wptr, wbytes, _stream())
     _check(st, fn_name)

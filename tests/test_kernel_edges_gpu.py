@@ -134,6 +134,39 @@ def test_any_span_length_on_the_matrix_cores(Hq, Hkv, L, D, S, A, k, form, q_pos
         assert float((LSE - RL).abs().max()) <= 1e-5
 
 
+@pytest.mark.parametrize("form", ["joint", "gated"])
+def test_optional_scratch_is_the_calls_own_and_can_be_missing(form, monkeypatch):
+    """A call that can run without scratch leaves the binding's shared workspace alone, and where there is no room
+    for the scratch it runs row by row."""
+    Q, K, V = make(806, 8, 2, 6000, 64, torch.bfloat16, scale=0.35)
+    S, k = 77, 8
+    idx, sc = B.sl_span_search_prefill(Q, K, None, S, k, want_scores=True)
+    assert takes_matrix_cores(Q, K, S, k)
+
+    def call(ws=None):
+        return B.sl_span_attention_prefill(Q, K, V, idx, S, ws=ws)[0] if form == "joint" else \
+            B.sl_span_attention_combined_prefill(Q, K, V, idx, sc, S, ws=ws)
+    R = row_form(Q, K, V, idx, None if form == "joint" else sc, S)
+    R = R[0] if form == "joint" else R
+    shared = B._ws(None)
+    before = shared.buf
+    monkeypatch.setattr(shared, "buf", None)
+    O = call()
+    assert shared.buf is None
+    monkeypatch.setattr(shared, "buf", before)
+    own = B.Workspace()
+    O2 = call(own)
+    assert own.buf is not None
+
+    def no_room(self, nbytes):
+        raise torch.cuda.OutOfMemoryError("no room")
+    monkeypatch.setattr(B.Workspace, "get", no_room)
+    N, N2 = call(), call(own)
+    torch.cuda.synchronize()
+    assert torch.equal(O, O2) and not torch.equal(O, R)
+    assert torch.equal(N, R) and torch.equal(N2, R)
+
+
 def test_armed_events_hold_the_routed_kernel_of_any_span_length():
     """The routed kernel is more than half of this call; the conditional recomputation behind it, which ends at
     once, is some microseconds."""
