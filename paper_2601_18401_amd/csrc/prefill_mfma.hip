@@ -525,9 +525,9 @@ __device__ __forceinline__ void flush_routed_output(char* lds, int grp, int w4, 
 // requested before the output tile is normalised and staged in LDS; a routed tile's staged
 // output goes to HBM during the next tile's first kv step (c.pending), a window tile's at once.
 //
-// FINE: the softmax weights keep fp32 precision: each is split into two bf16 parts (16 bits of mantissa
-// between them) and V is multiplied with both; the row sum is taken over the unsplit weights, partials are
-// written in fp32, and the output of a tile goes to HBM before the next one starts.
+// FINE: the softmax weights keep fp32 precision: each is split into three bf16 parts, which hold the 24 bits of its
+// mantissa between them, and V is multiplied with all three; the row sum is taken over the unsplit weights, partials
+// are written in fp32, and the output of a tile goes to HBM before the next one starts.
 template <int NG, bool LOCAL, bool FUSED, bool CLIP, int D = HD, bool FINE = false, typename RequestNext,
           typename DescribeNext>
 __device__ __forceinline__ void flash_tile(const FlashArgs& a, char* lds, const TileDesc& cur,
@@ -598,7 +598,7 @@ __device__ __forceinline__ void flash_tile(const FlashArgs& a, char* lds, const 
   for (int ks = 0; ks < 4; ++ks)
 #pragma unroll
     for (int e = 0; e < 8; ++e) pb[ks][e] = (__bf16)0.f;
-  bf16x8 pl[FINE ? 4 : 1];       // FINE: what pb leaves of the weights
+  bf16x8 pl[FINE ? 4 : 1], pm[FINE ? 4 : 1];  // FINE: what pb leaves of the weights, and what that leaves
 
   const int krow = perm_row(qc);
   const int kswz = k_swizzle<D>(krow);  // swizzle key of this lane's K rows (32*sub does not change it)
@@ -686,7 +686,9 @@ __device__ __forceinline__ void flash_tile(const FlashArgs& a, char* lds, const 
       for (int e = 0; e < 8; ++e) p[e] = fast_exp2(fmaf(s[ks >> 1][8 * (ks & 1) + e], sc, nm));
       pb[ks] = __builtin_convertvector(p, bf16x8);
       if constexpr (FINE) {
-        pl[ks] = __builtin_convertvector(p - __builtin_convertvector(pb[ks], f32x8), bf16x8);
+        const f32x8 rest = p - __builtin_convertvector(pb[ks], f32x8);
+        pl[ks] = __builtin_convertvector(rest, bf16x8);
+        pm[ks] = __builtin_convertvector(rest - __builtin_convertvector(pl[ks], f32x8), bf16x8);
 #pragma unroll
         for (int e = 0; e < 8; ++e) l += p[e];
         continue;
@@ -710,9 +712,12 @@ __device__ __forceinline__ void flash_tile(const FlashArgs& a, char* lds, const 
       for (int dt = 0; dt < NDT; ++dt) {
         const bf16x8 va = transposed8<D>(vt + vlane[dt] + 16 * ks * D);
         o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, pb[ks], o[dt], 0, 0, 0);
-        if constexpr (FINE) o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, pl[ks], o[dt], 0, 0, 0);
+        if constexpr (FINE) {
+          o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, pl[ks], o[dt], 0, 0, 0);
+          o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, pm[ks], o[dt], 0, 0, 0);
+        }
       }
-    constexpr int kPer = FINE ? 2 : 1;  // MFMAs per fragment
+    constexpr int kPer = FINE ? 3 : 1;  // MFMAs per fragment
     __builtin_amdgcn_sched_group_barrier(0x100, 8, 1);
 #pragma unroll
     for (int i = 0; i < 4 * NDT - 4; ++i) {
@@ -1606,13 +1611,14 @@ sl_status prefill_attention_mfma(const Problem& pb, const void* Q, const void* K
 // ------------------------------------------------------------------ any span length, fp32 weights
 // bf16 inputs that the kernels above do not take -- spans that are no multiple of 64 tokens, D = 64 -- on
 // the matrix cores without giving up the row-stationary kernels' precision: every product of the weights
-// with V is taken twice, with the weight's leading bf16 part and with what that leaves, partials are fp32.
-// Error against 64 bits as the row-stationary kernels' (1.6e-3 of a bf16 output, all of it the rounding of
-// the output; 2.4e-3 with bf16 weights and partials).
+// with V is taken three times, with the weight's leading bf16 part, with that of what it leaves, and with the rest;
+// partials are fp32.  Error against 64 bits: the row-stationary kernels' to all seven digits looked at (1.641783e-3
+// of a bf16 output of 20011 rows, nearly all of it the rounding of the output; with two parts, 16 to 17 bits,
+// 1.641784e-3 at 7 to 10 % less time; with bf16 weights and partials 2.4e-3).
 //
 // Measured (32:4 heads, top-8, D = 128 unless said otherwise; row-stationary -> this form, us):
-//   20011 rows, spans of 142: 16000 -> 1970; at D = 64: 8110 -> 1210; 2500 rows, spans of 50: 779 -> 181;
-//   200 rows behind 60000 tokens, spans of 245: 602 -> 77; 8 rows there: 158 -> 63.
+//   20011 rows, spans of 142: 16400 -> 1940; at D = 64: 8320 -> 1210; 2500 rows, spans of 50: 791 -> 191;
+//   200 rows behind 60000 tokens, spans of 245: 589 -> 83; 8 rows there: 157 -> 72.
 // 128-row tiles, two workgroups per compute unit (one's tile ends beside the other's kv loop): a span of
 // 142 tokens is three kv tiles, and 256-row tiles with one workgroup took 1381 us for the routed part where
 // these take 1288.
@@ -1623,7 +1629,7 @@ constexpr int kFineGroups = 1;
 
 // Estimated us of the two forms; the call takes the smaller.  Row-stationary: 0.02 ns per row and key, with
 // about 13 keys' worth of latency per slot, and no less than one row's own chain of loads.  This form: nine
-// launches, tiles of 4 us plus 2.2 us per kv tile on 512 workgroups (a bucket's last tile is padded),
+// launches, tiles of 4 us plus 2.6 us per kv tile on 512 workgroups (a bucket's last tile is padded),
 // partials written and read.  Of 22 measured calls (2 to 20000 rows, spans of 4 to 245 tokens) the estimates
 // choose the faster form in 18; the other four stay with the row kernels and lose 5 to 15 us, or half of
 // 415 us (1000 rows behind 60000 tokens in spans of 30, buckets a quarter full).
@@ -1633,7 +1639,7 @@ bool fine_is_faster(const Problem& pb) {
   const double by_rows = fmax(0.075 * keys, 2e-5 * d * rows * (keys + 13.0 * pb.topk));
   const double tiles = fmin(items, (double)pb.Hkv * pb.n) + items / 128;
   const double steps = (double)((pb.S + TN - 1) / TN);
-  return 45 + tiles * (4 + 2.2 * steps) / 512 + (items + rows) * pb.D * 8 / 4.5e6 < by_rows;
+  return 45 + tiles * (4 + 2.6 * steps) / 512 + (items + rows) * pb.D * 8 / 4.5e6 < by_rows;
 }
 
 constexpr size_t kFineMaxScratch = (size_t)4 << 30;
