@@ -889,9 +889,15 @@ sl_status launch_span_keys(const Problem& pb, const void* K, void* Ks, hipStream
 }
 
 // Up to this many candidates the selecting workgroup scores them itself: its 16 wavefronts hold all their key
-// rows in one round of loads, and the second launch costs more than it saves (whole steps, two launches ->
-// one: 128 candidates 18.1 -> 17.0 us, 511: 43.5 -> 43.0, 744: 54.2 -> 54.0, 1023: 58.2 -> 59.3).
-constexpr int64_t kOneLaunchCandidates = 768;
+// rows in one round of 16 loads each, and the second launch costs more than it saves (two launches -> one; bf16,
+// whole steps: 128 candidates 18.1 -> 17.0 us, 511: 43.5 -> 43.0, 744: 54.2 -> 54.0, 1023: 58.2 -> 59.3; fp32, D = 128,
+// whose rounds are 512 keys, the search alone: 500: 9.4 -> 8.5, 600: 9.4 -> 9.8, 760: 9.5 -> 10.3, but with 16 heads a
+// group, which the scoring launch takes in two halves, 600: 12.0 -> 10.0, 760: 12.1 -> 10.4).
+template <typename T, int D>
+int64_t one_launch_candidates(int G) {
+  constexpr int64_t round = (kDecodeSearchThreads / 64) * RowLayout<T, D>::RPW * 16;
+  return round < 768 && G <= 8 ? round : 768;
+}
 
 template <typename T, int D>
 sl_status launch_decode_search(const Problem& pb, const void* Qs, const void* K, const void* Ks,
@@ -903,7 +909,7 @@ sl_status launch_decode_search(const Problem& pb, const void* Qs, const void* K,
     // per head selects (block-parallel selection: candidates fit 4 registers per thread).
     // (a cache with more spans than that sizes no workspace: its shorter queries score in the
     // selecting workgroup itself)
-    float* sc_ws = c > kOneLaunchCandidates && pb.n <= (int64_t)kDecodeSearchThreads * 4 ? static_cast<float*>(ws) : nullptr;
+    float* sc_ws = c > one_launch_candidates<T, D>(pb.G) && pb.n <= (int64_t)kDecodeSearchThreads * 4 ? static_cast<float*>(ws) : nullptr;
     const int64_t ld = decode_score_ld(pb);
     if (c > 0 && sc_ws)
       hipLaunchKernelGGL((decode_score_group_kernel<T, D>), dim3((unsigned)((c + kScoreCand - 1) / kScoreCand), pb.Hkv),
