@@ -137,6 +137,62 @@ def test_any_span_length_on_the_matrix_cores(Hq, Hkv, L, D, S, A, k, form, q_pos
         assert float((LSE - RL).abs().max()) <= 1e-5
 
 
+def token_major(x):
+    """The same values with the heads of a token side by side and a gap behind them."""
+    H, T, D = x.shape
+    buf = torch.full((T, H + 1, D), float("nan"), dtype=x.dtype, device=x.device)
+    buf[:, :H] = x.transpose(0, 1)
+    return buf[:, :H].transpose(0, 1)
+
+
+@pytest.mark.parametrize("D,S,form", [(64, 64, "joint"), (128, 77, "joint"), (128, 77, "gated")])
+def test_any_span_length_with_strided_inputs(D, S, form):
+    """Token-major queries and caches with gaps: the packed inputs' result to the bit."""
+    Q, K, V = make(810 + D, 8, 2, 6000, D, torch.bfloat16, Lq=5000, scale=0.35)
+    idx, sc = B.sl_span_search_prefill(Q, K, None, S, 8, q_pos0=1000, want_scores=True)
+    q, kk, v = token_major(Q), token_major(K), token_major(V)
+    assert takes_matrix_cores(q, kk, S, 8, 1000) and takes_matrix_cores(Q, K, S, 8, 1000)
+    if form == "joint":
+        a, b = (B.sl_span_attention_prefill(*x, idx, S, q_pos0=1000) for x in ((Q, K, V), (q, kk, v)))
+    else:
+        a, b = ((B.sl_span_attention_combined_prefill(*x, idx, sc, S, q_pos0=1000),) for x in ((Q, K, V), (q, kk, v)))
+    torch.cuda.synchronize()
+    assert all(torch.equal(x, y) for x, y in zip(a, b)) and bool(torch.isfinite(a[0].float()).all())
+
+
+@pytest.mark.parametrize("D,k", [(64, 2), (128, 4)])
+def test_anchor_search_on_the_matrix_cores_with_strided_inputs(D, k):
+    """Token-major queries and keys with gaps: the packed inputs' result to the bit."""
+    L, q0 = 30000, 28500
+    Q, K, _ = make(1150 + D, 8, 2, L, D, torch.bfloat16, Lq=L - q0, scale=0.5)
+    a, b = (B.sl_anchor_search_prefill(*x, k, 24, q_pos0=q0, want_scores=True) for x in ((Q, K), (token_major(Q), token_major(K))))
+    torch.cuda.synchronize()
+    assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])
+
+
+@pytest.mark.parametrize("form", ["joint", "gated"])
+def test_any_span_length_in_several_passes_over_the_kv_heads(form):
+    """More partials than 4 GiB of scratch hold: three kv heads, then the fourth, in the same workspace."""
+    Hq, Hkv, L, D, S, k = 32, 4, 30011, 128, 174, 8
+    std = 1.0 if form == "joint" else 0.35
+    Q, K, V = make(820, Hq, Hkv, L, D, torch.bfloat16, scale=std)
+    idx, sc = B.sl_span_search_prefill(Q, K, None, S, k, want_scores=True)
+    need = B.workspace_bytes(B.make_params(Q, K, S, k), B.OP_ATTENTION_PREFILL)
+    assert 3 * Hq // Hkv * L * (k + 1) * D * 4 < need < Hq * L * (k + 1) * D * 4
+    if form == "joint":
+        O, LSE = B.sl_span_attention_prefill(Q, K, V, idx, S)
+        R, RL = row_form(Q, K, V, idx, None, S)
+        assert float((LSE - RL).abs().max()) <= 1e-5
+    else:
+        O, R = B.sl_span_attention_combined_prefill(Q, K, V, idx, sc, S), row_form(Q, K, V, idx, sc, S)
+    torch.cuda.synchronize()
+    o, r = O.float(), R.float()
+    assert float(((o - r).abs() - r.abs() * 2 ** -7).max()) <= 1e-4
+    for kv in range(Hkv):
+        turned = float((o != r)[kv * Hq // Hkv:(kv + 1) * Hq // Hkv].float().mean())
+        assert 0.0 < turned <= 0.02, (kv, turned)
+
+
 @pytest.mark.parametrize("D", [64, 128])
 def test_any_span_length_keeps_fp32_weights(D):
     """Rows whose softmax is three keys and whose values cancel: the output is what the weights' rounding leaves.
