@@ -538,6 +538,7 @@ __device__ __forceinline__ void flash_tile(const FlashArgs& a, char* lds, const 
   const int grp = wave >> 2, w4 = wave & 3;  // grp 0 = early, 1 = late
   const int qc = lane & 31, hf = lane >> 5;
   const int srow = w4 * 32 + qc;             // row inside the group's 128-row half tile
+  static_assert(NG == 1 || !FINE, "fp32 partials leave with their tile: one group's output region");
   constexpr bool kMasked = LOCAL || CLIP;
   using Lds = FlashLds<NG, D>;
   constexpr int kStageElems = Lds::kStageElems;
@@ -744,7 +745,7 @@ __device__ __forceinline__ void flash_tile(const FlashArgs& a, char* lds, const 
     __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
     __syncthreads();
     const int kb1 = kb == kStagesK - 1 ? 0 : kb + 1, vb1 = vb == kStagesV - 1 ? 0 : vb + 1;
-    if (NG == 2 && !LOCAL && !FINE && c.pending) {
+    if (NG == 2 && !LOCAL && c.pending) {
       // the previous tile's output: written out here, a step after it was staged, so that the wait
       // at the top of this tile did not have to cover its stores
       flush_routed_output(lds, grp, w4, lane);
@@ -954,8 +955,9 @@ __device__ __forceinline__ void flash_tile(const FlashArgs& a, char* lds, const 
 // CLIP (overlapping spans, anchor spacing A < S, joint softmax): a row's range in span j starts behind
 // the end of the nearest lower span that the row lists, so that every token of the union counts once.
 // FINE (with CLIP): fp32 weights and partials, spans of any length at any offset; a row's range is its whole
-// span unless a->clip says that spans of a row overlap in one softmax.
-template <bool CLIP, int NG = 2, int D = HD, bool FINE = false>
+// span unless a->clip says that spans of a row overlap in one softmax.  Tiles of 128 rows, two workgroups per
+// compute unit: one's tile ends run beside the other's kv loop.
+template <bool CLIP, int D = HD, bool FINE = false, int NG = FINE ? 1 : 2>
 __global__ __launch_bounds__(NG * 256, NG == 2 ? 1 : 2) void span_flash_routed_kernel(
     const FlashArgs a) {
   using Lds = FlashLds<NG, D>;
@@ -1000,43 +1002,42 @@ __global__ __launch_bounds__(NG * 256, NG == 2 ? 1 : 2) void span_flash_routed_k
   carry.kb = carry.vb = 0;
   carry.primed = false;
   carry.pending = false;
-  // The record and the items of a workgroup's next tile are requested during the current tile's
-  // first kv step as direct global->LDS loads into the wavefront's own 512 bytes (the items of tile t sit
-  // at t*TM, so the two do not depend on each other) and read back at its tail.
   if constexpr (NG == 1) {
-    // two workgroups per compute unit: one's tile ends run beside the other's kv loop
     for (int64_t t = t_begin; t < t_end; t += NWL) {
       TileDesc cur = describe(a.tile_info[t], a.items[t * TM + qrow]), unused = cur;
       flash_tile<1, false, false, CLIP, D, FINE>(a, lds, cur, unused, false, [] {}, [&] { return cur; }, carry);
       __syncthreads();  // the next tile's stages lie over the output slices of all wavefronts
     }
-    return;
+  } else {
+    // The record and the items of a workgroup's next tile are requested during the current tile's
+    // first kv step as direct global->LDS loads into the wavefront's own 512 bytes (the items of tile t sit
+    // at t*TM, so the two do not depend on each other) and read back at its tail.
+    int* const ahead = reinterpret_cast<int*>(lds + Lds::kAhead) + __builtin_amdgcn_readfirstlane(wave) * 128;
+    const int4 info0 = a.tile_info[t_begin];
+    TileDesc cur = describe(info0, a.items[t_begin * TM + qrow]);
+    for (int64_t t = t_begin; t < t_end; t += NWL) {
+      const bool has_next = t + NWL < t_end;
+      TileDesc nxt = cur;
+      flash_tile<2, false, false, CLIP>(
+          a, lds, cur, nxt, has_next,
+          [&] {
+            const ArgsPtr a = args_anew();
+            const int uw = __builtin_amdgcn_readfirstlane(wave);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(buffer_of(a->tile_info + (t + NWL), 16), SL_LDS_PTR(ahead), 4,
+                                                     (lane & 3) * 4, 0, 0, 0);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(buffer_of(a->items + (t + NWL) * TM + uw * 32, 128),
+                                                     SL_LDS_PTR(ahead + 64), 4, (lane & 31) * 4, 0, 0, 0);
+          },
+          [&] {
+            const int4 ninfo = make_int4(ahead[0], ahead[1], ahead[2], 0);
+            return describe(ninfo, ahead[64 + lane]);
+          },
+          carry);
+      cur = nxt;
+    }
+    // the last tile's output (its epilogue ended with the wavefront's own LDS writes)
+    if (carry.pending) flush_routed_output(lds, wave >> 2, wave & 3, lane);
   }
-  int* const ahead = reinterpret_cast<int*>(lds + Lds::kAhead) + __builtin_amdgcn_readfirstlane(wave) * 128;
-  const int4 info0 = a.tile_info[t_begin];
-  TileDesc cur = describe(info0, a.items[t_begin * TM + qrow]);
-  for (int64_t t = t_begin; t < t_end; t += NWL) {
-    const bool has_next = t + NWL < t_end;
-    TileDesc nxt = cur;
-    flash_tile<NG, false, false, CLIP, D, FINE>(
-        a, lds, cur, nxt, has_next,
-        [&] {
-          const ArgsPtr a = args_anew();
-          const int uw = __builtin_amdgcn_readfirstlane(wave);
-          __builtin_amdgcn_raw_ptr_buffer_load_lds(buffer_of(a->tile_info + (t + NWL), 16), SL_LDS_PTR(ahead), 4,
-                                                   (lane & 3) * 4, 0, 0, 0);
-          __builtin_amdgcn_raw_ptr_buffer_load_lds(buffer_of(a->items + (t + NWL) * TM + uw * 32, 128),
-                                                   SL_LDS_PTR(ahead + 64), 4, (lane & 31) * 4, 0, 0, 0);
-        },
-        [&] {
-          const int4 ninfo = make_int4(ahead[0], ahead[1], ahead[2], 0);
-          return describe(ninfo, ahead[64 + lane]);
-        },
-        carry);
-    cur = nxt;
-  }
-  // the last tile's output (its epilogue ended with the wavefront's own LDS writes)
-  if (!FINE && carry.pending) flush_routed_output(lds, wave >> 2, wave & 3, lane);
 }
 
 // The paper's geometry: routed tiles of a (kv head, end block) bucket.  Every row of a tile has
@@ -1625,8 +1626,6 @@ sl_status prefill_attention_mfma(const Problem& pb, const void* Q, const void* K
 // Calls without a workspace, or with one too small, take the row-stationary kernels as before.
 namespace {
 
-constexpr int kFineGroups = 1;
-
 // Estimated us of the two forms; the call takes the smaller.  Row-stationary: 0.02 ns per row and key, with
 // about 13 keys' worth of latency per slot, and no less than one row's own chain of loads.  This form: nine
 // launches, tiles of 4 us plus 2.6 us per kv tile on 512 workgroups (a bucket's last tile is padded),
@@ -1652,7 +1651,7 @@ Problem fine_part(const Problem& pb, int kv_heads) {  // the first kv_heads kv h
 }
 
 size_t fine_bytes(const Problem& pb) {
-  return carve(pb, kFineGroups * TG, sizeof(float)).total;
+  return carve(pb, TG, sizeof(float)).total;
 }
 
 // kv heads per pass: as many as fit the scratch limit
@@ -1670,9 +1669,9 @@ bool fine_setup(DeviceSetup* out) {
   if (!device_setup(out) || hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return false;
   std::lock_guard<std::mutex> lock(mu);
   if (!done[dev])
-    done[dev] = hipFuncSetAttribute(reinterpret_cast<const void*>(span_flash_routed_kernel<true, kFineGroups, D, true>),
+    done[dev] = hipFuncSetAttribute(reinterpret_cast<const void*>(span_flash_routed_kernel<true, D, true>),
                                     hipFuncAttributeMaxDynamicSharedMemorySize,
-                                    FlashLds<kFineGroups, D>::kBytes) == hipSuccess &&
+                                    FlashLds<1, D>::kBytes) == hipSuccess &&
                 hipFuncSetAttribute(reinterpret_cast<const void*>(span_flash_local_kernel<false, D, true>),
                                     hipFuncAttributeMaxDynamicSharedMemorySize, FlashLds<1, D>::kBytes) == hipSuccess;
   return done[dev];
@@ -1681,7 +1680,7 @@ bool fine_setup(DeviceSetup* out) {
 template <int D>
 sl_status fine_pass(const Problem& pb, const DeviceSetup& dev, const bf16_t* Q, const bf16_t* K, const bf16_t* V,
                     const int32_t* idx, bf16_t* O, float* LSE, char* base, hipStream_t st) {
-  const MfmaWs w = carve(pb, kFineGroups * TG, sizeof(float));
+  const MfmaWs w = carve(pb, TG, sizeof(float));
   int* item_off = reinterpret_cast<int*>(base + w.item_off);
   int* tile_off = reinterpret_cast<int*>(base + w.tile_off);
   int4* tile_info = reinterpret_cast<int4*>(base + w.tile_info);
@@ -1723,13 +1722,12 @@ sl_status fine_pass(const Problem& pb, const DeviceSetup& dev, const bf16_t* Q, 
                       GridItems{pb.A}, flag, st))
     return SL_ERR_LAUNCH;
   if (pb.prof_start) (void)hipEventRecord(pb.prof_start, st);
-  using RoutedLds = FlashLds<kFineGroups, D>;
-  using LocalLds = FlashLds<1, D>;
-  hipLaunchKernelGGL((span_flash_routed_kernel<true, kFineGroups, D, true>),
-                     dim3(dev.grid * (kFineGroups == 1 ? 2 : 1)), dim3(RoutedLds::kThreads), RoutedLds::kBytes, st, a);
+  using Lds = FlashLds<1, D>;
+  hipLaunchKernelGGL((span_flash_routed_kernel<true, D, true>),
+                     dim3(2 * dev.grid), dim3(Lds::kThreads), Lds::kBytes, st, a);
   if (pb.prof_stop) (void)hipEventRecord(pb.prof_stop, st);
   hipLaunchKernelGGL((span_flash_local_kernel<false, D, true>), dim3(local_grid(pb.Lq, pb.A, pb.Hkv, pb.G)),
-                     dim3(LocalLds::kThreads), LocalLds::kBytes, st, a);
+                     dim3(Lds::kThreads), Lds::kBytes, st, a);
   const int64_t rows = (int64_t)pb.Hq * pb.Lq;
   constexpr int kRowsPerBlock = 256 / (D / 4);
   const dim3 mgrid((unsigned)((rows + kRowsPerBlock - 1) / kRowsPerBlock));
