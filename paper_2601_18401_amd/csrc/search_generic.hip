@@ -606,15 +606,15 @@ struct AnchorList {
 };
 
 // The rows that the matrix-core kernel below has left, whose first slot holds this mark (anchors are token
-// positions or -1): a workgroup looks at 4 * RPW rows of up to 8 heads and does the marked ones one after the
-// other, all its row groups sharing a row's candidates.  (There is hardly ever more than one in a call, and its
-// time counts in full: 189 candidates by one row group 24 us, by a wavefront's four 10 to 15, by sixteen 5.)
+// positions or -1): a workgroup looks at `rows` (up to 256) rows of up to 8 heads and does the marked ones one after
+// the other, all its row groups sharing a row's candidates.  (There are hardly ever more than a few in a call, and
+// their time counts in full: 189 candidates by one row group 24 us, by a wavefront's four 10 to 15, by sixteen 5.)
 constexpr int32_t kLeft = INT32_MIN;
 
 template <int D, int KMAX>
 __global__ __launch_bounds__(256) void prefill_anchor_search_left_kernel(
     const bf16_t* __restrict__ Qs, const bf16_t* __restrict__ K, int32_t* __restrict__ anchors,
-    float* __restrict__ scores, int64_t Lq, int64_t q_pos0, int G, int topk, int s0, int root,
+    float* __restrict__ scores, int64_t Lq, int64_t q_pos0, int G, int topk, int s0, int root, int rows,
     int64_t qsh, int64_t qst, int64_t kvsh, int64_t kvst) {
   using RL = RowLayout<bf16_t, D>;
   constexpr int EPL = RL::EPL, LPR = RL::LPR, RPW = RL::RPW, HB = 8, U = 8, STEP = 4 * RPW;
@@ -624,17 +624,17 @@ __global__ __launch_bounds__(256) void prefill_anchor_search_left_kernel(
   const int g = lane / LPR, lr = lane % LPR;
   const int nb = (G + HB - 1) / HB;
   const int kv = blockIdx.y / nb, h0 = (blockIdx.y % nb) * HB;
-  const int64_t r0 = (int64_t)blockIdx.x * STEP, rl = r0 + wave * RPW + g;
-  const bool mark = rl < Lq && anchors[((int64_t)(kv * G + h0) * Lq + (rl < Lq ? rl : 0)) * topk] == kLeft;
+  const int64_t r0 = (int64_t)blockIdx.x * rows, rl = r0 + threadIdx.x;
+  const bool look = (int)threadIdx.x < rows && rl < Lq;
+  const bool mark = look && anchors[((int64_t)(kv * G + h0) * Lq + (look ? rl : 0)) * topk] == kLeft;
   const unsigned long long mine = __builtin_amdgcn_ballot_w64(mark);
   if (lane == 0) s_left[wave] = mine;
   __syncthreads();
   const bf16_t* Kb = K + kv * kvsh;
   for (int w = 0; w < 4; ++w) {
     for (unsigned long long left = s_left[w]; left != 0ull;) {
-      const int group = __builtin_ctzll(left) / LPR;
-      left &= ~(((1ull << LPR) - 1ull) << (group * LPR));
-      const int64_t r = r0 + w * RPW + group, i = q_pos0 + r;
+      const int64_t r = r0 + w * 64 + __builtin_ctzll(left), i = q_pos0 + r;
+      left &= left - 1ull;
       const int c = (int)(iroot_floor(i + 1, root) - s0);  // marked: there are candidates
       uint4 qraw[HB];
 #pragma unroll
@@ -1037,7 +1037,10 @@ sl_status launch_anchor_search_rows(const Problem& pb, const void* Qs, const voi
         const int rounds = (blocks + 8 * kAnchorMaxChunk - 1) / (8 * kAnchorMaxChunk);
         const int chunk = (blocks + 8 * rounds - 1) / (8 * rounds);
         const dim3 grid((unsigned)(8 * rounds * chunk), groups);
-        const dim3 left_grid((unsigned)((pb.Lq + 4 * RPW - 1) / (4 * RPW)), groups);
+        // rows per workgroup of the second kernel: 16 to 256, for about 2048 workgroups
+        const int64_t share = (pb.Lq * groups + 2047) / 2048;
+        const int left_rows = share <= 16 ? 16 : share >= 256 ? 256 : (int)share;
+        const dim3 left_grid((unsigned)((pb.Lq + left_rows - 1) / left_rows), groups);
 #define SL_ANCHOR_MFMA(KM)                                                                                   \
   do {                                                                                                       \
     hipLaunchKernelGGL((prefill_anchor_search_mfma_kernel<D, KM>), grid, dim3(256), 0, st,                   \
@@ -1045,7 +1048,7 @@ sl_status launch_anchor_search_rows(const Problem& pb, const void* Qs, const voi
                        pb.q_pos0, pb.G, pb.topk, s0, root, blocks, chunk, pb.qsh, pb.qst, pb.kvsh, pb.kvst); \
     hipLaunchKernelGGL((prefill_anchor_search_left_kernel<D, KM>), left_grid, dim3(256), 0, st,              \
                        static_cast<const bf16_t*>(Qs), static_cast<const bf16_t*>(K), anchors, scores, pb.Lq, \
-                       pb.q_pos0, pb.G, pb.topk, s0, root, pb.qsh, pb.qst, pb.kvsh, pb.kvst);                \
+                       pb.q_pos0, pb.G, pb.topk, s0, root, left_rows, pb.qsh, pb.qst, pb.kvsh, pb.kvst);     \
   } while (0)
         if (pb.topk <= 2) SL_ANCHOR_MFMA(2);
         else SL_ANCHOR_MFMA(4);
