@@ -605,80 +605,6 @@ struct AnchorList {
   }
 };
 
-// The rows that the matrix-core kernel below has left, whose first slot holds this mark (anchors are token
-// positions or -1): a workgroup looks at `rows` (up to 256) rows of up to 8 heads and does the marked ones one after
-// the other, all its row groups sharing a row's candidates.  (There are hardly ever more than a few in a call, and
-// their time counts in full: 189 candidates by one row group 24 us, by a wavefront's four 10 to 15, by sixteen 5.)
-constexpr int32_t kLeft = INT32_MIN;
-
-template <int D, int KMAX>
-__global__ __launch_bounds__(256) void prefill_anchor_search_left_kernel(
-    const bf16_t* __restrict__ Qs, const bf16_t* __restrict__ K, int32_t* __restrict__ anchors,
-    float* __restrict__ scores, int64_t Lq, int64_t q_pos0, int G, int topk, int s0, int root, int rows,
-    int64_t qsh, int64_t qst, int64_t kvsh, int64_t kvst) {
-  using RL = RowLayout<bf16_t, D>;
-  constexpr int EPL = RL::EPL, LPR = RL::LPR, RPW = RL::RPW, HB = 8, U = 8, STEP = 4 * RPW;
-  __shared__ unsigned long long s_left[4];
-  __shared__ AnchorList<KMAX> s_top[4][HB];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int g = lane / LPR, lr = lane % LPR;
-  const int nb = (G + HB - 1) / HB;
-  const int kv = blockIdx.y / nb, h0 = (blockIdx.y % nb) * HB;
-  const int64_t r0 = (int64_t)blockIdx.x * rows, rl = r0 + threadIdx.x;
-  const bool look = (int)threadIdx.x < rows && rl < Lq;
-  const bool mark = look && anchors[((int64_t)(kv * G + h0) * Lq + (look ? rl : 0)) * topk] == kLeft;
-  const unsigned long long mine = __builtin_amdgcn_ballot_w64(mark);
-  if (lane == 0) s_left[wave] = mine;
-  __syncthreads();
-  const bf16_t* Kb = K + kv * kvsh;
-  for (int w = 0; w < 4; ++w) {
-    for (unsigned long long left = s_left[w]; left != 0ull;) {
-      const int64_t r = r0 + w * 64 + __builtin_ctzll(left), i = q_pos0 + r;
-      left &= left - 1ull;
-      const int c = (int)(iroot_floor(i + 1, root) - s0);  // marked: there are candidates
-      uint4 qraw[HB];
-#pragma unroll
-      for (int hb = 0; hb < HB; ++hb)
-        qraw[hb] = load16(Qs + (int64_t)(kv * G + (h0 + hb < G ? h0 + hb : G - 1)) * qsh + r * qst + lr * EPL);
-      AnchorList<KMAX> top;
-      top.clear();
-      for (int jb = wave * RPW + g; jb - (wave * RPW + g) < c; jb += U * STEP) {
-        uint4 kr[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-          const int j = jb + u * STEP < c ? jb + u * STEP : c - 1;
-          kr[u] = load16(Kb + anchor_token_of(i, (int64_t)s0 + j, root) * kvst + lr * EPL);
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-          float part[HB];
-#pragma unroll
-          for (int hb = 0; hb < HB; ++hb) part[hb] = Piece<bf16_t>::dot(kr[u], qraw[hb], 0.f);
-          const float x = group_sum_scatter8<LPR>(part, lr);
-          const int j = jb + u * STEP;
-          top.insert(j < c ? x : -INFINITY, j, false);
-        }
-      }
-#pragma unroll
-      for (int off = LPR; off < 64; off <<= 1) top.merge(off);
-      if (lane < HB) s_top[wave][lane] = top;
-      __syncthreads();
-      if (threadIdx.x < HB && h0 + lane < G) {
-#pragma unroll
-        for (int o = 1; o < 4; ++o) {
-          const AnchorList<KMAX> other = s_top[o][lane];
-#pragma unroll
-          for (int e = 0; e < KMAX; ++e)
-            top.insert(other.id[e] >= 0 ? other.v[e] : -INFINITY, other.id[e], other.id[e] >= 0);
-        }
-        const int64_t row = (int64_t)(kv * G + h0 + lane) * Lq + r;
-        top.store(topk, i, s0, root, anchors + row * topk, scores ? scores + row * topk : nullptr);
-      }
-      __syncthreads();  // the lists are read
-    }
-  }
-}
-
 // The same search for bf16 and short lists on the matrix cores.  A wavefront owns two query rows and up to 8 query heads of
 // a kv head; the 16 columns of v_mfma_f32_16x16x32_bf16 are (row, head).  Sixteen candidates of one row
 // -- gathered key rows -- are the A operand; each row's keys are multiplied with all 16 columns and a lane
@@ -696,12 +622,12 @@ __global__ __launch_bounds__(256) void prefill_anchor_search_left_kernel(
 // 48645 tokens ran on one XCD, 78 -> 25 us):
 // at the same stride index their keys are neighbours and the next index finds them in that L2.  Rows with
 // the most candidates come first.  49157 rows, 32:4 heads, window 1088, top-2: 956 us with vector
-// instructions (two-element dot products and a lane-group sum per score), 677 us now, of which the second scoring
-// below takes 150 and keeping to the other kernels' selection (the margin, the rows left) 30.
+// instructions (two-element dot products and a lane-group sum per score), 675 us now, of which the second scoring
+// below takes 150 and keeping to the other kernels' selection (the margin, the rows left) 25.
 constexpr int kAnchorRowsPerBlock = 8, kAnchorMaxChunk = 64;
 
 template <int D, int KMAX>
-__global__ __launch_bounds__(256, 4) void prefill_anchor_search_mfma_kernel(
+__global__ __launch_bounds__(256, D == 64 ? (KMAX <= 2 ? 8 : 6) : 4) void prefill_anchor_search_mfma_kernel(
     const bf16_t* __restrict__ Qs, const bf16_t* __restrict__ K, int32_t* __restrict__ anchors,
     float* __restrict__ scores, int64_t Lq, int64_t q_pos0, int G, int topk, int s0, int root, int blocks, int chunk,
     int64_t qsh, int64_t qst, int64_t kvsh, int64_t kvst) {
@@ -827,7 +753,7 @@ __global__ __launch_bounds__(256, 4) void prefill_anchor_search_mfma_kernel(
       lost = lost || (id[KL - 1] >= 0 && !(v[e - 1] - v[KL - 1] > margin && in_range));
     }
   // A row with a head whose k-th score and the last of the list are that close (equal keys, or lengths that leave
-  // the range of their squares, or are not finite) is left to prefill_anchor_search_left_kernel: its first slot is marked.
+  // the range of their squares, or are not finite) is searched again below: one in 10^4 for random scores.
   const unsigned long long redo = __builtin_amdgcn_ballot_w64(lost);
   const bool left = (redo & (second ? 0xFF00FF00FF00FF00ull : 0x00FF00FF00FF00FFull)) != 0ull;
   // Otherwise the list holds the selection: where the k-th and the next are close (some in a thousand for random
@@ -868,11 +794,47 @@ __global__ __launch_bounds__(256, 4) void prefill_anchor_search_mfma_kernel(
     score_again(std::integral_constant<int, KMAX>{});
   }
   const int64_t r = second ? r0 + 1 : r0;
-  if (left) {
-    if (q4 == 0 && (n & 7) == 0 && r < Lq) anchors[((int64_t)(kv * G + h0) * Lq + r) * topk] = kLeft;
-  } else if (q4 == 0 && r < Lq && h0 + (n & 7) < G) {
+  if (!left && q4 == 0 && r < Lq && h0 + (n & 7) < G) {
     const int64_t row = (int64_t)(kv * G + head) * Lq + r;
     top.store(topk, q_pos0 + r, s0, root, anchors + row * topk, scores ? scores + row * topk : nullptr);
+  }
+  // The rows left: all their candidates with the vector kernel's arithmetic, the wavefront's row groups side by side.
+  // (A second launch that looked for marked rows took 6 to 13 us of every call.)
+  for (int half = 0; half < 2; ++half) {
+    if ((redo & (half ? 0xFF00FF00FF00FF00ull : 0x00FF00FF00FF00FFull)) == 0ull || r0 + half >= Lq) continue;
+    using RL = RowLayout<bf16_t, D>;
+    constexpr int LPR = RL::LPR, RPW = RL::RPW, U = 4;  // (eight loads cost the whole kernel registers)
+    const int g = lane / LPR, lr = lane % LPR, cr = half ? c1 : c0;
+    const int64_t i = q_pos0 + r0 + half;
+    uint4 qraw[HB];
+#pragma unroll
+    for (int hb = 0; hb < HB; ++hb)
+      qraw[hb] = load16(Qs + (int64_t)(kv * G + (h0 + hb < G ? h0 + hb : G - 1)) * qsh + (r0 + half) * qst + lr * RL::EPL);
+    AnchorList<KMAX> list;
+    list.clear();
+    for (int jb = 0; jb < cr; jb += U * RPW) {
+      uint4 kr[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int j = jb + u * RPW + g < cr ? jb + u * RPW + g : cr - 1;
+        kr[u] = load16(Kh + anchor_token_of(i, (int64_t)s0 + j, root) * kvst + lr * RL::EPL);
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        float part[HB];
+#pragma unroll
+        for (int hb = 0; hb < HB; ++hb) part[hb] = Piece<bf16_t>::dot(kr[u], qraw[hb], 0.f);
+        const float x = group_sum_scatter8<LPR>(part, lr);
+        const int j = jb + u * RPW + g;
+        list.insert(j < cr ? x : -INFINITY, j, false);
+      }
+    }
+#pragma unroll
+    for (int off = LPR; off < 64; off <<= 1) list.merge(off);
+    if (lane < HB && h0 + lane < G) {
+      const int64_t row = (int64_t)(kv * G + h0 + lane) * Lq + r0 + half;
+      list.store(topk, i, s0, root, anchors + row * topk, scores ? scores + row * topk : nullptr);
+    }
   }
 }
 
@@ -1019,37 +981,31 @@ sl_status launch_anchor_search_rows(const Problem& pb, const void* Qs, const voi
   if (pb.topk <= 8) {  // key rows shared by the heads of a kv group, top-k lists in registers
     const unsigned groups = (unsigned)(pb.Hkv * ((pb.G + 7) / 8));
     if (pb.prof_start) (void)hipEventRecord(pb.prof_start, st);
-    constexpr int RPW = RowLayout<T, D>::RPW;
     bool done = false;
     if constexpr (std::is_same<T, bf16_t>::value) {
       // The matrix cores where the rows have enough candidates (the middle row's number) to make up for what a
       // wavefront does once: set up, merge its lanes' lists, score the winners again.  Vector -> matrix cores, us,
-      // 32:4 heads, whole prompts, window 1088 unless said otherwise:
-      //   up to 2 anchors: 8000 rows (31 candidates) 61 -> 65, 8000 with window 255 (48) 83 -> 73, 12000 (45)
-      //     109 -> 97, 20000 (68) 237 -> 181; D = 64: 8000 44.7 -> 47.1, 20000 128 -> 120;
-      //   3 and 4: 12000 122 -> 154, 20000 267 -> 271, 30000 (90) 486 -> 437, 49157 (124) 1066 -> 855;
-      //     D = 64: 30000 259 -> 295, 49157 555 -> 520;
-      //   5 to 8: 20000 320 -> 746: every lane keeps a list of its own; 512 rows behind 48645 tokens 57 -> 202.
-      const int64_t mid = iroot_floor(pb.q_pos0 + pb.Lq / 2 + 1, root) - s0;
-      if (pb.topk <= 4 && mid >= (pb.topk <= 2 ? 40 : D == 128 ? 80 : 110)) {
+      // by rows x groups of up to 8 heads and candidates:
+      //   up to 2 anchors: 256 x 45 13.4 -> 13.3, 2048 x 45 14.4 -> 15.2, x 80 22.5 -> 20.0, 4096 x 80 23.7 -> 23.0,
+      //     8192 x 45 26.3 -> 24.7, 16384 x 45 50 -> 41, 32768 x 80 129 -> 83; whole prompt of 49157 955 -> 675;
+      //     D = 64: 2048 x 80 21 -> 16, 8192 x 60 20 -> 23, x 110 29 -> 25, 32768 x 80 76 -> 60;
+      //   3 and 4: 2048 x 110 30 -> 28, 4096 x 110 32 -> 36, 8192 x 80 41.8 -> 42.3, x 110 54 -> 48, 16384 x 45 56 -> 63,
+      //     x 80 80 -> 71, 32768 x 80 144 -> 123; whole prompt of 49157 1066 -> 855;  D = 64: 16384 x 110 54 -> 57, whole
+      //     prompt of 49157 555 -> 530;
+      //   5 to 8: whole prompt of 20000 320 -> 746: every lane keeps a list of its own; 2048 x 189 57 -> 202.
+      const int64_t mid = iroot_floor(pb.q_pos0 + pb.Lq / 2 + 1, root) - s0, work = pb.Lq * groups;
+      const int64_t least = pb.topk <= 2 ? (D == 64 ? 80 : work >= 8192 ? 40 : 64)
+                                         : (D == 64 ? 120 : work >= 16384 ? 72 : work >= 8192 ? 90 : 150);
+      if (pb.topk <= 4 && mid >= least) {
         const int blocks = (int)((pb.Lq + kAnchorRowsPerBlock - 1) / kAnchorRowsPerBlock);
         // as few rounds of one chunk for each XCD as the longest chunk allows, all chunks alike
         const int rounds = (blocks + 8 * kAnchorMaxChunk - 1) / (8 * kAnchorMaxChunk);
         const int chunk = (blocks + 8 * rounds - 1) / (8 * rounds);
         const dim3 grid((unsigned)(8 * rounds * chunk), groups);
-        // rows per workgroup of the second kernel: 16 to 256, for about 2048 workgroups
-        const int64_t share = (pb.Lq * groups + 2047) / 2048;
-        const int left_rows = share <= 16 ? 16 : share >= 256 ? 256 : (int)share;
-        const dim3 left_grid((unsigned)((pb.Lq + left_rows - 1) / left_rows), groups);
 #define SL_ANCHOR_MFMA(KM)                                                                                   \
-  do {                                                                                                       \
-    hipLaunchKernelGGL((prefill_anchor_search_mfma_kernel<D, KM>), grid, dim3(256), 0, st,                   \
-                       static_cast<const bf16_t*>(Qs), static_cast<const bf16_t*>(K), anchors, scores, pb.Lq, \
-                       pb.q_pos0, pb.G, pb.topk, s0, root, blocks, chunk, pb.qsh, pb.qst, pb.kvsh, pb.kvst); \
-    hipLaunchKernelGGL((prefill_anchor_search_left_kernel<D, KM>), left_grid, dim3(256), 0, st,              \
-                       static_cast<const bf16_t*>(Qs), static_cast<const bf16_t*>(K), anchors, scores, pb.Lq, \
-                       pb.q_pos0, pb.G, pb.topk, s0, root, left_rows, pb.qsh, pb.qst, pb.kvsh, pb.kvst);     \
-  } while (0)
+  hipLaunchKernelGGL((prefill_anchor_search_mfma_kernel<D, KM>), grid, dim3(256), 0, st,                     \
+                     static_cast<const bf16_t*>(Qs), static_cast<const bf16_t*>(K), anchors, scores, pb.Lq,  \
+                     pb.q_pos0, pb.G, pb.topk, s0, root, blocks, chunk, pb.qsh, pb.qst, pb.kvsh, pb.kvst)
         if (pb.topk <= 2) SL_ANCHOR_MFMA(2);
         else SL_ANCHOR_MFMA(4);
 #undef SL_ANCHOR_MFMA
@@ -1057,6 +1013,7 @@ sl_status launch_anchor_search_rows(const Problem& pb, const void* Qs, const voi
       }
     }
     if (!done) {
+      constexpr int RPW = RowLayout<T, D>::RPW;
       const dim3 grid((unsigned)((pb.Lq + 4 * RPW - 1) / (4 * RPW)), groups);
 #define SL_ANCHOR_GROUP(KM)                                                                               \
   hipLaunchKernelGGL((prefill_anchor_search_group_kernel<T, D, KM>), grid, dim3(256), 0, st,              \

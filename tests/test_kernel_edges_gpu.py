@@ -371,11 +371,11 @@ def test_decode_entries_sharing_chunks_go_in_pairs(form, dtype, Hq, Hkv, S, A, k
     (6, 2, 128, 9000, 3, 8, 3, 1030, 7970),      # cubes; rows past one chunk of the block order
     (8, 2, 128, 20, 2, 1088, 2, None, 0),        # no row has a candidate
     # the same where the rows have candidates enough for the matrix cores
-    (8, 1, 128, 8000, 2, 0, 2, None, 0),
+    (8, 1, 128, 8500, 2, 0, 2, None, 0),
     (8, 2, 128, 14001, 4, 0, 2, None, 0),
     (12, 1, 64, 30001, 4, 24, 2, 1501, 28500),
     (4, 4, 128, 40000, 3, 255, 2, 9, 39991),
-    (6, 1, 128, 600000, 3, 8, 3, 1030, 598970),
+    (6, 1, 128, 600000, 3, 8, 3, 17001, 582999),
 ])
 def test_anchor_search_on_the_matrix_cores(Hq, Hkv, D, L, k, w, root, Lq, q0):
     """Batches of 16 candidates, pairs of rows and the lists' merge against fp64 scores: the selection by the
@@ -426,7 +426,7 @@ def test_anchor_search_selects_as_the_decode_search_does(Hq, Hkv, D, k, kind):
     bit, and do not depend on how a prompt is cut.  Cancelling: two large channels of opposite sign, so that the
     order of the additions decides between scores.  Near-equal: three keys, each varying in one small element.  Zero: queries and stretches of keys that are all zero.  Infinite: a key that is not finite
     among finite ones."""
-    L, q0, w = 20000, 18000, 24
+    L, q0, w = 27000, 25000, 24
     Q, K, _ = make(1300 + D + k, Hq, Hkv, L, D, torch.bfloat16, Lq=L - q0, scale=0.3)
     if kind == "cancelling":
         Q[..., 3], Q[..., D - 20] = 61.0, -61.0
