@@ -44,26 +44,62 @@ struct TopVals {
   }
 };
 
-// Two passes over the candidate spans of 128 query rows (4 wavefronts x 32 columns):
+// Ascending order of N whole numbers (N a power of two): Batcher's odd-even merge exchange.
+template <int N, int P = 1, int K = 1>
+__device__ __forceinline__ void sort_ascending(int (&x)[N]) {
+#pragma unroll
+  for (int a = K % P; a + K < N; ++a)
+    if ((a - K % P) % (2 * K) < K && a / (2 * P) == (a + K) / (2 * P)) {
+      const int lo = min(x[a], x[a + K]), hi = max(x[a], x[a + K]);
+      x[a] = lo;
+      x[a + K] = hi;
+    }
+  if constexpr (K > 1) sort_ascending<N, P, K / 2>(x);
+  else if constexpr (2 * P < N) sort_ascending<N, 2 * P, 2 * P>(x);
+}
+
+// The value that lane l ^ 32 holds (both, in an order that depends on the half: the one that is not this lane's own).
+__device__ __forceinline__ float of_other_half(float x) {
+  const int own = __float_as_int(x);
+  auto a = __builtin_amdgcn_permlane32_swap(own, own, false, false);
+  return __int_as_float(a[0] == own ? a[1] : a[0]);
+}
+
+// The candidate spans of 128 query rows (4 wavefronts x 32 columns), scored by the matrix cores and selected in one
+// of two ways.  Both are bound by their vector instructions, not by loads or MFMAs: for 65536 rows x 256 spans, top-8,
+// the vector units were busy 78 % of the time, the matrix pipes 19 %, so instructions are what counts.
+//
+// One walk (no scores wanted, up to kPackedSpans candidates): a lane keeps its KMAX + 1 best scores with the span's
+// number in place of their lowest bits, a median instruction per list entry and score; the two lanes of a column merge
+// their lists.  Cutting a score towards zero keeps the order of scores that differ after it, so where the k'-th and
+// the next one do, the first k' entries are the selection, and no index had to be carried beside the scores.  Where
+// they agree in the bits that are left (one column in a thousand at 256 spans), and no third one does, those entries'
+// scores are computed again, by the same MFMAs on their own keys, and the lowest is dropped.  What is left over --
+// longer runs of equal scores, scores that are not finite or nearly so --
+// goes the other way, the whole workgroup.
+//
+// Two walks:
 //   pass 1  keeps, per lane, only the VALUES of the top-k scores it has seen (a lane sees half of
 //           its column's spans); the two lanes of a column are merged at the end, which gives the
 //           column's threshold T = k'-th largest score, k' = min(topk, c), and the number of
 //           scores above it;
-//   pass 2  recomputes the scores (the MFMAs are cheap next to the selection arithmetic) and
-//           appends every span with score > T, and up to need = k' - #(> T) spans per lane with
-//           score == T (its lowest-index ones), to the column's list in LDS;
+//   pass 2  recomputes the scores and appends every span with score > T, and up to
+//           need = k' - #(> T) spans per lane with score == T (its lowest-index ones), to the column's list in LDS;
 //   finish  one lane per column keeps the spans above T plus the `need` lowest-index spans at T
 //           (ties go to the lower index), and writes them in ascending span order.
-// Tracking values only makes the per-candidate cost of pass 1 k median instructions instead of
-// the compare-and-select chains that carrying the indices along would need.
 // WS: the scores of the selected spans are written too (their list costs LDS, which limits the
 // resident workgroups; most callers only want the indices).
 // DIRECT: stages of 32 span keys by direct global -> LDS loads into two buffers, one barrier each: while one is
-// scored the next is on its way.  Otherwise 64 keys through registers with two barriers.  Direct is the faster one
-// where four or five workgroups fit a compute unit; the lists of long selections and of scores leave fewer, and so do
-// grids that give a compute unit no more than four: there the longer stages win (see the launch).  Slower than both:
-// stages of 64 in two buffers (65536 rows x 32 heads, 256 spans, top-8: 390 us against 327) and three buffers of 32
-// (1024 spans: 934 us against 877).  Lists of at most 4 spans have their own KMAX: half of the median instructions.
+// scored the next is on its way.  Otherwise 64 keys through registers with two barriers.  The launch says which is
+// taken where.  Slower than both: stages of 64 in two buffers and three buffers of 32.  Lists of at most 4 spans have
+// their own KMAX: half of the median instructions.
+//
+// Two walks -> one, us, 32 heads: 65536 rows x 256 spans top-4 264 -> 160, top-8 312 -> 194, top-16 549 -> 298, top-32
+// 1320 -> 621; 16384 rows x 1024 spans, top-8 380 -> 232, x 2048 705 -> 516, x 4096 (where the second look at
+// agreeing scores is needed in most wavefronts) 1349 -> 1050; 500 rows x 256 23.4 -> 10.9; 3000 x 46 14.1 -> 8.9.  Where
+// all scores are equal the second way comes on top: 20000 x 156, top-8, 99 -> 135.
+constexpr int kPackedSpans = 4096;  // the most that was measured; beyond, too few bits of the score are left
+
 template <int KMAX, bool WS, bool DIRECT>
 __global__ __launch_bounds__(256, (KMAX <= 4 || (KMAX == 8 && !WS)) ? 4 : 1) void prefill_search_mfma_kernel(
     const bf16_t* __restrict__ Qs, const bf16_t* __restrict__ K, const bf16_t* __restrict__ Ks,
@@ -89,11 +125,13 @@ __global__ __launch_bounds__(256, (KMAX <= 4 || (KMAX == 8 && !WS)) ? 4 : 1) voi
   const int kv = h / G;
   const int64_t r = r0 + col;
   const int64_t rc = r < Lq ? r : Lq - 1;
-  const int c_q = (int)((q_pos0 + rc) / S);  // candidates of this lane's query: spans [0, c_q)
+  auto spans_below = [&](int64_t i) {  // (a 64-bit division by a variable takes four times the instructions)
+    return i < ((int64_t)1 << 31) ? (int)((uint32_t)i / (uint32_t)S) : (int)(i / S);
+  };
+  const int c_q = spans_below(q_pos0 + rc);  // candidates of this lane's query: spans [0, c_q)
   const int64_t r_last = (r0 + TMQ - 1 < Lq ? r0 + TMQ - 1 : Lq - 1);
-  const int c_max = (int)((q_pos0 + r_last) / S);
+  const int c_max = __builtin_amdgcn_readfirstlane(spans_below(q_pos0 + r_last));
   const int c_lo = __builtin_amdgcn_readfirstlane(c_q);  // rows ascend with the lane: lane 0 has the lowest c
-  if (tid < TMQ) s_cnt[tid] = 0;
 
   bf16x8 qf[8];
   {
@@ -101,27 +139,45 @@ __global__ __launch_bounds__(256, (KMAX <= 4 || (KMAX == 8 && !WS)) ? 4 : 1) voi
 #pragma unroll
     for (int kk = 0; kk < 8; ++kk) qf[kk] = *reinterpret_cast<const bf16x8*>(qp + kk * 16 + hf * 8);
   }
+  const bf16_t* const key0 = Ks ? Ks + (int64_t)kv * n * HD : K + kv * kvsh + (S - 1) * kvst;
+  const int64_t key_step = Ks ? HD : S * kvst;
+  auto key = [&](int j) { return key0 + j * key_step; };
 
-  // Walks the candidate spans in tiles of 32 and hands the lane's 16 scores of a tile, in
-  // ascending span order, to f(score, span index); scores of spans >= c_q come as -inf.
-  auto for_each_candidate = [&](auto f) {
-    auto key = [&](int j) {  // past the last candidate: that one again
-      const int64_t jj = j < c_max ? j : c_max - 1;
-      return Ks ? Ks + ((int64_t)kv * n + jj) * HD : K + kv * kvsh + ((jj + 1) * S - 1) * kvst;
-    };
-    // 16 lanes x 16 bytes per key.  DIRECT: 1 KB per load, pieces swizzled for the operand reads
-    auto stage = [&](int j0, int buf) {
+  // Walks the candidate spans in tiles of 32 and hands the lane's 16 scores of a tile to f(scores, first span of the
+  // tile, whether the tile reaches beyond the lowest c of the wavefront): score e is that of span 8 (e / 4) + 4 hf + e % 4 of it.
+  auto walk = [&](auto f) {
+    // 16 lanes x 16 bytes per key; DIRECT: 1 KB per load, pieces swizzled for the operand reads.  The lane's keys move
+    // on by one addition per stage; only the last stage looks for keys past the last candidate (that one again).
+    constexpr int NLD = DIRECT ? TNS / 16 : 4;
+    const bf16_t* src[NLD];
+    auto row_of = [&](int i) { return DIRECT ? (uwave * NLD + i) * 4 + (lane >> 4) : (tid >> 4) + 16 * i; };
+    auto piece_of = [&](int i) { return (DIRECT ? (lane & 15) ^ (row_of(i) & 15) : tid & 15) * 8; };
 #pragma unroll
-      for (int i = 0; i < TNS / 16; ++i) {
-        const int blk = uwave * (TNS / 16) + i, row = blk * 4 + (lane >> 4), piece = (lane & 15) ^ (row & 15);
-        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(key(j0 + row) + piece * 8),
-                                         (__attribute__((address_space(3))) void*)(s_k + buf * TNS * HD + blk * 512), 16, 0, 0);
+    for (int i = 0; i < NLD; ++i) src[i] = key(row_of(i)) + piece_of(i);
+    auto next_stage = [&](int j0) {
+      if (j0 + TNS > c_max) {
+#pragma unroll
+        for (int i = 0; i < NLD; ++i) src[i] = key(min(j0 + row_of(i), c_max - 1)) + piece_of(i);
       }
+    };
+    auto advance = [&]() {
+#pragma unroll
+      for (int i = 0; i < NLD; ++i) src[i] += TNS * key_step;
+    };
+    auto stage = [&](int j0, int buf) {
+      next_stage(j0);
+#pragma unroll
+      for (int i = 0; i < NLD; ++i)
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src[i],
+                                         (__attribute__((address_space(3))) void*)(s_k + buf * TNS * HD + (uwave * NLD + i) * 512), 16, 0, 0);
+      advance();
     };
     uint4 pre[DIRECT ? 1 : 4];
     auto fetch = [&](int j0) {
+      next_stage(j0);
 #pragma unroll
-      for (int i = 0; i < (DIRECT ? 0 : 4); ++i) pre[i] = load16(key(j0 + (tid >> 4) + 16 * i) + (tid & 15) * 8);
+      for (int i = 0; i < (DIRECT ? 0 : 4); ++i) pre[i] = load16(src[i]);
+      advance();
     };
     if (c_max > 0) {
       if constexpr (DIRECT) stage(0, 0);
@@ -156,24 +212,161 @@ __global__ __launch_bounds__(256, (KMAX <= 4 || (KMAX == 8 && !WS)) ? 4 : 1) voi
                     &cur[(32 * sub + qc) * St::kStride + (((2 * kk + hf) ^ (DIRECT ? qc & 15 : 0)) << 3)]);
             s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka, qf[kk], s, 0, 0, 0);
           }
-          // causal: only complete spans below the query's own.  A tile that ends at or below the
-          // lowest c of the wavefront (its first column's) needs no masking.
-          if (j0 + 32 * sub + 32 <= c_lo) {
-#pragma unroll
-            for (int e = 0; e < 16; ++e) f(s[e], j0 + 32 * sub + 8 * (e >> 2) + 4 * hf + (e & 3));
-          } else {
-#pragma unroll
-            for (int e = 0; e < 16; ++e) {
-              const int j = j0 + 32 * sub + 8 * (e >> 2) + 4 * hf + (e & 3);
-              f(j < c_q ? s[e] : -INFINITY, j);
-            }
-          }
+          f(s, j0 + 32 * sub, j0 + 32 * sub + 32 > c_lo);
         }
       }
       buf ^= 1;
     }
     __syncthreads();  // the next walk (or the lists' readers) may touch what this one used
   };
+  // The two-walk form's view: f(score, span index); scores of spans >= c_q (causal: only complete spans below the
+  // query's own) come as -inf.
+  auto for_each_candidate = [&](auto f) {
+    walk([&](const f32x16& s, int j0, bool edge) {
+      if (!edge) {
+#pragma unroll
+        for (int e = 0; e < 16; ++e) f(s[e], j0 + 8 * (e >> 2) + 4 * hf + (e & 3));
+      } else {
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+          const int j = j0 + 8 * (e >> 2) + 4 * hf + (e & 3);
+          f(j < c_q ? s[e] : -INFINITY, j);
+        }
+      }
+    });
+  };
+  const int kq = topk < c_q ? topk : c_q;  // spans to select for this column
+
+  if constexpr (!WS) {
+    if (c_max <= kPackedSpans) {
+      constexpr float kMasked = -3e38f, kNone = -3.3e38f;
+      const int number = (1 << (32 - __builtin_clz(c_max > 32 ? c_max - 1 : 31))) - 1;  // the bits of a span's number
+      int keep = ~number;
+      asm volatile("" : "+v"(keep));  // (in a vector register: an instruction takes one scalar operand, the number)
+      auto cut = [&](float x) { return __int_as_float(__float_as_int(x) & keep); };
+      TopVals<KMAX + 1> own;
+#pragma unroll
+      for (int e = 0; e <= KMAX; ++e) own.v[e] = cut(kNone);
+      // an infinite score with a number in its low bits is a NaN, and a signalling one: it would unsettle the list
+      int largest = 0;
+      unsigned lowest = 0x80000000u;  // of the negative ones, as unsigned numbers: larger is lower
+      float infinity = INFINITY;
+      asm volatile("" : "+v"(infinity));
+      auto numbered = [&](float x, int j) {
+        asm volatile("" : "+s"(j));  // one v_and_or
+        return (__float_as_int(x) & keep) | j;
+      };
+      auto push = [&](int p) {
+        const float f = __int_as_float(p);
+#pragma unroll
+        for (int e = KMAX; e >= 1; --e) own.v[e] = __builtin_amdgcn_fmed3f(f, own.v[e - 1], own.v[e]);
+        own.v[0] = __builtin_amdgcn_fmed3f(f, own.v[0], infinity);  // (a maximum that makes no numbers canonical first)
+      };
+      walk([&](const f32x16& s, int j0, bool edge) {
+        const int left = c_q - j0 - 4 * hf;
+        auto tile = [&](auto score) {
+#pragma unroll
+          for (int e = 0; e < 16; e += 2) {
+            const int u = 8 * (e >> 2) + (e & 3);
+            const int p = numbered(score(s[e], u), j0 + u), q = numbered(score(s[e + 1], u + 1), j0 + u + 1);
+            largest = max(max(largest, p), q);
+            lowest = max(max(lowest, (unsigned)p), (unsigned)q);
+            push(p);
+            push(q);
+          }
+        };
+        if (edge) tile([&](float x, int u) { return u < left ? x : kMasked; });
+        else tile([](float x, int) { return x; });
+      });
+      // bit 2 of a span's number is the lane's half
+      TopVals<KMAX + 2> top;
+      top.v[KMAX + 1] = cut(kNone);
+#pragma unroll
+      for (int e = 0; e <= KMAX; ++e) top.v[e] = own.v[e] = __int_as_float(__float_as_int(own.v[e]) | (hf << 2));
+#pragma unroll
+      for (int e = 0; e <= KMAX; ++e) own.v[e] = of_other_half(own.v[e]);
+      const float own_last = top.v[KMAX], other_last = own.v[KMAX];
+#pragma unroll
+      for (int e = 0; e <= KMAX; ++e) top.push(own.v[e]);
+      float kth = INFINITY, next = kNone, third = kNone;
+#pragma unroll
+      for (int e = 0; e < KMAX; ++e)
+        if (e == kq - 1) {
+          kth = top.v[e];
+          next = top.v[e + 1];
+          third = top.v[e + 2];
+        }
+      const float at = cut(kth);
+      const bool close = kq > 0 && next > 0.5f * kMasked && cut(next) == at;
+      const bool lost = close && (cut(third) == at || cut(own_last) == at || cut(other_last) == at);
+      const bool other_way = lost || largest >= 0x7f800000 || lowest >= 0xff800000u || (kq > 0 && !(kth > 0.5f * kMasked));
+      if (!__syncthreads_or(other_way)) {
+        if (__builtin_amdgcn_ballot_w64(close) != 0ull) {
+          // the entries that agree with the k'-th one, entry by entry: the column's own key as row qc of a product
+          // with all columns, of which the diagonal is taken
+          float worst = INFINITY;
+          int worst_j = -1, worst_e = KMAX;
+          for (int e = 0; e <= KMAX; ++e) {
+            float mine = top.v[0];
+#pragma unroll
+            for (int x = 1; x <= KMAX; ++x) mine = x == e ? top.v[x] : mine;
+            const bool in = close && e <= kq && cut(mine) == at;
+            if (__builtin_amdgcn_ballot_w64(in) == 0ull) continue;
+            const int j = in ? __float_as_int(mine) & number : 0;
+            const bf16_t* const kp = key(j) + hf * 8;
+            f32x16 s;
+#pragma unroll
+            for (int x = 0; x < 16; ++x) s[x] = 0.f;
+#pragma unroll
+            for (int kk = 0; kk < 8; ++kk)
+              s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8*>(kp + kk * 16), qf[kk], s, 0, 0, 0);
+            float x = -INFINITY;  // row qc of column qc lies in the half (qc / 4) % 2
+#pragma unroll
+            for (int y = 0; y < 16; ++y) x = (y == 4 * (qc >> 3) + (qc & 3) && hf == ((qc >> 2) & 1)) ? s[y] : x;
+            x = fmaxf(x, of_other_half(x));
+            if (in && (x < worst || (x == worst && j > worst_j))) {
+              worst = x;
+              worst_j = j;
+              worst_e = e;
+            }
+          }
+#pragma unroll
+          for (int e = 0; e < KMAX; ++e) top.v[e] = close && e == worst_e ? next : top.v[e];
+        }
+        int j[KMAX];
+#pragma unroll
+        for (int e = 0; e < KMAX; ++e) j[e] = e < kq ? __float_as_int(top.v[e]) & number : kEmpty;
+        sort_ascending(j);
+        int32_t* const oi = idx + ((int64_t)h * Lq + r) * topk;
+        // the column's lanes take four entries each in turn (picked by masks: a select between two array elements
+        // becomes one of their addresses, and the array goes to memory)
+        const int upper = -hf;
+#pragma unroll
+        for (int g = 0; g < KMAX / 4; g += 2) {
+          int w4[4];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const int up = 4 * g + 4 + e < KMAX ? 4 * g + 4 + e : 4 * g + e;
+            w4[e] = (j[4 * g + e] & ~upper) | (j[up] & upper);
+            w4[e] = w4[e] == kEmpty ? -1 : w4[e];
+          }
+          const int4 w = make_int4(w4[0], w4[1], w4[2], w4[3]);
+          const int e0 = 4 * (g + hf);
+          if (r < Lq && e0 < topk && g + hf < KMAX / 4) {
+            if ((topk & 3) == 0) *reinterpret_cast<int4*>(oi + e0) = w;
+            else {
+              oi[e0] = w.x;
+              if (e0 + 1 < topk) oi[e0 + 1] = w.y;
+              if (e0 + 2 < topk) oi[e0 + 2] = w.z;
+              if (e0 + 3 < topk) oi[e0 + 3] = w.w;
+            }
+          }
+        }
+        return;
+      }
+    }
+  }
+  if (tid < TMQ) s_cnt[tid] = 0;  // (read and added to after the first walk's barriers)
 
   // ---- pass 1: the column's top-k values
   TopVals<KMAX> top;
@@ -182,17 +375,10 @@ __global__ __launch_bounds__(256, (KMAX <= 4 || (KMAX == 8 && !WS)) ? 4 : 1) voi
   {
     float pv[KMAX];
 #pragma unroll
-    for (int e = 0; e < KMAX; ++e) {
-      // the two results are {own, partner} in an order that depends on the lane half: take
-      // the one that is not this lane's own (if both are equal either will do)
-      const int own = __float_as_int(top.v[e]);
-      auto a = __builtin_amdgcn_permlane32_swap(own, own, false, false);
-      pv[e] = __int_as_float(a[0] == own ? a[1] : a[0]);
-    }
+    for (int e = 0; e < KMAX; ++e) pv[e] = of_other_half(top.v[e]);
 #pragma unroll
     for (int e = 0; e < KMAX; ++e) top.push(pv[e]);
   }
-  const int kq = topk < c_q ? topk : c_q;  // spans to select for this column
   float thr = INFINITY;                    // kq == 0: nothing passes
   int n_gt = 0;
 #pragma unroll
@@ -257,27 +443,17 @@ void launch_as(const Problem& pb, int grid, const void* Qs, const void* K, const
                      scores, pb.Lq, pb.q_pos0, pb.G, pb.S, pb.topk, pb.n, pb.qsh, pb.qst, pb.kvsh, pb.kvst);
 }
 
-// Through registers -> direct, us, 32 heads:
-//   top-4: 65536 rows x 256 spans 315 -> 272, with scores 376 -> 288;  64 rows x 4096 spans 185 -> 169;
-//   top-8: 65536 x 256 339 -> 327, 8000 x 125 40.5 -> 39.0, 2000 x 31 11.3 -> 10.8, 16384 x 4096 1377 -> 1355;
-//     but with workgroups for no more than four per compute unit and more than one stage of keys
-//     4000 x 62 18.8 -> 19.3, 64 x 4096 194 -> 199, 4000 x 4096 385 -> 397;
-//     with scores 65536 x 256 419 -> 429, 64 x 4096 199 -> 212;
-//   top-16: 65536 x 256 555 -> 561, with scores 765 -> 773;  top-32: 1328 -> 1340, with scores 2410 -> 2425.
+// Through registers -> direct, us, 32 heads.  One walk: 65536 rows x 256 spans top-4 160.5 -> 163.8, top-8 193.6 ->
+// 195.7, top-16 343 -> 297; 8000 x 125, top-12, 38.5 -> 35.4; top-32 621 -> 614 (no second instantiation for that);
+// 4000 x 62, top-8, 11.6 -> 12.3.  Two walks with scores: top-4 65536 x 256 376 -> 288, 20000 x 156, top-2, 68.9 -> 66.5,
+// 64 rows x 4096 spans 185 -> 169; top-8 419 -> 429, top-16 765 -> 773, top-32 2410 -> 2425.
 template <int KMAX>
 sl_status launch(const Problem& pb, const void* Qs, const void* K, const void* Ks, int32_t* idx,
                  float* scores, hipStream_t st) {
   const int grid = pb.Hq * (int)((pb.Lq + TMQ - 1) / TMQ);
   if (pb.prof_start) (void)hipEventRecord(pb.prof_start, st);
-  if constexpr (KMAX <= 4) {
-    if (scores) launch_as<KMAX, true, true>(pb, grid, Qs, K, Ks, idx, scores, st);
-    else launch_as<KMAX, false, true>(pb, grid, Qs, K, Ks, idx, scores, st);
-  } else {
-    if (scores) launch_as<KMAX, true, false>(pb, grid, Qs, K, Ks, idx, scores, st);
-    else if (KMAX == 8 && (grid > 4 * 256 || (pb.n > 1 && pb.n <= Stages<true>::kKeys)))
-      launch_as<8, false, true>(pb, grid, Qs, K, Ks, idx, scores, st);
-    else launch_as<KMAX, false, false>(pb, grid, Qs, K, Ks, idx, scores, st);
-  }
+  if (scores) launch_as<KMAX, true, KMAX <= 4>(pb, grid, Qs, K, Ks, idx, scores, st);
+  else launch_as<KMAX, false, KMAX == 16>(pb, grid, Qs, K, Ks, idx, scores, st);
   if (pb.prof_stop) (void)hipEventRecord(pb.prof_stop, st);
   return hipGetLastError() == hipSuccess ? SL_OK : SL_ERR_LAUNCH;
 }

@@ -476,3 +476,58 @@ def test_prefill_search_stages_and_list_lengths(n, k, scores):
         for h, row in rows:
             for j, x in zip(ix[h, row], sc[h, row]):
                 assert (j < 0 and x == -np.inf) or abs(x - q[h, row] @ kn[h // 2, j]) <= 1e-3
+
+
+@pytest.mark.parametrize("n,k", [(31, 5), (32, 8), (33, 1), (64, 16), (257, 8), (1025, 4), (4096, 8), (4097, 8), (300, 32)])
+@pytest.mark.parametrize("kind", ["levels", "pairs", "equal", "negative", "infinite", "nan"])
+def test_prefill_search_scores_that_agree_in_their_leading_bits(n, k, kind):
+    """Scores that differ only in the bits whose place the span's number takes, in twos and in longer runs around the
+    k-th; all alike; out of range.  Whole numbers below 2^24: products and sums are exact, the oracle decides, to the
+    index.  What is not finite has no oracle: the form that returns scores carries none of the numbers."""
+    S, Lq, Hq, Hkv, D = 2, 200, 4, 2, 128
+    L = S * n + S - 1
+    Lq = min(Lq, L)
+    g = torch.Generator().manual_seed(n * 100 + k)
+    K = torch.zeros((Hkv, L, D))
+    Q = torch.zeros((Hq, Lq, D))
+    Q[:, :, 0], Q[:, :, 1] = 4096.0, 1.0
+    Q[:, :, 2] = torch.randint(-2, 3, (Hq, Lq), generator=g).float()
+    j = torch.randperm(n, generator=g).float()
+    if kind == "levels":        # a few leading parts, all of them with many different low parts
+        K[:, 1::2, 0], K[:, 1::2, 1] = (j % 7) + 64, torch.floor(j / 7) % 100
+        K[:, 1::2, 2] = (j % 3) - 1
+    elif kind == "pairs":       # every leading part twice, the low part decides (or nothing does)
+        lead = torch.floor(j / 2)
+        K[:, 1::2, 0], K[:, 1::2, 3] = lead % 128 + 1, torch.floor(lead / 128)
+        Q[:, :, 3] = 128 * 4096.0
+        K[:, 1::2, 1] = torch.where(lead % 3 == 0, torch.zeros(n), j % 2)
+    elif kind == "equal":
+        K[:, 1::2, 1] = 3.0
+        Q[:, :, 2] = 0.0
+    elif kind == "negative":
+        K[:, 1::2, 0], K[:, 1::2, 1] = -((j % 5) + 64), torch.floor(j / 5) % 100
+    else:
+        K[:, 1::2, 0] = torch.randn((Hkv, n), generator=g)
+        K[:, 1::2, 1] = torch.randn((Hkv, n), generator=g)
+        some = torch.rand((Hkv, n), generator=g) < 0.1
+        if kind == "infinite":
+            K[:, 1::2, 0] = torch.where(some, torch.sign(K[:, 1::2, 0]) * 3e38, K[:, 1::2, 0])
+        else:
+            K[:, 1::2, 5] = torch.where(some, torch.full((Hkv, n), float("nan")), torch.zeros(Hkv, n))
+    Q, K = Q.to(torch.bfloat16).to(DEV), K.to(torch.bfloat16).to(DEV)
+    q0 = L - Lq
+    idx = B.sl_span_search_prefill(Q, K, None, S, k, q_pos0=q0)
+    two, _ = B.sl_span_search_prefill(Q, K, None, S, k, q_pos0=q0, want_scores=True)
+    torch.cuda.synchronize()
+    if kind != "nan":
+        assert torch.equal(idx, two)
+    if kind in ("infinite", "nan"):
+        ok = ((idx >= -1) & (idx < n)).all()
+        assert bool(ok)
+        return
+    Qn, Kn, got = f64(Q), f64(B.sl_span_keys(K, S)), idx.cpu().numpy()
+    for h in range(Hq):
+        for r in sorted({0, 1, Lq // 2, Lq - 2, Lq - 1, *range(0, Lq, 17)}):
+            s = orc.search_scores_row(Qn[h, r], Kn[h // 2], (q0 + r) // S)
+            want = orc.select_topk(s, k)
+            assert got[h, r].tolist() == want + [-1] * (k - len(want)), (h, r)
