@@ -621,10 +621,21 @@ struct AnchorList {
 // and of equal length, so that every XCD has the same work: with all of them 512 rows long, 512 rows behind
 // 48645 tokens ran on one XCD, 78 -> 25 us):
 // at the same stride index their keys are neighbours and the next index finds them in that L2.  Rows with
-// the most candidates come first.  49157 rows, 32:4 heads, window 1088, top-2: 956 us with vector
-// instructions (two-element dot products and a lane-group sum per score), 675 us now, of which the second scoring
-// below takes 150 and keeping to the other kernels' selection (the margin, the rows left) 25.
+// the most candidates come first.
+//
+// 49157 rows, 32:4 heads, window 1088, top-2: 956 us with vector instructions (two-element dot products and a lane-group
+// sum per score); 660 with 16 rows of a product and a compare-and-select list with indices, an address for every load
+// and an AnchorList merge, vector units busy 80 % of the time (2870 instructions per wavefront); 542 with the numbers in
+// the scores' bits and scalar bases (1320 instructions, 44 %).  20000 rows, top-4: 267 (vector) -> 146.  What bounds the
+// long prompt now are the key rows that miss the L2, half of 5.8 GB: a kernel that only reads rows at random gets
+// 11.5 TB/s out of 12.6 MB, a kv head's keys here, and 30 out of 3 MB; this one gets 12.3 and 11.6.  Staging through
+// registers instead of direct loads, loads past the L1, and chunks of 1024 and 2048 rows change nothing.
 constexpr int kAnchorRowsPerBlock = 8, kAnchorMaxChunk = 64;
+
+__device__ __forceinline__ int64_t uniform64(int64_t v) {
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+  return (int64_t)(((uint64_t)hi << 32) | lo);
+}
 
 template <int D, int KMAX>
 __global__ __launch_bounds__(256, D == 64 ? (KMAX <= 2 ? 8 : 6) : 4) void prefill_anchor_search_mfma_kernel(
@@ -646,7 +657,16 @@ __global__ __launch_bounds__(256, D == 64 ? (KMAX <= 2 ? 8 : 6) : 4) void prefil
   const int64_t r1 = r0 + 1 < Lq ? r0 + 1 : r0;
   const int i0 = (int)(q_pos0 + r0), i1 = (int)(q_pos0 + r1);  // positions fit 32 bits
   auto candidates = [&](int i) {
-    const int s_max = (int)iroot_floor((int64_t)i + 1, root) - 1;  // (s+1)^root <= i + 1
+    const uint32_t x = (uint32_t)i + 1;
+    int s_max;  // (s+1)^root <= i + 1
+    if (root == 2) {  // (a rounded root is off by one at most; its square fits 32 bits)
+      uint32_t m = (uint32_t)__builtin_amdgcn_sqrtf((float)x);
+      m -= m * m > x ? 1 : 0;
+      m += (m + 1) * (m + 1) <= x ? 1 : 0;
+      s_max = (int)m - 1;
+    } else {
+      s_max = (int)iroot_floor(x, root) - 1;
+    }
     return __builtin_amdgcn_readfirstlane(s_max >= s0 ? s_max - s0 + 1 : 0);
   };
   const int c0 = candidates(i0), c1 = candidates(i1);
@@ -666,26 +686,67 @@ __global__ __launch_bounds__(256, D == 64 ? (KMAX <= 2 ? 8 : 6) : 4) void prefil
   bf16_t* const mine = s_keys[wave];
   const bf16_t* const Kh = K + kv * kvsh;
   auto swizzle = [](int m) { return D == 128 ? m & 15 : (m >> 1) & 7; };
-  // candidate tokens are top - (s+1)^root; a row without candidates takes any valid row, its own
-  const int some0 = c0 > 0 ? -1 : 0, some1 = c1 > 0 ? -1 : 0, top0 = i0 - some0, top1 = i1 - some1;
-  auto stage = [&](int jb) {
+  // Candidate m of a batch is token top - (E + m)^root, E = s0 + 1 + jb.  Where both rows have all 16, the lane's
+  // offsets count from the batch's last one, the same for both rows, whose bases are scalars: a batch takes four
+  // additions (root = 2) where an address for every load took 70 instructions.  The last batch counts from token 0.
+  const int top0 = i0 + 1, top1 = i1 + 1;
+  constexpr int NLD = 16 / RPI;  // loads per row and batch
+  const uint32_t step = (uint32_t)(kvst * sizeof(bf16_t));
+  auto power = [&](int e) { return (uint32_t)e * (uint32_t)e * (root == 2 ? 1u : (uint32_t)e); };
+  uint32_t ahead[NLD], grow[NLD];
 #pragma unroll
-    for (int u = 0; u < 32 / RPI; ++u) {
-      const bool b = u * RPI >= 16;
-      const int m = (u * RPI & 15) + lane / PPR, cnt = b ? c1 : c0;
-      const int e = s0 + 1 + (jb + m < cnt ? jb + m : cnt - 1);
-      const int back = e * (root == 2 ? e : e * e);
-      const int t = b ? top1 - (back & some1) : top0 - (back & some0);
-      const bf16_t* src = Kh + (int64_t)t * kvst + ((lane % PPR) ^ swizzle(m)) * 8;
-      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
-                                       (__attribute__((address_space(3))) void*)(mine + u * 512), 16, 0, 0);
+  for (int u = 0; u < NLD; ++u) {
+    const int m = u * RPI + lane / PPR, E = s0 + 1;
+    ahead[u] = (power(E + 15) - power(E + m)) * step + ((lane % PPR) ^ swizzle(m)) * 16;
+    grow[u] = (uint32_t)(15 - m) * 32 * step;  // (E + 31)^2 - (E + 16 + m)^2 - ((E + 15)^2 - (E + m)^2)
+  }
+  auto load = [&](const char* base, uint32_t off, int u) {
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(base + off),
+                                     (__attribute__((address_space(3))) void*)(mine + u * 512), 16, 0, 0);
+  };
+  auto stage = [&](int jb) {
+    const int E = s0 + 1 + jb;
+    if (jb + 16 <= c0) {
+      const char* const last0 = reinterpret_cast<const char*>(Kh + uniform64((int64_t)(top0 - (int)power(E + 15)) * kvst));
+      const char* const last1 = last0 + (top1 - top0) * (int64_t)step;
+#pragma unroll
+      for (int u = 0; u < NLD; ++u) {
+        load(last0, ahead[u], u);
+        load(last1, ahead[u], NLD + u);
+      }
+#pragma unroll
+      for (int u = 0; u < NLD; ++u) {
+        if (root == 2) ahead[u] += grow[u];
+        else ahead[u] += (power(E + 31) - power(E + 16 + u * RPI + lane / PPR) - power(E + 15) + power(E + u * RPI + lane / PPR)) * step;
+      }
+    } else {  // past a row's last candidate: that one again (a row without candidates: any key)
+#pragma unroll
+      for (int u = 0; u < 2 * NLD; ++u) {
+        const int m = (u % NLD) * RPI + lane / PPR, most = s0 + (u < NLD ? c0 : c1);
+        const int t = (u < NLD ? top0 : top1) - (int)power(E + m < most ? E + m : most);
+        load(reinterpret_cast<const char*>(Kh), (uint32_t)(t > 0 ? t : 0) * step + ((lane % PPR) ^ swizzle(m)) * 16, u);
+      }
     }
   };
+  // The best KL scores of the candidates a lane has seen, with the candidate's number in their lowest bits (its bits 2
+  // and 3 are the lane's quarter): one median instruction per entry and score, no index carried beside the score.  A
+  // score so changed is less than a unit of the bits left away from itself, which the margin takes into account.
+  // Scores that are not finite would unsettle the list; they come with lengths that are not, and such rows are left.
   constexpr int KL = KMAX + 2;  // two spares: see the margin
-  AnchorList<KL> top;
-  top.clear();
-  float (&v)[KL] = top.v;
-  int (&id)[KL] = top.id;
+  constexpr float kMasked = -3e38f, kNone = -3.3e38f;
+  const int bits = c1 > 16 ? 32 - __builtin_clz(c1 - 1) : 4, number = (1 << bits) - 1;
+  int keep = ~number;
+  asm volatile("" : "+v"(keep));
+  float v[KL];
+#pragma unroll
+  for (int e = 0; e < KL; ++e) v[e] = __int_as_float(__float_as_int(kNone) & keep);
+  float infinity = INFINITY;
+  asm volatile("" : "+v"(infinity));
+  auto push = [&](float x) {
+#pragma unroll
+    for (int e = KL - 1; e >= 1; --e) v[e] = __builtin_amdgcn_fmed3f(x, v[e - 1], v[e]);
+    v[0] = __builtin_amdgcn_fmed3f(x, v[0], infinity);  // (a maximum that makes no numbers canonical first)
+  };
   // squared length of the longest key of each row, a quarter of the dimensions per lane: see the margin
   auto square = [](const bf16x8 (&x)[KS]) {
     float sum = 0.f;
@@ -720,37 +781,69 @@ __global__ __launch_bounds__(256, D == 64 ? (KMAX <= 2 ? 8 : 6) : 4) void prefil
       sa = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka[kk], qf[kk], sa, 0, 0, 0);
       sb = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kb[kk], qf[kk], sb, 0, 0, 0);
     }
+    auto take = [&](auto score) {
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int j = jb + 4 * q4 + r;
-      const float x = second ? sb[r] : sa[r];
-      top.insert(j < c ? x : -INFINITY, j, false);
-    }
+      for (int r = 0; r < 4; ++r) {
+        int j = jb + r;
+        const float x = score(second ? sb[r] : sa[r], r);
+        asm volatile("" : "+s"(j));  // one v_and_or
+        push(__int_as_float((__float_as_int(x) & keep) | j));
+      }
+    };
+    if (jb + 16 <= c0) take([](float x, int) { return x; });
+    else take([&](float x, int r) { return jb + 4 * q4 + r < c ? x : kMasked; });
   }
 #pragma unroll
-  for (int off = 16; off <= 32; off <<= 1) top.merge(off);
+  for (int e = 0; e < KL; ++e) v[e] = __int_as_float(__float_as_int(v[e]) | (q4 << 2));
+  // the four lanes of a column
+#pragma unroll
+  for (int off = 16; off <= 32; off <<= 1) {
+    float other[KL];
+#pragma unroll
+    for (int e = 0; e < KL; ++e) {
+      const int own = __float_as_int(v[e]);
+      auto a = off == 16 ? __builtin_amdgcn_permlane16_swap(own, own, false, false)
+                         : __builtin_amdgcn_permlane32_swap(own, own, false, false);
+      other[e] = __int_as_float(a[0] == own ? a[1] : a[0]);
+    }
+#pragma unroll
+    for (int e = 0; e < KL; ++e) push(other[e]);
+  }
+  int id[KL];
+#pragma unroll
+  for (int e = 0; e < KL; ++e) {
+    const int j = __float_as_int(v[e]) & number;
+    id[e] = v[e] > 0.5f * kMasked && j < c ? j : -1;
+  }
   // The matrix unit adds in another order than the other search kernels (Piece::dot, group_sum).  Both sums have at
   // most D + 16 roundings, each of at most 2^-23 of what is added up, which is at most |q||k|: candidates whose
   // scores lie further apart than twice that are in the same order in both.
-#pragma unroll
-  for (int off = 1; off <= 8; off <<= 1) {  // the longest of the keys that the 16 lanes have staged ...
-    len_a = fmaxf(len_a, __shfl_xor(len_a, off, 64));
-    len_b = fmaxf(len_b, __shfl_xor(len_b, off, 64));
-  }
+  // the longest of the keys that the 16 lanes have staged ...
+  auto row_max = [](float x) {
+    x = fmaxf(x, dpp_f32<0xB1>(x));   // lane ^ 1
+    x = fmaxf(x, dpp_f32<0x4E>(x));   // lane ^ 2
+    x = fmaxf(x, dpp_f32<0x141>(x));  // mirrored within 8 lanes
+    return fmaxf(x, dpp_f32<0x140>(x));
+  };
+  len_a = row_max(len_a);
+  len_b = row_max(len_b);
   float len_k = second ? len_b : len_a, len_q = square(qf);
 #pragma unroll
   for (int off = 16; off <= 32; off <<= 1) {  // ... over all dimensions
     len_k += __shfl_xor(len_k, off, 64);
     len_q += __shfl_xor(len_q, off, 64);
   }
-  const float margin = 2.f * (D + 16) * 0x1p-23f * sqrtf(len_q) * sqrtf(len_k);
+  const float product = __builtin_amdgcn_sqrtf(len_q) * __builtin_amdgcn_sqrtf(len_k) * 1.0001f;  // above every |score|
+  const float margin = 2.f * (D + 16) * 0x1p-23f * product;
+  const float unit = 0x1p-22f * (float)(1 << bits);  // twice a unit of the bits left, relative
   const bool in_range = len_q > 1e-30f && len_k > 1e-30f;  // of the squares
-  bool close = false, lost = c > 0 && !(margin < INFINITY);
+  auto apart = [&](float x, float y) { return x - y > margin + unit * fmaxf(fabsf(x), fabsf(y)) && in_range; };
+  bool close = false, lost = c > 0 && !(product < 1e38f);
 #pragma unroll
   for (int e = 1; e < KL - 1; ++e)
     if (e == topk) {
-      close = id[e] >= 0 && !(v[e - 1] - v[e] > margin && in_range);
-      lost = lost || (id[KL - 1] >= 0 && !(v[e - 1] - v[KL - 1] > margin && in_range));
+      close = id[e] >= 0 && !apart(v[e - 1], v[e]);
+      lost = lost || (id[KL - 1] >= 0 && !apart(v[e - 1], v[KL - 1]));
     }
   // A row with a head whose k-th score and the last of the list are that close (equal keys, or lengths that leave
   // the range of their squares, or are not finite) is searched again below: one in 10^4 for random scores.
@@ -763,39 +856,57 @@ __global__ __launch_bounds__(256, D == 64 ? (KMAX <= 2 ? 8 : 6) : 4) void prefil
     using RL = RowLayout<bf16_t, D>;
     constexpr int LPR = RL::LPR, NGRP = 64 / LPR, ITS = 16 / NGRP, N = decltype(count)::value;
     const int g = lane / LPR, lr = lane % LPR;
-    uint4 qraw[ITS], kr[ITS][N];
+    // the query rows, from operand order to row order through the stage
 #pragma unroll
-    for (int it = 0; it < ITS; ++it) {
-      const int col = it * NGRP + g;
-      const int hc = h0 + (col & 7) < G ? h0 + (col & 7) : G - 1;
-      qraw[it] = load16(Qs + (int64_t)(kv * G + hc) * qsh + (col >= HB ? r1 : r0) * qst + lr * RL::EPL);
+    for (int kk = 0; kk < KS; ++kk) *reinterpret_cast<bf16x8*>(&mine[n * D + ((4 * kk + q4) ^ swizzle(n)) * 8]) = qf[kk];
+    __builtin_amdgcn_wave_barrier();
+    constexpr int PER = N > KMAX ? 1 : N > 2 ? 2 : ITS;  // columns of a group at a time
+#pragma unroll 1
+    for (int it0 = 0; it0 < ITS; it0 += PER) {
+      uint4 qraw[PER], kr[PER][N];
 #pragma unroll
-      for (int e = 0; e < N; ++e) {
-        const int j = __shfl(id[e], col, 64), x = s0 + j + 1;
-        const int t = (col >= HB ? i1 : i0) + (j >= 0 ? 1 - x * (root == 2 ? x : x * x) : 0);
-        kr[it][e] = load16(Kh + (int64_t)t * kvst + lr * RL::EPL);
+      for (int i = 0; i < PER; ++i) {
+        const int col = (it0 + i) * NGRP + g;
+#pragma unroll
+        for (int e = 0; e < N; ++e) {
+          const int j = __shfl(id[e], col, 64);
+          const int t = j >= 0 ? (col >= HB ? top1 : top0) - (int)power(s0 + 1 + j) : 0;
+          kr[i][e] = load16(reinterpret_cast<const char*>(Kh + lr * RL::EPL) + (uint64_t)(uint32_t)t * step);
+        }
+        qraw[i] = load16(&mine[col * D + (lr ^ swizzle(col)) * 8]);
       }
+#pragma unroll
+      for (int i = 0; i < PER; ++i)
+#pragma unroll
+        for (int e = 0; e < N; ++e) {
+          const float x = __shfl(group_sum<LPR>(Piece<bf16_t>::dot(kr[i][e], qraw[i], 0.f)), (n % NGRP) * LPR, 64);
+          if (n / NGRP == it0 + i && id[e] >= 0) v[e] = x;
+        }
     }
-#pragma unroll
-    for (int it = 0; it < ITS; ++it)
-#pragma unroll
-      for (int e = 0; e < N; ++e) {
-        const float x = __shfl(group_sum<LPR>(Piece<bf16_t>::dot(kr[it][e], qraw[it], 0.f)), (n % NGRP) * LPR, 64);
-        if (n / NGRP == it && id[e] >= 0) v[e] = x;
-      }
   };
   if (__builtin_amdgcn_ballot_w64(close && !left) != 0ull) {
     score_again(std::integral_constant<int, KL>{});
-    const AnchorList<KL> was = top;
+    AnchorList<KL> top;
     top.clear();
 #pragma unroll
-    for (int e = 0; e < KL; ++e) top.insert(was.id[e] >= 0 ? was.v[e] : -INFINITY, was.id[e], was.id[e] >= 0);
+    for (int e = 0; e < KL; ++e) top.insert(id[e] >= 0 ? v[e] : -INFINITY, id[e], id[e] >= 0);
+#pragma unroll
+    for (int e = 0; e < KL; ++e) {
+      v[e] = top.v[e];
+      id[e] = top.id[e];
+    }
   } else if (scores && __builtin_amdgcn_ballot_w64(!left) != 0ull) {
     score_again(std::integral_constant<int, KMAX>{});
   }
   const int64_t r = second ? r0 + 1 : r0;
   if (!left && q4 == 0 && r < Lq && h0 + (n & 7) < G) {
     const int64_t row = (int64_t)(kv * G + head) * Lq + r;
+    AnchorList<KMAX> top;
+#pragma unroll
+    for (int e = 0; e < KMAX; ++e) {
+      top.v[e] = v[e];
+      top.id[e] = id[e];
+    }
     top.store(topk, q_pos0 + r, s0, root, anchors + row * topk, scores ? scores + row * topk : nullptr);
   }
   // The rows left: all their candidates with the vector kernel's arithmetic, the wavefront's row groups side by side.
@@ -984,19 +1095,22 @@ sl_status launch_anchor_search_rows(const Problem& pb, const void* Qs, const voi
     bool done = false;
     if constexpr (std::is_same<T, bf16_t>::value) {
       // The matrix cores where the rows have enough candidates (the middle row's number) to make up for what a
-      // wavefront does once: set up, merge its lanes' lists, score the winners again.  Vector -> matrix cores, us,
-      // by rows x groups of up to 8 heads and candidates:
-      //   up to 2 anchors: 256 x 45 13.4 -> 13.3, 2048 x 45 14.4 -> 15.2, x 80 22.5 -> 20.0, 4096 x 80 23.7 -> 23.0,
-      //     8192 x 45 26.3 -> 24.7, 16384 x 45 50 -> 41, 32768 x 80 129 -> 83; whole prompt of 49157 955 -> 675;
-      //     D = 64: 2048 x 80 21 -> 16, 8192 x 60 20 -> 23, x 110 29 -> 25, 32768 x 80 76 -> 60;
-      //   3 and 4: 2048 x 110 30 -> 28, 4096 x 110 32 -> 36, 8192 x 80 41.8 -> 42.3, x 110 54 -> 48, 16384 x 45 56 -> 63,
-      //     x 80 80 -> 71, 32768 x 80 144 -> 123; whole prompt of 49157 1066 -> 855;  D = 64: 16384 x 110 54 -> 57, whole
-      //     prompt of 49157 555 -> 530;
-      //   5 to 8: whole prompt of 20000 320 -> 746: every lane keeps a list of its own; 2048 x 189 57 -> 202.
-      const int64_t mid = iroot_floor(pb.q_pos0 + pb.Lq / 2 + 1, root) - s0, work = pb.Lq * groups;
-      const int64_t least = pb.topk <= 2 ? (D == 64 ? 80 : work >= 8192 ? 40 : 64)
-                                         : (D == 64 ? 120 : work >= 16384 ? 72 : work >= 8192 ? 90 : 150);
-      if (pb.topk <= 4 && mid >= least) {
+      // wavefront does once: set up, merge its lanes' lists, score the winners again.  Vector -> matrix cores, us, 32:4
+      // heads, by rows and candidates of the middle row:
+      //   up to 2 anchors: 256 x 25 9.6 -> 7.2, 1024 x 25 11.3 -> 10.4, 2048 x 25 19.7 -> 14.4, 4096 x 45 40 -> 26, whole
+      //     prompts of 3000 (5 candidates) 12.7 -> 16.7, 8000 (30) 60.8 -> 39.6; D = 64: 256 x 25 9.5 -> 6.0, 1024 x 25
+      //     9.5 -> 7.1, whole prompts of 3000 10.5 -> 11.0, 8000 44 -> 25;
+      //   3 and 4: 256 x 25 10.5 -> 9.5, 1024 x 25 12.3 -> 13.0, x 45 17.2 -> 16.4, 2048 x 25 21.6 -> 19.0, whole prompts of
+      //     3000 14.2 -> 21.7, 8000 67.9 -> 49.9; D = 64: 1024 x 25 10.6 -> 11.5, x 45 16.3 -> 11.8, 8000 49 -> 33;
+      //   5 to 8: no instantiation (with lists that carried their indices a whole prompt of 20000 took 746, here 320).
+      const int64_t mid = iroot_floor(pb.q_pos0 + pb.Lq / 2 + 1, root) - s0;
+      const int64_t least = pb.topk <= 2 ? 24 : 30;
+      // The kernel's 32-bit offsets: 16 candidates of one row, and the last one's from token 0, lie less than 4 GiB apart.
+      auto offsets_fit = [&] {
+        const int64_t e = c_max + s0 + 16, first = e > 16 ? e - 16 : 0;
+        return ipow_root(e, root) - ipow_root(first, root) < ((int64_t)1 << 32) / (pb.kvst * (int64_t)sizeof(bf16_t));
+      };
+      if (pb.topk <= 4 && mid >= least && offsets_fit()) {
         const int blocks = (int)((pb.Lq + kAnchorRowsPerBlock - 1) / kAnchorRowsPerBlock);
         // as few rounds of one chunk for each XCD as the longest chunk allows, all chunks alike
         const int rounds = (blocks + 8 * kAnchorMaxChunk - 1) / (8 * kAnchorMaxChunk);

@@ -372,6 +372,7 @@ def test_decode_entries_sharing_chunks_go_in_pairs(form, dtype, Hq, Hkv, S, A, k
     (8, 2, 128, 20, 2, 1088, 2, None, 0),        # no row has a candidate
     # the same where the rows have candidates enough for the matrix cores
     (8, 1, 128, 8500, 2, 0, 2, None, 0),
+    (8, 2, 128, 2603, 2, 0, 2, None, 0),         # every count from 0 to 50, pairs of rows on both sides of a batch's end
     (8, 2, 128, 14001, 4, 0, 2, None, 0),
     (12, 1, 64, 30001, 4, 24, 2, 1501, 28500),
     (4, 4, 128, 40000, 3, 255, 2, 9, 39991),
@@ -419,13 +420,13 @@ def test_anchor_search_ties_go_to_the_nearer_anchor():
             assert an[h, r].tolist() == toks[pick].tolist()
 
 
-@pytest.mark.parametrize("kind", ["random", "cancelling", "near-equal", "zero", "infinite"])
+@pytest.mark.parametrize("kind", ["random", "cancelling", "near-equal", "zero", "infinite", "huge"])
 @pytest.mark.parametrize("Hq,Hkv,D,k", [(8, 1, 128, 2), (6, 2, 128, 4), (12, 1, 64, 3), (8, 2, 128, 6)])
 def test_anchor_search_selects_as_the_decode_search_does(Hq, Hkv, D, k, kind):
     """Whatever the scores: the selection and the returned scores of every row are the decode search's to the
     bit, and do not depend on how a prompt is cut.  Cancelling: two large channels of opposite sign, so that the
     order of the additions decides between scores.  Near-equal: three keys, each varying in one small element.  Zero: queries and stretches of keys that are all zero.  Infinite: a key that is not finite
-    among finite ones."""
+    among finite ones.  Huge: scores around 1e38, where no number may take the place of their low bits."""
     L, q0, w = 27000, 25000, 24
     Q, K, _ = make(1300 + D + k, Hq, Hkv, L, D, torch.bfloat16, Lq=L - q0, scale=0.3)
     if kind == "cancelling":
@@ -437,6 +438,9 @@ def test_anchor_search_selects_as_the_decode_search_does(Hq, Hkv, D, k, kind):
     elif kind == "zero":
         Q[:, 1::3] = 0
         K[:, 5000:12000] = 0
+    elif kind == "huge":
+        Q.mul_(3e18)
+        K.mul_(3e18)
     elif kind == "infinite":
         K[0, 12000, 7], K[0, 11000, 7] = float("inf"), float("-inf")
     an, sc = B.sl_anchor_search_prefill(Q, K, k, w, q_pos0=q0, want_scores=True)
