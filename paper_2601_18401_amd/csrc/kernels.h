@@ -93,6 +93,12 @@ size_t prefill_attention_fine_ws_bytes(const Problem& pb);
 sl_status prefill_attention_fine(const Problem& pb, const void* Q, const void* K, const void* V,
                                  const int32_t* idx, void* O, float* LSE, void* ws, hipStream_t st);
 
+// a4 .. a6 in fp32 on the matrix cores
+bool prefill_attention_f32_supported(const Problem& pb);
+size_t prefill_attention_f32_ws_bytes(const Problem& pb);
+sl_status prefill_attention_f32(const Problem& pb, const void* Q, const void* K, const void* V, const int32_t* idx,
+                                void* O, float* LSE, void* ws, hipStream_t st);
+
 // a3 .. a6: prefill span-attention.  Where the workspace is optional (no matrix-core form, or the one with
 // fp32 weights), ws may be NULL.
 bool prefill_attention_ws_optional(const Problem& pb);

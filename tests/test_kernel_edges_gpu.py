@@ -535,3 +535,67 @@ def test_prefill_search_scores_that_agree_in_their_leading_bits(n, k, kind):
             s = orc.search_scores_row(Qn[h, r], Kn[h // 2], (q0 + r) // S)
             want = orc.select_topk(s, k)
             assert got[h, r].tolist() == want + [-1] * (k - len(want)), (h, r)
+
+
+F32 = [
+    # Hq Hkv L   D    S    A    k  form     q_pos0 Lq
+    (4, 4, 2500, 64, 64, 64, 4, "joint", 0, 2500),
+    (4, 1, 3000, 64, 55, 55, 4, "gated", 0, 3000),         # windows that start inside a tile of 16 rows
+    (8, 2, 2600, 128, 39, 39, 9, "joint", 600, 1999),      # a list that is no whole number of slots at a time
+    (4, 2, 5000, 64, 81, 81, 8, "joint", 0, 5000),         # a row more than is staged at a time
+    (4, 4, 4000, 128, 65, 65, 3, "gated", 1001, 2999),
+    (8, 8, 3001, 64, 142, 142, 5, "joint", 0, 3001),
+    (8, 1, 4000, 64, 128, 64, 8, "gated", 0, 4000),        # overlapping spans, each its own softmax
+    (16, 1, 2500, 64, 80, 80, 17, "joint", 0, 2500),
+]
+
+
+def span_rows(Q, K, V, idx, sc, S, q0, stride):
+    """(this form, the row-stationary form) of a call, O first."""
+    if sc is None:
+        return (B.sl_span_attention_prefill(Q, K, V, idx, S, q_pos0=q0, span_stride=stride),
+                row_form(Q, K, V, idx, None, S, q0, stride))
+    return ((B.sl_span_attention_combined_prefill(Q, K, V, idx, sc, S, q_pos0=q0, span_stride=stride),),
+            (row_form(Q, K, V, idx, sc, S, q0, stride),))
+
+
+@pytest.mark.parametrize("Hq,Hkv,L,D,S,A,k,form,q_pos0,Lq", F32)
+def test_fp32_spans_on_the_matrix_cores(Hq, Hkv, L, D, S, A, k, form, q_pos0, Lq):
+    """fp32 tiles against the row-stationary kernels, packed and strided.  Both round some hundred sums of fp32 products
+    (2^-24 each, of terms below 5): outputs below 5 agree to 2^-24 * 5 * sqrt(700) * 2 = 1.6e-5, and are not all equal,
+    which they would be if the same kernels had run twice."""
+    stride = 0 if A == S else A
+    Q, K, V = make(2000 + L + S, Hq, Hkv, L, D, torch.float32, Lq=Lq, scale=1.0 if form == "joint" else 0.35)
+    idx, sc = B.sl_span_search_prefill(Q, K, None, A, k, q_pos0=q_pos0, want_scores=True)
+    sc = None if form == "joint" else torch.where(torch.isfinite(sc), sc, 0.0)
+    assert takes_matrix_cores(Q, K, S, k, q_pos0, stride)
+    got, want = span_rows(Q, K, V, idx, sc, S, q_pos0, stride)
+    strided, _ = span_rows(token_major(Q), token_major(K), token_major(V), idx, sc, S, q_pos0, stride)
+    torch.cuda.synchronize()
+    assert all(torch.equal(x, y) for x, y in zip(got, strided))
+    assert float((got[0] - want[0]).abs().max()) <= 1.6e-5
+    assert not torch.equal(got[0], want[0])
+    if form == "joint":
+        assert float((got[1] - want[1]).abs().max()) <= 1e-5
+        check_attention(*got, Q, K, V, idx, S, q_pos0, 0.0, [(h, r) for h in range(Hq) for r in range(0, Lq, 397)], stride=stride or None)
+
+
+@pytest.mark.parametrize("form", ["joint", "gated"])
+@pytest.mark.parametrize("span", [12, 50])     # a span that lies in no row's window; one that does
+@pytest.mark.parametrize("which,bad", [("V", float("nan")), ("V", float("inf")), ("K", float("nan")), ("K", float("inf"))])
+def test_fp32_spans_keep_what_is_not_finite_to_the_rows_that_attend_it(which, bad, span, form):
+    Hq, Hkv, L, D, S, k, q0 = 8, 2, 4200, 64, 61, 8, 1500
+    Q, K, V = make(2100, Hq, Hkv, L, D, torch.float32, Lq=L - q0, scale=1.0 if form == "joint" else 0.35)
+    idx, sc = B.sl_span_search_prefill(Q, K, None, S, k, q_pos0=q0, want_scores=True)
+    assert takes_matrix_cores(Q, K, S, k, q0)
+    t = S * span + 30
+    (K if which == "K" else V)[0, t, 5] = bad
+    got, want = span_rows(Q, K, V, idx, None if form == "joint" else sc, S, q0, 0)
+    torch.cuda.synchronize()
+    finite = torch.isfinite(got[0]).all(dim=2)
+    assert torch.equal(finite, torch.isfinite(want[0]).all(dim=2))
+    pos = q0 + torch.arange(L - q0, device=DEV)
+    attends = (idx == t // S).any(dim=2) | ((pos // S == t // S) & (pos >= t))[None, :]
+    attends[Hq // Hkv:] = False
+    assert not bool((~finite & ~attends).any())
+    assert bool((~finite).any())
