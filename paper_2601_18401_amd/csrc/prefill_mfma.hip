@@ -40,6 +40,13 @@ typedef float f32x8 __attribute__((ext_vector_type(8)));
 
 constexpr int TG = 128;            // rows of one wavefront group (4 wavefronts x 32 columns)
 constexpr int TN = 64;             // kv positions per staged tile
+// ... and of the kernels with fp32 weights.  At D = 64 tiles of 32 leave room (registers, LDS) for a third workgroup per
+// compute unit and end closer to a span's end: 20011 rows in spans of 142 1213 -> 1098 us, 8000 in spans of 90, top-4, 260 ->
+// 221, 8 rows behind 60000 tokens in spans of 245 57.2 -> 58.1.  At D = 128 the registers of a third do not suffice: 2000 ->
+// 2164.  (Nor does it help there to ask for the next tile's first stages, queries and record before a tile's output leaves,
+// over the stages of its last kv tile: 1929 -> 2015.)
+constexpr int fine_tile(int d) { return d == 64 ? 32 : 64; }
+constexpr int fine_blocks(int d) { return d == 64 ? 3 : 2; }  // workgroups per compute unit
 constexpr int HD = 128;            // head dimension of the kernels with bf16 weights
 
 // LDS of the flash kernels (dynamic).  Main loop: stages of the V tile and of the K tile, filled
@@ -65,9 +72,9 @@ constexpr int HD = 128;            // head dimension of the kernels with bf16 we
 //     lies over the V stages, which are dead by then.
 //   fp32-weight kernels: a wavefront's 32 rows go out in fp32, 64 columns at a time, through a slice of the
 //     same size (32 x 64 fp32 = 32 x 128 bf16); at D = 64 the V stages are too small to lie under it.
-template <int NG, int D = HD>
+template <int NG, int D = HD, int TNK = TN>
 struct FlashLds {
-  static constexpr int kStageElems = TN * D;  // D = 128: 8192 bf16 = 16 KB
+  static constexpr int kStageElems = TNK * D;  // D = 128: 8192 bf16 = 16 KB
   static constexpr int kStagesK = 2, kStagesV = NG == 2 ? 3 : 2;
   static constexpr int kV = 0;
   static constexpr int kK = kStagesV * kStageElems * 2;
@@ -540,7 +547,8 @@ __device__ __forceinline__ void flash_tile(const FlashArgs& a, char* lds, const 
   const int srow = w4 * 32 + qc;             // row inside the group's 128-row half tile
   static_assert(NG == 1 || !FINE, "fp32 partials leave with their tile: one group's output region");
   constexpr bool kMasked = LOCAL || CLIP;
-  using Lds = FlashLds<NG, D>;
+  constexpr int TT = FINE ? fine_tile(D) : TN;  // kv positions per tile
+  using Lds = FlashLds<NG, D, TT>;
   constexpr int kStageElems = Lds::kStageElems;
   constexpr int PPR = D / 8, RPB = 64 / PPR;  // 16-byte pieces per staged row, rows per 1 KB block
   constexpr int NDT = D / 32, NKK = D / 16;   // 32-row output tiles, 16-deep steps of the QK product
@@ -564,7 +572,7 @@ __device__ __forceinline__ void flash_tile(const FlashArgs& a, char* lds, const 
     // rows past the end of the sequence (FINE: of the tile's range) lie beyond the buffer: zeros in LDS
     // (masked later)
     const int64_t stop = FINE ? t_end : a.L;
-    const int rows = __builtin_amdgcn_readfirstlane(stop - t0 < TN ? (int)(stop - t0) : TN);
+    const int rows = __builtin_amdgcn_readfirstlane(stop - t0 < TT ? (int)(stop - t0) : TT);
     const int64_t first = uniform64((int64_t)kvh * a.kvsh + t0 * a.kvst);
     const uint32_t bytes = (uint32_t)(((rows - 1) * a.kvst + D) * sizeof(bf16_t));
     const BufferRsrc kr = buffer_of(a.K + first, bytes), vr = buffer_of(a.V + first, bytes);
@@ -594,12 +602,13 @@ __device__ __forceinline__ void flash_tile(const FlashArgs& a, char* lds, const 
 #pragma unroll
     for (int r = 0; r < 16; ++r) o[dt][r] = 0.f;
   float m = -INFINITY, l = 0.f;  // m in log2 units of the scaled logit
-  bf16x8 pb[4];                  // P^T fragments; the late group carries them to the next kv tile
+  constexpr int NS = TT / 32, NP = TT / 16;  // 32-row score tiles, weight fragments
+  bf16x8 pb[NP];                 // P^T fragments; the late group carries them to the next kv tile
 #pragma unroll
-  for (int ks = 0; ks < 4; ++ks)
+  for (int ks = 0; ks < NP; ++ks)
 #pragma unroll
     for (int e = 0; e < 8; ++e) pb[ks][e] = (__bf16)0.f;
-  bf16x8 pl[FINE ? 4 : 1], pm[FINE ? 4 : 1];  // FINE: what pb leaves of the weights, and what that leaves
+  bf16x8 pl[FINE ? NP : 1], pm[FINE ? NP : 1];  // FINE: what pb leaves of the weights, and what that leaves
 
   const int krow = perm_row(qc);
   const int kswz = k_swizzle<D>(krow);  // swizzle key of this lane's K rows (32*sub does not change it)
@@ -623,22 +632,22 @@ __device__ __forceinline__ void flash_tile(const FlashArgs& a, char* lds, const 
   // LDS fragment reads run four MFMAs ahead (0x100 = LDS read, 0x008 = MFMA).
   // base: the kv tile's offset from the tile's first token.
   auto qk_softmax = [&](const bf16_t* kt, int base) {
-    f32x16 s[2];
+    f32x16 s[NS];
 #pragma unroll
-    for (int sub = 0; sub < 2; ++sub)
+    for (int sub = 0; sub < NS; ++sub)
 #pragma unroll
       for (int r = 0; r < 16; ++r) s[sub][r] = 0.f;
 #pragma unroll
     for (int kk = 0; kk < NKK; ++kk)
 #pragma unroll
-      for (int sub = 0; sub < 2; ++sub) {
+      for (int sub = 0; sub < NS; ++sub) {
         const bf16x8 ka = *reinterpret_cast<const bf16x8*>(
             &kt[(32 * sub + krow) * D + (((2 * kk + hf) ^ kswz) << 3)]);
         s[sub] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka, c.qf[kk], s[sub], 0, 0, 0);
       }
     __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
 #pragma unroll
-    for (int i = 0; i < 2 * NKK - 4; ++i) {
+    for (int i = 0; i < NS * NKK - 4; ++i) {
       __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
       __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
     }
@@ -650,18 +659,18 @@ __device__ __forceinline__ void flash_tile(const FlashArgs& a, char* lds, const 
     // Per-row ranges (the causal window, a span clipped behind a lower one, an anchor's span): only the
     // tiles at the ends of a wavefront's ranges are masked, one unsigned compare per score.  (With two
     // 64-bit compares per score on every tile the paper's geometry at 48K took 4.50 ms, now 3.68.)
-    if (kMasked && __builtin_amdgcn_ballot_w64(lo_r > base || hi_r < base + TN - 1) != 0ull) {
+    if (kMasked && __builtin_amdgcn_ballot_w64(lo_r > base || hi_r < base + TT - 1) != 0ull) {
       const uint32_t width = hi_r >= lo_r ? (uint32_t)(hi_r - lo_r) : 0u;
       const uint32_t u = hi_r >= lo_r ? (uint32_t)(base + 8 * hf - lo_r) : 0x80000000u;
 #pragma unroll
-      for (int sub = 0; sub < 2; ++sub)
+      for (int sub = 0; sub < NS; ++sub)
 #pragma unroll
         for (int r = 0; r < 16; ++r)
           s[sub][r] = u + (uint32_t)(32 * sub + 16 * (r >> 3) + (r & 7)) <= width ? s[sub][r] : -INFINITY;
     }
     float mx = -INFINITY;
 #pragma unroll
-    for (int sub = 0; sub < 2; ++sub)
+    for (int sub = 0; sub < NS; ++sub)
 #pragma unroll
       for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[sub][r]);
     mx = pair_max(mx) * sc;
@@ -681,7 +690,7 @@ __device__ __forceinline__ void flash_tile(const FlashArgs& a, char* lds, const 
     }
     const float nm = m > -INFINITY ? -m : 0.f;  // whole column masked so far: exponentials are 0 anyway
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks) {
+    for (int ks = 0; ks < NP; ++ks) {
       f32x8 p;
 #pragma unroll
       for (int e = 0; e < 8; ++e) p[e] = fast_exp2(fmaf(s[ks >> 1][8 * (ks & 1) + e], sc, nm));
@@ -708,7 +717,7 @@ __device__ __forceinline__ void flash_tile(const FlashArgs& a, char* lds, const 
   // O^T += V^T P^T with the P^T fragments in pb
   auto pv = [&](const bf16_t* vt) {
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks)
+    for (int ks = 0; ks < NP; ++ks)
 #pragma unroll
       for (int dt = 0; dt < NDT; ++dt) {
         const bf16x8 va = transposed8<D>(vt + vlane[dt] + 16 * ks * D);
@@ -721,7 +730,7 @@ __device__ __forceinline__ void flash_tile(const FlashArgs& a, char* lds, const 
     constexpr int kPer = FINE ? 3 : 1;  // MFMAs per fragment
     __builtin_amdgcn_sched_group_barrier(0x100, 8, 1);
 #pragma unroll
-    for (int i = 0; i < 4 * NDT - 4; ++i) {
+    for (int i = 0; i < NP * NDT - 4; ++i) {
       __builtin_amdgcn_sched_group_barrier(0x008, kPer, 1);
       __builtin_amdgcn_sched_group_barrier(0x100, 2, 1);
     }
@@ -730,7 +739,7 @@ __device__ __forceinline__ void flash_tile(const FlashArgs& a, char* lds, const 
 
   // a kv tile that none of the wavefront's rows attends is passed over (its weights would all be 0)
   auto attends = [&](int base) {
-    return !kMasked || __builtin_amdgcn_ballot_w64(lo_r <= base + TN - 1 && hi_r >= base && hi_r >= lo_r) != 0ull;
+    return !kMasked || __builtin_amdgcn_ballot_w64(lo_r <= base + TT - 1 && hi_r >= base && hi_r >= lo_r) != 0ull;
   };
   int kb = c.kb, vb = c.vb, vb_prev = c.vb;
   // The late group of a bucket's last tile often has no row at all: it then only stages.  (4000 rows x 16
@@ -738,7 +747,7 @@ __device__ __forceinline__ void flash_tile(const FlashArgs& a, char* lds, const 
   // wavefront, cost the long prompt 1 %.)
   const bool idle = NG == 2 && grp == 1 && __builtin_amdgcn_ballot_w64(cur.row_out >= 0) == 0ull;
   bool owes_pv = false;  // late group: the previous kv tile's PV product is still to be taken
-  for (int64_t t0 = cur.kv_begin; t0 < cur.kv_end; t0 += TN) {
+  for (int64_t t0 = cur.kv_begin; t0 < cur.kv_end; t0 += TT) {
     // After the barrier the tile of this iteration is visible to every wavefront, every wavefront
     // is done with the K stage of the previous tile and the late group with the V stage before
     // that: exactly the stages that the next tile goes into.
@@ -751,7 +760,7 @@ __device__ __forceinline__ void flash_tile(const FlashArgs& a, char* lds, const 
       flush_routed_output(lds, grp, w4, lane);
       c.pending = false;
     }
-    if (t0 + TN < cur.kv_end) stage(cur.kv, t0 + TN, cur.kv_end, kb1, vb1);
+    if (t0 + TT < cur.kv_end) stage(cur.kv, t0 + TT, cur.kv_end, kb1, vb1);
     if (NG == 2 && has_next && t0 == cur.kv_begin) request_next();
     const int base = (int)(t0 - cur.kv_begin);
     const bool mine = attends(base);
@@ -958,9 +967,9 @@ __device__ __forceinline__ void flash_tile(const FlashArgs& a, char* lds, const 
 // span unless a->clip says that spans of a row overlap in one softmax.  Tiles of 128 rows, two workgroups per
 // compute unit: one's tile ends run beside the other's kv loop.
 template <bool CLIP, int D = HD, bool FINE = false, int NG = FINE ? 1 : 2>
-__global__ __launch_bounds__(NG * 256, NG == 2 ? 1 : 2) void span_flash_routed_kernel(
+__global__ __launch_bounds__(NG * 256, NG == 2 ? 1 : FINE ? fine_blocks(D) : 2) void span_flash_routed_kernel(
     const FlashArgs a) {
-  using Lds = FlashLds<NG, D>;
+  using Lds = FlashLds<NG, D, FINE ? fine_tile(D) : TN>;
   constexpr int TM = Lds::kRows;
   extern __shared__ __align__(16) char lds[];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -1158,7 +1167,7 @@ inline unsigned local_grid(int64_t Lq, int S, int Hkv, int G) {
 // writes the final output, which takes the merge's HBM traffic off the critical path of a
 // separate kernel and saves the window partial's round trip.
 template <bool FUSED, int D = HD, bool FINE = false>
-__global__ __launch_bounds__(FlashLds<1>::kThreads, 2) void span_flash_local_kernel(const FlashArgs a) {
+__global__ __launch_bounds__(FlashLds<1>::kThreads, FINE ? fine_blocks(D) : 2) void span_flash_local_kernel(const FlashArgs a) {
   extern __shared__ __align__(16) char lds[];
   constexpr int TML = FlashLds<1>::kRows;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -1620,7 +1629,7 @@ sl_status prefill_attention_mfma(const Problem& pb, const void* Q, const void* K
 // Measured (32:4 heads, top-8, D = 128 unless said otherwise; row-stationary -> this form, us):
 //   20011 rows, spans of 142: 16400 -> 1940; at D = 64: 8320 -> 1210; 2500 rows, spans of 50: 791 -> 191;
 //   200 rows behind 60000 tokens, spans of 245: 589 -> 83; 8 rows there: 157 -> 72.
-// 128-row tiles, two workgroups per compute unit (one's tile ends beside the other's kv loop): a span of
+// 128-row tiles, two workgroups per compute unit, three at D = 64 (one's tile ends beside the other's kv loop): a span of
 // 142 tokens is three kv tiles, and 256-row tiles with one workgroup took 1381 us for the routed part where
 // these take 1288.
 // Calls without a workspace, or with one too small, take the row-stationary kernels as before.
@@ -1671,9 +1680,9 @@ bool fine_setup(DeviceSetup* out) {
   if (!done[dev])
     done[dev] = hipFuncSetAttribute(reinterpret_cast<const void*>(span_flash_routed_kernel<true, D, true>),
                                     hipFuncAttributeMaxDynamicSharedMemorySize,
-                                    FlashLds<1, D>::kBytes) == hipSuccess &&
+                                    FlashLds<1, D, fine_tile(D)>::kBytes) == hipSuccess &&
                 hipFuncSetAttribute(reinterpret_cast<const void*>(span_flash_local_kernel<false, D, true>),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, FlashLds<1, D>::kBytes) == hipSuccess;
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, FlashLds<1, D, fine_tile(D)>::kBytes) == hipSuccess;
   return done[dev];
 }
 
@@ -1722,9 +1731,9 @@ sl_status fine_pass(const Problem& pb, const DeviceSetup& dev, const bf16_t* Q, 
                       GridItems{pb.A}, flag, st))
     return SL_ERR_LAUNCH;
   if (pb.prof_start) (void)hipEventRecord(pb.prof_start, st);
-  using Lds = FlashLds<1, D>;
+  using Lds = FlashLds<1, D, fine_tile(D)>;
   hipLaunchKernelGGL((span_flash_routed_kernel<true, D, true>),
-                     dim3(2 * dev.grid), dim3(Lds::kThreads), Lds::kBytes, st, a);
+                     dim3(fine_blocks(D) * dev.grid), dim3(Lds::kThreads), Lds::kBytes, st, a);
   if (pb.prof_stop) (void)hipEventRecord(pb.prof_stop, st);
   hipLaunchKernelGGL((span_flash_local_kernel<false, D, true>), dim3(local_grid(pb.Lq, pb.A, pb.Hkv, pb.G)),
                      dim3(Lds::kThreads), Lds::kBytes, st, a);
