@@ -466,7 +466,8 @@ struct TileDesc {
   int64_t q_off;      // element offset of the lane's Q vector
   int64_t row_out;    // partial record index of the lane's column (fused merge: its row index
                       // h*Lq + r), -1 = no row
-  int64_t row_base;   // fused merge: h*Lq of the tile's head
+  int64_t first_pos;  // fused merge: position of the tile's first row; column x holds row x & row_mask of the tile
+  int row_mask;
   int64_t i_q, lo_q;  // LOCAL: query position and start of its window
 };
 
@@ -882,7 +883,7 @@ __device__ __forceinline__ void flash_tile(const FlashArgs& a, char* lds, const 
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
         const int row = w4 * 32 + (half * 4 + u) * 4 + (lane >> 4), piece = lane & 15;
-        const int cq = (int)((a.q_pos0 + (outs[u] - cur.row_base)) / a.A);
+        const int cq = (int)((cur.first_pos + (row & cur.row_mask)) / a.A);
         const float lw = row_lse[row];
         float M = lw;
 #pragma unroll
@@ -1004,7 +1005,8 @@ __global__ __launch_bounds__(NG * 256, NG == 2 ? 1 : FINE ? fine_blocks(D) : 2) 
         if (jj >= 0 && jj < c && jj < j && (jj + 1) * a->A > d.lo_q) d.lo_q = (jj + 1) * a->A;
       }
     }
-    d.row_base = 0;
+    d.first_pos = 0;
+    d.row_mask = 0;
     return d;
   };
   FlashCarry carry;
@@ -1081,7 +1083,8 @@ __global__ __launch_bounds__(FlashLds<2>::kThreads, 1) void span_flash_anchor_ke
     d.row_out = real ? ((int64_t)h * a->Lq + r) * (a->topk + 1) + slot : -1;
     d.lo_q = sp.lo;
     d.i_q = sp.hi - 1;
-    d.row_base = 0;
+    d.first_pos = 0;
+    d.row_mask = 0;
     // the tile's kv range: from the lowest lo to the highest hi of its rows
     int64_t lo = real && sp.hi > sp.lo ? sp.lo : INT64_MAX, hi = real && sp.hi > sp.lo ? sp.hi : 0;
 #pragma unroll
@@ -1136,32 +1139,45 @@ __global__ __launch_bounds__(FlashLds<2>::kThreads, 1) void span_flash_anchor_ke
   if (carry.pending) flush_routed_output(lds, wave >> 2, wave & 3, lane);
 }
 
-// Row tiles of the local-window kernel and their grouping into chunks of `tps` tiles (the tiles
-// of one span when S is a multiple of the tile height).
+// A window tile's 128 columns are `heads` query heads of one kv head, which attend the same keys, times 128 / heads rows:
+// the fewer rows, the shorter the kv range that the tile walks beyond what each of its rows attends.  Heads: the largest
+// power of two that divides the group, up to 8.  Tiles of 128 rows of one head -> 16 rows of 8, this kernel, us, 32:4
+// heads: 20011 rows, spans of 142 (fp32 weights) 181 -> 140; 49157 rows, windows of 1088 tokens 990 -> 970; 4000 rows, spans
+// of 512 47 -> 43; 262144 rows, spans of 512, with the merge (bound by the partials) 5000 -> 4960.
+__host__ __device__ inline int local_heads(int G) {
+  const int p = G & -G;
+  return p < 8 ? p : 8;
+}
+// Row tiles and their grouping into chunks of `tps` tiles (the tiles of one span when S is a multiple of the tile height).
 struct LocalMap {
-  int tiles_per_head, tps, chunks;
+  int rows, tiles, tps, chunks;  // rows of a tile, tiles of a kv head (and group of `heads` heads)
 };
-__host__ __device__ inline LocalMap local_map(int64_t Lq, int S) {
+__host__ __device__ inline LocalMap local_map(int64_t Lq, int S, int G) {
   LocalMap m;
-  m.tiles_per_head = (int)((Lq + FlashLds<1>::kRows - 1) / FlashLds<1>::kRows);
-  m.tps = S / FlashLds<1>::kRows > 0 ? S / FlashLds<1>::kRows : 1;
-  m.chunks = (m.tiles_per_head + m.tps - 1) / m.tps;
+  m.rows = FlashLds<1>::kRows / local_heads(G);
+  m.tiles = (int)((Lq + m.rows - 1) / m.rows);
+  // No more than an eighth of the tiles in a run: the paper's geometry, whose runs are 1024 tokens long, 1024 rows behind
+  // 48133 tokens 407 -> 285 us, 4096 530 -> 444, a prompt of 3000 253 -> 161.
+  const int each = (m.tiles + 7) / 8;
+  m.tps = S / m.rows < each ? S / m.rows : each;
+  m.tps = m.tps > 0 ? m.tps : 1;
+  m.chunks = (m.tiles + m.tps - 1) / m.tps;
   return m;
 }
 // Blocks to launch: 8 x the largest per-XCD share.
 inline unsigned local_grid(int64_t Lq, int S, int Hkv, int G) {
-  const LocalMap m = local_map(Lq, S);
+  const LocalMap m = local_map(Lq, S, G);
   int best = 0;
   for (int x = 0; x < 8; ++x) {
     const int cx = (m.chunks - x + 7) / 8;
     const bool lx = m.chunks > 0 && (m.chunks - 1) % 8 == x;
-    const int tx = cx * m.tps - (lx ? m.chunks * m.tps - m.tiles_per_head : 0);
+    const int tx = cx * m.tps - (lx ? m.chunks * m.tps - m.tiles : 0);
     best = tx > best ? tx : best;
   }
-  return (unsigned)(8 * Hkv * best * G);
+  return (unsigned)(8 * Hkv * best * (G / local_heads(G)));
 }
 
-// Local window [c*S, i]: regular 128-row tiles of one head with the causal / window mask.
+// Local window [c*S, i]: regular tiles of 128 columns with the causal / window mask.
 // FUSED = false: writes the window's partial into the row's last slot (a merge kernel follows).
 // FUSED = true (joint softmax, topk <= 8): merges the row's routed partials in the epilogue and
 // writes the final output, which takes the merge's HBM traffic off the critical path of a
@@ -1169,35 +1185,36 @@ inline unsigned local_grid(int64_t Lq, int S, int Hkv, int G) {
 template <bool FUSED, int D = HD, bool FINE = false>
 __global__ __launch_bounds__(FlashLds<1>::kThreads, FINE ? fine_blocks(D) : 2) void span_flash_local_kernel(const FlashArgs a) {
   extern __shared__ __align__(16) char lds[];
-  constexpr int TML = FlashLds<1>::kRows;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int qrow = wave * 32 + (lane & 31);
-  // Workgroup -> (head, row tile), XCD-aware: blocks are dealt round-robin to the 8 XCDs, each
+  // Workgroup -> (heads, row tile), XCD-aware: blocks are dealt round-robin to the 8 XCDs, each
   // with its own L2.  A run of `tps` consecutive row tiles (one span's worth) goes to one XCD,
-  // and inside an XCD the G query heads of a kv head take the same row tile back to back, so the
-  // window's K/V tiles are fetched from HBM about once instead of once per head and row tile.
-  const LocalMap lm = local_map(a.Lq, a.A);
+  // and inside an XCD the groups of heads of a kv head take the same row tile back to back, so the
+  // window's K/V tiles are fetched from HBM about once.
+  const LocalMap lm = local_map(a.Lq, a.A, a.G);
+  const int heads = local_heads(a.G), sets = a.G / heads;
   const int xcd = blockIdx.x % 8, slot = blockIdx.x / 8;
   const int chunks_x = (lm.chunks - xcd + 7) / 8;                 // chunks xcd, xcd+8, ... of a kv head
   const bool has_last = lm.chunks > 0 && (lm.chunks - 1) % 8 == xcd;  // the only chunk that may be short
-  const int tiles_x = chunks_x * lm.tps - (has_last ? lm.chunks * lm.tps - lm.tiles_per_head : 0);
-  if (slot >= (a.Hq / a.G) * tiles_x * a.G) return;  // uniform: the grid is padded to 8 * the largest share
-  const int kvh = slot / (tiles_x * a.G), rem = slot % (tiles_x * a.G);
-  const int tile_local = rem / a.G, g = rem % a.G;
+  const int tiles_x = chunks_x * lm.tps - (has_last ? lm.chunks * lm.tps - lm.tiles : 0);
+  if (slot >= (a.Hq / a.G) * tiles_x * sets) return;  // uniform: the grid is padded to 8 * the largest share
+  const int kvh = slot / (tiles_x * sets), rem = slot % (tiles_x * sets);
+  const int tile_local = rem / sets;
   const int tile = (xcd + 8 * (tile_local / lm.tps)) * lm.tps + tile_local % lm.tps;
-  const int h = kvh * a.G + g;
-  const int64_t r0 = (int64_t)tile * TML;
-  const int64_t r = r0 + qrow;
+  const int h = kvh * a.G + rem % sets * heads + qrow / lm.rows;
+  const int64_t r0 = (int64_t)tile * lm.rows;
+  const int64_t r = r0 + qrow % lm.rows;
   const int64_t rc = r < a.Lq ? r : a.Lq - 1;
   TileDesc d;
-  d.kv = h / a.G;
+  d.kv = kvh;
   d.q_off = h * a.qsh + rc * a.qst;
-  d.row_base = (int64_t)h * a.Lq;
-  if (FUSED) d.row_out = r < a.Lq ? d.row_base + r : -1;
-  else d.row_out = r < a.Lq ? (d.row_base + r) * (a.topk + 1) + a.topk : -1;
+  d.first_pos = a.q_pos0 + r0;
+  d.row_mask = lm.rows - 1;
+  if (FUSED) d.row_out = r < a.Lq ? (int64_t)h * a.Lq + r : -1;
+  else d.row_out = r < a.Lq ? ((int64_t)h * a.Lq + r) * (a.topk + 1) + a.topk : -1;
   d.i_q = a.q_pos0 + rc;
   const int64_t i_first = a.q_pos0 + r0;
-  const int64_t i_last = min(a.q_pos0 + r0 + TML - 1, a.q_pos0 + a.Lq - 1);
+  const int64_t i_last = min(a.q_pos0 + r0 + lm.rows - 1, a.q_pos0 + a.Lq - 1);
   if (a.window > 0) {  // the paper's geometry: a sliding window [i - window + 1, i] per row
     d.lo_q = d.i_q - a.window + 1 > 0 ? d.i_q - a.window + 1 : 0;
     const int64_t first_lo = i_first - a.window + 1 > 0 ? i_first - a.window + 1 : 0;

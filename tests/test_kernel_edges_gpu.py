@@ -599,3 +599,26 @@ def test_fp32_spans_keep_what_is_not_finite_to_the_rows_that_attend_it(which, ba
     attends[Hq // Hkv:] = False
     assert not bool((~finite & ~attends).any())
     assert bool((~finite).any())
+
+
+@pytest.mark.parametrize("Hq,Hkv", [(1, 1), (3, 1), (6, 1), (12, 2), (8, 1), (16, 1)])
+@pytest.mark.parametrize("Lq,S", [(1, 64), (15, 64), (17, 192), (129, 128), (200, 77)])
+def test_window_tiles_of_several_heads(Hq, Hkv, Lq, S):
+    """Groups of 1, 3, 6, 8 and 16 heads: 1, 2 and 8 heads of a window tile, row counts around a tile's 128, 64 and 16
+    rows, with the merge in the window kernel and behind it, spans of any length, and the sliding window; against the
+    oracle and the row-stationary form."""
+    from tests.test_parity_gpu import check_combined
+    L, k = 64 * 30 + 11, 3
+    q0 = L - Lq
+    Q, K, V = make(2200 + Hq + Lq, Hq, Hkv, L, 128, torch.bfloat16, Lq=Lq, scale=0.5)
+    idx, sc = B.sl_span_search_prefill(Q, K, None, S, k, q_pos0=q0, want_scores=True)
+    O, LSE = B.sl_span_attention_prefill(Q, K, V, idx, S, q_pos0=q0)
+    C = B.sl_span_attention_combined_prefill(Q, K, V, idx, sc, S, q_pos0=q0)
+    an, asc = B.sl_anchor_search_prefill(Q, K, 2, 120, q_pos0=q0, want_scores=True)
+    A = B.sl_anchor_attention_prefill(Q, K, V, an, asc, 120, 2, 1, q_pos0=q0)
+    R = B.sl_anchor_attention_prefill(Q, K, V, an, asc, 120, 2, 1, q_pos0=q0, row_stationary=True)
+    torch.cuda.synchronize()
+    rows = [(h, r) for h in range(Hq) for r in sorted({0, 1, Lq // 2, Lq - 1, *range(0, Lq, 37)}) if r < Lq]
+    check_attention(O, LSE, Q, K, V, idx, S, q0, 0.0, rows)
+    check_combined(C, Q, K, V, idx, sc, S, q0, 0.0, rows)
+    assert float((A.float() - R.float()).abs().max()) <= 3e-2    # the bound of the masked kv tiles' test
