@@ -773,12 +773,25 @@ inline bool reduce_fits_lds(int64_t nrec, bool combined) {
   return nrec * (combined ? 2 : 1) * (int64_t)sizeof(float) <= 64 * 1024;
 }
 
+// Tokens per item.  A batch has items enough even for short spans; there it counts that a workgroup's four wavefronts,
+// which take a quarter of the chunk each, all have rows (512-token chunks for spans of 128 left three of them idle),
+// and that the last items, 256 KB of rows each at 512 tokens, do not run on alone.  Batches, us per step, 32:4 heads, by
+// sequences x (longest; down to a fifth of it), spans, top-k: 8 x 20000, 128, 16: 87.7 -> 53.9; 8 x 30000, 192, 16: 96 -> 72;
+// 8 x 50000, 256, 16: 108 -> 92; 7 x 100000, 320, 16: 114 -> 108; 8 x 300000, 512, 16: 167-171 -> 165, gated 180 -> 175;
+// 8 x 400000, 640, 16: 275 -> 213.  Spans of 448 stay at 512 (157; 256-token chunks, as badly filled, 161), 8 x 1M in spans
+// of 1024 too (318), 2 x 300000 at 128 (55; 64: 79).
 int pick_chunk_tokens(const Problem& pb, int batch = 1) {
   // Aim for a few thousand workgroups so the 256 CUs keep enough loads in flight, without
   // going below 64 tokens per item.
   const int64_t units = (int64_t)batch * pb.Hq * (pb.topk + 1);
+  auto chunks = [&](int ct) { return (int64_t)((pb.S + ct - 1) / ct); };
+  auto filled = [&](int ct, int tenths) { return 10 * (int64_t)pb.S >= tenths * chunks(ct) * ct; };
   int ct = 512;
-  while (ct > 64 && units * ((pb.S + ct - 1) / ct) < 4096) ct >>= 1;
+  while (ct > 64 && units * chunks(ct) < 4096) ct >>= 1;
+  if (batch > 1) {
+    if (ct == 512 && units * chunks(ct) < 8192 && filled(256, 9)) ct = 256;
+    while (ct > 128 && !filled(ct, 7)) ct >>= 1;
+  }
   return ct;
 }
 

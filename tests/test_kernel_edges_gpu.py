@@ -622,3 +622,33 @@ def test_window_tiles_of_several_heads(Hq, Hkv, Lq, S):
     check_attention(O, LSE, Q, K, V, idx, S, q0, 0.0, rows)
     check_combined(C, Q, K, V, idx, sc, S, q0, 0.0, rows)
     assert float((A.float() - R.float()).abs().max()) <= 3e-2    # the bound of the masked kv tiles' test
+
+
+@pytest.mark.parametrize("form", ["joint", "gated"])
+@pytest.mark.parametrize("S", [65, 128, 200, 320])
+def test_decode_batches_of_many_short_spans(S, form):
+    """Items enough for every chunk length (8 x 32 x 17): chunks of 128 and 256 tokens that spans fill badly, exactly and
+    with a remainder, against the single-sequence entry points.  Other chunks add in another order: outputs differ by a
+    rounding to bf16, 2^-7 of them, and what fp32 sums of some thousand terms differ by."""
+    gated = form == "gated"
+    seqs = [make(2300 + S + b, 32, 4, S * 18 + 700 - 83 * b, 128, torch.bfloat16, Lq=1, scale=0.5) for b in range(8)]
+    Q, K, V = ([s[x] for s in seqs] for x in range(3))
+    bt = B.DecodeBatch(Q, Q, K, V, [B.sl_span_keys(k, S) for k in K], S, 16, want_scores=gated)
+    if gated:
+        idx, sc = B.sl_span_search_decode_batched(bt)
+        O = B.sl_span_attention_combined_decode_batched(bt)
+    else:
+        idx = B.sl_span_search_decode_batched(bt)
+        O, LSE = B.sl_span_attention_decode_batched(bt)
+    for b in range(8):
+        if gated:
+            i1, s1 = B.sl_span_search_decode(Q[b], K[b], None, S, 16, want_scores=True)
+            o1 = B.sl_span_attention_combined_decode(Q[b], K[b], V[b], i1, s1, S)
+        else:
+            i1 = B.sl_span_search_decode(Q[b], K[b], None, S, 16)
+            o1, l1 = B.sl_span_attention_decode(Q[b], K[b], V[b], i1, S)
+        torch.cuda.synchronize()
+        assert torch.equal(idx[b], i1)
+        assert float(((O[b].float() - o1.float()).abs() - 2 ** -7 * o1.float().abs()).max()) <= 1e-5
+        if not gated:
+            assert float((LSE[b] - l1).abs().max()) <= 1e-5
