@@ -773,6 +773,16 @@ inline bool reduce_fits_lds(int64_t nrec, bool combined) {
   return nrec * (combined ? 2 : 1) * (int64_t)sizeof(float) <= 64 * 1024;
 }
 
+// No chunk is shorter than what the four wavefronts load at once, eight rows per row group: of a shorter one a wavefront
+// loads its last row again and again (bf16, D = 128: 128 tokens; D = 64: 256; fp32, D = 128: 64).  With 64 tokens throughout,
+// us per step, bf16 32:4 heads, top-16: 16411 tokens 20.1 -> 17.7, 65536 27.0 -> 23.1, 262144 42.2 -> 34.5, 524288 52.5 ->
+// 43.9, gated 59.7 -> 50.5; D = 64: 65536 26.2 -> 18.5, 524288 48.8 -> 28.9; the paper's geometry: 4000 tokens, top-4, 29.9 ->
+// 24.6, 200000, top-2, 38.9 -> 32.1, 1M, top-1, 43.1 -> 36.1.
+int least_chunk(const Problem& pb) {
+  const int rows = 4 * 8 * (1024 / (pb.D * (pb.dtype == SL_BF16 ? 2 : 4)));
+  return rows < 64 ? 64 : rows;
+}
+
 // Tokens per item.  A batch has items enough even for short spans; there it counts that a workgroup's four wavefronts,
 // which take a quarter of the chunk each, all have rows (512-token chunks for spans of 128 left three of them idle),
 // and that the last items, 256 KB of rows each at 512 tokens, do not run on alone.  Batches, us per step, 32:4 heads, by
@@ -781,13 +791,12 @@ inline bool reduce_fits_lds(int64_t nrec, bool combined) {
 // 8 x 400000, 640, 16: 275 -> 213.  Spans of 448 stay at 512 (157; 256-token chunks, as badly filled, 161), 8 x 1M in spans
 // of 1024 too (318), 2 x 300000 at 128 (55; 64: 79).
 int pick_chunk_tokens(const Problem& pb, int batch = 1) {
-  // Aim for a few thousand workgroups so the 256 CUs keep enough loads in flight, without
-  // going below 64 tokens per item.
+  // Aim for a few thousand workgroups so the 256 CUs keep enough loads in flight.
   const int64_t units = (int64_t)batch * pb.Hq * (pb.topk + 1);
   auto chunks = [&](int ct) { return (int64_t)((pb.S + ct - 1) / ct); };
   auto filled = [&](int ct, int tenths) { return 10 * (int64_t)pb.S >= tenths * chunks(ct) * ct; };
   int ct = 512;
-  while (ct > 64 && units * chunks(ct) < 4096) ct >>= 1;
+  while (ct > least_chunk(pb) && units * chunks(ct) < 4096) ct >>= 1;
   if (batch > 1) {
     if (ct == 512 && units * chunks(ct) < 8192 && filled(256, 9)) ct = 256;
     while (ct > 128 && !filled(ct, 7)) ct >>= 1;
@@ -841,7 +850,7 @@ AnchorPlan plan_anchor(const Problem& pb, int64_t window, int b, int f, int root
   if (a.maxlen > i + 1) a.maxlen = i + 1;
   const int64_t units = (int64_t)pb.Hq * (pb.topk + 1);
   int ct = 512;
-  while (ct > 64 && batch * units * ((a.maxlen + ct - 1) / ct) < 4096) ct >>= 1;
+  while (ct > least_chunk(pb) && batch * units * ((a.maxlen + ct - 1) / ct) < 4096) ct >>= 1;
   a.CT = ct;
   // chunks sit on the absolute CT-token lattice: a range of maxlen tokens touches one more of them
   // than its length alone fills
