@@ -670,6 +670,110 @@ __global__ __launch_bounds__(256) void decode_reduce_combined_batched_kernel(
                                     nchunks, wchunks);
 }
 
+// A joint step of short lists in one launch: one workgroup of eight wavefronts per head takes all its rows, cut into
+// units of what a wavefront loads at once, an equal share of consecutive units each (the next unit's rows are asked for
+// before one is computed); the wavefronts' running states are merged in LDS.  Bound by the launch and by the latency of
+// one head's rows through one compute unit, so it has a limit in bytes (decode_is_short).
+constexpr int kShortThreads = 512, kShortWaves = kShortThreads / 64;
+
+template <typename T, int D>
+__global__ __launch_bounds__(kShortThreads) void decode_short_kernel(
+    const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V, const int32_t* __restrict__ idx,
+    T* __restrict__ O, float* __restrict__ LSE, int64_t q_pos, int G, int S, int A, int topk, int parts,
+    float scale_log2e, int64_t qsh, int64_t kvsh, int64_t kvst) {
+  using RL = RowLayout<T, D>;
+  constexpr int EPL = RL::EPL, LPR = RL::LPR, RPW = RL::RPW, U = 8, ROWS = RPW * U;
+  static_assert(D <= kShortThreads && SL_MAX_TOPK <= 64, "a thread per column, a lane per slot");
+  __shared__ float s_m[kShortWaves], s_l[kShortWaves], s_o[kShortWaves][D];
+  const int h = blockIdx.x, kv = h / G;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lr = lane % LPR;
+  const int64_t c = q_pos / A;
+  const T* const Kb = K + (int64_t)kv * kvsh;
+  const T* const Vb = V + (int64_t)kv * kvsh;
+  // the head's list, a slot per lane: a load of it between the rows' would wait for them
+  const int list = lane < topk ? idx[(int64_t)h * topk + lane] : -1;
+  float q2[EPL];
+  Elem<T>::unpack(load16(Q + (int64_t)h * qsh + lr * EPL), q2);
+#pragma unroll
+  for (int e = 0; e < EPL; ++e) q2[e] *= scale_log2e;
+  // unit u: rows [t0, t1) of slot u / parts (slot topk: the window), at most ROWS of them
+  auto unit_rows = [&](int u, int64_t& t0, int64_t& t1) {
+    const int slot = u / parts;
+    int64_t begin = c * A, end = q_pos + 1;
+    if (slot < topk) {
+      const int64_t j = __builtin_amdgcn_readlane(list, slot);
+      end = (j + 1) * A;
+      begin = end - S > 0 ? end - S : 0;
+      if (A < S) {  // spans that overlap: behind the nearest lower one
+        for (int s2 = 0; s2 < topk; ++s2) {
+          const int64_t jj = __builtin_amdgcn_readlane(list, s2);
+          if (jj >= 0 && jj < j && (jj + 1) * A > begin) begin = (jj + 1) * A;
+        }
+      }
+      if (j < 0 || j >= c) end = begin = 0;
+    }
+    t0 = begin + (u % parts) * ROWS;
+    t1 = t0 + ROWS < end ? t0 + ROWS : end;
+  };
+  AttendState<T, D> st;
+  st.init();
+  const int units = (topk + 1) * parts, u0 = units * wave / kShortWaves, u1 = units * (wave + 1) / kShortWaves;
+  uint4 kr[2][U], vr[2][U];
+  int64_t t0[2], t1[2];
+  auto ask = [&](int u, auto at) {
+    constexpr int b = decltype(at)::value;
+    unit_rows(u, t0[b], t1[b]);
+    if (t0[b] < t1[b]) load_rows<T, D, U, false>(Kb, Vb, kvst, t0[b], t1[b], lane, kr[b], vr[b]);
+  };
+  auto take = [&](auto at) {
+    constexpr int b = decltype(at)::value;
+    if (t0[b] < t1[b]) attend_loaded<T, D, U>(q2, kr[b], vr[b], t0[b], t0[b], t1[b], lane, st);
+  };
+  using First = std::integral_constant<int, 0>;
+  using Second = std::integral_constant<int, 1>;
+  if (u0 < u1) ask(u0, First{});
+  for (int u = u0; u < u1; u += 2) {
+    if (u + 1 < u1) ask(u + 1, Second{});
+    take(First{});
+    if (u + 2 < u1) ask(u + 2, First{});
+    if (u + 1 < u1) take(Second{});
+  }
+#pragma unroll
+  for (int off = LPR; off < 64; off <<= 1) {  // the wavefront's row groups
+    const float mo = __shfl_xor(st.m, off, 64), lo = __shfl_xor(st.l, off, 64);
+    const float M = fmaxf(st.m, mo);
+    const float wa = st.m > -INFINITY ? fast_exp2(st.m - M) : 0.f, wb = mo > -INFINITY ? fast_exp2(mo - M) : 0.f;
+    st.l = st.l * wa + lo * wb;
+#pragma unroll
+    for (int e = 0; e < EPL; ++e) {
+      const float oo = __shfl_xor(st.o[e], off, 64);
+      st.o[e] = st.o[e] * wa + oo * wb;
+    }
+    st.m = M;
+  }
+  if (lane < LPR) {
+#pragma unroll
+    for (int e = 0; e < EPL; ++e) s_o[wave][lr * EPL + e] = st.o[e];
+    if (lane == 0) {
+      s_m[wave] = st.m;
+      s_l[wave] = st.l;
+    }
+  }
+  __syncthreads();
+  if (tid >= D) return;
+  float m = -INFINITY, l = 0.f, o = 0.f;
+#pragma unroll
+  for (int w = 0; w < kShortWaves; ++w) m = fmaxf(m, s_m[w]);
+#pragma unroll
+  for (int w = 0; w < kShortWaves; ++w) {
+    const float x = s_m[w] > -INFINITY ? fast_exp2(s_m[w] - m) : 0.f;
+    l = fmaf(x, s_l[w], l);
+    o = fmaf(x, s_o[w][tid], o);
+  }
+  Elem<T>::store1(O + (int64_t)h * D + tid, o / l);
+  if (tid == 0) LSE[h] = (m + __log2f(l)) * kLn2;
+}
+
 // Loads in flight per lane: a wavefront's quarter of a 512-token chunk is two batches of 16 K and
 // 16 V loads (measured 4.5 % faster than four batches of 8 at the 10M cache); shorter chunks keep
 // 8, which covers a 128-token chunk's quarter in one batch and leaves registers for a fifth
@@ -804,9 +908,36 @@ int pick_chunk_tokens(const Problem& pb, int batch = 1) {
   return ct;
 }
 
+// The step in one launch (decode_short_kernel) for joint bf16 lists of up to 160 KB of K a head.  us per step (search and
+// attention, graph), 32:4 heads, chunks and reduction -> one launch: 5 x 64 rows 13.9 -> 11.7, 9 x 64 15.0 -> 13.4, 5 x 128 15.2
+// -> 14.4, D = 64: 9 x 128 15.7 -> 13.4, 5 x 256 16.2 -> 14.6; 64:8 heads 5 x 64 15.5 -> 12.0; and a launch less for the host,
+// 3 us of a step issued call by call.  More rows wait for one compute unit: 9 x 90 15.9 -> 16.7, 9 x 128 16.3 -> 18.4 (all D = 128).
+// A gated list gains from 5 x 64 rows only (its units are records of their own), and fp32 keeps the shorter sums of chunks
+// (error against 64 bits 1.57e-7, in one launch 1.65e-7).
+bool decode_is_short(const Problem& pb) {
+  return pb.dtype == SL_BF16 && !pb.combined && (int64_t)(pb.topk + 1) * pb.S * pb.D <= 80 * 1024;
+}
+
+template <typename T, int D>
+void launch_short(const Problem& pb, const void* Q, const void* K, const void* V, const int32_t* idx, void* O, float* LSE,
+                  hipStream_t st) {
+  const int rows = RowLayout<T, D>::RPW * 8;
+  hipLaunchKernelGGL((decode_short_kernel<T, D>), dim3(pb.Hq), dim3(kShortThreads), 0, st, static_cast<const T*>(Q),
+                     static_cast<const T*>(K), static_cast<const T*>(V), idx, static_cast<T*>(O), LSE, pb.q_pos0, pb.G,
+                     pb.S, pb.A, pb.topk, (pb.S + rows - 1) / rows, pb.scale * kLog2e, pb.qsh, pb.kvsh, pb.kvst);
+}
+
 template <typename T, int D>
 sl_status launch_decode(const Problem& pb, const void* Q, const void* K, const void* V,
                         const int32_t* idx, void* O, float* LSE, void* ws, hipStream_t st) {
+  if constexpr (sizeof(T) == 2) {
+    if (decode_is_short(pb)) {
+      if (pb.prof_start) (void)hipEventRecord(pb.prof_start, st);
+      launch_short<T, D>(pb, Q, K, V, idx, O, LSE, st);
+      if (pb.prof_stop) (void)hipEventRecord(pb.prof_stop, st);
+      return hipGetLastError() == hipSuccess ? SL_OK : SL_ERR_LAUNCH;
+    }
+  }
   const int CT = pick_chunk_tokens(pb);
   const int nchunks = (pb.S + CT - 1) / CT;
   const int n_routed = pb.Hq * pb.topk * nchunks;

@@ -652,3 +652,25 @@ def test_decode_batches_of_many_short_spans(S, form):
         assert float(((O[b].float() - o1.float()).abs() - 2 ** -7 * o1.float().abs()).max()) <= 1e-5
         if not gated:
             assert float((LSE[b] - l1).abs().max()) <= 1e-5
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("rows", [0, 1])
+def test_decode_steps_on_both_sides_of_one_launch(D, rows):
+    """160 KB of K a head (and a row more) in slots of several sizes and forms: spans of a wavefront's load and less, more
+    and with a remainder, spans that overlap, empty and foreign slots, no slot at all."""
+    limit = 80 * 1024 // D
+    for S, A, k in ((limit // 5 + rows, limit // 5 + rows, 4), (limit // 33 + rows, limit // 33 + rows, 32),
+                    (limit + rows, limit + rows, 0), (limit // 2 + rows, (limit // 2 + rows) // 3, 1),
+                    (limit // 10 + rows, (limit // 10 + rows + 1) // 2, 9), (7, 7, 5), (1, 1, 2)):
+        L = A * (k + 9) + S + 1
+        Q, K, V = make(3100 + S + k, 8, 2, L, D, torch.bfloat16, Lq=1)
+        c = (L - 1) // A
+        g = torch.Generator().manual_seed(S)
+        idx = torch.stack([torch.randperm(c, generator=g)[:k] for _ in range(8)]).to(torch.int32).reshape(8, 1, k)
+        if k > 1:
+            idx[1, 0, 0], idx[2, 0, k - 1], idx[3, 0, 1], idx[4] = -1, c, 10 ** 6, -1
+        idx = idx.to(DEV)
+        O, LSE = B.sl_span_attention_decode(Q, K, V, idx, S, span_stride=A)
+        torch.cuda.synchronize()
+        check_attention(O, LSE, Q, K, V, idx, S, L - 1, 0.0, stride=A)
