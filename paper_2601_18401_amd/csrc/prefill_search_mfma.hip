@@ -69,7 +69,7 @@ __device__ __forceinline__ float of_other_half(float x) {
 // of two ways.  Both are bound by their vector instructions, not by loads or MFMAs: for 65536 rows x 256 spans, top-8,
 // the vector units were busy 78 % of the time, the matrix pipes 19 %, so instructions are what counts.
 //
-// One walk (no scores wanted, up to kPackedSpans candidates): a lane keeps its KMAX + 1 best scores with the span's
+// One walk (no scores wanted, up to `packed` candidates): a lane keeps its KMAX + 1 best scores with the span's
 // number in place of their lowest bits, a median instruction per list entry and score; the two lanes of a column merge
 // their lists.  Cutting a score towards zero keeps the order of scores that differ after it, so where the k'-th and
 // the next one do, the first k' entries are the selection, and no index had to be carried beside the scores.  Where
@@ -94,17 +94,16 @@ __device__ __forceinline__ float of_other_half(float x) {
 // taken where.  Slower than both: stages of 64 in two buffers and three buffers of 32.  Lists of at most 4 spans have
 // their own KMAX: half of the median instructions.
 //
-// Two walks -> one, us, 32 heads: 65536 rows x 256 spans top-4 264 -> 160, top-8 312 -> 194, top-16 549 -> 298, top-32
-// 1320 -> 621; 16384 rows x 1024 spans, top-8 380 -> 232, x 2048 705 -> 516, x 4096 (where the second look at
-// agreeing scores is needed in most wavefronts) 1349 -> 1050; 500 rows x 256 23.4 -> 10.9; 3000 x 46 14.1 -> 8.9.  Where
+// Two walks -> one, us, 32 heads: 65536 rows x 256 spans top-4 264 -> 166, top-8 315 -> 200, top-16 549 -> 302, top-32
+// 1320 -> 626; 16384 rows x 1024 spans, top-8 380 -> 238, x 2048 694 -> 525, x 4096 (where the second look at
+// agreeing scores is needed in most wavefronts) 1326 -> 1055; 500 rows x 256 23.4 -> 10.9; 3000 x 46 14.1 -> 9.1.  Where
 // all scores are equal the second way comes on top: 20000 x 156, top-8, 99 -> 135.
-constexpr int kPackedSpans = 4096;  // the most that was measured; beyond, too few bits of the score are left
 
 template <int KMAX, bool WS, bool DIRECT>
 __global__ __launch_bounds__(256, (KMAX <= 4 || (KMAX == 8 && !WS)) ? 4 : 1) void prefill_search_mfma_kernel(
     const bf16_t* __restrict__ Qs, const bf16_t* __restrict__ K, const bf16_t* __restrict__ Ks,
     int32_t* __restrict__ idx, float* __restrict__ scores, int64_t Lq, int64_t q_pos0, int G, int S,
-    int topk, int64_t n, int64_t qsh, int64_t qst, int64_t kvsh, int64_t kvst) {
+    int topk, int64_t n, int packed, int64_t qsh, int64_t qst, int64_t kvsh, int64_t kvst) {
   constexpr int CAP = 3 * KMAX;  // list entries per column: < KMAX above T, <= KMAX at T from each lane
   using St = Stages<DIRECT>;
   constexpr int TNS = St::kKeys;
@@ -238,7 +237,7 @@ __global__ __launch_bounds__(256, (KMAX <= 4 || (KMAX == 8 && !WS)) ? 4 : 1) voi
   const int kq = topk < c_q ? topk : c_q;  // spans to select for this column
 
   if constexpr (!WS) {
-    if (c_max <= kPackedSpans) {
+    if (c_max <= packed) {
       constexpr float kMasked = -3e38f, kNone = -3.3e38f;
       const int number = (1 << (32 - __builtin_clz(c_max > 32 ? c_max - 1 : 31))) - 1;  // the bits of a span's number
       int keep = ~number;
@@ -435,17 +434,29 @@ __global__ __launch_bounds__(256, (KMAX <= 4 || (KMAX == 8 && !WS)) ? 4 : 1) voi
   }
 }
 
+// Up to how many candidates a workgroup goes one walk.  Long runs of agreeing scores become eight times as frequent
+// with twice the spans (at 4096, one workgroup in 30), and each such workgroup pays both ways: of many workgroups one in
+// 30 does not show, but where all run at once the slowest is the call's time.  us, two walks -> one, top-8, mean of 8
+// inputs: 2048 spans, 128 workgroups 108 -> 86, 256: 108 -> 99, 512: 135 -> 145, 2000: 379 -> 315; 4096 spans, 32 workgroups
+// 196 -> 205, 256: 194 -> 276, 1000: 394 -> 440, 2000: 716 -> 661; at 1024 spans every grid gains (256: 63 -> 35).
+// Above 4096 spans too few bits of the score are left.
+constexpr int kFewWorkgroups = 1536;
+
+int one_walk_spans(int64_t grid) {
+  return grid > kFewWorkgroups ? 4096 : grid <= 256 ? 2048 : 1024;
+}
+
 template <int KMAX, bool WS, bool DIRECT>
 void launch_as(const Problem& pb, int grid, const void* Qs, const void* K, const void* Ks, int32_t* idx, float* scores,
                hipStream_t st) {
   hipLaunchKernelGGL((prefill_search_mfma_kernel<KMAX, WS, DIRECT>), dim3(grid), dim3(256), Stages<DIRECT>::kBytes, st,
                      static_cast<const bf16_t*>(Qs), static_cast<const bf16_t*>(K), static_cast<const bf16_t*>(Ks), idx,
-                     scores, pb.Lq, pb.q_pos0, pb.G, pb.S, pb.topk, pb.n, pb.qsh, pb.qst, pb.kvsh, pb.kvst);
+                     scores, pb.Lq, pb.q_pos0, pb.G, pb.S, pb.topk, pb.n, one_walk_spans(grid), pb.qsh, pb.qst, pb.kvsh, pb.kvst);
 }
 
-// Through registers -> direct, us, 32 heads.  One walk: 65536 rows x 256 spans top-4 160.5 -> 163.8, top-8 193.6 ->
-// 195.7, top-16 343 -> 297; 8000 x 125, top-12, 38.5 -> 35.4; top-32 621 -> 614 (no second instantiation for that);
-// 4000 x 62, top-8, 11.6 -> 12.3.  Two walks with scores: top-4 65536 x 256 376 -> 288, 20000 x 156, top-2, 68.9 -> 66.5,
+// Through registers -> direct, us, 32 heads.  One walk: 65536 rows x 256 spans top-4 165.7 -> 169.4, top-8 200.1 ->
+// 201.7, top-16 343 -> 302; 8000 x 125, top-12, 38.5 -> 35.7; top-32 621 -> 614 (no second instantiation for that);
+// 4000 x 62, top-8, 11.8 -> 12.7.  Two walks with scores: top-4 65536 x 256 376 -> 288, 20000 x 156, top-2, 68.9 -> 66.5,
 // 64 rows x 4096 spans 185 -> 169; top-8 419 -> 429, top-16 765 -> 773, top-32 2410 -> 2425.
 template <int KMAX>
 sl_status launch(const Problem& pb, const void* Qs, const void* K, const void* Ks, int32_t* idx,
@@ -466,7 +477,12 @@ bool prefill_search_mfma_supported(const Problem& pb) {
 
 sl_status prefill_search_mfma(const Problem& pb, const void* Qs, const void* K, const void* Ks,
                               int32_t* idx, float* scores, hipStream_t st) {
-  if (pb.topk <= 4) return launch<4>(pb, Qs, K, Ks, idx, scores, st);
+  // A list of four in lanes of five: one column in 16 whose fourth and fifth score agree has all five in one lane, which
+  // then cannot tell whether a sixth does.  Longer lanes' lists instead where one such workgroup is the call's time and one
+  // walk is taken: 500 rows x 1024 spans, top-4, two walks 55.4 us, lanes of five 57.6, of nine 27.4; x 2048 97, 113, 48.6.
+  const int64_t grid = pb.Hq * ((pb.Lq + TMQ - 1) / TMQ), spans = (pb.q_pos0 + pb.Lq - 1) / pb.S;
+  const bool longer = pb.topk == 4 && !scores && grid <= kFewWorkgroups && spans > 512 && spans <= one_walk_spans(grid);
+  if (pb.topk <= 4 && !longer) return launch<4>(pb, Qs, K, Ks, idx, scores, st);
   if (pb.topk <= 8) return launch<8>(pb, Qs, K, Ks, idx, scores, st);
   if (pb.topk <= 16) return launch<16>(pb, Qs, K, Ks, idx, scores, st);
   return launch<32>(pb, Qs, K, Ks, idx, scores, st);

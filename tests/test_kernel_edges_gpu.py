@@ -482,7 +482,8 @@ def test_prefill_search_stages_and_list_lengths(n, k, scores):
                 assert (j < 0 and x == -np.inf) or abs(x - q[h, row] @ kn[h // 2, j]) <= 1e-3
 
 
-@pytest.mark.parametrize("n,k", [(31, 5), (32, 8), (33, 1), (64, 16), (257, 8), (1025, 4), (4096, 8), (4097, 8), (300, 32)])
+@pytest.mark.parametrize("n,k", [(31, 5), (32, 8), (33, 1), (64, 16), (257, 8), (500, 4), (1025, 4), (2050, 4),
+                                 (4096, 8), (4097, 8), (300, 32)])
 @pytest.mark.parametrize("kind", ["levels", "pairs", "equal", "negative", "infinite", "nan"])
 def test_prefill_search_scores_that_agree_in_their_leading_bits(n, k, kind):
     """Scores that differ only in the bits whose place the span's number takes, in twos and in longer runs around the
@@ -674,3 +675,16 @@ def test_decode_steps_on_both_sides_of_one_launch(D, rows):
         O, LSE = B.sl_span_attention_decode(Q, K, V, idx, S, span_stride=A)
         torch.cuda.synchronize()
         check_attention(O, LSE, Q, K, V, idx, S, L - 1, 0.0, stride=A)
+
+
+@pytest.mark.parametrize("Lq", [6143, 6145, 8200])    # 1536 workgroups, more of them; 4097 candidates at the last rows
+@pytest.mark.parametrize("k", [4, 8])
+def test_prefill_search_of_many_candidates_at_both_grid_sizes(Lq, k):
+    """Few and many workgroups, which go different ways from 1025 and 2049 candidates on: the form that returns scores
+    computes the same ones and carries no numbers in them, so the selections are equal."""
+    L = 8200
+    Q, K, V = make(3300 + Lq + k, 32, 4, L, 128, torch.bfloat16, Lq=Lq)
+    idx = B.sl_span_search_prefill(Q, K, None, 2, k, q_pos0=L - Lq)
+    two, _ = B.sl_span_search_prefill(Q, K, None, 2, k, q_pos0=L - Lq, want_scores=True)
+    torch.cuda.synchronize()
+    assert torch.equal(idx, two)
