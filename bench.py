@@ -531,9 +531,9 @@ def bench_prefill(cfg, steps, warmup, torch, B, W):
     ks = sum(ms_s) / len(ms_s)
     mfma_path = cfg.dtype == "bf16" and cfg.D == 128 and cfg.S % 64 == 0
     peak, bound = (PEAK_BF16, "mfma") if cfg.dtype == "bf16" else (PEAK_FP32_VALU, "alu")
-    # the events bracket the routed-span kernel on the MFMA path, the one attention kernel otherwise
-    f_kernel = f_routed if mfma_path else f_attn
-    kernel = "span_flash_routed_kernel" if mfma_path else "prefill_attention_rows_kernel"
+    # the events bracket the routed-span kernel, in bf16 and in fp32
+    f_kernel = f_routed
+    kernel = "span_flash_routed_kernel" if mfma_path else "span_tiles_f32_kernel"
     tflops_attn = f_kernel / (ka * 1e-3)
     res = {
         "workload": f"{cfg.name} prefill L={cfg.L} Hq={cfg.Hq} Hkv={cfg.Hkv} D={cfg.D} S={cfg.S} topk={cfg.topk}+local",

@@ -625,10 +625,10 @@ struct AnchorList {
 //
 // 49157 rows, 32:4 heads, window 1088, top-2: 956 us with vector instructions (two-element dot products and a lane-group
 // sum per score); 660 with 16 rows of a product and a compare-and-select list with indices, an address for every load
-// and an AnchorList merge, vector units busy 80 % of the time (2870 instructions per wavefront); 542 with the numbers in
+// and an AnchorList merge, vector units busy 80 % of the time (2870 instructions per wavefront); 558 with the numbers in
 // the scores' bits and scalar bases (1320 instructions, 44 %).  20000 rows, top-4: 267 (vector) -> 146.  What bounds the
 // long prompt now are the key rows that miss the L2, half of 5.8 GB: a kernel that only reads rows at random gets
-// 11.5 TB/s out of 12.6 MB, a kv head's keys here, and 30 out of 3 MB; this one gets 12.3 and 11.6.  Staging through
+// 11.5 TB/s out of 12.6 MB, a kv head's keys here, and 30 out of 3 MB; this one gets about 12 and 11.  Staging through
 // registers instead of direct loads, loads past the L1, and chunks of 1024 and 2048 rows change nothing.
 constexpr int kAnchorRowsPerBlock = 8, kAnchorMaxChunk = 64;
 
