@@ -197,19 +197,24 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void span_tiles_f32_kernel(
           }
         mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
         mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-        const float m_new = fmaxf(m, mx);
+        // Rows whose scores are all -inf have no weight, whatever their values hold: m stays -inf and l 0 (a score
+        // that is NaN shows in l), and o starts anew behind them.
+        const float m_new = fmaxf(m, mx), base = m_new > -INFINITY ? m_new : 0.f;
         if (t0 > begin) {
-          const float corr = fast_exp2(m - m_new);
+          const bool some = m > -INFINITY;
+          const float corr = fast_exp2(m - base);
           l *= corr;
 #pragma unroll
-          for (int x = 0; x < NJ; ++x) o[x] *= corr;
+          for (int x = 0; x < NJ; ++x)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[x][e] = some ? o[x][e] * corr : 0.f;
         }
         m = m_new;
 #pragma unroll
         for (int t = 0; t < N; ++t)
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
-            s[t][e] = fast_exp2(s[t][e] - m);
+            s[t][e] = fast_exp2(s[t][e] - base);
             l += s[t][e];
           }
         // (16 kv rows at a time, for the same reason)
@@ -245,13 +250,16 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void span_tiles_f32_kernel(
     l += __shfl_xor(l, 16, 64);
     l += __shfl_xor(l, 32, 64);
     if (at < count) {
+      const bool some = m > -INFINITY;
       const int64_t rec = ((int64_t)h * Lq + r) * topk + slot;
       float* const po = part_o + rec * D;
 #pragma unroll
       for (int half = 0; half < D / 64; ++half)
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          const f32x4 w = {o[4 * half][e], o[4 * half + 1][e], o[4 * half + 2][e], o[4 * half + 3][e]};
+          f32x4 w;
+#pragma unroll
+          for (int dt = 0; dt < 4; ++dt) w[dt] = some ? o[4 * half + dt][e] : 0.f;
           *reinterpret_cast<f32x4*>(po + 64 * half + 16 * g + 4 * e) = w;
         }
       if (g == 0) part_ml[rec] = make_float2(m, l);
@@ -328,7 +336,7 @@ __device__ void window_row(const WindowArgs& a, int h, int64_t r, int lane) {
       float f[4];
       Elem<float>::unpack(b, f);
       const float M = fmaxf(st.m, a.x);
-      const float ws = st.m > -INFINITY ? fast_exp2(st.m - M) : 0.f, wp = fast_exp2(a.x - M);
+      const float ws = st.m > -INFINITY ? fast_exp2(st.m - M) : 0.f, wp = a.x > -INFINITY ? fast_exp2(a.x - M) : 0.f;
       st.m = M;
       st.l = st.l * ws + a.y * wp;
 #pragma unroll
@@ -548,7 +556,8 @@ __global__ __launch_bounds__(256, 2) void window_f32_kernel(const WindowArgs a) 
 #pragma unroll
     for (int u = 0; u < B; ++u) {
       if (!ok[u]) continue;
-      const float M = fmaxf(m, ml[u].x), ww = fast_exp2(m - M), wp = fast_exp2(ml[u].x - M);
+      const float M = fmaxf(m, ml[u].x), at = COMBINED || M > -INFINITY ? M : 0.f;  // (joint: a list may begin with -inf alone)
+      const float ww = fast_exp2(m - at), wp = fast_exp2(ml[u].x - at);
       if constexpr (!COMBINED) {
         m = M;
         l = l * ww + ml[u].y * wp;

@@ -602,6 +602,55 @@ def test_fp32_spans_keep_what_is_not_finite_to_the_rows_that_attend_it(which, ba
     assert bool((~finite).any())
 
 
+MASKED = [
+    # D  S    first and last masked key of the span
+    (64, 64, 0, 64),        # a whole span of one stage
+    (64, 142, 0, 80),       # the first of two stages (80 rows at D = 64), exactly
+    (64, 142, 0, 79), (64, 142, 0, 142), (64, 142, 80, 142),
+    (128, 65, 0, 64),       # ... (64 at D = 128): one key is left
+    (128, 65, 0, 65),
+]
+
+
+@pytest.mark.parametrize("D,S,lo,hi,form,how", [(*m, f, how) for m in MASKED for f in ("joint", "gated") for how in ("masked", "overflow")]
+                         + [(*m, "gated", "values") for m in MASKED if m[2:] == (0, m[1])])
+def test_fp32_spans_whose_scores_are_all_minus_infinity(D, S, lo, hi, form, how):
+    """Keys masked with -inf in one channel, or finite ones whose products overflow to it, or masked ones beside values
+    that are infinite (in the gated form, where the row form too meets a span's values by themselves): what is left of the
+    span counts, a span of which nothing is left has no weight, and no row becomes NaN by it; in slots and in windows;
+    against the row-stationary kernels.  The sums' bound is that of test_fp32_spans_on_the_matrix_cores."""
+    Hq, Hkv, L, k, span = 8, 2, 4200, 4, 7
+    q0 = span * S + S // 2      # the first rows' window is the span's, and in the middle of it
+    Q, K, V = make(2150 + S, Hq, Hkv, L, D, torch.float32, Lq=L - q0, scale=1.0 if form == "joint" else 0.35)
+    Q[:, :, 5] = Q[:, :, 5].abs() + 0.1
+    K[:, :, 5] = 0
+    idx, sc = B.sl_span_search_prefill(Q, K, None, S, k, q_pos0=q0, want_scores=True)
+    lists = (idx == span).any(dim=2)
+    takes = ~lists & ((q0 + torch.arange(L - q0, device=DEV)) // S > span)[None, :]
+    takes[:, 1::2] = False
+    takes[0] = False
+    for h in range(Hq):         # in every slot, the first and the last among them
+        idx[h, :, h % k] = torch.where(takes[h], span, idx[h, :, h % k])
+    assert takes_matrix_cores(Q, K, S, k, q0)
+    at = slice(S * span + lo, S * span + hi)
+    if how == "overflow":
+        Q[:, :, 5] *= 1e20
+        K[:, at, 5] = -1e22
+    else:
+        K[:, at, 5] = float("-inf")
+    if how == "values":
+        V[:, at, 3] = float("inf")
+    got, want = span_rows(Q, K, V, idx, None if form == "joint" else sc, S, q0, 0)
+    torch.cuda.synchronize()
+    for x, y in zip(got, want):
+        ok = torch.isfinite(y)
+        assert torch.equal(torch.isfinite(x), ok)
+        assert float(torch.where(ok, x - y, 0.0).abs().max()) <= 1.6e-5
+    later = slice(S, None)      # rows whose window holds none of the masked keys
+    assert bool(torch.isfinite(got[0][:, later]).all())
+    assert bool(takes[:, later].any()) and bool((idx[:, later] == span).any())
+
+
 @pytest.mark.parametrize("Hq,Hkv", [(1, 1), (3, 1), (6, 1), (12, 2), (8, 1), (16, 1)])
 @pytest.mark.parametrize("Lq,S", [(1, 64), (15, 64), (17, 192), (129, 128), (200, 77)])
 def test_window_tiles_of_several_heads(Hq, Hkv, Lq, S):
