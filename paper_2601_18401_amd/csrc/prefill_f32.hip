@@ -27,7 +27,7 @@ namespace {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int kListItems = 2048;  // query heads of a group x rows of a chunk: a row lists a span once
+constexpr int kListItems = 2048;  // query heads of a group x rows of a chunk at most: a row has one place (see the look through)
 
 // Which workgroup takes what.  Rows at position p choose topk of p / A spans, so the further back a row stands the more
 // rows it takes for a span to find a tile's worth: the rows go in segments over which the position grows by half (at most),
@@ -111,25 +111,43 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void span_tiles_f32_kernel(
   if (tid == 0) s_count = 0;
   __syncthreads();
   const int per_head = (int)(rb - ra) * topk;
-  for (int hl = 0; hl < G; ++hl) {
-    const int32_t* const list = idx + ((int64_t)(kv * G + hl) * Lq + ra) * topk;
-    for (int e0 = tid; e0 < per_head; e0 += 1024) {
-      int v[4];
+  // A row that lists the span more than once (its own result is anyone's guess) must not cost another row its place:
+  // where the places do not suffice, only the first such slot of a row takes one, and its partial goes to the others too.
+  auto look_through = [&](auto first_only) {
+    for (int hl = 0; hl < G; ++hl) {
+      const int32_t* const list = idx + ((int64_t)(kv * G + hl) * Lq + ra) * topk;
+      for (int e0 = tid; e0 < per_head; e0 += 1024) {
+        int v[4];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) v[u] = e0 + 256 * u < per_head ? list[e0 + 256 * u] : -1;
+        for (int u = 0; u < 4; ++u) v[u] = e0 + 256 * u < per_head ? list[e0 + 256 * u] : -1;
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        if (v[u] != j) continue;
-        const int r = (e0 + 256 * u) / topk, slot = (e0 + 256 * u) % topk;
-        if (end > q_pos0 + ra + r) continue;  // not a candidate of this row
-        const int at = atomicAdd(&s_count, 1);
-        if (at < kListItems) s_list[at] = (hl * chunk_rows + r) << 5 | slot;  // (the order does not matter: a row's arithmetic is its own)
+        for (int u = 0; u < 4; ++u) {
+          if (v[u] != j) continue;
+          const int r = (e0 + 256 * u) / topk, slot = (e0 + 256 * u) % topk;
+          if (end > q_pos0 + ra + r) continue;  // not a candidate of this row
+          if constexpr (decltype(first_only)::value) {
+            bool again = false;
+            for (int s = 0; s < slot; ++s) again |= list[r * topk + s] == j;
+            if (again) continue;
+          }
+          const int at = atomicAdd(&s_count, 1);
+          if (at < kListItems) s_list[at] = (hl * chunk_rows + r) << 5 | slot;  // (the order does not matter: a row's arithmetic is its own)
+        }
       }
     }
-  }
+  };
+  look_through(std::false_type{});
   put();
   __syncthreads();
-  const int count = min(s_count, kListItems), tiles = (count + 15) / 16;
+  const bool repeated = s_count > kListItems;
+  if (repeated) {
+    __syncthreads();
+    if (tid == 0) s_count = 0;
+    __syncthreads();
+    look_through(std::true_type{});
+    __syncthreads();
+  }
+  const int count = s_count, tiles = (count + 15) / 16;
   if (count == 0) return;
 
 #pragma unroll 1
@@ -263,6 +281,21 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void span_tiles_f32_kernel(
           *reinterpret_cast<f32x4*>(po + 64 * half + 16 * g + 4 * e) = w;
         }
       if (g == 0) part_ml[rec] = make_float2(m, l);
+    }
+  }
+  if (!repeated) return;
+#pragma unroll 1
+  for (int at = wave * 16 + i16; at < count; at += 64) {  // a lane copies what it has written
+    const int item = s_list[at], slot = item & 31;
+    const int64_t rec = ((int64_t)(kv * G + (item >> 5) / chunk_rows) * Lq + ra + (item >> 5) % chunk_rows) * topk + slot;
+    for (int s = 1; s < topk - slot; ++s) {
+      if (idx[rec + s] != j) continue;
+#pragma unroll
+      for (int x = 0; x < NJ; ++x) {
+        const int at_d = 64 * (x / 4) + 16 * g + 4 * (x % 4);
+        *reinterpret_cast<f32x4*>(part_o + (rec + s) * D + at_d) = *reinterpret_cast<const f32x4*>(part_o + rec * D + at_d);
+      }
+      if (g == 0) part_ml[rec + s] = part_ml[rec];
     }
   }
 }
@@ -604,7 +637,7 @@ __global__ __launch_bounds__(256, 2) void window_f32_kernel(const WindowArgs a) 
 // stages the span.
 F32Plan f32_plan(const Problem& pb) {
   F32Plan plan;
-  const int64_t most = kListItems / pb.G;  // a row lists a span once
+  const int64_t most = kListItems / pb.G;  // a place for every row
   for (int64_t target = 64;; target *= 2) {
     plan.count = 0;
     plan.blocks = 0;

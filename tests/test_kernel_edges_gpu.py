@@ -651,6 +651,37 @@ def test_fp32_spans_whose_scores_are_all_minus_infinity(D, S, lo, hi, form, how)
     assert bool(takes[:, later].any()) and bool((idx[:, later] == span).any())
 
 
+@pytest.mark.parametrize("form", ["joint", "gated"])
+@pytest.mark.parametrize("repeats", [0, 1, 4])
+def test_fp32_rows_that_list_a_span_twice_cost_no_other_row_its_span(repeats, form):
+    """Chunks whose every row lists one span fill its list of rows to the last place; some rows that list it in several
+    slots (their own result is unspecified) leave the others as they are, in a workspace that holds NaN."""
+    Hq, Hkv, L, D, S, k, Lq = 8, 1, 64 * 264, 64, 64, 4, 512     # two chunks of 256 rows x 8 heads
+    q0 = L - Lq
+    Q, K, V = make(2170, Hq, Hkv, L, D, torch.float32, Lq=Lq, scale=1.0 if form == "joint" else 0.35)
+    g = torch.Generator().manual_seed(repeats)
+    idx = torch.stack([torch.randperm(250, generator=g)[:k] for _ in range(Hq * Lq)]).to(torch.int32).reshape(Hq, Lq, k)
+    idx = torch.where(idx == 77, 251, idx)
+    idx[:, :, 2] = 77
+    bad = torch.zeros((Hq, Lq), dtype=torch.bool)
+    if repeats:
+        bad[:, 100::200] = True
+        idx[:, 100::200, :repeats] = 77
+    idx, bad = idx.to(DEV), bad.to(DEV)
+    sc = None if form == "joint" else torch.randn((Hq, Lq, k), generator=g).to(DEV)
+    assert takes_matrix_cores(Q, K, S, k, q0)
+    ws = B.Workspace()
+    ws.get(B.workspace_bytes(B.make_params(Q, K, S, k, q0), B.OP_ATTENTION_PREFILL))
+    ws.buf.fill_(255)
+    if form == "joint":
+        got, want = B.sl_span_attention_prefill(Q, K, V, idx, S, q_pos0=q0, ws=ws)[0], row_form(Q, K, V, idx, None, S, q0)[0]
+    else:
+        got, want = B.sl_span_attention_combined_prefill(Q, K, V, idx, sc, S, q_pos0=q0, ws=ws), row_form(Q, K, V, idx, sc, S, q0)
+    torch.cuda.synchronize()
+    assert bool(torch.isfinite(got).all())
+    assert float((got - want)[~bad].abs().max()) <= 1.6e-5     # the bound of test_fp32_spans_on_the_matrix_cores
+
+
 @pytest.mark.parametrize("Hq,Hkv", [(1, 1), (3, 1), (6, 1), (12, 2), (8, 1), (16, 1)])
 @pytest.mark.parametrize("Lq,S", [(1, 64), (15, 64), (17, 192), (129, 128), (200, 77)])
 def test_window_tiles_of_several_heads(Hq, Hkv, Lq, S):
