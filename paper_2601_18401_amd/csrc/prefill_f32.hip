@@ -715,18 +715,65 @@ sl_status f32_pass(const Problem& pb, const float* Q, const float* K, const floa
   return hipGetLastError() == hipSuccess ? SL_OK : SL_ERR_LAUNCH;
 }
 
-// Estimated us of the two forms; the call takes the smaller.  Row-stationary: one row's own chain of loads, and 14.5 ps
-// per row and key (D = 64) with about 13 keys' worth of latency per slot.  This form: two launches and their chains, the
-// workgroups (list, stage), the products.  Measured, D = 64, 4 heads, spans of 64, top-4 unless said otherwise, rows ->
-// this form: 4096 rows 82 -> 45, top-2 52 -> 34, D = 128 165 -> 77; 1500 rows 34 -> 26; 6000 rows, spans of 78, 139 -> 70;
-// behind 4096 tokens 512 rows 23 -> 20, 64 rows 18.6 -> 16 (taken by the rows), 8 rows 12.3 -> 15; 64 rows, top-1,
-// 6.4 -> 13.9; 400 rows, spans of 16, 6.4 -> 15; 512 rows behind 30000 tokens in spans of 8, top-8, 14.5 -> 94; 64 rows
-// behind 20000 in spans of 142, top-8, 69 -> 41.
+// Estimated us of the two forms; the call takes this one where it is the faster.  Fitted to 6500 shapes of 1 to 128 heads, 1
+// to 100000 rows, spans of 1 to 2048 tokens, top-1 to top-32, both forms measured: each sum is within a fifth of the time
+// for eight shapes in ten.  A call of few rows is one chain of latencies, and there the estimates err most, so it needs a
+// lead.  Of the 6500, this form runs 2807, 94 of them more than 2 % and 50 more than 10 % slower than by rows; all 6500
+// take 1.0 % longer than the faster form each, by rows throughout 45 %.  (The size of the scratch is asked for without
+// saying which softmax it is for, so the rule does not look at that: the gated rows take 0.4 us a slot more.)
+// What counts, us, rows -> this form (heads, D, rows of a prompt of L, spans, top-k):
+//   the lists: a workgroup looks through those of its whole chunk, for every span of it: 64:4, 128, 5986 of 19015, spans of
+//     4, top-24 3530 -> 32300; 64:4, 128, 1372, spans of 1, top-32 673 -> 3080; 8:1, 128, 300 of 1241, spans of 6 21 -> 64;
+//   the window: one wavefront takes 16 rows' keys, 64 (D = 128: 32) at a time, one behind the other: 2:1, 64, 27 of 1223,
+//     spans of 896, top-1 38 -> 76; 16:1, 128, 16 of 2111, spans of 1432, top-12 131 -> 234 (a span of several stages, too);
+//   a wavefront of the other form has all slots' keys behind one another, and past the L2 every row reads its own from
+//     memory: 8:4, 128, 1 of 25613, spans of 982, top-12 1250 -> 129; 64:8, 128, 1000 of 59212, 64, top-12 6590 -> 1350;
+//   4:4, 64, 4096, 64, top-4 82 -> 46, top-8 141 -> 62, D = 128 165 -> 79; 32:4, 128, 1024 of 65536, 256, top-8 8400 -> 716.
 bool f32_is_faster(const Problem& pb, const F32Plan& plan) {
-  const double rows = (double)pb.Hq * pb.Lq, d = pb.D / 64.0, keys = (double)pb.topk * pb.S + pb.A / 2;
-  const double by_rows = 4 + 0.03 * keys + 1.45e-5 * d * rows * (keys + 13.0 * pb.topk);
-  const double by_tiles = 13 + (double)plan.blocks * pb.Hkv * (4e-3 + 1e-6 * pb.S * pb.D) + 6.2e-8 * rows * pb.topk * pb.S * pb.D;
-  return by_tiles < by_rows;
+  auto up = [](int64_t a, int64_t b) { return (a + b - 1) / b; };
+  const int64_t q0 = pb.q_pos0, first = q0 / pb.A, last = (q0 + pb.Lq - 1) / pb.A;
+  const double rows = (double)pb.Hq * pb.Lq, d = pb.D / 64, k = pb.topk, key = pb.D / 4096.0;
+  // slots in use: the most, and a row's mean (the candidates grow evenly until there are topk)
+  const double most = last < k ? last : k;
+  double slots = k;
+  if (last <= k) slots = 0.5 * (first + last);
+  else if (first < k) slots = k - (k * pb.A - q0) / (double)pb.Lq * (k - 0.5 * (first + k));
+  // window lengths: the longest, and their mean
+  const int64_t at = q0 % pb.A, head = pb.Lq < pb.A - at ? pb.Lq : pb.A - at, rest = pb.Lq - head;
+  const int64_t longest = rest >= pb.A ? pb.A : at + head > rest ? at + head : rest, part = rest % pb.A;
+  const double window = (head * (at + 0.5 * (head + 1)) + 0.5 * (rest - part) * (pb.A + 1) + 0.5 * part * (part + 1)) / pb.Lq;
+
+  const int64_t at_once = 1024 / pb.D;  // keys that a wavefront of the row-stationary kernel takes at a time
+  const double keys = slots * pb.S + window, group = (double)pb.G * pb.Lq;  // keys of a row, rows of a kv head
+  // reads that miss the 4 MB of an XCD's L2: keys read for the first time there, and what the kv heads in flight do not leave
+  const double visible = (double)(q0 + pb.Lq), in_flight = 8192 / group, heads = in_flight < 1 ? 1 : in_flight > pb.Hkv ? pb.Hkv : in_flight;
+  const double fresh = 8 * visible / (group * keys), evicted = 1 - (4 << 20) / (heads * visible * pb.D * 8);
+  const double miss = fresh > 1 || evicted > 1 ? 1 : fresh > evicted ? fresh : evicted;
+  const double chain_rows = most * up(pb.S, at_once) + up(longest, at_once);
+  const double by_rows = 3.5 + (0.387 + 0.159 * miss) * chain_rows + 0.2 * most +
+                         rows * (2.31e-4 * (slots * up(pb.S, at_once) + window / at_once + 0.5) + 0.95e-4 * slots +
+                                 1.77e-3 * slots * pb.S * key * miss);
+
+  const int64_t stage = pb.D == 64 ? F32Tiles<64>::kRows : F32Tiles<128>::kRows, over = pb.S % stage, wkeys = pb.D == 64 ? 64 : 32;
+  const double computed = pb.S - over + (over == 0 ? 0 : over <= 16 ? 16 : over <= 48 ? 48 : over <= 64 ? 64 : 80);
+  double scan = 0, chain = 0, scans = 0, tiles = 0;
+  for (int x = 0; x < plan.count; ++x) {
+    const F32Segment& g = plan.seg[x];
+    const double blocks = (x + 1 < plan.count ? plan.seg[x + 1].block : (double)plan.blocks) - g.block;
+    const double looks = (double)pb.G * up((int64_t)g.rows * pb.topk, 1024);
+    const double c = (double)((q0 + g.row) / pb.A), of = c < 1 ? 1 : c;
+    const double items = (double)pb.G * g.rows * (of < k ? 1 : k / of);
+    const double many = up(pb.S, stage) * up(up((int64_t)(items + 2 * std::sqrt(items)) + 1, 16), 4);
+    scan = looks > scan ? looks : scan;
+    chain = many > chain ? many : chain;
+    scans += blocks * looks;
+    tiles += blocks * (items / 16 + 0.5);
+  }
+  const double waves = (double)pb.Hq * up(pb.Lq, 16);
+  const double by_tiles = 5.3 + 5.18 * up(longest, wkeys) + 2.61 * up((int64_t)most, pb.D == 64 ? 4 : 2) + 0.273 * scan + 1.68 * d * chain +
+                          waves * d * (7.9e-4 * d * ((window + 8) / wkeys + 0.5) + 2.54e-3 * slots) +
+                          pb.Hkv * (6.6e-4 * scans + 7e-3 * plan.blocks * pb.S * key + 7.3e-4 * tiles * computed * key);
+  return (rows < 4096 ? 1.1 * by_tiles + 1 : by_tiles) < by_rows;
 }
 
 }  // namespace

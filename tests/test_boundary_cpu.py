@@ -218,3 +218,28 @@ def test_workloads_are_seeded_and_shaped():
     d = W.generate(W.CONFIGS["C3"].scaled(L=8192, S=128), n_queries=3)
     assert d["Q"].shape == (3, 32, 1, 128)
     assert [W.CONFIGS[c].n_spans for c in ("C1", "C2", "C3", "C4", "C5")] == [64, 256, 1024, 512, 2560]
+
+
+@pytest.mark.parametrize("Hq,Hkv,D,L,Lq,S,k,rows_us,tiles_us", [
+    (64, 4, 128, 19015, 5986, 4, 24, 3530, 32329),      # every span's workgroups look through all lists
+    (64, 4, 128, 1372, 1372, 1, 32, 673, 3080),
+    (8, 1, 128, 1241, 300, 6, 16, 21.5, 64),
+    (16, 2, 128, 6766, 1726, 5, 32, 316, 1198),
+    (2, 1, 64, 1223, 27, 896, 1, 38, 76),               # one wavefront takes 16 rows' windows
+    (1, 1, 128, 1659, 809, 1410, 32, 105, 308),
+    (16, 1, 128, 2111, 16, 1432, 12, 131, 234),
+    (4, 4, 64, 4096, 64, 64, 1, 6.4, 13.9),
+    (4, 4, 64, 4096, 4096, 64, 4, 82, 46),
+    (4, 4, 128, 4096, 4096, 64, 8, 330, 114),
+    (4, 4, 64, 1500, 1500, 64, 4, 34, 26),
+    (32, 4, 128, 65536, 1024, 256, 8, 8400, 716),
+    (32, 4, 128, 85840, 1000, 64, 12, 3548, 912),
+    (12, 2, 128, 6734, 6734, 576, 1, 2388, 690),
+    (64, 4, 128, 60195, 300, 64, 16, 2675, 617),
+])
+def test_fp32_prefill_takes_the_form_that_measured_faster(Hq, Hkv, D, L, Lq, S, k, rows_us, tiles_us):
+    """Shapes at which one form takes at least 1.3 times as long as the other, both measured on an MI355X: the call asks
+    for scratch where the matrix-core form is the faster one, and for none where the row-stationary form is."""
+    assert max(rows_us, tiles_us) >= 1.3 * min(rows_us, tiles_us)
+    p = good(L=L, Lq=Lq, q_pos0=L - Lq, Hq=Hq, Hkv=Hkv, D=D, S=S, topk=k, dtype=B.SL_F32)
+    assert (B.workspace_bytes(p, B.OP_ATTENTION_PREFILL) > 0) == (tiles_us < rows_us)
