@@ -299,10 +299,12 @@ def _attention(fn_name, op, Q, K, V, idx, S, q_pos0, scale, ws, prof, out, span_
         LSE = torch.empty((Hq, Lq), dtype=torch.float32, device=Q.device)
     else:
         O, LSE = out
-    if op == OP_ATTENTION_PREFILL:
-        wptr, wbytes, held = _prefill_scratch(p, ws, Q.device)
-    else:
+    if op != OP_ATTENTION_PREFILL:
         wptr, wbytes = _ws(ws).get(workspace_bytes(p, op))
+    elif p.dtype == SL_F32 and 0 < p.span_stride < p.S:  # overlapping spans in one softmax go row by row in fp32
+        wptr, wbytes, held = None, 0, None
+    else:
+        wptr, wbytes, held = _prefill_scratch(p, ws, Q.device)
     _arm(prof)
     st = getattr(lib, fn_name)(ctypes.byref(p), _ptr(Q), _ptr(K), _ptr(V), _ptr(idx), _ptr(O), _ptr(LSE),
                                wptr, wbytes, _stream())

@@ -682,6 +682,28 @@ def test_fp32_rows_that_list_a_span_twice_cost_no_other_row_its_span(repeats, fo
     assert float((got - want)[~bad].abs().max()) <= 1.6e-5     # the bound of test_fp32_spans_on_the_matrix_cores
 
 
+def test_fp32_overlapping_spans_in_one_softmax_take_no_scratch():
+    """They go through the row-stationary kernels whatever scratch there is, so the call allocates its outputs only; the
+    gated form of the same shape, which does not, allocates partials."""
+    Hq, Hkv, L, D, S, A, k = 8, 1, 4000, 64, 128, 64, 8
+    Q, K, V = make(2180, Hq, Hkv, L, D, torch.float32, scale=0.35)
+    idx, sc = B.sl_span_search_prefill(Q, K, None, A, k, want_scores=True)
+    sc = torch.where(torch.isfinite(sc), sc, 0.0)
+    assert takes_matrix_cores(Q, K, S, k, 0, A)
+    partials = Hq * L * k * D * 4
+    grown = []
+    for call in (lambda: B.sl_span_attention_prefill(Q, K, V, idx, S, span_stride=A),
+                 lambda: B.sl_span_attention_combined_prefill(Q, K, V, idx, sc, S, span_stride=A)):
+        torch.cuda.synchronize()
+        torch.cuda.reset_peak_memory_stats()
+        before = torch.cuda.memory_allocated()
+        out = call()
+        torch.cuda.synchronize()
+        grown.append(torch.cuda.max_memory_allocated() - before)
+        del out
+    assert grown[0] < 2 * Hq * L * (D + 1) * 4 < partials < grown[1]
+
+
 @pytest.mark.parametrize("Hq,Hkv", [(1, 1), (3, 1), (6, 1), (12, 2), (8, 1), (16, 1)])
 @pytest.mark.parametrize("Lq,S", [(1, 64), (15, 64), (17, 192), (129, 128), (200, 77)])
 def test_window_tiles_of_several_heads(Hq, Hkv, Lq, S):
