@@ -922,9 +922,18 @@ template <typename T, int D>
 void launch_short(const Problem& pb, const void* Q, const void* K, const void* V, const int32_t* idx, void* O, float* LSE,
                   hipStream_t st) {
   const int rows = RowLayout<T, D>::RPW * 8;
-  hipLaunchKernelGGL((decode_short_kernel<T, D>), dim3(pb.Hq), dim3(kShortThreads), 0, st, static_cast<const T*>(Q),
-                     static_cast<const T*>(K), static_cast<const T*>(V), idx, static_cast<T*>(O), LSE, pb.q_pos0, pb.G,
-                     pb.S, pb.A, pb.topk, (pb.S + rows - 1) / rows, pb.scale * kLog2e, pb.qsh, pb.kvsh, pb.kvst);
+  const int parts = (pb.S + rows - 1) / rows;
+  const float scale_log2e = pb.scale * kLog2e;
+  if (pb.prof_start) {  // the launch carries the events, as in launch_split_u
+    hipExtLaunchKernelGGL((decode_short_kernel<T, D>), dim3(pb.Hq), dim3(kShortThreads), 0, st, pb.prof_start,
+                          pb.prof_stop, 0, static_cast<const T*>(Q), static_cast<const T*>(K), static_cast<const T*>(V),
+                          idx, static_cast<T*>(O), LSE, pb.q_pos0, pb.G, pb.S, pb.A, pb.topk, parts, scale_log2e, pb.qsh,
+                          pb.kvsh, pb.kvst);
+  } else {
+    hipLaunchKernelGGL((decode_short_kernel<T, D>), dim3(pb.Hq), dim3(kShortThreads), 0, st, static_cast<const T*>(Q),
+                       static_cast<const T*>(K), static_cast<const T*>(V), idx, static_cast<T*>(O), LSE, pb.q_pos0,
+                       pb.G, pb.S, pb.A, pb.topk, parts, scale_log2e, pb.qsh, pb.kvsh, pb.kvst);
+  }
 }
 
 template <typename T, int D>
@@ -932,9 +941,7 @@ sl_status launch_decode(const Problem& pb, const void* Q, const void* K, const v
                         const int32_t* idx, void* O, float* LSE, void* ws, hipStream_t st) {
   if constexpr (sizeof(T) == 2) {
     if (decode_is_short(pb)) {
-      if (pb.prof_start) (void)hipEventRecord(pb.prof_start, st);
       launch_short<T, D>(pb, Q, K, V, idx, O, LSE, st);
-      if (pb.prof_stop) (void)hipEventRecord(pb.prof_stop, st);
       return hipGetLastError() == hipSuccess ? SL_OK : SL_ERR_LAUNCH;
     }
   }
