@@ -40,13 +40,12 @@ typedef float f32x8 __attribute__((ext_vector_type(8)));
 
 constexpr int TG = 128;            // rows of one wavefront group (4 wavefronts x 32 columns)
 constexpr int TN = 64;             // kv positions per staged tile
-// ... and of the kernels with fp32 weights.  At D = 64 tiles of 32 leave room (registers, LDS) for a third workgroup per
+// Of the kernels with fp32 weights, too; at D = 64 tiles of 32 leave room (registers, LDS) for a third workgroup per
 // compute unit and end closer to a span's end: 20011 rows in spans of 142 1213 -> 1098 us, 8000 in spans of 90, top-4, 260 ->
-// 221, 8 rows behind 60000 tokens in spans of 245 57.2 -> 58.1.  At D = 128 the registers of a third do not suffice: 2000 ->
+// 221 (short_routed_tiles: not where the tiles are few).  At D = 128 the registers of a third do not suffice: 2000 ->
 // 2164.  (Nor does it help there to ask for the next tile's first stages, queries and record before a tile's output leaves,
 // over the stages of its last kv tile: 1929 -> 2015.)
-constexpr int fine_tile(int d) { return d == 64 ? 32 : 64; }
-constexpr int fine_blocks(int d) { return d == 64 ? 3 : 2; }  // workgroups per compute unit
+constexpr int fine_blocks(int tile) { return tile == 32 ? 3 : 2; }  // workgroups per compute unit
 constexpr int HD = 128;            // head dimension of the kernels with bf16 weights
 
 // LDS of the flash kernels (dynamic).  Main loop: stages of the V tile and of the K tile, filled
@@ -536,7 +535,7 @@ __device__ __forceinline__ void flush_routed_output(char* lds, int grp, int w4, 
 // FINE: the softmax weights keep fp32 precision: each is split into three bf16 parts, which hold the 24 bits of its
 // mantissa between them, and V is multiplied with all three; the row sum is taken over the unsplit weights, partials
 // are written in fp32, and the output of a tile goes to HBM before the next one starts.
-template <int NG, bool LOCAL, bool FUSED, bool CLIP, int D = HD, bool FINE = false, typename RequestNext,
+template <int NG, bool LOCAL, bool FUSED, bool CLIP, int D = HD, bool FINE = false, int TT = TN, typename RequestNext,
           typename DescribeNext>
 __device__ __forceinline__ void flash_tile(const FlashArgs& a, char* lds, const TileDesc& cur,
                                            TileDesc& next, bool has_next, RequestNext&& request_next,
@@ -548,7 +547,6 @@ __device__ __forceinline__ void flash_tile(const FlashArgs& a, char* lds, const 
   const int srow = w4 * 32 + qc;             // row inside the group's 128-row half tile
   static_assert(NG == 1 || !FINE, "fp32 partials leave with their tile: one group's output region");
   constexpr bool kMasked = LOCAL || CLIP;
-  constexpr int TT = FINE ? fine_tile(D) : TN;  // kv positions per tile
   using Lds = FlashLds<NG, D, TT>;
   constexpr int kStageElems = Lds::kStageElems;
   constexpr int PPR = D / 8, RPB = 64 / PPR;  // 16-byte pieces per staged row, rows per 1 KB block
@@ -967,10 +965,10 @@ __device__ __forceinline__ void flash_tile(const FlashArgs& a, char* lds, const 
 // FINE (with CLIP): fp32 weights and partials, spans of any length at any offset; a row's range is its whole
 // span unless a->clip says that spans of a row overlap in one softmax.  Tiles of 128 rows, two workgroups per
 // compute unit: one's tile ends run beside the other's kv loop.
-template <bool CLIP, int D = HD, bool FINE = false, int NG = FINE ? 1 : 2>
-__global__ __launch_bounds__(NG * 256, NG == 2 ? 1 : FINE ? fine_blocks(D) : 2) void span_flash_routed_kernel(
+template <bool CLIP, int D = HD, bool FINE = false, int TT = TN, int NG = FINE ? 1 : 2>
+__global__ __launch_bounds__(NG * 256, NG == 2 ? 1 : FINE ? fine_blocks(TT) : 2) void span_flash_routed_kernel(
     const FlashArgs a) {
-  using Lds = FlashLds<NG, D, FINE ? fine_tile(D) : TN>;
+  using Lds = FlashLds<NG, D, TT>;
   constexpr int TM = Lds::kRows;
   extern __shared__ __align__(16) char lds[];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -1016,7 +1014,7 @@ __global__ __launch_bounds__(NG * 256, NG == 2 ? 1 : FINE ? fine_blocks(D) : 2) 
   if constexpr (NG == 1) {
     for (int64_t t = t_begin; t < t_end; t += NWL) {
       TileDesc cur = describe(a.tile_info[t], a.items[t * TM + qrow]), unused = cur;
-      flash_tile<1, false, false, CLIP, D, FINE>(a, lds, cur, unused, false, [] {}, [&] { return cur; }, carry);
+      flash_tile<1, false, false, CLIP, D, FINE, TT>(a, lds, cur, unused, false, [] {}, [&] { return cur; }, carry);
       __syncthreads();  // the next tile's stages lie over the output slices of all wavefronts
     }
   } else {
@@ -1182,8 +1180,8 @@ inline unsigned local_grid(int64_t Lq, int S, int Hkv, int G) {
 // FUSED = true (joint softmax, topk <= 8): merges the row's routed partials in the epilogue and
 // writes the final output, which takes the merge's HBM traffic off the critical path of a
 // separate kernel and saves the window partial's round trip.
-template <bool FUSED, int D = HD, bool FINE = false>
-__global__ __launch_bounds__(FlashLds<1>::kThreads, FINE ? fine_blocks(D) : 2) void span_flash_local_kernel(const FlashArgs a) {
+template <bool FUSED, int D = HD, bool FINE = false, int TT = TN>
+__global__ __launch_bounds__(FlashLds<1>::kThreads, FINE ? fine_blocks(TT) : 2) void span_flash_local_kernel(const FlashArgs a) {
   extern __shared__ __align__(16) char lds[];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int qrow = wave * 32 + (lane & 31);
@@ -1229,7 +1227,7 @@ __global__ __launch_bounds__(FlashLds<1>::kThreads, FINE ? fine_blocks(D) : 2) v
   carry.primed = false;
   carry.pending = false;
   TileDesc unused = d;
-  flash_tile<1, true, FUSED, false, D, FINE>(a, lds, d, unused, false, [] {}, [&] { return d; }, carry);
+  flash_tile<1, true, FUSED, false, D, FINE, TT>(a, lds, d, unused, false, [] {}, [&] { return d; }, carry);
 }
 
 // ------------------------------------------------------------------ merge
@@ -1652,6 +1650,12 @@ sl_status prefill_attention_mfma(const Problem& pb, const void* Q, const void* K
 // Calls without a workspace, or with one too small, take the row-stationary kernels as before.
 namespace {
 
+// Tiles that the routed part has at most: one that is not full for every span with a row, and the full ones.
+double fine_tiles(const Problem& pb) {
+  const double items = (double)pb.Hq * pb.Lq * pb.topk;
+  return fmin(items, (double)pb.Hkv * pb.n) + items / TG;
+}
+
 // Estimated us of the two forms; the call takes the smaller.  Row-stationary: 0.02 ns per row and key, with
 // about 13 keys' worth of latency per slot, and no less than one row's own chain of loads.  This form: nine
 // launches, tiles of 4 us plus 2.6 us per kv tile on 512 workgroups (a bucket's last tile is padded),
@@ -1662,9 +1666,8 @@ bool fine_is_faster(const Problem& pb) {
   const double rows = (double)pb.Hq * pb.Lq, items = rows * pb.topk, keys = (double)pb.topk * pb.S + pb.A / 2;
   const double d = pb.D / 128.0;
   const double by_rows = fmax(0.075 * keys, 2e-5 * d * rows * (keys + 13.0 * pb.topk));
-  const double tiles = fmin(items, (double)pb.Hkv * pb.n) + items / 128;
   const double steps = (double)((pb.S + TN - 1) / TN);
-  return 45 + tiles * (4 + 2.6 * steps) / 512 + (items + rows) * pb.D * 8 / 4.5e6 < by_rows;
+  return 45 + fine_tiles(pb) * (4 + 2.6 * steps) / 512 + (items + rows) * pb.D * 8 / 4.5e6 < by_rows;
 }
 
 constexpr size_t kFineMaxScratch = (size_t)4 << 30;
@@ -1687,6 +1690,19 @@ int fine_heads(const Problem& pb) {
   return h;
 }
 
+// D = 64: kv tiles of 32 tokens, three workgroups per compute unit, pay where there are tiles for a second round.  Where two
+// workgroups per compute unit take them all at once, the call lasts as long as one tile's chain of kv steps, and half as
+// many steps of 64 are shorter; so they are over long spans.  500 calls of 1 to 64 heads, 64 -> 32 tokens, time of the call
+// (means): up to 512 tiles, spans of up to 64 1.00, 256 1.03, 512 1.06, longer ones 1.11 (2253 tokens, 24:4 heads, one row
+// 110 -> 133 us); 1024 to 2048 tiles 0.96, 0.97, 0.97, 1.06; more 0.93, 0.94, 0.98, 1.03.
+// The window alone: up to a workgroup per compute unit 1.01 (spans beyond 512 tokens 1.03), from two on 0.98.
+bool short_routed_tiles(const Problem& pb, const DeviceSetup& dev) {
+  return pb.D == 64 && fine_tiles(pb) > 2 * dev.grid && pb.S <= 512;
+}
+bool short_window_tiles(const Problem& pb, const DeviceSetup& dev, unsigned grid) {
+  return pb.D == 64 && grid > (unsigned)dev.grid;
+}
+
 template <int D>
 bool fine_setup(DeviceSetup* out) {
   static std::mutex mu;
@@ -1694,12 +1710,15 @@ bool fine_setup(DeviceSetup* out) {
   int dev = -1;
   if (!device_setup(out) || hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return false;
   std::lock_guard<std::mutex> lock(mu);
-  if (!done[dev])
-    done[dev] = hipFuncSetAttribute(reinterpret_cast<const void*>(span_flash_routed_kernel<true, D, true>),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize,
-                                    FlashLds<1, D, fine_tile(D)>::kBytes) == hipSuccess &&
-                hipFuncSetAttribute(reinterpret_cast<const void*>(span_flash_local_kernel<false, D, true>),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, FlashLds<1, D, fine_tile(D)>::kBytes) == hipSuccess;
+  auto allow = [](auto routed, auto local, int bytes) {
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(routed), hipFuncAttributeMaxDynamicSharedMemorySize, bytes) == hipSuccess &&
+           hipFuncSetAttribute(reinterpret_cast<const void*>(local), hipFuncAttributeMaxDynamicSharedMemorySize, bytes) == hipSuccess;
+  };
+  if (!done[dev]) {
+    done[dev] = allow(span_flash_routed_kernel<true, D, true>, span_flash_local_kernel<false, D, true>, FlashLds<1, D>::kBytes);
+    if constexpr (D == 64)
+      done[dev] = done[dev] && allow(span_flash_routed_kernel<true, D, true, 32>, span_flash_local_kernel<false, D, true, 32>, FlashLds<1, D, 32>::kBytes);
+  }
   return done[dev];
 }
 
@@ -1748,12 +1767,24 @@ sl_status fine_pass(const Problem& pb, const DeviceSetup& dev, const bf16_t* Q, 
                       GridItems{pb.A}, flag, st))
     return SL_ERR_LAUNCH;
   if (pb.prof_start) (void)hipEventRecord(pb.prof_start, st);
-  using Lds = FlashLds<1, D, fine_tile(D)>;
-  hipLaunchKernelGGL((span_flash_routed_kernel<true, D, true>),
-                     dim3(fine_blocks(D) * dev.grid), dim3(Lds::kThreads), Lds::kBytes, st, a);
+  const unsigned lgrid = local_grid(pb.Lq, pb.A, pb.Hkv, pb.G);
+  auto routed = [&](auto tile) {
+    constexpr int TT = decltype(tile)::value;
+    hipLaunchKernelGGL((span_flash_routed_kernel<true, D, true, TT>), dim3(fine_blocks(TT) * dev.grid), dim3(256),
+                       (FlashLds<1, D, TT>::kBytes), st, a);
+  };
+  auto local = [&](auto tile) {
+    constexpr int TT = decltype(tile)::value;
+    hipLaunchKernelGGL((span_flash_local_kernel<false, D, true, TT>), dim3(lgrid), dim3(256),
+                       (FlashLds<1, D, TT>::kBytes), st, a);
+  };
+  using Short = std::integral_constant<int, D == 64 ? 32 : TN>;
+  using Long = std::integral_constant<int, TN>;
+  if (short_routed_tiles(pb, dev)) routed(Short{});
+  else routed(Long{});
   if (pb.prof_stop) (void)hipEventRecord(pb.prof_stop, st);
-  hipLaunchKernelGGL((span_flash_local_kernel<false, D, true>), dim3(local_grid(pb.Lq, pb.A, pb.Hkv, pb.G)),
-                     dim3(Lds::kThreads), Lds::kBytes, st, a);
+  if (short_window_tiles(pb, dev, lgrid)) local(Short{});
+  else local(Long{});
   const int64_t rows = (int64_t)pb.Hq * pb.Lq;
   constexpr int kRowsPerBlock = 256 / (D / 4);
   const dim3 mgrid((unsigned)((rows + kRowsPerBlock - 1) / kRowsPerBlock));

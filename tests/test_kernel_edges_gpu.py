@@ -137,6 +137,19 @@ def test_any_span_length_on_the_matrix_cores(Hq, Hkv, L, D, S, A, k, form, q_pos
         assert float((LSE - RL).abs().max()) <= 1e-5
 
 
+@pytest.mark.parametrize("Hq,Hkv,L,D,S,A,k,form,q_pos0,Lq", [
+    (12, 2, 15272, 64, 1920, 960, 12, "gated", 15152, 120),    # few tiles: kv tiles of 64, routed and window
+    (4, 1, 3000, 64, 1441, 1441, 4, "joint", 2700, 300),
+    (8, 2, 6000, 64, 129, 129, 8, "joint", 5700, 300),
+    (64, 8, 8000, 64, 100, 100, 8, "joint", 7700, 300),        # of 32 for the routed part, the window alone 64
+    (32, 4, 9000, 64, 600, 600, 8, "gated", 6000, 3000),       # long spans: 64 for the routed part, the window alone 32
+    (8, 2, 8000, 64, 81, 81, 8, "joint", 3900, 4100),          # both 32
+])
+def test_kv_tiles_of_both_lengths_at_64_dimensions(Hq, Hkv, L, D, S, A, k, form, q_pos0, Lq):
+    """Each choice of kv tiles for spans and windows, with remainders, on test_any_span_length_on_the_matrix_cores's terms."""
+    test_any_span_length_on_the_matrix_cores(Hq, Hkv, L, D, S, A, k, form, q_pos0, Lq)
+
+
 def token_major(x):
     """The same values with the heads of a token side by side and a gap behind them."""
     H, T, D = x.shape
