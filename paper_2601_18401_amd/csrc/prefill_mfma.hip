@@ -1148,16 +1148,18 @@ __host__ __device__ inline int local_heads(int G) {
 }
 // Row tiles and their grouping into chunks of `tps` tiles (the tiles of one span when S is a multiple of the tile height).
 struct LocalMap {
-  int rows, tiles, tps, chunks;  // rows of a tile, tiles of a kv head (and group of `heads` heads)
+  int shift, rows;         // rows of a tile, a power of two: what depends on it is shifted, not divided
+  int tiles, tps, chunks;  // tiles of a kv head (and group of `heads` heads)
 };
 __host__ __device__ inline LocalMap local_map(int64_t Lq, int S, int G) {
   LocalMap m;
-  m.rows = FlashLds<1>::kRows / local_heads(G);
-  m.tiles = (int)((Lq + m.rows - 1) / m.rows);
+  m.shift = __builtin_ctz(FlashLds<1>::kRows / local_heads(G));
+  m.rows = 1 << m.shift;
+  m.tiles = (int)((Lq + m.rows - 1) >> m.shift);
   // No more than an eighth of the tiles in a run: the paper's geometry, whose runs are 1024 tokens long, 1024 rows behind
   // 48133 tokens 407 -> 285 us, 4096 530 -> 444, a prompt of 3000 253 -> 161.
   const int each = (m.tiles + 7) / 8;
-  m.tps = S / m.rows < each ? S / m.rows : each;
+  m.tps = (S >> m.shift) < each ? S >> m.shift : each;
   m.tps = m.tps > 0 ? m.tps : 1;
   m.chunks = (m.tiles + m.tps - 1) / m.tps;
   return m;
@@ -1190,7 +1192,7 @@ __global__ __launch_bounds__(FlashLds<1>::kThreads, FINE ? fine_blocks(TT) : 2) 
   // and inside an XCD the groups of heads of a kv head take the same row tile back to back, so the
   // window's K/V tiles are fetched from HBM about once.
   const LocalMap lm = local_map(a.Lq, a.A, a.G);
-  const int heads = local_heads(a.G), sets = a.G / heads;
+  const int heads = FlashLds<1>::kRows >> lm.shift, sets = a.G / heads;
   const int xcd = blockIdx.x % 8, slot = blockIdx.x / 8;
   const int chunks_x = (lm.chunks - xcd + 7) / 8;                 // chunks xcd, xcd+8, ... of a kv head
   const bool has_last = lm.chunks > 0 && (lm.chunks - 1) % 8 == xcd;  // the only chunk that may be short
@@ -1199,9 +1201,9 @@ __global__ __launch_bounds__(FlashLds<1>::kThreads, FINE ? fine_blocks(TT) : 2) 
   const int kvh = slot / (tiles_x * sets), rem = slot % (tiles_x * sets);
   const int tile_local = rem / sets;
   const int tile = (xcd + 8 * (tile_local / lm.tps)) * lm.tps + tile_local % lm.tps;
-  const int h = kvh * a.G + rem % sets * heads + qrow / lm.rows;
-  const int64_t r0 = (int64_t)tile * lm.rows;
-  const int64_t r = r0 + qrow % lm.rows;
+  const int h = kvh * a.G + rem % sets * heads + (qrow >> lm.shift);
+  const int64_t r0 = (int64_t)tile << lm.shift;
+  const int64_t r = r0 + (qrow & (lm.rows - 1));
   const int64_t rc = r < a.Lq ? r : a.Lq - 1;
   TileDesc d;
   d.kv = kvh;
