@@ -757,7 +757,7 @@ __global__ __launch_bounds__(256, D == 64 ? (KMAX <= 2 ? 8 : 6) : 4) void prefil
     }
     return sum;
   };
-  float len_a = 0.f, len_b = 0.f;
+  float len_a = 0.f, len_b = 0.f;  // (maxima that keep what is not a number)
   if (c1 > 0) stage(0);
   for (int jb = 0; jb < c1; jb += 16) {  // c1 >= c0
     __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the batch is in LDS (this wavefront's own: no barrier)
@@ -773,8 +773,8 @@ __global__ __launch_bounds__(256, D == 64 ? (KMAX <= 2 ? 8 : 6) : 4) void prefil
 #pragma unroll
     for (int kk = 0; kk < KS; ++kk) asm volatile("" : "+v"(ka[kk]), "+v"(kb[kk])::"memory");
     if (jb + 16 < c1) stage(jb + 16);
-    len_a = fmaxf(len_a, square(ka));
-    len_b = fmaxf(len_b, square(kb));
+    len_a = __builtin_elementwise_maximum(len_a, square(ka));
+    len_b = __builtin_elementwise_maximum(len_b, square(kb));
     f32x4 sa = {0.f, 0.f, 0.f, 0.f}, sb = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int kk = 0; kk < KS; ++kk) {
@@ -820,10 +820,10 @@ __global__ __launch_bounds__(256, D == 64 ? (KMAX <= 2 ? 8 : 6) : 4) void prefil
   // scores lie further apart than twice that are in the same order in both.
   // the longest of the keys that the 16 lanes have staged ...
   auto row_max = [](float x) {
-    x = fmaxf(x, dpp_f32<0xB1>(x));   // lane ^ 1
-    x = fmaxf(x, dpp_f32<0x4E>(x));   // lane ^ 2
-    x = fmaxf(x, dpp_f32<0x141>(x));  // mirrored within 8 lanes
-    return fmaxf(x, dpp_f32<0x140>(x));
+    x = __builtin_elementwise_maximum(x, dpp_f32<0xB1>(x));   // lane ^ 1
+    x = __builtin_elementwise_maximum(x, dpp_f32<0x4E>(x));   // lane ^ 2
+    x = __builtin_elementwise_maximum(x, dpp_f32<0x141>(x));  // mirrored within 8 lanes
+    return __builtin_elementwise_maximum(x, dpp_f32<0x140>(x));
   };
   len_a = row_max(len_a);
   len_b = row_max(len_b);

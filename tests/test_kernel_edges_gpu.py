@@ -433,13 +433,13 @@ def test_anchor_search_ties_go_to_the_nearer_anchor():
             assert an[h, r].tolist() == toks[pick].tolist()
 
 
-@pytest.mark.parametrize("kind", ["random", "cancelling", "near-equal", "zero", "infinite", "huge"])
+@pytest.mark.parametrize("kind", ["random", "cancelling", "near-equal", "zero", "infinite", "nan", "huge"])
 @pytest.mark.parametrize("Hq,Hkv,D,k", [(8, 1, 128, 2), (6, 2, 128, 4), (12, 1, 64, 3), (8, 2, 128, 6)])
 def test_anchor_search_selects_as_the_decode_search_does(Hq, Hkv, D, k, kind):
     """Whatever the scores: the selection and the returned scores of every row are the decode search's to the
     bit, and do not depend on how a prompt is cut.  Cancelling: two large channels of opposite sign, so that the
-    order of the additions decides between scores.  Near-equal: three keys, each varying in one small element.  Zero: queries and stretches of keys that are all zero.  Infinite: a key that is not finite
-    among finite ones.  Huge: scores around 1e38, where no number may take the place of their low bits."""
+    order of the additions decides between scores.  Near-equal: three keys, each varying in one small element.  Zero: queries and stretches of keys that are all zero.  Infinite, nan: keys that are not
+    finite among finite ones, one and many.  Huge: scores around 1e38, where no number may take the place of their low bits."""
     L, q0, w = 27000, 25000, 24
     Q, K, _ = make(1300 + D + k, Hq, Hkv, L, D, torch.bfloat16, Lq=L - q0, scale=0.3)
     if kind == "cancelling":
@@ -456,6 +456,9 @@ def test_anchor_search_selects_as_the_decode_search_does(Hq, Hkv, D, k, kind):
         K.mul_(3e18)
     elif kind == "infinite":
         K[0, 12000, 7], K[0, 11000, 7] = float("inf"), float("-inf")
+    elif kind == "nan":
+        K[0, 12000, 7] = float("nan")
+        K[Hkv - 1, 14000:20000:3, D - 1] = float("nan")
     an, sc = B.sl_anchor_search_prefill(Q, K, k, w, q_pos0=q0, want_scores=True)
     only = B.sl_anchor_search_prefill(Q, K, k, w, q_pos0=q0)
     parts = [B.sl_anchor_search_prefill(Q[:, a:b], K[:, :q0 + b], k, w, q_pos0=q0 + a, want_scores=True)
