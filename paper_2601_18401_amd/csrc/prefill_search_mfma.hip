@@ -3,8 +3,9 @@
 // Scores (eq. (2)) are computed transposed, S^T[span][query] = Ks[span][:] . Qs[query][:], so
 // that after v_mfma_f32_32x32x16_bf16 a lane owns one query column: lane l holds query l%32 and
 // the 16 spans 8*(r/4) + 4*(l/32) + r%4 of a 32-span tile.  Each lane keeps the running top-k
-// (eq. (3)) of the spans it sees; the selection itself is a threshold found in a first pass and
-// applied in a second one (see the kernel).  Scores never leave the chip.
+// (eq. (3)) of the spans it sees: scores with their span's number in the low bits, in one walk over the candidates,
+// or, where the scores are returned too or the spans are many, their values alone, which give a threshold that a
+// second walk applies (see the kernel).  Scores never leave the chip.
 //
 // Ties: among the spans whose score equals the threshold, the lower indices are kept.
 #include "kernels.h"
@@ -74,9 +75,10 @@ __device__ __forceinline__ float of_other_half(float x) {
 // their lists.  Cutting a score towards zero keeps the order of scores that differ after it, so where the k'-th and
 // the next one do, the first k' entries are the selection, and no index had to be carried beside the scores.  Where
 // they agree in the bits that are left (one column in a thousand at 256 spans), and no third one does, those entries'
-// scores are computed again, by the same MFMAs on their own keys, and the lowest is dropped.  What is left over --
-// longer runs of equal scores, scores that are not finite or nearly so --
-// goes the other way, the whole workgroup.
+// scores are computed again, by the same MFMAs on their own keys, and the lowest is dropped.  For longer runs the
+// workgroup walks a second time and keeps, of the scores that agree with the k'-th one, the bits that the number took and
+// the number, as one whole number each: equal scores everywhere take two walks, as in the other way.  Scores come into a
+// finite range first; a column whose k'-th score lies outside it goes the other way, and its workgroup with it.
 //
 // Two walks:
 //   pass 1  keeps, per lane, only the VALUES of the top-k scores it has seen (a lane sees half of
@@ -95,12 +97,12 @@ __device__ __forceinline__ float of_other_half(float x) {
 // their own KMAX: half of the median instructions.
 //
 // Two walks -> one, us, 32 heads: 65536 rows x 256 spans top-4 264 -> 166, top-8 315 -> 200, top-16 549 -> 302, top-32
-// 1320 -> 626; 16384 rows x 1024 spans, top-8 380 -> 238, x 2048 694 -> 525, x 4096 (where the second look at
-// agreeing scores is needed in most wavefronts) 1326 -> 1055; 500 rows x 256 23.4 -> 10.9; 3000 x 46 14.1 -> 9.1.  Where
-// all scores are equal the second way comes on top: 20000 x 156, top-8, 99 -> 135.
+// 1320 -> 607; 16384 rows x 1024 spans, top-8 380 -> 238, x 2048 694 -> 507, x 4096 (where the second look at
+// agreeing scores is needed in most wavefronts) 1326 -> 1020; 500 rows x 256 23.4 -> 10.8; 3000 x 46 14.1 -> 8.8.  Where
+// all scores are equal one walk becomes two: 20000 x 156, top-4 68 -> 83, top-8 99 -> 103, top-32 740 -> 332.
 
 template <int KMAX, bool WS, bool DIRECT>
-__global__ __launch_bounds__(256, (KMAX <= 4 || (KMAX == 8 && !WS)) ? 4 : 1) void prefill_search_mfma_kernel(
+__global__ __launch_bounds__(256, (KMAX <= 4 || (KMAX == 8 && !WS)) ? 4 : KMAX == 32 && !WS ? 2 : 1) void prefill_search_mfma_kernel(
     const bf16_t* __restrict__ Qs, const bf16_t* __restrict__ K, const bf16_t* __restrict__ Ks,
     int32_t* __restrict__ idx, float* __restrict__ scores, int64_t Lq, int64_t q_pos0, int G, int S,
     int topk, int64_t n, int packed, int64_t qsh, int64_t qst, int64_t kvsh, int64_t kvst) {
@@ -111,6 +113,7 @@ __global__ __launch_bounds__(256, (KMAX <= 4 || (KMAX == 8 && !WS)) ? 4 : 1) voi
   // them in front of the next read of it, other stage or not.
   extern __shared__ __align__(16) char s_stage[];
   bf16_t* const s_k = reinterpret_cast<bf16_t*>(s_stage);
+  __shared__ int s_way;
   __shared__ int s_cnt[TMQ];
   __shared__ int s_j[TMQ][CAP + 1];  // odd row stride: the lanes of a wavefront read their own rows
   __shared__ float s_x[WS ? TMQ : 1][CAP + 1];
@@ -243,14 +246,14 @@ __global__ __launch_bounds__(256, (KMAX <= 4 || (KMAX == 8 && !WS)) ? 4 : 1) voi
       int keep = ~number;
       asm volatile("" : "+v"(keep));  // (in a vector register: an instruction takes one scalar operand, the number)
       auto cut = [&](float x) { return __int_as_float(__float_as_int(x) & keep); };
+      if (tid == 0) s_way = 0;  // (the walk ends with a barrier)
       TopVals<KMAX + 1> own;
 #pragma unroll
       for (int e = 0; e <= KMAX; ++e) own.v[e] = cut(kNone);
-      // an infinite score with a number in its low bits is a NaN, and a signalling one: it would unsettle the list
-      int largest = 0;
-      unsigned lowest = 0x80000000u;  // of the negative ones, as unsigned numbers: larger is lower
-      float infinity = INFINITY;
-      asm volatile("" : "+v"(infinity));
+      // Scores come into this range before they are numbered: an infinite one with a number in its low bits is a NaN, and
+      // a signalling one, which would unsettle the list.  (What is not a number becomes the lowest one.)
+      float infinity = INFINITY, high = 2.9e38f, low = -2.9e38f;
+      asm volatile("" : "+v"(infinity), "+v"(high), "+v"(low));
       auto numbered = [&](float x, int j) {
         asm volatile("" : "+s"(j));  // one v_and_or
         return (__float_as_int(x) & keep) | j;
@@ -265,13 +268,9 @@ __global__ __launch_bounds__(256, (KMAX <= 4 || (KMAX == 8 && !WS)) ? 4 : 1) voi
         const int left = c_q - j0 - 4 * hf;
         auto tile = [&](auto score) {
 #pragma unroll
-          for (int e = 0; e < 16; e += 2) {
+          for (int e = 0; e < 16; ++e) {
             const int u = 8 * (e >> 2) + (e & 3);
-            const int p = numbered(score(s[e], u), j0 + u), q = numbered(score(s[e + 1], u + 1), j0 + u + 1);
-            largest = max(max(largest, p), q);
-            lowest = max(max(lowest, (unsigned)p), (unsigned)q);
-            push(p);
-            push(q);
+            push(numbered(score(__builtin_amdgcn_fmed3f(s[e], low, high), u), j0 + u));
           }
         };
         if (edge) tile([&](float x, int u) { return u < left ? x : kMasked; });
@@ -296,22 +295,63 @@ __global__ __launch_bounds__(256, (KMAX <= 4 || (KMAX == 8 && !WS)) ? 4 : 1) voi
           third = top.v[e + 2];
         }
       const float at = cut(kth);
-      const bool close = kq > 0 && next > 0.5f * kMasked && cut(next) == at;
+      bool close = kq > 0 && next > 0.5f * kMasked && cut(next) == at;
       const bool lost = close && (cut(third) == at || cut(own_last) == at || cut(other_last) == at);
-      const bool other_way = lost || largest >= 0x7f800000 || lowest >= 0xff800000u || (kq > 0 && !(kth > 0.5f * kMasked));
-      if (!__syncthreads_or(other_way)) {
+      const bool other_way = kq > 0 && !(kth > 0.5f * kMasked && at < cut(high));
+      const int mine = (__builtin_amdgcn_ballot_w64(lost) != 0ull ? 1 : 0) | (__builtin_amdgcn_ballot_w64(other_way) != 0ull ? 2 : 0);
+      if (mine != 0 && lane == 0) atomicOr(&s_way, mine);
+      __syncthreads();
+      const int way = __builtin_amdgcn_readfirstlane(s_way);
+      if ((way & 2) == 0) {
+        if (way != 0) {
+          // A second walk over the scores that agree with the k'-th one: the bits that the number took and the number,
+          // lower ones first, are all that is left to order them by, and make a whole number of at most 25 bits
+          // (the exponent makes it a float that nothing flushes).  Those above the k'-th are in `top`.
+          const float wanted = lost ? at : __builtin_nanf("");
+          const int bits = __builtin_popcount(number);
+          constexpr int kNothing = 0x20000000, kAbove = 0x30000000;
+#pragma unroll
+          for (int e = 0; e <= KMAX; ++e) own.v[e] = __int_as_float(kNothing);
+          walk([&](const f32x16& s, int j0, bool) {
+            if ((mine & 1) == 0) return;
+            const int left = c_q - j0 - 4 * hf;
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+              const int u = 8 * (e >> 2) + (e & 3), x = __float_as_int(s[e]), part = x & number;
+              const int key = (((x < 0 ? -part : part) + number + 1) << bits) | (number - (j0 + u)) | kNothing;
+              push(cut(s[e]) == wanted && u < left ? key : kNothing);
+            }
+          });
+          TopVals<KMAX + 1> other;
+#pragma unroll
+          for (int e = 0; e <= KMAX; ++e) {
+            own.v[e] = __int_as_float(__float_as_int(own.v[e]) & ~(hf << 2));
+            other.v[e] = of_other_half(own.v[e]);
+          }
+#pragma unroll
+          for (int e = 0; e <= KMAX; ++e) push(__float_as_int(other.v[e]));
+#pragma unroll
+          for (int e = 0; e < KMAX; ++e) {
+            const int j = __float_as_int(top.v[e]) & number;
+            push(e < kq && cut(top.v[e]) > at ? kAbove | (number - j) : kNothing);
+          }
+#pragma unroll
+          for (int e = 0; e < KMAX; ++e)
+            top.v[e] = lost ? __int_as_float(number - (__float_as_int(own.v[e]) & number)) : top.v[e];
+        }
+        close = close && !lost;
         if (__builtin_amdgcn_ballot_w64(close) != 0ull) {
           // the entries that agree with the k'-th one, entry by entry: the column's own key as row qc of a product
           // with all columns, of which the diagonal is taken
           float worst = INFINITY;
           int worst_j = -1, worst_e = KMAX;
           for (int e = 0; e <= KMAX; ++e) {
-            float mine = top.v[0];
+            float entry = top.v[0];
 #pragma unroll
-            for (int x = 1; x <= KMAX; ++x) mine = x == e ? top.v[x] : mine;
-            const bool in = close && e <= kq && cut(mine) == at;
+            for (int x = 1; x <= KMAX; ++x) entry = x == e ? top.v[x] : entry;
+            const bool in = close && e <= kq && cut(entry) == at;
             if (__builtin_amdgcn_ballot_w64(in) == 0ull) continue;
-            const int j = in ? __float_as_int(mine) & number : 0;
+            const int j = in ? __float_as_int(entry) & number : 0;
             const bf16_t* const kp = key(j) + hf * 8;
             f32x16 s;
 #pragma unroll
@@ -435,15 +475,15 @@ __global__ __launch_bounds__(256, (KMAX <= 4 || (KMAX == 8 && !WS)) ? 4 : 1) voi
 }
 
 // Up to how many candidates a workgroup goes one walk.  Long runs of agreeing scores become eight times as frequent
-// with twice the spans (at 4096, one workgroup in 30), and each such workgroup pays both ways: of many workgroups one in
+// with twice the spans (at 4096, one workgroup in 30), and each such workgroup walks twice: of many workgroups one in
 // 30 does not show, but where all run at once the slowest is the call's time.  us, two walks -> one, top-8, mean of 8
-// inputs: 2048 spans, 128 workgroups 108 -> 86, 256: 108 -> 99, 512: 135 -> 145, 2000: 379 -> 315; 4096 spans, 32 workgroups
-// 196 -> 205, 256: 194 -> 276, 1000: 394 -> 440, 2000: 716 -> 661; at 1024 spans every grid gains (256: 63 -> 35).
-// Above 4096 spans too few bits of the score are left.
+// inputs: 1024 spans, 256 workgroups 63 -> 31, 1000: 116 -> 81; 2048 spans, 32 workgroups 110 -> 48, 256: 108 -> 81, 512:
+// 134 -> 117, 1000: 209 -> 170, 2000: 377 -> 269; 4096 spans, 32 workgroups 197 -> 170, 128: 194 -> 216, 512: 244 -> 267,
+// 1000: 392 -> 371, 2000: 717 -> 571.  Above 4096 spans too few bits of the score are left.
 constexpr int kFewWorkgroups = 1536;
 
 int one_walk_spans(int64_t grid) {
-  return grid > kFewWorkgroups ? 4096 : grid <= 256 ? 2048 : 1024;
+  return grid > kFewWorkgroups ? 4096 : 2048;
 }
 
 template <int KMAX, bool WS, bool DIRECT>
@@ -479,7 +519,7 @@ sl_status prefill_search_mfma(const Problem& pb, const void* Qs, const void* K, 
                               int32_t* idx, float* scores, hipStream_t st) {
   // A list of four in lanes of five: one column in 16 whose fourth and fifth score agree has all five in one lane, which
   // then cannot tell whether a sixth does.  Longer lanes' lists instead where one such workgroup is the call's time and one
-  // walk is taken: 500 rows x 1024 spans, top-4, two walks 55.4 us, lanes of five 57.6, of nine 27.4; x 2048 97, 113, 48.6.
+  // walk is taken: 500 rows x 1024 spans, top-4, two walks 55.5 us, lanes of five 43.7, of nine 27.2; x 2048 97, 90, 48.4.
   const int64_t grid = pb.Hq * ((pb.Lq + TMQ - 1) / TMQ), spans = (pb.q_pos0 + pb.Lq - 1) / pb.S;
   const bool longer = pb.topk == 4 && !scores && grid <= kFewWorkgroups && spans > 512 && spans <= one_walk_spans(grid);
   if (pb.topk <= 4 && !longer) return launch<4>(pb, Qs, K, Ks, idx, scores, st);
