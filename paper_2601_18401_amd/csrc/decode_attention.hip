@@ -877,15 +877,14 @@ inline bool reduce_fits_lds(int64_t nrec, bool combined) {
   return nrec * (combined ? 2 : 1) * (int64_t)sizeof(float) <= 64 * 1024;
 }
 
-// No bf16 chunk is shorter than what the four wavefronts load at once, eight rows per row group: of a shorter one a
-// wavefront loads its last row again and again (D = 128: 128 tokens; D = 64: 256).  With 64 tokens throughout,
+// No chunk is shorter than what the four wavefronts load at once, eight rows per row group: of a shorter one a wavefront
+// loads its last row again and again (bf16, D = 128: 128 tokens; D = 64: 256; fp32, D = 128: 64).  With 64 tokens throughout,
 // us per step, bf16 32:4 heads, top-16: 16411 tokens 20.1 -> 17.7, 65536 27.0 -> 23.1, 262144 42.2 -> 34.5, 524288 52.5 ->
 // 43.9, gated 59.7 -> 50.5; D = 64: 65536 26.2 -> 18.5, 524288 48.8 -> 28.9; the paper's geometry: 4000 tokens, top-4, 29.9 ->
-// 24.6, 200000, top-2, 38.9 -> 32.1, 1M, top-1, 43.1 -> 36.1.  fp32 keeps 64: 128 tokens at D = 64, what its wavefronts load
-// at once, are faster by 1 to 5 %, but the sums of spans of 100 to 128 tokens get longer (error against 64 bits 1.743e-7 ->
-// 1.766e-7 at 16411 tokens in spans of 128, 1.705e-7 -> 1.736e-7 at 20000 in spans of 100).
+// 24.6, 200000, top-2, 38.9 -> 32.1, 1M, top-1, 43.1 -> 36.1.
 int least_chunk(const Problem& pb) {
-  return pb.dtype == SL_BF16 ? 4 * 8 * (512 / pb.D) : 64;
+  const int rows = 4 * 8 * (1024 / (pb.D * (pb.dtype == SL_BF16 ? 2 : 4)));
+  return rows < 64 ? 64 : rows;
 }
 
 // Tokens per item.  A batch has items enough even for short spans; there it counts that a workgroup's four wavefronts,
