@@ -896,7 +896,8 @@ int least_chunk(const Problem& pb) {
 // sequences x (longest; down to a fifth of it), spans, top-k: 8 x 20000, 128, 16: 87.7 -> 53.9; 8 x 30000, 192, 16: 96 -> 72;
 // 8 x 50000, 256, 16: 108 -> 92; 7 x 100000, 320, 16: 114 -> 108; 8 x 300000, 512, 16: 167-171 -> 165, gated 180 -> 175;
 // 8 x 400000, 640, 16: 275 -> 213.  Spans of 448 stay at 512 (157; 256-token chunks, as badly filled, 161), 8 x 1M in spans
-// of 1024 too (318), 2 x 300000 at 128 (55; 64: 79).
+// of 1024 too (318), 2 x 300000 at 128 (55; 64: 79).  Not below least_chunk here either: bf16, D = 64, 64:8 heads, 2 x 2223,
+// 137, 16: 36.1 -> 24.7 with 256 for 128, 32:4, 3 x 67763, 260, 4: 27.0 -> 23.6; at most 3 % the other way (8:4, 3 x 71289, 267, 2).
 int pick_chunk_tokens(const Problem& pb, int batch = 1) {
   // Aim for a few thousand workgroups so the 256 CUs keep enough loads in flight.
   const int64_t units = (int64_t)batch * pb.Hq * (pb.topk + 1);
@@ -906,7 +907,7 @@ int pick_chunk_tokens(const Problem& pb, int batch = 1) {
   while (ct > least_chunk(pb) && units * chunks(ct) < 4096) ct >>= 1;
   if (batch > 1) {
     if (ct == 512 && units * chunks(ct) < 8192 && filled(256, 9)) ct = 256;
-    while (ct > 128 && !filled(ct, 7)) ct >>= 1;
+    while (ct > (least_chunk(pb) > 128 ? least_chunk(pb) : 128) && !filled(ct, 7)) ct >>= 1;
   }
   return ct;
 }

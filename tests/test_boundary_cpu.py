@@ -243,3 +243,12 @@ def test_fp32_prefill_takes_the_form_that_measured_faster(Hq, Hkv, D, L, Lq, S, 
     assert max(rows_us, tiles_us) >= 1.3 * min(rows_us, tiles_us)
     p = good(L=L, Lq=Lq, q_pos0=L - Lq, Hq=Hq, Hkv=Hkv, D=D, S=S, topk=k, dtype=B.SL_F32)
     assert (B.workspace_bytes(p, B.OP_ATTENTION_PREFILL) > 0) == (tiles_us < rows_us)
+
+
+@pytest.mark.parametrize("D,S,chunks", [(64, 256, 1), (64, 300, 2), (64, 137, 1), (128, 300, 3), (128, 256, 1)])
+def test_batched_chunks_are_no_shorter_than_what_a_workgroup_loads_at_once(D, S, chunks):
+    """bf16, D = 64: 256 tokens, also where spans fill longer chunks badly (D = 128: 128)."""
+    p = good(L=20000, Lq=1, q_pos0=19999, Hq=32, Hkv=4, D=D, S=S, topk=16)
+    one = good(L=20000, Lq=1, q_pos0=19999, Hq=32, Hkv=4, D=D, S=64, topk=16)     # a chunk a slot
+    need, single = (B.load().sl_decode_batched_workspace_bytes(ctypes.byref(x), 8) for x in (p, one))
+    assert need == chunks * single

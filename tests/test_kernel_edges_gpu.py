@@ -777,13 +777,13 @@ def test_window_tiles_of_several_heads(Hq, Hkv, Lq, S):
 
 
 @pytest.mark.parametrize("form", ["joint", "gated"])
-@pytest.mark.parametrize("S", [65, 128, 200, 320])
-def test_decode_batches_of_many_short_spans(S, form):
+@pytest.mark.parametrize("D,S", [(128, 65), (128, 128), (128, 200), (128, 320), (64, 137), (64, 300)])
+def test_decode_batches_of_many_short_spans(D, S, form):
     """Items enough for every chunk length (8 x 32 x 17): chunks of 128 and 256 tokens that spans fill badly, exactly and
     with a remainder, against the single-sequence entry points.  Other chunks add in another order: outputs differ by a
     rounding to bf16, 2^-7 of them, and what fp32 sums of some thousand terms differ by."""
     gated = form == "gated"
-    seqs = [make(2300 + S + b, 32, 4, S * 18 + 700 - 83 * b, 128, torch.bfloat16, Lq=1, scale=0.5) for b in range(8)]
+    seqs = [make(2300 + S + b, 32, 4, S * 18 + 700 - 83 * b, D, torch.bfloat16, Lq=1, scale=0.5) for b in range(8)]
     Q, K, V = ([s[x] for s in seqs] for x in range(3))
     bt = B.DecodeBatch(Q, Q, K, V, [B.sl_span_keys(k, S) for k in K], S, 16, want_scores=gated)
     if gated:
