@@ -631,6 +631,30 @@ def test_fp32_spans_on_the_matrix_cores(Hq, Hkv, L, D, S, A, k, form, q_pos0, Lq
 
 
 @pytest.mark.parametrize("form", ["joint", "gated"])
+def test_fp32_spans_in_several_passes_over_the_kv_heads(form):
+    """More partials than 4 GiB of scratch hold: three kv heads, then the fourth, in the same workspace; packed and strided.
+    The sums' bound is that of test_fp32_spans_on_the_matrix_cores."""
+    Hq, Hkv, L, D, S, k = 32, 4, 19411, 128, 64, 16
+    Q, K, V = make(2060, Hq, Hkv, L, D, torch.float32, scale=1.0 if form == "joint" else 0.35)
+    idx, sc = B.sl_span_search_prefill(Q, K, None, S, k, want_scores=True)
+    sc = None if form == "joint" else torch.where(torch.isfinite(sc), sc, 0.0)
+    need = B.workspace_bytes(B.make_params(Q, K, S, k), B.OP_ATTENTION_PREFILL)
+    assert 3 * Hq // Hkv * L * k * D * 4 < need < Hq * L * k * D * 4
+    got, want = span_rows(Q, K, V, idx, sc, S, 0, 0)
+    torch.cuda.synchronize()
+    for x, y in zip(got, want):
+        assert float((x - y).abs().max()) <= 1.6e-5
+    for kv in range(Hkv):       # all of them by this form
+        heads = slice(kv * Hq // Hkv, (kv + 1) * Hq // Hkv)
+        assert not torch.equal(got[0][heads], want[0][heads]), kv
+    del want
+    strided = B.sl_span_attention_prefill(token_major(Q), token_major(K), token_major(V), idx, S)[0] if sc is None else \
+        B.sl_span_attention_combined_prefill(token_major(Q), token_major(K), token_major(V), idx, sc, S)
+    torch.cuda.synchronize()
+    assert torch.equal(got[0], strided)
+
+
+@pytest.mark.parametrize("form", ["joint", "gated"])
 @pytest.mark.parametrize("span", [12, 50])     # a span that lies in no row's window; one that does
 @pytest.mark.parametrize("which,bad", [("V", float("nan")), ("V", float("inf")), ("K", float("nan")), ("K", float("inf"))])
 def test_fp32_spans_keep_what_is_not_finite_to_the_rows_that_attend_it(which, bad, span, form):
