@@ -738,19 +738,7 @@ __global__ __launch_bounds__(kShortThreads) void decode_short_kernel(
     if (u + 2 < u1) ask(u + 2, First{});
     if (u + 1 < u1) take(Second{});
   }
-#pragma unroll
-  for (int off = LPR; off < 64; off <<= 1) {  // the wavefront's row groups
-    const float mo = __shfl_xor(st.m, off, 64), lo = __shfl_xor(st.l, off, 64);
-    const float M = fmaxf(st.m, mo);
-    const float wa = st.m > -INFINITY ? fast_exp2(st.m - M) : 0.f, wb = mo > -INFINITY ? fast_exp2(mo - M) : 0.f;
-    st.l = st.l * wa + lo * wb;
-#pragma unroll
-    for (int e = 0; e < EPL; ++e) {
-      const float oo = __shfl_xor(st.o[e], off, 64);
-      st.o[e] = st.o[e] * wa + oo * wb;
-    }
-    st.m = M;
-  }
+  merge_row_groups<T, D>(st);
   if (lane < LPR) {
 #pragma unroll
     for (int e = 0; e < EPL; ++e) s_o[wave][lr * EPL + e] = st.o[e];

@@ -386,20 +386,7 @@ __device__ void window_row(const WindowArgs& a, int h, int64_t r, int lane) {
       if (v) add(a, b);
     }
   }
-  // the groups' states
-#pragma unroll
-  for (int off = LPR; off < 64; off <<= 1) {
-    const float mo = __shfl_xor(st.m, off, 64), lo = __shfl_xor(st.l, off, 64);
-    const float M = fmaxf(st.m, mo);
-    const float wa = st.m > -INFINITY ? fast_exp2(st.m - M) : 0.f, wb = mo > -INFINITY ? fast_exp2(mo - M) : 0.f;
-    st.l = st.l * wa + lo * wb;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const float oo = __shfl_xor(st.o[e], off, 64);
-      st.o[e] = st.o[e] * wa + oo * wb;
-    }
-    st.m = M;
-  }
+  merge_row_groups<float, D>(st);
   float out[4];
   if constexpr (!COMBINED) {
     const float inv = 1.f / st.l;  // the local window always holds the query's own token: l > 0

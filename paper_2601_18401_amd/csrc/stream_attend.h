@@ -105,4 +105,26 @@ __device__ __forceinline__ void attend_range(const float* q2, const T* __restric
   }
 }
 
+// Merges the row groups of a wavefront (lanes with equal lane % LPR hold the same d-slice); on
+// return every lane holds the state of all rows the wavefront attended.
+template <typename T, int D>
+__device__ __forceinline__ void merge_row_groups(AttendState<T, D>& st) {
+  constexpr int EPL = RowLayout<T, D>::EPL, LPR = RowLayout<T, D>::LPR;
+#pragma unroll
+  for (int off = LPR; off < 64; off <<= 1) {
+    const float mo = __shfl_xor(st.m, off, 64);
+    const float lo = __shfl_xor(st.l, off, 64);
+    const float M = fmaxf(st.m, mo);
+    const float wa = st.m > -INFINITY ? fast_exp2(st.m - M) : 0.f;
+    const float wb = mo > -INFINITY ? fast_exp2(mo - M) : 0.f;
+    st.l = st.l * wa + lo * wb;
+#pragma unroll
+    for (int e = 0; e < EPL; ++e) {
+      const float oo = __shfl_xor(st.o[e], off, 64);
+      st.o[e] = st.o[e] * wa + oo * wb;
+    }
+    st.m = M;
+  }
+}
+
 }  // namespace sl
