@@ -24,7 +24,7 @@ if ROOT not in sys.path:
 
 PEAK_HBM = 8.0e12           # B/s, MI355X HBM3E
 PEAK_BF16 = 2.5e15          # flop/s, dense bf16 MFMA
-PEAK_FP32_VALU = 157.3e12   # flop/s, fp32 vector
+PEAK_FP32 = 157.3e12        # flop/s, fp32: the vector and the matrix units have the same peak
 N_DECODE_QUERIES = 8        # decode steps rotate over this many independent queries (different span sets)
 MAIN_ONLY = False           # --main-only: time only each configuration's own step (clean profiler traces)
 
@@ -80,7 +80,7 @@ def device_facts(torch):
             # 4 SIMDs x 1024 flop/clk (a 32x32x16 bf16 MFMA = 32768 flop in 32 cycles) per compute unit
             "derived_bf16_mfma_peak_tflops": cus * 4096 * mhz * 1e6 / 1e12,
             "peaks_used": {"hbm_GBps": PEAK_HBM / 1e9, "bf16_mfma_tflops": PEAK_BF16 / 1e12,
-                           "fp32_valu_tflops": PEAK_FP32_VALU / 1e12}}
+                           "fp32_tflops": PEAK_FP32 / 1e12}}
 
 
 def prefill_flops(cfg):
@@ -529,11 +529,13 @@ def bench_prefill(cfg, steps, warmup, torch, B, W):
     f_attn = f_routed + f_local
     ka = sum(ms_a) / len(ms_a)
     ks = sum(ms_s) / len(ms_s)
-    mfma_path = cfg.dtype == "bf16" and cfg.D == 128 and cfg.S % 64 == 0
-    peak, bound = (PEAK_BF16, "mfma") if cfg.dtype == "bf16" else (PEAK_FP32_VALU, "alu")
-    # the events bracket the routed-span kernel, in bf16 and in fp32
-    f_kernel = f_routed
-    kernel = "span_flash_routed_kernel" if mfma_path else "span_tiles_f32_kernel"
+    # the events hold the routed-span kernel of the matrix-core forms, which take scratch, or the one kernel of the
+    # row-stationary form, which takes none and computes the window too
+    tiles = B.workspace_bytes(B.make_params(Q, K, cfg.S, cfg.topk), B.OP_ATTENTION_PREFILL) > 0
+    peak, bound = PEAK_BF16 if cfg.dtype == "bf16" else PEAK_FP32, "mfma" if tiles else "alu"
+    f_kernel = f_routed if tiles else f_attn
+    kernel = ("prefill_attention_rows_kernel" if not tiles else
+              "span_flash_routed_kernel" if cfg.dtype == "bf16" else "span_tiles_f32_kernel")
     tflops_attn = f_kernel / (ka * 1e-3)
     res = {
         "workload": f"{cfg.name} prefill L={cfg.L} Hq={cfg.Hq} Hkv={cfg.Hkv} D={cfg.D} S={cfg.S} topk={cfg.topk}+local",

@@ -2,15 +2,17 @@
 //
 // The row-stationary kernel reads every key and value row once per query row and slot through the L1: 4096 rows x 4 heads,
 // D = 64, spans of 64, top-4 is 2.4 GB of reads and as many vector instructions (the vector units busy 79 % of 82 us) for
-// 1.2 GFLOP.  Here the rows that attend a span share it: 45 us, of which 34 span_tiles_f32 (its MFMAs alone take 9;
-// 1900 workgroups in two and a half rounds of three per compute unit, each a chain of loads, look through, products) and
-// 11 window_f32.  D = 128 165 -> 77, top-8 141 -> 62, 32 heads x 1024 rows behind 65536 tokens in spans of 256 8400 -> 716.
+// 1.2 GFLOP.  Here the rows that attend a span share it: 46 us, of which 35 span_tiles_f32 (its MFMAs alone take 9;
+// 1900 workgroups in two and a half rounds of three per compute unit, each a chain of loads, look through, products; at
+// this bound of three two registers spill) and 11 window_f32.  D = 128 165 -> 79, top-8 141 -> 64, 32 heads x 1024 rows
+// behind 65536 tokens in spans of 256 8400 -> 716.
 //
 //   span_tiles_f32       one workgroup per (kv head, span, chunk of query rows) looks through the chunk's index lists
 //                        for its span (no bucketing launches: the lists are a few KB), stages the span in LDS and
 //                        takes the rows found 16 at a time per wavefront; partial (o, m, l) per (row, slot)
-//   window_f32           one wavefront per row: streams the local window (vector instructions: rows beyond the query are
-//                        never touched, whatever they hold) and merges the row's partials
+//   window_f32           sixteen rows of a head per wavefront: their local windows on the matrix cores, and the merge with
+//                        their partials.  Keys and values behind a row's query are loaded and have weight 0; where a
+//                        value is not finite the rows go one by one, by vector instructions, which touch none of them
 //
 // S^T = K Q^T and O^T += V^T P^T, so that a lane owns a query column: with 16x16x4, lane l of a result holds column l % 16
 // and rows 4 (l / 16) + r.  The contraction may run over the dimensions and the kv rows in any order: QK takes d = 16 j +

@@ -457,8 +457,9 @@ __device__ __forceinline__ int perm_row(int rho) {
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-// One 256-row tile as seen by a lane: the kv head and kv range [kv_begin, kv_end) (a multiple of
-// TN long) shared by the workgroup, and the lane's own query column.
+// One tile (256 rows, 128 of the window and fp32-weight kernels) as seen by a lane: the kv head and kv range [kv_begin,
+// kv_end) shared by the workgroup (walked in kv tiles; what lies behind its end is masked or zero), and the lane's own
+// query column.
 struct TileDesc {
   int kv;
   int64_t kv_begin, kv_end;
