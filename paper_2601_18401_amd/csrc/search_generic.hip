@@ -257,7 +257,10 @@ __device__ __forceinline__ void decode_search_block_body(
     gt_before += is_gt ? 1 : 0;
     eq_before += is_eq ? 1 : 0;
   }
-  if (tid >= kk && tid < topk) {
+  // what is left is empty: slots without a candidate, and those of candidates whose score is -inf or no number, which
+  // are not selected
+  const int eq_total = total >> 16, taken = gt_total + (eq_total < need_eq ? eq_total : need_eq);
+  if (tid >= (taken < kk ? taken : kk) && tid < topk) {
     oi[tid] = -1;
     if (os) os[tid] = -INFINITY;
   }

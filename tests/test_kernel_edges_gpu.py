@@ -563,6 +563,42 @@ def test_prefill_search_scores_that_agree_in_their_leading_bits(n, k, kind):
             assert got[h, r].tolist() == want + [-1] * (k - len(want)), (h, r)
 
 
+@pytest.mark.parametrize("n", [7, 300, 900])     # one launch, one launch of several loads, two launches
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_decode_search_writes_every_slot_where_scores_are_minus_infinity(n, dtype):
+    """Fewer finite scores than slots: the candidates with one are selected, the other slots say that they are empty,
+    whatever the output held; single and batched, grid and anchors."""
+    S, k, Hq, Hkv, D = 3, 10, 4, 2, 128
+    L = S * n + 2
+    Q, K, V = make(3450 + n, Hq, Hkv, L, D, dtype, Lq=1)
+    Q[..., 3] = 1.0
+    left = sorted({0, n // 2, n - 1})
+    K[:, :, 3] = float("-inf")
+    for j in left:
+        K[:, S * (j + 1) - 1, 3] = 0.0
+    p = B.make_params(Q, K, S, k, L - 1)
+    ws, stream = B.Workspace(), torch.cuda.current_stream().cuda_stream
+    wptr, wbytes = ws.get(B.workspace_bytes(p, B.OP_SEARCH_DECODE))
+    idx = torch.full((Hq, 1, k), 5, dtype=torch.int32, device=DEV)
+    sc = torch.full((Hq, 1, k), 5.0, device=DEV)
+    assert B.load().sl_span_search_decode(ctypes.byref(p), Q.data_ptr(), K.data_ptr(), None, idx.data_ptr(), sc.data_ptr(),
+                                          wptr, wbytes, stream) == B.SL_OK
+    bt = B.DecodeBatch([Q, Q], [Q, Q], [K, K], [V, V], None, S, k, want_scores=True)
+    bt.idx.fill_(5), bt.scores.fill_(5.0)
+    B.sl_span_search_decode_batched(bt)
+    anchors = torch.full((Hq, 1, k), 5, dtype=torch.int32, device=DEV)
+    pa, g = B.make_params(Q, K, 1, k, L - 1), B.SlAnchorGeometry(0, 0, 0, 2, 0)
+    assert B.load().sl_anchor_search_decode(ctypes.byref(pa), ctypes.byref(g), Q.data_ptr(), K.data_ptr(), anchors.data_ptr(),
+                                            None, stream) == B.SL_OK
+    torch.cuda.synchronize()
+    for i, s in ((idx, sc), (bt.idx[0], bt.scores[0]), (bt.idx[1], bt.scores[1])):
+        assert i[:, 0].tolist() == [left + [-1] * (k - len(left))] * Hq
+        assert bool(torch.isfinite(s[:, 0, :len(left)]).all()) and bool((s[:, 0, len(left):] == float("-inf")).all())
+    # anchors i - (s + 1)^2 + 1 whose keys are not masked, the nearest first
+    near = [t for t in (L - (x + 1) ** 2 for x in range(L)) if t >= 0 and bool(torch.isfinite(K[0, t, 3]))]
+    assert anchors[:, 0].tolist() == [near[:k] + [-1] * (k - len(near))] * Hq
+
+
 def test_prefill_search_of_equal_scores_takes_two_walks():
     """Two walks over the candidates, not three: 1.85 times the time of scores that differ (three: 2.5)."""
     L, S, k = 20000, 128, 8
