@@ -7,14 +7,16 @@
 //
 //   bucket (count) / unit_scan / scan / tiles / bucket (fill)   invert idx into per-(kv, span)
 //                                   lists of query rows (integer work, LDS histograms)
-//   span_flash_routed               persistent workgroups walk the (bucket, 256-row tile) list:
+//   span_flash_wide                 persistent workgroups take tiles of 256 (or 128) rows of a bucket:
 //                                   gathered Q rows against the span's K/V tiles staged through
 //                                   LDS, flash softmax, MFMA QK^T and PV; writes a normalised
 //                                   partial (o, lse) per (row, slot)
-//   span_flash_local                the local window [c*S, i]: regular 128-row tiles of one
-//                                   head with the causal mask; joint form with topk <= 8: merges
+//   span_window_wide                the local window [c*S, i]: regular tiles of as many columns
+//                                   with the causal mask; joint form with topk <= 8: merges
 //                                   the row's routed partials in its epilogue (log-sum-exp) and
 //                                   writes O and LSE; otherwise writes the row's last partial
+//   span_flash_routed / _local      the same two with fp32 softmax weights and partials (spans of
+//                                   any length, D = 64)
 //   merge_partials / merge_combined streaming merge of the <= topk + 1 partials of every row
 //                                   (topk > 8, and the gated combination of Section 3.4)
 //
@@ -38,7 +40,8 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x8 __attribute__((ext_vector_type(8)));
 
-constexpr int TG = 128;            // rows of one wavefront group (4 wavefronts x 32 columns)
+constexpr int TG = 128;            // rows of a tile of the fp32-weight kernels (4 wavefronts x 32 columns)
+constexpr int TM = 256;            // rows of a tile of the kernels with bf16 weights (4 wavefronts x 64 columns)
 constexpr int TN = 64;             // kv positions per staged tile
 // Of the kernels with fp32 weights, too; at D = 64 tiles of 32 leave room (registers, LDS) for a third workgroup per
 // compute unit and end closer to a span's end: 20011 rows in spans of 142 1213 -> 1098 us, 8000 in spans of 90, top-4, 260 ->
@@ -48,7 +51,7 @@ constexpr int TN = 64;             // kv positions per staged tile
 constexpr int fine_blocks(int tile) { return tile == 32 ? 3 : 2; }  // workgroups per compute unit
 constexpr int HD = 128;            // head dimension of the kernels with bf16 weights
 
-// LDS of the flash kernels (dynamic).  Main loop: stages of the V tile and of the K tile, filled
+// LDS of the flash kernels (dynamic).  Main loop: two stages of the K and of the V tile, filled
 // by direct global->LDS loads (16 bytes per lane, a wavefront instruction fills 1 KB
 // contiguously); rows are unpadded and their 16-byte pieces XOR-swizzled so that the MFMA
 // operand reads of 16 consecutive lanes hit 16 distinct bank groups:
@@ -56,42 +59,25 @@ constexpr int HD = 128;            // head dimension of the kernels with bf16 we
 //   V tile [64][128]: piece p of row r at position p ^ ((r & 3) << 2): the four rows that 16 lanes read
 //                     64 bytes of (with the 16 lanes beside them) lie in different bank groups
 // V is staged as it lies in memory and transposed by the LDS reads (ds_read_b64_tr_b16): a transposed
-// copy of V in the workspace cost a pass over the whole cache per call, however few the rows: 63 us for
-// 4000 new rows behind 196000 tokens (0.945 -> 0.931 ms in all, the twice as many LDS reads take back part
-// of it), 22 us at 48K on the paper's geometry (4.45 -> 4.41 ms); with all 262144 rows, where the copy was
-// 87 us of 25.8 ms, the attention takes 26.0 ms.
-// Epilogue: each wavefront group stages its output tile [128][128] bf16 (piece p of row r at
-// p ^ (r & 15)).
-//   NG = 2 (routed, 512 threads, 256 rows, one workgroup per compute unit, 154624 bytes): two K
-//     and three V stages (the late group reads a V tile one step after the early group); the
-//     output region is separate, so the first K/V tile of the next 256-row tile can be fetched
-//     while the current one is written out.
-//   NG = 1 (local window, 256 threads, 128 rows, 67072 bytes: two workgroups per compute unit, so
-//     one's epilogue runs beside the other's main loop): two stages each; the output region
-//     lies over the V stages, which are dead by then.
-//   fp32-weight kernels: a wavefront's 32 rows go out in fp32, 64 columns at a time, through a slice of the
-//     same size (32 x 64 fp32 = 32 x 128 bf16); at D = 64 the V stages are too small to lie under it.
-template <int NG, int D = HD, int TNK = TN>
+// copy of V in the workspace cost a pass over the whole cache per call, however few the rows (63 us for
+// 4000 new rows behind 196000 tokens).
+// Output rows go out through LDS (piece p of row r at p ^ (r & 15)), 256 bytes a row, over stages that are dead by then.
+// fp32-weight kernels: 64 columns at a time; at D = 64 the V stages are too small to lie under the output.
+template <int D, int TNK = TN>
 struct FlashLds {
   static constexpr int kStageElems = TNK * D;  // D = 128: 8192 bf16 = 16 KB
-  static constexpr int kStagesK = 2, kStagesV = NG == 2 ? 3 : 2;
+  static constexpr int kStages = 2;            // of K and of V
   static constexpr int kV = 0;
-  static constexpr int kK = kStagesV * kStageElems * 2;
-  static constexpr int kStagesEnd = (kStagesV + kStagesK) * kStageElems * 2;
-  static constexpr bool kOver = NG == 1 && D == 128;  // the output region lies over the V stages
-  static constexpr int kOutBytes = NG * TG * 256;
-  static constexpr int kOut = kOver ? 0 : kStagesEnd;                               // [NG][TG][256 bytes]
-  static constexpr int kRowOut = kOver ? kStagesEnd : kOut + kOutBytes;             // int64[NG][TG]
-  static constexpr int kRowLse = kRowOut + NG * TG * 8;                             // float[NG][TG]
-  // NG = 2: per wavefront 256 bytes for the next tile's record and 256 for its items, fetched by
-  // direct global->LDS loads while the current tile runs (they hold no registers meanwhile)
-  static constexpr int kAhead = kRowLse + NG * TG * 4;
-  static constexpr int kBytes = kAhead + (NG == 2 ? 8 * 512 : 0);
-  static constexpr int kThreads = NG * 256;
-  static constexpr int kRows = NG * TG;  // query rows per workgroup
-  static constexpr int kBlocksPerWave = kStageElems * 2 / 1024 / (4 * NG);  // 1 KB blocks of a staged tile per wavefront
+  static constexpr int kK = kStages * kStageElems * 2;
+  static constexpr int kStagesEnd = 2 * kStages * kStageElems * 2;
+  static constexpr bool kOver = D == 128;  // the output region lies over the V stages
+  static constexpr int kOutBytes = TG * 256;
+  static constexpr int kOut = kOver ? 0 : kStagesEnd;                    // [TG][256 bytes]
+  static constexpr int kRowOut = kOver ? kStagesEnd : kOut + kOutBytes;  // int64[TG]
+  static constexpr int kRowLse = kRowOut + TG * 8;                       // float[TG]
+  static constexpr int kBytes = kRowLse + TG * 4;
+  static constexpr int kBlocksPerWave = kStageElems * 2 / 1024 / 4;  // 1 KB blocks of a staged tile per wavefront
 };
-constexpr int TM = FlashLds<2>::kRows;  // rows of a routed tile
 
 #define SL_LDS_PTR(p) ((__attribute__((address_space(3))) void*)(p))
 
@@ -99,8 +85,6 @@ constexpr int TM = FlashLds<2>::kRows;  // rows of a routed tile
 // offsets (a lane past it stores zeros).  The flat form (global_load_lds) counts as an LDS operation
 // too, and the compiler then waits for every LDS read with lgkmcnt(0): the fragment reads that run four
 // MFMAs ahead were drained at every fourth MFMA.  With the buffer form those waits are lgkmcnt(3).
-// Measured: attention of a 256K prompt 27.09 -> 26.86 ms, the paper's geometry at 48K 4.75 -> 4.56 ms (its
-// masked kernel no longer spills); the long kernel is held to 1.93 GHz by its power, so stalls cost it little.
 typedef __amdgpu_buffer_rsrc_t BufferRsrc;
 __device__ __forceinline__ BufferRsrc buffer_of(const void* base, uint32_t bytes) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, bytes, 0x00020000);
@@ -110,15 +94,25 @@ __device__ __forceinline__ int64_t uniform64(int64_t v) {
   return (int64_t)(((uint64_t)hi << 32) | lo);
 }
 
-// Two transposing LDS reads: the lane's column of kv rows 0..3 and 4..7 behind p (its own block address).
+// Two transposing LDS reads: the lane's column of kv rows 0..3 and 4..7 behind p (its own block address).  (Without
+// __restrict__ the compiler knows nothing of what the reads may alias and waits for the next tile's staging loads in front of
+// the products: the paper's geometry at 48K 3.55 -> 3.51 ms, 4000 rows behind 196000 tokens 845 -> 833 us.)
 template <int D>
-__device__ __forceinline__ bf16x8 transposed8(const bf16_t* p) {
+__device__ __forceinline__ bf16x8 transposed8(const bf16_t* __restrict__ p) {
   typedef short s16x4 __attribute__((ext_vector_type(4)));
   typedef short s16x8 __attribute__((ext_vector_type(8)));
   typedef __attribute__((address_space(3))) s16x4* LdsPtr;
   const s16x4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LdsPtr)p);
   const s16x4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LdsPtr)(p + 4 * D));
   return __builtin_bit_cast(bf16x8, __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
+template <int D>
+__device__ __forceinline__ bf16x8 transposed8(uint32_t at) {  // at: address in LDS
+  return transposed8<D>((const bf16_t*)(const __attribute__((address_space(3))) bf16_t*)(uintptr_t)at);
+}
+__device__ __forceinline__ uint32_t lds_address(const void* p) {
+  return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)p;
 }
 
 __device__ __forceinline__ float pair_max(float x) {
@@ -340,10 +334,11 @@ __global__ __launch_bounds__(1024) void bucket_scan_kernel(const int* __restrict
                                                            int* __restrict__ item_off,
                                                            int* __restrict__ tile_off,
                                                            int* __restrict__ g_cursor, int B, int tm,
-                                                           int* __restrict__ flag) {
+                                                           int* __restrict__ flag, int* __restrict__ claims) {
   __shared__ int s_items[1024], s_tiles[1024];
   const int tid = threadIdx.x;
   if (flag && tid == 0) *flag = 0;
+  if (tid < 8) claims[32 * tid] = 0;
   const int per = (B + 1023) / 1024;
   const int b0 = tid * per, b1 = min(B, b0 + per);
   int ni = 0, nt = 0;
@@ -408,6 +403,7 @@ struct FlashArgs {
   const int* tile_off;
   const int4* tile_info;
   const int* items;
+  int* claims;      // [8][32]: tiles taken of each XCD's share
   bf16_t* part_o;   // bf16 partials
   float* part_of;   // fp32 partials (fp32-weight kernels)
   float* part_lse;
@@ -457,102 +453,37 @@ __device__ __forceinline__ int perm_row(int rho) {
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-// One tile (256 rows, 128 of the window and fp32-weight kernels) as seen by a lane: the kv head and kv range [kv_begin,
-// kv_end) shared by the workgroup (walked in kv tiles; what lies behind its end is masked or zero), and the lane's own
-// query column.
+// One tile of 128 rows as seen by a lane: the kv head and kv range [kv_begin, kv_end) shared by the workgroup (walked in kv
+// tiles; what lies behind its end is zero), and the lane's own query column.
 struct TileDesc {
   int kv;
   int64_t kv_begin, kv_end;
   int64_t q_off;      // element offset of the lane's Q vector
-  int64_t row_out;    // partial record index of the lane's column (fused merge: its row index
-                      // h*Lq + r), -1 = no row
-  int64_t first_pos;  // fused merge: position of the tile's first row; column x holds row x & row_mask of the tile
-  int row_mask;
-  int64_t i_q, lo_q;  // LOCAL: query position and start of its window
+  int64_t row_out;    // partial record index of the lane's column, -1 = no row
+  int64_t i_q, lo_q;  // the last and the first token that the row attends
 };
 
-// State a workgroup carries from one tile to the next: the rotating stage indices, whether the
-// tile's first K/V stage and Q fragments were already fetched by the previous tile's tail, and
-// the Q fragments themselves.
-struct FlashCarry {
-  int kb, vb;
-  bool primed;
-  bool pending;  // the previous tile's output still sits in LDS (routed tiles write it out a step later)
-  bf16x8 qf[8];
-};
-
-// Writes a wavefront's staged output rows (normalised partial o as bf16, lse) of a routed tile
-// from the group's LDS region to the partial buffers: 16 lanes per row, 16 bytes per lane.
-// Called when no direct global->LDS load is in flight (the compiler orders an LDS read after all
-// outstanding vector-memory operations once such loads exist).
-__device__ __forceinline__ void flush_routed_output(char* lds, int grp, int w4, int lane) {
-  using Lds = FlashLds<2>;
-  const ArgsPtr a = args_anew();
-  const bf16_t* const ost = reinterpret_cast<const bf16_t*>(lds + Lds::kOut) + grp * TG * HD;
-  const int64_t* const row_out = reinterpret_cast<const int64_t*>(lds + Lds::kRowOut) + grp * TG;
-  const float* const row_lse = reinterpret_cast<const float*>(lds + Lds::kRowLse) + grp * TG;
-  const int piece = lane & 15;
-  // two rows per lane at a time: the tile's accumulators are live here, registers are scarce
+// Direct global -> LDS loads of N blocks of 1 KB.
+template <int N>
+__device__ __forceinline__ void stage_blocks(bf16_t* dst, BufferRsrc from, const uint32_t (&off)[N]) {
 #pragma unroll
-  for (int ub = 0; ub < 8; ub += 2) {
-    int64_t outs[2];
-    uint4 vals[2];
-    float lses[2];
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int row = w4 * 32 + (ub + u) * 4 + (lane >> 4);
-      outs[u] = row_out[row];
-      lses[u] = row_lse[row];
-      vals[u] = *reinterpret_cast<const uint4*>(&ost[row * HD + ((piece ^ (row & 15)) << 3)]);
-    }
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      if (outs[u] >= 0) {
-        // streamed past the caches: the partials (gigabytes) are read back by a later kernel, and
-        // the K/V tiles keep the L2
-        store16_stream(a->part_o + outs[u] * HD + piece * 8, vals[u]);
-        if (piece == 0) __builtin_nontemporal_store(lses[u], &a->part_lse[outs[u]]);
-      }
-    }
-  }
+  for (int i = 0; i < N; ++i) __builtin_amdgcn_raw_ptr_buffer_load_lds(from, SL_LDS_PTR(dst + i * 512), 16, off[i], 0, 0, 0);
 }
 
-// One tile of NG*128 rows.  All threads call.  If has_next, request_next() issues the caller's
-// loads for the tile this workgroup processes afterwards and describe_next() turns them into
-// `next`: the first is called right after the first kv step's barrier (next to that step's K/V
-// loads, so the wait before the second step covers it), the second after the kv loop.
-//
-// The eight wavefronts form two groups of four (each group owns 128 rows, a wavefront 32
-// columns); SIMD s hosts wavefront s of both groups.  Both groups consume the same staged K/V
-// tiles, but the late group runs its PV product one kv tile behind:
-//     early, per kv tile i:   QK(i)    softmax(i)  PV(i)
-//     late,  per kv tile i:   PV(i-1)  QK(i)       softmax(i)          (+ PV(last) after the loop)
-// so that between two barriers the softmax arithmetic of one group runs in the shadow of the
-// other group's MFMAs instead of both groups asking for the matrix pipe at the same time.
-// When the kv loop is over, the first K/V stage and the Q fragments of the next tile are
-// requested before the output tile is normalised and staged in LDS; a routed tile's staged
-// output goes to HBM during the next tile's first kv step (c.pending), a window tile's at once.
-//
-// FINE: the softmax weights keep fp32 precision: each is split into three bf16 parts, which hold the 24 bits of its
-// mantissa between them, and V is multiplied with all three; the row sum is taken over the unsplit weights, partials
-// are written in fp32, and the output of a tile goes to HBM before the next one starts.
-template <int NG, bool LOCAL, bool FUSED, bool CLIP, int D = HD, bool FINE = false, int TT = TN, typename RequestNext,
-          typename DescribeNext>
-__device__ __forceinline__ void flash_tile(const FlashArgs& a, char* lds, const TileDesc& cur,
-                                           TileDesc& next, bool has_next, RequestNext&& request_next,
-                                           DescribeNext&& describe_next, FlashCarry& c) {
+// One tile of 128 rows of the fp32-weight kernels.  All threads call.  Every softmax weight is split into three bf16 parts,
+// which hold the 24 bits of its mantissa between them, and V is multiplied with all three; the row sum is taken over the
+// unsplit weights, partials are written in fp32.
+template <int D, int TT>
+__device__ __forceinline__ void flash_tile(const FlashArgs& a, char* const lds, const TileDesc& cur) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int uwave = __builtin_amdgcn_readfirstlane(wave);
-  const int grp = wave >> 2, w4 = wave & 3;  // grp 0 = early, 1 = late
   const int qc = lane & 31, hf = lane >> 5;
-  const int srow = w4 * 32 + qc;             // row inside the group's 128-row half tile
-  static_assert(NG == 1 || !FINE, "fp32 partials leave with their tile: one group's output region");
-  constexpr bool kMasked = LOCAL || CLIP;
-  using Lds = FlashLds<NG, D, TT>;
+  const int srow = wave * 32 + qc;
+  using Lds = FlashLds<D, TT>;
   constexpr int kStageElems = Lds::kStageElems;
   constexpr int PPR = D / 8, RPB = 64 / PPR;  // 16-byte pieces per staged row, rows per 1 KB block
   constexpr int NDT = D / 32, NKK = D / 16;   // 32-row output tiles, 16-deep steps of the QK product
-  constexpr int kStagesK = Lds::kStagesK, kStagesV = Lds::kStagesV, BPW = Lds::kBlocksPerWave;
+  constexpr int BPW = Lds::kBlocksPerWave;
   bf16_t* const ldsV = reinterpret_cast<bf16_t*>(lds + Lds::kV);
   bf16_t* const ldsK = reinterpret_cast<bf16_t*>(lds + Lds::kK);
 
@@ -567,34 +498,19 @@ __device__ __forceinline__ void flash_tile(const FlashArgs& a, char* lds, const 
     koff[i] = (uint32_t)((row * a.kvst + (pc ^ k_swizzle<D>(row)) * 8) * sizeof(bf16_t));
     voff[i] = (uint32_t)((row * a.kvst + (pc ^ v_swizzle<D>(row)) * 8) * sizeof(bf16_t));
   }
-  // wavefront w fills blocks w*BPW .. w*BPW + BPW-1 of both tiles
-  auto stage = [&](int kvh, int64_t t0, int64_t t_end, int kb, int vb) {
-    // rows past the end of the sequence (FINE: of the tile's range) lie beyond the buffer: zeros in LDS
-    // (masked later)
-    const int64_t stop = FINE ? t_end : a.L;
-    const int rows = __builtin_amdgcn_readfirstlane(stop - t0 < TT ? (int)(stop - t0) : TT);
-    const int64_t first = uniform64((int64_t)kvh * a.kvsh + t0 * a.kvst);
+  // wavefront w fills blocks w*BPW .. w*BPW + BPW-1 of both tiles; rows past the end of the tile's range are zeros in LDS
+  auto stage = [&](int64_t t0, int b) {
+    const int rows = __builtin_amdgcn_readfirstlane(cur.kv_end - t0 < TT ? (int)(cur.kv_end - t0) : TT);
+    const int64_t first = uniform64((int64_t)cur.kv * a.kvsh + t0 * a.kvst);
     const uint32_t bytes = (uint32_t)(((rows - 1) * a.kvst + D) * sizeof(bf16_t));
-    const BufferRsrc kr = buffer_of(a.K + first, bytes), vr = buffer_of(a.V + first, bytes);
-#pragma unroll
-    for (int i = 0; i < BPW; ++i)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(kr, SL_LDS_PTR(ldsK + kb * kStageElems + (uwave * BPW + i) * 512), 16,
-                                               koff[i], 0, 0, 0);
-#pragma unroll
-    for (int i = 0; i < BPW; ++i)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(vr, SL_LDS_PTR(ldsV + vb * kStageElems + (uwave * BPW + i) * 512), 16,
-                                               voff[i], 0, 0, 0);
+    stage_blocks(ldsK + b * kStageElems + uwave * BPW * 512, buffer_of(a.K + first, bytes), koff);
+    stage_blocks(ldsV + b * kStageElems + uwave * BPW * 512, buffer_of(a.V + first, bytes), voff);
   };
-  // Q row of a lane's column, as the B operand of S^T = K Q^T
-  auto load_q = [&](int64_t q_off) {
-    const bf16_t* qp = a.Q + q_off;
+  stage(cur.kv_begin, 0);
+  // Q row of the lane's column, as the B operand of S^T = K Q^T
+  bf16x8 qf[NKK];
 #pragma unroll
-    for (int kk = 0; kk < NKK; ++kk) c.qf[kk] = *reinterpret_cast<const bf16x8*>(qp + kk * 16 + hf * 8);
-  };
-  if (!c.primed) {
-    stage(cur.kv, cur.kv_begin, cur.kv_end, c.kb, c.vb);
-    load_q(cur.q_off);
-  }
+  for (int kk = 0; kk < NKK; ++kk) qf[kk] = *reinterpret_cast<const bf16x8*>(a.Q + cur.q_off + kk * 16 + hf * 8);
 
   f32x16 o[NDT];
 #pragma unroll
@@ -603,12 +519,7 @@ __device__ __forceinline__ void flash_tile(const FlashArgs& a, char* lds, const 
     for (int r = 0; r < 16; ++r) o[dt][r] = 0.f;
   float m = -INFINITY, l = 0.f;  // m in log2 units of the scaled logit
   constexpr int NS = TT / 32, NP = TT / 16;  // 32-row score tiles, weight fragments
-  bf16x8 pb[NP];                 // P^T fragments; the late group carries them to the next kv tile
-#pragma unroll
-  for (int ks = 0; ks < NP; ++ks)
-#pragma unroll
-    for (int e = 0; e < 8; ++e) pb[ks][e] = (__bf16)0.f;
-  bf16x8 pl[FINE ? NP : 1], pm[FINE ? NP : 1];  // FINE: what pb leaves of the weights, and what that leaves
+  bf16x8 pb[NP], pl[NP], pm[NP];  // P^T fragments: the weights' leading parts, what those leave, and what that leaves
 
   const int krow = perm_row(qc);
   const int kswz = k_swizzle<D>(krow);  // swizzle key of this lane's K rows (32*sub does not change it)
@@ -626,9 +537,9 @@ __device__ __forceinline__ void flash_tile(const FlashArgs& a, char* lds, const 
     const int64_t d = t - cur.kv_begin;
     return (int)(d < -1 ? -1 : d > (1 << 30) ? (1 << 30) : d);
   };
-  const int lo_r = kMasked ? offset_of(cur.lo_q) : 0, hi_r = kMasked ? offset_of(cur.i_q) : 0;
+  const int lo_r = offset_of(cur.lo_q), hi_r = offset_of(cur.i_q);
 
-  // S^T = K Q^T (two 32-row halves of the tile), mask, running maximum, exponentials -> pb.
+  // S^T = K Q^T (32-row parts of the tile), mask, running maximum, exponentials -> pb, pl, pm.
   // LDS fragment reads run four MFMAs ahead (0x100 = LDS read, 0x008 = MFMA).
   // base: the kv tile's offset from the tile's first token.
   auto qk_softmax = [&](const bf16_t* kt, int base) {
@@ -643,7 +554,7 @@ __device__ __forceinline__ void flash_tile(const FlashArgs& a, char* lds, const 
       for (int sub = 0; sub < NS; ++sub) {
         const bf16x8 ka = *reinterpret_cast<const bf16x8*>(
             &kt[(32 * sub + krow) * D + (((2 * kk + hf) ^ kswz) << 3)]);
-        s[sub] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka, c.qf[kk], s[sub], 0, 0, 0);
+        s[sub] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka, qf[kk], s[sub], 0, 0, 0);
       }
     __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
 #pragma unroll
@@ -656,10 +567,9 @@ __device__ __forceinline__ void flash_tile(const FlashArgs& a, char* lds, const 
     // other wavefront; that one needs a slot every 32 cycles, this one needs most of them.
     __builtin_amdgcn_s_setprio(3);
 
-    // Per-row ranges (the causal window, a span clipped behind a lower one, an anchor's span): only the
-    // tiles at the ends of a wavefront's ranges are masked, one unsigned compare per score.  (With two
-    // 64-bit compares per score on every tile the paper's geometry at 48K took 4.50 ms, now 3.68.)
-    if (kMasked && __builtin_amdgcn_ballot_w64(lo_r > base || hi_r < base + TT - 1) != 0ull) {
+    // Per-row ranges (the causal window, a span clipped behind a lower one): only the tiles at the ends of a wavefront's
+    // ranges are masked, one unsigned compare per score.
+    if (__builtin_amdgcn_ballot_w64(lo_r > base || hi_r < base + TT - 1) != 0ull) {
       const uint32_t width = hi_r >= lo_r ? (uint32_t)(hi_r - lo_r) : 0u;
       const uint32_t u = hi_r >= lo_r ? (uint32_t)(base + 8 * hf - lo_r) : 0x80000000u;
 #pragma unroll
@@ -695,26 +605,15 @@ __device__ __forceinline__ void flash_tile(const FlashArgs& a, char* lds, const 
 #pragma unroll
       for (int e = 0; e < 8; ++e) p[e] = fast_exp2(fmaf(s[ks >> 1][8 * (ks & 1) + e], sc, nm));
       pb[ks] = __builtin_convertvector(p, bf16x8);
-      if constexpr (FINE) {
-        const f32x8 rest = p - __builtin_convertvector(pb[ks], f32x8);
-        pl[ks] = __builtin_convertvector(rest, bf16x8);
-        pm[ks] = __builtin_convertvector(rest - __builtin_convertvector(pl[ks], f32x8), bf16x8);
+      const f32x8 rest = p - __builtin_convertvector(pb[ks], f32x8);
+      pl[ks] = __builtin_convertvector(rest, bf16x8);
+      pm[ks] = __builtin_convertvector(rest - __builtin_convertvector(pl[ks], f32x8), bf16x8);
 #pragma unroll
-        for (int e = 0; e < 8; ++e) l += p[e];
-        continue;
-      }
-      // the row sum is taken over the rounded weights, the ones the PV product uses
-#pragma unroll
-      for (int e = 0; e < 8; e += 2) {
-        typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-        const bf16x2 pr = {pb[ks][e], pb[ks][e + 1]};
-        const bf16x2 one = {(__bf16)1.0f, (__bf16)1.0f};
-        l = __builtin_amdgcn_fdot2_f32_bf16(pr, one, l, false);
-      }
+      for (int e = 0; e < 8; ++e) l += p[e];
     }
     __builtin_amdgcn_s_setprio(0);
   };
-  // O^T += V^T P^T with the P^T fragments in pb
+  // O^T += V^T P^T
   auto pv = [&](const bf16_t* vt) {
 #pragma unroll
     for (int ks = 0; ks < NP; ++ks)
@@ -722,12 +621,10 @@ __device__ __forceinline__ void flash_tile(const FlashArgs& a, char* lds, const 
       for (int dt = 0; dt < NDT; ++dt) {
         const bf16x8 va = transposed8<D>(vt + vlane[dt] + 16 * ks * D);
         o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, pb[ks], o[dt], 0, 0, 0);
-        if constexpr (FINE) {
-          o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, pl[ks], o[dt], 0, 0, 0);
-          o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, pm[ks], o[dt], 0, 0, 0);
-        }
+        o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, pl[ks], o[dt], 0, 0, 0);
+        o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, pm[ks], o[dt], 0, 0, 0);
       }
-    constexpr int kPer = FINE ? 3 : 1;  // MFMAs per fragment
+    constexpr int kPer = 3;  // MFMAs per fragment
     __builtin_amdgcn_sched_group_barrier(0x100, 8, 1);
 #pragma unroll
     for (int i = 0; i < NP * NDT - 4; ++i) {
@@ -737,138 +634,795 @@ __device__ __forceinline__ void flash_tile(const FlashArgs& a, char* lds, const 
     __builtin_amdgcn_sched_group_barrier(0x008, 4 * kPer, 1);
   };
 
-  // a kv tile that none of the wavefront's rows attends is passed over (its weights would all be 0)
-  auto attends = [&](int base) {
-    return !kMasked || __builtin_amdgcn_ballot_w64(lo_r <= base + TT - 1 && hi_r >= base && hi_r >= lo_r) != 0ull;
-  };
-  int kb = c.kb, vb = c.vb, vb_prev = c.vb;
-  // The late group of a bucket's last tile often has no row at all: it then only stages.  (4000 rows x 16
-  // slots, six tiles a bucket: 885 -> 850 us for the call.  The same test in the early group, per
-  // wavefront, cost the long prompt 1 %.)
-  const bool idle = NG == 2 && grp == 1 && __builtin_amdgcn_ballot_w64(cur.row_out >= 0) == 0ull;
-  bool owes_pv = false;  // late group: the previous kv tile's PV product is still to be taken
+  int b = 0;
   for (int64_t t0 = cur.kv_begin; t0 < cur.kv_end; t0 += TT) {
-    // After the barrier the tile of this iteration is visible to every wavefront, every wavefront
-    // is done with the K stage of the previous tile and the late group with the V stage before
-    // that: exactly the stages that the next tile goes into.
+    // After the barrier the tile of this iteration is visible to every wavefront, and every wavefront is done with the
+    // stage of the previous one, which the next tile goes into.
     __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
     __syncthreads();
-    const int kb1 = kb == kStagesK - 1 ? 0 : kb + 1, vb1 = vb == kStagesV - 1 ? 0 : vb + 1;
-    if (NG == 2 && !LOCAL && c.pending) {
-      // the previous tile's output: written out here, a step after it was staged, so that the wait
-      // at the top of this tile did not have to cover its stores
-      flush_routed_output(lds, grp, w4, lane);
-      c.pending = false;
-    }
-    if (t0 + TT < cur.kv_end) stage(cur.kv, t0 + TT, cur.kv_end, kb1, vb1);
-    if (NG == 2 && has_next && t0 == cur.kv_begin) request_next();
+    if (t0 + TT < cur.kv_end) stage(t0 + TT, b ^ 1);
+    // a kv tile that none of the wavefront's rows attends is passed over (its weights would all be 0)
     const int base = (int)(t0 - cur.kv_begin);
-    const bool mine = attends(base);
-    if (grp == 0) {
-      if (mine) {
-        qk_softmax(ldsK + kb * kStageElems, base);
-        pv(ldsV + vb * kStageElems);
-      }
-    } else if (!idle) {
-      if (owes_pv) pv(ldsV + vb_prev * kStageElems);
-      if (mine) qk_softmax(ldsK + kb * kStageElems, base);
-      owes_pv = mine;
+    if (__builtin_amdgcn_ballot_w64(lo_r <= base + TT - 1 && hi_r >= base && hi_r >= lo_r) != 0ull) {
+      qk_softmax(ldsK + b * kStageElems, base);
+      pv(ldsV + b * kStageElems);
     }
-    vb_prev = vb;
-    kb = kb1;
-    vb = vb1;
+    b ^= 1;
   }
-  // Every wavefront is past its last QK: all K stages and the Q fragments are dead, and so is
-  // every V stage except the last tile's (the late group still owes its PV).  Request the next
-  // tile's first stage and Q fragments now; they land while this tile is written out.
   __syncthreads();
-  c.kb = kb;
-  c.vb = vb;
-  c.primed = NG == 2 && has_next;  // NG = 1: the output region lies over the stages, nothing is fetched ahead
-  if (NG == 2 && has_next) {
-    next = describe_next();
-    stage(next.kv, next.kv_begin, next.kv_end, kb, vb);
-    load_q(next.q_off);
-  }
-  // From here to the end of the tile the late group is the critical path (it still owes a PV):
-  // its wavefronts go first wherever both groups want an issue slot.
-  if (NG == 2 && grp == 1) __builtin_amdgcn_s_setprio(2);
-  if (grp == 1 && owes_pv) pv(ldsV + vb_prev * kStageElems);  // the late group's last PV
 
-  // epilogue, wavefront-local (no workgroup barrier): normalise, stage the wavefront's 32 rows as
-  // [row][d] bf16 in its own slice of the group's LDS region (swizzled 16-byte pieces), then
-  // write 16 lanes per row, 16 bytes per lane.  LDS operations of one wavefront complete in
-  // issue order, so the reads below see the writes of the other lanes.
+  // epilogue, wavefront-local (no workgroup barrier): normalise and write the wavefront's 32 rows in fp32, 64 columns at a
+  // time, through its own slice of the output region (swizzled 16-byte pieces): 16 lanes per row, 16 bytes per lane.  LDS
+  // operations of one wavefront complete in issue order, so the reads below see the writes of the other lanes.
   const float lt = pair_sum(l);
   const float inv = 1.f / lt;
-  bf16_t* const ost = reinterpret_cast<bf16_t*>(lds + Lds::kOut) + grp * TG * HD;  // 256 bytes per row
-  int64_t* const row_out = reinterpret_cast<int64_t*>(lds + Lds::kRowOut) + grp * TG;
-  float* const row_lse = reinterpret_cast<float*>(lds + Lds::kRowLse) + grp * TG;
+  float* const fst = reinterpret_cast<float*>(lds + Lds::kOut);  // 256 bytes per row
+  int64_t* const row_out = reinterpret_cast<int64_t*>(lds + Lds::kRowOut);
+  float* const row_lse = reinterpret_cast<float*>(lds + Lds::kRowLse);
   if (hf == 0) {
     row_lse[srow] = (m + __log2f(lt)) * kLn2;
     row_out[srow] = cur.row_out;
   }
-  if constexpr (FINE) {
-    // fp32 partial, 64 columns at a time: 16 lanes per row, 16 bytes per lane
-    float* const fst = reinterpret_cast<float*>(ost);
-    const ArgsPtr b = args_anew();
-    const int piece = lane & 15;
+  const ArgsPtr args = args_anew();
+  const int piece = lane & 15;
 #pragma unroll
-    for (int half = 0; half < D / 64; ++half) {
+  for (int half = 0; half < D / 64; ++half) {
 #pragma unroll
-      for (int dd = 0; dd < 2; ++dd)
+    for (int dd = 0; dd < 2; ++dd)
 #pragma unroll
-        for (int g4 = 0; g4 < 4; ++g4) {
-          f32x4 v;
+      for (int g4 = 0; g4 < 4; ++g4) {
+        f32x4 v;
 #pragma unroll
-          for (int e = 0; e < 4; ++e) v[e] = o[2 * half + dd][4 * g4 + e] * inv;
-          *reinterpret_cast<f32x4*>(&fst[srow * 64 + (((8 * dd + 2 * g4 + hf) ^ (srow & 15)) << 2)]) = v;
-        }
-      __builtin_amdgcn_wave_barrier();
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const int row = w4 * 32 + u * 4 + (lane >> 4);
-        const int64_t at = row_out[row];
-        const uint4 v = *reinterpret_cast<const uint4*>(&fst[row * 64 + ((piece ^ (row & 15)) << 2)]);
-        if (at >= 0) {
-          // past the caches, like the bf16 partials: they are gigabytes, the K/V tiles keep the L2
-          store16_stream(b->part_of + at * D + half * 64 + piece * 4, v);
-          if (half == 0 && piece == 0) b->part_lse[at] = row_lse[row];
-        }
+        for (int e = 0; e < 4; ++e) v[e] = o[2 * half + dd][4 * g4 + e] * inv;
+        *reinterpret_cast<f32x4*>(&fst[srow * 64 + (((8 * dd + 2 * g4 + hf) ^ (srow & 15)) << 2)]) = v;
       }
-      __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int row = wave * 32 + u * 4 + (lane >> 4);
+      const int64_t at = row_out[row];
+      const uint4 v = *reinterpret_cast<const uint4*>(&fst[row * 64 + ((piece ^ (row & 15)) << 2)]);
+      if (at >= 0) {
+        // past the caches, like the bf16 partials: they are gigabytes, the K/V tiles keep the L2
+        store16_stream(args->part_of + at * D + half * 64 + piece * 4, v);
+        if (half == 0 && piece == 0) args->part_lse[at] = row_lse[row];
+      }
     }
-    __builtin_amdgcn_s_setprio(0);
-    return;
+    __builtin_amdgcn_wave_barrier();
   }
-#pragma unroll
-  for (int dt = 0; dt < NDT; ++dt)
-#pragma unroll
-    for (int g4 = 0; g4 < 4; ++g4) {
-      const int unit = (4 * dt + g4) ^ (srow & 15);
-      f32x4 v;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) v[e] = o[dt][4 * g4 + e] * inv;
-      const bf16x4 w = __builtin_convertvector(v, bf16x4);
-      *reinterpret_cast<bf16x4*>(&ost[srow * HD + unit * 8 + 4 * hf]) = w;
+}
+
+// Routed spans of the fp32-weight kernels: workgroups walk the tile list.  XCD x (workgroups with
+// blockIdx % 8 == x) owns the contiguous chunk [x*T/8, (x+1)*T/8) of the tile list; its
+// workgroups walk the chunk interleaved, so at any moment they sit on neighbouring tiles -- the
+// same one or two buckets -- and share the span through that XCD's L2.  Spans of any length at any offset; a row's range is
+// its whole span unless a.clip says that spans of a row overlap in one softmax: it starts then behind the end of the nearest
+// lower span that the row lists, so that every token of the union counts once.  Several workgroups per
+// compute unit: one's tile ends run beside the other's kv loop.
+template <int D, int TT>
+__global__ __launch_bounds__(256, fine_blocks(TT)) void span_flash_routed_kernel(const FlashArgs a) {
+  extern __shared__ __align__(16) char lds[];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int qrow = wave * 32 + (lane & 31);
+  const int64_t T = a.tile_off[a.Hq / a.G * a.n];
+  const int NWL = gridDim.x / 8;  // workgroups per XCD (the grid is a multiple of 8)
+  const int xcd = blockIdx.x % 8, wl = blockIdx.x / 8;
+  const int64_t t_end = T * (xcd + 1) / 8;
+  for (int64_t t = T * xcd / 8 + wl; t < t_end; t += NWL) {
+    const ArgsPtr p = args_anew();
+    const int4 info = p->tile_info[t];
+    const int item = p->items[t * TG + qrow];
+    TileDesc d;
+    d.kv = info.x / p->n;
+    const int j = info.x % p->n;
+    d.kv_end = (int64_t)(j + 1) * p->A;
+    d.kv_begin = d.kv_end - p->S > 0 ? d.kv_end - p->S : 0;
+    const int rowid = item >> 5, slot = item & 31;
+    const int hl = rowid / (int)p->Lq;
+    const int64_t r = rowid - (int64_t)hl * p->Lq;
+    const int h = d.kv * p->G + hl;
+    d.q_off = h * p->qsh + r * p->qst;
+    d.row_out = qrow < info.z ? ((int64_t)h * p->Lq + r) * (p->topk + 1) + slot : -1;
+    d.i_q = d.kv_end - 1;
+    d.lo_q = d.kv_begin;
+    if (p->clip) {
+      const int64_t c = (p->q_pos0 + r) / p->A;
+      const int32_t* irow = p->idx + ((int64_t)h * p->Lq + r) * p->topk;
+      for (int s2 = 0; s2 < p->topk; ++s2) {
+        const int64_t jj = irow[s2];
+        if (jj >= 0 && jj < c && jj < j && (jj + 1) * p->A > d.lo_q) d.lo_q = (jj + 1) * p->A;
+      }
     }
-  __builtin_amdgcn_wave_barrier();
-  if constexpr (FUSED) {
-    // Local-window tile with the merge fused in (topk <= 8): the lane that would store 16 bytes
-    // of the window's partial instead loads the same 16 bytes of the row's routed partials
-    // (written by the routed kernel, which ran before on the stream), does the log-sum-exp merge
-    // and stores the final output.  Every load is issued before the first dependent use; slots
-    // that take no part may hold anything and are discarded by selects, never by arithmetic.
-    const int topk = a.topk, nslot = topk + 1;
+    flash_tile<D, TT>(a, lds, d);
+    __syncthreads();  // the next tile's stages lie over the output slices of all wavefronts
+  }
+}
+
+// ------------------------------------------------------------------ tiles of the kernels with bf16 weights
+// A wavefront has CB blocks of 32 query columns, a workgroup four wavefronts; two workgroups share a compute unit, so that one's
+// tile ends run beside the other's kv loop and their softmax and matrix phases take turns by themselves.
+//
+// What bounds them.  With one block of columns a product needs a fragment of 1 KB from the LDS, the LDS's whole rate; with two
+// blocks half of that, and what is left is the power: the matrix pipes are busy half the time at 1.83 GHz, where a dense bf16
+// product of 8192^3 reaches 1230 TFLOP/s and spans of 2048 tokens 1100 to 1150 here (980 with eight wavefronts of one block in two
+// phase-shifted groups, one workgroup per compute unit).  A tile costs 1.8 us per kv step of 64 tokens and 5 us around them (2.0
+// and 6 then): the gathered queries, the output.  Beside the other workgroup's products an instruction takes 8 cycles, an
+// exponential 13, of which a step has what a lane's 64 scores need and little else.
+// Routed part of 262144 rows, top-8, spans of 512 20.5 -> 17.8 ms; of 4000 rows x 16 spans of 512 behind 196000 tokens 700 -> 600
+// us; of 49157 rows on the paper's geometry 2250 -> 2000, its windows 905 -> 780.
+//
+// Two blocks of columns leave no register for what can be had again: values that only address things are derived anew where
+// they are used.
+__device__ __forceinline__ int anew(int x) {
+  asm volatile("" : "+v"(x));
+  return x;
+}
+__device__ __forceinline__ int lane_anew() {
+  int x;
+  asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=&v"(x));
+  return x;
+}
+struct WideLds {
+  static constexpr int kStage = TN * HD;          // K and V tile of a stage, one after the other
+  static constexpr int kAhead = 4 * kStage * 2;   // per wavefront: the next tile's record (256 bytes) and items
+  static constexpr int kRow = kAhead + 4 * 512;   // per wavefront: int row[2][64], int q[64], float lse[64], ranges
+  static constexpr int kRange = kRow + 4 * 2048;  // int2[2][4]
+  static constexpr int kClaim = kRange + 64;
+  static constexpr int kBytes = kClaim + 16;
+};
+
+struct Range {  // of a tile; the last four: over the rows of a wavefront
+  int kv, begin, end;
+  int live;              // the wavefront has a row at all
+  int any_lo, any_last;  // the first and last token that any of its rows attends
+  int all_lo, all_last;  // the range that all of them attend
+  // kv rows that no row of the wavefront attends are passed over
+  template <bool MASKED, int ROWS>
+  __device__ __forceinline__ bool attended(int t0) const {
+    return live != 0 && (!MASKED || (t0 + ROWS - 1 >= any_lo && t0 <= any_last));
+  }
+};
+
+// The state and the steps of a wavefront's columns.
+template <int CB>
+struct WideTile {
+  // kv rows at a time: 64 for one block of columns, 32 for two
+  static constexpr int KB = 2 / CB, kRows = 32 * KB, NP = 2 * KB;
+  bf16x8 qf[CB][8];
+  f32x16 o[CB][4], s[CB][KB];
+  float m[CB];
+  f32x4 l[CB];
+  bf16x8 pb[CB][NP];
+  int kbase, vbase;
+  uint32_t one;
+  float sc;
+
+  __device__ __forceinline__ void setup(float scale) {
+    sc = scale;
+    const int lane = lane_anew();
+    const int qc = lane & 31, hf = lane >> 5;
+    one = (lane & 3) == 0 && (((lane >> 2) ^ (lane >> 4)) & 1) == 0 ? 0x3f803f80u : 0u;
+    const int krow = perm_row(qc);
+    kbase = 2 * (krow * HD + ((hf ^ k_swizzle<HD>(krow)) << 3));
+    const int vrow = (lane & 15) >> 2;
+    vbase = 2 * ((8 * hf + vrow) * HD + (((2 * ((lane >> 4) & 1) + ((lane & 3) >> 1)) ^ v_swizzle<HD>(vrow)) << 3) + 4 * (lane & 1));
+  }
+  __device__ __forceinline__ void clear() {
 #pragma unroll
-    for (int half = 0; half < 2; ++half) {
+    for (int cb = 0; cb < CB; ++cb) {
+      m[cb] = -INFINITY;
+      l[cb] = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) o[cb][dt][r] = 0.f;
+    }
+  }
+  // row_q: element offsets of the wavefront's queries
+  __device__ __forceinline__ void load_q(const bf16_t* Q, const int* row_q) {
+    const int ln = lane_anew(), hf = ln >> 5;
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb) {
+      const bf16_t* const qp = Q + (uint32_t)row_q[cb * 32 + (ln & 31)] + hf * 8;
+#pragma unroll
+      for (int kk = 0; kk < 8; ++kk) qf[cb][kk] = *reinterpret_cast<const bf16x8*>(qp + kk * 16);
+    }
+  }
+  __device__ __forceinline__ void qk(const bf16_t* kt) {
+    const uint32_t at = lds_address(kt) + anew(kbase);
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+      for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) s[cb][kb][r] = 0.f;
+#pragma unroll
+    for (int kk = 0; kk < 8; ++kk)
+#pragma unroll
+      for (int kb = 0; kb < KB; ++kb) {
+        const bf16x8 ka = *reinterpret_cast<const __attribute__((address_space(3))) bf16x8*>((at ^ (kk << 5)) + 64 * HD * kb);
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb) s[cb][kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka, qf[cb][kk], s[cb][kb], 0, 0, 0);
+      }
+    // fragment reads run four MFMAs ahead (0x100 = LDS read, 0x008 = MFMA)
+    __builtin_amdgcn_sched_group_barrier(0x100, 4 / CB, 0);
+#pragma unroll
+    for (int i = 0; i < 8 * KB - 4 / CB; ++i) {
+      __builtin_amdgcn_sched_group_barrier(0x008, CB, 0);
+      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+    }
+    __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
+  }
+  // Weights are taken against a bound of the column's scores (log2 units), which moves to the maximum + 8 when a score
+  // passes it, and is looked at every 32 kv rows, whatever the number of blocks, so that a row's result does not depend on the
+  // form that takes it.  Weights lie in [0, 1]; the clamp that makes sure of it also keeps what is not a number out of the row
+  // sums, whose product mixes columns.  A score that is not a number makes the bound one, and with it the column's output.
+  __device__ __forceinline__ float highest(int cb, int kb) const {
+    float mx = s[cb][kb][0];
+#pragma unroll
+    for (int r = 1; r < 16; ++r) mx = __builtin_elementwise_maximum(mx, s[cb][kb][r]);
+    auto pair = __builtin_amdgcn_permlane32_swap(__float_as_int(mx), __float_as_int(mx), false, false);
+    return __builtin_elementwise_maximum(__int_as_float(pair[0]), __int_as_float(pair[1])) * sc;
+  }
+  __device__ __forceinline__ bool passed(const float (&mx)[CB]) const {
+    bool any = !(mx[0] <= m[0]);
+    if (CB == 2) any = any || !(mx[CB - 1] <= m[CB - 1]);
+    return __builtin_amdgcn_ballot_w64(any) != 0ull;
+  }
+  __device__ __forceinline__ void move_bounds(const float (&mx)[CB]) {
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb) {
+      const bool grow = !(mx[cb] <= m[cb]);
+      const float to = grow ? mx[cb] + 8.f : m[cb];
+      const float alpha = grow ? fast_exp2(m[cb] - to) : 1.f;
+      m[cb] = to;
+      l[cb][0] *= alpha;
+#pragma unroll
+      for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) o[cb][dt][r] *= alpha;
+    }
+  }
+  __device__ __forceinline__ void weights(int kb) {
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb) {
+      const float nm = m[cb] == -INFINITY ? 0.f : -m[cb];
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks) {
+        f32x8 p;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) p[e] = __builtin_amdgcn_fmed3f(fast_exp2(fmaf(s[cb][kb][8 * ks + e], sc, nm)), 0.f, 1.f);
+        pb[cb][2 * kb + ks] = __builtin_convertvector(p, bf16x8);
+      }
+    }
+  }
+  // Row sums of the rounded weights, as a product with ones: the columns of a 16x16x32 product are columns n and n + 16 of the
+  // weights, the latter as kv rows 8 .. 15 and 24 .. 31; row 0 and 8 of A ask for the former, row 4 and 12 for the latter, so that
+  // the first accumulator of every lane is its own column's sum, of both halves.  (Two-element dot instructions run on the
+  // matrix pipe too and take 22 cycles each beside the other workgroup's products, 350 of the 1500 that 32 kv rows took.)
+  template <int B>  // block of 32 kv rows
+  __device__ __forceinline__ void pv(const bf16_t* vt) {
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    const uint32_t x = (uint32_t)anew((int)one);
+    const bf16x8 ones = __builtin_bit_cast(bf16x8, (u32x4){x, x, x, x});
+#pragma unroll
+    for (int ks = 2 * B; ks < 2 * B + 2; ++ks)  // (while the first fragments are on their way)
+#pragma unroll
+      for (int cb = 0; cb < CB; ++cb) l[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pb[cb][ks], l[cb], 0, 0, 0);
+    const uint32_t at = lds_address(vt) + anew(vbase);
+#pragma unroll
+    for (int ks = 2 * B; ks < 2 * B + 2; ++ks)
+#pragma unroll
+      for (int dt = 0; dt < 4; ++dt) {
+        const bf16x8 va = transposed8<HD>((at ^ (dt << 6)) + 32 * ks * HD);
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb) o[cb][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, pb[cb][ks], o[cb][dt], 0, 0, 0);
+      }
+    __builtin_amdgcn_sched_group_barrier(0x100, 8 / CB, 1);
+#pragma unroll
+    for (int i = 0; i < 8 - 4 / CB; ++i) {
+      __builtin_amdgcn_sched_group_barrier(0x008, CB, 1);
+      __builtin_amdgcn_sched_group_barrier(0x100, 2, 1);
+    }
+    __builtin_amdgcn_sched_group_barrier(0x008, 4, 1);
+  }
+  // What follows the scores of the kv rows from t0 on: masks, weights, O^T += V^T P^T.  The vector instructions compete for
+  // issue slots with the products of the SIMD's other wavefront; that one needs a slot every 32 cycles, this one most.
+  template <bool MASKED>
+  __device__ __forceinline__ void attend(int t0, const Range& r, const int* row_range, const bf16_t* vt) {
+    __builtin_amdgcn_s_setprio(3);
+    // per-row ranges: only where not all rows attend
+    if (MASKED && (t0 < r.all_lo || t0 + kRows - 1 > r.all_last)) {
+      const int ln = lane_anew();
+#pragma unroll
+      for (int cb = 0; cb < CB; ++cb) {
+        const int lo = row_range[32 * cb + (ln & 31)], last = row_range[128 + 32 * cb + (ln & 31)];
+        const uint32_t width = last >= lo ? (uint32_t)(last - lo) : 0u;
+        const uint32_t u = last >= lo ? (uint32_t)(t0 + 8 * (ln >> 5) - lo) : 0x80000000u;
+#pragma unroll
+        for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+          for (int e = 0; e < 16; ++e)
+            s[cb][kb][e] = u + (uint32_t)(32 * kb + 16 * (e >> 3) + (e & 7)) <= width ? s[cb][kb][e] : -INFINITY;
+      }
+    }
+    float mx[CB];
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb) mx[cb] = highest(cb, 0);
+    if constexpr (KB == 1) {
+      if (passed(mx)) move_bounds(mx);
+      weights(0);
+      __builtin_amdgcn_s_setprio(0);
+      pv<0>(vt);
+    } else {
+      const float second[CB] = {highest(0, KB - 1)}, both[CB] = {__builtin_elementwise_maximum(mx[0], second[0])};
+      const bool any = passed(both);  // rare: both halves' weights are there before the first product otherwise
+      if (any && passed(mx)) move_bounds(mx);
+      weights(0);
+      if (!any) weights(KB - 1);
+      __builtin_amdgcn_s_setprio(0);
+      pv<0>(vt);
+      if (any) {
+        if (passed(second)) move_bounds(second);
+        weights(KB - 1);
+      }
+      pv<KB - 1>(vt);
+    }
+  }
+  // The normalised output of 32 columns to LDS, [32][HD] bf16 with swizzled 16-byte pieces, and their lse.
+  __device__ __forceinline__ void stage_output(int cb, bf16_t* ost, float* row_lse) {
+    const int ln = lane_anew(), qc = ln & 31, hf = ln >> 5;
+    const float lt = l[cb][0];
+    const float inv = 1.f / lt;
+    if (hf == 0) row_lse[cb * 32 + qc] = (m[cb] + __log2f(lt)) * kLn2;
+#pragma unroll
+    for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+      for (int g4 = 0; g4 < 4; ++g4) {
+        const int unit = (4 * dt + g4) ^ (qc & 15);
+        f32x4 v;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = o[cb][dt][4 * g4 + e] * inv;
+        *reinterpret_cast<bf16x4*>(&ost[qc * HD + unit * 8 + 4 * hf]) = __builtin_convertvector(v, bf16x4);
+      }
+    __builtin_amdgcn_wave_barrier();
+  }
+  // staged output rows -> their partials: out = record of each row, -1 = none
+  __device__ __forceinline__ void write_output(int cb, const bf16_t* ost, const int* out, bf16_t* part_o) {
+    const int ln = lane_anew(), piece = ln & 15;
+#pragma unroll
+    for (int ub = 0; ub < 8; ub += 4) {
+      int outs[4];
+      bf16x8 vals[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int row = (ub + u) * 4 + (ln >> 4);
+        outs[u] = out[cb * 32 + row];
+        vals[u] = *reinterpret_cast<const bf16x8*>(&ost[row * HD + ((piece ^ (row & 15)) << 3)]);
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (outs[u] >= 0) store16_stream(part_o + (int64_t)outs[u] * HD + piece * 8, __builtin_bit_cast(uint4, vals[u]));
+    }
+    __builtin_amdgcn_wave_barrier();
+  }
+};
+
+// (LDS operations only: a fence would wait for the stores)
+__device__ __forceinline__ void lds_barrier() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
+// Direct global -> LDS loads of a K and a V tile of 64 rows by four wavefronts, K at dst, V behind it.  BOUNDED: rows may lie
+// behind the end of the sequence (zeros).  ANEW: offsets and arguments are derived where they are used (two blocks of columns).
+template <bool BOUNDED, bool ANEW>
+struct WideStage {
+  BufferRsrc kr, vr;
+  uint32_t row, kp, vp, step;
+  __device__ __forceinline__ WideStage(int wave, int kvh, int t0) {
+    const ArgsPtr a = ANEW ? args_anew() : (ArgsPtr)__builtin_amdgcn_kernarg_segment_ptr();
+    const int rows = __builtin_amdgcn_readfirstlane(a->L - t0 < TN ? (int)(a->L - t0) : TN);
+    const int64_t first = uniform64((int64_t)kvh * a->kvsh + t0 * a->kvst);
+    const uint32_t bytes = (uint32_t)(((rows - 1) * a->kvst + HD) * sizeof(bf16_t));
+    kr = buffer_of(a->K + first, bytes);
+    vr = buffer_of(a->V + first, bytes);
+    // block i of the wavefront holds rows 16 * wave + 4 * i + lane / 16: what depends on i is scalar, but for K's swizzle
+    const int ln = ANEW ? lane_anew() : (int)(threadIdx.x & 63);
+    step = 4 * (uint32_t)a->kvst * (uint32_t)sizeof(bf16_t);
+    row = (uint32_t)(wave * 16 + ln / 16) * ((uint32_t)a->kvst * (uint32_t)sizeof(bf16_t));
+    kp = ((ln ^ (ln >> 4)) & 15) << 4;
+    vp = row + (((ln & 15) ^ ((ln >> 4) << 2)) << 4);
+  }
+  __device__ __forceinline__ void issue(bf16_t* dst, int wave) const {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(kr, SL_LDS_PTR(dst + (wave * 4 + i) * 512), 16,
+                                               row + (kp ^ (i << 6)) + (BOUNDED ? i * step : 0), BOUNDED ? 0 : i * step, 0, 0);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(vr, SL_LDS_PTR(dst + WideLds::kStage + (wave * 4 + i) * 512), 16,
+                                               vp + (BOUNDED ? i * step : 0), BOUNDED ? 0 : i * step, 0, 0);
+    }
+  }
+};
+
+// Routed spans: XCD x (workgroups with blockIdx % 8 == x) owns the contiguous chunk [x*T/8, (x+1)*T/8) of the tile list, so that at
+// any moment its workgroups sit on neighbouring tiles -- the same one or two buckets -- and share the span through that
+// XCD's L2.  The record and the items of a workgroup's next tile are requested in a tile's first kv step, by direct
+// global->LDS loads into the wavefront's own 512 bytes (the items of tile t sit at t * rows, so the two do not depend on each
+// other), and turned into addresses in its second; its queries are asked for when the last scores are there.
+//   kWhole    the grid's spans
+//   kClipped  overlapping spans (anchor spacing A < S) in one joint softmax: a row's range in span j starts behind the end of the
+//             nearest lower span that the row lists, so that every token of the union counts once
+//   kAnchor   the paper's geometry, tiles of a (kv head, end block) bucket: every row has its own range, ending inside the
+//             bucket's block; the tile walks from the lowest to the highest token of its rows
+enum class Spans { kWhole, kClipped, kAnchor };
+
+template <Spans MODE, int CB>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, CB == 1 ? 2 : 8))) void span_flash_wide_kernel(const FlashArgs a) {
+  constexpr bool kMasked = MODE != Spans::kWhole;
+  constexpr int kCols = 32 * CB, kRows = 4 * kCols, kStep = WideTile<CB>::kRows;  // columns of a wavefront, rows of a tile, kv rows at a time
+  using Lds = WideLds;
+  extern __shared__ __align__(16) char lds[];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t T = a.tile_off[a.Hq / a.G * a.n];
+  const int NWL = gridDim.x / 8;
+  const int xcd = blockIdx.x % 8, wl = blockIdx.x / 8;
+  const int c_begin = (int)(T * xcd / 8), t_begin = c_begin + wl, t_end = (int)(T * (xcd + 1) / 8);
+  if (t_begin >= t_end) return;
+  bf16_t* const ldsK = reinterpret_cast<bf16_t*>(lds);  // stage b: K at 2 * b * kStage, V behind it
+  int* const ahead = reinterpret_cast<int*>(lds + Lds::kAhead) + wave * 128;
+  int* const row_out = reinterpret_cast<int*>(lds + Lds::kRow) + wave * 512;
+  int* const row_q = row_out + 128;
+  float* const row_lse = reinterpret_cast<float*>(row_out + 192);
+  int* const row_range = row_out + 256;  // kMasked: int lo[2][64], last[2][64]
+  int2* const s_range = reinterpret_cast<int2*>(lds + Lds::kRange);
+  int* const s_claim = reinterpret_cast<int*>(lds + Lds::kClaim);
+
+  // what a tile's record and items say: its kv range, and, per row, where its query and its partial are (to LDS)
+  auto describe = [&](int bucket, int count, const int* items, int turn) {
+    const ArgsPtr a = args_anew();
+    const int ln = lane_anew() & (kCols - 1);
+    Range r = {};
+    r.kv = bucket / a->n;
+    r.live = wave * kCols < count;
+    const int j = bucket % a->n;
+    r.end = (j + 1) * a->A;
+    r.begin = r.end - a->S > 0 ? r.end - a->S : 0;
+    const int item = items[ln];
+    const int rowid = item >> 5, slot = item & 31;
+    const int hl = (uint32_t)rowid / (uint32_t)a->Lq;
+    const int row = rowid - hl * (int)a->Lq;
+    const int h = r.kv * a->G + hl;
+    const bool real = wave * kCols + ln < count;
+    row_q[ln] = (int)(h * a->qsh + row * a->qst);
+    row_out[64 * turn + ln] = real ? (h * (int)a->Lq + row) * (a->topk + 1) + slot : -1;
+    if constexpr (kMasked) {
+      int lo = r.begin, last = r.end - 1;
+      const int32_t* const irow = a->idx + ((int64_t)h * a->Lq + row) * a->topk;
+      if constexpr (MODE == Spans::kClipped) {
+        const int c = (int)((uint32_t)(a->q_pos0 + row) / (uint32_t)a->A);  // (positions lie below 2^24)
+        for (int s2 = 0; s2 < a->topk; ++s2) {
+          const int jj = irow[s2];
+          if (jj >= 0 && jj < c && jj < j && (jj + 1) * a->A > lo) lo = (jj + 1) * a->A;
+        }
+      } else {
+        const int64_t i = a->q_pos0 + row;
+        const AnchorSpan sp = anchor_span_of(i, irow[slot], span_base_length(i, a->aroot), a->window, a->ab, a->af);
+        lo = (int)sp.lo;
+        last = (int)sp.hi - 1;
+      }
+      row_range[64 * turn + ln] = lo;
+      row_range[128 + 64 * turn + ln] = last;
+      const bool some = real && last >= lo;
+      r.any_lo = some ? lo : INT32_MAX;
+      r.all_lo = some ? lo : 0;
+      r.any_last = some ? last : -1;
+      r.all_last = some ? last : INT32_MAX;
+#pragma unroll
+      for (int off = 32; off >= 1; off >>= 1) {
+        r.any_lo = min(r.any_lo, __shfl_xor(r.any_lo, off, 64));
+        r.all_lo = max(r.all_lo, __shfl_xor(r.all_lo, off, 64));
+        r.any_last = max(r.any_last, __shfl_xor(r.any_last, off, 64));
+        r.all_last = min(r.all_last, __shfl_xor(r.all_last, off, 64));
+      }
+      r.any_lo = __builtin_amdgcn_readfirstlane(r.any_lo);
+      r.all_lo = __builtin_amdgcn_readfirstlane(r.all_lo);
+      r.any_last = __builtin_amdgcn_readfirstlane(r.any_last);
+      r.all_last = __builtin_amdgcn_readfirstlane(r.all_last);
+      if (MODE == Spans::kAnchor && ln == 0) s_range[4 * turn + wave] = make_int2(r.any_lo, r.any_last);
+    }
+    return r;
+  };
+  // kAnchor: from the lowest token to the highest of the tile's rows, behind a barrier
+  auto whole_range = [&](Range& r, int turn) {
+    if constexpr (MODE == Spans::kAnchor) {
+      int lo = INT32_MAX, last = -1;
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        const int2 x = s_range[4 * turn + w];
+        lo = min(lo, x.x);
+        last = max(last, x.y);
+      }
+      lo = __builtin_amdgcn_readfirstlane(last < lo ? 0 : lo);
+      last = __builtin_amdgcn_readfirstlane(last < 0 ? 0 : last);
+      r.begin = lo / TN * TN;
+      r.end = (last / TN + 1) * TN;
+    }
+  };
+  WideTile<CB> tile;
+  tile.setup(a.scale_log2e);
+  auto stage = [&](int kvh, int t0, int b) { WideStage<kMasked, CB == 2>(wave, kvh, t0).issue(ldsK + 2 * b * Lds::kStage, wave); };
+  auto load_q = [&] { tile.load_q(args_anew()->Q, row_q); };
+
+  int b = 0, turn = 0;
+  Range cur;
+  {
+    const int4 info = a.tile_info[t_begin];
+    cur = describe(info.x, info.z, a.items + (int64_t)t_begin * kRows + wave * kCols, 0);
+    if (MODE == Spans::kAnchor) {
+      lds_barrier();
+      whole_range(cur, 0);
+    }
+    load_q();
+    stage(cur.kv, cur.begin, b);
+    __builtin_amdgcn_s_waitcnt(0x0F70);
+  }
+  // Tiles are claimed one by one, from a counter of the XCD's (equal shares: 12 % of the time without a tile at the end): a
+  // workgroup has its second one from the start, and asks for the one after its next while it ends a tile.
+  int claimed = 0;
+  for (bool first = true;; first = false) {
+    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+    if (!first && wave == 0 && lane_anew() == 0) *s_claim = claimed;
+    lds_barrier();
+    const int next = first ? t_begin + NWL : c_begin + 2 * NWL + __builtin_amdgcn_readfirstlane(*s_claim);
+    const bool has_next = next < t_end;
+    Range nxt = cur;
+    tile.clear();
+#pragma unroll 1
+    for (int t0 = cur.begin; t0 < cur.end; t0 += TN) {
+      if (t0 != cur.begin) {
+        __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+        lds_barrier();
+      }
+      if (t0 + TN < cur.end) stage(cur.kv, t0 + TN, b ^ 1);
+      if (has_next && t0 == cur.begin) {
+        const ArgsPtr a = args_anew();
+        const int ln = lane_anew();
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(buffer_of(a->tile_info + next, 16), SL_LDS_PTR(ahead), 4, (ln & 3) * 4, 0, 0, 0);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(buffer_of(a->items + (int64_t)next * kRows + wave * kCols, kCols * 4),
+                                                 SL_LDS_PTR(ahead + 64), 4, ln * 4, 0, 0, 0);
+      }
+      const bool last = t0 + TN >= cur.end;
+      if (has_next && (t0 == cur.begin + TN || (last && t0 == cur.begin))) {
+        if (last) __builtin_amdgcn_s_waitcnt(0x0F70);  // (one step: they are not here yet)
+        nxt = describe(__builtin_amdgcn_readfirstlane(ahead[0]), __builtin_amdgcn_readfirstlane(ahead[2]), ahead + 64, turn ^ 1);
+      }
+      const bf16_t* const kt = ldsK + 2 * b * Lds::kStage;
+#pragma unroll 1
+      for (int sub = 0; sub < TN; sub += kStep) {
+        if (last && sub == TN - kStep) break;
+        if (!cur.attended<kMasked, kStep>(t0 + sub)) continue;
+        tile.qk(kt + sub * HD);
+        tile.template attend<kMasked>(t0 + sub, cur, row_range + 64 * turn, kt + Lds::kStage + sub * HD);
+      }
+      b ^= 1;
+    }
+    // the tile's last kv rows: the queries are needed no more once their scores are there
+    const bf16_t* const kt = ldsK + (2 * (b ^ 1) * Lds::kStage + (TN - kStep) * HD);
+    tile.qk(kt);
+    if (has_next) {
+      load_q();
+      if (wave == 0 && lane_anew() == 0)
+        claimed = (int)__builtin_amdgcn_atomic_inc32((uint32_t*)&args_anew()->claims[32 * xcd], 0xffffffffu, __ATOMIC_RELAXED, "agent");
+    }
+    tile.template attend<kMasked>(cur.end - kStep, cur, row_range + 64 * turn, kt + Lds::kStage);
+    lds_barrier();
+    if (has_next) {
+      whole_range(nxt, turn ^ 1);
+      stage(nxt.kv, nxt.begin, b);
+    }
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    // the other stage is dead until the next tile's first barrier
+    bf16_t* const ost = ldsK + 2 * (b ^ 1) * Lds::kStage + wave * 4096;
+    const int* const out = row_out + 64 * turn;
+    const ArgsPtr pa = args_anew();
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb) {
+      tile.stage_output(cb, ost, row_lse);
+      tile.write_output(cb, ost, out, pa->part_o);
+    }
+    {
+      const int ln = lane_anew(), to = out[ln & (kCols - 1)];
+      if (ln < kCols && to >= 0) __builtin_nontemporal_store(row_lse[ln], &pa->part_lse[to]);
+    }
+    if (!has_next) break;
+    cur = nxt;
+    turn ^= 1;
+  }
+}
+
+// A window tile's columns (128 or 256) are `heads` query heads of one kv head, which attend the same keys, times columns / heads rows:
+// the fewer rows, the shorter the kv range that the tile walks beyond what each of its rows attends.  Heads: the largest
+// power of two that divides the group, up to 8.  Tiles of 128 rows of one head -> 16 rows of 8, us, 32:4 heads: 20011 rows,
+// spans of 142 (fp32 weights) 181 -> 140; 4000 rows, spans of 512 47 -> 43.
+__host__ __device__ inline int local_heads(int G) {
+  const int p = G & -G;
+  return p < 8 ? p : 8;
+}
+// Row tiles and their grouping into chunks of `tps` tiles (the tiles of one span when S is a multiple of the tile height).
+struct LocalMap {
+  int shift, rows;         // rows of a tile, a power of two: what depends on it is shifted, not divided
+  int tiles, tps, chunks;  // tiles of a kv head (and group of `heads` heads)
+};
+__host__ __device__ inline LocalMap local_map(int64_t Lq, int S, int G, int columns) {
+  LocalMap m;
+  m.shift = __builtin_ctz(columns / local_heads(G));
+  m.rows = 1 << m.shift;
+  m.tiles = (int)((Lq + m.rows - 1) >> m.shift);
+  // No more than an eighth of the tiles in a run: the paper's geometry, whose runs are 1024 tokens long, 1024 rows behind
+  // 48133 tokens 407 -> 285 us, 4096 530 -> 444, a prompt of 3000 253 -> 161.
+  const int each = (m.tiles + 7) / 8;
+  m.tps = (S >> m.shift) < each ? S >> m.shift : each;
+  m.tps = m.tps > 0 ? m.tps : 1;
+  m.chunks = (m.tiles + m.tps - 1) / m.tps;
+  return m;
+}
+// Blocks to launch: 8 x the largest per-XCD share.
+inline unsigned local_grid(int64_t Lq, int S, int Hkv, int G, int columns) {
+  const LocalMap m = local_map(Lq, S, G, columns);
+  int best = 0;
+  for (int x = 0; x < 8; ++x) {
+    const int cx = (m.chunks - x + 7) / 8;
+    const bool lx = m.chunks > 0 && (m.chunks - 1) % 8 == x;
+    const int tx = cx * m.tps - (lx ? m.chunks * m.tps - m.tiles : 0);
+    best = tx > best ? tx : best;
+  }
+  return (unsigned)(8 * Hkv * best * (G / local_heads(G)));
+}
+
+// Workgroup -> (heads, row tile) of a window kernel, XCD-aware: blocks are dealt round-robin to the 8 XCDs, each
+// with its own L2.  A run of `tps` consecutive row tiles (one span's worth) goes to one XCD,
+// and inside an XCD the groups of heads of a kv head take the same row tile back to back, so the
+// window's K/V tiles are fetched from HBM about once.
+struct LocalTile {
+  bool any;  // the grid is padded to 8 * the largest share
+  int kv, tile, head0;
+};
+__device__ __forceinline__ LocalTile local_tile(const LocalMap& lm, int columns, int Hkv, int G) {
+  const int heads = columns >> lm.shift, sets = G / heads;
+  const int xcd = blockIdx.x % 8, slot = blockIdx.x / 8;
+  const int chunks_x = (lm.chunks - xcd + 7) / 8;                 // chunks xcd, xcd+8, ... of a kv head
+  const bool has_last = lm.chunks > 0 && (lm.chunks - 1) % 8 == xcd;  // the only chunk that may be short
+  const int tiles_x = chunks_x * lm.tps - (has_last ? lm.chunks * lm.tps - lm.tiles : 0);
+  LocalTile t;
+  t.any = slot < Hkv * tiles_x * sets;
+  if (!t.any) return t;
+  t.kv = slot / (tiles_x * sets);
+  const int rem = slot % (tiles_x * sets), tile_local = rem / sets;
+  t.tile = (xcd + 8 * (tile_local / lm.tps)) * lm.tps + tile_local % lm.tps;
+  t.head0 = t.kv * G + rem % sets * heads;
+  return t;
+}
+
+// Local window [c*S, i] of the fp32-weight kernels: tiles of 128 columns with the causal mask; writes the window's partial into
+// the row's last slot.
+template <int D, int TT>
+__global__ __launch_bounds__(256, fine_blocks(TT)) void span_flash_local_kernel(const FlashArgs a) {
+  extern __shared__ __align__(16) char lds[];
+  const int qrow = (threadIdx.x >> 6) * 32 + (threadIdx.x & 31);
+  const LocalMap lm = local_map(a.Lq, a.A, a.G, TG);
+  const LocalTile lt = local_tile(lm, TG, a.Hq / a.G, a.G);
+  if (!lt.any) return;
+  const int h = lt.head0 + (qrow >> lm.shift);
+  const int64_t r0 = (int64_t)lt.tile << lm.shift;
+  const int64_t r = r0 + (qrow & (lm.rows - 1));
+  const int64_t rc = r < a.Lq ? r : a.Lq - 1;
+  TileDesc d;
+  d.kv = lt.kv;
+  d.q_off = h * a.qsh + rc * a.qst;
+  d.row_out = r < a.Lq ? ((int64_t)h * a.Lq + r) * (a.topk + 1) + a.topk : -1;
+  d.i_q = a.q_pos0 + rc;
+  d.lo_q = (d.i_q / a.A) * a.A;
+  d.kv_begin = ((a.q_pos0 + r0) / a.A) * a.A;
+  d.kv_end = a.q_pos0 + (r0 + lm.rows < a.Lq ? r0 + lm.rows : a.Lq);
+  flash_tile<D, TT>(a, lds, d);
+}
+
+// Windows: regular tiles of 128 or 256 columns with the causal / window mask.
+// FUSED = false: writes the window's partial into the row's last slot (a merge kernel follows).
+// FUSED = true (joint softmax, topk <= 8): merges the row's routed partials in the epilogue and
+// writes the final output, which takes the merge's HBM traffic off the critical path of a
+// separate kernel and saves the window partial's round trip.
+template <bool FUSED, int CB>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, CB == 1 ? 2 : 8))) void span_window_wide_kernel(const FlashArgs a) {
+  using Lds = WideLds;
+  constexpr int kCols = 32 * CB, kTile = 4 * kCols, kStep = WideTile<CB>::kRows;
+  extern __shared__ __align__(16) char lds[];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  bf16_t* const ldsK = reinterpret_cast<bf16_t*>(lds);
+  int* const row_out = reinterpret_cast<int*>(lds + Lds::kRow) + wave * 512;
+  int* const row_q = row_out + 128;
+  float* const row_lse = reinterpret_cast<float*>(row_out + 192);
+  int* const row_range = row_out + 256;
+  const LocalMap lm = local_map(a.Lq, a.A, a.G, kTile);
+  const LocalTile lt = local_tile(lm, kTile, a.Hq / a.G, a.G);
+  if (!lt.any) return;
+  const int kvh = lt.kv;
+  const int r0 = lt.tile << lm.shift;
+  auto window_of = [&](int64_t i) {
+    if (a.window > 0) return i - a.window + 1 > 0 ? (int)(i - a.window + 1) : 0;
+    return (int)((uint32_t)i / (uint32_t)a.A) * a.A;  // (positions lie below 2^24)
+  };
+  {
+    const int ln = lane & (kCols - 1), col = wave * kCols + ln;
+    const int h = lt.head0 + (col >> lm.shift);
+    const int r = r0 + (col & (lm.rows - 1));
+    const int rc = r < (int)a.Lq ? r : (int)a.Lq - 1;
+    row_q[ln] = (int)(h * a.qsh + rc * a.qst);
+    row_out[ln] = r < (int)a.Lq ? (FUSED ? h * (int)a.Lq + r : (h * (int)a.Lq + r) * (a.topk + 1) + a.topk) : -1;
+    row_range[ln] = window_of(a.q_pos0 + rc);
+    row_range[128 + ln] = (int)(a.q_pos0 + rc);
+  }
+  // rows of the wavefront: a run of the tile's (all of them where a tile has no more than a wavefront columns)
+  const int f = lm.rows > kCols ? wave * kCols & (lm.rows - 1) : 0, n = lm.rows > kCols ? kCols : lm.rows;
+  auto pos = [&](int r) { return (int)(a.q_pos0 + (r < (int)a.Lq ? r : (int)a.Lq - 1)); };
+  Range cur;
+  cur.kv = kvh;
+  cur.live = r0 + f < (int)a.Lq;
+  cur.any_lo = window_of(pos(r0 + f));
+  cur.all_lo = window_of(pos(r0 + f + n - 1));
+  cur.all_last = pos(r0 + f);
+  cur.any_last = pos(r0 + f + n - 1);
+  cur.begin = window_of(pos(r0)) / TN * TN;
+  cur.end = (pos(r0 + lm.rows - 1) / TN + 1) * TN;
+
+  WideTile<CB> t;
+  t.setup(a.scale_log2e);
+  int b = 0;
+  WideStage<true, CB == 2>(wave, kvh, cur.begin).issue(ldsK, wave);
+  t.load_q(a.Q, row_q);
+  t.clear();
+#pragma unroll 1
+  for (int t0 = cur.begin; t0 < cur.end; t0 += TN) {
+    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+    lds_barrier();
+    if (t0 + TN < cur.end) WideStage<true, CB == 2>(wave, kvh, t0 + TN).issue(ldsK + 2 * (b ^ 1) * Lds::kStage, wave);
+    const bf16_t* const kt = ldsK + 2 * b * Lds::kStage;
+#pragma unroll 1
+    for (int sub = 0; sub < TN; sub += kStep) {
+      if (!cur.attended<true, kStep>(t0 + sub)) continue;
+      t.qk(kt + sub * HD);
+      t.template attend<true>(t0 + sub, cur, row_range, kt + Lds::kStage + sub * HD);
+    }
+    b ^= 1;
+  }
+  lds_barrier();
+  // the stages are dead: 64 rows of 256 bytes per wavefront
+  bf16_t* const ost = ldsK + wave * CB * 4096;
+#pragma unroll
+  for (int cb = 0; cb < CB; ++cb) t.stage_output(cb, ost + cb * 4096, row_lse);
+  if constexpr (!FUSED) {
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb) t.write_output(cb, ost + cb * 4096, row_out, a.part_o);
+    if (lane < kCols && row_out[lane] >= 0) a.part_lse[row_out[lane]] = row_lse[lane];
+  } else {
+    // The merge (topk <= 8): the lane that would store 16 bytes of the window's partial instead loads the same 16 bytes of the
+    // row's routed partials (written by the routed kernel, which ran before on the stream), does the log-sum-exp merge and
+    // stores the final output.  Every load is issued before the first dependent use; slots that take no part may hold
+    // anything and are discarded by selects, never by arithmetic.
+    const int topk = a.topk, nslot = topk + 1;
+#pragma unroll 1
+    for (int ub = 0; ub < kCols; ub += 16) {
       int64_t outs[4];
       int js[4][8];
       float ls[4][8];
       uint4 ov[4][8];
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
-        const int row = w4 * 32 + (half * 4 + u) * 4 + (lane >> 4), piece = lane & 15;
+        const int row = ub + u * 4 + (lane >> 4), piece = lane & 15;
         outs[u] = row_out[row];
         const int64_t rg = outs[u] >= 0 ? outs[u] : 0;
 #pragma unroll
@@ -881,8 +1435,8 @@ __device__ __forceinline__ void flash_tile(const FlashArgs& a, char* lds, const 
       }
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
-        const int row = w4 * 32 + (half * 4 + u) * 4 + (lane >> 4), piece = lane & 15;
-        const int cq = (int)((cur.first_pos + (row & cur.row_mask)) / a.A);
+        const int row = ub + u * 4 + (lane >> 4), piece = lane & 15;
+        const int cq = row_range[128 + row] / a.A;
         const float lw = row_lse[row];
         float M = lw;
 #pragma unroll
@@ -920,317 +1474,7 @@ __device__ __forceinline__ void flash_tile(const FlashArgs& a, char* lds, const 
         }
       }
     }
-  } else if (NG == 2 && !LOCAL) {
-    c.pending = true;  // written out during the next tile's first kv step, or by the caller after the last tile
-  } else {
-    // Every LDS read comes before the first store, and the values are pinned there: the compiler
-    // orders an LDS read after all outstanding vector-memory operations once direct global->LDS
-    // loads are in flight (the next tile's), so a read between two stores would wait for the
-    // earlier store to be acknowledged.
-    int64_t outs[8];
-    uint4 vals[8];
-    float lses[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int row = w4 * 32 + u * 4 + (lane >> 4), piece = lane & 15;
-      outs[u] = row_out[row];
-      lses[u] = row_lse[row];
-      vals[u] = *reinterpret_cast<const uint4*>(&ost[row * HD + ((piece ^ (row & 15)) << 3)]);
-    }
-#pragma unroll
-    for (int u = 0; u < 8; ++u)
-      asm volatile("" : "+v"(vals[u].x), "+v"(vals[u].y), "+v"(vals[u].z), "+v"(vals[u].w), "+v"(lses[u]),
-                   "+v"(outs[u]));
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int piece = lane & 15;
-      if (outs[u] >= 0) {
-        store16_stream(a.part_o + outs[u] * HD + piece * 8, vals[u]);
-        if (piece == 0) a.part_lse[outs[u]] = lses[u];
-      }
-    }
   }
-  __builtin_amdgcn_s_setprio(0);
-  __builtin_amdgcn_wave_barrier();
-  // No trailing barrier: a wavefront's output slice is private to it, and the K/V stages are
-  // handed over through c.kb / c.vb.
-}
-
-// Routed spans: persistent workgroups walk the tile list.  XCD x (workgroups with
-// blockIdx % 8 == x) owns the contiguous chunk [x*T/8, (x+1)*T/8) of the tile list; its
-// workgroups walk the chunk interleaved, so at any moment they sit on neighbouring tiles -- the
-// same one or two buckets -- and share the span through that XCD's L2.  The record and the item
-// of a workgroup's next tile are fetched while its current tile is computed.
-// CLIP (overlapping spans, anchor spacing A < S, joint softmax): a row's range in span j starts behind
-// the end of the nearest lower span that the row lists, so that every token of the union counts once.
-// FINE (with CLIP): fp32 weights and partials, spans of any length at any offset; a row's range is its whole
-// span unless a->clip says that spans of a row overlap in one softmax.  Tiles of 128 rows, two workgroups per
-// compute unit: one's tile ends run beside the other's kv loop.
-template <bool CLIP, int D = HD, bool FINE = false, int TT = TN, int NG = FINE ? 1 : 2>
-__global__ __launch_bounds__(NG * 256, NG == 2 ? 1 : FINE ? fine_blocks(TT) : 2) void span_flash_routed_kernel(
-    const FlashArgs a) {
-  using Lds = FlashLds<NG, D, TT>;
-  constexpr int TM = Lds::kRows;
-  extern __shared__ __align__(16) char lds[];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int qrow = (wave >> 2) * TG + (wave & 3) * 32 + (lane & 31);
-  const int64_t T = a.tile_off[a.Hq / a.G * a.n];
-  const int NWL = gridDim.x / 8;  // workgroups per XCD (the grid is a multiple of 8)
-  const int xcd = blockIdx.x % 8, wl = blockIdx.x / 8;
-  const int64_t c_begin = T * xcd / 8, c_end = T * (xcd + 1) / 8;
-  const int64_t t_begin = c_begin + wl, t_end = c_end;
-  if (t_begin >= t_end) return;
-
-  auto describe = [&](const int4& info, int item) {
-    const ArgsPtr a = args_anew();
-    TileDesc d;
-    d.kv = info.x / a->n;
-    const int j = info.x % a->n;
-    d.kv_end = (int64_t)(j + 1) * a->A;
-    d.kv_begin = d.kv_end - a->S > 0 ? d.kv_end - a->S : 0;
-    const int rowid = item >> 5, slot = item & 31;
-    const int hl = rowid / (int)a->Lq;
-    const int64_t r = rowid - (int64_t)hl * a->Lq;
-    const int h = d.kv * a->G + hl;
-    d.q_off = h * a->qsh + r * a->qst;
-    d.row_out = qrow < info.z ? ((int64_t)h * a->Lq + r) * (a->topk + 1) + slot : -1;
-    d.i_q = d.kv_end - 1;
-    d.lo_q = d.kv_begin;
-    if (FINE ? a->clip : CLIP) {
-      const int64_t c = (a->q_pos0 + r) / a->A;
-      const int32_t* irow = a->idx + ((int64_t)h * a->Lq + r) * a->topk;
-      for (int s2 = 0; s2 < a->topk; ++s2) {
-        const int64_t jj = irow[s2];
-        if (jj >= 0 && jj < c && jj < j && (jj + 1) * a->A > d.lo_q) d.lo_q = (jj + 1) * a->A;
-      }
-    }
-    d.first_pos = 0;
-    d.row_mask = 0;
-    return d;
-  };
-  FlashCarry carry;
-  carry.kb = carry.vb = 0;
-  carry.primed = false;
-  carry.pending = false;
-  if constexpr (NG == 1) {
-    for (int64_t t = t_begin; t < t_end; t += NWL) {
-      TileDesc cur = describe(a.tile_info[t], a.items[t * TM + qrow]), unused = cur;
-      flash_tile<1, false, false, CLIP, D, FINE, TT>(a, lds, cur, unused, false, [] {}, [&] { return cur; }, carry);
-      __syncthreads();  // the next tile's stages lie over the output slices of all wavefronts
-    }
-  } else {
-    // The record and the items of a workgroup's next tile are requested during the current tile's
-    // first kv step as direct global->LDS loads into the wavefront's own 512 bytes (the items of tile t sit
-    // at t*TM, so the two do not depend on each other) and read back at its tail.
-    int* const ahead = reinterpret_cast<int*>(lds + Lds::kAhead) + __builtin_amdgcn_readfirstlane(wave) * 128;
-    const int4 info0 = a.tile_info[t_begin];
-    TileDesc cur = describe(info0, a.items[t_begin * TM + qrow]);
-    for (int64_t t = t_begin; t < t_end; t += NWL) {
-      const bool has_next = t + NWL < t_end;
-      TileDesc nxt = cur;
-      flash_tile<2, false, false, CLIP>(
-          a, lds, cur, nxt, has_next,
-          [&] {
-            const ArgsPtr a = args_anew();
-            const int uw = __builtin_amdgcn_readfirstlane(wave);
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(buffer_of(a->tile_info + (t + NWL), 16), SL_LDS_PTR(ahead), 4,
-                                                     (lane & 3) * 4, 0, 0, 0);
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(buffer_of(a->items + (t + NWL) * TM + uw * 32, 128),
-                                                     SL_LDS_PTR(ahead + 64), 4, (lane & 31) * 4, 0, 0, 0);
-          },
-          [&] {
-            const int4 ninfo = make_int4(ahead[0], ahead[1], ahead[2], 0);
-            return describe(ninfo, ahead[64 + lane]);
-          },
-          carry);
-      cur = nxt;
-    }
-    // the last tile's output (its epilogue ended with the wavefront's own LDS writes)
-    if (carry.pending) flush_routed_output(lds, wave >> 2, wave & 3, lane);
-  }
-}
-
-// The paper's geometry: routed tiles of a (kv head, end block) bucket.  Every row of a tile has
-// its own token range [lo, hi) (hi inside the bucket's block); the tile walks the kv range from
-// the lowest lo to the highest hi of its rows (rounded to whole 64-token tiles) with per-row masks.
-__global__ __launch_bounds__(FlashLds<2>::kThreads, 1) void span_flash_anchor_kernel(const FlashArgs a) {
-  extern __shared__ __align__(16) char lds[];
-  __shared__ int64_t s_lo[8], s_hi[8];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int qrow = (wave >> 2) * TG + (wave & 3) * 32 + (lane & 31);
-  const int64_t T = a.tile_off[a.Hq / a.G * a.n];
-  const int NWL = gridDim.x / 8;
-  const int xcd = blockIdx.x % 8, wl = blockIdx.x / 8;
-  const int64_t c_begin = T * xcd / 8, c_end = T * (xcd + 1) / 8;
-  const int64_t t_begin = c_begin + wl, t_end = c_end;
-  if (t_begin >= t_end) return;
-
-  // all threads call (two barriers inside)
-  auto describe = [&](const int4& info, int item) {
-    const ArgsPtr a = args_anew();
-    TileDesc d;
-    d.kv = info.x / a->n;
-    const int rowid = item >> 5, slot = item & 31;
-    const int hl = rowid / (int)a->Lq;
-    const int64_t r = rowid - (int64_t)hl * a->Lq;
-    const int h = d.kv * a->G + hl;
-    const int64_t i = a->q_pos0 + r;
-    const bool real = qrow < info.z;
-    const int64_t t = a->idx[((int64_t)h * a->Lq + r) * a->topk + slot];
-    const AnchorSpan sp = anchor_span_of(i, t, span_base_length(i, a->aroot), a->window, a->ab, a->af);
-    d.q_off = h * a->qsh + r * a->qst;
-    d.row_out = real ? ((int64_t)h * a->Lq + r) * (a->topk + 1) + slot : -1;
-    d.lo_q = sp.lo;
-    d.i_q = sp.hi - 1;
-    d.first_pos = 0;
-    d.row_mask = 0;
-    // the tile's kv range: from the lowest lo to the highest hi of its rows
-    int64_t lo = real && sp.hi > sp.lo ? sp.lo : INT64_MAX, hi = real && sp.hi > sp.lo ? sp.hi : 0;
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-      const int64_t lo2 = __shfl_xor(lo, off, 64), hi2 = __shfl_xor(hi, off, 64);
-      lo = lo2 < lo ? lo2 : lo;
-      hi = hi2 > hi ? hi2 : hi;
-    }
-    __syncthreads();  // earlier readers of s_lo / s_hi are done
-    if (lane == 0) {
-      s_lo[wave] = lo;
-      s_hi[wave] = hi;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int w = 0; w < 8; ++w) {
-      lo = s_lo[w] < lo ? s_lo[w] : lo;
-      hi = s_hi[w] > hi ? s_hi[w] : hi;
-    }
-    if (hi <= lo) lo = hi = 0;  // cannot happen for a tile with items; keeps the range sane
-    d.kv_begin = lo / TN * TN;
-    d.kv_end = (hi + TN - 1) / TN * TN;
-    return d;
-  };
-  FlashCarry carry;
-  carry.kb = carry.vb = 0;
-  carry.primed = false;
-  carry.pending = false;
-  int* const ahead = reinterpret_cast<int*>(lds + FlashLds<2>::kAhead) + __builtin_amdgcn_readfirstlane(wave) * 128;
-  const int4 info0 = a.tile_info[t_begin];
-  TileDesc cur = describe(info0, a.items[t_begin * TM + qrow]);
-  for (int64_t t = t_begin; t < t_end; t += NWL) {
-    const bool has_next = t + NWL < t_end;
-    TileDesc nxt = cur;
-    flash_tile<2, false, false, true>(
-        a, lds, cur, nxt, has_next,
-        [&] {
-          const ArgsPtr a = args_anew();
-          const int uw = __builtin_amdgcn_readfirstlane(wave);
-          __builtin_amdgcn_raw_ptr_buffer_load_lds(buffer_of(a->tile_info + (t + NWL), 16), SL_LDS_PTR(ahead), 4,
-                                                   (lane & 3) * 4, 0, 0, 0);
-          __builtin_amdgcn_raw_ptr_buffer_load_lds(buffer_of(a->items + (t + NWL) * TM + uw * 32, 128),
-                                                   SL_LDS_PTR(ahead + 64), 4, (lane & 31) * 4, 0, 0, 0);
-        },
-        [&] {
-          const int4 ninfo = make_int4(ahead[0], ahead[1], ahead[2], 0);
-          return describe(ninfo, ahead[64 + lane]);
-        },
-        carry);
-    cur = nxt;
-  }
-  if (carry.pending) flush_routed_output(lds, wave >> 2, wave & 3, lane);
-}
-
-// A window tile's 128 columns are `heads` query heads of one kv head, which attend the same keys, times 128 / heads rows:
-// the fewer rows, the shorter the kv range that the tile walks beyond what each of its rows attends.  Heads: the largest
-// power of two that divides the group, up to 8.  Tiles of 128 rows of one head -> 16 rows of 8, this kernel, us, 32:4
-// heads: 20011 rows, spans of 142 (fp32 weights) 181 -> 140; 49157 rows, windows of 1088 tokens 990 -> 970; 4000 rows, spans
-// of 512 47 -> 43; 262144 rows, spans of 512, with the merge (bound by the partials) 5000 -> 4960.
-__host__ __device__ inline int local_heads(int G) {
-  const int p = G & -G;
-  return p < 8 ? p : 8;
-}
-// Row tiles and their grouping into chunks of `tps` tiles (the tiles of one span when S is a multiple of the tile height).
-struct LocalMap {
-  int shift, rows;         // rows of a tile, a power of two: what depends on it is shifted, not divided
-  int tiles, tps, chunks;  // tiles of a kv head (and group of `heads` heads)
-};
-__host__ __device__ inline LocalMap local_map(int64_t Lq, int S, int G) {
-  LocalMap m;
-  m.shift = __builtin_ctz(FlashLds<1>::kRows / local_heads(G));
-  m.rows = 1 << m.shift;
-  m.tiles = (int)((Lq + m.rows - 1) >> m.shift);
-  // No more than an eighth of the tiles in a run: the paper's geometry, whose runs are 1024 tokens long, 1024 rows behind
-  // 48133 tokens 407 -> 285 us, 4096 530 -> 444, a prompt of 3000 253 -> 161.
-  const int each = (m.tiles + 7) / 8;
-  m.tps = (S >> m.shift) < each ? S >> m.shift : each;
-  m.tps = m.tps > 0 ? m.tps : 1;
-  m.chunks = (m.tiles + m.tps - 1) / m.tps;
-  return m;
-}
-// Blocks to launch: 8 x the largest per-XCD share.
-inline unsigned local_grid(int64_t Lq, int S, int Hkv, int G) {
-  const LocalMap m = local_map(Lq, S, G);
-  int best = 0;
-  for (int x = 0; x < 8; ++x) {
-    const int cx = (m.chunks - x + 7) / 8;
-    const bool lx = m.chunks > 0 && (m.chunks - 1) % 8 == x;
-    const int tx = cx * m.tps - (lx ? m.chunks * m.tps - m.tiles : 0);
-    best = tx > best ? tx : best;
-  }
-  return (unsigned)(8 * Hkv * best * (G / local_heads(G)));
-}
-
-// Local window [c*S, i]: regular tiles of 128 columns with the causal / window mask.
-// FUSED = false: writes the window's partial into the row's last slot (a merge kernel follows).
-// FUSED = true (joint softmax, topk <= 8): merges the row's routed partials in the epilogue and
-// writes the final output, which takes the merge's HBM traffic off the critical path of a
-// separate kernel and saves the window partial's round trip.
-template <bool FUSED, int D = HD, bool FINE = false, int TT = TN>
-__global__ __launch_bounds__(FlashLds<1>::kThreads, FINE ? fine_blocks(TT) : 2) void span_flash_local_kernel(const FlashArgs a) {
-  extern __shared__ __align__(16) char lds[];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int qrow = wave * 32 + (lane & 31);
-  // Workgroup -> (heads, row tile), XCD-aware: blocks are dealt round-robin to the 8 XCDs, each
-  // with its own L2.  A run of `tps` consecutive row tiles (one span's worth) goes to one XCD,
-  // and inside an XCD the groups of heads of a kv head take the same row tile back to back, so the
-  // window's K/V tiles are fetched from HBM about once.
-  const LocalMap lm = local_map(a.Lq, a.A, a.G);
-  const int heads = FlashLds<1>::kRows >> lm.shift, sets = a.G / heads;
-  const int xcd = blockIdx.x % 8, slot = blockIdx.x / 8;
-  const int chunks_x = (lm.chunks - xcd + 7) / 8;                 // chunks xcd, xcd+8, ... of a kv head
-  const bool has_last = lm.chunks > 0 && (lm.chunks - 1) % 8 == xcd;  // the only chunk that may be short
-  const int tiles_x = chunks_x * lm.tps - (has_last ? lm.chunks * lm.tps - lm.tiles : 0);
-  if (slot >= (a.Hq / a.G) * tiles_x * sets) return;  // uniform: the grid is padded to 8 * the largest share
-  const int kvh = slot / (tiles_x * sets), rem = slot % (tiles_x * sets);
-  const int tile_local = rem / sets;
-  const int tile = (xcd + 8 * (tile_local / lm.tps)) * lm.tps + tile_local % lm.tps;
-  const int h = kvh * a.G + rem % sets * heads + (qrow >> lm.shift);
-  const int64_t r0 = (int64_t)tile << lm.shift;
-  const int64_t r = r0 + (qrow & (lm.rows - 1));
-  const int64_t rc = r < a.Lq ? r : a.Lq - 1;
-  TileDesc d;
-  d.kv = kvh;
-  d.q_off = h * a.qsh + rc * a.qst;
-  d.first_pos = a.q_pos0 + r0;
-  d.row_mask = lm.rows - 1;
-  if (FUSED) d.row_out = r < a.Lq ? (int64_t)h * a.Lq + r : -1;
-  else d.row_out = r < a.Lq ? ((int64_t)h * a.Lq + r) * (a.topk + 1) + a.topk : -1;
-  d.i_q = a.q_pos0 + rc;
-  const int64_t i_first = a.q_pos0 + r0;
-  const int64_t i_last = min(a.q_pos0 + r0 + lm.rows - 1, a.q_pos0 + a.Lq - 1);
-  if (a.window > 0) {  // the paper's geometry: a sliding window [i - window + 1, i] per row
-    d.lo_q = d.i_q - a.window + 1 > 0 ? d.i_q - a.window + 1 : 0;
-    const int64_t first_lo = i_first - a.window + 1 > 0 ? i_first - a.window + 1 : 0;
-    d.kv_begin = first_lo / TN * TN;
-  } else {
-    d.lo_q = (d.i_q / a.A) * a.A;
-    d.kv_begin = (i_first / a.A) * a.A;
-  }
-  d.kv_end = FINE ? i_last + 1 : d.kv_begin + ((i_last - d.kv_begin) / TN + 1) * TN;
-  FlashCarry carry;
-  carry.kb = carry.vb = 0;
-  carry.primed = false;
-  carry.pending = false;
-  TileDesc unused = d;
-  flash_tile<1, true, FUSED, false, D, FINE, TT>(a, lds, d, unused, false, [] {}, [&] { return d; }, carry);
 }
 
 // ------------------------------------------------------------------ merge
@@ -1418,11 +1662,14 @@ __global__ __launch_bounds__(256) void merge_combined_kernel(
 // ------------------------------------------------------------------ workspace carving
 struct MfmaWs {
   int tm;  // rows of a tile
-  size_t counts, unit_cnt, item_off, tile_off, cursor, tile_info, items, part_lse, part_o, flag, total;
+  size_t counts, claims, unit_cnt, item_off, tile_off, cursor, tile_info, items, part_lse, part_o, flag, total;
   BucketPlan plan;
   int B, max_tiles;
   int64_t max_items;
 };
+
+using One = std::integral_constant<int, 1>;
+using Two = std::integral_constant<int, 2>;
 
 // Per-device facts, looked up on the first call with that device current: the grid of the
 // persistent kernel (one resident workgroup of eight wavefronts per compute unit) and whether the
@@ -1444,17 +1691,17 @@ bool device_setup(DeviceSetup* out) {
     int cus = 0;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
       cus = 256;
-    d.lds_ok =
-        hipFuncSetAttribute(reinterpret_cast<const void*>(span_flash_routed_kernel<false>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, FlashLds<2>::kBytes) == hipSuccess &&
-        hipFuncSetAttribute(reinterpret_cast<const void*>(span_flash_routed_kernel<true>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, FlashLds<2>::kBytes) == hipSuccess &&
-        hipFuncSetAttribute(reinterpret_cast<const void*>(span_flash_anchor_kernel),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, FlashLds<2>::kBytes) == hipSuccess &&
-        hipFuncSetAttribute(reinterpret_cast<const void*>(span_flash_local_kernel<false>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, FlashLds<1>::kBytes) == hipSuccess &&
-        hipFuncSetAttribute(reinterpret_cast<const void*>(span_flash_local_kernel<true>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, FlashLds<1>::kBytes) == hipSuccess;
+    auto allow = [](auto kernel) {
+      return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, WideLds::kBytes) ==
+             hipSuccess;
+    };
+    auto allow_both = [&](auto columns) {
+      constexpr int CB = decltype(columns)::value;
+      return allow(span_flash_wide_kernel<Spans::kWhole, CB>) && allow(span_flash_wide_kernel<Spans::kClipped, CB>) &&
+             allow(span_flash_wide_kernel<Spans::kAnchor, CB>) && allow(span_window_wide_kernel<false, CB>) &&
+             allow(span_window_wide_kernel<true, CB>);
+    };
+    d.lds_ok = allow_both(One{}) && allow_both(Two{});
     d.grid = (cus + 7) / 8 * 8;
   }
   *out = d;
@@ -1474,7 +1721,26 @@ BucketPlan bucket_plan(const Problem& pb) {
   return p;
 }
 
-MfmaWs carve(const Problem& pb, int tm = TM, size_t part_elem = sizeof(bf16_t)) {
+// Columns of a wavefront of the kernels with bf16 weights, in blocks of 32.  With two a fragment of K or V feeds two products,
+// and the long prompt's routed kernel runs at 1050 to 1150 TFLOP/s where one reaches 970 to 1040; but a tile that is mostly
+// empty, or that alone keeps the call waiting, takes twice the time.  460 random calls (1 to 64 heads, 1 to 150000 rows, grid
+// and paper's geometry, two -> one): from 1024 tiles of 256 rows and 500 items a bucket on 0.86 to 1.10, geometric mean 0.97;
+// below 256 tiles 1.0 to 1.6, mean 1.15.  With these two numbers the calls are within 0.3 % of the faster form each (0.7 % with
+// one block throughout, 0.8 % with two from 512 tiles on, whatever the buckets hold).
+int routed_blocks(const Problem& pb) {
+  const double items = (double)pb.Hq * pb.Lq * pb.topk, buckets = fmin(items, (double)pb.Hkv * pb.n);
+  return items >= 500 * buckets && items / 256 + 0.5 * buckets >= 1024 ? 2 : 1;
+}
+// Windows (tokens: how many a row's has on average) by workgroups of 256 rows: where they are not two a compute unit, one block is
+// faster (up to 32 two -> one 1.17, up to 256 1.05); from there on two win where windows are long: 384000 rows and windows of
+// 1088 tokens 692 us the call with one block, 634 with two, 1.6 million 3.15 ms, 3.04; 8.4 million, spans of 512, with the
+// merge 5.0 ms, 4.8.  Up to 2048 workgroups of half spans of 512 tokens and less 1.00 to 1.02.
+int window_blocks(const Problem& pb, double tokens) {
+  const double rows = (double)pb.Hq * pb.Lq;
+  return rows >= 512 * 256 && rows * tokens >= 2048.0 * 256 * 256 ? 2 : 1;
+}
+
+MfmaWs carve(const Problem& pb, int tm, size_t part_elem = sizeof(bf16_t)) {
   MfmaWs w;
   w.tm = tm;
   w.B = pb.Hkv * (int)pb.n;
@@ -1487,6 +1753,7 @@ MfmaWs carve(const Problem& pb, int tm = TM, size_t part_elem = sizeof(bf16_t)) 
     return at;
   };
   w.counts = take((size_t)w.B * sizeof(int));
+  w.claims = take(8 * 32 * sizeof(int));
   w.plan = bucket_plan(pb);
   w.unit_cnt = take((size_t)pb.Hq * w.plan.units * pb.n * sizeof(int));
   w.item_off = take((size_t)(w.B + 1) * sizeof(int));
@@ -1506,7 +1773,7 @@ MfmaWs carve(const Problem& pb, int tm = TM, size_t part_elem = sizeof(bf16_t)) 
 template <typename Items>
 bool launch_buckets(const Problem& pb, const MfmaWs& w, const int32_t* idx, int* unit_cnt, int* counts,
                     int* item_off, int* tile_off, int* cursor, int4* tile_info, int* items, float* part_lse,
-                    const Items& it, int* flag, hipStream_t st) {
+                    const Items& it, int* flag, int* claims, hipStream_t st) {
   const int n = (int)pb.n;
   const int per_block = 4;  // 4 * 4096 counters = 64 KB
   const dim3 grid((unsigned)((w.plan.units + per_block - 1) / per_block), pb.Hq);
@@ -1516,7 +1783,7 @@ bool launch_buckets(const Problem& pb, const MfmaWs& w, const int32_t* idx, int*
   hipLaunchKernelGGL(bucket_unit_scan_kernel, dim3((n + 31) / 32, pb.Hkv), dim3(1024), 0, st, unit_cnt, counts,
                      pb.G * w.plan.units, n);
   hipLaunchKernelGGL(bucket_scan_kernel, dim3(1), dim3(1024), 0, st, counts, item_off, tile_off, cursor, w.B,
-                     w.tm, flag);
+                     w.tm, flag, claims);
   hipLaunchKernelGGL(bucket_tiles_kernel, dim3(w.B), dim3(256), 0, st, tile_off, item_off, tile_info, items, w.tm);
   hipLaunchKernelGGL((bucket_kernel<true, Items>), grid, dim3(64 * per_block), lds, st, idx, unit_cnt, cursor,
                      items, part_lse, pb.Lq, pb.q_pos0, pb.G, pb.topk, n, w.plan, it);
@@ -1541,12 +1808,13 @@ bool prefill_attention_mfma_supported(const Problem& pb) {
          (int64_t)pb.Hq * pb.qsh + pb.Lq * pb.qst < ((int64_t)1 << 31);
 }
 
-size_t prefill_attention_mfma_ws_bytes(const Problem& pb) { return carve(pb).total; }
+size_t prefill_attention_mfma_ws_bytes(const Problem& pb) { return carve(pb, 128 * routed_blocks(pb)).total; }
 
 sl_status prefill_attention_mfma(const Problem& pb, const void* Q, const void* K, const void* V,
                                  const int32_t* idx, void* O, float* LSE, void* ws,
                                  hipStream_t st) {
-  const MfmaWs w = carve(pb);
+  const int blocks = routed_blocks(pb);
+  const MfmaWs w = carve(pb, 128 * blocks);
   DeviceSetup dev;
   if (!device_setup(&dev) || !dev.lds_ok) return SL_ERR_LAUNCH;
   char* base = static_cast<char*>(ws);
@@ -1570,6 +1838,7 @@ sl_status prefill_attention_mfma(const Problem& pb, const void* Q, const void* K
   a.tile_off = tile_off;
   a.tile_info = tile_info;
   a.items = items;
+  a.claims = reinterpret_cast<int*>(base + w.claims);
   a.part_o = part_o;
   a.part_of = nullptr;
   a.part_lse = part_lse;
@@ -1597,25 +1866,31 @@ sl_status prefill_attention_mfma(const Problem& pb, const void* Q, const void* K
 
   if (pb.topk > 0) {
     if (!launch_buckets(pb, w, idx, unit_cnt, counts, item_off, tile_off, cursor, tile_info, items, part_lse,
-                        GridItems{pb.A}, nullptr, st))
+                        GridItems{pb.A}, nullptr, a.claims, st))
       return SL_ERR_LAUNCH;
     if (pb.prof_start) (void)hipEventRecord(pb.prof_start, st);
-    if (pb.A < pb.S && !pb.combined)  // overlapping spans in one joint softmax: per-row clipping
-      hipLaunchKernelGGL(span_flash_routed_kernel<true>, dim3(dev.grid), dim3(FlashLds<2>::kThreads),
-                         FlashLds<2>::kBytes, st, a);
-    else
-      hipLaunchKernelGGL(span_flash_routed_kernel<false>, dim3(dev.grid), dim3(FlashLds<2>::kThreads),
-                         FlashLds<2>::kBytes, st, a);
+    auto routed = [&](auto columns) {
+      constexpr int CB = decltype(columns)::value;
+      const dim3 grid(2 * dev.grid), block(256);
+      if (pb.A < pb.S && !pb.combined)  // overlapping spans in one joint softmax: per-row clipping
+        hipLaunchKernelGGL((span_flash_wide_kernel<Spans::kClipped, CB>), grid, block, WideLds::kBytes, st, a);
+      else
+        hipLaunchKernelGGL((span_flash_wide_kernel<Spans::kWhole, CB>), grid, block, WideLds::kBytes, st, a);
+    };
+    if (blocks == 1) routed(One{});
+    else routed(Two{});
     if (pb.prof_stop) (void)hipEventRecord(pb.prof_stop, st);
   }
-  const unsigned lgrid = local_grid(pb.Lq, pb.A, pb.Hkv, pb.G);
-  if (!pb.combined && pb.topk <= 8) {  // the window kernel merges and writes the final output
-    hipLaunchKernelGGL(span_flash_local_kernel<true>, dim3(lgrid), dim3(FlashLds<1>::kThreads),
-                       FlashLds<1>::kBytes, st, a);
-    return hipGetLastError() == hipSuccess ? SL_OK : SL_ERR_LAUNCH;
-  }
-  hipLaunchKernelGGL(span_flash_local_kernel<false>, dim3(lgrid), dim3(FlashLds<1>::kThreads),
-                     FlashLds<1>::kBytes, st, a);
+  const bool fused = !pb.combined && pb.topk <= 8;  // the window kernel merges and writes the final output
+  auto window = [&](auto columns) {
+    constexpr int CB = decltype(columns)::value;
+    const dim3 grid(local_grid(pb.Lq, pb.A, pb.Hkv, pb.G, 128 * CB)), block(256);
+    if (fused) hipLaunchKernelGGL((span_window_wide_kernel<true, CB>), grid, block, WideLds::kBytes, st, a);
+    else hipLaunchKernelGGL((span_window_wide_kernel<false, CB>), grid, block, WideLds::kBytes, st, a);
+  };
+  if (window_blocks(pb, 0.5 * pb.A) == 1) window(One{});
+  else window(Two{});
+  if (fused) return hipGetLastError() == hipSuccess ? SL_OK : SL_ERR_LAUNCH;
   const int64_t rows = (int64_t)pb.Hq * pb.Lq;
   const dim3 mgrid((unsigned)((rows + 15) / 16));
 #define SL_MERGE(KM)                                                                             \
@@ -1718,9 +1993,9 @@ bool fine_setup(DeviceSetup* out) {
            hipFuncSetAttribute(reinterpret_cast<const void*>(local), hipFuncAttributeMaxDynamicSharedMemorySize, bytes) == hipSuccess;
   };
   if (!done[dev]) {
-    done[dev] = allow(span_flash_routed_kernel<true, D, true>, span_flash_local_kernel<false, D, true>, FlashLds<1, D>::kBytes);
+    done[dev] = allow(span_flash_routed_kernel<D, TN>, span_flash_local_kernel<D, TN>, FlashLds<D>::kBytes);
     if constexpr (D == 64)
-      done[dev] = done[dev] && allow(span_flash_routed_kernel<true, D, true, 32>, span_flash_local_kernel<false, D, true, 32>, FlashLds<1, D, 32>::kBytes);
+      done[dev] = done[dev] && allow(span_flash_routed_kernel<D, 32>, span_flash_local_kernel<D, 32>, FlashLds<D, 32>::kBytes);
   }
   return done[dev];
 }
@@ -1745,6 +2020,7 @@ sl_status fine_pass(const Problem& pb, const DeviceSetup& dev, const bf16_t* Q, 
   a.tile_off = tile_off;
   a.tile_info = tile_info;
   a.items = items;
+  a.claims = reinterpret_cast<int*>(base + w.claims);
   a.part_of = part_o;
   a.part_lse = part_lse;
   a.O = O;
@@ -1767,19 +2043,19 @@ sl_status fine_pass(const Problem& pb, const DeviceSetup& dev, const bf16_t* Q, 
   a.kvst = pb.kvst;
   if (!launch_buckets(pb, w, idx, reinterpret_cast<int*>(base + w.unit_cnt), reinterpret_cast<int*>(base + w.counts),
                       item_off, tile_off, reinterpret_cast<int*>(base + w.cursor), tile_info, items, part_lse,
-                      GridItems{pb.A}, flag, st))
+                      GridItems{pb.A}, flag, a.claims, st))
     return SL_ERR_LAUNCH;
   if (pb.prof_start) (void)hipEventRecord(pb.prof_start, st);
-  const unsigned lgrid = local_grid(pb.Lq, pb.A, pb.Hkv, pb.G);
+  const unsigned lgrid = local_grid(pb.Lq, pb.A, pb.Hkv, pb.G, TG);
   auto routed = [&](auto tile) {
     constexpr int TT = decltype(tile)::value;
-    hipLaunchKernelGGL((span_flash_routed_kernel<true, D, true, TT>), dim3(fine_blocks(TT) * dev.grid), dim3(256),
-                       (FlashLds<1, D, TT>::kBytes), st, a);
+    hipLaunchKernelGGL((span_flash_routed_kernel<D, TT>), dim3(fine_blocks(TT) * dev.grid), dim3(256),
+                       (FlashLds<D, TT>::kBytes), st, a);
   };
   auto local = [&](auto tile) {
     constexpr int TT = decltype(tile)::value;
-    hipLaunchKernelGGL((span_flash_local_kernel<false, D, true, TT>), dim3(lgrid), dim3(256),
-                       (FlashLds<1, D, TT>::kBytes), st, a);
+    hipLaunchKernelGGL((span_flash_local_kernel<D, TT>), dim3(lgrid), dim3(256),
+                       (FlashLds<D, TT>::kBytes), st, a);
   };
   using Short = std::integral_constant<int, D == 64 ? 32 : TN>;
   using Long = std::integral_constant<int, TN>;
@@ -1858,36 +2134,56 @@ sl_status prefill_attention_fine(const Problem& pb, const void* Q, const void* K
 // ------------------------------------------------------------------ the paper's geometry on the matrix cores
 namespace {
 
-// End-block size E of the buckets: the smallest power-of-two multiple of 64 tokens that gives a
-// bucket about two 256-row tiles of items on average, and at most 4096 blocks per kv head.
-int anchor_block_tokens(const Problem& pb) {
-  const int64_t items = (int64_t)pb.G * pb.Lq * (pb.topk > 0 ? pb.topk : 1);
-  int64_t E = 64;
-  while (E < 4096 && (items * E < 512 * pb.L || (pb.L + E - 1) / E > 4096)) E <<= 1;
-  return (int)E;
-}
-
-Problem anchor_view(const Problem& pb) {
+Problem anchor_view(const Problem& pb, int E) {
   Problem q = pb;
-  q.A = anchor_block_tokens(pb);
+  q.A = E;
   q.n = (pb.L + q.A - 1) / q.A;
   return q;
+}
+
+// 4096 blocks per kv head (their histograms), 32-bit positions in the tile-by-tile item list.
+bool anchor_blocks_fit(const Problem& pb, int E) {
+  const int64_t n = (pb.L + E - 1) / E;
+  return n <= 4096 && (int64_t)pb.Hq * pb.Lq * pb.topk + ((int64_t)pb.Hkv * n + 1) * TM < ((int64_t)1 << 31);
+}
+
+// End-block size E of the buckets, a power-of-two multiple of 64 tokens, at most 4096 blocks per kv head.  A tile walks E
+// tokens and the length of a span; smaller blocks leave more tiles that are not full.  With x items per token and kv head the
+// tokens walked are (x E / rows + 1/2) (E + span) for every E of them, least at E^2 = rows * span / 2x.  Where that leaves
+// compute units without a tile the call lasts as long as its longest tile, so blocks are halved while there are fewer.
+int anchor_block_tokens(const Problem& pb, double span, int tile_rows) {
+  const double x = (double)pb.G * pb.Lq * pb.topk / pb.L, best = sqrt(0.5 * tile_rows * span / x);
+  int64_t E = 64;
+  while (E < 4096 && E * 1.4142 < best) E <<= 1;
+  while (E > 64 && pb.Hkv * (pb.L / (double)E + x * pb.L / tile_rows) < 256) E >>= 1;
+  while (!anchor_blocks_fit(pb, (int)E)) E <<= 1;
+  return (int)E;
 }
 
 }  // namespace
 
 bool prefill_anchor_mfma_supported(const Problem& pb, int64_t window) {
-  const Problem q = anchor_view(pb);
-  return window >= 1 && pb.topk >= 1 && pb.dtype == SL_BF16 && pb.D == HD && q.n <= 4096 &&
+  return window >= 1 && pb.topk >= 1 && pb.dtype == SL_BF16 && pb.D == HD && anchor_blocks_fit(pb, 4096) &&
          (int64_t)pb.G * pb.Lq < ((int64_t)1 << 26) &&
          pb.L <= kMaxTokens &&
          64 * pb.kvst * 2 < ((int64_t)1 << 31) &&
          (int64_t)pb.Hq * pb.Lq * (pb.topk + 1) < ((int64_t)1 << 31) &&
-         (int64_t)pb.Hq * pb.Lq * pb.topk + ((int64_t)pb.Hkv * q.n + 1) * TM < ((int64_t)1 << 31) &&
          (int64_t)pb.Hq * pb.qsh + pb.Lq * pb.qst < ((int64_t)1 << 31);
 }
 
-size_t prefill_anchor_mfma_ws_bytes(const Problem& pb) { return carve(anchor_view(pb)).total; }
+// Enough for every block size, so that it does not depend on the spans' length.
+size_t prefill_anchor_mfma_ws_bytes(const Problem& pb) {
+  size_t most = 0;
+  for (int E = 64; E <= 4096; E <<= 1)
+    if (anchor_blocks_fit(pb, E)) {
+      const Problem q = anchor_view(pb, E);
+      for (int blocks = 1; blocks <= 2; ++blocks) {
+        const size_t bytes = carve(q, 128 * blocks).total;
+        most = bytes > most ? bytes : most;
+      }
+    }
+  return most;
+}
 
 // Span-attention and combination on the paper's geometry (Section 3.3-3.4, Algorithm 1), matrix-core
 // form following Section 4.3's bucketing by key-block footprint: (row, slot) pairs are bucketed by
@@ -1896,8 +2192,12 @@ size_t prefill_anchor_mfma_ws_bytes(const Problem& pb) { return carve(anchor_vie
 sl_status prefill_anchor_attention_mfma(const Problem& pb, int64_t window, int b, int f, int root,
                                         const void* Q, const void* K, const void* V,
                                         const int32_t* anchors, void* O, void* ws, hipStream_t st) {
-  const Problem q = anchor_view(pb);
-  const MfmaWs w = carve(q);
+  const int64_t mid = pb.q_pos0 + pb.Lq / 2, reach = (int64_t)(b + f) * span_base_length(mid, root);
+  const double span = (double)(reach < mid ? reach : mid) + 1;
+  Problem q = anchor_view(pb, anchor_block_tokens(pb, span, 256));
+  const int blocks = routed_blocks(q);
+  if (blocks == 1) q = anchor_view(pb, anchor_block_tokens(pb, span, 128));
+  const MfmaWs w = carve(q, 128 * blocks);
   DeviceSetup dev;
   if (!device_setup(&dev) || !dev.lds_ok) return SL_ERR_LAUNCH;
   char* base = static_cast<char*>(ws);
@@ -1921,6 +2221,7 @@ sl_status prefill_anchor_attention_mfma(const Problem& pb, int64_t window, int b
   a.tile_off = tile_off;
   a.tile_info = tile_info;
   a.items = items;
+  a.claims = reinterpret_cast<int*>(base + w.claims);
   a.part_o = part_o;
   a.part_of = nullptr;
   a.part_lse = part_lse;
@@ -1951,15 +2252,18 @@ sl_status prefill_anchor_attention_mfma(const Problem& pb, int64_t window, int b
   wa.plan.unit_h = 1;  // items of a bucket by row, then by head
   wa.plan.unit_u = pb.G;
   if (!launch_buckets(q, wa, anchors, unit_cnt, counts, item_off, tile_off, cursor, tile_info, items, part_lse,
-                      AnchorItems{window, b, f, root, a.E}, nullptr, st))
+                      AnchorItems{window, b, f, root, a.E}, nullptr, a.claims, st))
     return SL_ERR_LAUNCH;
   if (pb.prof_start) (void)hipEventRecord(pb.prof_start, st);
-  hipLaunchKernelGGL(span_flash_anchor_kernel, dim3(dev.grid), dim3(FlashLds<2>::kThreads),
-                     FlashLds<2>::kBytes, st, a);
+  if (blocks == 1)
+    hipLaunchKernelGGL((span_flash_wide_kernel<Spans::kAnchor, 1>), dim3(2 * dev.grid), dim3(256), WideLds::kBytes, st, a);
+  else
+    hipLaunchKernelGGL((span_flash_wide_kernel<Spans::kAnchor, 2>), dim3(2 * dev.grid), dim3(256), WideLds::kBytes, st, a);
   if (pb.prof_stop) (void)hipEventRecord(pb.prof_stop, st);
-  const unsigned lgrid = local_grid(pb.Lq, a.A, pb.Hkv, pb.G);
-  hipLaunchKernelGGL(span_flash_local_kernel<false>, dim3(lgrid), dim3(FlashLds<1>::kThreads),
-                     FlashLds<1>::kBytes, st, a);
+  if (window_blocks(pb, (double)(window < pb.L ? window : pb.L)) == 1)
+    hipLaunchKernelGGL((span_window_wide_kernel<false, 1>), dim3(local_grid(pb.Lq, a.A, pb.Hkv, pb.G, 128)), dim3(256), WideLds::kBytes, st, a);
+  else
+    hipLaunchKernelGGL((span_window_wide_kernel<false, 2>), dim3(local_grid(pb.Lq, a.A, pb.Hkv, pb.G, 256)), dim3(256), WideLds::kBytes, st, a);
   const int64_t rows = (int64_t)pb.Hq * pb.Lq;
   const dim3 mgrid((unsigned)((rows + 15) / 16));
   // the first position with topk anchors outside the window: stride indices floor(window^(1/root)) and up

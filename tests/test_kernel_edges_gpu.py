@@ -954,3 +954,69 @@ def test_prefill_search_of_many_candidates_at_both_grid_sizes(Lq, k):
     two, _ = B.sl_span_search_prefill(Q, K, None, 2, k, q_pos0=L - Lq, want_scores=True)
     torch.cuda.synchronize()
     assert torch.equal(idx, two)
+
+
+TILES = [
+    # kind     Hq  Hkv L      Lq     S or w  A    k
+    ("grid", 8, 1, 9001, 8200, 64, 64, 4),          # joint: routed tiles of 256 rows, windows of 128
+    ("grid", 16, 1, 20011, 16400, 1024, 1024, 2),   # windows of 256 that merge, too
+    ("gated", 8, 1, 9001, 8200, 64, 64, 4),
+    ("grid", 8, 1, 9001, 8200, 128, 64, 4),         # clipped spans
+    ("anchor", 8, 1, 17003, 16391, 1088, 1, 2),     # windows of 256
+]
+
+
+def tile_call(kind, Q, K, V, idx, sc, S, A, q0):
+    if kind == "anchor":
+        return (B.sl_anchor_attention_prefill(Q, K, V, idx, sc, S, 3, 1, q_pos0=q0),)
+    stride = 0 if A == S else A
+    if kind == "gated":
+        return (B.sl_span_attention_combined_prefill(Q, K, V, idx, sc, S, q_pos0=q0, span_stride=stride),)
+    return B.sl_span_attention_prefill(Q, K, V, idx, S, q_pos0=q0, span_stride=stride)
+
+
+def tile_inputs(kind, Hq, Hkv, L, Lq, S, A, k):
+    q0 = L - Lq
+    Q, K, V = make(71, Hq, Hkv, L, 128, torch.bfloat16, scale=0.5, Lq=Lq)
+    if kind == "anchor":
+        idx, sc = B.sl_anchor_search_prefill(Q, K, k, S, q_pos0=q0, want_scores=True)
+    else:
+        idx, sc = B.sl_span_search_prefill(Q, K, None, A, k, q_pos0=q0, want_scores=True)
+    return q0, Q, K, V, idx, torch.where(torch.isfinite(sc), sc, 0.0)
+
+
+@pytest.mark.parametrize("kind,Hq,Hkv,L,Lq,S,A,k", TILES)
+def test_rows_are_alike_in_tiles_of_one_and_two_column_blocks(kind, Hq, Hkv, L, Lq, S, A, k):
+    """A long call takes tiles of two blocks of columns, its pieces of one: the same arithmetic for every row, whatever tile,
+    wavefront (31 to 33, 63 to 65 rows) and kv rows at a time take it."""
+    q0, Q, K, V, idx, sc = tile_inputs(kind, Hq, Hkv, L, Lq, S, A, k)
+    whole = tile_call(kind, Q, K, V, idx, sc, S, A, q0)
+    at = 0
+    for n in (1, 31, 33, 65, 127, 129, 300, 1025):
+        r0 = min(Lq - n, at)
+        part = tile_call(kind, Q[:, r0:r0 + n].contiguous(), K[:, :q0 + r0 + n].contiguous(), V[:, :q0 + r0 + n].contiguous(),
+                         idx[:, r0:r0 + n].contiguous(), sc[:, r0:r0 + n].contiguous(), S, A, q0 + r0)
+        torch.cuda.synchronize()
+        for w, p in zip(whole, part):
+            assert torch.equal(w[:, r0:r0 + n], p), (kind, n, r0)
+        at += Lq // 8
+
+
+@pytest.mark.parametrize("rows", ["few", "many"])
+@pytest.mark.parametrize("kind,Hq,Hkv,L,Lq,S,A,k", TILES)
+def test_queries_that_are_not_finite_reach_no_other_row(kind, Hq, Hkv, L, Lq, S, A, k, rows):
+    """Row sums come from a product that mixes columns of a tile: a row whose scores are not numbers, or infinite, is NaN,
+    and every other row is what it was."""
+    q0, Q, K, V, idx, sc = tile_inputs(kind, Hq, Hkv, L, Lq, S, A, k)
+    if rows == "few":
+        q0, Q, idx, sc = q0 + Lq - 200, Q[:, -200:].contiguous(), idx[:, -200:].contiguous(), sc[:, -200:].contiguous()
+    clean = tile_call(kind, Q, K, V, idx, sc, S, A, q0)
+    spoilt, bad = Q.clone(), torch.zeros(Q.shape[:2], dtype=torch.bool, device=DEV)
+    for h, r, x in ((0, 3, math.nan), (Hq - 1, Q.shape[1] // 2, math.nan), (1, 17, math.inf), (2, Q.shape[1] - 1, -math.inf)):
+        spoilt[h, r, 5] = x
+        bad[h, r] = True
+    got = tile_call(kind, spoilt, K, V, idx, sc, S, A, q0)
+    torch.cuda.synchronize()
+    assert bool(torch.isnan(got[0][bad]).all())
+    for c, g in zip(clean, got):
+        assert torch.equal(c[~bad], g[~bad])
