@@ -15,7 +15,7 @@
 //                                   with the causal mask; joint form with topk <= 8: merges
 //                                   the row's routed partials in its epilogue (log-sum-exp) and
 //                                   writes O and LSE; otherwise writes the row's last partial
-//   span_flash_routed / _local      the same two with fp32 softmax weights and partials (spans of
+//   span_fine / span_fine_window    the same two with fp32 softmax weights and partials (spans of
 //                                   any length, D = 64)
 //   merge_partials / merge_combined streaming merge of the <= topk + 1 partials of every row
 //                                   (topk > 8, and the gated combination of Section 3.4)
@@ -43,12 +43,6 @@ typedef float f32x8 __attribute__((ext_vector_type(8)));
 constexpr int TG = 128;            // rows of a tile of the fp32-weight kernels (4 wavefronts x 32 columns)
 constexpr int TM = 256;            // rows of a tile of the kernels with bf16 weights (4 wavefronts x 64 columns)
 constexpr int TN = 64;             // kv positions per staged tile
-// Of the kernels with fp32 weights, too; at D = 64 tiles of 32 leave room (registers, LDS) for a third workgroup per
-// compute unit and end closer to a span's end: 20011 rows in spans of 142 1213 -> 1098 us, 8000 in spans of 90, top-4, 260 ->
-// 221 (short_routed_tiles: not where the tiles are few).  At D = 128 the registers of a third do not suffice: 2000 ->
-// 2164.  (Nor does it help there to ask for the next tile's first stages, queries and record before a tile's output leaves,
-// over the stages of its last kv tile: 1929 -> 2015.)
-constexpr int fine_blocks(int tile) { return tile == 32 ? 3 : 2; }  // workgroups per compute unit
 constexpr int HD = 128;            // head dimension of the kernels with bf16 weights
 
 // LDS of the flash kernels (dynamic).  Main loop: two stages of the K and of the V tile, filled
@@ -61,24 +55,7 @@ constexpr int HD = 128;            // head dimension of the kernels with bf16 we
 // V is staged as it lies in memory and transposed by the LDS reads (ds_read_b64_tr_b16): a transposed
 // copy of V in the workspace cost a pass over the whole cache per call, however few the rows (63 us for
 // 4000 new rows behind 196000 tokens).
-// Output rows go out through LDS (piece p of row r at p ^ (r & 15)), 256 bytes a row, over stages that are dead by then.
-// fp32-weight kernels: 64 columns at a time; at D = 64 the V stages are too small to lie under the output.
-template <int D, int TNK = TN>
-struct FlashLds {
-  static constexpr int kStageElems = TNK * D;  // D = 128: 8192 bf16 = 16 KB
-  static constexpr int kStages = 2;            // of K and of V
-  static constexpr int kV = 0;
-  static constexpr int kK = kStages * kStageElems * 2;
-  static constexpr int kStagesEnd = 2 * kStages * kStageElems * 2;
-  static constexpr bool kOver = D == 128;  // the output region lies over the V stages
-  static constexpr int kOutBytes = TG * 256;
-  static constexpr int kOut = kOver ? 0 : kStagesEnd;                    // [TG][256 bytes]
-  static constexpr int kRowOut = kOver ? kStagesEnd : kOut + kOutBytes;  // int64[TG]
-  static constexpr int kRowLse = kRowOut + TG * 8;                       // float[TG]
-  static constexpr int kBytes = kRowLse + TG * 4;
-  static constexpr int kBlocksPerWave = kStageElems * 2 / 1024 / 4;  // 1 KB blocks of a staged tile per wavefront
-};
-
+// Output rows go out through LDS in swizzled pieces, over stages that are dead by then.
 #define SL_LDS_PTR(p) ((__attribute__((address_space(3))) void*)(p))
 
 // Direct global->LDS loads go through buffer instructions: base is wave-uniform, `bytes` bounds the
@@ -452,291 +429,6 @@ __device__ __forceinline__ int perm_row(int rho) {
 
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-
-// One tile of 128 rows as seen by a lane: the kv head and kv range [kv_begin, kv_end) shared by the workgroup (walked in kv
-// tiles; what lies behind its end is zero), and the lane's own query column.
-struct TileDesc {
-  int kv;
-  int64_t kv_begin, kv_end;
-  int64_t q_off;      // element offset of the lane's Q vector
-  int64_t row_out;    // partial record index of the lane's column, -1 = no row
-  int64_t i_q, lo_q;  // the last and the first token that the row attends
-};
-
-// Direct global -> LDS loads of N blocks of 1 KB.
-template <int N>
-__device__ __forceinline__ void stage_blocks(bf16_t* dst, BufferRsrc from, const uint32_t (&off)[N]) {
-#pragma unroll
-  for (int i = 0; i < N; ++i) __builtin_amdgcn_raw_ptr_buffer_load_lds(from, SL_LDS_PTR(dst + i * 512), 16, off[i], 0, 0, 0);
-}
-
-// One tile of 128 rows of the fp32-weight kernels.  All threads call.  Every softmax weight is split into three bf16 parts,
-// which hold the 24 bits of its mantissa between them, and V is multiplied with all three; the row sum is taken over the
-// unsplit weights, partials are written in fp32.
-template <int D, int TT>
-__device__ __forceinline__ void flash_tile(const FlashArgs& a, char* const lds, const TileDesc& cur) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int uwave = __builtin_amdgcn_readfirstlane(wave);
-  const int qc = lane & 31, hf = lane >> 5;
-  const int srow = wave * 32 + qc;
-  using Lds = FlashLds<D, TT>;
-  constexpr int kStageElems = Lds::kStageElems;
-  constexpr int PPR = D / 8, RPB = 64 / PPR;  // 16-byte pieces per staged row, rows per 1 KB block
-  constexpr int NDT = D / 32, NKK = D / 16;   // 32-row output tiles, 16-deep steps of the QK product
-  constexpr int BPW = Lds::kBlocksPerWave;
-  bf16_t* const ldsV = reinterpret_cast<bf16_t*>(lds + Lds::kV);
-  bf16_t* const ldsK = reinterpret_cast<bf16_t*>(lds + Lds::kK);
-
-  // Direct global -> LDS staging of one (K, V) tile pair in 1 KB blocks (4 rows each at D = 128); lane L
-  // of a block lands at byte 16*L.
-  // Per-lane byte offsets are loop-invariant 32-bit values; the kv head and the tile position
-  // go into the wave-uniform base pointer.
-  uint32_t koff[BPW], voff[BPW];
-#pragma unroll
-  for (int i = 0; i < BPW; ++i) {
-    const int row = (wave * BPW + i) * RPB + lane / PPR, pc = lane % PPR;
-    koff[i] = (uint32_t)((row * a.kvst + (pc ^ k_swizzle<D>(row)) * 8) * sizeof(bf16_t));
-    voff[i] = (uint32_t)((row * a.kvst + (pc ^ v_swizzle<D>(row)) * 8) * sizeof(bf16_t));
-  }
-  // wavefront w fills blocks w*BPW .. w*BPW + BPW-1 of both tiles; rows past the end of the tile's range are zeros in LDS
-  auto stage = [&](int64_t t0, int b) {
-    const int rows = __builtin_amdgcn_readfirstlane(cur.kv_end - t0 < TT ? (int)(cur.kv_end - t0) : TT);
-    const int64_t first = uniform64((int64_t)cur.kv * a.kvsh + t0 * a.kvst);
-    const uint32_t bytes = (uint32_t)(((rows - 1) * a.kvst + D) * sizeof(bf16_t));
-    stage_blocks(ldsK + b * kStageElems + uwave * BPW * 512, buffer_of(a.K + first, bytes), koff);
-    stage_blocks(ldsV + b * kStageElems + uwave * BPW * 512, buffer_of(a.V + first, bytes), voff);
-  };
-  stage(cur.kv_begin, 0);
-  // Q row of the lane's column, as the B operand of S^T = K Q^T
-  bf16x8 qf[NKK];
-#pragma unroll
-  for (int kk = 0; kk < NKK; ++kk) qf[kk] = *reinterpret_cast<const bf16x8*>(a.Q + cur.q_off + kk * 16 + hf * 8);
-
-  f32x16 o[NDT];
-#pragma unroll
-  for (int dt = 0; dt < NDT; ++dt)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) o[dt][r] = 0.f;
-  float m = -INFINITY, l = 0.f;  // m in log2 units of the scaled logit
-  constexpr int NS = TT / 32, NP = TT / 16;  // 32-row score tiles, weight fragments
-  bf16x8 pb[NP], pl[NP], pm[NP];  // P^T fragments: the weights' leading parts, what those leave, and what that leaves
-
-  const int krow = perm_row(qc);
-  const int kswz = k_swizzle<D>(krow);  // swizzle key of this lane's K rows (32*sub does not change it)
-  // V^T fragments come from transposing reads: 16 lanes read a [4 kv][16 d] block, 8 bytes each, and lane
-  // i of them receives column i.  Lane offset (elements) of the block for d tile dt, kv rows 8*hf .. 8*hf+3.
-  const int vrow = (lane & 15) >> 2;
-  int vlane[NDT];
-#pragma unroll
-  for (int dt = 0; dt < NDT; ++dt)
-    vlane[dt] = (8 * hf + vrow) * D +
-                (((4 * dt + 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1)) ^ v_swizzle<D>(vrow)) << 3) + 4 * (lane & 1);
-  const float sc = a.scale_log2e;
-  // the lane's own range [lo_q, i_q] as 32-bit offsets from the tile's first token
-  auto offset_of = [&](int64_t t) {
-    const int64_t d = t - cur.kv_begin;
-    return (int)(d < -1 ? -1 : d > (1 << 30) ? (1 << 30) : d);
-  };
-  const int lo_r = offset_of(cur.lo_q), hi_r = offset_of(cur.i_q);
-
-  // S^T = K Q^T (32-row parts of the tile), mask, running maximum, exponentials -> pb, pl, pm.
-  // LDS fragment reads run four MFMAs ahead (0x100 = LDS read, 0x008 = MFMA).
-  // base: the kv tile's offset from the tile's first token.
-  auto qk_softmax = [&](const bf16_t* kt, int base) {
-    f32x16 s[NS];
-#pragma unroll
-    for (int sub = 0; sub < NS; ++sub)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) s[sub][r] = 0.f;
-#pragma unroll
-    for (int kk = 0; kk < NKK; ++kk)
-#pragma unroll
-      for (int sub = 0; sub < NS; ++sub) {
-        const bf16x8 ka = *reinterpret_cast<const bf16x8*>(
-            &kt[(32 * sub + krow) * D + (((2 * kk + hf) ^ kswz) << 3)]);
-        s[sub] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka, qf[kk], s[sub], 0, 0, 0);
-      }
-    __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
-#pragma unroll
-    for (int i = 0; i < NS * NKK - 4; ++i) {
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-    }
-    __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
-    // The softmax arithmetic below competes for issue slots with the MFMA stream of the SIMD's
-    // other wavefront; that one needs a slot every 32 cycles, this one needs most of them.
-    __builtin_amdgcn_s_setprio(3);
-
-    // Per-row ranges (the causal window, a span clipped behind a lower one): only the tiles at the ends of a wavefront's
-    // ranges are masked, one unsigned compare per score.
-    if (__builtin_amdgcn_ballot_w64(lo_r > base || hi_r < base + TT - 1) != 0ull) {
-      const uint32_t width = hi_r >= lo_r ? (uint32_t)(hi_r - lo_r) : 0u;
-      const uint32_t u = hi_r >= lo_r ? (uint32_t)(base + 8 * hf - lo_r) : 0x80000000u;
-#pragma unroll
-      for (int sub = 0; sub < NS; ++sub)
-#pragma unroll
-        for (int r = 0; r < 16; ++r)
-          s[sub][r] = u + (uint32_t)(32 * sub + 16 * (r >> 3) + (r & 7)) <= width ? s[sub][r] : -INFINITY;
-    }
-    float mx = -INFINITY;
-#pragma unroll
-    for (int sub = 0; sub < NS; ++sub)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[sub][r]);
-    mx = pair_max(mx) * sc;
-    // Lazy rescale, decided per column: a column's running maximum only moves when that column
-    // grew by more than 2^8; until then its exponentials are taken against the old maximum
-    // (p <= 256).  The branch is per wavefront, the arithmetic of a column does not depend on the
-    // columns it shares the wavefront with (so a row's result does not depend on its tile-mates).
-    const bool grow = mx > m + 8.f || (m == -INFINITY && mx > -INFINITY);
-    if (__builtin_amdgcn_ballot_w64(grow) != 0ull) {
-      const float alpha = grow ? fast_exp2(m - mx) : 1.f;  // m = -inf: 0, and l and o are still 0
-      m = grow ? mx : m;
-      l *= alpha;
-#pragma unroll
-      for (int dt = 0; dt < NDT; ++dt)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) o[dt][r] *= alpha;
-    }
-    const float nm = m > -INFINITY ? -m : 0.f;  // whole column masked so far: exponentials are 0 anyway
-#pragma unroll
-    for (int ks = 0; ks < NP; ++ks) {
-      f32x8 p;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) p[e] = fast_exp2(fmaf(s[ks >> 1][8 * (ks & 1) + e], sc, nm));
-      pb[ks] = __builtin_convertvector(p, bf16x8);
-      const f32x8 rest = p - __builtin_convertvector(pb[ks], f32x8);
-      pl[ks] = __builtin_convertvector(rest, bf16x8);
-      pm[ks] = __builtin_convertvector(rest - __builtin_convertvector(pl[ks], f32x8), bf16x8);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) l += p[e];
-    }
-    __builtin_amdgcn_s_setprio(0);
-  };
-  // O^T += V^T P^T
-  auto pv = [&](const bf16_t* vt) {
-#pragma unroll
-    for (int ks = 0; ks < NP; ++ks)
-#pragma unroll
-      for (int dt = 0; dt < NDT; ++dt) {
-        const bf16x8 va = transposed8<D>(vt + vlane[dt] + 16 * ks * D);
-        o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, pb[ks], o[dt], 0, 0, 0);
-        o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, pl[ks], o[dt], 0, 0, 0);
-        o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, pm[ks], o[dt], 0, 0, 0);
-      }
-    constexpr int kPer = 3;  // MFMAs per fragment
-    __builtin_amdgcn_sched_group_barrier(0x100, 8, 1);
-#pragma unroll
-    for (int i = 0; i < NP * NDT - 4; ++i) {
-      __builtin_amdgcn_sched_group_barrier(0x008, kPer, 1);
-      __builtin_amdgcn_sched_group_barrier(0x100, 2, 1);
-    }
-    __builtin_amdgcn_sched_group_barrier(0x008, 4 * kPer, 1);
-  };
-
-  int b = 0;
-  for (int64_t t0 = cur.kv_begin; t0 < cur.kv_end; t0 += TT) {
-    // After the barrier the tile of this iteration is visible to every wavefront, and every wavefront is done with the
-    // stage of the previous one, which the next tile goes into.
-    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
-    __syncthreads();
-    if (t0 + TT < cur.kv_end) stage(t0 + TT, b ^ 1);
-    // a kv tile that none of the wavefront's rows attends is passed over (its weights would all be 0)
-    const int base = (int)(t0 - cur.kv_begin);
-    if (__builtin_amdgcn_ballot_w64(lo_r <= base + TT - 1 && hi_r >= base && hi_r >= lo_r) != 0ull) {
-      qk_softmax(ldsK + b * kStageElems, base);
-      pv(ldsV + b * kStageElems);
-    }
-    b ^= 1;
-  }
-  __syncthreads();
-
-  // epilogue, wavefront-local (no workgroup barrier): normalise and write the wavefront's 32 rows in fp32, 64 columns at a
-  // time, through its own slice of the output region (swizzled 16-byte pieces): 16 lanes per row, 16 bytes per lane.  LDS
-  // operations of one wavefront complete in issue order, so the reads below see the writes of the other lanes.
-  const float lt = pair_sum(l);
-  const float inv = 1.f / lt;
-  float* const fst = reinterpret_cast<float*>(lds + Lds::kOut);  // 256 bytes per row
-  int64_t* const row_out = reinterpret_cast<int64_t*>(lds + Lds::kRowOut);
-  float* const row_lse = reinterpret_cast<float*>(lds + Lds::kRowLse);
-  if (hf == 0) {
-    row_lse[srow] = (m + __log2f(lt)) * kLn2;
-    row_out[srow] = cur.row_out;
-  }
-  const ArgsPtr args = args_anew();
-  const int piece = lane & 15;
-#pragma unroll
-  for (int half = 0; half < D / 64; ++half) {
-#pragma unroll
-    for (int dd = 0; dd < 2; ++dd)
-#pragma unroll
-      for (int g4 = 0; g4 < 4; ++g4) {
-        f32x4 v;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = o[2 * half + dd][4 * g4 + e] * inv;
-        *reinterpret_cast<f32x4*>(&fst[srow * 64 + (((8 * dd + 2 * g4 + hf) ^ (srow & 15)) << 2)]) = v;
-      }
-    __builtin_amdgcn_wave_barrier();
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int row = wave * 32 + u * 4 + (lane >> 4);
-      const int64_t at = row_out[row];
-      const uint4 v = *reinterpret_cast<const uint4*>(&fst[row * 64 + ((piece ^ (row & 15)) << 2)]);
-      if (at >= 0) {
-        // past the caches, like the bf16 partials: they are gigabytes, the K/V tiles keep the L2
-        store16_stream(args->part_of + at * D + half * 64 + piece * 4, v);
-        if (half == 0 && piece == 0) args->part_lse[at] = row_lse[row];
-      }
-    }
-    __builtin_amdgcn_wave_barrier();
-  }
-}
-
-// Routed spans of the fp32-weight kernels: workgroups walk the tile list.  XCD x (workgroups with
-// blockIdx % 8 == x) owns the contiguous chunk [x*T/8, (x+1)*T/8) of the tile list; its
-// workgroups walk the chunk interleaved, so at any moment they sit on neighbouring tiles -- the
-// same one or two buckets -- and share the span through that XCD's L2.  Spans of any length at any offset; a row's range is
-// its whole span unless a.clip says that spans of a row overlap in one softmax: it starts then behind the end of the nearest
-// lower span that the row lists, so that every token of the union counts once.  Several workgroups per
-// compute unit: one's tile ends run beside the other's kv loop.
-template <int D, int TT>
-__global__ __launch_bounds__(256, fine_blocks(TT)) void span_flash_routed_kernel(const FlashArgs a) {
-  extern __shared__ __align__(16) char lds[];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int qrow = wave * 32 + (lane & 31);
-  const int64_t T = a.tile_off[a.Hq / a.G * a.n];
-  const int NWL = gridDim.x / 8;  // workgroups per XCD (the grid is a multiple of 8)
-  const int xcd = blockIdx.x % 8, wl = blockIdx.x / 8;
-  const int64_t t_end = T * (xcd + 1) / 8;
-  for (int64_t t = T * xcd / 8 + wl; t < t_end; t += NWL) {
-    const ArgsPtr p = args_anew();
-    const int4 info = p->tile_info[t];
-    const int item = p->items[t * TG + qrow];
-    TileDesc d;
-    d.kv = info.x / p->n;
-    const int j = info.x % p->n;
-    d.kv_end = (int64_t)(j + 1) * p->A;
-    d.kv_begin = d.kv_end - p->S > 0 ? d.kv_end - p->S : 0;
-    const int rowid = item >> 5, slot = item & 31;
-    const int hl = rowid / (int)p->Lq;
-    const int64_t r = rowid - (int64_t)hl * p->Lq;
-    const int h = d.kv * p->G + hl;
-    d.q_off = h * p->qsh + r * p->qst;
-    d.row_out = qrow < info.z ? ((int64_t)h * p->Lq + r) * (p->topk + 1) + slot : -1;
-    d.i_q = d.kv_end - 1;
-    d.lo_q = d.kv_begin;
-    if (p->clip) {
-      const int64_t c = (p->q_pos0 + r) / p->A;
-      const int32_t* irow = p->idx + ((int64_t)h * p->Lq + r) * p->topk;
-      for (int s2 = 0; s2 < p->topk; ++s2) {
-        const int64_t jj = irow[s2];
-        if (jj >= 0 && jj < c && jj < j && (jj + 1) * p->A > d.lo_q) d.lo_q = (jj + 1) * p->A;
-      }
-    }
-    flash_tile<D, TT>(a, lds, d);
-    __syncthreads();  // the next tile's stages lie over the output slices of all wavefronts
-  }
-}
 
 // ------------------------------------------------------------------ tiles of the kernels with bf16 weights
 // A wavefront has CB blocks of 32 query columns, a workgroup four wavefronts; two workgroups share a compute unit, so that one's
@@ -1307,28 +999,418 @@ __device__ __forceinline__ LocalTile local_tile(const LocalMap& lm, int columns,
   return t;
 }
 
+// ------------------------------------------------------------------ tiles of the kernels with fp32 weights
+// Tiles of 128 rows, one block of 32 query columns per wavefront, the kv rows 32 at a time; spans of any length at any offset.
+// Every softmax weight is split into three bf16 parts, which hold the 24 bits of its mantissa between them, and V is
+// multiplied with all three; the row sum is taken over the unsplit weights, partials are written in fp32.
+//
+// What bounds them: a step of 32 kv rows is 32 products (D = 128) and 40000 tiles take 119 us for it, 1.4 PFLOP/s, the power's
+// rate; a tile's 64 KB of partials take 490 us in all at what scattered 512-byte rows are written at (5.2 TB/s), its gathered
+// queries 190 at least.  20011 rows, top-8, 32:4 heads, spans of 142: routed part 1275 -> 972 us (D = 64: 641 -> 510); 6400 rows
+// with spans of 80 282 -> 191; 2500 with 50 89 -> 75.  What gave it:
+//   - steps of 32 instead of 64 kv rows, so that three workgroups share a compute unit (D = 64: four) and a span of 142 is 160
+//     rows' work instead of 192's;
+//   - the next tile's record, queries and first stage are asked for before a tile's output leaves, and its stores are not waited
+//     for: what is older than they are is (vector memory completes in order);
+//   - the split by cutting, not rounding: 11 instructions for two weights instead of 15;
+//   - lse stored through the caches, next to the row's other slots' (past them, 4 bytes at a time, 2500 rows: 98 us).
+// Measured and not taken: whole rows of 256 bytes per store instruction (+1 %), records two tiles ahead, fragment reads in a
+// fixed order (+-1 %), a workgroup per tile (+4 %).
+constexpr int fine_blocks(int D, int TT) { return TT * D == 4096 ? (D == 128 ? 3 : 4) : 2; }  // workgroups per compute unit
+
+template <int D, int TT>  // TT: tokens of a staged K and V tile
+struct FineLds {
+  static constexpr int kStage = TT * D;
+  static constexpr int kAhead = 4 * kStage * 2;          // per wavefront: the next tile's record (256 bytes) and items
+  static constexpr int kRow = kAhead + 4 * 512;          // per wavefront: int row[2][32], int q[32], float lse[32], int lo[2][32], last[2][32]
+  static constexpr int kClaim = kRow + 4 * 1024;
+  static constexpr int kBytes = kClaim + 16;
+};
+
+// p = hi + mid + low exactly: 8 bits of the mantissa each.
+__device__ __forceinline__ void split24(f32x8 p, bf16x8* hi, bf16x8* mid, bf16x8* low) {
+  typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+  u32x4 part[3];
+#pragma unroll
+  for (int e = 0; e < 8; e += 2) {
+    float x = p[e], y = p[e + 1];
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      part[i][e / 2] = __builtin_amdgcn_perm(__float_as_uint(y), __float_as_uint(x), 0x07060302u);  // the upper halves of x and y
+      x -= __uint_as_float(__float_as_uint(x) & 0xffff0000u);
+      y -= __uint_as_float(__float_as_uint(y) & 0xffff0000u);
+    }
+  }
+  *hi = __builtin_bit_cast(bf16x8, part[0]);
+  *mid = __builtin_bit_cast(bf16x8, part[1]);
+  *low = __builtin_bit_cast(bf16x8, part[2]);
+}
+
+// fp32 partials of a pass: less than 4 GiB of them (kFineMaxScratch holds the lists, too), so that 32-bit offsets reach all.
+struct FlashPartials {
+  float* o;
+  float* lse;
+  uint32_t records;
+};
+constexpr uint32_t kNoRecord = 0xffff0000u;
+
+template <int D>
+struct FineTile {
+  static constexpr int NDT = D / 32, NKK = D / 16;
+  bf16x8 qf[NKK];
+  f32x16 o[NDT], s;
+  float m, l;  // m in log2 units of the scaled logit; l of the lane's half of the kv rows
+  int kbase, vbase;
+  float sc;
+
+  __device__ __forceinline__ void setup(float scale) {
+    sc = scale;
+    const int lane = threadIdx.x & 63, qc = lane & 31, hf = lane >> 5;
+    const int krow = perm_row(qc);
+    kbase = 2 * (krow * D + ((hf ^ k_swizzle<D>(krow)) << 3));
+    const int vrow = (lane & 15) >> 2;
+    vbase = 2 * ((8 * hf + vrow) * D + (((2 * ((lane >> 4) & 1) + ((lane & 3) >> 1)) ^ v_swizzle<D>(vrow)) << 3) + 4 * (lane & 1));
+  }
+  __device__ __forceinline__ void clear() {
+    m = -INFINITY;
+    l = 0.f;
+#pragma unroll
+    for (int dt = 0; dt < NDT; ++dt)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) o[dt][r] = 0.f;
+  }
+  __device__ __forceinline__ void load_q(const bf16_t* Q, const int* row_q) {
+    const int ln = lane_anew();
+    const bf16_t* const qp = Q + (uint32_t)row_q[ln & 31] + (ln >> 5) * 8;
+#pragma unroll
+    for (int kk = 0; kk < NKK; ++kk) qf[kk] = *reinterpret_cast<const bf16x8*>(qp + kk * 16);
+  }
+  __device__ __forceinline__ void qk(const bf16_t* kt) {
+    const uint32_t at = lds_address(kt) + kbase;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) s[r] = 0.f;
+#pragma unroll
+    for (int kk = 0; kk < NKK; ++kk) {
+      const bf16x8 ka = *reinterpret_cast<const __attribute__((address_space(3))) bf16x8*>(at ^ (kk << 5));
+      s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka, qf[kk], s, 0, 0, 0);
+    }
+  }
+  // What follows the scores of the 32 kv rows from t0 on.  fresh: the tile's first; masked: not all rows of the wavefront attend
+  // them all.
+  __device__ __forceinline__ void attend(int t0, bool fresh, bool masked, const int* row_range, const bf16_t* vt) {
+    __builtin_amdgcn_s_setprio(3);
+    if (masked) {
+      const int ln = lane_anew();
+      const int lo = row_range[ln & 31], last = row_range[64 + (ln & 31)];
+      const uint32_t width = last >= lo ? (uint32_t)(last - lo) : 0u;
+      const uint32_t u = last >= lo ? (uint32_t)(t0 + 8 * (ln >> 5) - lo) : 0x80000000u;
+#pragma unroll
+      for (int e = 0; e < 16; ++e) s[e] = u + (uint32_t)(16 * (e >> 3) + (e & 7)) <= width ? s[e] : -INFINITY;
+    }
+    float mx = -INFINITY;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[r]);
+    mx = pair_max(mx) * sc;
+    // Lazy rescale, decided per column: a column's running maximum only moves when that column grew by more than 2^8; until
+    // then its exponentials are taken against the old maximum (p <= 256).  The branch is per wavefront, the arithmetic of a
+    // column does not depend on the columns it shares the wavefront with.
+    const bool grow = mx > m + 8.f || (m == -INFINITY && mx > -INFINITY);
+    if (__builtin_amdgcn_ballot_w64(grow) != 0ull) {
+      const float alpha = grow ? fast_exp2(m - mx) : 1.f;  // m = -inf: 0, and l and o are still 0
+      m = grow ? mx : m;
+      if (!fresh) {
+        l *= alpha;
+#pragma unroll
+        for (int dt = 0; dt < NDT; ++dt)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) o[dt][r] *= alpha;
+      }
+    }
+    const float nm = m > -INFINITY ? -m : 0.f;  // whole column masked so far: exponentials are 0 anyway
+    const uint32_t at = lds_address(vt) + vbase;
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+      f32x8 p;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) p[e] = fast_exp2(fmaf(s[8 * ks + e], sc, nm));
+#pragma unroll
+      for (int e = 0; e < 8; ++e) l += p[e];
+      bf16x8 hi, mid, low;
+      split24(p, &hi, &mid, &low);
+#pragma unroll
+      for (int dt = 0; dt < NDT; ++dt) {
+        const bf16x8 va = transposed8<D>((at ^ (dt << 6)) + 32 * ks * D);
+        o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, hi, o[dt], 0, 0, 0);
+        o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, mid, o[dt], 0, 0, 0);
+        o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, low, o[dt], 0, 0, 0);
+      }
+    }
+    __builtin_amdgcn_s_setprio(0);
+  }
+  // The normalised output in fp32, 32 columns of o at a time through 4 KB of LDS (swizzled 16-byte pieces), 8 lanes a row.
+  // Written past the caches: the partials are gigabytes, the K/V tiles keep the L2.  D / 8 + 1 stores, whatever rows there
+  // are: those of a row without a record (out = -1) lie out of the buffer's range and are dropped.
+  __device__ __forceinline__ void write_output(float* ost, const int* out, const FlashPartials& to) {
+    const int ln = lane_anew(), qc = ln & 31, hf = ln >> 5, piece = ln & 7;
+    const float lt = pair_sum(l), inv = 1.f / lt;
+    const BufferRsrc ob = buffer_of(to.o, to.records * (D * 4)), lb = buffer_of(to.lse, to.records * 4);
+    constexpr int kNt = 2;
+    {
+      const int at = out[qc];
+      __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint((m + __log2f(lt)) * kLn2), lb, at >= 0 && hf == 0 ? (uint32_t)at * 4u : kNoRecord, 0, 0);
+    }
+    uint32_t to_row[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int at = out[8 * u + (ln >> 3)];
+      to_row[u] = at >= 0 ? (uint32_t)at * (D * 4u) + 16 * piece : kNoRecord;
+    }
+#pragma unroll
+    for (int dt = 0; dt < NDT; ++dt) {
+#pragma unroll
+      for (int g4 = 0; g4 < 4; ++g4) {
+        f32x4 v;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = o[dt][4 * g4 + e] * inv;
+        *reinterpret_cast<f32x4*>(&ost[qc * 32 + (((2 * g4 + hf) ^ (qc & 7)) << 2)]) = v;
+      }
+      __builtin_amdgcn_wave_barrier();
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+        const int row = 8 * u + (ln >> 3);
+        const f32x4 v = *reinterpret_cast<const f32x4*>(&ost[row * 32 + ((piece ^ (row & 7)) << 2)]);
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), ob, to_row[u] + 128 * dt, 0, kNt);
+      }
+      __builtin_amdgcn_wave_barrier();
+    }
+  }
+};
+
+__device__ __forceinline__ void stage_block(bf16_t* dst, BufferRsrc from, uint32_t off) {  // 1 KB, global -> LDS
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(from, SL_LDS_PTR(dst), 16, off, 0, 0, 0);
+}
+
+// Direct global -> LDS loads of a staged K and V tile, K at dst, V behind it; rows from `end` on are zeros.
+template <int D, int TT>
+struct FineStage {
+  static constexpr int kBlocks = TT * D / 2048;  // of 1 KB, per wavefront
+  BufferRsrc kr, vr;
+  uint32_t koff[kBlocks], voff[kBlocks];
+  __device__ __forceinline__ FineStage(int wave, int kvh, int t0, int end) {
+    constexpr int PPR = D / 8, RPB = 64 / PPR;  // 16-byte pieces per row, rows per 1 KB block
+    const ArgsPtr a = (ArgsPtr)__builtin_amdgcn_kernarg_segment_ptr();
+    const int rows = __builtin_amdgcn_readfirstlane(end - t0 < TT ? end - t0 : TT);
+    const int64_t first = uniform64((int64_t)kvh * a->kvsh + t0 * a->kvst);
+    const uint32_t bytes = (uint32_t)(((rows - 1) * a->kvst + D) * sizeof(bf16_t));
+    kr = buffer_of(a->K + first, bytes);
+    vr = buffer_of(a->V + first, bytes);
+    const int ln = lane_anew();
+#pragma unroll
+    for (int i = 0; i < kBlocks; ++i) {
+      const int row = (wave * kBlocks + i) * RPB + ln / PPR, pc = ln % PPR;
+      koff[i] = (uint32_t)((row * a->kvst + (pc ^ k_swizzle<D>(row)) * 8) * sizeof(bf16_t));
+      voff[i] = (uint32_t)((row * a->kvst + (pc ^ v_swizzle<D>(row)) * 8) * sizeof(bf16_t));
+    }
+  }
+  __device__ __forceinline__ void issue(bf16_t* dst, int wave) const {
+#pragma unroll
+    for (int i = 0; i < kBlocks; ++i) {
+      stage_block(dst + (wave * kBlocks + i) * 512, kr, koff[i]);
+      stage_block(dst + TT * D + (wave * kBlocks + i) * 512, vr, voff[i]);
+    }
+  }
+};
+
+// Routed spans of the fp32-weight kernels: tiles shared out and claimed as in span_flash_wide_kernel.  a.clip: spans of a row
+// overlap in one joint softmax, and a row's range starts behind the end of the nearest lower span that it lists.
+template <int D, int TT>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(TT * D > 4096 ? 2 : D == 128 ? 3 : 4, TT * D > 4096 ? 2 : D == 128 ? 3 : 4)))
+void span_fine_kernel(const FlashArgs a) {
+  using Lds = FineLds<D, TT>;
+  extern __shared__ __align__(16) char lds[];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t T = a.tile_off[a.Hq / a.G * a.n];
+  const int NWL = gridDim.x / 8;
+  const int xcd = blockIdx.x % 8, wl = blockIdx.x / 8;
+  const int c_begin = (int)(T * xcd / 8), t_begin = c_begin + wl, t_end = (int)(T * (xcd + 1) / 8);
+  if (t_begin >= t_end) return;
+  bf16_t* const stages = reinterpret_cast<bf16_t*>(lds);  // stage b: K at 2 * b * kStage, V behind it
+  int* const ahead = reinterpret_cast<int*>(lds + Lds::kAhead) + wave * 128;
+  int* const row_out = reinterpret_cast<int*>(lds + Lds::kRow) + wave * 256;
+  int* const row_q = row_out + 64;
+  int* const row_range = row_out + 128;  // int lo[2][32], last[2][32]
+  int* const s_claim = reinterpret_cast<int*>(lds + Lds::kClaim);
+
+  struct Span {
+    int kv, begin, end, live, all_lo;  // all_lo: where the last of the wavefront's rows starts
+  };
+  auto describe = [&](int bucket, int count, const int* items, int turn) {
+    const ArgsPtr p = args_anew();
+    const int ln = lane & 31;
+    Span r;
+    r.kv = bucket / p->n;
+    r.live = wave * 32 < count;
+    const int j = bucket % p->n;
+    r.end = (j + 1) * p->A;
+    r.begin = r.end - p->S > 0 ? r.end - p->S : 0;
+    const int item = items[ln];
+    const int rowid = item >> 5, slot = item & 31;
+    const int hl = (uint32_t)rowid / (uint32_t)p->Lq;
+    const int row = rowid - hl * (int)p->Lq;
+    const int h = r.kv * p->G + hl;
+    row_q[ln] = (int)(h * p->qsh + row * p->qst);
+    row_out[32 * turn + ln] = wave * 32 + ln < count ? (h * (int)p->Lq + row) * (p->topk + 1) + slot : -1;
+    int lo = r.begin;
+    r.all_lo = r.begin;
+    if (p->clip) {
+      const int c = (int)((uint32_t)(p->q_pos0 + row) / (uint32_t)p->A);  // (positions lie below 2^24)
+      const int32_t* irow = p->idx + ((int64_t)h * p->Lq + row) * p->topk;
+      for (int s2 = 0; s2 < p->topk; ++s2) {
+        const int jj = irow[s2];
+        if (jj >= 0 && jj < c && jj < j && (jj + 1) * p->A > lo) lo = (jj + 1) * p->A;
+      }
+      int most = lo;
+#pragma unroll
+      for (int off = 16; off >= 1; off >>= 1) most = max(most, __shfl_xor(most, off, 64));
+      r.all_lo = __builtin_amdgcn_readfirstlane(most);
+    }
+    row_range[32 * turn + ln] = lo;
+    row_range[64 + 32 * turn + ln] = r.end - 1;
+    return r;
+  };
+
+  FineTile<D> tile;
+  tile.setup(a.scale_log2e);
+  int b = 0, turn = 0;
+  Span cur;
+  {
+    const int4 info = a.tile_info[t_begin];
+    cur = describe(info.x, info.z, a.items + (int64_t)t_begin * TG + wave * 32, 0);
+    FineStage<D, TT>(wave, cur.kv, cur.begin, cur.end).issue(stages, wave);
+    tile.load_q(a.Q, row_q);
+    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+  }
+  int claimed = 0;
+  for (bool first = true;; first = false) {
+    if (!first && threadIdx.x == 0) *s_claim = claimed;
+    lds_barrier();
+    const int next = first ? t_begin + NWL : c_begin + 2 * NWL + __builtin_amdgcn_readfirstlane(*s_claim);
+    const bool has_next = next < t_end;
+    Span nxt = cur;
+    tile.clear();
+    const int final = cur.begin + (cur.end - cur.begin - 1) / 32 * 32;  // the span's last 32 kv rows, or fewer
+#pragma unroll 1
+    for (int t0 = cur.begin; t0 < cur.end; t0 += TT) {
+      if (t0 != cur.begin) {
+        __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+        lds_barrier();
+      }
+      const bool last = t0 + TT >= cur.end;
+      if (!last) FineStage<D, TT>(wave, cur.kv, t0 + TT, cur.end).issue(stages + 2 * (b ^ 1) * Lds::kStage, wave);
+      if (has_next && t0 == cur.begin) {
+        const ArgsPtr p = args_anew();
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(buffer_of(p->tile_info + next, 16), SL_LDS_PTR(ahead), 4, (lane & 3) * 4, 0, 0, 0);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(buffer_of(p->items + (int64_t)next * TG + wave * 32, 128), SL_LDS_PTR(ahead + 64), 4,
+                                                 lane * 4, 0, 0, 0);
+      }
+      const bf16_t* const kt = stages + 2 * b * Lds::kStage;
+      const int until = t0 + TT < final ? t0 + TT : final;
+      if (cur.live) {
+#pragma unroll 1
+        for (int at = t0; at < until; at += 32) {
+          tile.qk(kt + (at - t0) * D);
+          tile.attend(at, at == cur.begin, at < cur.all_lo, row_range + 32 * turn, kt + Lds::kStage + (at - t0) * D);
+        }
+      }
+      b ^= 1;
+    }
+    if (has_next) {
+      if (cur.end - cur.begin <= TT) __builtin_amdgcn_s_waitcnt(0x0F70);  // (one stage: they may not be here yet)
+      nxt = describe(__builtin_amdgcn_readfirstlane(ahead[0]), __builtin_amdgcn_readfirstlane(ahead[2]), ahead + 64, turn ^ 1);
+    }
+    // the span's last kv rows: the queries are needed no more once their scores are there
+    const bf16_t* const kt = stages + (2 * (b ^ 1) * Lds::kStage + (final - cur.begin) % TT * D);
+    tile.qk(kt);
+    if (has_next) {
+      tile.load_q(args_anew()->Q, row_q);
+      if (threadIdx.x == 0)
+        claimed = (int)__builtin_amdgcn_atomic_inc32((uint32_t*)&args_anew()->claims[32 * xcd], 0xffffffffu, __ATOMIC_RELAXED, "agent");
+    }
+    tile.attend(final, final == cur.begin, final < cur.all_lo || final + 32 > cur.end, row_range + 32 * turn, kt + Lds::kStage);
+    lds_barrier();
+    if (has_next) FineStage<D, TT>(wave, nxt.kv, nxt.begin, nxt.end).issue(stages + 2 * b * Lds::kStage, wave);
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    // the other stage is dead until the next tile's first barrier
+    const ArgsPtr pa = args_anew();
+    tile.write_output(reinterpret_cast<float*>(stages + 2 * (b ^ 1) * Lds::kStage + wave * 2048), row_out + 32 * turn,
+                      FlashPartials{pa->part_of, pa->part_lse, (uint32_t)(pa->Hq * (int)pa->Lq * (pa->topk + 1))});
+    // What is older than the output's last D / 8 stores: the next tile's queries and its first stage.
+    __builtin_amdgcn_s_waitcnt(D == 128 ? 0x4F70 : 0x0F78);
+    if (!has_next) break;
+    cur = nxt;
+    turn ^= 1;
+  }
+}
+
 // Local window [c*S, i] of the fp32-weight kernels: tiles of 128 columns with the causal mask; writes the window's partial into
 // the row's last slot.
 template <int D, int TT>
-__global__ __launch_bounds__(256, fine_blocks(TT)) void span_flash_local_kernel(const FlashArgs a) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(TT * D > 4096 ? 2 : D == 128 ? 3 : 4, TT * D > 4096 ? 2 : D == 128 ? 3 : 4)))
+void span_fine_window_kernel(const FlashArgs a) {
+  using Lds = FineLds<D, TT>;
   extern __shared__ __align__(16) char lds[];
-  const int qrow = (threadIdx.x >> 6) * 32 + (threadIdx.x & 31);
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  bf16_t* const stages = reinterpret_cast<bf16_t*>(lds);
+  int* const row_out = reinterpret_cast<int*>(lds + Lds::kRow) + wave * 256;
+  int* const row_q = row_out + 64;
+  int* const row_range = row_out + 128;
   const LocalMap lm = local_map(a.Lq, a.A, a.G, TG);
   const LocalTile lt = local_tile(lm, TG, a.Hq / a.G, a.G);
   if (!lt.any) return;
-  const int h = lt.head0 + (qrow >> lm.shift);
-  const int64_t r0 = (int64_t)lt.tile << lm.shift;
-  const int64_t r = r0 + (qrow & (lm.rows - 1));
-  const int64_t rc = r < a.Lq ? r : a.Lq - 1;
-  TileDesc d;
-  d.kv = lt.kv;
-  d.q_off = h * a.qsh + rc * a.qst;
-  d.row_out = r < a.Lq ? ((int64_t)h * a.Lq + r) * (a.topk + 1) + a.topk : -1;
-  d.i_q = a.q_pos0 + rc;
-  d.lo_q = (d.i_q / a.A) * a.A;
-  d.kv_begin = ((a.q_pos0 + r0) / a.A) * a.A;
-  d.kv_end = a.q_pos0 + (r0 + lm.rows < a.Lq ? r0 + lm.rows : a.Lq);
-  flash_tile<D, TT>(a, lds, d);
+  const int r0 = lt.tile << lm.shift;
+  auto window_of = [&](int i) { return (int)((uint32_t)i / (uint32_t)a.A) * a.A; };  // (positions lie below 2^24)
+  auto pos = [&](int r) { return (int)(a.q_pos0 + (r < (int)a.Lq ? r : (int)a.Lq - 1)); };
+  {
+    const int ln = lane & 31, col = wave * 32 + ln;
+    const int h = lt.head0 + (col >> lm.shift);
+    const int r = r0 + (col & (lm.rows - 1));
+    const int rc = r < (int)a.Lq ? r : (int)a.Lq - 1;
+    row_q[ln] = (int)(h * a.qsh + rc * a.qst);
+    row_out[ln] = r < (int)a.Lq ? (h * (int)a.Lq + r) * (a.topk + 1) + a.topk : -1;
+    row_range[ln] = window_of(pos(r));
+    row_range[64 + ln] = pos(r);
+  }
+  // rows of the wavefront: a run of the tile's (all of them where a tile has no more than a wavefront columns)
+  const int f = lm.rows > 32 ? wave * 32 & (lm.rows - 1) : 0, n = lm.rows > 32 ? 32 : lm.rows;
+  const int any_lo = window_of(pos(r0 + f)), all_lo = window_of(pos(r0 + f + n - 1));
+  const int all_last = pos(r0 + f), any_last = r0 + f < (int)a.Lq ? pos(r0 + f + n - 1) : -1;
+  const int begin = window_of(pos(r0)), end = pos(r0 + lm.rows - 1) + 1;
+  FineTile<D> t;
+  t.setup(a.scale_log2e);
+  int b = 0;
+  FineStage<D, TT>(wave, lt.kv, begin, end).issue(stages, wave);
+  t.load_q(a.Q, row_q);
+  t.clear();
+#pragma unroll 1
+  for (int t0 = begin; t0 < end; t0 += TT) {
+    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+    lds_barrier();
+    if (t0 + TT < end) FineStage<D, TT>(wave, lt.kv, t0 + TT, end).issue(stages + 2 * (b ^ 1) * Lds::kStage, wave);
+    const bf16_t* const kt = stages + 2 * b * Lds::kStage;
+    const int until = t0 + TT < any_last + 1 ? t0 + TT : any_last + 1;
+#pragma unroll 1
+    for (int at = t0; at < until; at += 32) {
+      if (at + 31 < any_lo) continue;
+      t.qk(kt + (at - t0) * D);
+      t.attend(at, at == begin, at < all_lo || at + 31 > all_last, row_range, kt + Lds::kStage + (at - t0) * D);
+    }
+    b ^= 1;
+  }
+  lds_barrier();
+  t.write_output(reinterpret_cast<float*>(stages) + wave * 1024, row_out,
+                 FlashPartials{a.part_of, a.part_lse, (uint32_t)(a.Hq * (int)a.Lq * (a.topk + 1))});
 }
 
 // Windows: regular tiles of 128 or 256 columns with the causal / window mask.
@@ -1920,11 +2002,8 @@ sl_status prefill_attention_mfma(const Problem& pb, const void* Q, const void* K
 // 1.641784e-3 at 7 to 10 % less time; with bf16 weights and partials 2.4e-3).
 //
 // Measured (32:4 heads, top-8, D = 128 unless said otherwise; row-stationary -> this form, us):
-//   20011 rows, spans of 142: 16400 -> 1940; at D = 64: 8320 -> 1210; 2500 rows, spans of 50: 791 -> 191;
-//   200 rows behind 60000 tokens, spans of 245: 589 -> 83; 8 rows there: 157 -> 72.
-// 128-row tiles, two workgroups per compute unit, three at D = 64 (one's tile ends beside the other's kv loop): a span of
-// 142 tokens is three kv tiles, and 256-row tiles with one workgroup took 1381 us for the routed part where
-// these take 1288.
+//   20011 rows, spans of 142: 16400 -> 1605; at D = 64: 8320 -> 860; 2500 rows, spans of 50: 791 -> 172;
+//   200 rows behind 60000 tokens, spans of 245: 589 -> 82; 8 rows there: 157 -> 60.
 // Calls without a workspace, or with one too small, take the row-stationary kernels as before.
 namespace {
 
@@ -1968,18 +2047,10 @@ int fine_heads(const Problem& pb) {
   return h;
 }
 
-// D = 64: kv tiles of 32 tokens, three workgroups per compute unit, pay where there are tiles for a second round.  Where two
-// workgroups per compute unit take them all at once, the call lasts as long as one tile's chain of kv steps, and half as
-// many steps of 64 are shorter; so they are over long spans.  500 calls of 1 to 64 heads, 64 -> 32 tokens, time of the call
-// (means): up to 512 tiles, spans of up to 64 1.00, 256 1.03, 512 1.06, longer ones 1.11 (2253 tokens, 24:4 heads, one row
-// 110 -> 133 us); 1024 to 2048 tiles 0.96, 0.97, 0.97, 1.06; more 0.93, 0.94, 0.98, 1.03.
-// The window alone: up to a workgroup per compute unit 1.01 (spans beyond 512 tokens 1.03), from two on 0.98.
-bool short_routed_tiles(const Problem& pb, const DeviceSetup& dev) {
-  return pb.D == 64 && fine_tiles(pb) > 2 * dev.grid && pb.S <= 512;
-}
-bool short_window_tiles(const Problem& pb, const DeviceSetup& dev, unsigned grid) {
-  return pb.D == 64 && grid > (unsigned)dev.grid;
-}
+// Stages of twice the tokens, two workgroups per compute unit: where these take all tiles at once, a call lasts as long as one
+// tile's chain of stages.  D = 128, us: 57 tiles, spans of 838 79 -> 73, 54 of 525 74 -> 71, 117 of 191 56 -> 54, 488 of 867
+// 151 -> 148; 667 of 864 152 -> 166, more up to 13 % slower.  At D = 64 a stage holds 64 tokens as it is, and 128 were never faster.
+bool long_stages(const Problem& pb, const DeviceSetup& dev, double tiles) { return pb.D == 128 && tiles <= 2 * dev.grid; }
 
 template <int D>
 bool fine_setup(DeviceSetup* out) {
@@ -1988,15 +2059,14 @@ bool fine_setup(DeviceSetup* out) {
   int dev = -1;
   if (!device_setup(out) || hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return false;
   std::lock_guard<std::mutex> lock(mu);
-  auto allow = [](auto routed, auto local, int bytes) {
+  auto allow = [](auto routed, auto window, int bytes) {
     return hipFuncSetAttribute(reinterpret_cast<const void*>(routed), hipFuncAttributeMaxDynamicSharedMemorySize, bytes) == hipSuccess &&
-           hipFuncSetAttribute(reinterpret_cast<const void*>(local), hipFuncAttributeMaxDynamicSharedMemorySize, bytes) == hipSuccess;
+           hipFuncSetAttribute(reinterpret_cast<const void*>(window), hipFuncAttributeMaxDynamicSharedMemorySize, bytes) == hipSuccess;
   };
-  if (!done[dev]) {
-    done[dev] = allow(span_flash_routed_kernel<D, TN>, span_flash_local_kernel<D, TN>, FlashLds<D>::kBytes);
-    if constexpr (D == 64)
-      done[dev] = done[dev] && allow(span_flash_routed_kernel<D, 32>, span_flash_local_kernel<D, 32>, FlashLds<D, 32>::kBytes);
-  }
+  constexpr int kShort = 4096 / D, kLong = 64;  // tokens of a stage; D = 64 has one length
+  if (!done[dev])
+    done[dev] = allow(span_fine_kernel<D, kShort>, span_fine_window_kernel<D, kShort>, FineLds<D, kShort>::kBytes) &&
+                allow(span_fine_kernel<D, kLong>, span_fine_window_kernel<D, kLong>, FineLds<D, kLong>::kBytes);
   return done[dev];
 }
 
@@ -2047,23 +2117,15 @@ sl_status fine_pass(const Problem& pb, const DeviceSetup& dev, const bf16_t* Q, 
     return SL_ERR_LAUNCH;
   if (pb.prof_start) (void)hipEventRecord(pb.prof_start, st);
   const unsigned lgrid = local_grid(pb.Lq, pb.A, pb.Hkv, pb.G, TG);
-  auto routed = [&](auto tile) {
-    constexpr int TT = decltype(tile)::value;
-    hipLaunchKernelGGL((span_flash_routed_kernel<D, TT>), dim3(fine_blocks(TT) * dev.grid), dim3(256),
-                       (FlashLds<D, TT>::kBytes), st, a);
+  constexpr int kShort = 4096 / D, kLong = 64;  // tokens of a stage; D = 64 has one length
+  auto launch = [&](void (*kernel)(FlashArgs), unsigned grid, int bytes) {
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), bytes, st, a);
   };
-  auto local = [&](auto tile) {
-    constexpr int TT = decltype(tile)::value;
-    hipLaunchKernelGGL((span_flash_local_kernel<D, TT>), dim3(lgrid), dim3(256),
-                       (FlashLds<D, TT>::kBytes), st, a);
-  };
-  using Short = std::integral_constant<int, D == 64 ? 32 : TN>;
-  using Long = std::integral_constant<int, TN>;
-  if (short_routed_tiles(pb, dev)) routed(Short{});
-  else routed(Long{});
+  if (long_stages(pb, dev, fine_tiles(pb))) launch(span_fine_kernel<D, kLong>, fine_blocks(D, kLong) * dev.grid, FineLds<D, kLong>::kBytes);
+  else launch(span_fine_kernel<D, kShort>, fine_blocks(D, kShort) * dev.grid, FineLds<D, kShort>::kBytes);
   if (pb.prof_stop) (void)hipEventRecord(pb.prof_stop, st);
-  if (short_window_tiles(pb, dev, lgrid)) local(Short{});
-  else local(Long{});
+  if (long_stages(pb, dev, lgrid)) launch(span_fine_window_kernel<D, kLong>, lgrid, FineLds<D, kLong>::kBytes);
+  else launch(span_fine_window_kernel<D, kShort>, lgrid, FineLds<D, kShort>::kBytes);
   const int64_t rows = (int64_t)pb.Hq * pb.Lq;
   constexpr int kRowsPerBlock = 256 / (D / 4);
   const dim3 mgrid((unsigned)((rows + kRowsPerBlock - 1) / kRowsPerBlock));

@@ -1020,3 +1020,20 @@ def test_queries_that_are_not_finite_reach_no_other_row(kind, Hq, Hkv, L, Lq, S,
     assert bool(torch.isnan(got[0][bad]).all())
     for c, g in zip(clean, got):
         assert torch.equal(c[~bad], g[~bad])
+
+
+@pytest.mark.parametrize("Hq,Hkv,L,D,S,A,k,form,q_pos0,Lq", [
+    (8, 2, 4000, 128, 33, 33, 8, "joint", 0, 4000),          # a span is two steps, the second of one token
+    (8, 2, 5000, 128, 31, 31, 8, "gated", 0, 5000),          # one step, and no other
+    (8, 2, 6000, 128, 97, 50, 8, "joint", 0, 6000),          # overlapping spans, a last step of one token
+    (32, 4, 6000, 128, 129, 129, 8, "joint", 5000, 1000),    # many tiles: stages of 32 tokens
+    (8, 8, 4488, 128, 838, 838, 2, "gated", 4412, 76),       # few: of 64
+    (4, 1, 3000, 128, 641, 641, 4, "joint", 2700, 300),
+    (4, 1, 3000, 128, 703, 400, 4, "joint", 2700, 300),
+    (8, 2, 5000, 64, 65, 65, 8, "joint", 0, 5000),
+    (8, 2, 5000, 64, 97, 40, 8, "joint", 0, 5000),
+])
+def test_steps_and_stages_of_any_span_length(Hq, Hkv, L, D, S, A, k, form, q_pos0, Lq):
+    """Spans that end with or one token behind a step of 32 kv rows or a stage, stages of both lengths, on
+    test_any_span_length_on_the_matrix_cores's terms."""
+    test_any_span_length_on_the_matrix_cores(Hq, Hkv, L, D, S, A, k, form, q_pos0, Lq)
