@@ -1013,7 +1013,8 @@ __device__ __forceinline__ LocalTile local_tile(const LocalMap& lm, int columns,
 //   - the next tile's record, queries and first stage are asked for before a tile's output leaves, and its stores are not waited
 //     for: what is older than they are is (vector memory completes in order);
 //   - the split by cutting, not rounding: 11 instructions for two weights instead of 15;
-//   - lse stored through the caches, next to the row's other slots' (past them, 4 bytes at a time, 2500 rows: 98 us).
+//   - lse stored through the caches, next to the row's other slots' (past them, 4 bytes at a time, 2500 rows: 98 us; the bf16
+//     partials' kernel is the other way round: 8192 rows, spans of 64 201 past them, 216 through).
 // Measured and not taken: whole rows of 256 bytes per store instruction (+1 %), records two tiles ahead, fragment reads in a
 // fixed order (+-1 %), a workgroup per tile (+4 %).
 constexpr int fine_blocks(int D, int TT) { return TT * D == 4096 ? (D == 128 ? 3 : 4) : 2; }  // workgroups per compute unit
@@ -1494,7 +1495,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, CB == 1 
     // The merge (topk <= 8): the lane that would store 16 bytes of the window's partial instead loads the same 16 bytes of the
     // row's routed partials (written by the routed kernel, which ran before on the stream), does the log-sum-exp merge and
     // stores the final output.  Every load is issued before the first dependent use; slots that take no part may hold
-    // anything and are discarded by selects, never by arithmetic.
+    // anything and are discarded by selects, never by arithmetic.  Partials are read and outputs written past the caches, which
+    // are left to the queries (read by eight spans' tiles) and the keys and values: 8192 rows, 32:4 heads, top-8, spans of 64
+    // 386 -> 357 us (routed 201 -> 186, this kernel 148 -> 137), 16384 with 128 800 -> 735, 262144 with 512 24.57 -> 24.48 ms.
     const int topk = a.topk, nslot = topk + 1;
 #pragma unroll 1
     for (int ub = 0; ub < kCols; ub += 16) {
@@ -1512,7 +1515,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, CB == 1 
           const bool in = sl < topk;
           js[u][sl] = in ? a.idx[rg * topk + sl] : -1;
           ls[u][sl] = in ? a.part_lse[rg * nslot + sl] : 0.f;
-          ov[u][sl] = in ? load16(a.part_o + (rg * nslot + sl) * HD + piece * 8) : make_uint4(0, 0, 0, 0);
+          ov[u][sl] = in ? load16_stream(a.part_o + (rg * nslot + sl) * HD + piece * 8) : make_uint4(0, 0, 0, 0);
         }
       }
 #pragma unroll
@@ -1551,7 +1554,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, CB == 1 
         res.z = (uint32_t)f32_to_bf16(acc[4] * winv) | ((uint32_t)f32_to_bf16(acc[5] * winv) << 16);
         res.w = (uint32_t)f32_to_bf16(acc[6] * winv) | ((uint32_t)f32_to_bf16(acc[7] * winv) << 16);
         if (outs[u] >= 0) {
-          *reinterpret_cast<uint4*>(a.O + outs[u] * HD + piece * 8) = res;
+          store16_stream(a.O + outs[u] * HD + piece * 8, res);
           if (piece == 0) a.LSE[outs[u]] = M + __logf(wsum);
         }
       }
@@ -1561,14 +1564,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, CB == 1 
 
 // ------------------------------------------------------------------ merge
 // A lane's 16 bytes of a partial: 8 bf16 (P = bf16_t) or 4 fp32 (P = float) columns.
+// Past the caches, as in the window kernel: 20011 rows, top-8, spans of 142 1609 -> 1538 us, of 66 1428 -> 1323, in calls that
+// follow each other.
 template <typename P>
 __device__ __forceinline__ void store_columns(bf16_t* p, const float* v) {
   uint32_t w[Elem<P>::EPL / 2];
 #pragma unroll
   for (int e = 0; e < Elem<P>::EPL / 2; ++e)
     w[e] = (uint32_t)f32_to_bf16(v[2 * e]) | ((uint32_t)f32_to_bf16(v[2 * e + 1]) << 16);
-  if constexpr (Elem<P>::EPL == 8) *reinterpret_cast<uint4*>(p) = make_uint4(w[0], w[1], w[2], w[3]);
-  else *reinterpret_cast<uint2*>(p) = make_uint2(w[0], w[1]);
+  if constexpr (Elem<P>::EPL == 8) store16_stream(p, make_uint4(w[0], w[1], w[2], w[3]));
+  else __builtin_nontemporal_store((uint64_t)w[1] << 32 | w[0], reinterpret_cast<uint64_t*>(p));
 }
 
 // fp32 partials: an output that is not finite marks the call (see rerun_flag).
