@@ -521,7 +521,7 @@ def bench_prefill(cfg, steps, warmup, torch, B, W):
             f_paper = keys * 4 * cfg.D
             paper = {"rows": cfg.L, "window": PW, "topk": PK, "backward_factor": PB, "forward_factor": PF,
                      "ms_per_step": dt_p * 1e3, "value": cfg.L / dt_p, "unit": "tokens/s",
-                     "roofline": {"bound": "mfma", "kernel": "span_flash_anchor_kernel", "kernel_ms": kp,
+                     "roofline": {"bound": "mfma", "kernel": "span_flash_wide_kernel<Spans::kAnchor>", "kernel_ms": kp,
                                   "algorithmic_flops": f_paper, "achieved": f_paper / (kp * 1e-3) / 1e12,
                                   "peak": PEAK_BF16 / 1e12, "unit": "TFLOP/s", "frac": f_paper / (kp * 1e-3) / PEAK_BF16}}
             del an
@@ -535,7 +535,7 @@ def bench_prefill(cfg, steps, warmup, torch, B, W):
     peak, bound = PEAK_BF16 if cfg.dtype == "bf16" else PEAK_FP32, "mfma" if tiles else "alu"
     f_kernel = f_routed if tiles else f_attn
     kernel = ("prefill_attention_rows_kernel" if not tiles else
-              "span_flash_routed_kernel" if cfg.dtype == "bf16" else "span_tiles_f32_kernel")
+              "span_flash_wide_kernel" if cfg.dtype == "bf16" else "span_tiles_f32_kernel")
     tflops_attn = f_kernel / (ka * 1e-3)
     res = {
         "workload": f"{cfg.name} prefill L={cfg.L} Hq={cfg.Hq} Hkv={cfg.Hkv} D={cfg.D} S={cfg.S} topk={cfg.topk}+local",
