@@ -465,13 +465,13 @@ struct WideLds {
 
 struct Range {  // of a tile; the last four: over the rows of a wavefront
   int kv, begin, end;
-  int live;              // the wavefront has a row at all
+  int live;              // rows of the tile from the wavefront's first on: none if not positive
   int any_lo, any_last;  // the first and last token that any of its rows attends
   int all_lo, all_last;  // the range that all of them attend
   // kv rows that no row of the wavefront attends are passed over
   template <bool MASKED, int ROWS>
   __device__ __forceinline__ bool attended(int t0) const {
-    return live != 0 && (!MASKED || (t0 + ROWS - 1 >= any_lo && t0 <= any_last));
+    return live > 0 && (!MASKED || (t0 + ROWS - 1 >= any_lo && t0 <= any_last));
   }
 };
 
@@ -479,12 +479,12 @@ struct Range {  // of a tile; the last four: over the rows of a wavefront
 template <int CB>
 struct WideTile {
   // kv rows at a time: 64 for one block of columns, 32 for two
-  static constexpr int KB = 2 / CB, kRows = 32 * KB, NP = 2 * KB;
+  static constexpr int KB = 2 / CB, kRows = 32 * KB;
   bf16x8 qf[CB][8];
-  f32x16 o[CB][4], s[CB][KB];
+  f32x16 o[CB][4], s[CB][2];
   float m[CB];
   f32x4 l[CB];
-  bf16x8 pb[CB][NP];
+  bf16x8 pb[CB][4];
   int kbase, vbase;
   uint32_t one;
   float sc;
@@ -501,8 +501,12 @@ struct WideTile {
   }
   __device__ __forceinline__ void clear() {
 #pragma unroll
+    for (int cb = 0; cb < CB; ++cb) m[cb] = -INFINITY;
+    clear_sums();
+  }
+  __device__ __forceinline__ void clear_sums() {
+#pragma unroll
     for (int cb = 0; cb < CB; ++cb) {
-      m[cb] = -INFINITY;
       l[cb] = (f32x4){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int dt = 0; dt < 4; ++dt)
@@ -520,18 +524,19 @@ struct WideTile {
       for (int kk = 0; kk < 8; ++kk) qf[cb][kk] = *reinterpret_cast<const bf16x8*>(qp + kk * 16);
     }
   }
+  template <int HALVES = KB>
   __device__ __forceinline__ void qk(const bf16_t* kt) {
     const uint32_t at = lds_address(kt) + anew(kbase);
 #pragma unroll
     for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
-      for (int kb = 0; kb < KB; ++kb)
+      for (int kb = 0; kb < HALVES; ++kb)
 #pragma unroll
         for (int r = 0; r < 16; ++r) s[cb][kb][r] = 0.f;
 #pragma unroll
     for (int kk = 0; kk < 8; ++kk)
 #pragma unroll
-      for (int kb = 0; kb < KB; ++kb) {
+      for (int kb = 0; kb < HALVES; ++kb) {
         const bf16x8 ka = *reinterpret_cast<const __attribute__((address_space(3))) bf16x8*>((at ^ (kk << 5)) + 64 * HD * kb);
 #pragma unroll
         for (int cb = 0; cb < CB; ++cb) s[cb][kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka, qf[cb][kk], s[cb][kb], 0, 0, 0);
@@ -539,16 +544,23 @@ struct WideTile {
     // fragment reads run four MFMAs ahead (0x100 = LDS read, 0x008 = MFMA)
     __builtin_amdgcn_sched_group_barrier(0x100, 4 / CB, 0);
 #pragma unroll
-    for (int i = 0; i < 8 * KB - 4 / CB; ++i) {
+    for (int i = 0; i < 8 * HALVES - 4 / CB; ++i) {
       __builtin_amdgcn_sched_group_barrier(0x008, CB, 0);
       __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
     }
     __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
   }
-  // Weights are taken against a bound of the column's scores (log2 units), which moves to the maximum + 8 when a score
-  // passes it, and is looked at every 32 kv rows, whatever the number of blocks, so that a row's result does not depend on the
-  // form that takes it.  Weights lie in [0, 1]; the clamp that makes sure of it also keeps what is not a number out of the row
+  // Weights are taken against a bound of the column's scores (log2 units), which moves when a score passes it and is looked at
+  // every 32 kv rows.  Weights lie in [0, 1]; the clamp that makes sure of it also keeps what is not a number out of the row
   // sums, whose product mixes columns.  A score that is not a number makes the bound one, and with it the column's output.
+  //
+  // The bound moves to a maximum + 8, so that the weight of that maximum, the heaviest, is a power of two and not rounded.  Where
+  // the first 32 rows of a step of 64 move it, it is the maximum of all 64: with that of the 32 alone, a heavier weight, rounded,
+  // is among the second 32 half the time, and the error of lse against 64 bits was 1.12 times as large at spans of 64 tokens, 1.04
+  // at 128 and 1.02 at 512; 2.2 at spans of 64 with scores twice as steep.  One block of columns has the scores of both halves at
+  // hand.  Two have them for the first step of whole spans, whose sums' registers are free; otherwise (a row's range begins
+  // later, or a score passes its bound, which is rare) the second half's maxima are computed ahead.  The rule is the column's own,
+  // so that a row's result does not depend on the form that takes it.
   __device__ __forceinline__ float highest(int cb, int kb) const {
     float mx = s[cb][kb][0];
 #pragma unroll
@@ -561,11 +573,12 @@ struct WideTile {
     if (CB == 2) any = any || !(mx[CB - 1] <= m[CB - 1]);
     return __builtin_amdgcn_ballot_w64(any) != 0ull;
   }
-  __device__ __forceinline__ void move_bounds(const float (&mx)[CB]) {
+  // Columns whose mx passes their bound: to top + 8.
+  __device__ __forceinline__ void move_bounds(const float (&mx)[CB], const float (&top)[CB]) {
 #pragma unroll
     for (int cb = 0; cb < CB; ++cb) {
       const bool grow = !(mx[cb] <= m[cb]);
-      const float to = grow ? mx[cb] + 8.f : m[cb];
+      const float to = grow ? top[cb] + 8.f : m[cb];
       const float alpha = grow ? fast_exp2(m[cb] - to) : 1.f;
       m[cb] = to;
       l[cb][0] *= alpha;
@@ -618,13 +631,10 @@ struct WideTile {
     }
     __builtin_amdgcn_sched_group_barrier(0x008, 4, 1);
   }
-  // What follows the scores of the kv rows from t0 on: masks, weights, O^T += V^T P^T.  The vector instructions compete for
-  // issue slots with the products of the SIMD's other wavefront; that one needs a slot every 32 cycles, this one most.
-  template <bool MASKED>
-  __device__ __forceinline__ void attend(int t0, const Range& r, const int* row_range, const bf16_t* vt) {
-    __builtin_amdgcn_s_setprio(3);
-    // per-row ranges: only where not all rows attend
-    if (MASKED && (t0 < r.all_lo || t0 + kRows - 1 > r.all_last)) {
+  // per-row ranges: only where not all rows attend
+  template <bool MASKED, int HALVES = KB>
+  __device__ __forceinline__ void mask(int t0, const Range& r, const int* row_range) {
+    if (MASKED && (t0 < r.all_lo || t0 + 32 * HALVES - 1 > r.all_last)) {
       const int ln = lane_anew();
 #pragma unroll
       for (int cb = 0; cb < CB; ++cb) {
@@ -632,33 +642,130 @@ struct WideTile {
         const uint32_t width = last >= lo ? (uint32_t)(last - lo) : 0u;
         const uint32_t u = last >= lo ? (uint32_t)(t0 + 8 * (ln >> 5) - lo) : 0x80000000u;
 #pragma unroll
-        for (int kb = 0; kb < KB; ++kb)
+        for (int kb = 0; kb < HALVES; ++kb)
 #pragma unroll
           for (int e = 0; e < 16; ++e)
             s[cb][kb][e] = u + (uint32_t)(32 * kb + 16 * (e >> 3) + (e & 7)) <= width ? s[cb][kb][e] : -INFINITY;
       }
     }
+  }
+  // Two blocks of columns: the maxima of 32 kv rows, scores and all.
+  template <bool MASKED>
+  __device__ __forceinline__ void maxima(int t0, const Range& r, const int* row_range, const bf16_t* kt, float (&mx)[CB]) {
+    qk(kt);
+    mask<MASKED>(t0, r, row_range);
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb) mx[cb] = highest(cb, 0);
+  }
+  // What follows the scores of the kv rows from t0 on: masks, weights, O^T += V^T P^T.  The vector instructions compete for
+  // issue slots with the products of the SIMD's other wavefront; that one needs a slot every 32 cycles, this one most.
+  template <bool MASKED>
+  __device__ __forceinline__ void attend(int t0, const Range& r, const int* row_range, const bf16_t* vt) {
+    static_assert(CB == 1);
+    __builtin_amdgcn_s_setprio(3);
+    mask<MASKED>(t0, r, row_range);
+    const float first[CB] = {highest(0, 0)}, second[CB] = {highest(0, KB - 1)};
+    const float both[CB] = {__builtin_elementwise_maximum(first[0], second[0])};
+    const bool any = passed(both);  // rare: both halves' weights are there before the first product otherwise
+    if (any && passed(first)) move_bounds(first, both);
+    weights(0);
+    if (!any) weights(KB - 1);
+    __builtin_amdgcn_s_setprio(0);
+    pv<0>(vt);
+    if (any) {
+      if (passed(second)) move_bounds(second, second);
+      weights(KB - 1);
+    }
+    pv<KB - 1>(vt);
+  }
+  // The same for two blocks of columns, 32 kv rows, whose keys lie at kt.  first: of a step's 64; second: then the maxima of the
+  // other 32, if they are known.
+  template <bool MASKED>
+  __device__ __forceinline__ void attend(int t0, const Range& r, const int* row_range, const bf16_t* kt, const bf16_t* vt, bool first,
+                                         bool known, const float (&second)[CB]) {
+    static_assert(CB == 2);
+    __builtin_amdgcn_s_setprio(3);
+    mask<MASKED>(t0, r, row_range);
     float mx[CB];
 #pragma unroll
     for (int cb = 0; cb < CB; ++cb) mx[cb] = highest(cb, 0);
-    if constexpr (KB == 1) {
-      if (passed(mx)) move_bounds(mx);
-      weights(0);
-      __builtin_amdgcn_s_setprio(0);
-      pv<0>(vt);
-    } else {
-      const float second[CB] = {highest(0, KB - 1)}, both[CB] = {__builtin_elementwise_maximum(mx[0], second[0])};
-      const bool any = passed(both);  // rare: both halves' weights are there before the first product otherwise
-      if (any && passed(mx)) move_bounds(mx);
-      weights(0);
-      if (!any) weights(KB - 1);
-      __builtin_amdgcn_s_setprio(0);
-      pv<0>(vt);
-      if (any) {
-        if (passed(second)) move_bounds(second);
-        weights(KB - 1);
+    if (passed(mx)) {
+      float top[CB];
+#pragma unroll
+      for (int cb = 0; cb < CB; ++cb) top[cb] = second[cb];
+      if (first && !known) {
+        maxima<MASKED>(t0 + 32, r, row_range, kt + 32 * HD, top);
+        maxima<MASKED>(t0, r, row_range, kt, mx);
       }
-      pv<KB - 1>(vt);
+#pragma unroll
+      for (int cb = 0; cb < CB; ++cb) top[cb] = __builtin_elementwise_maximum(mx[cb], top[cb]);
+      move_bounds(mx, top);
+    }
+    weights(0);
+    __builtin_amdgcn_s_setprio(0);
+    pv<0>(vt);
+  }
+  // The first 64 kv rows of a whole span, two blocks of columns: there are no sums yet, whose registers hold the second half's
+  // scores.  (Computed ahead here too, the maxima cost 262144 rows with spans of 512 3.5 %.)  `ask` follows the scores.
+  template <typename Ask>
+  __device__ __forceinline__ void begin(const bf16_t* kt, Ask&& ask) {
+    static_assert(CB == 2);
+    qk<2>(kt);
+    ask();
+    __builtin_amdgcn_s_setprio(3);
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb) {
+      const float mx = __builtin_elementwise_maximum(highest(cb, 0), highest(cb, 1));
+      m[cb] = mx <= -INFINITY ? -INFINITY : mx + 8.f;
+    }
+    weights(0);
+    weights(1);
+    __builtin_amdgcn_s_setprio(0);
+    __builtin_amdgcn_sched_barrier(0);
+    clear_sums();
+    pv<0>(kt + WideLds::kStage);
+    pv<1>(kt + WideLds::kStage);
+  }
+  // Two blocks of columns: whether a column without a score yet attends any of the 32 kv rows from t0 on.
+  __device__ __forceinline__ bool begins(int t0, const int* row_range) const {
+    const int ln = lane_anew();
+    bool any = false;
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb) any = any || (m[cb] == -INFINITY && row_range[32 * cb + (ln & 31)] < t0 + 32);
+    return __builtin_amdgcn_ballot_w64(any) != 0ull;
+  }
+  // A step's 64 kv rows, or (last) all but those that end a tile.
+  template <bool MASKED>
+  __device__ __forceinline__ void step(int t0, const Range& r, const int* row_range, const bf16_t* kt, bool last) {
+    const bf16_t* const vt = kt + WideLds::kStage;
+    if constexpr (CB == 1) {
+      if (last || !r.template attended<MASKED, 64>(t0)) return;
+      qk(kt);
+      attend<MASKED>(t0, r, row_range, vt);
+    } else {
+      float second[CB] = {-INFINITY, -INFINITY};
+      const bool ahead = MASKED && t0 <= r.all_lo && begins(t0, row_range);
+      if (ahead && r.template attended<MASKED, 32>(t0 + 32)) maxima<MASKED>(t0 + 32, r, row_range, kt + 32 * HD, second);
+#pragma unroll 1
+      for (int at = 0; at < (last ? 32 : 64); at += 32) {
+        if (!r.template attended<MASKED, 32>(t0 + at)) continue;
+        qk(kt + at * HD);
+        attend<MASKED>(t0 + at, r, row_range, kt + at * HD, vt + at * HD, at == 0, ahead, second);
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb) second[cb] = -INFINITY;
+      }
+    }
+  }
+  // The kv rows that end a tile, kRows of them; `ask` follows their scores.
+  template <bool MASKED, typename Ask>
+  __device__ __forceinline__ void finish(int t0, const Range& r, const int* row_range, const bf16_t* kt, Ask&& ask) {
+    qk(kt);
+    ask();
+    if constexpr (CB == 1) {
+      attend<MASKED>(t0, r, row_range, kt + WideLds::kStage);
+    } else {
+      const float none[CB] = {-INFINITY, -INFINITY};
+      attend<MASKED>(t0, r, row_range, kt, kt + WideLds::kStage, false, false, none);
     }
   }
   // The normalised output of 32 columns to LDS, [32][HD] bf16 with swizzled 16-byte pieces, and their lse.
@@ -778,7 +885,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, CB == 1 
     const int ln = lane_anew() & (kCols - 1);
     Range r = {};
     r.kv = bucket / a->n;
-    r.live = wave * kCols < count;
+    r.live = count - wave * kCols;
     const int j = bucket % a->n;
     r.end = (j + 1) * a->A;
     r.begin = r.end - a->S > 0 ? r.end - a->S : 0;
@@ -844,7 +951,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, CB == 1 
     }
   };
   WideTile<CB> tile;
-  tile.setup(a.scale_log2e);
   auto stage = [&](int kvh, int t0, int b) { WideStage<kMasked, CB == 2>(wave, kvh, t0).issue(ldsK + 2 * b * Lds::kStage, wave); };
   auto load_q = [&] { tile.load_q(args_anew()->Q, row_q); };
 
@@ -861,25 +967,23 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, CB == 1 
     stage(cur.kv, cur.begin, b);
     __builtin_amdgcn_s_waitcnt(0x0F70);
   }
+  int claimed = 0;
   // Tiles are claimed one by one, from a counter of the XCD's (equal shares: 12 % of the time without a tile at the end): a
   // workgroup has its second one from the start, and asks for the one after its next while it ends a tile.
-  int claimed = 0;
   for (bool first = true;; first = false) {
     __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
     if (!first && wave == 0 && lane_anew() == 0) *s_claim = claimed;
+    claimed = 0;
+    tile.setup(args_anew()->scale_log2e);
     lds_barrier();
     const int next = first ? t_begin + NWL : c_begin + 2 * NWL + __builtin_amdgcn_readfirstlane(*s_claim);
     const bool has_next = next < t_end;
     Range nxt = cur;
-    tile.clear();
-#pragma unroll 1
-    for (int t0 = cur.begin; t0 < cur.end; t0 += TN) {
-      if (t0 != cur.begin) {
-        __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
-        lds_barrier();
-      }
+    // what comes before a step's scores: the next step's rows, and word of the next tile
+    auto arrive = [&](int t0) {
       if (t0 + TN < cur.end) stage(cur.kv, t0 + TN, b ^ 1);
-      if (has_next && t0 == cur.begin) {
+      if (!has_next) return;
+      if (t0 == cur.begin) {
         const ArgsPtr a = args_anew();
         const int ln = lane_anew();
         __builtin_amdgcn_raw_ptr_buffer_load_lds(buffer_of(a->tile_info + next, 16), SL_LDS_PTR(ahead), 4, (ln & 3) * 4, 0, 0, 0);
@@ -887,30 +991,45 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, CB == 1 
                                                  SL_LDS_PTR(ahead + 64), 4, ln * 4, 0, 0, 0);
       }
       const bool last = t0 + TN >= cur.end;
-      if (has_next && (t0 == cur.begin + TN || (last && t0 == cur.begin))) {
+      if (t0 == cur.begin + TN || (last && t0 == cur.begin)) {
         if (last) __builtin_amdgcn_s_waitcnt(0x0F70);  // (one step: they are not here yet)
         nxt = describe(__builtin_amdgcn_readfirstlane(ahead[0]), __builtin_amdgcn_readfirstlane(ahead[2]), ahead + 64, turn ^ 1);
       }
-      const bf16_t* const kt = ldsK + 2 * b * Lds::kStage;
-#pragma unroll 1
-      for (int sub = 0; sub < TN; sub += kStep) {
-        if (last && sub == TN - kStep) break;
-        if (!cur.attended<kMasked, kStep>(t0 + sub)) continue;
-        tile.qk(kt + sub * HD);
-        tile.template attend<kMasked>(t0 + sub, cur, row_range + 64 * turn, kt + Lds::kStage + sub * HD);
+    };
+    // the queries are needed no more once the scores of the tile's last kv rows are there
+    auto ask = [&] {
+      if (has_next) load_q();
+    };
+    int t0 = cur.begin;
+    bool asked = false;
+    if constexpr (CB == 2 && !kMasked) {
+      arrive(t0);
+      if (cur.live > 0) {
+        asked = t0 + TN >= cur.end;
+        tile.begin(ldsK + 2 * b * Lds::kStage, [&] { if (asked) ask(); });
+      } else {
+        tile.clear();
       }
       b ^= 1;
+      t0 += TN;
+    } else {
+      tile.clear();
     }
-    // the tile's last kv rows: the queries are needed no more once their scores are there
-    const bf16_t* const kt = ldsK + (2 * (b ^ 1) * Lds::kStage + (TN - kStep) * HD);
-    tile.qk(kt);
-    if (has_next) {
-      load_q();
-      if (wave == 0 && lane_anew() == 0)
-        claimed = (int)__builtin_amdgcn_atomic_inc32((uint32_t*)&args_anew()->claims[32 * xcd], 0xffffffffu, __ATOMIC_RELAXED, "agent");
+#pragma unroll 1
+    for (; t0 < cur.end; t0 += TN) {
+      if (t0 != cur.begin) {
+        __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+        lds_barrier();
+      }
+      arrive(t0);
+      tile.template step<kMasked>(t0, cur, row_range + 64 * turn, ldsK + 2 * b * Lds::kStage, t0 + TN >= cur.end);
+      b ^= 1;
     }
-    tile.template attend<kMasked>(cur.end - kStep, cur, row_range + 64 * turn, kt + Lds::kStage);
+    if (!asked)
+      tile.template finish<kMasked>(cur.end - kStep, cur, row_range + 64 * turn, ldsK + (2 * (b ^ 1) * Lds::kStage + (TN - kStep) * HD), ask);
     lds_barrier();
+    if (has_next && wave == 0 && lane_anew() == 0)
+      claimed = (int)__builtin_amdgcn_atomic_inc32((uint32_t*)&args_anew()->claims[32 * xcd], 0xffffffffu, __ATOMIC_RELAXED, "agent");
     if (has_next) {
       whole_range(nxt, turn ^ 1);
       stage(nxt.kv, nxt.begin, b);
@@ -1422,7 +1541,7 @@ void span_fine_window_kernel(const FlashArgs a) {
 template <bool FUSED, int CB>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, CB == 1 ? 2 : 8))) void span_window_wide_kernel(const FlashArgs a) {
   using Lds = WideLds;
-  constexpr int kCols = 32 * CB, kTile = 4 * kCols, kStep = WideTile<CB>::kRows;
+  constexpr int kCols = 32 * CB, kTile = 4 * kCols;
   extern __shared__ __align__(16) char lds[];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   bf16_t* const ldsK = reinterpret_cast<bf16_t*>(lds);
@@ -1454,7 +1573,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, CB == 1 
   auto pos = [&](int r) { return (int)(a.q_pos0 + (r < (int)a.Lq ? r : (int)a.Lq - 1)); };
   Range cur;
   cur.kv = kvh;
-  cur.live = r0 + f < (int)a.Lq;
+  cur.live = (int)a.Lq - (r0 + f);
   cur.any_lo = window_of(pos(r0 + f));
   cur.all_lo = window_of(pos(r0 + f + n - 1));
   cur.all_last = pos(r0 + f);
@@ -1473,13 +1592,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, CB == 1 
     __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
     lds_barrier();
     if (t0 + TN < cur.end) WideStage<true, CB == 2>(wave, kvh, t0 + TN).issue(ldsK + 2 * (b ^ 1) * Lds::kStage, wave);
-    const bf16_t* const kt = ldsK + 2 * b * Lds::kStage;
-#pragma unroll 1
-    for (int sub = 0; sub < TN; sub += kStep) {
-      if (!cur.attended<true, kStep>(t0 + sub)) continue;
-      t.qk(kt + sub * HD);
-      t.template attend<true>(t0 + sub, cur, row_range, kt + Lds::kStage + sub * HD);
-    }
+    t.template step<true>(t0, cur, row_range, ldsK + 2 * b * Lds::kStage, false);
     b ^= 1;
   }
   lds_barrier();
