@@ -486,14 +486,12 @@ struct WideTile {
   f32x4 l[CB];
   bf16x8 pb[CB][4];
   int kbase, vbase;
-  uint32_t one;
   float sc;
 
   __device__ __forceinline__ void setup(float scale) {
     sc = scale;
     const int lane = lane_anew();
     const int qc = lane & 31, hf = lane >> 5;
-    one = (lane & 3) == 0 && (((lane >> 2) ^ (lane >> 4)) & 1) == 0 ? 0x3f803f80u : 0u;
     const int krow = perm_row(qc);
     kbase = 2 * (krow * HD + ((hf ^ k_swizzle<HD>(krow)) << 3));
     const int vrow = (lane & 15) >> 2;
@@ -608,7 +606,9 @@ struct WideTile {
   template <int B>  // block of 32 kv rows
   __device__ __forceinline__ void pv(const bf16_t* vt) {
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-    const uint32_t x = (uint32_t)anew((int)one);
+    uint64_t with = 0x1010010110100101ull;  // the lanes that hold ones: l % 4 = 0, l / 4 and l / 16 both even or both odd
+    asm volatile("" : "+s"(with));
+    const uint32_t x = __builtin_amdgcn_inverse_ballot_w64(with) ? 0x3f803f80u : 0u;
     const bf16x8 ones = __builtin_bit_cast(bf16x8, (u32x4){x, x, x, x});
 #pragma unroll
     for (int ks = 2 * B; ks < 2 * B + 2; ++ks)  // (while the first fragments are on their way)
@@ -724,6 +724,7 @@ struct WideTile {
     __builtin_amdgcn_sched_barrier(0);
     clear_sums();
     pv<0>(kt + WideLds::kStage);
+    __builtin_amdgcn_sched_barrier(0);
     pv<1>(kt + WideLds::kStage);
   }
   // Two blocks of columns: whether a column without a score yet attends any of the 32 kv rows from t0 on.
@@ -882,7 +883,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, CB == 1 
   // what a tile's record and items say: its kv range, and, per row, where its query and its partial are (to LDS)
   auto describe = [&](int bucket, int count, const int* items, int turn) {
     const ArgsPtr a = args_anew();
-    const int ln = lane_anew() & (kCols - 1);
+    const int lane = lane_anew(), ln = lane & (kCols - 1);  // (anew: what the exchanges below address is not kept)
     Range r = {};
     r.kv = bucket / a->n;
     r.live = count - wave * kCols;
@@ -921,10 +922,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, CB == 1 
       r.all_last = some ? last : INT32_MAX;
 #pragma unroll
       for (int off = 32; off >= 1; off >>= 1) {
-        r.any_lo = min(r.any_lo, __shfl_xor(r.any_lo, off, 64));
-        r.all_lo = max(r.all_lo, __shfl_xor(r.all_lo, off, 64));
-        r.any_last = max(r.any_last, __shfl_xor(r.any_last, off, 64));
-        r.all_last = min(r.all_last, __shfl_xor(r.all_last, off, 64));
+        const int from = (lane ^ off) << 2;
+        r.any_lo = min(r.any_lo, __builtin_amdgcn_ds_bpermute(from, r.any_lo));
+        r.all_lo = max(r.all_lo, __builtin_amdgcn_ds_bpermute(from, r.all_lo));
+        r.any_last = max(r.any_last, __builtin_amdgcn_ds_bpermute(from, r.any_last));
+        r.all_last = min(r.all_last, __builtin_amdgcn_ds_bpermute(from, r.all_last));
       }
       r.any_lo = __builtin_amdgcn_readfirstlane(r.any_lo);
       r.all_lo = __builtin_amdgcn_readfirstlane(r.all_lo);
