@@ -556,9 +556,9 @@ struct WideTile {
   // the first 32 rows of a step of 64 move it, it is the maximum of all 64: with that of the 32 alone, a heavier weight, rounded,
   // is among the second 32 half the time, and the error of lse against 64 bits was 1.12 times as large at spans of 64 tokens, 1.04
   // at 128 and 1.02 at 512; 2.2 at spans of 64 with scores twice as steep.  One block of columns has the scores of both halves at
-  // hand.  Two have them for the first step of whole spans, whose sums' registers are free; otherwise (a row's range begins
-  // later, or a score passes its bound, which is rare) the second half's maxima are computed ahead.  The rule is the column's own,
-  // so that a row's result does not depend on the form that takes it.
+  // hand.  Two have them in a tile's first step, where the sums' registers are free; otherwise (a row's range begins later, or a
+  // score passes its bound, which is rare) the second half's maxima are computed ahead.  The rule is the column's own, so that a
+  // row's result does not depend on the form that takes it.
   __device__ __forceinline__ float highest(int cb, int kb) const {
     float mx = s[cb][kb][0];
 #pragma unroll
@@ -705,14 +705,14 @@ struct WideTile {
     __builtin_amdgcn_s_setprio(0);
     pv<0>(vt);
   }
-  // The first 64 kv rows of a whole span, two blocks of columns: there are no sums yet, whose registers hold the second half's
-  // scores.  (Computed ahead here too, the maxima cost 262144 rows with spans of 512 3.5 %.)  `ask` follows the scores.
-  template <typename Ask>
-  __device__ __forceinline__ void begin(const bf16_t* kt, Ask&& ask) {
-    static_assert(CB == 2);
+  // A tile's first 64 kv rows, two blocks of columns: there are no sums yet, whose registers hold the second half's scores.
+  // (Computed ahead here too, the maxima cost 262144 rows with spans of 512 3.5 %.)  `ask` follows the scores.
+  template <bool MASKED, typename Ask>
+  __device__ __forceinline__ void begin(int t0, const Range& r, const int* row_range, const bf16_t* kt, Ask&& ask) {
     qk<2>(kt);
     ask();
     __builtin_amdgcn_s_setprio(3);
+    mask<MASKED, 2>(t0, r, row_range);
 #pragma unroll
     for (int cb = 0; cb < CB; ++cb) {
       const float mx = __builtin_elementwise_maximum(highest(cb, 0), highest(cb, 1));
@@ -735,38 +735,28 @@ struct WideTile {
     for (int cb = 0; cb < CB; ++cb) any = any || (m[cb] == -INFINITY && row_range[32 * cb + (ln & 31)] < t0 + 32);
     return __builtin_amdgcn_ballot_w64(any) != 0ull;
   }
-  // A step's 64 kv rows, or (last) all but those that end a tile.
-  template <bool MASKED>
-  __device__ __forceinline__ void step(int t0, const Range& r, const int* row_range, const bf16_t* kt, bool last) {
+  // A step's 64 kv rows.  `ask` follows the scores of the last ones.
+  template <bool MASKED, typename Ask>
+  __device__ __forceinline__ void step(int t0, const Range& r, const int* row_range, const bf16_t* kt, Ask&& ask) {
     const bf16_t* const vt = kt + WideLds::kStage;
     if constexpr (CB == 1) {
-      if (last || !r.template attended<MASKED, 64>(t0)) return;
+      if (!r.template attended<MASKED, 64>(t0)) return;
       qk(kt);
+      ask();
       attend<MASKED>(t0, r, row_range, vt);
     } else {
       float second[CB] = {-INFINITY, -INFINITY};
       const bool ahead = MASKED && t0 <= r.all_lo && begins(t0, row_range);
       if (ahead && r.template attended<MASKED, 32>(t0 + 32)) maxima<MASKED>(t0 + 32, r, row_range, kt + 32 * HD, second);
 #pragma unroll 1
-      for (int at = 0; at < (last ? 32 : 64); at += 32) {
+      for (int at = 0; at < 64; at += 32) {
         if (!r.template attended<MASKED, 32>(t0 + at)) continue;
         qk(kt + at * HD);
+        if (at != 0) ask();
         attend<MASKED>(t0 + at, r, row_range, kt + at * HD, vt + at * HD, at == 0, ahead, second);
 #pragma unroll
         for (int cb = 0; cb < CB; ++cb) second[cb] = -INFINITY;
       }
-    }
-  }
-  // The kv rows that end a tile, kRows of them; `ask` follows their scores.
-  template <bool MASKED, typename Ask>
-  __device__ __forceinline__ void finish(int t0, const Range& r, const int* row_range, const bf16_t* kt, Ask&& ask) {
-    qk(kt);
-    ask();
-    if constexpr (CB == 1) {
-      attend<MASKED>(t0, r, row_range, kt + WideLds::kStage);
-    } else {
-      const float none[CB] = {-INFINITY, -INFINITY};
-      attend<MASKED>(t0, r, row_range, kt, kt + WideLds::kStage, false, false, none);
     }
   }
   // The normalised output of 32 columns to LDS, [32][HD] bf16 with swizzled 16-byte pieces, and their lse.
@@ -862,7 +852,7 @@ enum class Spans { kWhole, kClipped, kAnchor };
 template <Spans MODE, int CB>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, CB == 1 ? 2 : 8))) void span_flash_wide_kernel(const FlashArgs a) {
   constexpr bool kMasked = MODE != Spans::kWhole;
-  constexpr int kCols = 32 * CB, kRows = 4 * kCols, kStep = WideTile<CB>::kRows;  // columns of a wavefront, rows of a tile, kv rows at a time
+  constexpr int kCols = 32 * CB, kRows = 4 * kCols;  // columns of a wavefront, rows of a tile
   using Lds = WideLds;
   extern __shared__ __align__(16) char lds[];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -999,36 +989,31 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, CB == 1 
       }
     };
     // the queries are needed no more once the scores of the tile's last kv rows are there
-    auto ask = [&] {
-      if (has_next) load_q();
-    };
     int t0 = cur.begin;
-    bool asked = false;
-    if constexpr (CB == 2 && !kMasked) {
-      arrive(t0);
-      if (cur.live > 0) {
-        asked = t0 + TN >= cur.end;
-        tile.begin(ldsK + 2 * b * Lds::kStage, [&] { if (asked) ask(); });
-      } else {
-        tile.clear();
-      }
+    bool asked = !has_next;
+    auto ask = [&] {
+      if (asked || t0 + TN < cur.end) return;
+      load_q();
+      asked = true;
+    };
+    arrive(t0);
+    tile.clear();
+    if (CB == 2 && cur.attended<kMasked, 32>(t0) && cur.attended<kMasked, 32>(t0 + 32)) {
+      tile.template begin<kMasked>(t0, cur, row_range + 64 * turn, ldsK + 2 * b * Lds::kStage, ask);
       b ^= 1;
       t0 += TN;
-    } else {
-      tile.clear();
     }
 #pragma unroll 1
     for (; t0 < cur.end; t0 += TN) {
       if (t0 != cur.begin) {
         __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
         lds_barrier();
+        arrive(t0);
       }
-      arrive(t0);
-      tile.template step<kMasked>(t0, cur, row_range + 64 * turn, ldsK + 2 * b * Lds::kStage, t0 + TN >= cur.end);
+      tile.template step<kMasked>(t0, cur, row_range + 64 * turn, ldsK + 2 * b * Lds::kStage, ask);
       b ^= 1;
     }
-    if (!asked)
-      tile.template finish<kMasked>(cur.end - kStep, cur, row_range + 64 * turn, ldsK + (2 * (b ^ 1) * Lds::kStage + (TN - kStep) * HD), ask);
+    ask();  // (a wavefront none of whose rows attends the last ones)
     lds_barrier();
     if (has_next && wave == 0 && lane_anew() == 0)
       claimed = (int)__builtin_amdgcn_atomic_inc32((uint32_t*)&args_anew()->claims[32 * xcd], 0xffffffffu, __ATOMIC_RELAXED, "agent");
@@ -1588,13 +1573,23 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, CB == 1 
   int b = 0;
   WideStage<true, CB == 2>(wave, kvh, cur.begin).issue(ldsK, wave);
   t.load_q(a.Q, row_q);
-  t.clear();
-#pragma unroll 1
-  for (int t0 = cur.begin; t0 < cur.end; t0 += TN) {
+  auto arrive = [&](int t0) {
     __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
     lds_barrier();
     if (t0 + TN < cur.end) WideStage<true, CB == 2>(wave, kvh, t0 + TN).issue(ldsK + 2 * (b ^ 1) * Lds::kStage, wave);
-    t.template step<true>(t0, cur, row_range, ldsK + 2 * b * Lds::kStage, false);
+  };
+  int t0 = cur.begin;
+  arrive(t0);
+  t.clear();
+  if (CB == 2 && cur.attended<true, 32>(t0) && cur.attended<true, 32>(t0 + 32)) {
+    t.template begin<true>(t0, cur, row_range, ldsK + 2 * b * Lds::kStage, [] {});
+    b ^= 1;
+    t0 += TN;
+  }
+#pragma unroll 1
+  for (; t0 < cur.end; t0 += TN) {
+    if (t0 != cur.begin) arrive(t0);
+    t.template step<true>(t0, cur, row_range, ldsK + 2 * b * Lds::kStage, [] {});
     b ^= 1;
   }
   lds_barrier();

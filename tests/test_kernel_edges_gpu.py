@@ -1022,6 +1022,25 @@ def test_queries_that_are_not_finite_reach_no_other_row(kind, Hq, Hkv, L, Lq, S,
         assert torch.equal(c[~bad], g[~bad])
 
 
+@pytest.mark.parametrize("Hq,Lq,k,b,run", [(16, 1000, 1, 2, 64), (32, 8000, 3, 20, 128)])   # one block of columns, two
+def test_anchor_wavefronts_pass_over_what_none_of_their_rows_attends(Hq, Lq, k, b, run):
+    """Rows of one end block in runs of two wavefronts, one's span ends 140 or 180 tokens behind the other's: the tile's last kv rows, one of whose V
+    is not a number, are attended by every other run alone."""
+    L, w = 9000, 255
+    t0, t1 = (5140, 5280) if Lq == 1000 else (520, 700)
+    Q, K, V = make(33, Hq, Hq, L, 128, torch.bfloat16, scale=0.5, Lq=Lq)
+    late = torch.arange(Lq, device=DEV) // run % 2 == 1
+    an = torch.full((Hq, Lq, k), -1, dtype=torch.int32, device=DEV)
+    an[:, :, 0] = torch.where(late, t1, t0)
+    sc = torch.zeros((Hq, Lq, k), dtype=torch.float32, device=DEV)
+    spoilt = V.clone()
+    spoilt[:, t1 - 1, 7] = math.nan
+    clean, got = (B.sl_anchor_attention_prefill(Q, K, v, an, sc, w, b, 0, q_pos0=L - Lq) for v in (V, spoilt))
+    torch.cuda.synchronize()
+    assert bool(torch.isnan(got[:, late, 7]).all())
+    assert torch.equal(got[:, ~late], clean[:, ~late])
+
+
 def lse_with_rounded_weights(Q, K, idx, S, A, q0, rows):
     """(lse as bf16-weight tiles have it, lse) in 64 bits, [Hq, rows].  A partial (a span, the window) goes 64 keys at a time;
     its weights are rounded to bf16 against a bound, which the first 64 keys' maximum sets and a maximum moves that exceeds it
