@@ -2128,18 +2128,28 @@ double fine_tiles(const Problem& pb) {
   return fmin(items, (double)pb.Hkv * pb.n) + items / TG;
 }
 
-// Estimated us of the two forms; the call takes the smaller.  Row-stationary: 0.02 ns per row and key, with
-// about 13 keys' worth of latency per slot, and no less than one row's own chain of loads.  This form: nine
-// launches, tiles of 4 us plus 2.6 us per kv tile on 512 workgroups (a bucket's last tile is padded),
-// partials written and read.  Of 22 measured calls (2 to 20000 rows, spans of 4 to 245 tokens) the estimates
-// choose the faster form in 18; the other four stay with the row kernels and lose 5 to 15 us, or half of
-// 415 us (1000 rows behind 60000 tokens in spans of 30, buckets a quarter full).
+// Estimated us of the two forms in calls that follow each other; the call takes the smaller.  Row-stationary: so many ps a row and
+// key, with 22 keys' worth of latency per slot in use and 30 per row, and no less than one row's own chain of loads.  This form:
+// nine launches; routed tiles of 6.3 us and a step cost, on as many workgroups as are resident; windows; partials written and
+// read.  14358 random calls (1 to 20000 rows of 1 to 64 heads behind up to 250000 tokens, spans of 4 to 900, lists of 1 to 32,
+// one in five with overlapping spans, both D, both softmaxes): the estimates choose the slower form in 6.7 %, which costs 1.5 %
+// over all calls, and more than 30 % in 2.2 %; of 5156 others in 7.5 %, 1.7 % and 2.5 %.  (With the figures of the kernels before
+// these, 64 kv rows a step on 512 workgroups: 24.6 %, 13.1 % and 17.3 %, most of them row kernels that take up to 4.7 times as
+// long; never the row kernels: 13.9 % over all.)  What is left are calls of 20 to 150 us, the worst of them long lists of
+// overlapping spans, whose row kernel looks through the list for every slot.
 bool fine_is_faster(const Problem& pb) {
-  const double rows = (double)pb.Hq * pb.Lq, items = rows * pb.topk, keys = (double)pb.topk * pb.S + pb.A / 2;
-  const double d = pb.D / 128.0;
-  const double by_rows = fmax(0.075 * keys, 2e-5 * d * rows * (keys + 13.0 * pb.topk));
-  const double steps = (double)((pb.S + TN - 1) / TN);
-  return 45 + fine_tiles(pb) * (4 + 2.6 * steps) / 512 + (items + rows) * pb.D * 8 / 4.5e6 < by_rows;
+  const double rows = (double)pb.Hq * pb.Lq, window = 0.5 * fmin(pb.A, pb.L), full = (double)pb.topk * pb.A;
+  // slots in use: the row at position i has i / A candidates
+  auto slots_before = [&](double i) { return i < full ? 0.5 * i * i / pb.A : pb.topk * (i - 0.5 * full); };
+  const double slots = (slots_before((double)(pb.q_pos0 + pb.Lq)) - slots_before((double)pb.q_pos0)) / pb.Lq, items = rows * slots;
+  const bool half = pb.D == 64;
+  const double most = fmin(pb.topk, (double)(pb.L / pb.A));
+  const double by_rows = 9 + fmax(0.037 * (most * pb.S + window), (half ? 1.1e-5 : 1.7e-5) * rows * (slots * (pb.S + 22) + window + 30));
+  const double workgroups = half ? 1024 : 768, step = half ? 0.9 : 1.4;
+  const double tiles = fmin(items, (double)pb.Hkv * pb.n) + items / TG;
+  const double routed = (6.3 + step * ((pb.S + 31) / 32)) * fmax(1, tiles / workgroups);
+  const double windows = rows / TG / workgroups * (15 + step * (window / 32 + 1));
+  return 29 + routed + windows + (items + rows) * pb.D * 8 / 7.5e6 < by_rows;
 }
 
 constexpr size_t kFineMaxScratch = (size_t)4 << 30;

@@ -245,6 +245,24 @@ def test_fp32_prefill_takes_the_form_that_measured_faster(Hq, Hkv, D, L, Lq, S, 
     assert (B.workspace_bytes(p, B.OP_ATTENTION_PREFILL) > 0) == (tiles_us < rows_us)
 
 
+@pytest.mark.parametrize("Hq,Hkv,D,S,A,k,Lq,q0,rows_us,tiles_us", [
+    (8, 1, 64, 13, 13, 8, 14112, 304, 595, 157),        # short spans, tiles of 32 kv rows
+    (16, 4, 64, 17, 17, 8, 4125, 46, 348, 95),
+    (32, 4, 64, 26, 26, 2, 3046, 0, 196, 68),
+    (8, 1, 128, 39, 39, 2, 6166, 95775, 251, 114),      # far behind a cache
+    (4, 1, 64, 46, 46, 4, 11452, 106377, 231, 102),
+    (32, 4, 64, 8, 4, 2, 5606, 1007, 352, 142),         # overlapping spans
+    (2, 2, 128, 96, 96, 32, 295, 33, 19, 53),           # lists that have three spans at most
+    (4, 4, 64, 261, 261, 8, 565, 0, 20, 46),
+    (8, 8, 128, 102, 102, 8, 219, 0, 16, 39),
+    (4, 1, 128, 229, 114, 4, 254, 0, 15, 45),
+])
+def test_bf16_prefill_takes_the_form_that_measured_faster(Hq, Hkv, D, S, A, k, Lq, q0, rows_us, tiles_us):
+    """Spans that the bf16-weight tiles do not take: calls whose two forms differ by a factor of two and more."""
+    p = good(L=q0 + Lq, Lq=Lq, q_pos0=q0, Hq=Hq, Hkv=Hkv, D=D, S=S, topk=k, span_stride=0 if A == S else A, dtype=B.SL_BF16)
+    assert (B.workspace_bytes(p, B.OP_ATTENTION_PREFILL) > 0) == (tiles_us < rows_us)
+
+
 @pytest.mark.parametrize("D,S,chunks", [(64, 256, 1), (64, 300, 2), (64, 137, 1), (128, 300, 3), (128, 256, 1)])
 def test_batched_chunks_are_no_shorter_than_what_a_workgroup_loads_at_once(D, S, chunks):
     """bf16, D = 64: 256 tokens, also where spans fill longer chunks badly (D = 128: 128)."""
