@@ -138,15 +138,48 @@ def test_any_span_length_on_the_matrix_cores(Hq, Hkv, L, D, S, A, k, form, q_pos
 
 
 @pytest.mark.parametrize("Hq,Hkv,L,D,S,A,k,form,q_pos0,Lq", [
-    (12, 2, 15272, 64, 1920, 960, 12, "gated", 15152, 120),    # few tiles: kv tiles of 64, routed and window
+    (12, 2, 15272, 64, 1920, 960, 12, "gated", 15152, 120),
     (4, 1, 3000, 64, 1441, 1441, 4, "joint", 2700, 300),
     (8, 2, 6000, 64, 129, 129, 8, "joint", 5700, 300),
-    (64, 8, 8000, 64, 100, 100, 8, "joint", 7700, 300),        # of 32 for the routed part, the window alone 64
-    (32, 4, 9000, 64, 600, 600, 8, "gated", 6000, 3000),       # long spans: 64 for the routed part, the window alone 32
-    (8, 2, 8000, 64, 81, 81, 8, "joint", 3900, 4100),          # both 32
+    (64, 8, 8000, 64, 100, 100, 8, "joint", 7700, 300),
+    (32, 4, 9000, 64, 600, 600, 8, "gated", 6000, 3000),
+    (8, 2, 8000, 64, 81, 81, 8, "joint", 3900, 4100),
 ])
-def test_kv_tiles_of_both_lengths_at_64_dimensions(Hq, Hkv, L, D, S, A, k, form, q_pos0, Lq):
-    """Each choice of kv tiles for spans and windows, with remainders, on test_any_span_length_on_the_matrix_cores's terms."""
+def test_long_and_short_spans_at_64_dimensions(Hq, Hkv, L, D, S, A, k, form, q_pos0, Lq):
+    """Few tiles and many, one stage a span and thirty, with remainders, on test_any_span_length_on_the_matrix_cores's terms."""
+    test_any_span_length_on_the_matrix_cores(Hq, Hkv, L, D, S, A, k, form, q_pos0, Lq)
+
+
+def local_heads(G):
+    return min(G & -G, 8)
+
+
+def long_stages(Hq, Hkv, L, A, k, Lq):
+    """Whether the routed and the window kernel of any span length (D = 128) stage 64 tokens, and not 32, at a time: where as many
+    workgroups as 256 compute units hold of that form take all tiles at once."""
+    n, G, items = -(-L // A), Hq // Hkv, Hq * Lq * k
+    routed = min(items, Hkv * n) + items / 128
+    rows = 128 // local_heads(G)
+    tiles = -(-Lq // rows)
+    run = max(1, min(A // rows, -(-tiles // 8)))
+    chunks = -(-tiles // run)
+    most = max((chunks - x + 7) // 8 * run - (chunks * run - tiles if (chunks - 1) % 8 == x else 0) for x in range(8))
+    return routed <= 512, 8 * Hkv * most * (G // local_heads(G)) <= 512
+
+
+@pytest.mark.parametrize("Hq,Hkv,L,D,S,A,k,form,q_pos0,Lq,routed,window", [
+    (8, 2, 5100, 128, 417, 417, 4, "joint", 4900, 200, True, True),
+    (8, 2, 5100, 128, 450, 225, 4, "gated", 4900, 200, True, True),
+    (72, 72, 3391, 128, 838, 838, 4, "joint", 3351, 40, True, False),      # many kv heads: the grid of the windows is padded
+    (72, 72, 3391, 128, 838, 838, 4, "gated", 3351, 40, True, False),
+    (32, 4, 9001, 128, 47, 47, 8, "joint", 8501, 500, False, True),
+    (32, 4, 9001, 128, 141, 47, 8, "joint", 8501, 500, False, True),
+    (16, 4, 17001, 128, 65, 65, 8, "gated", 0, 17001, False, False),
+    (16, 4, 17001, 128, 97, 97, 8, "joint", 0, 17001, False, False),
+])
+def test_stages_of_both_lengths(Hq, Hkv, L, D, S, A, k, form, q_pos0, Lq, routed, window):
+    """Each choice of a stage's length for spans and windows, with remainders, on test_any_span_length_on_the_matrix_cores's terms."""
+    assert long_stages(Hq, Hkv, L, A, k, Lq) == (routed, window)
     test_any_span_length_on_the_matrix_cores(Hq, Hkv, L, D, S, A, k, form, q_pos0, Lq)
 
 
@@ -957,13 +990,38 @@ def test_prefill_search_of_many_candidates_at_both_grid_sizes(Lq, k):
 
 
 TILES = [
-    # kind     Hq  Hkv L      Lq     S or w  A    k
-    ("grid", 8, 1, 9001, 8200, 64, 64, 4),          # joint: routed tiles of 256 rows, windows of 128
-    ("grid", 16, 1, 20011, 16400, 1024, 1024, 2),   # windows of 256 that merge, too
-    ("gated", 8, 1, 9001, 8200, 64, 64, 4),
-    ("grid", 8, 1, 9001, 8200, 128, 64, 4),         # clipped spans
-    ("anchor", 8, 1, 17003, 16391, 1088, 1, 2),     # windows of 256
+    # kind     Hq  Hkv L      Lq     S or w  A    k  blocks of the whole call's routed tiles and windows
+    ("grid", 8, 1, 14001, 13000, 64, 64, 4, 2, 1),
+    ("grid", 16, 1, 28011, 25000, 1024, 1024, 2, 2, 2),    # windows that merge
+    ("gated", 8, 1, 14001, 13000, 64, 64, 4, 2, 1),
+    ("gated", 16, 1, 28011, 25000, 1024, 1024, 2, 2, 2),   # windows that do not
+    ("grid", 8, 1, 14001, 13000, 128, 64, 4, 2, 1),        # clipped spans
+    ("gated", 8, 1, 14001, 13000, 128, 64, 4, 2, 1),       # whole spans that overlap
+    ("anchor", 8, 1, 27003, 25000, 1088, 1, 2, 2, 2),
 ]
+
+
+def end_block(Hq, Hkv, L, Lq, k, reach, tile_rows):
+    """Tokens of an end block of the paper's geometry, in whose buckets rows share tiles."""
+    x, span = Hq // Hkv * Lq * k / L, reach * math.ceil(math.sqrt(L - Lq + Lq // 2)) + 1
+    best, E = math.sqrt(0.5 * tile_rows * span / x), 64
+    while E < 4096 and E * 1.4142 < best:
+        E *= 2
+    while E > 64 and Hkv * (L / E + x * L / tile_rows) < 256:
+        E //= 2
+    return E
+
+
+def column_blocks(kind, Hq, Hkv, L, Lq, S, A, k, reach=4):
+    """Blocks of 32 columns that a wavefront of the routed and of the window kernel takes, and how far the sizes that decide it
+    lie from the lines, as a factor."""
+    items, tokens = Hq * Lq * k, S if kind == "anchor" else A / 2
+    if kind == "anchor":
+        A = end_block(Hq, Hkv, L, Lq, k, reach, 256)
+    buckets = min(items, Hkv * -(-L // A))
+    routed = (items / (500 * buckets), (items / 256 + buckets / 2) / 1024)
+    window = (Hq * Lq / (512 * 256), Hq * Lq * tokens / (2048 * 65536))
+    return [(2 if min(f) >= 1 else 1, min(f) if min(f) >= 1 else 1 / min(f)) for f in (routed, window)]
 
 
 def tile_call(kind, Q, K, V, idx, sc, S, A, q0):
@@ -985,15 +1043,18 @@ def tile_inputs(kind, Hq, Hkv, L, Lq, S, A, k):
     return q0, Q, K, V, idx, torch.where(torch.isfinite(sc), sc, 0.0)
 
 
-@pytest.mark.parametrize("kind,Hq,Hkv,L,Lq,S,A,k", TILES)
-def test_rows_are_alike_in_tiles_of_one_and_two_column_blocks(kind, Hq, Hkv, L, Lq, S, A, k):
+@pytest.mark.parametrize("kind,Hq,Hkv,L,Lq,S,A,k,routed,window", TILES)
+def test_rows_are_alike_in_tiles_of_one_and_two_column_blocks(kind, Hq, Hkv, L, Lq, S, A, k, routed, window):
     """A long call takes tiles of two blocks of columns, its pieces of one: the same arithmetic for every row, whatever tile,
     wavefront (31 to 33, 63 to 65 rows) and kv rows at a time take it."""
+    blocks = column_blocks(kind, Hq, Hkv, L, Lq, S, A, k)
+    assert [b for b, _ in blocks] == [routed, window] and all(far >= 1.5 for b, far in blocks if b == 2)
     q0, Q, K, V, idx, sc = tile_inputs(kind, Hq, Hkv, L, Lq, S, A, k)
     whole = tile_call(kind, Q, K, V, idx, sc, S, A, q0)
     at = 0
     for n in (1, 31, 33, 65, 127, 129, 300, 1025):
         r0 = min(Lq - n, at)
+        assert [b for b, _ in column_blocks(kind, Hq, Hkv, q0 + r0 + n, n, S, A, k)] == [1, 1]
         part = tile_call(kind, Q[:, r0:r0 + n].contiguous(), K[:, :q0 + r0 + n].contiguous(), V[:, :q0 + r0 + n].contiguous(),
                          idx[:, r0:r0 + n].contiguous(), sc[:, r0:r0 + n].contiguous(), S, A, q0 + r0)
         torch.cuda.synchronize()
@@ -1003,7 +1064,7 @@ def test_rows_are_alike_in_tiles_of_one_and_two_column_blocks(kind, Hq, Hkv, L, 
 
 
 @pytest.mark.parametrize("rows", ["few", "many"])
-@pytest.mark.parametrize("kind,Hq,Hkv,L,Lq,S,A,k", TILES)
+@pytest.mark.parametrize("kind,Hq,Hkv,L,Lq,S,A,k", [t[:8] for t in TILES])
 def test_queries_that_are_not_finite_reach_no_other_row(kind, Hq, Hkv, L, Lq, S, A, k, rows):
     """Row sums come from a product that mixes columns of a tile: a row whose scores are not numbers, or infinite, is NaN,
     and every other row is what it was."""
@@ -1028,6 +1089,9 @@ def test_anchor_wavefronts_pass_over_what_none_of_their_rows_attends(Hq, Lq, k, 
     is not a number, are attended by every other run alone."""
     L, w = 9000, 255
     t0, t1 = (5140, 5280) if Lq == 1000 else (520, 700)
+    blocks = column_blocks("anchor", Hq, Hq, L, Lq, w, 1, k, reach=b)[0][0]
+    E = end_block(Hq, Hq, L, Lq, k, b, 128 * blocks)
+    assert blocks == (1 if Lq == 1000 else 2) and t0 // E == t1 // E
     Q, K, V = make(33, Hq, Hq, L, 128, torch.bfloat16, scale=0.5, Lq=Lq)
     late = torch.arange(Lq, device=DEV) // run % 2 == 1
     an = torch.full((Hq, Lq, k), -1, dtype=torch.int32, device=DEV)
@@ -1083,7 +1147,7 @@ def lse_with_rounded_weights(Q, K, idx, S, A, q0, rows):
     return torch.logsumexp(torch.stack(parts), dim=0), torch.logsumexp(torch.stack(exact), dim=0)
 
 
-@pytest.mark.parametrize("S,A,k", [(64, 64, 8), (64, 64, 16), (128, 128, 8), (128, 64, 4), (192, 64, 4)])
+@pytest.mark.parametrize("S,A,k", [(64, 64, 8), (64, 64, 16), (128, 128, 8), (128, 64, 8), (192, 64, 8)])
 @pytest.mark.parametrize("Lq", [8200, 300])          # tiles of two blocks of columns, of one
 @pytest.mark.parametrize("std", [1.0, 1.5])
 def test_heaviest_weight_of_a_span_is_not_rounded(S, A, k, Lq, std):
@@ -1092,6 +1156,7 @@ def test_heaviest_weight_of_a_span_is_not_rounded(S, A, k, Lq, std):
     rows by far less than 3 %; a bound from the first 32 keys alone makes it 12 % larger at spans of 64 and unit variance, 4 % at
     128, and more with steeper scores."""
     L, q0 = 9000, 9000 - Lq
+    assert column_blocks("grid", 8, 1, L, Lq, S, A, k)[0][0] == (2 if Lq > 300 else 1)
     Q, K, V = make(90 + S + A, 8, 1, L, 128, torch.bfloat16, scale=std, Lq=Lq)
     idx = B.sl_span_search_prefill(Q, K, None, A, k, q_pos0=q0)
     _, LSE = B.sl_span_attention_prefill(Q, K, V, idx, S, q_pos0=q0, span_stride=0 if A == S else A)
