@@ -376,7 +376,6 @@ struct FlashArgs {
   const bf16_t* V;
   const int32_t* idx;
   // routed
-  const int* item_off;
   const int* tile_off;
   const int4* tile_info;
   const int* items;
@@ -395,7 +394,7 @@ struct FlashArgs {
   // Buckets are (kv head, end block): block e holds the spans whose last token lies in
   // [e*E, (e+1)*E), E a multiple of 64 (the key-block bucketing of Section 4.3); n = ceil(L / E).
   int64_t window;
-  int ab, af, aroot, E;
+  int ab, af, aroot;
   int clip;  // fp32-weight kernels: overlapping spans in one joint softmax
   float scale_log2e;
   int64_t qsh, qst, kvsh, kvst;
@@ -1129,8 +1128,8 @@ template <int D, int TT>  // TT: tokens of a staged K and V tile
 struct FineLds {
   static constexpr int kStage = TT * D;
   static constexpr int kAhead = 4 * kStage * 2;          // per wavefront: the next tile's record (256 bytes) and items
-  static constexpr int kRow = kAhead + 4 * 512;          // per wavefront: int row[2][32], int q[32], float lse[32], int lo[2][32], last[2][32]
-  static constexpr int kClaim = kRow + 4 * 1024;
+  static constexpr int kRow = kAhead + 4 * 512;          // per wavefront: int row[2][32], int q[32], int lo[2][32], last[2][32]
+  static constexpr int kClaim = kRow + 4 * 896;
   static constexpr int kBytes = kClaim + 16;
 };
 
@@ -1344,9 +1343,9 @@ void span_fine_kernel(const FlashArgs a) {
   if (t_begin >= t_end) return;
   bf16_t* const stages = reinterpret_cast<bf16_t*>(lds);  // stage b: K at 2 * b * kStage, V behind it
   int* const ahead = reinterpret_cast<int*>(lds + Lds::kAhead) + wave * 128;
-  int* const row_out = reinterpret_cast<int*>(lds + Lds::kRow) + wave * 256;
+  int* const row_out = reinterpret_cast<int*>(lds + Lds::kRow) + wave * 224;
   int* const row_q = row_out + 64;
-  int* const row_range = row_out + 128;  // int lo[2][32], last[2][32]
+  int* const row_range = row_out + 96;  // int lo[2][32], last[2][32]
   int* const s_claim = reinterpret_cast<int*>(lds + Lds::kClaim);
 
   struct Span {
@@ -1470,9 +1469,9 @@ void span_fine_window_kernel(const FlashArgs a) {
   extern __shared__ __align__(16) char lds[];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   bf16_t* const stages = reinterpret_cast<bf16_t*>(lds);
-  int* const row_out = reinterpret_cast<int*>(lds + Lds::kRow) + wave * 256;
+  int* const row_out = reinterpret_cast<int*>(lds + Lds::kRow) + wave * 224;
   int* const row_q = row_out + 64;
-  int* const row_range = row_out + 128;
+  int* const row_range = row_out + 96;
   const LocalMap lm = local_map(a.Lq, a.A, a.G, TG);
   const LocalTile lt = local_tile(lm, TG, a.Hq / a.G, a.G);
   if (!lt.any) return;
@@ -1868,11 +1867,10 @@ struct MfmaWs {
 using One = std::integral_constant<int, 1>;
 using Two = std::integral_constant<int, 2>;
 
-// Per-device facts, looked up on the first call with that device current: the grid of the
-// persistent kernel (one resident workgroup of eight wavefronts per compute unit) and whether the
+// Per-device facts, looked up on the first call with that device current: compute units, and whether the
 // flash kernels were granted more dynamic LDS than the 64 KB a kernel gets by default.
 struct DeviceSetup {
-  int grid = 0;     // 0 = not looked up yet
+  int grid = 0;     // compute units, rounded up to a multiple of 8; 0 = not looked up yet
   bool lds_ok = false;
 };
 constexpr int kMaxDevices = 64;
@@ -2031,7 +2029,6 @@ sl_status prefill_attention_mfma(const Problem& pb, const void* Q, const void* K
   a.K = static_cast<const bf16_t*>(K);
   a.V = static_cast<const bf16_t*>(V);
   a.idx = idx;
-  a.item_off = item_off;
   a.tile_off = tile_off;
   a.tile_info = tile_info;
   a.items = items;
@@ -2051,7 +2048,6 @@ sl_status prefill_attention_mfma(const Problem& pb, const void* Q, const void* K
   a.window = 0;
   a.ab = a.af = 0;
   a.aroot = 2;
-  a.E = 0;
   a.clip = 0;
   a.topk = pb.topk;
   a.n = n;
@@ -2211,7 +2207,6 @@ sl_status fine_pass(const Problem& pb, const DeviceSetup& dev, const bf16_t* Q, 
   a.K = K;
   a.V = V;
   a.idx = idx;
-  a.item_off = item_off;
   a.tile_off = tile_off;
   a.tile_info = tile_info;
   a.items = items;
@@ -2404,7 +2399,6 @@ sl_status prefill_anchor_attention_mfma(const Problem& pb, int64_t window, int b
   a.K = static_cast<const bf16_t*>(K);
   a.V = static_cast<const bf16_t*>(V);
   a.idx = anchors;
-  a.item_off = item_off;
   a.tile_off = tile_off;
   a.tile_info = tile_info;
   a.items = items;
@@ -2427,7 +2421,6 @@ sl_status prefill_anchor_attention_mfma(const Problem& pb, int64_t window, int b
   a.ab = b;
   a.af = f;
   a.aroot = root;
-  a.E = q.A;
   a.clip = 0;
   a.scale_log2e = pb.scale * kLog2e;
   a.qsh = pb.qsh;
@@ -2439,7 +2432,7 @@ sl_status prefill_anchor_attention_mfma(const Problem& pb, int64_t window, int b
   wa.plan.unit_h = 1;  // items of a bucket by row, then by head
   wa.plan.unit_u = pb.G;
   if (!launch_buckets(q, wa, anchors, unit_cnt, counts, item_off, tile_off, cursor, tile_info, items, part_lse,
-                      AnchorItems{window, b, f, root, a.E}, nullptr, a.claims, st))
+                      AnchorItems{window, b, f, root, q.A}, nullptr, a.claims, st))
     return SL_ERR_LAUNCH;
   if (pb.prof_start) (void)hipEventRecord(pb.prof_start, st);
   if (blocks == 1)
