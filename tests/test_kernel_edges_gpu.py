@@ -275,6 +275,31 @@ def test_any_span_length_keeps_fp32_weights(D):
     assert off[0] <= 2 * off[1], off
 
 
+@pytest.mark.parametrize("Hq,Hkv,L,D,S,k", [(32, 4, 5000, 128, 142, 8), (32, 4, 3000, 128, 55, 8), (8, 8, 9000, 128, 838, 2), (32, 4, 5000, 64, 90, 8)])
+def test_any_span_length_rounds_lse_to_the_last_place(Hq, Hkv, L, D, S, k):
+    """lse with nine roundings of partials that average out, the logarithm of their sum and the last addition, 0.3 of a unit in
+    the last place each: 0.4 to 0.45 units are seen.  Logarithms of whole sums of weights, which lie at 16 to 64, added half as much."""
+    Q, K, V = make(800 + S, Hq, Hkv, L, D, torch.bfloat16)
+    Lq = min(L, 3000)
+    Q, q0 = Q[:, -Lq:].contiguous(), L - Lq
+    idx = B.sl_span_search_prefill(Q, K, None, S, k, q_pos0=q0)
+    assert takes_matrix_cores(Q, K, S, k, q0)
+    _, LSE = B.sl_span_attention_prefill(Q, K, V, idx, S, q_pos0=q0)
+    torch.cuda.synchronize()
+    rows = torch.arange(0, Lq, max(1, Lq // 300), device=DEV)
+    pos, kv = q0 + rows, torch.arange(Hq, device=DEV)[:, None] // (Hq // Hkv)
+    q, spans = Q[:, rows].double() / math.sqrt(D), idx[:, rows].long()
+    parts = []
+    for s in range(k + 1):
+        start = spans[:, :, s] * S if s < k else (pos // S * S).expand(Hq, -1)
+        at = start[:, :, None] + torch.arange(S, device=DEV)
+        z = torch.stack([(K[kv[h], at[h].clamp(0, L - 1)].double() @ q[h, :, :, None])[..., 0] for h in range(Hq)])
+        parts.append(z.masked_fill((at < 0) | (at > pos[None, :, None]), -math.inf).logsumexp(dim=2))
+    want = torch.stack(parts).logsumexp(dim=0)
+    units = (LSE[:, rows].double() - want) / torch.exp2(want.abs().log2().floor() - 23)
+    assert float(units.pow(2).mean().sqrt()) <= 0.5
+
+
 @pytest.mark.parametrize("form", ["joint", "gated"])
 def test_optional_scratch_is_the_calls_own_and_can_be_missing(form, monkeypatch):
     """A call that can run without scratch leaves the binding's shared workspace alone, and where there is no room
