@@ -434,13 +434,13 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 // tile ends run beside the other's kv loop and their softmax and matrix phases take turns by themselves.
 //
 // What bounds them.  With one block of columns a product needs a fragment of 1 KB from the LDS, the LDS's whole rate; with two
-// blocks half of that, and what is left is the power: the matrix pipes are busy half the time at 1.83 GHz, where a dense bf16
-// product of 8192^3 reaches 1230 TFLOP/s and spans of 2048 tokens 1100 to 1150 here (980 with eight wavefronts of one block in two
-// phase-shifted groups, one workgroup per compute unit).  A tile costs 1.8 us per kv step of 64 tokens and 5 us around them (2.0
+// blocks half of that, and what is left is the power: the matrix pipes are busy half the time at 1.80 GHz, where a dense bf16
+// product of 8192^3 reaches 1170 to 1230 TFLOP/s and spans of 2048 tokens 1200 here (980 with eight wavefronts of one block in two
+// phase-shifted groups, one workgroup per compute unit).  A tile costs 1.65 us per kv step of 64 tokens and 5 us around them (2.0
 // and 6 then): the gathered queries, the output.  Beside the other workgroup's products an instruction takes 8 cycles, an
 // exponential 13, of which a step has what a lane's 64 scores need and little else.
-// Routed part of 262144 rows, top-8, spans of 512 20.5 -> 17.8 ms; of 4000 rows x 16 spans of 512 behind 196000 tokens 700 -> 600
-// us; of 49157 rows on the paper's geometry 2250 -> 2000, its windows 905 -> 780.
+// Routed part of 262144 rows, top-8, spans of 512 21.4 -> 18.4 ms; of 4000 rows x 16 spans of 512 behind 196000 tokens 724 -> 640
+// us; of 49157 rows on the paper's geometry 2450 -> 2250 (eight wavefronts of one block -> this, the same card in turn).
 //
 // Two blocks of columns leave no register for what can be had again: values that only address things are derived anew where
 // they are used.
@@ -987,7 +987,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, CB == 1 
         nxt = describe(__builtin_amdgcn_readfirstlane(ahead[0]), __builtin_amdgcn_readfirstlane(ahead[2]), ahead + 64, turn ^ 1);
       }
     };
-    // the queries are needed no more once the scores of the tile's last kv rows are there
+    // The queries are needed no more once the scores of the tile's last kv rows are there.  (The compiler then waits for the next
+    // rows behind the first products of every step: the long prompt 0.3 % slower than with the last rows behind the loop.)
     int t0 = cur.begin;
     bool asked = !has_next;
     auto ask = [&] {
@@ -1109,10 +1110,11 @@ __device__ __forceinline__ LocalTile local_tile(const LocalMap& lm, int columns,
 // Every softmax weight is split into three bf16 parts, which hold the 24 bits of its mantissa between them, and V is
 // multiplied with all three; the row sum is taken over the unsplit weights, partials are written in fp32.
 //
-// What bounds them: a step of 32 kv rows is 32 products (D = 128) and 40000 tiles take 119 us for it, 1.4 PFLOP/s, the power's
-// rate; a tile's 64 KB of partials take 490 us in all at what scattered 512-byte rows are written at (5.2 TB/s), its gathered
-// queries 190 at least.  20011 rows, top-8, 32:4 heads, spans of 142: routed part 1275 -> 972 us (D = 64: 641 -> 510); 6400 rows
-// with spans of 80 282 -> 191; 2500 with 50 89 -> 75.  What gave it:
+// What bounds them: a step of 32 kv rows is 32 products (D = 128), and 39000 tiles take 103 us for each (spans of 78 to 238 tokens
+// lie on a line; 72 at D = 64), 1.6 PFLOP/s, where a dense product reaches 1.2: a measured cost, not a limit that is known.  A
+// tile's 64 KB of partials take 490 us in all at what scattered 512-byte rows are written at (5.2 TB/s), its gathered queries 190
+// at least.  Routed part, kernels of 64 kv rows at a time -> these, us: 20011 rows, top-8, 32:4 heads, spans of 142 1250 -> 930 (D = 64:
+// 690 -> 555); 6400 rows with spans of 80 306 -> 210; 2500 with 50 92 -> 76.  What gave it:
 //   - steps of 32 instead of 64 kv rows, so that three workgroups share a compute unit (D = 64: four) and a span of 142 is 160
 //     rows' work instead of 192's;
 //   - the next tile's record, queries and first stage are asked for before a tile's output leaves, and its stores are not waited
