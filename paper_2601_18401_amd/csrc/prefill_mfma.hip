@@ -435,7 +435,7 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 //
 // What bounds them.  With one block of columns a product needs a fragment of 1 KB from the LDS, the LDS's whole rate; with two
 // blocks half of that, and what is left is the power: the matrix pipes are busy half the time at 1.80 GHz, where a dense bf16
-// product of 8192^3 reaches 1170 to 1230 TFLOP/s and spans of 2048 tokens 1200 here (980 with eight wavefronts of one block in two
+// product of 8192^3 reaches 1170 to 1230 TFLOP/s and spans of 2048 tokens 1050 to 1200 here, by card (980 with eight wavefronts of one block in two
 // phase-shifted groups, one workgroup per compute unit).  A tile costs 1.65 us per kv step of 64 tokens and 5 us around them (2.0
 // and 6 then): the gathered queries, the output.  Beside the other workgroup's products an instruction takes 8 cycles, an
 // exponential 13, of which a step has what a lane's 64 scores need and little else.
@@ -987,24 +987,22 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, CB == 1 
         nxt = describe(__builtin_amdgcn_readfirstlane(ahead[0]), __builtin_amdgcn_readfirstlane(ahead[2]), ahead + 64, turn ^ 1);
       }
     };
-    // The queries are needed no more once the scores of the tile's last kv rows are there.  (The compiler then waits for the next
-    // rows behind the first products of every step: the long prompt 0.3 % slower than with the last rows behind the loop.)
     int t0 = cur.begin;
+    arrive(t0);
+    tile.clear();
+    // the queries are needed no more once the scores of the tile's last kv rows are there
     bool asked = !has_next;
     auto ask = [&] {
       if (asked || t0 + TN < cur.end) return;
       load_q();
       asked = true;
     };
-    arrive(t0);
-    tile.clear();
     if (CB == 2 && cur.attended<kMasked, 32>(t0) && cur.attended<kMasked, 32>(t0 + 32)) {
       tile.template begin<kMasked>(t0, cur, row_range + 64 * turn, ldsK + 2 * b * Lds::kStage, ask);
       b ^= 1;
       t0 += TN;
     }
-#pragma unroll 1
-    for (; t0 < cur.end; t0 += TN) {
+    auto next_step = [&](auto&& ask) {
       if (t0 != cur.begin) {
         __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
         lds_barrier();
@@ -1012,7 +1010,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, CB == 1 
       }
       tile.template step<kMasked>(t0, cur, row_range + 64 * turn, ldsK + 2 * b * Lds::kStage, ask);
       b ^= 1;
+      t0 += TN;
+    };
+    // Loads of queries inside the loop make the compiler wait for the next kv rows behind the first products of every step: 0.3 %
+    // of a long prompt, but a quarter of a call whose tiles are too few to fill the chip.  The paper's geometry with two blocks of
+    // columns, which only large calls have, has no registers for the last step's own code (44 of 256 would go to memory).
+    constexpr bool kOwnLast = CB == 1 || MODE != Spans::kAnchor;
+#pragma unroll 1
+    while (t0 + (kOwnLast ? TN : 0) < cur.end) {
+      if constexpr (kOwnLast) next_step([] {});
+      else next_step(ask);
     }
+    if (kOwnLast && t0 < cur.end) next_step(ask);
     ask();  // (a wavefront none of whose rows attends the last ones)
     lds_barrier();
     if (has_next && wave == 0 && lane_anew() == 0)
