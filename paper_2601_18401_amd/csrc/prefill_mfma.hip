@@ -726,6 +726,15 @@ struct WideTile {
     __builtin_amdgcn_sched_barrier(0);
     pv<1>(kt + WideLds::kStage);
   }
+  // One block of columns, 64 kv rows from t0 on between the first and the last token that the wavefront's rows attend: whether none
+  // attends any of them.  That takes rows without a token in common, in end blocks longer than a span: those of the paper's geometry
+  // far behind a prompt's start, a few rows to a tile (8 rows of 8 heads behind 178499 tokens, spans of 424: 135 -> 104 us).  Blocks
+  // with enough rows for tiles of two blocks of columns are shorter.
+  __device__ __forceinline__ bool between(int t0, const Range& r, const int* row_range) const {
+    if (r.all_lo <= r.all_last) return false;
+    const int ln = lane_anew() & 31, lo = row_range[ln], last = row_range[128 + ln];
+    return __builtin_amdgcn_ballot_w64(lo <= (last < t0 + 63 ? last : t0 + 63) && last >= t0) == 0ull;
+  }
   // Two blocks of columns: whether a column without a score yet attends any of the 32 kv rows from t0 on.
   __device__ __forceinline__ bool begins(int t0, const int* row_range) const {
     const int ln = lane_anew();
@@ -739,7 +748,7 @@ struct WideTile {
   __device__ __forceinline__ void step(int t0, const Range& r, const int* row_range, const bf16_t* kt, Ask&& ask) {
     const bf16_t* const vt = kt + WideLds::kStage;
     if constexpr (CB == 1) {
-      if (!r.template attended<MASKED, 64>(t0)) return;
+      if (!r.template attended<MASKED, 64>(t0) || (MASKED && between(t0, r, row_range))) return;
       qk(kt);
       ask();
       attend<MASKED>(t0, r, row_range, vt);
@@ -902,8 +911,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, CB == 1 
         lo = (int)sp.lo;
         last = (int)sp.hi - 1;
       }
-      row_range[64 * turn + ln] = lo;
-      row_range[128 + 64 * turn + ln] = last;
+      row_range[64 * turn + ln] = real ? lo : INT32_MAX;  // (padding attends nothing)
+      row_range[128 + 64 * turn + ln] = real ? last : -1;
       const bool some = real && last >= lo;
       r.any_lo = some ? lo : INT32_MAX;
       r.all_lo = some ? lo : 0;

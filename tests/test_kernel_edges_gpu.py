@@ -1130,6 +1130,21 @@ def test_anchor_wavefronts_pass_over_what_none_of_their_rows_attends(Hq, Lq, k, 
     assert torch.equal(got[:, ~late], clean[:, ~late])
 
 
+def test_anchor_wavefronts_pass_over_what_lies_between_their_rows_spans():
+    """Rows of a wavefront whose spans lie apart, with 64 kv rows between them that none attends, one of whose V is not a number."""
+    H, L, Lq, w, t0, t1 = 16, 9000, 1000, 255, 5130, 5370
+    E = end_block(H, H, L, Lq, 1, 1, 128)
+    assert t0 // E == t1 // E and t1 - math.ceil(math.sqrt(L)) > 5248 and column_blocks("anchor", H, H, L, Lq, w, 1, 1, reach=1)[0][0] == 1
+    Q, K, V = make(35, H, H, L, 128, torch.bfloat16, scale=0.5, Lq=Lq)
+    an = torch.where(torch.arange(Lq, device=DEV) % 2 == 1, t1, t0).to(torch.int32).expand(H, Lq)[:, :, None].contiguous()
+    sc = torch.zeros((H, Lq, 1), dtype=torch.float32, device=DEV)
+    spoilt = V.clone()
+    spoilt[:, 5210] = math.nan
+    clean, got = (B.sl_anchor_attention_prefill(Q, K, v, an, sc, w, 1, 0, q_pos0=L - Lq) for v in (V, spoilt))
+    torch.cuda.synchronize()
+    assert torch.equal(got, clean)
+
+
 def lse_with_rounded_weights(Q, K, idx, S, A, q0, rows):
     """(lse as bf16-weight tiles have it, lse) in 64 bits, [Hq, rows].  A partial (a span, the window) goes 64 keys at a time;
     its weights are rounded to bf16 against a bound, which the first 64 keys' maximum sets and a maximum moves that exceeds it
