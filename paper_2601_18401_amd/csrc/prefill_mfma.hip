@@ -1940,14 +1940,23 @@ BucketPlan bucket_plan(const Problem& pb) {
   return p;
 }
 
+// Slots of its list that a row has candidates for, on average: the row at position i has i / A.
+double grid_slots(const Problem& pb) {
+  const double full = (double)pb.topk * pb.A;
+  auto before = [&](double i) { return i < full ? 0.5 * i * i / pb.A : pb.topk * (i - 0.5 * full); };
+  return (before((double)(pb.q_pos0 + pb.Lq)) - before((double)pb.q_pos0)) / pb.Lq;
+}
+
 // Columns of a wavefront of the kernels with bf16 weights, in blocks of 32.  With two a fragment of K or V feeds two products,
 // and the long prompt's routed kernel runs at 1050 to 1150 TFLOP/s where one reaches 970 to 1040; but a tile that is mostly
 // empty, or that alone keeps the call waiting, takes twice the time.  460 random calls (1 to 64 heads, 1 to 150000 rows, grid
 // and paper's geometry, two -> one): from 1024 tiles of 256 rows and 500 items a bucket on 0.86 to 1.10, geometric mean 0.97;
 // below 256 tiles 1.0 to 1.6, mean 1.15.  With these two numbers the calls are within 0.3 % of the faster form each (0.7 % with
-// one block throughout, 0.8 % with two from 512 tiles on, whatever the buckets hold).
-int routed_blocks(const Problem& pb) {
-  const double items = (double)pb.Hq * pb.Lq * pb.topk, buckets = fmin(items, (double)pb.Hkv * pb.n);
+// one block throughout, 0.8 % with two from 512 tiles on, whatever the buckets hold).  `slots` of its list are in use by a row, on the
+// grid those it has candidates for: with lists of 8 taken as full 850 rows of 64:8 heads behind 655, anchors every 1024, took 126 us and not 102.
+int routed_blocks(const Problem& pb, double slots) {
+  const double spans = fmin((double)pb.n, fmax(1, (double)((pb.q_pos0 + pb.Lq) / pb.A)));
+  const double items = (double)pb.Hq * pb.Lq * slots, buckets = fmin(items, pb.Hkv * spans);
   return items >= 500 * buckets && items / 256 + 0.5 * buckets >= 1024 ? 2 : 1;
 }
 // Windows (tokens: how many a row's has on average) by workgroups of 256 rows: where they are not two a compute unit, one block is
@@ -2027,12 +2036,16 @@ bool prefill_attention_mfma_supported(const Problem& pb) {
          (int64_t)pb.Hq * pb.qsh + pb.Lq * pb.qst < ((int64_t)1 << 31);
 }
 
-size_t prefill_attention_mfma_ws_bytes(const Problem& pb) { return carve(pb, 128 * routed_blocks(pb)).total; }
+// Enough for either form, so that it does not depend on where the rows stand.
+size_t prefill_attention_mfma_ws_bytes(const Problem& pb) {
+  const size_t one = carve(pb, 128).total, two = carve(pb, 256).total;
+  return one > two ? one : two;
+}
 
 sl_status prefill_attention_mfma(const Problem& pb, const void* Q, const void* K, const void* V,
                                  const int32_t* idx, void* O, float* LSE, void* ws,
                                  hipStream_t st) {
-  const int blocks = routed_blocks(pb);
+  const int blocks = routed_blocks(pb, grid_slots(pb));
   const MfmaWs w = carve(pb, 128 * blocks);
   DeviceSetup dev;
   if (!device_setup(&dev) || !dev.lds_ok) return SL_ERR_LAUNCH;
@@ -2158,10 +2171,7 @@ double fine_tiles(const Problem& pb) {
 // long; never the row kernels: 13.9 % over all.)  What is left are calls of 20 to 150 us, the worst of them long lists of
 // overlapping spans, whose row kernel looks through the list for every slot.
 bool fine_is_faster(const Problem& pb) {
-  const double rows = (double)pb.Hq * pb.Lq, window = 0.5 * fmin(pb.A, pb.L), full = (double)pb.topk * pb.A;
-  // slots in use: the row at position i has i / A candidates
-  auto slots_before = [&](double i) { return i < full ? 0.5 * i * i / pb.A : pb.topk * (i - 0.5 * full); };
-  const double slots = (slots_before((double)(pb.q_pos0 + pb.Lq)) - slots_before((double)pb.q_pos0)) / pb.Lq, items = rows * slots;
+  const double rows = (double)pb.Hq * pb.Lq, window = 0.5 * fmin(pb.A, pb.L), slots = grid_slots(pb), items = rows * slots;
   const bool half = pb.D == 64;
   const double most = fmin(pb.topk, (double)(pb.L / pb.A));
   const double by_rows = 9 + fmax(0.037 * (most * pb.S + window), (half ? 1.1e-5 : 1.7e-5) * rows * (slots * (pb.S + 22) + window + 30));
@@ -2401,7 +2411,7 @@ sl_status prefill_anchor_attention_mfma(const Problem& pb, int64_t window, int b
   const int64_t mid = pb.q_pos0 + pb.Lq / 2, reach = (int64_t)(b + f) * span_base_length(mid, root);
   const double span = (double)(reach < mid ? reach : mid) + 1;
   Problem q = anchor_view(pb, anchor_block_tokens(pb, span, 256));
-  const int blocks = routed_blocks(q);
+  const int blocks = routed_blocks(q, q.topk);
   if (blocks == 1) q = anchor_view(pb, anchor_block_tokens(pb, span, 128));
   const MfmaWs w = carve(q, 128 * blocks);
   DeviceSetup dev;

@@ -1040,10 +1040,14 @@ def end_block(Hq, Hkv, L, Lq, k, reach, tile_rows):
 def column_blocks(kind, Hq, Hkv, L, Lq, S, A, k, reach=4):
     """Blocks of 32 columns that a wavefront of the routed and of the window kernel takes, and how far the sizes that decide it
     lie from the lines, as a factor."""
-    items, tokens = Hq * Lq * k, S if kind == "anchor" else A / 2
+    tokens, slots = S if kind == "anchor" else A / 2, k
     if kind == "anchor":
         A = end_block(Hq, Hkv, L, Lq, k, reach, 256)
-    buckets = min(items, Hkv * -(-L // A))
+    else:                                        # slots of a row's list that it has candidates for, on average
+        before = [i * i / A / 2 if i < k * A else k * (i - k * A / 2) for i in (L - Lq, L)]
+        slots = (before[1] - before[0]) / Lq
+    items = Hq * Lq * slots
+    buckets = min(items, Hkv * max(1, L // A))
     routed = (items / (500 * buckets), (items / 256 + buckets / 2) / 1024)
     window = (Hq * Lq / (512 * 256), Hq * Lq * tokens / (2048 * 65536))
     return [(2 if min(f) >= 1 else 1, min(f) if min(f) >= 1 else 1 / min(f)) for f in (routed, window)]
