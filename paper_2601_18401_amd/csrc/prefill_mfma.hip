@@ -2161,25 +2161,35 @@ double fine_tiles(const Problem& pb) {
   return fmin(items, (double)pb.Hkv * pb.n) + items / TG;
 }
 
-// Estimated us of the two forms in calls that follow each other; the call takes the smaller.  Row-stationary: so many ps a row and
-// key, with 22 keys' worth of latency per slot in use and 30 per row, and no less than one row's own chain of loads.  This form:
-// nine launches; routed tiles of 6.3 us and a step cost, on as many workgroups as are resident; windows; partials written and
-// read.  14358 random calls (1 to 20000 rows of 1 to 64 heads behind up to 250000 tokens, spans of 4 to 900, lists of 1 to 32,
-// one in five with overlapping spans, both D, both softmaxes): the estimates choose the slower form in 6.7 %, which costs 1.5 %
-// over all calls, and more than 30 % in 2.2 %; of 5156 others in 7.5 %, 1.7 % and 2.5 %.  (With the figures of the kernels before
-// these, 64 kv rows a step on 512 workgroups: 24.6 %, 13.1 % and 17.3 %, most of them row kernels that take up to 4.7 times as
-// long; never the row kernels: 13.9 % over all.)  What is left are calls of 20 to 150 us, the worst of them long lists of
-// overlapping spans, whose row kernel looks through the list for every slot.
+// Estimated us of the two forms in calls that follow each other; the call takes the smaller.
+//
+// Row-stationary, 16 keys (D = 64: 32) at a time: one row's chain of loads, 0.5 us each and up to 2.5 times that where the keys and
+// values that the rows touch leave the L2, and what all rows take, by key and by slot in use; neither hides behind the other entirely.
+// Spans that overlap are looked up in the whole list each, to be clipped, and cover no more than the cache.  (One rule for both
+// softmaxes: the scratch is asked for without saying which.)
+// This form: nine launches, some of them over all buckets; routed tiles of 6.3 us and a step cost, on as many workgroups as are resident;
+// windows; partials written and read.
+//
+// 60667 random calls (1 to 20000 rows of 1 to 64 heads behind up to 200000 tokens, spans of 4 to 900, lists of 1 to 32, one in five
+// with overlapping spans, both D, both softmaxes), 40000 of them fitted: of the others the estimates choose the slower form in 3.2 %,
+// which costs 0.4 % over all calls, and more than 30 % in 0.3 %.  (With one figure a key for the chain, wherever the keys lie, and
+// nothing for looking through lists 6.8, 1.8 and 2.7 %, calls of 50 to 150 us at twice their time among them.)
 bool fine_is_faster(const Problem& pb) {
-  const double rows = (double)pb.Hq * pb.Lq, window = 0.5 * fmin(pb.A, pb.L), slots = grid_slots(pb), items = rows * slots;
-  const bool half = pb.D == 64;
-  const double most = fmin(pb.topk, (double)(pb.L / pb.A));
-  const double by_rows = 9 + fmax(0.037 * (most * pb.S + window), (half ? 1.1e-5 : 1.7e-5) * rows * (slots * (pb.S + 22) + window + 30));
+  const double end = (double)(pb.q_pos0 + pb.Lq), rows = (double)pb.Hq * pb.Lq, window = 0.5 * fmin(pb.A, end);
+  const double slots = grid_slots(pb), items = rows * slots, most = fmin(pb.topk, floor(end / pb.A));
+  const bool half = pb.D == 64, overlap = pb.A < pb.S;
+  const double span = overlap ? fmin(pb.S, fmax(pb.A, end / fmax(1, most))) : pb.S;
+  const double touched = fmin(pb.Hkv * end, items * span + rows * window) * pb.D * 4, far = touched / (touched + 23e6);
+  const double at_once = half ? 32 : 16, look = overlap ? pb.topk : 0;
+  const double chain = 0.5 * (1 + 1.5 * far) * (most * ceil(span / at_once) + ceil(window / at_once)) + most * (0.07 + 0.063 * look);
+  const double key = (half ? 7.9e-6 : 15.5e-6) * (1 + 1.36 * far);
+  const double all = rows * (key * (slots * span + window) + slots * (3.1e-4 + 1.3e-5 * look) + 4.7e-4);
+  const double by_rows = 9 + pow(pow(chain, 1.5) + pow(all, 1.5), 2.0 / 3);
   const double workgroups = half ? 1024 : 768, step = half ? 0.9 : 1.4;
   const double tiles = fmin(items, (double)pb.Hkv * pb.n) + items / TG;
   const double routed = (6.3 + step * ((pb.S + 31) / 32)) * fmax(1, tiles / workgroups);
   const double windows = rows / TG / workgroups * (15 + step * (window / 32 + 1));
-  return 29 + routed + windows + (items + rows) * pb.D * 8 / 7.5e6 < by_rows;
+  return 29 + 0.002 * pb.Hkv * pb.n + routed + windows + (items + rows) * pb.D * 8 / 7.5e6 < by_rows;
 }
 
 constexpr size_t kFineMaxScratch = (size_t)4 << 30;
