@@ -267,6 +267,14 @@ def test_bf16_prefill_takes_the_form_that_measured_faster(Hq, Hkv, D, S, A, k, L
     assert (B.workspace_bytes(p, B.OP_ATTENTION_PREFILL) > 0) == (tiles_us < rows_us)
 
 
+@pytest.mark.parametrize("S,A,k", [(1024, 1024, 8), (2048, 1024, 16), (64, 64, 4)])
+def test_scratch_of_bf16_tiles_does_not_depend_on_where_the_rows_stand(S, A, k):
+    """A size asked for one chunk of a prompt serves the others, which take tiles of other sizes."""
+    sizes = {B.workspace_bytes(good(L=40000, Lq=2000, q_pos0=q0, Hq=64, Hkv=8, D=128, S=S, topk=k, span_stride=0 if A == S else A, dtype=B.SL_BF16),
+                               B.OP_ATTENTION_PREFILL) for q0 in (0, 500, 5000, 38000)}
+    assert len(sizes) == 1 and min(sizes) > 0
+
+
 @pytest.mark.parametrize("D,S,chunks", [(64, 256, 1), (64, 300, 2), (64, 137, 1), (128, 300, 3), (128, 256, 1)])
 def test_batched_chunks_are_no_shorter_than_what_a_workgroup_loads_at_once(D, S, chunks):
     """bf16, D = 64: 256 tokens, also where spans fill longer chunks badly (D = 128: 128)."""
